@@ -43,7 +43,6 @@ struct alignas(8) BlockRow {
     uint32_t first_chunk, n_chunks;
     uint32_t groups_per_chunk;
     uint32_t vec_first;     // first entry of the block in the list of chunks finalize walks chunk-wise; kNoVec when tiled
-    uint32_t first_slab, n_slabs;   // the block's slabs of partial rows (first stage of the per-block sum)
     uint32_t first_prow, n_prows;   // the block's partial rows of the step kernel (one per workgroup: chunk x slice)
     uint64_t rank[4];       // order statistics wanted from v: lo(0.1), lo+1, lo(0.9), lo+1
 };
@@ -370,102 +369,110 @@ __global__ __launch_bounds__(64 * NW) void k_step(
     }
 }
 
-// Per-block sums of the partial rows, in fp64.  Blocks with more than kSlabRows chunks are summed in
-// two stages (slabs of kSlabRows rows by k_slab_reduce, then k_block_reduce); smaller ones directly.
-constexpr uint32_t kSlabRows = 4096;      // partial rows summed by one workgroup of the first stage
+// Per-block sums of the partial rows, in fp64.  A block of more than kDirectRows rows is summed in parts first
+// (k_reduce_parts, one workgroup each); k_reduce adds a block's rows, or the sums of its parts, and folds the
+// step into the block's record.
+// Bound by latency: a chain of descriptor load, row loads and reduction, and for the largest layouts by the
+// rows themselves (64 B for every 512 coordinates of an fp32 layout).  A lane reads 16 bytes of a row, a
+// wavefront 1 KB at a time, a workgroup 32 KB per round; the 64 row slots of a sum meet in two exchange
+// levels and one trip through LDS.  Measured (16 LDS trees of eight barriers and parts of 4,096 rows before):
+// 32,768 coordinates 14.3 -> 3.0 us, 124 M fp32 38.8 -> 9.9 us, 1.3 G fp32 44 -> 29.7 us.  One launch in which the
+// last part of a block to arrive folds it was slower where there are many parts (1.3 G: 106 us): its
+// release writes back the whole L2 of an XCD for every part.
+// kDirectRows: the second launch costs 4.7 us, about what six rounds take.
+constexpr uint32_t kPartRows = 1024, kDirectRows = 3072;
 
-struct alignas(8) Slab { uint32_t first_row, n_rows; };
+struct alignas(8) Part { uint32_t block, part; };
 
-// First stage for large blocks: one workgroup adds a slab of partial rows in fp64.
-__global__ __launch_bounds__(256) void k_slab_reduce(const float* __restrict__ partials, const Slab* __restrict__ slabs,
-                                                     double* __restrict__ slab_sums)
+// Sum of n partial rows; thread s < 16 returns sum s.  Called by a whole workgroup of 256.
+__device__ __forceinline__ double sum_rows(const float* __restrict__ partials, uint32_t n, double (*sh)[kNumSums])
 {
-    const Slab sl = slabs[blockIdx.x];
-    double acc[kNumSums];
+    const uint32_t tid = threadIdx.x, quad = tid & 3u, slot = tid >> 2;
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    for (uint32_t c = slot; c < n; c += 512) {
+        f4 x[8];
 #pragma unroll
-    for (int i = 0; i < (int)kNumSums; ++i) acc[i] = 0.0;
-    for (uint32_t c = threadIdx.x; c < sl.n_rows; c += 256) {
-        const f4* row = reinterpret_cast<const f4*>(partials + (uint64_t)(sl.first_row + c) * kNumSums);
+        for (int q = 0; q < 8; ++q)
+            x[q] = c + 64 * q < n ? *reinterpret_cast<const f4*>(partials + (uint64_t)(c + 64 * q) * kNumSums + 4 * quad) : f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const f4 t = row[q];
-            acc[4 * q + 0] += (double)t.x; acc[4 * q + 1] += (double)t.y;
-            acc[4 * q + 2] += (double)t.z; acc[4 * q + 3] += (double)t.w;
-        }
+        for (int q = 0; q < 8; ++q) { a[0] += (double)x[q].x; a[1] += (double)x[q].y; a[2] += (double)x[q].z; a[3] += (double)x[q].w; }
     }
-    __shared__ double sh[256];
-#pragma unroll 1
-    for (int i = 0; i < (int)kNumSums; ++i) {
-        sh[threadIdx.x] = acc[i];
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) slab_sums[(uint64_t)blockIdx.x * kNumSums + i] = sh[0];
-        __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {                              // the four slots of a row of 16 lanes
+        a[i] += __shfl_xor(a[i], 4);
+        a[i] += __shfl_xor(a[i], 8);
     }
-}
-
-// Second stage, one workgroup per parameter block: the block's slab sums -- or, for a block of at
-// most one slab (n_slabs == 0), its partial rows directly -- are added in fp64, then the step is
-// folded into the running direction stability (Eq. 5, left):
-//   cos_t = <g_t,g_{t-1}> / (|g_t| |g_{t-1}| + eps), NaN -> 0 (App. A.1);
-//   the first cosine initialises rho_bar, later ones enter with weight 1 - beta_rho.
-__global__ __launch_bounds__(256) void k_block_reduce(
-    const float* __restrict__ partials, const double* __restrict__ slab_sums, const BlockRow* __restrict__ rows,
-    double* __restrict__ rec_all, double beta_rho, double eps)
-{
-    const BlockRow br = rows[blockIdx.x];
-    double* rec = rec_all + (uint64_t)blockIdx.x * kRecDoubles;
-    if (br.n_slabs) {
-        if (threadIdx.x < kNumSums) {
-            double a = 0.0;
-            for (uint32_t t = 0; t < br.n_slabs; ++t) a += slab_sums[(uint64_t)(br.first_slab + t) * kNumSums + threadIdx.x];
-            rec[threadIdx.x] = a;
-        }
-    } else {
-        double acc[kNumSums];
+    if ((tid & 12u) == 0) {
 #pragma unroll
-        for (int i = 0; i < (int)kNumSums; ++i) acc[i] = 0.0;
-        for (uint32_t c = threadIdx.x; c < br.n_prows; c += 256) {
-            const f4* row = reinterpret_cast<const f4*>(partials + (uint64_t)(br.first_prow + c) * kNumSums);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const f4 t = row[q];
-                acc[4 * q + 0] += (double)t.x; acc[4 * q + 1] += (double)t.y;
-                acc[4 * q + 2] += (double)t.z; acc[4 * q + 3] += (double)t.w;
-            }
-        }
-        __shared__ double sh[256];
-#pragma unroll 1
-        for (int i = 0; i < (int)kNumSums; ++i) {
-            sh[threadIdx.x] = acc[i];
-            __syncthreads();
-            for (int w = 128; w > 0; w >>= 1) {
-                if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-                __syncthreads();
-            }
-            if (threadIdx.x == 0) rec[i] = sh[0];
-            __syncthreads();
-        }
+        for (int i = 0; i < 4; ++i) sh[tid >> 4][4 * quad + i] = a[i];
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        // The step index lives in the block's record, not in a launch argument: a captured launch of a
-        // steady-state step can be replayed for later steps.
-        const uint32_t step = (uint32_t)rec[R_STEPS] + 1u;
-        const double S_gg = rec[S_GG], S_gp = rec[S_GP];
-        if (step >= 2) {
-            double c = S_gp / (sqrt(S_gg) * sqrt(rec[R_SPP]) + eps);
-            if (c != c) c = 0.0;
-            const double n = rec[R_NCOS];
-            rec[R_RHO] = (n == 0.0) ? c : beta_rho * rec[R_RHO] + (1.0 - beta_rho) * c;
-            rec[R_COS] = c;
-            rec[R_NCOS] = n + 1.0;
+    double total = 0.0;
+    if (tid < kNumSums) {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) total += sh[q][tid];
+    }
+    return total;
+}
+
+// A block's rows are cut into n_prows / kPartRows parts, the last one with the remainder (so no part has fewer than
+// two rows).  The part's sums take the place of its first two rows, which nobody else reads.
+__global__ __launch_bounds__(256) void k_reduce_parts(float* partials, const BlockRow* __restrict__ rows, const Part* __restrict__ parts)
+{
+    __shared__ double sh[16][kNumSums];
+    const Part p = parts[blockIdx.x];
+    const uint32_t first = p.part * kPartRows, left = rows[p.block].n_prows - first;
+    const uint32_t n = left < 2 * kPartRows ? left : kPartRows;
+    float* mine = partials + (uint64_t)(rows[p.block].first_prow + first) * kNumSums;
+    const double total = sum_rows(mine, n, sh);
+    if (threadIdx.x < kNumSums) reinterpret_cast<double*>(mine)[threadIdx.x] = total;
+}
+
+__global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partials, const BlockRow* __restrict__ rows,
+                                                double* __restrict__ rec_all, double beta_rho, double eps)
+{
+    __shared__ double sh[16][kNumSums];
+    const uint32_t tid = threadIdx.x, n_prows = rows[blockIdx.x].n_prows;
+    const float* base = partials + (uint64_t)rows[blockIdx.x].first_prow * kNumSums;
+    double* rec = rec_all + (uint64_t)blockIdx.x * kRecDoubles;
+    double total = 0.0;
+    if (n_prows <= kDirectRows) {
+        total = sum_rows(base, n_prows, sh);
+    } else {
+        const uint32_t s = tid & 15u, g = tid >> 4, n_parts = n_prows / kPartRows;
+        double t = 0.0;
+#pragma unroll 4
+        for (uint32_t q = g; q < n_parts; q += 16)
+            t += reinterpret_cast<const double*>(base + (uint64_t)q * kPartRows * kNumSums)[s];
+        sh[g][s] = t;
+        __syncthreads();
+        if (tid < kNumSums) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) total += sh[q][tid];
         }
-        rec[R_SPP] = S_gg;
-        rec[R_STEPS] = (double)step;
+    }
+    if (tid < kNumSums) rec[tid] = total;
+    // Fold the step into the running direction stability (Eq. 5, left):
+    //   cos_t = <g_t,g_{t-1}> / (|g_t| |g_{t-1}| + eps), NaN -> 0 (App. A.1);
+    //   the first cosine initialises rho_bar, later ones enter with weight 1 - beta_rho.
+    static_assert(S_GG == 0 && S_GP == 1, "lane 0 holds |g|^2 and takes <g, g'> from lane 1");
+    if (tid < 64) {
+        const double S_gp = __shfl_down(total, 1);
+        if (tid == 0) {
+            // The step index lives in the block's record, not in a launch argument: a captured launch of a
+            // steady-state step can be replayed for later steps.
+            const uint32_t step = (uint32_t)rec[R_STEPS] + 1u;
+            if (step >= 2) {
+                double c = S_gp / (sqrt(total) * sqrt(rec[R_SPP]) + eps);
+                if (c != c) c = 0.0;
+                const double cosines = rec[R_NCOS];
+                rec[R_RHO] = (cosines == 0.0) ? c : beta_rho * rec[R_RHO] + (1.0 - beta_rho) * c;
+                rec[R_COS] = c;
+                rec[R_NCOS] = cosines + 1.0;
+            }
+            rec[R_SPP] = total;
+            rec[R_STEPS] = (double)step;
+        }
     }
 }
 
@@ -1240,8 +1247,8 @@ struct Plan {
     std::vector<BlockRow> rows;
     std::vector<MatRow> mats;     // matrix blocks (rows*cols == numel), for Eq. 7
     uint64_t n_tasks = 0, n_quads = 0, n_vec_chunks = 0;
-    std::vector<Slab> slabs;
-    uint64_t off_slabs = 0, off_slabsums = 0;
+    std::vector<Part> parts;      // of blocks of more than kDirectRows partial rows
+    uint64_t off_parts = 0;
     uint64_t off_mats = 0, off_rvec = 0, off_cvec = 0, off_rowpart = 0, off_colpart = 0, off_residpart = 0, off_mu = 0,
              off_psumpart = 0, off_veclist = 0, off_cand = 0, off_candcount = 0, off_scan3 = 0, off_finpart = 0;
     uint64_t padded = 0;          // coordinates in m / v / g_prev
@@ -1313,7 +1320,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     const uint32_t cg = prm->chunk_groups ? prm->chunk_groups : std::max(ds.chunk_groups, round);
     P.slices = prm->chunk_slices ? std::min(prm->chunk_slices, cg) : std::max(1u, cg / round);   // default: one round per slice
     P.slice_groups = (cg + P.slices - 1) / P.slices;
-    P.n_chunks = 0; P.rows.resize(n); P.slabs.clear();
+    P.n_chunks = 0; P.rows.resize(n); P.parts.clear();
     uint64_t state = 0;
     for (uint32_t i = 0; i < n; ++i) {
         const baoc_block& b = blocks[i];
@@ -1328,11 +1335,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
         const uint64_t prows = (uint64_t)r.n_chunks * P.slices, first_prow = P.n_chunks * P.slices;
         if (first_prow + prows > 0x7fffffffull) return BAOC_ERR_UNSUPPORTED;
         r.first_prow = (uint32_t)first_prow; r.n_prows = (uint32_t)prows;
-        r.first_slab = (uint32_t)P.slabs.size();
-        if (r.n_prows > kSlabRows)                                   // small blocks are summed directly
-            for (uint32_t c = 0; c < r.n_prows; c += kSlabRows)
-                P.slabs.push_back(Slab{r.first_prow + c, std::min(kSlabRows, r.n_prows - c)});
-        r.n_slabs = (uint32_t)P.slabs.size() - r.first_slab;
+        for (uint32_t q = 0; prows > kDirectRows && q < prows / kPartRows; ++q) P.parts.push_back(Part{i, q});
         P.n_chunks += r.n_chunks;
         for (int q = 0; q < 2; ++q) {                                // ranks bracketing position q (d-1)
             const double pos = (q == 0 ? 0.1 : 0.9) * (double)(b.numel - 1);
@@ -1399,8 +1402,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     P.off_residpart = o; o = align_up(o + P.n_tasks * 4 * 4, 256);
     P.off_psumpart = o; o = align_up(o + P.n_tasks * 4, 256);
     P.off_veclist = o;  o = align_up(o + P.n_vec_chunks * 4, 256);
-    P.off_slabs = o;    o = align_up(o + P.slabs.size() * sizeof(Slab), 256);
-    P.off_slabsums = o; o = align_up(o + P.slabs.size() * kNumSums * 8, 256);
+    P.off_parts = o;    o = align_up(o + P.parts.size() * sizeof(Part), 256);
     P.off_candcount = o; o = align_up(o + P.n_tasks * 4, 256);
     P.off_scan3 = o;    o = align_up(o + (uint64_t)n * 4, 256);
     P.off_finpart = o;  o = align_up(o + P.mats.size() * kFinSlices * 2 * 8, 256);
@@ -1462,8 +1464,8 @@ static int begin_on(const baoc_block* blocks, uint32_t n_blocks, const baoc_prof
     // (padding included), so only the small tail of the workspace is cleared here.
     hipError_t e = hipMemset(h->ws + P.off_rec, 0, P.off_mats - P.off_rec);
     if (e == hipSuccess) e = hipMemcpy(h->ws + P.off_rows, P.rows.data(), P.rows.size() * sizeof(BlockRow), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !P.slabs.empty())
-        e = hipMemcpy(h->ws + P.off_slabs, P.slabs.data(), P.slabs.size() * sizeof(Slab), hipMemcpyHostToDevice);
+    if (e == hipSuccess && !P.parts.empty())
+        e = hipMemcpy(h->ws + P.off_parts, P.parts.data(), P.parts.size() * sizeof(Part), hipMemcpyHostToDevice);
     if (e == hipSuccess && !P.mats.empty())
         e = hipMemcpy(h->ws + P.off_mats, P.mats.data(), P.mats.size() * sizeof(MatRow), hipMemcpyHostToDevice);
     if (e == hipSuccess) {
@@ -1535,13 +1537,12 @@ extern "C" int baoc_profile_step(baoc_profiler* h, const void* d_grad_flat, uint
         launch_step<BAOC_GRAD_BF16>(first, P.gpw, P.nw, grid, lds, st, static_cast<const uint16_t*>(d_grad_flat), m, v,
                                     reinterpret_cast<uint16_t*>(h->ws + P.off_gp), ch, part, k, P.slices, P.slice_groups);
     h->steps += 1;
-    double* slab_sums = reinterpret_cast<double*>(h->ws + P.off_slabsums);
-    if (!P.slabs.empty())
-        hipLaunchKernelGGL(k_slab_reduce, dim3((uint32_t)P.slabs.size()), dim3(256), 0, st,
-                           part, reinterpret_cast<const Slab*>(h->ws + P.off_slabs), slab_sums);
-    hipLaunchKernelGGL(k_block_reduce, dim3((uint32_t)P.rows.size()), dim3(256), 0, st,
-                       part, slab_sums, reinterpret_cast<const BlockRow*>(h->ws + P.off_rows),
-                       reinterpret_cast<double*>(h->ws + P.off_rec), q.beta_rho, q.eps);
+    const BlockRow* rows = reinterpret_cast<const BlockRow*>(h->ws + P.off_rows);
+    if (!P.parts.empty())
+        hipLaunchKernelGGL(k_reduce_parts, dim3((uint32_t)P.parts.size()), dim3(256), 0, st,
+                           part, rows, reinterpret_cast<const Part*>(h->ws + P.off_parts));
+    hipLaunchKernelGGL(k_reduce, dim3((uint32_t)P.rows.size()), dim3(256), 0, st,
+                       part, rows, reinterpret_cast<double*>(h->ws + P.off_rec), q.beta_rho, q.eps);
     if (hipGetLastError() != hipSuccess) { h->sticky = BAOC_ERR_HIP; return BAOC_ERR_HIP; }
     return BAOC_OK;
 }

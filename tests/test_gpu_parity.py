@@ -511,3 +511,14 @@ def test_error_paths(env):
     p = binding.default_profile_params()
     assert binding.load_library().baoc_profile_begin(arr, 1, C.byref(p), ws.data_ptr(), 1024, C.byref(h)) == binding.ERR_WORKSPACE
     assert binding.load_library().baoc_profile_begin(arr, 1, C.byref(p), ws.data_ptr() + 1, 10 ** 9, C.byref(h)) == binding.ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("rows_per_step", [3071, 3072, 3073, 4096, 4097])
+def test_partial_row_sums_around_the_two_stage_edge(env, rows_per_step):
+    """Blocks of just below and above the number of partial rows that takes a second stage, one of them with a
+    last part of a single row (4097 = 4 x 1024 + 1), next to a block of a single row."""
+    per = 2 * 256                                            # coordinates per partial row with this launch shape
+    n = rows_per_step * per - 3
+    w = W.Workload("parts", [W._vec("a", 7), W._vec("b", n), W._vec("c", 300)], 3, "f32", "cycle", **W.K6)
+    W.layout(w, 1); W.draw_stream_params(w, 3)
+    run_both(env, w, 3, seed=8, chunk_groups=2, groups_per_wave=2, waves_per_workgroup=1)
