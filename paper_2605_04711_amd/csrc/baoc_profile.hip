@@ -153,10 +153,15 @@ template <typename T> __device__ __forceinline__ void st_stream(void* p, T val)
 
 template <int GT> struct GradIO;
 
+// Loads of the caller's buffers (gradients, parameters) assume the alignment of one element only: gfx950 takes global
+// loads at any address, and a 16- or 8-byte load that crosses a cache line is still one request where four
+// element loads are four (step on bf16 blocks packed at odd offsets, 60 M coordinates: 271 -> 224 us a launch).
 template <> struct GradIO<BAOC_GRAD_F32> {
     typedef float elem;
     typedef f4 vec4;                                      // four elements as loaded
+    typedef f4 vec4_any __attribute__((aligned(4)));
     __device__ static __forceinline__ vec4 loadv(const elem* p) { return ld_stream<f4>(p); }
+    __device__ static __forceinline__ vec4 loadv_any(const elem* p) { return ld_stream<vec4_any>(p); }
     __device__ static __forceinline__ void unpack(vec4 t, float g[4]) { g[0] = t.x; g[1] = t.y; g[2] = t.z; g[3] = t.w; }
     __device__ static __forceinline__ void load4(const elem* p, float g[4]) { unpack(loadv(p), g); }
     __device__ static __forceinline__ float load1(const elem* p) { return *p; }
@@ -171,7 +176,9 @@ template <> struct GradIO<BAOC_GRAD_F32> {
 template <> struct GradIO<BAOC_GRAD_BF16> {
     typedef uint16_t elem;
     typedef u2 vec4;
+    typedef u2 vec4_any __attribute__((aligned(2)));
     __device__ static __forceinline__ vec4 loadv(const elem* p) { return ld_stream<u2>(p); }
+    __device__ static __forceinline__ vec4 loadv_any(const elem* p) { return ld_stream<vec4_any>(p); }
     __device__ static __forceinline__ void unpack(vec4 t, float g[4])
     {
         g[0] = __builtin_bit_cast(float, t.x << 16); g[1] = __builtin_bit_cast(float, t.x & 0xffff0000u);
@@ -216,7 +223,6 @@ __global__ __launch_bounds__(64 * NW) void k_step(
     const uint32_t g_begin = slice * slice_groups;
     const uint32_t ngroups = min((ck.count + (kQB - 1)) / kQB, g_begin + slice_groups);
     const typename IO::elem* gsrc = grad + ck.grad_start;
-    const bool vec_ok = (reinterpret_cast<uintptr_t>(gsrc) & IO::kAlignMask) == 0;
 
     float acc[kNumSums];
 #pragma unroll
@@ -235,7 +241,7 @@ __global__ __launch_bounds__(64 * NW) void k_step(
                 const uint32_t e = grp * kQB + lane * 4;
                 const uint64_t si = ck.state_start + e;   // states are padded to whole groups
                 if (!FIRST) { nm[i] = ld_stream<f4>(m_all + si); nv[i] = ld_stream<f4>(v_all + si); np[i] = IO::loadv(gp_all + si); }
-                if (vec_ok && e + 4 <= ck.count) ng[i] = IO::loadv(gsrc + e);
+                if (e + 4 <= ck.count) ng[i] = IO::loadv_any(gsrc + e);
             }
         }
     };
@@ -264,9 +270,9 @@ __global__ __launch_bounds__(64 * NW) void k_step(
                 v[0] = cv[i].x; v[1] = cv[i].y; v[2] = cv[i].z; v[3] = cv[i].w;
                 IO::unpack(cp[i], p);
             }
-            if (vec_ok && e + 4 <= ck.count) {
+            if (e + 4 <= ck.count) {
                 IO::unpack(cg[i], g);
-            } else {                                          // ragged tail or unaligned block start
+            } else {                                          // ragged tail
 #pragma unroll
                 for (int j = 0; j < 4; ++j) g[j] = (e + j < ck.count) ? IO::load1(gsrc + e + j) : 0.f;
             }
