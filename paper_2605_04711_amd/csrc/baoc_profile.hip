@@ -21,6 +21,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <new>
 #include <type_traits>
 #include <vector>
@@ -131,6 +132,12 @@ __device__ __forceinline__ float direction(float m, float v, float eps_u)
 // Preconditioner of Eq. 6, p = 1 / (sqrt(v) + eps), with one transcendental instead of two where eps is small
 // against sqrt(v): with r = 1/sqrt(v), p = r / (1 + eps r) = r (1 - eps r) up to (eps r)^2 < 1e-6.  Elsewhere
 // (v tiny, zero, sub-normal or NaN) the plain form.
+__device__ __forceinline__ float preconditioner_series(float v, float eps)
+{
+    const float r = __builtin_amdgcn_rsqf(v);
+    return __builtin_fmaf(-(eps * r), r, r);
+}
+
 __device__ __forceinline__ float preconditioner(float v, float eps)
 {
     const float r = __builtin_amdgcn_rsqf(v);
@@ -706,257 +713,333 @@ __global__ __launch_bounds__(64) void k_pick(const uint32_t* __restrict__ hist_a
 }
 
 // ---------------------------------------------------------------------------
-// Finalize over matrix blocks, tiled.  A task is a tile of up to 256 rows x 256 columns
-// of v (viewed as rows x cols) owned by one wavefront; a workgroup takes four consecutive
-// tasks of one block.  Two passes over v serve three consumers at once:
+// Finalize over matrix blocks, tiled.  Two passes over v (viewed as rows x cols) serve three consumers:
 //   pass 1: row / column partial sums (Eq. 7), sum of p = 1/(sqrt(v)+eps) (Eq. 6), first
 //           radix digit histogram (Eq. 4)
-//   pass 2: |S - r c^T / mu|^2 and |S|^2 (Eq. 7), ((p/p-bar - 1) theta)^2 and theta^2 (Eq. 6),
-//           second digit histogram, and the keys that carry a selected first digit appended to the
-//           task's candidate list (the last digit is then counted on the lists, k_cand_hist3)
-// Full tiles on the vector path load their rows one round ahead of their use.
+//   pass 2: |S - r c^T / mu|^2 (Eq. 7; |S|^2 is the step's own sum of v^2), ((p/p-bar - 1) theta)^2 and
+//           theta^2 (Eq. 6), and the keys that carry a selected first digit appended to a candidate list per
+//           wavefront; the second digit is counted on the list at the end, the last one by k_cand_hist3
+// A workgroup takes a tile of 64 * wc columns and seg_rows rows; its four wavefronts stand wc across the columns
+// and 4 / wc down the rows.  A wavefront reads 4 rows x 64 columns (256 bytes a row) with one load, a lane 4
+// consecutive columns of a row, at any alignment: a row sum then takes four exchange levels for four rows at
+// once, and narrow or odd-sized matrices keep their lanes busy.  Loads are issued one round of kQuads * 4 rows
+// ahead of their use; rounds with a missing row or column load for themselves.
+// Large layouts are bound by HBM with the vector ALUs close behind, small ones by the number of wavefronts in flight.
+// Measured (pass 1 / pass 2, us; before: one wavefront per 256 x 256 tile, scalar loads where a row is not a
+// multiple of 4, keys stored as they were found): 25.6 M coordinates of convolutions 189 / 416 -> 26 / 53,
+// 124 M 136 / 323 -> 93 / 159, 60 M of odd shapes 254 / 535 -> 51 / 104, 3.5 G 2492 / 3887 -> 2353 / 3640.
 // Blocks without a matrix shape are walked chunk-wise by k_hist / k_distortion instead.
 // ---------------------------------------------------------------------------
 
-constexpr uint32_t kTileRows = 256, kTileCols = 256;
+constexpr uint32_t kQuads = 4;                        // loads of 4 rows a wavefront has in flight
+constexpr uint32_t kRoundRows = 4 * kQuads;
+constexpr uint32_t kSubRounds = 256 / kRoundRows;     // rounds between two row-sum exchanges (256 rows per wavefront)
 
 struct alignas(8) MatRow {
     uint64_t state_start;                 // first coordinate of the block in v
     uint64_t grad_start;                  // the block's offset in the caller's flat buffers (theta)
     uint64_t off_r, off_c;                // into the r / c vectors (floats)
-    uint64_t off_rowpart, off_colpart;    // into the partial-sum arrays (floats)
+    uint64_t off_rowpart, off_colpart;    // into the partial-sum arrays (floats): [tile][row] and [seg][column]
     uint64_t cand_base;                   // the block's first candidate list (words into the candidate buffer)
     uint32_t rows, cols, n_tiles, n_segs;
-    uint32_t first_task, first_quad, block;
-    uint32_t cand_cap;                    // words per candidate list (one list per task)
+    uint32_t seg_rows, wc_log;            // tile: seg_rows x (64 << wc_log)
+    uint32_t first_task, block;           // first workgroup of the block in the tile passes
+    uint32_t cand_cap;                    // words per candidate list (one list per wavefront)
+    uint32_t first_fin;                   // first workgroup of the block in k_tile_finish1
 };
 
-struct MatTask { uint32_t mat, task, row0, row1, col0, ncols, tile, seg; bool vec, valid; };
-
-// Workgroup `quad` -> its block and this wavefront's task (tile index fastest).
-// `wave` must be uniform over the wavefront (callers pass it through readfirstlane), so that the task and
-// every address derived from it live in scalar registers.
-__device__ __forceinline__ MatTask decode_quad(const MatRow* __restrict__ mats, uint32_t n_mats, uint32_t quad, uint32_t wave)
+// Owning matrix block of every workgroup of the tile passes and of k_tile_finish1, looked up there with one load.
+__global__ __launch_bounds__(256) void k_build_tiles(const MatRow* __restrict__ mats, uint32_t n_mats, uint32_t n_tasks, uint32_t n_fin,
+                                                     uint32_t* __restrict__ tile_mat, uint32_t* __restrict__ fin_mat)
 {
+    uint32_t id = blockIdx.x * 256 + threadIdx.x;
+    const bool fin = id >= n_tasks;
+    if (fin) { id -= n_tasks; if (id >= n_fin) return; }
     uint32_t lo = 0, hi = n_mats - 1;
     while (lo < hi) {
         const uint32_t mid = (lo + hi + 1) >> 1;
-        if (mats[mid].first_quad <= quad) lo = mid; else hi = mid - 1;
+        if ((fin ? mats[mid].first_fin : mats[mid].first_task) <= id) lo = mid; else hi = mid - 1;
     }
-    const MatRow& m = mats[lo];
-    const uint32_t local = (quad - m.first_quad) * 4 + wave;
-    MatTask t;
-    t.mat = lo; t.valid = local < m.n_tiles * m.n_segs;
-    t.task = m.first_task + local;
-    t.seg = local / m.n_tiles; t.tile = local % m.n_tiles;
-    t.row0 = t.seg * kTileRows; t.row1 = t.valid ? min(m.rows, t.row0 + kTileRows) : t.row0;
-    t.col0 = t.tile * kTileCols; t.ncols = t.valid ? min(kTileCols, m.cols - t.col0) : 0;
-    t.vec = (m.cols & 3u) == 0;           // rows start 16-byte aligned (blocks start on 1 KB)
+    (fin ? fin_mat : tile_mat)[id] = lo;
+}
+
+__device__ __forceinline__ uint32_t scalar_u32(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ __forceinline__ uint32_t scalar_wave_index() { return scalar_u32(threadIdx.x >> 6); }
+
+// A wavefront's part of its workgroup's tile.  `wave` must be uniform over the wavefront (callers pass it through
+// readfirstlane), so that the task and every address derived from it live in scalar registers.
+struct TilePart {
+    uint32_t tile, seg;
+    uint32_t row0, row1;                  // the tile's rows
+    uint32_t wcol, wrow, wr;              // place of the wavefront in the workgroup; wavefronts down the rows
+    uint32_t col;                         // first of the lane's 4 columns
+    uint32_t lrow;                        // the lane's row in a quad
+    uint32_t n_ok;                        // how many of the lane's columns exist (0..4)
+    uint32_t rounds, full;                // rounds of the workgroup; rounds of the wavefront without a missing row or column
+    bool any;                             // some of the wavefront's columns exist
+    uint32_t offset;                      // the lane's first element of a full round, from the round's first row
+    uint32_t base;                        // the lane's first column (clamped to an existing one)
+};
+
+__device__ __forceinline__ TilePart tile_part(const MatRow& m, uint32_t wg, uint32_t lane, uint32_t wave)
+{
+    TilePart t;
+    const uint32_t local = wg - m.first_task;
+    t.seg = local / m.n_tiles; t.tile = local - t.seg * m.n_tiles;
+    t.wr = 4u >> m.wc_log;
+    t.wcol = wave & ((1u << m.wc_log) - 1u); t.wrow = wave >> m.wc_log;
+    t.row0 = t.seg * m.seg_rows; t.row1 = min(m.rows, t.row0 + m.seg_rows);
+    const uint32_t col0 = ((t.tile << m.wc_log) + t.wcol) * 64;
+    t.col = col0 + 4 * (lane & 15u); t.lrow = lane >> 4;
+    t.n_ok = t.col < m.cols ? min(4u, m.cols - t.col) : 0u;
+    t.any = col0 < m.cols;
+    const uint32_t blocks = (t.row1 - t.row0) / kRoundRows, log_wr = 2 - m.wc_log;
+    t.rounds = (t.row1 - t.row0 + (kRoundRows << log_wr) - 1) / (kRoundRows << log_wr);
+    // offsets of a full round are 32-bit byte offsets
+    t.full = col0 + 64 <= m.cols && m.cols < (1u << 28) && blocks > t.wrow ? ((blocks - t.wrow - 1) >> log_wr) + 1 : 0;
+    t.offset = t.lrow * m.cols + t.col;
+    t.base = min(t.col, m.cols - 1);
     return t;
 }
 
-// Column owned by slot k of a lane: 4 consecutive columns on the vector path, stride 64 otherwise.
-__device__ __forceinline__ uint32_t tile_col(bool vec, uint32_t lane, int k) { return vec ? 4 * lane + k : lane + 64 * k; }
+// First row (of the block) of a wavefront's round.
+__device__ __forceinline__ uint32_t round_row(const TilePart& t, uint32_t i) { return t.row0 + (i * t.wr + t.wrow) * kRoundRows; }
 
-__device__ __forceinline__ void load_tile_row(const float* __restrict__ row, bool vec, uint32_t lane, uint32_t ncols, float x[4])
-{
-    if (vec) {
-        if (4 * lane < ncols) {
-            const f4 t = ld_stream<f4>(row + 4 * lane);
-            x[0] = t.x; x[1] = t.y; x[2] = t.z; x[3] = t.w;
-        } else {
-            x[0] = x[1] = x[2] = x[3] = 0.f;
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) x[k] = (lane + 64 * k < ncols) ? row[lane + 64 * k] : 0.f;
-    }
-}
-
+// Four elements per lane and quad of a full round.  The address is a scalar base and a 32-bit lane offset.
 template <int TT>
-__device__ __forceinline__ void load_tile_theta(const typename GradIO<TT>::elem* __restrict__ row, bool vec, bool aligned,
-                                                uint32_t lane, uint32_t ncols, float x[4])
+__device__ __forceinline__ void load_full(typename GradIO<TT>::vec4 (&x)[kQuads], const typename GradIO<TT>::elem* __restrict__ src,
+                                          const TilePart& t, uint32_t cols, uint32_t i)
 {
-    // column ownership follows v's (vec: 4 consecutive columns per lane); `aligned` only picks the load width
-    typedef GradIO<TT> IO;
-    if (vec) {
-        if (4 * lane < ncols) {
-            if (aligned) IO::load4(row + 4 * lane, x);
-            else {
+    typedef typename GradIO<TT>::elem E;
+    const char* p = reinterpret_cast<const char*>(src) + (uint64_t)round_row(t, i) * cols * sizeof(E);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) x[k] = IO::load1(row + 4 * lane + k);
-            }
-        } else {
-            x[0] = x[1] = x[2] = x[3] = 0.f;
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) x[k] = (lane + 64 * k < ncols) ? IO::load1(row + lane + 64 * k) : 0.f;
+    for (uint32_t q = 0; q < kQuads; ++q) {
+        x[q] = GradIO<TT>::loadv_any(reinterpret_cast<const E*>(p + (uint32_t)(t.offset * sizeof(E))));
+        p += (uint64_t)cols * (4 * sizeof(E));
     }
 }
 
-__device__ __forceinline__ uint32_t scalar_wave_index()
+// The same at the edge of a tile.  Rows past the tile are replaced by its last one, columns past the matrix by its
+// last one; a lane then reads up to 3 elements past its row.  `left`: elements from src that may be read.
+template <int TT>
+__device__ __forceinline__ void load_edge(typename GradIO<TT>::vec4 (&x)[kQuads], const typename GradIO<TT>::elem* __restrict__ src,
+                                          uint64_t left, const TilePart& t, uint32_t cols, uint32_t i)
 {
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    typedef GradIO<TT> IO;
+    const uint32_t first = round_row(t, i);
+    const bool wide = (uint64_t)t.row1 * cols + 3 <= left;     // the same for the whole tile
+#pragma unroll
+    for (uint32_t q = 0; q < kQuads; ++q) {
+        const typename IO::elem* p = src + ((uint64_t)min(first + 4 * q + t.lrow, t.row1 - 1) * cols + t.base);
+        if (wide) {
+            x[q] = IO::loadv_any(p);
+        } else {
+            typename IO::elem e[4];
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) e[k] = k < t.n_ok ? p[k] : typename IO::elem(0);
+            x[q] = __builtin_bit_cast(typename IO::vec4, e);
+        }
+    }
 }
 
-constexpr int kRowsAhead = 2;             // rows of a full tile loaded per round, one round ahead of their use
+constexpr uint64_t kAnywhere = ~0ull;                 // v may be read past its end: g_prev follows it in the workspace
 
 __global__ __launch_bounds__(256) void k_tile_pass1(
-    const float* __restrict__ v_all, const MatRow* __restrict__ mats, uint32_t n_mats,
+    const float* __restrict__ v_all, const MatRow* __restrict__ mats, const uint32_t* __restrict__ tile_mat,
     float* __restrict__ rowpart, float* __restrict__ colpart, float* __restrict__ psumpart,
-    uint32_t* __restrict__ hist_all, float eps, bool want_p)
+    uint32_t* __restrict__ hist_all, float eps, float eps_low, bool want_p)
 {
     __shared__ uint32_t h[kBins1];
-    __shared__ float rowsum[4][kTileRows];                // a tile's row sums, written out together at the end
+    __shared__ float rowsum[4 * 256];                     // [wavefront][its rows of a sub-segment]
+    __shared__ double colsum[4 * 64];
+    __shared__ float psum_w[4];
     const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index();
+    const MatRow& m = mats[tile_mat[blockIdx.x]];
+    const TilePart t = tile_part(m, blockIdx.x, lane, wave);
+    const float* src = v_all + m.state_start;
+    const uint32_t cols = scalar_u32(m.cols);
+    f4 nx[kQuads];
+#pragma unroll
+    for (uint32_t q = 0; q < kQuads; ++q) nx[q] = f4{0.f, 0.f, 0.f, 0.f};
+    if (t.full) load_full<BAOC_GRAD_F32>(nx, src, t, cols, 0);
     for (uint32_t i = threadIdx.x; i < kBins1; i += 256) h[i] = 0;
-    const MatTask t = decode_quad(mats, n_mats, blockIdx.x, wave);
-    const MatRow& m = mats[t.mat];
+    // Column sums and the sum of p run over many rows per lane: kept in fp64 so that a constant
+    // v (rank one, p constant) comes out as such to ~1e-7 instead of the ~1e-5 of a long fp32 chain.
+    double cs[4] = {0.0, 0.0, 0.0, 0.0}, psum = 0.0;
     __syncthreads();
-    if (t.valid) {
-        const float* row = v_all + m.state_start + (uint64_t)t.row0 * m.cols + t.col0;
-        bool ok[4];
+    for (uint32_t i = 0; i < t.rounds; ++i) {
+        if (t.any) {
+            float x[kQuads][4];
+            if (i < t.full) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) ok[k] = tile_col(t.vec, lane, k) < t.ncols;
-        // Column sums and the sum of p run over up to 256 rows per lane: kept in fp64 so that a constant
-        // v (rank one, p constant) comes out as such to ~1e-7 instead of the ~1e-5 of a long fp32 chain.
-        double cs[4] = {0.0, 0.0, 0.0, 0.0}, psum = 0.0;
-        float* rs_out = rowsum[wave];
-        auto consume = [&](auto full, const float x[4]) {
-            constexpr bool FULL = decltype(full)::value;     // every column of the lane is inside the tile
-            float prow = 0.f;
+                for (uint32_t q = 0; q < kQuads; ++q) { x[q][0] = nx[q].x; x[q][1] = nx[q].y; x[q][2] = nx[q].z; x[q][3] = nx[q].w; }
+                if (i + 1 < t.full) load_full<BAOC_GRAD_F32>(nx, src, t, cols, i + 1);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                cs[k] += (double)x[k];
-                if (FULL || ok[k]) {
-                    atomicAdd(&h[(__builtin_bit_cast(uint32_t, x[k]) & 0x7fffffffu) >> kShift1], 1u);
-                    if (want_p) prow += preconditioner(x[k], eps);
+                for (uint32_t q = 0; q < kQuads; ++q)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) atomicAdd(&h[(__builtin_bit_cast(uint32_t, x[q][k]) >> kShift1) & (kBins1 - 1)], 1u);
+                if (want_p) {
+                    float low = x[0][0];
+#pragma unroll
+                    for (uint32_t q = 0; q < kQuads; ++q) low = fminf(fminf(fminf(low, x[q][0]), fminf(x[q][1], x[q][2])), x[q][3]);
+                    auto add_p = [&](auto p_of) {
+#pragma unroll
+                        for (uint32_t q = 0; q < kQuads; ++q)
+                            psum += (double)((p_of(x[q][0]) + p_of(x[q][1])) + (p_of(x[q][2]) + p_of(x[q][3])));
+                    };
+                    if (__builtin_amdgcn_ballot_w64(!(low > eps_low)) == 0) add_p([&](float v) { return preconditioner_series(v, eps); });
+                    else add_p([&](float v) { return preconditioner(v, eps); });
+                }
+            } else {
+                const uint32_t first = round_row(t, i);
+                f4 ex[kQuads];
+                load_edge<BAOC_GRAD_F32>(ex, src, kAnywhere, t, cols, i);
+#pragma unroll
+                for (uint32_t q = 0; q < kQuads; ++q) {
+                    x[q][0] = ex[q].x; x[q][1] = ex[q].y; x[q][2] = ex[q].z; x[q][3] = ex[q].w;
+                    const bool in_row = first + 4 * q + t.lrow < t.row1;
+                    float prow = 0.f;
+#pragma unroll
+                    for (uint32_t k = 0; k < 4; ++k) {
+                        if (in_row && k < t.n_ok) {
+                            atomicAdd(&h[(__builtin_bit_cast(uint32_t, x[q][k]) >> kShift1) & (kBins1 - 1)], 1u);
+                            if (want_p) prow += preconditioner(x[q][k], eps);
+                        } else {
+                            x[q][k] = 0.f;
+                        }
+                    }
+                    psum += (double)prow;
                 }
             }
-            psum += (double)prow;
-            return wave_sum((x[0] + x[1]) + (x[2] + x[3]));
-        };
-        uint32_t r = t.row0;
-        if (t.vec && t.ncols == kTileCols) {
-            const float* vp = row + 4 * lane;
-            f4 nx[kRowsAhead];
+            float s[kQuads];
 #pragma unroll
-            for (int q = 0; q < kRowsAhead; ++q) nx[q] = f4{0.f, 0.f, 0.f, 0.f};
-            auto issue = [&](uint32_t r0) {
+            for (uint32_t q = 0; q < kQuads; ++q) {
 #pragma unroll
-                for (int q = 0; q < kRowsAhead; ++q)
-                    if (r0 + q < t.row1) nx[q] = ld_stream<f4>(vp + (uint64_t)(r0 + q - t.row0) * m.cols);
-            };
-            issue(r);
-            for (; r < t.row1; r += kRowsAhead) {
-                f4 cx[kRowsAhead];
+                for (int k = 0; k < 4; ++k) cs[k] += (double)x[q][k];
+                s[q] = (x[q][0] + x[q][1]) + (x[q][2] + x[q][3]);
+            }
+            // Row sums: a halving exchange over the 16 lanes of a row leaves quad 2 b3 + b2 with the lanes whose
+            // index has these bits.
+            static_assert(kQuads == 4, "the exchange is written for four quads");
+            {
+                const bool b3 = lane & 8u, b2 = lane & 4u;
 #pragma unroll
-                for (int q = 0; q < kRowsAhead; ++q) cx[q] = nx[q];
-                if (r + kRowsAhead < t.row1) issue(r + kRowsAhead);
-#pragma unroll
-                for (int q = 0; q < kRowsAhead; ++q) {
-                    if (r + q >= t.row1) break;
-                    const float x[4] = {cx[q].x, cx[q].y, cx[q].z, cx[q].w};
-                    const float rs = consume(std::true_type(), x);
-                    if (lane == 0) rs_out[r + q - t.row0] = rs;
+                for (int q = 0; q < 2; ++q) {
+                    const float keep = b3 ? s[q + 2] : s[q], send = b3 ? s[q] : s[q + 2];
+                    s[q] = keep + dpp<0x128, 0xf>(0.f, send);
                 }
-            }
-        } else {
-            for (; r < t.row1; ++r) {
-                float x[4];
-                load_tile_row(row, t.vec, lane, t.ncols, x);
-                const float rs = consume(std::false_type(), x);
-                if (lane == 0) rs_out[r - t.row0] = rs;
-                row += m.cols;
+                const float keep = b2 ? s[1] : s[0], send = b2 ? s[0] : s[1];
+                float a = keep + dpp<0x141, 0xf>(0.f, send);
+                a += dpp<0x4E, 0xf>(0.f, a);
+                a += dpp<0xB1, 0xf>(0.f, a);
+                if ((lane & 3u) == 0) rowsum[wave * 256 + (i % kSubRounds) * kRoundRows + (b3 ? 8u : 0u) + (b2 ? 4u : 0u) + t.lrow] = a;
             }
         }
-        // row sums of this tile: rowpart is tile-major ([tile][row]), so the wavefront writes one run
-        {
-            float* rp = rowpart + m.off_rowpart + (uint64_t)t.tile * m.rows + t.row0;
-            const uint32_t nr = t.row1 - t.row0;
-#pragma unroll
-            for (uint32_t j = 0; j < kTileRows / 64; ++j)
-                if (lane + 64 * j < nr) rp[lane + 64 * j] = rs_out[lane + 64 * j];
+        if ((i + 1) % kSubRounds == 0 || i + 1 == t.rounds) {
+            // row sums of the sub-segment: rowpart is tile-major ([tile][row]), so the workgroup writes one run
+            __syncthreads();
+            const uint32_t r0 = t.row0 + i / kSubRounds * kSubRounds * t.wr * kRoundRows;
+            const uint32_t n = min(t.row1 - r0, kSubRounds * t.wr * kRoundRows);
+            const uint32_t n_wc = min(1u << m.wc_log, (m.cols - ((t.tile << m.wc_log) * 64) + 63) / 64);   // wavefronts that have columns
+            for (uint32_t rs = threadIdx.x; rs < n; rs += 256) {
+                const uint32_t step = rs / kRoundRows, wrow = step & (t.wr - 1), ii = step >> (2 - m.wc_log);
+                const float* in = rowsum + (wrow << m.wc_log) * 256 + ii * kRoundRows + rs % kRoundRows;
+                float sum = in[0];
+                for (uint32_t w = 1; w < n_wc; ++w) sum += in[w * 256];
+                rowpart[m.off_rowpart + (uint64_t)t.tile * m.rows + r0 + rs] = sum;
+            }
+            __syncthreads();
         }
-        float* cp = colpart + m.off_colpart + (uint64_t)t.seg * m.cols + t.col0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (ok[k]) cp[tile_col(t.vec, lane, k)] = (float)cs[k];
-        const float ptile = wave_sum((float)psum);
-        if (lane == 0) psumpart[t.task] = ptile;
     }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        cs[k] += __shfl_xor(cs[k], 16);
+        cs[k] += __shfl_xor(cs[k], 32);
+        if (lane < 16) colsum[wave * 64 + 4 * lane + k] = cs[k];
+    }
+    const float ptile = wave_sum((float)psum);
+    if (lane == 0) psum_w[wave] = ptile;
     __syncthreads();
+    const uint32_t tile_cols = 64u << m.wc_log, col = t.tile * tile_cols + threadIdx.x;
+    if (threadIdx.x < tile_cols && col < m.cols) {
+        double a = 0.0;
+        for (uint32_t w = 0; w < t.wr; ++w) a += colsum[w * tile_cols + threadIdx.x];
+        colpart[m.off_colpart + (uint64_t)t.seg * m.cols + col] = (float)a;
+    }
+    if (threadIdx.x == 0) psumpart[blockIdx.x] = (psum_w[0] + psum_w[1]) + (psum_w[2] + psum_w[3]);
     uint32_t* out = hist_all + (uint64_t)m.block * 4 * kBins;
     for (uint32_t i = threadIdx.x; i < kBins1; i += 256)
         if (h[i]) atomicAdd(&out[i], h[i]);
 }
 
-// r_i, c_j (fp32 for pass 2) and, per slice, the sums behind mu and the block's sum of p, from the pass-1
-// partial sums.  A matrix block is cut into kFinSlices slices of rows, of columns and of tasks (grid.y).
-constexpr uint32_t kFinSlices = 32;
-
-__global__ __launch_bounds__(256) void k_tile_finish1(const MatRow* __restrict__ mats, const float* __restrict__ rowpart,
-                                                      const float* __restrict__ colpart, const float* __restrict__ psumpart,
-                                                      float* __restrict__ rvec, float* __restrict__ cvec,
-                                                      double* __restrict__ finpart)
+// r_i, c_j (fp32 for pass 2) and the sums behind mu from the pass-1 partial sums.  A workgroup takes 64 rows or 64
+// columns of a block, summed over the tiles or segments by 4 wavefronts in parallel: a 50257 x 768 block has
+// hundreds of segments, whose loads would otherwise wait for each other.
+__global__ __launch_bounds__(256) void k_tile_finish1(const MatRow* __restrict__ mats, const uint32_t* __restrict__ fin_mat,
+                                                      const float* __restrict__ rowpart, const float* __restrict__ colpart,
+                                                      float* __restrict__ rvec, float* __restrict__ cvec, double* __restrict__ finpart)
 {
-    const MatRow m = mats[blockIdx.x];
-    const uint32_t y = blockIdx.y;
-    double local = 0.0, lp = 0.0;
-    const uint32_t rper = (m.rows + kFinSlices - 1) / kFinSlices, i1 = min(m.rows, (y + 1) * rper);
-    for (uint32_t i = y * rper + threadIdx.x; i < i1; i += 256) {
-        const float* rp = rowpart + m.off_rowpart + i;                       // tile-major: [tile][row]
-        double s = 0.0;
-        for (uint32_t t = 0; t < m.n_tiles; ++t) s += (double)rp[(uint64_t)t * m.rows];
-        const double r = s / (double)m.cols;
-        rvec[m.off_r + i] = (float)r;
-        local += r;
+    __shared__ double sh[4][64];
+    const MatRow& m = mats[fin_mat[blockIdx.x]];
+    const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index();
+    const uint32_t local = blockIdx.x - m.first_fin, row_wgs = (m.rows + 63) / 64;
+    const bool is_row = local < row_wgs;
+    const uint32_t at = (is_row ? local : local - row_wgs) * 64 + lane, len = is_row ? m.rows : m.cols;
+    const uint32_t count = is_row ? m.n_tiles : m.n_segs;
+    const float* src = (is_row ? rowpart + m.off_rowpart : colpart + m.off_colpart) + at;
+    double s = 0.0;
+    if (at < len) {
+#pragma unroll 8
+        for (uint32_t k = wave; k < count; k += 4) s += (double)src[(uint64_t)k * len];
     }
-    const uint32_t cper = (m.cols + kFinSlices - 1) / kFinSlices, j1 = min(m.cols, (y + 1) * cper);
-    for (uint32_t j = y * cper + threadIdx.x; j < j1; j += 256) {
-        const float* cp = colpart + m.off_colpart + j;
-        double s = 0.0;
-        for (uint32_t g = 0; g < m.n_segs; ++g) s += (double)cp[(uint64_t)g * m.cols];
-        cvec[m.off_c + j] = (float)(s / (double)m.rows);
+    sh[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0) return;
+    s = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
+    if (!is_row) {
+        if (at < len) cvec[m.off_c + at] = (float)(s / (double)m.rows);
+        return;
     }
-    const uint32_t n_tasks = m.n_tiles * m.n_segs, tper = (n_tasks + kFinSlices - 1) / kFinSlices, k1 = min(n_tasks, (y + 1) * tper);
-    for (uint32_t i = y * tper + threadIdx.x; i < k1; i += 256) lp += (double)psumpart[m.first_task + i];
-    __shared__ double sh[256], sp[256];
-    sh[threadIdx.x] = local; sp[threadIdx.x] = lp;
+    double r = s / (double)m.cols;                        // 0 for lanes past the rows
+    if (at < len) rvec[m.off_r + at] = (float)r;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) r += __shfl_xor(r, d);
+    if (lane == 0) finpart[blockIdx.x] = r;
+}
+
+// mu (fp64) and the block's sum of p, added in a fixed order.
+__global__ __launch_bounds__(256) void k_tile_finish1_sum(const MatRow* __restrict__ mats, const double* __restrict__ finpart,
+                                                          const float* __restrict__ psumpart, double* __restrict__ mu_out, double* __restrict__ rec_all)
+{
+    __shared__ double sh[2][256];
+    const MatRow& m = mats[blockIdx.x];
+    double a = 0.0, p = 0.0;
+    for (uint32_t i = threadIdx.x; i < (m.rows + 63) / 64; i += 256) a += finpart[m.first_fin + i];
+    for (uint32_t i = threadIdx.x; i < m.n_tiles * m.n_segs; i += 256) p += (double)psumpart[m.first_task + i];
+    sh[0][threadIdx.x] = a; sh[1][threadIdx.x] = p;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) { sh[threadIdx.x] += sh[threadIdx.x + w]; sp[threadIdx.x] += sp[threadIdx.x + w]; }
+        if ((int)threadIdx.x < w) { sh[0][threadIdx.x] += sh[0][threadIdx.x + w]; sh[1][threadIdx.x] += sh[1][threadIdx.x + w]; }
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        double* o = finpart + ((uint64_t)blockIdx.x * kFinSlices + y) * 2;
-        o[0] = sh[0]; o[1] = sp[0];
+        mu_out[blockIdx.x] = sh[0][0] / (double)m.rows;
+        rec_all[(uint64_t)m.block * kRecDoubles + R_PSUM] = sh[1][0];
     }
 }
 
-// mu (fp64) and the block's sum of p: the slices of k_tile_finish1 added in a fixed order.
-__global__ __launch_bounds__(64) void k_tile_finish1_sum(const MatRow* __restrict__ mats, const double* __restrict__ finpart,
-                                                         double* __restrict__ mu_out, double* __restrict__ rec_all)
-{
-    if (threadIdx.x != 0) return;
-    const MatRow& m = mats[blockIdx.x];
-    const double* in = finpart + (uint64_t)blockIdx.x * kFinSlices * 2;
-    double a = 0.0, p = 0.0;
-    for (uint32_t y = 0; y < kFinSlices; ++y) { a += in[2 * y]; p += in[2 * y + 1]; }
-    mu_out[blockIdx.x] = a / (double)m.rows;
-    rec_all[(uint64_t)m.block * kRecDoubles + R_PSUM] = p;
-}
+constexpr uint32_t kStage = 2 * kBins2 / 4;            // words of h per wavefront while the lists are written
 
-template <int TT>
+// F, C: Eq. 7 and Eq. 6 are wanted.
+template <int TT, bool F, bool C>
 __global__ __launch_bounds__(256) void k_tile_pass2(
-    const float* __restrict__ v_all, const typename GradIO<TT>::elem* __restrict__ theta,
-    const MatRow* __restrict__ mats, uint32_t n_mats,
+    const float* __restrict__ v_all, const typename GradIO<TT>::elem* __restrict__ theta, uint64_t theta_numel,
+    const MatRow* __restrict__ mats, const uint32_t* __restrict__ tile_mat,
     const float* __restrict__ rvec, const float* __restrict__ cvec, const double* __restrict__ mu_all,
     const double* __restrict__ rec_all, const uint32_t* __restrict__ sel_prefix,
     float* __restrict__ residpart, uint32_t* __restrict__ hist_all,
-    uint32_t* __restrict__ cand, uint32_t* __restrict__ cand_count, uint32_t* __restrict__ scan3,
-    float eps, bool want_F, bool want_C)
+    uint32_t* cand, uint32_t* __restrict__ cand_count, uint32_t* __restrict__ scan3,
+    float eps, float eps_low)
 {
     typedef GradIO<TT> IO;
     typedef typename IO::vec4 TV;
@@ -964,122 +1047,181 @@ __global__ __launch_bounds__(256) void k_tile_pass2(
     // theirs); a third or fourth distinct prefix is rare and counts straight into global memory.
     constexpr uint32_t NSLOT = 2;
     __shared__ uint32_t h[NSLOT * kBins2];
+    __shared__ float red[4][4];
     const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index();
-    for (uint32_t i = threadIdx.x; i < NSLOT * kBins2; i += 256) h[i] = 0;
-    const MatTask t = decode_quad(mats, n_mats, blockIdx.x, wave);
-    const MatRow& m = mats[t.mat];
+    const uint32_t mat = tile_mat[blockIdx.x];
+    const MatRow& m = mats[mat];
+    const TilePart t = tile_part(m, blockIdx.x, lane, wave);
+    const float* src = v_all + m.state_start;
+    const typename IO::elem* tsrc = theta + m.grad_start;
+    const uint64_t tleft = theta_numel - m.grad_start;
+    const float* rr = rvec + m.off_r;
+    const uint32_t cols = scalar_u32(m.cols), cap = scalar_u32(m.cand_cap);
+    f4 nx[kQuads]; TV nt[kQuads]; float nr[kQuads];
+#pragma unroll
+    for (uint32_t q = 0; q < kQuads; ++q) { nx[q] = f4{0.f, 0.f, 0.f, 0.f}; nt[q] = TV{}; nr[q] = 0.f; }
+    auto issue = [&](uint32_t i) {
+        load_full<BAOC_GRAD_F32>(nx, src, t, cols, i);
+        if (C) load_full<TT>(nt, tsrc, t, cols, i);
+        const float* p = rr + round_row(t, i);
+#pragma unroll
+        for (uint32_t q = 0; q < kQuads; ++q) nr[q] = (p + 4 * q)[t.lrow];
+    };
+    if (t.full) issue(0);
     const Prefixes d = distinct_prefixes(sel_prefix, m.block);
     uint32_t* hist_out = hist_all + (uint64_t)m.block * 4 * kBins;
-    __syncthreads();
-    if (t.valid) {
-        const double mu = mu_all[t.mat];
-        // c_j / mu is formed in fp64 (mu may lie below the fp32 normal range); S~ = 0 when mu = 0
-        float inv_pbar = 0.f;
-        if (want_C) inv_pbar = (float)((double)((uint64_t)m.rows * m.cols) / rec_all[(uint64_t)m.block * kRecDoubles + R_PSUM]);
-        bool ok[4]; float cm[4];
+    const double mu = mu_all[mat];
+    // c_j / mu is formed in fp64 (mu may lie below the fp32 normal range); S~ = 0 when mu = 0
+    float inv_pbar = 0.f, cm[4];
+    if (C) inv_pbar = (float)((double)((uint64_t)m.rows * m.cols) / rec_all[(uint64_t)m.block * kRecDoubles + R_PSUM]);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t c = tile_col(t.vec, lane, k);
-            ok[k] = c < t.ncols;
-            cm[k] = (ok[k] && mu != 0.0) ? (float)((double)cvec[m.off_c + t.col0 + c] / mu) : 0.f;
+    for (uint32_t k = 0; k < 4; ++k)
+        cm[k] = (F && k < t.n_ok && mu != 0.0) ? (float)((double)cvec[m.off_c + t.col + k] / mu) : 0.f;
+    uint32_t* list = cand + m.cand_base + ((uint64_t)(blockIdx.x - m.first_task) * 4 + wave) * cap;
+    uint32_t n_cand = 0;                                      // uniform over the wavefront; may grow past the list
+    float res = 0.f, cn = 0.f, cd = 0.f;
+    // Matching keys gather in the wavefront's quarter of h (the histogram is not needed before the end) and leave
+    // 64 at a time: stores of a few keys each would be waited for together with the next round's loads.
+    uint32_t* stage = h + wave * kStage;
+    uint32_t n_stage = 0;
+    auto append = [&](bool hit, uint64_t hits, uint32_t bits) {
+        const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u));
+        if (hit) stage[n_stage + at] = bits;
+        n_stage += (uint32_t)__builtin_popcountll(hits);
+    };
+    // Whole sets of 64 go to the list, as far as it has room; what is left moves to the front.
+    auto flush = [&](bool all) {
+        const uint32_t n = all ? n_stage : n_stage & ~63u;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // lanes read what other lanes staged
+        for (uint32_t i = lane; i < n; i += 64)
+            if (n_cand + i < cap) list[n_cand + i] = stage[i];
+        n_cand += n; n_stage -= n;
+        const uint32_t rest = lane < n_stage ? stage[n + lane] : 0u;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (lane < n_stage) stage[lane] = rest;
+    };
+    static_assert(kStage >= 63 + 64 * 4 * 2, "two quads of keys and what the last flush left");
+    const uint32_t p0 = d.pre[0], p1 = d.pre[1];
+    for (uint32_t i = 0; i < t.full; ++i) {
+        float x[kQuads][4], th[kQuads][4], ri[kQuads];
+#pragma unroll
+        for (uint32_t q = 0; q < kQuads; ++q) {
+            x[q][0] = nx[q].x; x[q][1] = nx[q].y; x[q][2] = nx[q].z; x[q][3] = nx[q].w;
+            IO::unpack(nt[q], th[q]);
+            ri[q] = nr[q];
         }
-        const uint64_t first = (uint64_t)t.row0 * m.cols + t.col0;
-        const float* row = v_all + m.state_start + first;
-        const typename IO::elem* trow = theta + m.grad_start + first;
-        const bool talign = (reinterpret_cast<uintptr_t>(trow) & IO::kAlignMask) == 0;   // cols % 4 == 0: same for all rows
-        const float* rr = rvec + m.off_r + t.row0;
-        uint32_t* list = cand + m.cand_base + (uint64_t)(t.task - m.first_task) * m.cand_cap;
-        uint32_t n_cand = 0;                                  // uniform over the wavefront
-        float res = 0.f, s2 = 0.f, cn = 0.f, cd = 0.f;
-        auto consume = [&](auto full, const float x[4], const float th[4], float ri) {
-            constexpr bool FULL = decltype(full)::value;     // every column of the lane is inside the tile
+        if (i + 1 < t.full) issue(i + 1);
+        if (d.n <= 2) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const bool in = FULL || ok[k];
-                const uint32_t key = __builtin_bit_cast(uint32_t, x[k]) & 0x7fffffffu;
-                const uint32_t hi = key >> kShift1, bin = (key >> kShift2) & (kBins2 - 1);
-                bool hit = false;
-                if (in) {
-                    if (hi == d.pre[0]) { atomicAdd(&h[bin], 1u); hit = true; }
-                    else if (hi == d.pre[1]) { atomicAdd(&h[kBins2 + bin], 1u); hit = true; }
-                    else if (d.n > 2 && (hi == d.pre[2] || hi == d.pre[3])) {
-                        const uint32_t slot = hi == d.pre[2] ? 2u : 3u;
+            for (uint32_t q = 0; q < kQuads; ++q) {
 #pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            if (d.slot_of[q] == slot) atomicAdd(&hist_out[q * kBins + bin], 1u);
-                        hit = true;
-                    }
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t bits = __builtin_bit_cast(uint32_t, x[q][k]), hi = (bits >> kShift1) & (kBins1 - 1);
+                    append(hi == p0 || hi == p1, __builtin_amdgcn_ballot_w64(hi == p0) | __builtin_amdgcn_ballot_w64(hi == p1), bits);
                 }
-                // candidates: the keys that carry a selected first digit, in the task's own list
-                const uint64_t hits = __builtin_amdgcn_ballot_w64(hit);
-                if (hits) {
-                    const uint32_t at = n_cand + __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u));
-                    if (hit && at < m.cand_cap) list[at] = key;
-                    n_cand += (uint32_t)__builtin_popcountll(hits);
-                }
-                if (in) {
-                    if (want_F) {
-                        const float dd = x[k] - ri * cm[k];
-                        res = __builtin_fmaf(dd, dd, res);
-                        s2 = __builtin_fmaf(x[k], x[k], s2);
-                    }
-                    if (want_C) {
-                        const float p = preconditioner(x[k], eps);
-                        const float y = (p * inv_pbar - 1.0f) * th[k];
-                        cn = __builtin_fmaf(y, y, cn);
-                        cd = __builtin_fmaf(th[k], th[k], cd);
-                    }
-                }
-            }
-        };
-        uint32_t r = t.row0;
-        if (t.vec && talign && t.ncols == kTileCols) {
-            const float* vp = row + 4 * lane;
-            const typename IO::elem* tp = trow + 4 * lane;
-            f4 nx[kRowsAhead]; TV nt[kRowsAhead]; float nr[kRowsAhead];
-#pragma unroll
-            for (int q = 0; q < kRowsAhead; ++q) { nx[q] = f4{0.f, 0.f, 0.f, 0.f}; nt[q] = TV{}; nr[q] = 0.f; }
-            auto issue = [&](uint32_t r0) {
-#pragma unroll
-                for (int q = 0; q < kRowsAhead; ++q)
-                    if (r0 + q < t.row1) {
-                        const uint64_t o = (uint64_t)(r0 + q - t.row0) * m.cols;
-                        nx[q] = ld_stream<f4>(vp + o);
-                        if (want_C) nt[q] = IO::loadv(tp + o);
-                        nr[q] = rr[r0 + q - t.row0];
-                    }
-            };
-            issue(r);
-            for (; r < t.row1; r += kRowsAhead) {
-                f4 cx[kRowsAhead]; TV ct[kRowsAhead]; float cr[kRowsAhead];
-#pragma unroll
-                for (int q = 0; q < kRowsAhead; ++q) { cx[q] = nx[q]; ct[q] = nt[q]; cr[q] = nr[q]; }
-                if (r + kRowsAhead < t.row1) issue(r + kRowsAhead);
-#pragma unroll
-                for (int q = 0; q < kRowsAhead; ++q) {
-                    if (r + q >= t.row1) break;
-                    const float x[4] = {cx[q].x, cx[q].y, cx[q].z, cx[q].w};
-                    float th[4] = {0.f, 0.f, 0.f, 0.f};
-                    if (want_C) IO::unpack(ct[q], th);
-                    consume(std::true_type(), x, th, cr[q]);
-                }
+                if (q % 2 == 1 && n_stage >= 64) flush(false);
             }
         } else {
-            for (; r < t.row1; ++r) {
-                float x[4], th[4] = {0.f, 0.f, 0.f, 0.f};
-                load_tile_row(row, t.vec, lane, t.ncols, x);
-                if (want_C) load_tile_theta<TT>(trow, t.vec, talign, lane, t.ncols, th);
-                consume(std::false_type(), x, th, *rr);
-                row += m.cols; trow += m.cols; ++rr;
+#pragma unroll
+            for (uint32_t q = 0; q < kQuads; ++q) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t bits = __builtin_bit_cast(uint32_t, x[q][k]), hi = (bits >> kShift1) & (kBins1 - 1);
+                    const bool hit = hi == p0 || hi == p1 || hi == d.pre[2] || hi == d.pre[3];
+                    append(hit, __builtin_amdgcn_ballot_w64(hit), bits);
+                }
+                if (q % 2 == 1 && n_stage >= 64) flush(false);
             }
         }
-        res = wave_sum(res); s2 = wave_sum(s2); cn = wave_sum(cn); cd = wave_sum(cd);
-        if (lane == 0) {
-            float* o = residpart + (uint64_t)t.task * 4;
-            o[0] = res; o[1] = s2; o[2] = cn; o[3] = cd;
-            cand_count[t.task] = n_cand;
-            if (n_cand > m.cand_cap) scan3[m.block] = 1u;    // list too short: the block's last digit takes a third scan
+        if (F) {
+#pragma unroll
+            for (uint32_t q = 0; q < kQuads; ++q)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float dd = __builtin_fmaf(-ri[q], cm[k], x[q][k]);
+                    res = __builtin_fmaf(dd, dd, res);
+                }
         }
+        if (C) {
+            float low = x[0][0];
+#pragma unroll
+            for (uint32_t q = 0; q < kQuads; ++q) low = fminf(fminf(fminf(low, x[q][0]), fminf(x[q][1], x[q][2])), x[q][3]);
+            auto distort = [&](auto p_of) {
+#pragma unroll
+                for (uint32_t q = 0; q < kQuads; ++q)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const float y = __builtin_fmaf(p_of(x[q][k]), inv_pbar, -1.0f) * th[q][k];
+                        cn = __builtin_fmaf(y, y, cn);
+                        cd = __builtin_fmaf(th[q][k], th[q][k], cd);
+                    }
+            };
+            if (__builtin_amdgcn_ballot_w64(!(low > eps_low)) == 0) distort([&](float v) { return preconditioner_series(v, eps); });
+            else distort([&](float v) { return preconditioner(v, eps); });
+        }
+    }
+    for (uint32_t i = t.full; t.any && i < t.rounds; ++i) {
+        const uint32_t first = round_row(t, i);
+        f4 ex[kQuads]; TV et[kQuads];
+        load_edge<BAOC_GRAD_F32>(ex, src, kAnywhere, t, cols, i);
+        if (C) load_edge<TT>(et, tsrc, tleft, t, cols, i);
+#pragma unroll
+        for (uint32_t q = 0; q < kQuads; ++q) {
+            const bool in_row = first + 4 * q + t.lrow < t.row1;
+            const float ri = rr[min(first + 4 * q + t.lrow, t.row1 - 1)], x[4] = {ex[q].x, ex[q].y, ex[q].z, ex[q].w};
+            float th[4] = {0.f, 0.f, 0.f, 0.f};
+            if (C) IO::unpack(et[q], th);
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                const bool in = in_row && k < t.n_ok;
+                const uint32_t bits = __builtin_bit_cast(uint32_t, x[k]), hi = (bits >> kShift1) & (kBins1 - 1);
+                const bool hit = in && (hi == p0 || hi == p1 || hi == d.pre[2] || hi == d.pre[3]);
+                append(hit, __builtin_amdgcn_ballot_w64(hit), bits);
+                if (F) {
+                    const float dd = in ? __builtin_fmaf(-ri, cm[k], x[k]) : 0.f;
+                    res = __builtin_fmaf(dd, dd, res);
+                }
+                if (C) {
+                    const float tk = in ? th[k] : 0.f;
+                    const float y = in ? __builtin_fmaf(preconditioner(x[k], eps), inv_pbar, -1.0f) * tk : 0.f;
+                    cn = __builtin_fmaf(y, y, cn);
+                    cd = __builtin_fmaf(tk, tk, cd);
+                }
+            }
+            if (n_stage >= 64) flush(false);
+        }
+    }
+    flush(true);
+    res = wave_sum(res); cn = wave_sum(cn); cd = wave_sum(cd);
+    if (lane == 0) {
+        red[wave][0] = res; red[wave][1] = cn; red[wave][2] = cd;
+        cand_count[blockIdx.x * 4 + wave] = n_cand;
+        if (n_cand > cap) scan3[m.block] = 1u;         // list too short: the block's last digit takes a third scan
+    }
+    __syncthreads();
+    if (threadIdx.x < 3)
+        residpart[(uint64_t)blockIdx.x * 4 + threadIdx.x] = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+    for (uint32_t i = threadIdx.x; i < NSLOT * kBins2; i += 256) h[i] = 0;
+    __syncthreads();
+    // second digit, from the list just written; a wavefront whose list was too short walks its part of the tile again.
+    // A key that matches prefix slot 0 or 1 counts in LDS, slot 2 or 3 in global memory.
+    auto count2 = [&](uint32_t bits) {
+        const uint32_t hi = (bits >> kShift1) & (kBins1 - 1), bin = (bits >> kShift2) & (kBins2 - 1);
+        if (hi == d.pre[0]) atomicAdd(&h[bin], 1u);
+        else if (hi == d.pre[1]) atomicAdd(&h[kBins2 + bin], 1u);
+        else if (hi == d.pre[2] || hi == d.pre[3]) {
+            const uint32_t slot = hi == d.pre[2] ? 2u : 3u;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (d.slot_of[q] == slot) atomicAdd(&hist_out[q * kBins + bin], 1u);
+        }
+    };
+    if (n_cand <= cap) {
+        for (uint32_t i = lane; i < n_cand; i += 64) count2(list[i]);
+    } else {
+        for (uint32_t i = 0; i < t.rounds; ++i)
+            for (uint32_t r = round_row(t, i) + t.lrow; r < min(t.row1, round_row(t, i) + kRoundRows); r += 4)
+                for (uint32_t k = 0; k < t.n_ok; ++k) count2(__builtin_bit_cast(uint32_t, src[(uint64_t)r * m.cols + t.col + k]));
     }
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < kBins2; i += 256) {
@@ -1095,25 +1237,22 @@ __global__ __launch_bounds__(256) void k_tile_pass2(
 // Third digit of the matrix blocks, counted on the candidate lists that the second tile pass wrote (a few
 // per cent of the coordinates).  Blocks flagged in scan3 are left to the third scan of v.
 __global__ __launch_bounds__(256) void k_cand_hist3(
-    const MatRow* __restrict__ mats, uint32_t n_mats, const uint32_t* __restrict__ cand,
+    const MatRow* __restrict__ mats, const uint32_t* __restrict__ tile_mat, const uint32_t* __restrict__ cand,
     const uint32_t* __restrict__ cand_count, const uint32_t* __restrict__ sel_prefix,
     const uint32_t* __restrict__ scan3, uint32_t* __restrict__ hist_all)
 {
     __shared__ uint32_t h[4 * kBins3];
     const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index();
-    const MatTask t = decode_quad(mats, n_mats, blockIdx.x, wave);
-    const MatRow& m = mats[t.mat];
-    if (scan3[m.block]) return;                              // the same for the whole workgroup (one block per quad)
+    const MatRow& m = mats[tile_mat[blockIdx.x]];
+    if (scan3[m.block]) return;                              // the same for the whole workgroup
     for (uint32_t i = threadIdx.x; i < 4 * kBins3; i += 256) h[i] = 0;
     const Prefixes d = distinct_prefixes(sel_prefix, m.block);
     __syncthreads();
-    if (t.valid) {
-        const uint32_t n = min(cand_count[t.task], m.cand_cap);
-        const uint32_t* list = cand + m.cand_base + (uint64_t)(t.task - m.first_task) * m.cand_cap;
-        for (uint32_t i = lane; i < n; i += 64) {
-            const uint32_t key = list[i];
-            count_match(h, d, kBins3, key >> kShift2, key & (kBins3 - 1));
-        }
+    const uint32_t n = min(cand_count[blockIdx.x * 4 + wave], m.cand_cap);
+    const uint32_t* list = cand + m.cand_base + ((uint64_t)(blockIdx.x - m.first_task) * 4 + wave) * m.cand_cap;
+    for (uint32_t i = lane; i < n; i += 64) {
+        const uint32_t key = list[i] & 0x7fffffffu;
+        count_match(h, d, kBins3, key >> kShift2, key & (kBins3 - 1));
     }
     __syncthreads();
     uint32_t* out = hist_all + (uint64_t)m.block * 4 * kBins;
@@ -1131,25 +1270,25 @@ __global__ __launch_bounds__(256) void k_tile_finish2(const MatRow* __restrict__
 {
     const MatRow m = mats[blockIdx.x];
     const uint32_t n = m.n_tiles * m.n_segs;
-    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    double a[3] = {0.0, 0.0, 0.0};
     for (uint32_t i = threadIdx.x; i < n; i += 256) {
         const f4 t = *reinterpret_cast<const f4*>(residpart + (uint64_t)(m.first_task + i) * 4);
-        a[0] += (double)t.x; a[1] += (double)t.y; a[2] += (double)t.z; a[3] += (double)t.w;
+        a[0] += (double)t.x; a[1] += (double)t.y; a[2] += (double)t.z;
     }
-    __shared__ double sh[4][256];
+    __shared__ double sh[3][256];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) sh[q][threadIdx.x] = a[q];
+    for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] = a[q];
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + w];
+            for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + w];
         }
         __syncthreads();
     }
     if (threadIdx.x == 0) {
         double* rec = rec_all + (uint64_t)m.block * kRecDoubles;
-        rec[R_FRES] = sh[0][0]; rec[R_FS2] = sh[1][0]; rec[R_CNUM] = sh[2][0]; rec[R_CDEN] = sh[3][0];
+        rec[R_FRES] = sh[0][0]; rec[R_CNUM] = sh[1][0]; rec[R_CDEN] = sh[2][0];
     }
 }
 
@@ -1252,11 +1391,11 @@ struct Plan {
     uint64_t n_prows = 0;         // partial rows of the step kernel = n_chunks * slices
     std::vector<BlockRow> rows;
     std::vector<MatRow> mats;     // matrix blocks (rows*cols == numel), for Eq. 7
-    uint64_t n_tasks = 0, n_quads = 0, n_vec_chunks = 0;
+    uint64_t n_tasks = 0, n_fin = 0, n_vec_chunks = 0;   // workgroups of the tile passes and of k_tile_finish1
     std::vector<Part> parts;      // of blocks of more than kDirectRows partial rows
     uint64_t off_parts = 0;
     uint64_t off_mats = 0, off_rvec = 0, off_cvec = 0, off_rowpart = 0, off_colpart = 0, off_residpart = 0, off_mu = 0,
-             off_psumpart = 0, off_veclist = 0, off_cand = 0, off_candcount = 0, off_scan3 = 0, off_finpart = 0;
+             off_psumpart = 0, off_veclist = 0, off_cand = 0, off_candcount = 0, off_scan3 = 0, off_finpart = 0, off_tilemat = 0, off_finmat = 0;
     uint64_t padded = 0;          // coordinates in m / v / g_prev
     uint64_t off_m = 0, off_v = 0, off_gp = 0, off_partials = 0, off_chunks = 0, off_rows = 0,
              off_rec = 0, off_hist = 0, off_selp = 0, off_selr = 0, off_ostat = 0, total = 0;
@@ -1276,6 +1415,12 @@ struct baoc_profiler {
 };
 
 static uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
+
+// Coordinates of a tile (one workgroup of the tile passes): doubled from the smallest until the layout's matrix blocks
+// need no more than kTileTarget tiles, which still fills the chip's 4 to 5 workgroups per CU twice.  A smaller tile pays
+// for its histograms more often (finalize of 124 M coordinates, tiles of 65,536: 407 us, of 16,384: 470 us), and so does
+// a cap below 262,144 on large layouts (3.5 G coordinates: 6.21 ms, with 131,072 6.33 ms, with 1 M 6.55 ms).
+constexpr uint64_t kTileCoordsMin = 8192, kTileCoordsMax = 262144, kTileTarget = 2048;
 
 static int check_params(const baoc_profile_params* p)
 {
@@ -1356,8 +1501,12 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     P.n_prows = P.n_chunks * P.slices;
     // Finalize walks blocks with a real matrix shape tile-wise and the rest chunk-wise.  A shape with a
     // single row or column is rank one by construction (F = 0 exactly) and stays on the chunk path.
-    P.mats.clear(); P.n_tasks = 0; P.n_quads = 0; P.n_vec_chunks = 0;
-    uint64_t n_r = 0, n_c = 0, n_rowpart = 0, n_colpart = 0, n_cand = 0;
+    P.mats.clear(); P.n_tasks = 0; P.n_fin = 0; P.n_vec_chunks = 0;
+    uint64_t n_r = 0, n_c = 0, n_rowpart = 0, n_colpart = 0, n_cand = 0, n_mat_coords = 0;
+    for (uint32_t i = 0; i < n; ++i)
+        if (blocks[i].rows >= 2 && blocks[i].cols >= 2) n_mat_coords += blocks[i].numel;
+    uint64_t tile_coords = kTileCoordsMin;
+    while (tile_coords < kTileCoordsMax && tile_coords * kTileTarget < n_mat_coords) tile_coords *= 2;
     for (uint32_t i = 0; i < n; ++i) {
         const baoc_block& b = blocks[i];
         if (b.rows < 2 || b.cols < 2) {
@@ -1369,21 +1518,25 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
         MatRow m;
         m.state_start = P.rows[i].state_start; m.grad_start = b.offset;
         m.rows = b.rows; m.cols = b.cols;
-        m.n_tiles = (b.cols + kTileCols - 1) / kTileCols; m.n_segs = (b.rows + kTileRows - 1) / kTileRows;
+        // columns of a tile: 256, 128 or 64, the widest that leaves at most an eighth of the lanes without a column
+        m.wc_log = 2;
+        while (m.wc_log > 0 && align_up(b.cols, 64u << m.wc_log) * 8 > (uint64_t)b.cols * 9) --m.wc_log;
+        const uint64_t round_rows = (4u >> m.wc_log) * kRoundRows, tile_cols = 64u << m.wc_log;
+        m.seg_rows = (uint32_t)align_up(std::max<uint64_t>(1, tile_coords / std::min<uint64_t>(b.cols, tile_cols)), round_rows);
+        m.n_tiles = (uint32_t)((b.cols + tile_cols - 1) / tile_cols); m.n_segs = (uint32_t)(((uint64_t)b.rows + m.seg_rows - 1) / m.seg_rows);
         m.off_r = n_r; m.off_c = n_c; m.off_rowpart = n_rowpart; m.off_colpart = n_colpart;
-        m.first_task = (uint32_t)P.n_tasks; m.first_quad = (uint32_t)P.n_quads; m.block = i;
+        m.first_task = (uint32_t)P.n_tasks; m.first_fin = (uint32_t)P.n_fin; m.block = i;
         n_r += b.rows; n_c += b.cols;
         n_rowpart += (uint64_t)b.rows * m.n_tiles; n_colpart += (uint64_t)m.n_segs * b.cols;
         const uint64_t tasks = (uint64_t)m.n_tiles * m.n_segs;
-        // one candidate list per task, an eighth of a tile long (the keys that share a selected first digit
-        // are a few per cent of a block unless its v is nearly constant; then the list overflows and the
-        // block takes the third scan)
-        const uint64_t tile_elems = (uint64_t)std::min(b.rows, kTileRows) * std::min(b.cols, kTileCols);
-        m.cand_cap = (uint32_t)align_up(std::max<uint64_t>(64, tile_elems / 8), 64);
+        // one candidate list per wavefront; a block's lists have room for an eighth of its coordinates (the keys that
+        // share a selected first digit are a few per cent of a block unless its v is nearly constant; then a list
+        // overflows and the block takes the third scan)
+        m.cand_cap = (uint32_t)align_up((b.numel + 32 * tasks - 1) / (32 * tasks), 4);
         m.cand_base = n_cand;
-        n_cand += tasks * m.cand_cap;
-        P.n_tasks += tasks; P.n_quads += (tasks + 3) / 4;
-        if (P.n_tasks > 0x7fffffffull) return BAOC_ERR_UNSUPPORTED;
+        n_cand += tasks * 4 * m.cand_cap;
+        P.n_tasks += tasks; P.n_fin += ((uint64_t)b.rows + 63) / 64 + ((uint64_t)b.cols + 63) / 64;
+        if (P.n_tasks + P.n_fin > 0x7fffffffull) return BAOC_ERR_UNSUPPORTED;
         P.mats.push_back(m);
     }
     const uint64_t gsz = prm->grad_dtype == BAOC_GRAD_F32 ? 4 : 2;
@@ -1403,16 +1556,18 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     P.off_mu = o;       o = align_up(o + P.mats.size() * 8, 256);
     P.off_rvec = o;     o = align_up(o + n_r * 4, 256);
     P.off_cvec = o;     o = align_up(o + n_c * 4, 256);
-    P.off_rowpart = o;  o = align_up(o + n_rowpart * 4, 256);
-    P.off_colpart = o;  o = align_up(o + n_colpart * 4, 256);
     P.off_residpart = o; o = align_up(o + P.n_tasks * 4 * 4, 256);
     P.off_psumpart = o; o = align_up(o + P.n_tasks * 4, 256);
     P.off_veclist = o;  o = align_up(o + P.n_vec_chunks * 4, 256);
     P.off_parts = o;    o = align_up(o + P.parts.size() * sizeof(Part), 256);
-    P.off_candcount = o; o = align_up(o + P.n_tasks * 4, 256);
+    P.off_candcount = o; o = align_up(o + P.n_tasks * 4 * 4, 256);
     P.off_scan3 = o;    o = align_up(o + (uint64_t)n * 4, 256);
-    P.off_finpart = o;  o = align_up(o + P.mats.size() * kFinSlices * 2 * 8, 256);
-    P.off_cand = o;     o = align_up(o + n_cand * 4, 256);
+    P.off_finpart = o;  o = align_up(o + P.n_fin * 8, 256);
+    P.off_tilemat = o;  o = align_up(o + P.n_tasks * 4, 256);
+    P.off_finmat = o;   o = align_up(o + P.n_fin * 4, 256);
+    // the row and column partial sums of pass 1 are folded before pass 2 writes the candidate lists in their place
+    P.off_cand = o;     P.off_rowpart = o; P.off_colpart = align_up(o + n_rowpart * 4, 256);
+    o = std::max(align_up(o + n_cand * 4, 256), align_up(P.off_colpart + n_colpart * 4, 256));
     P.total = o;
     return BAOC_OK;
 }
@@ -1479,6 +1634,10 @@ static int begin_on(const baoc_block* blocks, uint32_t n_blocks, const baoc_prof
                            reinterpret_cast<const BlockRow*>(h->ws + P.off_rows), n_blocks,
                            reinterpret_cast<Chunk*>(h->ws + P.off_chunks), (uint32_t)P.n_chunks,
                            reinterpret_cast<uint32_t*>(h->ws + P.off_veclist));
+        if (!P.mats.empty())
+            hipLaunchKernelGGL(k_build_tiles, dim3((uint32_t)((P.n_tasks + P.n_fin + 255) / 256)), dim3(256), 0, nullptr,
+                               reinterpret_cast<const MatRow*>(h->ws + P.off_mats), (uint32_t)P.mats.size(), (uint32_t)P.n_tasks, (uint32_t)P.n_fin,
+                               reinterpret_cast<uint32_t*>(h->ws + P.off_tilemat), reinterpret_cast<uint32_t*>(h->ws + P.off_finmat));
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -1576,7 +1735,7 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
 
     const Plan& P = h->plan;
     const uint32_t N = (uint32_t)P.rows.size(), nch = (uint32_t)P.n_chunks;
-    const uint32_t n_vec = (uint32_t)P.n_vec_chunks, n_mats = (uint32_t)P.mats.size(), n_quads = (uint32_t)P.n_quads;
+    const uint32_t n_vec = (uint32_t)P.n_vec_chunks, n_mats = (uint32_t)P.mats.size(), n_tiles = (uint32_t)P.n_tasks;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const float* v = reinterpret_cast<const float*>(h->ws + P.off_v);
     const Chunk* ch = reinterpret_cast<const Chunk*>(h->ws + P.off_chunks);
@@ -1597,6 +1756,8 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
     float* part = reinterpret_cast<float*>(h->ws + P.off_partials);
     double* rec = reinterpret_cast<double*>(h->ws + P.off_rec);
     const float epsf = (float)h->params.eps;
+    // v above which eps stays below a thousandth of sqrt(v) (and v is a normal number)
+    const float eps_low = std::max(std::numeric_limits<float>::min(), (float)(1e6 * h->params.eps * h->params.eps));
     const bool th32 = rp.theta_dtype == BAOC_GRAD_F32;
     const float* th_f = static_cast<const float*>(rp.d_theta_flat);
     const uint16_t* th_h = static_cast<const uint16_t*>(rp.d_theta_flat);
@@ -1606,13 +1767,15 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
     uint32_t* cand = reinterpret_cast<uint32_t*>(h->ws + P.off_cand);
     uint32_t* cand_count = reinterpret_cast<uint32_t*>(h->ws + P.off_candcount);
     uint32_t* scan3 = reinterpret_cast<uint32_t*>(h->ws + P.off_scan3);
+    const uint32_t* tile_mat = reinterpret_cast<const uint32_t*>(h->ws + P.off_tilemat);
+    const uint32_t* fin_mat = reinterpret_cast<const uint32_t*>(h->ws + P.off_finmat);
     const uint32_t* no_list = nullptr;
     const uint32_t* no_flags = nullptr;
 
     // pass 1 over v: first digit everywhere; row/column sums and the sum of p on the way
     hipLaunchKernelGGL(k_fill_u32, dim3(fill_grid), dim3(256), 0, st, hist, hist_words, 0u);
-    if (n_quads)
-        hipLaunchKernelGGL(k_tile_pass1, dim3(n_quads), dim3(256), 0, st, v, mats, n_mats, rowpart, colpart, psumpart, hist, epsf, want_C);
+    if (n_mats)
+        hipLaunchKernelGGL(k_tile_pass1, dim3(n_tiles), dim3(256), 0, st, v, mats, tile_mat, rowpart, colpart, psumpart, hist, epsf, eps_low, want_C);
     if (n_vec) {
         hipLaunchKernelGGL(k_hist<1>, dim3(std::min(n_vec, kHistGrid)), dim3(256), 0, st, v, ch, vec_list, n_vec, selp, hist, rows, no_flags);
         if (want_C) {
@@ -1621,19 +1784,27 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
             hipLaunchKernelGGL(k_reduce_partials, dim3(N), dim3(256), 0, st, part, rows, rec, 1u, (uint32_t)R_PSUM);
         }
     }
-    if (n_quads) {
+    if (n_mats) {
         double* finpart = reinterpret_cast<double*>(h->ws + P.off_finpart);
-        hipLaunchKernelGGL(k_tile_finish1, dim3(n_mats, kFinSlices), dim3(256), 0, st, mats, rowpart, colpart, psumpart, rvec, cvec, finpart);
-        hipLaunchKernelGGL(k_tile_finish1_sum, dim3(n_mats), dim3(64), 0, st, mats, finpart, mu, rec);
+        hipLaunchKernelGGL(k_tile_finish1, dim3((uint32_t)P.n_fin), dim3(256), 0, st, mats, fin_mat, rowpart, colpart, rvec, cvec, finpart);
+        hipLaunchKernelGGL(k_tile_finish1_sum, dim3(n_mats), dim3(256), 0, st, mats, finpart, psumpart, mu, rec);
     }
     hipLaunchKernelGGL(k_pick<1>, dim3(N * 4), dim3(64), 0, st, hist, rows, selp, selr, ostat, scan3);
 
     // pass 2 over v (and theta): second digit; rank-1 residual and distortion on the way; matrix blocks
     // also set aside the keys that carry a selected first digit
     hipLaunchKernelGGL(k_fill_u32, dim3(fill_grid), dim3(256), 0, st, hist, hist_words, 0u);
-    if (n_quads) {
-        if (th32) hipLaunchKernelGGL(k_tile_pass2<BAOC_GRAD_F32>, dim3(n_quads), dim3(256), 0, st, v, th_f, mats, n_mats, rvec, cvec, mu, rec, selp, residpart, hist, cand, cand_count, scan3, epsf, want_F, want_C);
-        else hipLaunchKernelGGL(k_tile_pass2<BAOC_GRAD_BF16>, dim3(n_quads), dim3(256), 0, st, v, th_h, mats, n_mats, rvec, cvec, mu, rec, selp, residpart, hist, cand, cand_count, scan3, epsf, want_F, want_C);
+    if (n_mats) {
+        auto pass2 = [&](auto tt, auto f, auto c, const auto* theta) {
+            hipLaunchKernelGGL((k_tile_pass2<decltype(tt)::value, decltype(f)::value, decltype(c)::value>), dim3(n_tiles), dim3(256), 0, st,
+                               v, theta, rp.theta_numel, mats, tile_mat, rvec, cvec, mu, rec, selp, residpart, hist, cand, cand_count, scan3, epsf, eps_low);
+        };
+        const std::true_type yes; const std::false_type no;
+        const std::integral_constant<int, BAOC_GRAD_F32> t32; const std::integral_constant<int, BAOC_GRAD_BF16> t16;
+        if (!want_C) { if (want_F) pass2(t32, yes, no, th_f); else pass2(t32, no, no, th_f); }
+        else if (th32) { if (want_F) pass2(t32, yes, yes, th_f); else pass2(t32, no, yes, th_f); }
+        else if (want_F) pass2(t16, yes, yes, th_h);
+        else pass2(t16, no, yes, th_h);
         hipLaunchKernelGGL(k_tile_finish2, dim3(n_mats), dim3(256), 0, st, mats, residpart, rec);
     }
     if (n_vec) {
@@ -1649,8 +1820,8 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
     // last digit: on the candidate lists of the matrix blocks; by a third scan of v for the blocks walked
     // chunk-wise and for matrix blocks whose lists overflowed (scan3 flags, skipped a block at a time otherwise)
     hipLaunchKernelGGL(k_fill_u32, dim3(fill_grid), dim3(256), 0, st, hist, hist_words, 0u);
-    if (n_quads)
-        hipLaunchKernelGGL(k_cand_hist3, dim3(n_quads), dim3(256), 0, st, mats, n_mats, cand, cand_count, selp, scan3, hist);
+    if (n_mats)
+        hipLaunchKernelGGL(k_cand_hist3, dim3(n_tiles), dim3(256), 0, st, mats, tile_mat, cand, cand_count, selp, scan3, hist);
     hipLaunchKernelGGL(k_hist<3>, dim3(std::min(nch, kHistGrid)), dim3(256), 0, st, v, ch, no_list, nch, selp, hist, rows, static_cast<const uint32_t*>(scan3));
     hipLaunchKernelGGL(k_pick<3>, dim3(N * 4), dim3(64), 0, st, hist, rows, selp, selr, ostat, scan3);
 
@@ -1674,7 +1845,7 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
         const double eps = h->params.eps;
         double C_raw = rp.C_raw ? rp.C_raw[i] : 0.0, F_raw = rp.F_raw ? rp.F_raw[i] : 0.0;
         if (want_C) C_raw = std::sqrt(rec[R_CNUM]) / (std::sqrt(rec[R_CDEN]) + eps);                  // Eq. 6
-        if (want_F && P.rows[i].vec_first == kNoVec) F_raw = std::sqrt(rec[R_FRES]) / (std::sqrt(rec[R_FS2]) + eps);   // Eq. 7
+        if (want_F && P.rows[i].vec_first == kNoVec) F_raw = std::sqrt(rec[R_FRES]) / (std::sqrt(rec[S_VV]) + eps);   // Eq. 7
         block_metrics(r, eps, rp, C_raw, F_raw, &stats[i]);
     }
     if (out_stats) std::memcpy(out_stats, stats.data(), sizeof(baoc_block_stats) * N);

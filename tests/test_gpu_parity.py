@@ -522,3 +522,20 @@ def test_partial_row_sums_around_the_two_stage_edge(env, rows_per_step):
     w = W.Workload("parts", [W._vec("a", 7), W._vec("b", n), W._vec("c", 300)], 3, "f32", "cycle", **W.K6)
     W.layout(w, 1); W.draw_stream_params(w, 3)
     run_both(env, w, 3, seed=8, chunk_groups=2, groups_per_wave=2, waves_per_workgroup=1)
+
+
+@pytest.mark.parametrize("dtype,pad", [("f32", 1), ("bf16", 1), ("bf16", 64)])
+def test_matrix_tiles_at_their_edges(env, dtype, pad):
+    """Widths around the 64, 128 and 256 columns of a tile, heights around the 16 rows of a wavefront's round and the
+    rows of a tile, rows that start at any alignment, and a last block that ends with the parameter buffer (nothing
+    behind it may be read): statistics, F and C as the oracle has them, once with every digit prefix distinct
+    (blocks of a few coordinates) and once with two."""
+    torch = env["torch"]
+    shapes = [(16, 64), (15, 63), (17, 65), (64, 128), (65, 127), (63, 129), (48, 257), (33, 255), (130, 256), (31, 192), (7, 321),
+              (2, 2), (3, 5), (129, 4), (1025, 62), (513, 66), (16, 576), (5, 2049), (9, 1027)]
+    blocks = [W._mat(f"m{r}x{c}", r, c) for r, c in shapes]
+    w = W.Workload("tiles", blocks, 3, dtype, "cycle", **W.K6)
+    W.layout(w, pad); W.draw_stream_params(w, 12)
+    w.buffer_numel = max(b.offset + b.numel for b in w.blocks)
+    run_both(env, w, 3, seed=9, theta_dtype=torch.float32)
+    run_both(env, w, 2, seed=10, theta_dtype=torch.bfloat16)
