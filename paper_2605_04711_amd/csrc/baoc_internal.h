@@ -30,7 +30,9 @@ enum Sum : int {
 
 // per-block record kept on the device, doubles
 enum Rec : int {
-    R_SPP = 16, R_RHO, R_COS, R_NCOS, R_STEPS, R_PSUM, R_CNUM, R_CDEN, R_FRES, kRecDoubles = 32
+    R_SPP = 16, R_RHO, R_COS, R_NCOS, R_STEPS, R_PSUM, R_CNUM, R_CDEN, R_FRES, R_MU,
+    R_ORDER,                             // four order statistics of v
+    kRecDoubles = 32
 };
 
 // Raw per-block numbers handed from the device path to the host-side metrics.

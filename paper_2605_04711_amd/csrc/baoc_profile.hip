@@ -43,16 +43,13 @@ struct alignas(8) BlockRow {
     uint64_t numel;
     uint32_t first_chunk, n_chunks;
     uint32_t groups_per_chunk;
-    uint32_t vec_first;     // first entry of the block in the list of chunks finalize walks chunk-wise; kNoVec when tiled
     uint32_t first_prow, n_prows;   // the block's partial rows of the step kernel (one per workgroup: chunk x slice)
-    uint64_t rank[4];       // order statistics wanted from v: lo(0.1), lo+1, lo(0.9), lo+1
+    uint32_t pad_;
 };
 
 struct StepConsts {
     float beta_m, beta_v, om_m, om_v, eps_u;
 };
-
-constexpr uint32_t kNoVec = 0xffffffffu;
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
@@ -490,56 +487,104 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
 }
 
 // ---------------------------------------------------------------------------
-// Eq. 4: exact order statistics of v per block by a three-digit radix selection
-// on the bit patterns (v >= 0, so the pattern order is the value order).
-// Digits: bits 30..19, 18..8, 7..0.  Four ranks per block share every pass.
-// Matrix blocks read v twice only: the pass that counts the second digit also
-// writes the few coordinates that carry a selected first digit into a candidate
-// list, and the third digit is counted on that list.
+// Finalize: three passes over the blocks' workgroups
+//   k_final1: first radix digit (Eq. 4); sum of p = 1/(sqrt(v)+eps) (Eq. 6); matrix blocks: mu, row and
+//             column partial sums (Eq. 7), folded to r and c by k_fold_means
+//   k_final2: second digit; ((p/p-bar - 1) theta)^2 and theta^2 (Eq. 6); |S - r c^T / mu|^2 (Eq. 7; |S|^2 is the
+//             step's own sum of v^2)
+//   k_final3: last digit
+// The quantiles are exact order statistics, found by a three-digit radix selection on the bit patterns (v >= 0, so
+// the pattern order is the value order).  Digits: bits 30..19, 18..9, 8..0.  Four ranks per block share every pass.
+// The workgroup of a block that finishes last folds what the others left: the digit of the four ranks, the block's
+// sums.  As launches of their own (fills, picks, partial sums, separate walks over the blocks without a matrix shape: 19
+// launches, now 4) that took longer than the passes themselves: finalize of 25.6 M coordinates 247 -> 151 us, of 60 M
+// of odd shapes 435 -> 277 us, of 32,768 104 -> 52 us.  What crosses workgroups inside a launch is written by
+// device-scope atomics and stores that go through to memory and read the same way, so no cache is written back or
+// invalidated; vmcnt(0) before the arrival counter is all the order they need.
 // ---------------------------------------------------------------------------
 
-// Chunk table from the block rows (one thread per chunk; the owning block by bisection on
-// first_chunk).  A block's groups are split evenly over its chunks, whole groups each.
-__global__ __launch_bounds__(256) void k_build_chunks(const BlockRow* __restrict__ rows, uint32_t n_blocks,
-                                                      Chunk* __restrict__ chunks, uint32_t n_chunks,
-                                                      uint32_t* __restrict__ vec_list)
+template <typename T> __device__ __forceinline__ void st_device(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T> __device__ __forceinline__ T ld_device(const T* p) { return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Called by a whole workgroup: true in the last of the n that share the counter, which is then back at zero.
+__device__ __forceinline__ bool arrive_last(uint32_t* counter, uint32_t n)
 {
-    const uint32_t c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= n_chunks) return;
-    uint32_t lo = 0, hi = n_blocks - 1;
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi + 1) >> 1;
-        if (rows[mid].first_chunk <= c) lo = mid; else hi = mid - 1;
+    __shared__ uint32_t last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this wavefront's stores and atomics have been performed
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        last = n == 1 || __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+        if (last && n > 1) st_device(counter, 0u);
     }
-    const BlockRow r = rows[lo];
-    const uint64_t g0 = (uint64_t)(c - r.first_chunk) * r.groups_per_chunk;
-    const uint64_t groups = (r.numel + kQB - 1) / kQB;
-    const uint64_t g1 = min(groups, g0 + r.groups_per_chunk);
-    Chunk ck;
-    ck.grad_start = r.grad_start + g0 * kQB;
-    ck.state_start = r.state_start + g0 * kQB;
-    ck.count = (uint32_t)(min(r.numel, g1 * kQB) - g0 * kQB);
-    ck.block = lo;
-    chunks[c] = ck;
-    if (r.vec_first != kNoVec) vec_list[r.vec_first + (c - r.first_chunk)] = c;
+    __syncthreads();
+    return last;
 }
 
-__global__ void k_fill_u32(uint32_t* p, uint64_t n, uint32_t val)
-{
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) p[i] = val;
-}
+// How finalize walks a block: tiles of a matrix (rows, cols > 0) or runs of coordinates (rows = cols = 0), a
+// workgroup (task) each.
+struct alignas(8) TileRow {
+    uint64_t state_start;                 // first coordinate of the block in v
+    uint64_t grad_start;                  // the block's offset in the caller's flat buffers (theta)
+    uint64_t numel;
+    uint64_t off_r, off_c;                // into the r / c vectors (floats)
+    uint64_t off_rowpart, off_colpart;    // into the partial-sum arrays (floats): [tile][row] and [seg][column]
+    uint64_t cand_base;                   // the block's first candidate list (words into the candidate buffer)
+    uint32_t rows, cols;
+    uint32_t n_tiles, n_segs;
+    uint32_t seg_len;                     // rows of a tile, or coordinates of a run
+    uint32_t wc_log;                      // a tile is seg_len x (64 << wc_log)
+    uint32_t first_task;
+    uint32_t cand_cap;                    // words per candidate list (one list per wavefront)
+    uint32_t first_fin;                   // first workgroup of the block in k_fold_means
+    uint32_t rank[4];                     // order statistics wanted from v: lo(0.1), lo+1, lo(0.9), lo+1
+    uint32_t pad_;
+};
 
-constexpr uint32_t kBins = 2048;          // words of one rank's histogram; a block owns four of them
-constexpr uint32_t kBits2 = 11, kBits3 = 8;                       // 12 + 11 + 8 bits of the 31-bit key
+constexpr uint32_t kHistWords = 4096;     // histogram words a block owns
+constexpr uint32_t kBits2 = 10, kBits3 = 9;                       // 12 + 10 + 9 bits of the 31-bit key
 constexpr uint32_t kShift1 = kBits2 + kBits3, kShift2 = kBits3;   // key >> kShift1: first digit; key >> kShift2: first two
 constexpr uint32_t kBins1 = 1u << (31 - kShift1), kBins2 = 1u << kBits2, kBins3 = 1u << kBits3;
-static_assert(kBins1 == 2 * kBins && kBins2 == kBins, "the first-digit histogram fills two of a block's four slots");
+static_assert(kBins1 <= kHistWords && 4 * kBins2 <= kHistWords && 4 * kBins3 <= kHistWords, "one first-digit histogram, four of the others");
+
+// Tables that begin() leaves on the device, and the clearing of what must start at zero: chunks from the block rows
+// (the owning block by bisection on first_chunk; a block's groups are split evenly over its chunks, whole groups
+// each) and the owning block of every workgroup of the finalize passes and of k_fold_means.
+__global__ __launch_bounds__(256) void k_build(const BlockRow* __restrict__ rows, const TileRow* __restrict__ tiles, uint32_t n_blocks,
+                                               Chunk* __restrict__ chunks, uint32_t n_chunks, uint32_t* __restrict__ task_block, uint32_t n_tasks,
+                                               uint32_t* __restrict__ fin_block, uint32_t n_fin, uint4* __restrict__ clear, uint64_t n_clear)
+{
+    const uint64_t id0 = (uint64_t)blockIdx.x * 256 + threadIdx.x, stride = (uint64_t)gridDim.x * 256;
+    auto owner = [&](uint32_t id, auto first_of) {
+        uint32_t lo = 0, hi = n_blocks - 1;
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1) >> 1;
+            if (first_of(mid) <= id) lo = mid; else hi = mid - 1;
+        }
+        return lo;
+    };
+    for (uint64_t c = id0; c < n_chunks; c += stride) {
+        const uint32_t b = owner((uint32_t)c, [&](uint32_t i) { return rows[i].first_chunk; });
+        const BlockRow r = rows[b];
+        const uint64_t g0 = (c - r.first_chunk) * r.groups_per_chunk;
+        const uint64_t groups = (r.numel + kQB - 1) / kQB;
+        const uint64_t g1 = min(groups, g0 + r.groups_per_chunk);
+        Chunk ck;
+        ck.grad_start = r.grad_start + g0 * kQB;
+        ck.state_start = r.state_start + g0 * kQB;
+        ck.count = (uint32_t)(min(r.numel, g1 * kQB) - g0 * kQB);
+        ck.block = b;
+        chunks[c] = ck;
+    }
+    for (uint64_t t = id0; t < n_tasks; t += stride) task_block[t] = owner((uint32_t)t, [&](uint32_t i) { return tiles[i].first_task; });
+    for (uint64_t f = id0; f < n_fin; f += stride) fin_block[f] = owner((uint32_t)f, [&](uint32_t i) { return tiles[i].first_fin; });
+    for (uint64_t i = id0; i < n_clear; i += stride) clear[i] = uint4{0u, 0u, 0u, 0u};
+}
 
 // The four ranks of a block usually share their key prefix pairwise (lo and lo+1 of a quantile fall
-// into one bin).  Elements are matched against the distinct prefixes only; slot_of[t] names the LDS
-// histogram that serves rank t, and the flush adds it to every rank that shares it.
+// into one bin).  Elements are matched against the distinct prefixes only; slot_of[t] names the
+// histogram that serves rank t.
 struct Prefixes { uint32_t pre[4]; uint32_t slot_of[4]; uint32_t n; };
-constexpr uint32_t kNoPrefix = 0xffffffffu;             // never equals a key prefix (at most 23 bits)
+constexpr uint32_t kNoPrefix = 0xffffffffu;             // never equals a key prefix (at most 22 bits)
 __device__ __forceinline__ Prefixes distinct_prefixes(const uint32_t* __restrict__ sel_prefix, uint32_t block)
 {
     // fully unrolled with static indices so that everything stays in (scalar) registers
@@ -579,189 +624,108 @@ __device__ __forceinline__ void count_match(uint32_t* h, const Prefixes& d, uint
     if (hit) atomicAdd(&h[at], 1u);
 }
 
-constexpr uint32_t kHistGrid = 2048;     // persistent workgroups of the histogram passes (8 per CU)
-
-// Each workgroup walks a contiguous run of chunks and keeps the histogram of the parameter block it
-// is in in LDS; the LDS copy is added to the block's global histogram (integer atomics) only when
-// the run crosses into another block and at its end.
-template <int PASS>
-__global__ __launch_bounds__(256) void k_hist(
-    const float* __restrict__ v_all, const Chunk* __restrict__ chunks, const uint32_t* __restrict__ list,
-    uint32_t n_chunks, const uint32_t* __restrict__ sel_prefix, uint32_t* __restrict__ hist_all,
-    const BlockRow* __restrict__ rows, const uint32_t* __restrict__ scan3)
+// The digit of one rank, by one wavefront: the bin of its histogram that holds the rank, and the rank inside the bin.
+// Bins i * 64 + lane of the NB are read by `load`.
+template <uint32_t NB, typename L>
+__device__ __forceinline__ uint2 pick_bin(uint32_t rank, uint32_t lane, L load)
 {
-    // list == nullptr: every chunk; otherwise the chunks named by list[0 .. n_chunks).
-    // scan3 (third pass over every chunk only): blocks whose flag is 0 have had their last digit counted on
-    // their candidate lists and are skipped, a whole block per iteration.
-    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-    constexpr int NT = PASS == 1 ? 1 : 4;
-    constexpr uint32_t NB = PASS == 1 ? kBins1 : (PASS == 2 ? kBins2 : kBins3);
-    __shared__ uint32_t h[NT * NB];
-    const uint32_t per = (n_chunks + gridDim.x - 1) / gridDim.x;
-    const uint32_t c0 = blockIdx.x * per, c1 = min(n_chunks, c0 + per);
-    if (c0 >= c1) return;
-    for (uint32_t i = threadIdx.x; i < NT * NB; i += 256) h[i] = 0;
-    uint32_t cur = chunks[list ? list[c0] : c0].block;
-    Prefixes d;
-    d.n = 0;
-    auto load_prefixes = [&]() {
-        if (PASS > 1) d = distinct_prefixes(sel_prefix, cur);
-    };
-    auto flush = [&]() {
-        __syncthreads();
-        uint32_t* out = hist_all + (uint64_t)cur * 4 * kBins;
-        if (PASS == 1) {
-            for (uint32_t i = threadIdx.x; i < NB; i += 256) {
-                const uint32_t c = h[i];
-                if (c) { atomicAdd(&out[i], c); h[i] = 0; }
-            }
-        } else {
-            for (uint32_t i = threadIdx.x; i < NB; i += 256) {
+    uint32_t c[NB / 64];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {                 // static t: slot_of stays in registers
-                    const uint32_t c = h[d.slot_of[t] * NB + i];
-                    if (c) atomicAdd(&out[t * kBins + i], c);
-                }
-            }
-            __syncthreads();
-            for (uint32_t i = threadIdx.x; i < NT * NB; i += 256) h[i] = 0;
+    for (uint32_t i = 0; i < NB / 64; ++i) c[i] = load(i * 64 + lane);
+    uint32_t mine = 0, at = 0;                                // the 64 bins that hold the rank
+    bool found = false;
+#pragma unroll
+    for (uint32_t i = 0; i < NB / 64; ++i) {
+        uint32_t x = c[i];
+        x += dpp_u32<0xB1, 0xf>(0u, x);
+        x += dpp_u32<0x4E, 0xf>(0u, x);
+        x += dpp_u32<0x124, 0xf>(0u, x);
+        x += dpp_u32<0x128, 0xf>(0u, x);
+        x += dpp_u32<0x142, 0xa>(0u, x);
+        x += dpp_u32<0x143, 0xc>(0u, x);
+        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+        if (!found) {
+            if (rank < total || i == NB / 64 - 1) { found = true; mine = c[i]; at = i * 64; }
+            else rank -= total;
         }
-        __syncthreads();
-    };
-    load_prefixes();
-    __syncthreads();
-    for (uint32_t c = c0; c < c1;) {
-        const Chunk ck = chunks[list ? list[c] : c];
-        if (PASS == 3 && scan3 && !scan3[ck.block]) {        // chunk ids of a block are consecutive (list == nullptr here)
-            c = rows[ck.block].first_chunk + rows[ck.block].n_chunks;
-            continue;
-        }
-        if (ck.block != cur) { flush(); cur = ck.block; load_prefixes(); }
-        const uint32_t* bits = reinterpret_cast<const uint32_t*>(v_all + ck.state_start);
-        for (uint32_t e0 = threadIdx.x * 4; e0 < ck.count; e0 += 4096) {
-            u4 w[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q)                              // padded state: e < count is in bounds
-                if (e0 + q * 1024 < ck.count) w[q] = ld_stream<u4>(bits + e0 + q * 1024);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t e = e0 + q * 1024;
-                if (e >= ck.count) break;
-                const uint32_t key[4] = {w[q].x & 0x7fffffffu, w[q].y & 0x7fffffffu, w[q].z & 0x7fffffffu, w[q].w & 0x7fffffffu};
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (e + j >= ck.count) break;
-                    if (PASS == 1) {
-                        atomicAdd(&h[key[j] >> kShift1], 1u);
-                    } else {
-                        const uint32_t hi = PASS == 2 ? key[j] >> kShift1 : key[j] >> kShift2;
-                        const uint32_t bin = PASS == 2 ? (key[j] >> kShift2) & (kBins2 - 1) : key[j] & (kBins3 - 1);
-                        count_match(h, d, NB, hi, bin);
-                    }
-                }
-            }
-        }
-        ++c;
     }
-    flush();
-}
-
-// One wavefront per (block, rank): every lane sums a run of consecutive bins, a wavefront scan
-// finds the lane whose run holds the rank, and that lane walks its run.  The key prefix grows by
-// the digit found and the rank is made relative to that bin.  Counts fit 32 bits (numel < 2^32).
-template <int PASS>
-__global__ __launch_bounds__(64) void k_pick(const uint32_t* __restrict__ hist_all, const BlockRow* __restrict__ rows,
-                                             uint32_t* __restrict__ sel_prefix, uint32_t* __restrict__ sel_rank,
-                                             float* __restrict__ order_stat, uint32_t* __restrict__ scan3)
-{
-    constexpr uint32_t NB = PASS == 1 ? kBins1 : (PASS == 2 ? kBins2 : kBins3), PER = NB / 64;
-    const uint32_t id = blockIdx.x, b = id >> 2, t = id & 3, lane = threadIdx.x;
-    // the first-digit histogram is shared by the four ranks and fills the block's first two slots
-    const uint32_t* h = hist_all + ((uint64_t)b * 4 + (PASS == 1 ? 0 : t)) * kBins + lane * PER;
-    const uint32_t r = PASS == 1 ? (uint32_t)rows[b].rank[t] : sel_rank[id];
-    // Blocks walked chunk-wise have their last digit counted by a third scan; matrix blocks only if
-    // a candidate list overflows (set by the second tile pass).
-    if (PASS == 1 && t == 0 && lane == 0) scan3[b] = rows[b].vec_first != kNoVec;
-    uint32_t cnt[PER], mine = 0;
-#pragma unroll
-    for (uint32_t i = 0; i < PER; ++i) { cnt[i] = h[i]; mine += cnt[i]; }
     uint32_t incl = mine;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
         const uint32_t o = __shfl_up(incl, d);
         if ((int)lane >= d) incl += o;
     }
-    const uint32_t excl = incl - mine;
-    const uint64_t holders = __ballot(r >= excl && r < incl);
+    const uint64_t holders = __ballot(rank >= incl - mine && rank < incl);
     const uint32_t owner = holders ? (uint32_t)__builtin_ctzll(holders) : 63u;
-    if (lane == owner) {
-        uint32_t rr = r - excl, bin = PER - 1;
-        bool found = false;
-#pragma unroll
-        for (uint32_t i = 0; i < PER; ++i) {
-            if (!found) {
-                if (rr < cnt[i] || i == PER - 1) { bin = i; found = true; }
-                else rr -= cnt[i];
-            }
-        }
-        bin += lane * PER;
-        const uint32_t prefix = PASS == 1 ? bin : ((sel_prefix[id] << (PASS == 2 ? kBits2 : kBits3)) | bin);
-        sel_prefix[id] = prefix;
-        sel_rank[id] = rr;
-        if (PASS == 3) order_stat[id] = __builtin_bit_cast(float, prefix);
+    return uint2{at + owner, rank - (uint32_t)__builtin_amdgcn_readlane((int)(incl - mine), owner)};
+}
+
+struct Selection { uint32_t *hist, *prefix, *rank; };     // per block: histogram words; four key prefixes; four ranks within them
+
+// The PASS-th digit of a block's four ranks, a wavefront each, by the workgroup that arrived last.  A block of a
+// single workgroup never left LDS (h); others added theirs to the block's global histogram, which is cleared again.
+// Counts fit 32 bits (numel < 2^32).
+template <int PASS>
+__device__ __forceinline__ void pick_digit(const Selection& sel, const TileRow& row, uint32_t block, bool single, const uint32_t* h,
+                                           uint32_t lane, uint32_t wave, double* rec)
+{
+    constexpr uint32_t NB = PASS == 1 ? kBins1 : (PASS == 2 ? kBins2 : kBins3);
+    const uint32_t id = block * 4 + wave;
+    uint32_t* hist = sel.hist + (uint64_t)block * kHistWords;
+    uint32_t slot = 0, rank = row.rank[wave], prefix = 0;
+    if (PASS > 1) {
+        const Prefixes d = distinct_prefixes(sel.prefix, block);
+        slot = wave == 0 ? d.slot_of[0] : (wave == 1 ? d.slot_of[1] : (wave == 2 ? d.slot_of[2] : d.slot_of[3]));
+        rank = sel.rank[id]; prefix = sel.prefix[id];
     }
+    const uint2 p = single ? pick_bin<NB>(rank, lane, [&](uint32_t i) { return h[slot * NB + i]; })
+                           : pick_bin<NB>(rank, lane, [&](uint32_t i) { return ld_device(hist + slot * NB + i); });
+    __syncthreads();                                          // all four have read the prefixes and the histogram
+    prefix = PASS == 1 ? p.x : ((prefix << (PASS == 2 ? kBits2 : kBits3)) | p.x);
+    if (lane == 0) {
+        if (PASS < 3) { sel.prefix[id] = prefix; sel.rank[id] = p.y; }
+        else rec[R_ORDER + wave] = (double)__builtin_bit_cast(float, prefix);
+    }
+    if (!single)
+        for (uint32_t i = threadIdx.x; i < (PASS == 1 ? NB : 4 * NB); i += 256) hist[i] = 0;
+}
+
+// Adds a workgroup's LDS histogram to the block's.
+__device__ __forceinline__ void flush_hist(uint32_t* hist, const uint32_t* h, uint32_t n)
+{
+    for (uint32_t i = threadIdx.x; i < n; i += 256)
+        if (h[i]) atomicAdd(&hist[i], h[i]);
+}
+
+// Sum over the workgroup in a fixed order; every thread calls it, thread 0 has the result.
+__device__ __forceinline__ double group_sum(double x, uint32_t lane, uint32_t wave, double* sh)
+{
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d);
+    __syncthreads();
+    if (lane == 0) sh[wave] = x;
+    __syncthreads();
+    return (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
 // ---------------------------------------------------------------------------
-// Finalize over matrix blocks, tiled.  Two passes over v (viewed as rows x cols) serve three consumers:
-//   pass 1: row / column partial sums (Eq. 7), sum of p = 1/(sqrt(v)+eps) (Eq. 6), first
-//           radix digit histogram (Eq. 4)
-//   pass 2: |S - r c^T / mu|^2 (Eq. 7; |S|^2 is the step's own sum of v^2), ((p/p-bar - 1) theta)^2 and
-//           theta^2 (Eq. 6), and the keys that carry a selected first digit appended to a candidate list per
-//           wavefront; the second digit is counted on the list at the end, the last one by k_cand_hist3
-// A workgroup takes a tile of 64 * wc columns and seg_rows rows; its four wavefronts stand wc across the columns
+// Matrix blocks (v viewed as rows x cols), tiled.
+// A workgroup takes a tile of 64 * wc columns and seg_len rows; its four wavefronts stand wc across the columns
 // and 4 / wc down the rows.  A wavefront reads 4 rows x 64 columns (256 bytes a row) with one load, a lane 4
 // consecutive columns of a row, at any alignment: a row sum then takes four exchange levels for four rows at
 // once, and narrow or odd-sized matrices keep their lanes busy.  Loads are issued one round of kQuads * 4 rows
 // ahead of their use; rounds with a missing row or column load for themselves.
+// In the second pass the keys that carry a selected first digit (a few per cent) are appended to a candidate list
+// per wavefront; the second digit is counted on the list at the end, the last digit by k_final3.
 // Large layouts are bound by HBM with the vector ALUs close behind, small ones by the number of wavefronts in flight.
 // Measured (pass 1 / pass 2, us; before: one wavefront per 256 x 256 tile, scalar loads where a row is not a
 // multiple of 4, keys stored as they were found): 25.6 M coordinates of convolutions 189 / 416 -> 26 / 53,
 // 124 M 136 / 323 -> 93 / 159, 60 M of odd shapes 254 / 535 -> 51 / 104, 3.5 G 2492 / 3887 -> 2353 / 3640.
-// Blocks without a matrix shape are walked chunk-wise by k_hist / k_distortion instead.
 // ---------------------------------------------------------------------------
 
 constexpr uint32_t kQuads = 4;                        // loads of 4 rows a wavefront has in flight
 constexpr uint32_t kRoundRows = 4 * kQuads;
 constexpr uint32_t kSubRounds = 256 / kRoundRows;     // rounds between two row-sum exchanges (256 rows per wavefront)
-
-struct alignas(8) MatRow {
-    uint64_t state_start;                 // first coordinate of the block in v
-    uint64_t grad_start;                  // the block's offset in the caller's flat buffers (theta)
-    uint64_t off_r, off_c;                // into the r / c vectors (floats)
-    uint64_t off_rowpart, off_colpart;    // into the partial-sum arrays (floats): [tile][row] and [seg][column]
-    uint64_t cand_base;                   // the block's first candidate list (words into the candidate buffer)
-    uint32_t rows, cols, n_tiles, n_segs;
-    uint32_t seg_rows, wc_log;            // tile: seg_rows x (64 << wc_log)
-    uint32_t first_task, block;           // first workgroup of the block in the tile passes
-    uint32_t cand_cap;                    // words per candidate list (one list per wavefront)
-    uint32_t first_fin;                   // first workgroup of the block in k_tile_finish1
-};
-
-// Owning matrix block of every workgroup of the tile passes and of k_tile_finish1, looked up there with one load.
-__global__ __launch_bounds__(256) void k_build_tiles(const MatRow* __restrict__ mats, uint32_t n_mats, uint32_t n_tasks, uint32_t n_fin,
-                                                     uint32_t* __restrict__ tile_mat, uint32_t* __restrict__ fin_mat)
-{
-    uint32_t id = blockIdx.x * 256 + threadIdx.x;
-    const bool fin = id >= n_tasks;
-    if (fin) { id -= n_tasks; if (id >= n_fin) return; }
-    uint32_t lo = 0, hi = n_mats - 1;
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi + 1) >> 1;
-        if ((fin ? mats[mid].first_fin : mats[mid].first_task) <= id) lo = mid; else hi = mid - 1;
-    }
-    (fin ? fin_mat : tile_mat)[id] = lo;
-}
 
 __device__ __forceinline__ uint32_t scalar_u32(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 __device__ __forceinline__ uint32_t scalar_wave_index() { return scalar_u32(threadIdx.x >> 6); }
@@ -781,14 +745,14 @@ struct TilePart {
     uint32_t base;                        // the lane's first column (clamped to an existing one)
 };
 
-__device__ __forceinline__ TilePart tile_part(const MatRow& m, uint32_t wg, uint32_t lane, uint32_t wave)
+__device__ __forceinline__ TilePart tile_part(const TileRow& m, uint32_t wg, uint32_t lane, uint32_t wave)
 {
     TilePart t;
     const uint32_t local = wg - m.first_task;
     t.seg = local / m.n_tiles; t.tile = local - t.seg * m.n_tiles;
     t.wr = 4u >> m.wc_log;
     t.wcol = wave & ((1u << m.wc_log) - 1u); t.wrow = wave >> m.wc_log;
-    t.row0 = t.seg * m.seg_rows; t.row1 = min(m.rows, t.row0 + m.seg_rows);
+    t.row0 = t.seg * m.seg_len; t.row1 = min(m.rows, t.row0 + m.seg_len);
     const uint32_t col0 = ((t.tile << m.wc_log) + t.wcol) * 64;
     t.col = col0 + 4 * (lane & 15u); t.lrow = lane >> 4;
     t.n_ok = t.col < m.cols ? min(4u, m.cols - t.col) : 0u;
@@ -844,17 +808,12 @@ __device__ __forceinline__ void load_edge(typename GradIO<TT>::vec4 (&x)[kQuads]
 
 constexpr uint64_t kAnywhere = ~0ull;                 // v may be read past its end: g_prev follows it in the workspace
 
-__global__ __launch_bounds__(256) void k_tile_pass1(
-    const float* __restrict__ v_all, const MatRow* __restrict__ mats, const uint32_t* __restrict__ tile_mat,
-    float* __restrict__ rowpart, float* __restrict__ colpart, float* __restrict__ psumpart,
-    uint32_t* __restrict__ hist_all, float eps, float eps_low, bool want_p)
+// First pass over a tile.  Returns the lane's sum of p and leaves the thread's part of the sum of v in `total`; counts
+// into h (cleared here).
+__device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, const TileRow& m, uint32_t lane, uint32_t wave,
+                                             float* __restrict__ rowpart, float* __restrict__ colpart, uint32_t* h, float* rowsum, double* colsum,
+                                             float eps, float eps_low, bool want_p, double& total)
 {
-    __shared__ uint32_t h[kBins1];
-    __shared__ float rowsum[4 * 256];                     // [wavefront][its rows of a sub-segment]
-    __shared__ double colsum[4 * 64];
-    __shared__ float psum_w[4];
-    const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index();
-    const MatRow& m = mats[tile_mat[blockIdx.x]];
     const TilePart t = tile_part(m, blockIdx.x, lane, wave);
     const float* src = v_all + m.state_start;
     const uint32_t cols = scalar_u32(m.cols);
@@ -947,6 +906,7 @@ __global__ __launch_bounds__(256) void k_tile_pass1(
                 float sum = in[0];
                 for (uint32_t w = 1; w < n_wc; ++w) sum += in[w * 256];
                 rowpart[m.off_rowpart + (uint64_t)t.tile * m.rows + r0 + rs] = sum;
+                total += (double)sum;
             }
             __syncthreads();
         }
@@ -957,8 +917,6 @@ __global__ __launch_bounds__(256) void k_tile_pass1(
         cs[k] += __shfl_xor(cs[k], 32);
         if (lane < 16) colsum[wave * 64 + 4 * lane + k] = cs[k];
     }
-    const float ptile = wave_sum((float)psum);
-    if (lane == 0) psum_w[wave] = ptile;
     __syncthreads();
     const uint32_t tile_cols = 64u << m.wc_log, col = t.tile * tile_cols + threadIdx.x;
     if (threadIdx.x < tile_cols && col < m.cols) {
@@ -966,21 +924,113 @@ __global__ __launch_bounds__(256) void k_tile_pass1(
         for (uint32_t w = 0; w < t.wr; ++w) a += colsum[w * tile_cols + threadIdx.x];
         colpart[m.off_colpart + (uint64_t)t.seg * m.cols + col] = (float)a;
     }
-    if (threadIdx.x == 0) psumpart[blockIdx.x] = (psum_w[0] + psum_w[1]) + (psum_w[2] + psum_w[3]);
-    uint32_t* out = hist_all + (uint64_t)m.block * 4 * kBins;
-    for (uint32_t i = threadIdx.x; i < kBins1; i += 256)
-        if (h[i]) atomicAdd(&out[i], h[i]);
+    return psum;
 }
 
-// r_i, c_j (fp32 for pass 2) and the sums behind mu from the pass-1 partial sums.  A workgroup takes 64 rows or 64
-// columns of a block, summed over the tiles or segments by 4 wavefronts in parallel: a 50257 x 768 block has
-// hundreds of segments, whose loads would otherwise wait for each other.
-__global__ __launch_bounds__(256) void k_tile_finish1(const MatRow* __restrict__ mats, const uint32_t* __restrict__ fin_mat,
-                                                      const float* __restrict__ rowpart, const float* __restrict__ colpart,
-                                                      float* __restrict__ rvec, float* __restrict__ cvec, double* __restrict__ finpart)
+// A run of a block without a matrix shape: 16 coordinates per thread and round.  Calls f(v, theta, how many of the
+// 16 exist) with the loads of a round issued together.  Runs start on a multiple of 4 coordinates, so a quad of v is
+// aligned and inside the padded state; theta is read at any alignment and not past the block's last coordinate.
+template <int TT, bool THETA, typename Fn>
+__device__ __forceinline__ void walk_run(const float* __restrict__ v_all, const typename GradIO<TT>::elem* __restrict__ theta, const TileRow& m, Fn f)
+{
+    typedef GradIO<TT> IO;
+    const uint64_t e0 = (uint64_t)(blockIdx.x - m.first_task) * m.seg_len;
+    const uint32_t n = (uint32_t)min((uint64_t)m.seg_len, m.numel - e0);
+    const float* src = v_all + m.state_start + e0;
+    const typename IO::elem* tsrc = theta + (m.grad_start + e0);
+    for (uint32_t at = threadIdx.x * 4; at < n; at += 4096) {
+        f4 x[4];
+        typename IO::vec4 th[4];
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) { x[q] = f4{0.f, 0.f, 0.f, 0.f}; th[q] = typename IO::vec4{}; }
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q)
+            if (at + q * 1024 < n) x[q] = ld_stream<f4>(src + at + q * 1024);
+        if (THETA) {
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) {
+                const uint32_t e = at + q * 1024;
+                if (e + 4 <= n) th[q] = IO::loadv_any(tsrc + e);
+                else if (e < n) {
+                    typename IO::elem part[4];
+#pragma unroll
+                    for (uint32_t k = 0; k < 4; ++k) part[k] = e + k < n ? tsrc[e + k] : typename IO::elem(0);
+                    th[q] = __builtin_bit_cast(typename IO::vec4, part);
+                }
+            }
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+            const uint32_t e = at + q * 1024;
+            if (e >= n) break;
+            const float xv[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+            float tv[4];
+            IO::unpack(th[q], tv);
+            f(xv, tv, min(4u, n - e));
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void k_final1(
+    const float* __restrict__ v_all, const TileRow* __restrict__ tiles, const uint32_t* __restrict__ task_block,
+    float* __restrict__ rowpart, float* __restrict__ colpart, double* __restrict__ taskpart,
+    Selection sel, uint32_t* __restrict__ arrived, uint32_t* __restrict__ scan3, double* __restrict__ rec_all, float eps, float eps_low, bool want_p)
+{
+    __shared__ uint32_t h[kBins1];
+    __shared__ float rowsum[4 * 256];                     // [wavefront][its rows of a sub-segment]
+    __shared__ double colsum[4 * 64], sums[8];
+    const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index(), block = task_block[blockIdx.x];
+    const TileRow& m = tiles[block];
+    double psum = 0.0, total = 0.0;
+    if (m.rows) {
+        psum = tile_pass1(v_all, m, lane, wave, rowpart, colpart, h, rowsum, colsum, eps, eps_low, want_p, total);
+    } else {
+        for (uint32_t i = threadIdx.x; i < kBins1; i += 256) h[i] = 0;
+        __syncthreads();
+        walk_run<BAOC_GRAD_F32, false>(v_all, nullptr, m, [&](const float x[4], const float*, uint32_t n) {
+            float prow = 0.f;
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k)
+                if (k < n) {
+                    atomicAdd(&h[(__builtin_bit_cast(uint32_t, x[k]) >> kShift1) & (kBins1 - 1)], 1u);
+                    if (want_p) prow += preconditioner(x[k], eps);
+                }
+            psum += (double)prow;
+        });
+    }
+    total = group_sum(total, lane, wave, sums);
+    psum = group_sum(psum, lane, wave, sums + 4);             // ends with every wavefront's counts in h
+    const uint32_t n_tasks = m.n_tiles * m.n_segs;
+    const bool single = n_tasks == 1;
+    if (threadIdx.x == 0) { st_device(&taskpart[2 * blockIdx.x], total); st_device(&taskpart[2 * blockIdx.x + 1], psum); }
+    if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, kBins1);
+    if (!arrive_last(arrived + block, n_tasks)) return;
+    double* rec = rec_all + (uint64_t)block * kRecDoubles;
+    pick_digit<1>(sel, m, block, single, h, lane, wave, rec);
+    double a = 0.0, p = 0.0;
+    for (uint32_t i = threadIdx.x; i < n_tasks; i += 256) {
+        a += ld_device(&taskpart[2 * (m.first_task + i)]);
+        p += ld_device(&taskpart[2 * (m.first_task + i) + 1]);
+    }
+    a = group_sum(a, lane, wave, sums);
+    p = group_sum(p, lane, wave, sums + 4);
+    if (threadIdx.x == 0) {
+        // mu is the mean of the row means to the last bit of what they are made of: the tiles' row sums, added in fp64
+        if (m.rows) rec[R_MU] = a / ((double)m.rows * (double)m.cols);
+        rec[R_PSUM] = p;
+        scan3[block] = m.rows == 0;                       // raised by k_final2 where a candidate list overflows
+    }
+}
+
+// r_i and c_j (fp32 for the second pass) from the partial sums of the first.  A workgroup takes 64 rows or 64 columns of
+// a block, summed over the tiles or segments by 4 wavefronts in parallel: a 50257 x 768 block has hundreds of
+// segments, whose loads would otherwise wait for each other (62 -> 6 us on that layout).
+__global__ __launch_bounds__(256) void k_fold_means(const TileRow* __restrict__ tiles, const uint32_t* __restrict__ fin_block,
+                                                    const float* __restrict__ rowpart, const float* __restrict__ colpart,
+                                                    float* __restrict__ rvec, float* __restrict__ cvec)
 {
     __shared__ double sh[4][64];
-    const MatRow& m = mats[fin_mat[blockIdx.x]];
+    const TileRow& m = tiles[fin_block[blockIdx.x]];
     const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index();
     const uint32_t local = blockIdx.x - m.first_fin, row_wgs = (m.rows + 63) / 64;
     const bool is_row = local < row_wgs;
@@ -994,378 +1044,276 @@ __global__ __launch_bounds__(256) void k_tile_finish1(const MatRow* __restrict__
     }
     sh[wave][lane] = s;
     __syncthreads();
-    if (wave != 0) return;
+    if (wave != 0 || at >= len) return;
     s = (sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]);
-    if (!is_row) {
-        if (at < len) cvec[m.off_c + at] = (float)(s / (double)m.rows);
-        return;
-    }
-    double r = s / (double)m.cols;                        // 0 for lanes past the rows
-    if (at < len) rvec[m.off_r + at] = (float)r;
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) r += __shfl_xor(r, d);
-    if (lane == 0) finpart[blockIdx.x] = r;
+    if (is_row) rvec[m.off_r + at] = (float)(s / (double)m.cols);
+    else cvec[m.off_c + at] = (float)(s / (double)m.rows);
 }
 
-// mu (fp64) and the block's sum of p, added in a fixed order.
-__global__ __launch_bounds__(256) void k_tile_finish1_sum(const MatRow* __restrict__ mats, const double* __restrict__ finpart,
-                                                          const float* __restrict__ psumpart, double* __restrict__ mu_out, double* __restrict__ rec_all)
-{
-    __shared__ double sh[2][256];
-    const MatRow& m = mats[blockIdx.x];
-    double a = 0.0, p = 0.0;
-    for (uint32_t i = threadIdx.x; i < (m.rows + 63) / 64; i += 256) a += finpart[m.first_fin + i];
-    for (uint32_t i = threadIdx.x; i < m.n_tiles * m.n_segs; i += 256) p += (double)psumpart[m.first_task + i];
-    sh[0][threadIdx.x] = a; sh[1][threadIdx.x] = p;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) { sh[0][threadIdx.x] += sh[0][threadIdx.x + w]; sh[1][threadIdx.x] += sh[1][threadIdx.x + w]; }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        mu_out[blockIdx.x] = sh[0][0] / (double)m.rows;
-        rec_all[(uint64_t)m.block * kRecDoubles + R_PSUM] = sh[1][0];
-    }
-}
-
-constexpr uint32_t kStage = 2 * kBins2 / 4;            // words of h per wavefront while the lists are written
+constexpr uint32_t kStage = 4 * kBins2 / 4;            // words of h per wavefront while the lists are written
 
 // F, C: Eq. 7 and Eq. 6 are wanted.
 template <int TT, bool F, bool C>
-__global__ __launch_bounds__(256) void k_tile_pass2(
+__global__ __launch_bounds__(256) void k_final2(
     const float* __restrict__ v_all, const typename GradIO<TT>::elem* __restrict__ theta, uint64_t theta_numel,
-    const MatRow* __restrict__ mats, const uint32_t* __restrict__ tile_mat,
-    const float* __restrict__ rvec, const float* __restrict__ cvec, const double* __restrict__ mu_all,
-    const double* __restrict__ rec_all, const uint32_t* __restrict__ sel_prefix,
-    float* __restrict__ residpart, uint32_t* __restrict__ hist_all,
-    uint32_t* cand, uint32_t* __restrict__ cand_count, uint32_t* __restrict__ scan3,
-    float eps, float eps_low)
+    const TileRow* __restrict__ tiles, const uint32_t* __restrict__ task_block, const float* __restrict__ rvec, const float* __restrict__ cvec,
+    float* __restrict__ residpart, Selection sel, uint32_t* __restrict__ arrived, uint32_t* cand, uint32_t* __restrict__ cand_count,
+    uint32_t* __restrict__ scan3, double* __restrict__ rec_all, float eps, float eps_low)
 {
     typedef GradIO<TT> IO;
     typedef typename IO::vec4 TV;
-    // LDS histograms for the first two distinct prefixes (lo and lo+1 of a quantile almost always share
-    // theirs); a third or fourth distinct prefix is rare and counts straight into global memory.
-    constexpr uint32_t NSLOT = 2;
-    __shared__ uint32_t h[NSLOT * kBins2];
+    __shared__ uint32_t h[4 * kBins2];                    // a histogram per distinct prefix
     __shared__ float red[4][4];
-    const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index();
-    const uint32_t mat = tile_mat[blockIdx.x];
-    const MatRow& m = mats[mat];
-    const TilePart t = tile_part(m, blockIdx.x, lane, wave);
-    const float* src = v_all + m.state_start;
-    const typename IO::elem* tsrc = theta + m.grad_start;
-    const uint64_t tleft = theta_numel - m.grad_start;
-    const float* rr = rvec + m.off_r;
-    const uint32_t cols = scalar_u32(m.cols), cap = scalar_u32(m.cand_cap);
-    f4 nx[kQuads]; TV nt[kQuads]; float nr[kQuads];
-#pragma unroll
-    for (uint32_t q = 0; q < kQuads; ++q) { nx[q] = f4{0.f, 0.f, 0.f, 0.f}; nt[q] = TV{}; nr[q] = 0.f; }
-    auto issue = [&](uint32_t i) {
-        load_full<BAOC_GRAD_F32>(nx, src, t, cols, i);
-        if (C) load_full<TT>(nt, tsrc, t, cols, i);
-        const float* p = rr + round_row(t, i);
-#pragma unroll
-        for (uint32_t q = 0; q < kQuads; ++q) nr[q] = (p + 4 * q)[t.lrow];
-    };
-    if (t.full) issue(0);
-    const Prefixes d = distinct_prefixes(sel_prefix, m.block);
-    uint32_t* hist_out = hist_all + (uint64_t)m.block * 4 * kBins;
-    const double mu = mu_all[mat];
-    // c_j / mu is formed in fp64 (mu may lie below the fp32 normal range); S~ = 0 when mu = 0
-    float inv_pbar = 0.f, cm[4];
-    if (C) inv_pbar = (float)((double)((uint64_t)m.rows * m.cols) / rec_all[(uint64_t)m.block * kRecDoubles + R_PSUM]);
-#pragma unroll
-    for (uint32_t k = 0; k < 4; ++k)
-        cm[k] = (F && k < t.n_ok && mu != 0.0) ? (float)((double)cvec[m.off_c + t.col + k] / mu) : 0.f;
-    uint32_t* list = cand + m.cand_base + ((uint64_t)(blockIdx.x - m.first_task) * 4 + wave) * cap;
-    uint32_t n_cand = 0;                                      // uniform over the wavefront; may grow past the list
+    __shared__ double sums[4];
+    const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index(), block = task_block[blockIdx.x];
+    const TileRow& m = tiles[block];
+    const Prefixes d = distinct_prefixes(sel.prefix, block);
+    const double* rec_in = rec_all + (uint64_t)block * kRecDoubles;
+    float inv_pbar = 0.f;
+    if (C) inv_pbar = (float)((double)m.numel / rec_in[R_PSUM]);
+    auto count2 = [&](uint32_t bits) { count_match(h, d, kBins2, (bits >> kShift1) & (kBins1 - 1), (bits >> kShift2) & (kBins2 - 1)); };
     float res = 0.f, cn = 0.f, cd = 0.f;
-    // Matching keys gather in the wavefront's quarter of h (the histogram is not needed before the end) and leave
-    // 64 at a time: stores of a few keys each would be waited for together with the next round's loads.
-    uint32_t* stage = h + wave * kStage;
-    uint32_t n_stage = 0;
-    auto append = [&](bool hit, uint64_t hits, uint32_t bits) {
-        const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u));
-        if (hit) stage[n_stage + at] = bits;
-        n_stage += (uint32_t)__builtin_popcountll(hits);
-    };
-    // Whole sets of 64 go to the list, as far as it has room; what is left moves to the front.
-    auto flush = [&](bool all) {
-        const uint32_t n = all ? n_stage : n_stage & ~63u;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // lanes read what other lanes staged
-        for (uint32_t i = lane; i < n; i += 64)
-            if (n_cand + i < cap) list[n_cand + i] = stage[i];
-        n_cand += n; n_stage -= n;
-        const uint32_t rest = lane < n_stage ? stage[n + lane] : 0u;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (lane < n_stage) stage[lane] = rest;
-    };
-    static_assert(kStage >= 63 + 64 * 4 * 2, "two quads of keys and what the last flush left");
-    const uint32_t p0 = d.pre[0], p1 = d.pre[1];
-    for (uint32_t i = 0; i < t.full; ++i) {
-        float x[kQuads][4], th[kQuads][4], ri[kQuads];
+    if (m.rows) {
+        const TilePart t = tile_part(m, blockIdx.x, lane, wave);
+        const float* src = v_all + m.state_start;
+        const typename IO::elem* tsrc = theta + m.grad_start;
+        const uint64_t tleft = theta_numel - m.grad_start;
+        const float* rr = rvec + m.off_r;
+        const uint32_t cols = scalar_u32(m.cols), cap = scalar_u32(m.cand_cap);
+        f4 nx[kQuads]; TV nt[kQuads]; float nr[kQuads];
 #pragma unroll
-        for (uint32_t q = 0; q < kQuads; ++q) {
-            x[q][0] = nx[q].x; x[q][1] = nx[q].y; x[q][2] = nx[q].z; x[q][3] = nx[q].w;
-            IO::unpack(nt[q], th[q]);
-            ri[q] = nr[q];
-        }
-        if (i + 1 < t.full) issue(i + 1);
-        if (d.n <= 2) {
+        for (uint32_t q = 0; q < kQuads; ++q) { nx[q] = f4{0.f, 0.f, 0.f, 0.f}; nt[q] = TV{}; nr[q] = 0.f; }
+        auto issue = [&](uint32_t i) {
+            load_full<BAOC_GRAD_F32>(nx, src, t, cols, i);
+            if (C) load_full<TT>(nt, tsrc, t, cols, i);
+            if (F) {
+                const float* p = rr + round_row(t, i);
+#pragma unroll
+                for (uint32_t q = 0; q < kQuads; ++q) nr[q] = (p + 4 * q)[t.lrow];
+            }
+        };
+        if (t.full) issue(0);
+        const double mu = F ? rec_in[R_MU] : 0.0;
+        // c_j / mu is formed in fp64 (mu may lie below the fp32 normal range); S~ = 0 when mu = 0
+        float cm[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+            cm[k] = (F && k < t.n_ok && mu != 0.0) ? (float)((double)cvec[m.off_c + t.col + k] / mu) : 0.f;
+        uint32_t* list = cand + m.cand_base + ((uint64_t)(blockIdx.x - m.first_task) * 4 + wave) * cap;
+        uint32_t n_cand = 0;                                      // uniform over the wavefront; may grow past the list
+        // Matching keys gather in the wavefront's quarter of h (the histogram is not needed before the end) and leave
+        // 64 at a time: stores of a few keys each would be waited for together with the next round's loads.
+        uint32_t* stage = h + wave * kStage;
+        uint32_t n_stage = 0;
+        auto append = [&](bool hit, uint64_t hits, uint32_t bits) {
+            const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u));
+            if (hit) stage[n_stage + at] = bits;
+            n_stage += (uint32_t)__builtin_popcountll(hits);
+        };
+        // Whole sets of 64 go to the list, as far as it has room; what is left moves to the front.
+        auto flush = [&](bool all) {
+            const uint32_t n = all ? n_stage : n_stage & ~63u;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // lanes read what other lanes staged
+            for (uint32_t i = lane; i < n; i += 64)
+                if (n_cand + i < cap) list[n_cand + i] = stage[i];
+            n_cand += n; n_stage -= n;
+            const uint32_t rest = lane < n_stage ? stage[n + lane] : 0u;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (lane < n_stage) stage[lane] = rest;
+        };
+        static_assert(kStage >= 63 + 64 * 4 * 2, "two quads of keys and what the last flush left");
+        const uint32_t p0 = d.pre[0], p1 = d.pre[1];
+        for (uint32_t i = 0; i < t.full; ++i) {
+            float x[kQuads][4], th[kQuads][4], ri[kQuads];
 #pragma unroll
             for (uint32_t q = 0; q < kQuads; ++q) {
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const uint32_t bits = __builtin_bit_cast(uint32_t, x[q][k]), hi = (bits >> kShift1) & (kBins1 - 1);
-                    append(hi == p0 || hi == p1, __builtin_amdgcn_ballot_w64(hi == p0) | __builtin_amdgcn_ballot_w64(hi == p1), bits);
-                }
-                if (q % 2 == 1 && n_stage >= 64) flush(false);
+                x[q][0] = nx[q].x; x[q][1] = nx[q].y; x[q][2] = nx[q].z; x[q][3] = nx[q].w;
+                IO::unpack(nt[q], th[q]);
+                ri[q] = nr[q];
             }
-        } else {
+            if (i + 1 < t.full) issue(i + 1);
+            if (d.n <= 2) {
 #pragma unroll
-            for (uint32_t q = 0; q < kQuads; ++q) {
+                for (uint32_t q = 0; q < kQuads; ++q) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const uint32_t bits = __builtin_bit_cast(uint32_t, x[q][k]), hi = (bits >> kShift1) & (kBins1 - 1);
-                    const bool hit = hi == p0 || hi == p1 || hi == d.pre[2] || hi == d.pre[3];
-                    append(hit, __builtin_amdgcn_ballot_w64(hit), bits);
+                    for (int k = 0; k < 4; ++k) {
+                        const uint32_t bits = __builtin_bit_cast(uint32_t, x[q][k]), hi = (bits >> kShift1) & (kBins1 - 1);
+                        append(hi == p0 || hi == p1, __builtin_amdgcn_ballot_w64(hi == p0) | __builtin_amdgcn_ballot_w64(hi == p1), bits);
+                    }
+                    if (q % 2 == 1 && n_stage >= 64) flush(false);
                 }
-                if (q % 2 == 1 && n_stage >= 64) flush(false);
+            } else {
+#pragma unroll
+                for (uint32_t q = 0; q < kQuads; ++q) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const uint32_t bits = __builtin_bit_cast(uint32_t, x[q][k]), hi = (bits >> kShift1) & (kBins1 - 1);
+                        const bool hit = hi == p0 || hi == p1 || hi == d.pre[2] || hi == d.pre[3];
+                        append(hit, __builtin_amdgcn_ballot_w64(hit), bits);
+                    }
+                    if (q % 2 == 1 && n_stage >= 64) flush(false);
+                }
             }
-        }
-        if (F) {
-#pragma unroll
-            for (uint32_t q = 0; q < kQuads; ++q)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const float dd = __builtin_fmaf(-ri[q], cm[k], x[q][k]);
-                    res = __builtin_fmaf(dd, dd, res);
-                }
-        }
-        if (C) {
-            float low = x[0][0];
-#pragma unroll
-            for (uint32_t q = 0; q < kQuads; ++q) low = fminf(fminf(fminf(low, x[q][0]), fminf(x[q][1], x[q][2])), x[q][3]);
-            auto distort = [&](auto p_of) {
+            if (F) {
 #pragma unroll
                 for (uint32_t q = 0; q < kQuads; ++q)
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
-                        const float y = __builtin_fmaf(p_of(x[q][k]), inv_pbar, -1.0f) * th[q][k];
-                        cn = __builtin_fmaf(y, y, cn);
-                        cd = __builtin_fmaf(th[q][k], th[q][k], cd);
+                        const float dd = __builtin_fmaf(-ri[q], cm[k], x[q][k]);
+                        res = __builtin_fmaf(dd, dd, res);
                     }
-            };
-            if (__builtin_amdgcn_ballot_w64(!(low > eps_low)) == 0) distort([&](float v) { return preconditioner_series(v, eps); });
-            else distort([&](float v) { return preconditioner(v, eps); });
-        }
-    }
-    for (uint32_t i = t.full; t.any && i < t.rounds; ++i) {
-        const uint32_t first = round_row(t, i);
-        f4 ex[kQuads]; TV et[kQuads];
-        load_edge<BAOC_GRAD_F32>(ex, src, kAnywhere, t, cols, i);
-        if (C) load_edge<TT>(et, tsrc, tleft, t, cols, i);
-#pragma unroll
-        for (uint32_t q = 0; q < kQuads; ++q) {
-            const bool in_row = first + 4 * q + t.lrow < t.row1;
-            const float ri = rr[min(first + 4 * q + t.lrow, t.row1 - 1)], x[4] = {ex[q].x, ex[q].y, ex[q].z, ex[q].w};
-            float th[4] = {0.f, 0.f, 0.f, 0.f};
-            if (C) IO::unpack(et[q], th);
-#pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) {
-                const bool in = in_row && k < t.n_ok;
-                const uint32_t bits = __builtin_bit_cast(uint32_t, x[k]), hi = (bits >> kShift1) & (kBins1 - 1);
-                const bool hit = in && (hi == p0 || hi == p1 || hi == d.pre[2] || hi == d.pre[3]);
-                append(hit, __builtin_amdgcn_ballot_w64(hit), bits);
-                if (F) {
-                    const float dd = in ? __builtin_fmaf(-ri, cm[k], x[k]) : 0.f;
-                    res = __builtin_fmaf(dd, dd, res);
-                }
-                if (C) {
-                    const float tk = in ? th[k] : 0.f;
-                    const float y = in ? __builtin_fmaf(preconditioner(x[k], eps), inv_pbar, -1.0f) * tk : 0.f;
-                    cn = __builtin_fmaf(y, y, cn);
-                    cd = __builtin_fmaf(tk, tk, cd);
-                }
             }
-            if (n_stage >= 64) flush(false);
+            if (C) {
+                float low = x[0][0];
+#pragma unroll
+                for (uint32_t q = 0; q < kQuads; ++q) low = fminf(fminf(fminf(low, x[q][0]), fminf(x[q][1], x[q][2])), x[q][3]);
+                auto distort = [&](auto p_of) {
+#pragma unroll
+                    for (uint32_t q = 0; q < kQuads; ++q)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const float y = __builtin_fmaf(p_of(x[q][k]), inv_pbar, -1.0f) * th[q][k];
+                            cn = __builtin_fmaf(y, y, cn);
+                            cd = __builtin_fmaf(th[q][k], th[q][k], cd);
+                        }
+                };
+                if (__builtin_amdgcn_ballot_w64(!(low > eps_low)) == 0) distort([&](float v) { return preconditioner_series(v, eps); });
+                else distort([&](float v) { return preconditioner(v, eps); });
+            }
         }
+        for (uint32_t i = t.full; t.any && i < t.rounds; ++i) {
+            const uint32_t first = round_row(t, i);
+            f4 ex[kQuads]; TV et[kQuads];
+            load_edge<BAOC_GRAD_F32>(ex, src, kAnywhere, t, cols, i);
+            if (C) load_edge<TT>(et, tsrc, tleft, t, cols, i);
+#pragma unroll
+            for (uint32_t q = 0; q < kQuads; ++q) {
+                const bool in_row = first + 4 * q + t.lrow < t.row1;
+                const float ri = F ? rr[min(first + 4 * q + t.lrow, t.row1 - 1)] : 0.f, x[4] = {ex[q].x, ex[q].y, ex[q].z, ex[q].w};
+                float th[4] = {0.f, 0.f, 0.f, 0.f};
+                if (C) IO::unpack(et[q], th);
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) {
+                    const bool in = in_row && k < t.n_ok;
+                    const uint32_t bits = __builtin_bit_cast(uint32_t, x[k]), hi = (bits >> kShift1) & (kBins1 - 1);
+                    const bool hit = in && (hi == p0 || hi == p1 || hi == d.pre[2] || hi == d.pre[3]);
+                    append(hit, __builtin_amdgcn_ballot_w64(hit), bits);
+                    if (F) {
+                        const float dd = in ? __builtin_fmaf(-ri, cm[k], x[k]) : 0.f;
+                        res = __builtin_fmaf(dd, dd, res);
+                    }
+                    if (C) {
+                        const float tk = in ? th[k] : 0.f;
+                        const float y = in ? __builtin_fmaf(preconditioner(x[k], eps), inv_pbar, -1.0f) * tk : 0.f;
+                        cn = __builtin_fmaf(y, y, cn);
+                        cd = __builtin_fmaf(tk, tk, cd);
+                    }
+                }
+                if (n_stage >= 64) flush(false);
+            }
+        }
+        flush(true);
+        if (lane == 0) {
+            cand_count[blockIdx.x * 4 + wave] = n_cand;
+            if (n_cand > cap) scan3[block] = 1u;              // list too short: the last digit of the block takes another walk over v
+        }
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < 4 * kBins2; i += 256) h[i] = 0;
+        __syncthreads();
+        // second digit, from the list just written; a wavefront whose list was too short walks its part of the tile again
+        if (n_cand <= cap) {
+            for (uint32_t i = lane; i < n_cand; i += 64) count2(list[i]);
+        } else {
+            for (uint32_t i = 0; i < t.rounds; ++i)
+                for (uint32_t r = round_row(t, i) + t.lrow; r < min(t.row1, round_row(t, i) + kRoundRows); r += 4)
+                    for (uint32_t k = 0; k < t.n_ok; ++k) count2(__builtin_bit_cast(uint32_t, src[(uint64_t)r * m.cols + t.col + k]));
+        }
+    } else {
+        for (uint32_t i = threadIdx.x; i < 4 * kBins2; i += 256) h[i] = 0;
+        __syncthreads();
+        double an = 0.0, ad = 0.0;
+        walk_run<TT, C>(v_all, theta, m, [&](const float x[4], const float th[4], uint32_t n) {
+            float yn = 0.f, yd = 0.f;
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k)
+                if (k < n) {
+                    count2(__builtin_bit_cast(uint32_t, x[k]));
+                    if (C) {
+                        const float y = __builtin_fmaf(preconditioner(x[k], eps), inv_pbar, -1.0f) * th[k];
+                        yn = __builtin_fmaf(y, y, yn);
+                        yd = __builtin_fmaf(th[k], th[k], yd);
+                    }
+                }
+            an += (double)yn; ad += (double)yd;
+        });
+        cn = (float)an; cd = (float)ad;
     }
-    flush(true);
     res = wave_sum(res); cn = wave_sum(cn); cd = wave_sum(cd);
-    if (lane == 0) {
-        red[wave][0] = res; red[wave][1] = cn; red[wave][2] = cd;
-        cand_count[blockIdx.x * 4 + wave] = n_cand;
-        if (n_cand > cap) scan3[m.block] = 1u;         // list too short: the block's last digit takes a third scan
-    }
+    if (lane == 0) { red[wave][0] = res; red[wave][1] = cn; red[wave][2] = cd; }
     __syncthreads();
     if (threadIdx.x < 3)
-        residpart[(uint64_t)blockIdx.x * 4 + threadIdx.x] = (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
-    for (uint32_t i = threadIdx.x; i < NSLOT * kBins2; i += 256) h[i] = 0;
-    __syncthreads();
-    // second digit, from the list just written; a wavefront whose list was too short walks its part of the tile again.
-    // A key that matches prefix slot 0 or 1 counts in LDS, slot 2 or 3 in global memory.
-    auto count2 = [&](uint32_t bits) {
-        const uint32_t hi = (bits >> kShift1) & (kBins1 - 1), bin = (bits >> kShift2) & (kBins2 - 1);
-        if (hi == d.pre[0]) atomicAdd(&h[bin], 1u);
-        else if (hi == d.pre[1]) atomicAdd(&h[kBins2 + bin], 1u);
-        else if (hi == d.pre[2] || hi == d.pre[3]) {
-            const uint32_t slot = hi == d.pre[2] ? 2u : 3u;
+        st_device(&residpart[(uint64_t)blockIdx.x * 4 + threadIdx.x], (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]));
+    const uint32_t n_tasks = m.n_tiles * m.n_segs;
+    const bool single = n_tasks == 1;
+    if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, d.n * kBins2);
+    if (!arrive_last(arrived + block, n_tasks)) return;
+    double* rec = rec_all + (uint64_t)block * kRecDoubles;
+    pick_digit<2>(sel, m, block, single, h, lane, wave, rec);
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (d.slot_of[q] == slot) atomicAdd(&hist_out[q * kBins + bin], 1u);
-        }
-    };
-    if (n_cand <= cap) {
-        for (uint32_t i = lane; i < n_cand; i += 64) count2(list[i]);
-    } else {
-        for (uint32_t i = 0; i < t.rounds; ++i)
-            for (uint32_t r = round_row(t, i) + t.lrow; r < min(t.row1, round_row(t, i) + kRoundRows); r += 4)
-                for (uint32_t k = 0; k < t.n_ok; ++k) count2(__builtin_bit_cast(uint32_t, src[(uint64_t)r * m.cols + t.col + k]));
-    }
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < kBins2; i += 256) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (d.slot_of[q] >= NSLOT) continue;
-            const uint32_t c = h[d.slot_of[q] * kBins2 + i];
-            if (c) atomicAdd(&hist_out[q * kBins + i], c);
-        }
+    for (int q = 0; q < 3; ++q) {
+        double a = 0.0;
+        for (uint32_t i = threadIdx.x; i < n_tasks; i += 256) a += (double)ld_device(&residpart[(uint64_t)(m.first_task + i) * 4 + q]);
+        a = group_sum(a, lane, wave, sums);
+        if (threadIdx.x == 0) rec[q == 0 ? R_FRES : (q == 1 ? R_CNUM : R_CDEN)] = a;
     }
 }
 
-// Third digit of the matrix blocks, counted on the candidate lists that the second tile pass wrote (a few
-// per cent of the coordinates).  Blocks flagged in scan3 are left to the third scan of v.
-__global__ __launch_bounds__(256) void k_cand_hist3(
-    const MatRow* __restrict__ mats, const uint32_t* __restrict__ tile_mat, const uint32_t* __restrict__ cand,
-    const uint32_t* __restrict__ cand_count, const uint32_t* __restrict__ sel_prefix,
-    const uint32_t* __restrict__ scan3, uint32_t* __restrict__ hist_all)
+// Last digit: on the candidate lists that the second pass wrote, or on v where a block has none or one of them
+// overflowed.
+__global__ __launch_bounds__(256) void k_final3(
+    const float* __restrict__ v_all, const TileRow* __restrict__ tiles, const uint32_t* __restrict__ task_block, const uint32_t* __restrict__ cand,
+    const uint32_t* __restrict__ cand_count, Selection sel, uint32_t* __restrict__ arrived, const uint32_t* __restrict__ scan3, double* __restrict__ rec_all)
 {
     __shared__ uint32_t h[4 * kBins3];
-    const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index();
-    const MatRow& m = mats[tile_mat[blockIdx.x]];
-    if (scan3[m.block]) return;                              // the same for the whole workgroup
+    const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index(), block = task_block[blockIdx.x];
+    const TileRow& m = tiles[block];
     for (uint32_t i = threadIdx.x; i < 4 * kBins3; i += 256) h[i] = 0;
-    const Prefixes d = distinct_prefixes(sel_prefix, m.block);
+    const Prefixes d = distinct_prefixes(sel.prefix, block);
+    auto count3 = [&](uint32_t bits) { count_match(h, d, kBins3, (bits & 0x7fffffffu) >> kShift2, bits & (kBins3 - 1)); };
     __syncthreads();
-    const uint32_t n = min(cand_count[blockIdx.x * 4 + wave], m.cand_cap);
-    const uint32_t* list = cand + m.cand_base + ((uint64_t)(blockIdx.x - m.first_task) * 4 + wave) * m.cand_cap;
-    for (uint32_t i = lane; i < n; i += 64) {
-        const uint32_t key = list[i] & 0x7fffffffu;
-        count_match(h, d, kBins3, key >> kShift2, key & (kBins3 - 1));
-    }
-    __syncthreads();
-    uint32_t* out = hist_all + (uint64_t)m.block * 4 * kBins;
-    for (uint32_t i = threadIdx.x; i < kBins3; i += 256) {
+    if (m.rows == 0) {
+        walk_run<BAOC_GRAD_F32, false>(v_all, nullptr, m, [&](const float x[4], const float*, uint32_t n) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint32_t c = h[d.slot_of[q] * kBins3 + i];
-            if (c) atomicAdd(&out[q * kBins + i], c);
-        }
-    }
-}
-
-__global__ __launch_bounds__(256) void k_tile_finish2(const MatRow* __restrict__ mats, const float* __restrict__ residpart,
-                                                      double* __restrict__ rec_all)
-{
-    const MatRow m = mats[blockIdx.x];
-    const uint32_t n = m.n_tiles * m.n_segs;
-    double a[3] = {0.0, 0.0, 0.0};
-    for (uint32_t i = threadIdx.x; i < n; i += 256) {
-        const f4 t = *reinterpret_cast<const f4*>(residpart + (uint64_t)(m.first_task + i) * 4);
-        a[0] += (double)t.x; a[1] += (double)t.y; a[2] += (double)t.z;
-    }
-    __shared__ double sh[3][256];
+            for (uint32_t k = 0; k < 4; ++k)
+                if (k < n) count3(__builtin_bit_cast(uint32_t, x[k]));
+        });
+    } else if (!scan3[block]) {
+        const uint32_t n = min(cand_count[blockIdx.x * 4 + wave], m.cand_cap);
+        const uint32_t* list = cand + m.cand_base + ((uint64_t)(blockIdx.x - m.first_task) * 4 + wave) * m.cand_cap;
+        for (uint32_t i = lane; i < n; i += 64) count3(list[i]);
+    } else {
+        const TilePart t = tile_part(m, blockIdx.x, lane, wave);
+        const float* src = v_all + m.state_start;
+        for (uint32_t i = 0; t.any && i < t.rounds; ++i) {
+            f4 x[kQuads];
+            if (i < t.full) load_full<BAOC_GRAD_F32>(x, src, t, m.cols, i);
+            else load_edge<BAOC_GRAD_F32>(x, src, kAnywhere, t, m.cols, i);
 #pragma unroll
-    for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] = a[q];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
+            for (uint32_t q = 0; q < kQuads; ++q) {
+                if (round_row(t, i) + 4 * q + t.lrow >= t.row1) continue;
+                const float xv[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
 #pragma unroll
-            for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + w];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        double* rec = rec_all + (uint64_t)m.block * kRecDoubles;
-        rec[R_FRES] = sh[0][0]; rec[R_CNUM] = sh[1][0]; rec[R_CDEN] = sh[2][0];
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Eq. 6 on the chunks of blocks without a matrix shape.  p = 1/(sqrt(v) + eps).
-// Pass 1: sum of p per chunk (-> p-bar per block).  Pass 2: sum of
-// ((p/p-bar - 1) theta)^2 and of theta^2 per chunk.  theta is laid out like the
-// gradient buffer.  Partial rows reuse the step's partial-sum buffer.
-// ---------------------------------------------------------------------------
-
-template <int TT, int PASS>
-__global__ __launch_bounds__(256) void k_distortion(
-    const float* __restrict__ v_all, const typename GradIO<TT>::elem* __restrict__ theta,
-    const Chunk* __restrict__ chunks, const uint32_t* __restrict__ list, const BlockRow* __restrict__ rows,
-    const double* __restrict__ rec_all, float* __restrict__ partials, float eps)
-{
-    typedef GradIO<TT> IO;
-    const uint32_t cid = list[blockIdx.x];
-    const Chunk ck = chunks[cid];
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const typename IO::elem* tsrc = theta + ck.grad_start;
-    const bool vec_ok = (reinterpret_cast<uintptr_t>(tsrc) & IO::kAlignMask) == 0;
-    float inv_pbar = 0.f;
-    if (PASS == 2) inv_pbar = (float)((double)rows[ck.block].numel / rec_all[(uint64_t)ck.block * kRecDoubles + R_PSUM]);
-    float a0 = 0.f, a1 = 0.f;
-    for (uint32_t e = threadIdx.x * 4; e < ck.count; e += 1024) {
-        const f4 vv = ld_stream<f4>(v_all + ck.state_start + e);
-        const float v[4] = {vv.x, vv.y, vv.z, vv.w};
-        float th[4] = {0.f, 0.f, 0.f, 0.f};
-        if (PASS == 2) {
-            if (vec_ok && e + 4 <= ck.count) IO::load4(tsrc + e, th);
-            else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) th[j] = (e + j < ck.count) ? IO::load1(tsrc + e + j) : 0.f;
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (e + j < ck.count) {                          // padding coordinates are not part of the block
-                const float p = preconditioner(v[j], eps);
-                if (PASS == 1) a0 += p;
-                else {
-                    const float x = (p * inv_pbar - 1.0f) * th[j];
-                    a0 = __builtin_fmaf(x, x, a0);
-                    a1 = __builtin_fmaf(th[j], th[j], a1);
-                }
+                for (uint32_t k = 0; k < 4; ++k)
+                    if (k < t.n_ok) count3(__builtin_bit_cast(uint32_t, xv[k]));
             }
         }
     }
-    __shared__ float red[4][2];
-    a0 = wave_sum(a0); a1 = wave_sum(a1);
-    if (lane == 0) { red[wave][0] = a0; red[wave][1] = a1; }
     __syncthreads();
-    if (threadIdx.x < 2)
-        partials[(uint64_t)cid * kNumSums + threadIdx.x] =
-            (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
-}
-
-// Per chunk-walked block: fp64 sum of the first `ncols` entries of its partial rows into rec[dst .. dst+ncols).
-__global__ __launch_bounds__(256) void k_reduce_partials(const float* __restrict__ partials, const BlockRow* __restrict__ rows,
-                                                         double* __restrict__ rec_all, uint32_t ncols, uint32_t dst)
-{
-    const BlockRow br = rows[blockIdx.x];
-    if (br.vec_first == kNoVec) return;                      // tiled block: its sums come from k_tile_finish*
-    __shared__ double sh[256];
-    for (uint32_t col = 0; col < ncols; ++col) {
-        double a = 0.0;
-        for (uint32_t c = threadIdx.x; c < br.n_chunks; c += 256) a += (double)partials[(uint64_t)(br.first_chunk + c) * kNumSums + col];
-        sh[threadIdx.x] = a;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) rec_all[(uint64_t)blockIdx.x * kRecDoubles + dst + col] = sh[0];
-        __syncthreads();
-    }
+    const uint32_t n_tasks = m.n_tiles * m.n_segs;
+    const bool single = n_tasks == 1;
+    if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, d.n * kBins3);
+    if (!arrive_last(arrived + block, n_tasks)) return;
+    pick_digit<3>(sel, m, block, single, h, lane, wave, rec_all + (uint64_t)block * kRecDoubles);
 }
 
 }  // namespace baoc
@@ -1390,15 +1338,16 @@ struct Plan {
     uint32_t gpw = 1, nw = 4, slices = 1, slice_groups = 4, resident = 8;   // launch shape of the step kernel
     uint64_t n_prows = 0;         // partial rows of the step kernel = n_chunks * slices
     std::vector<BlockRow> rows;
-    std::vector<MatRow> mats;     // matrix blocks (rows*cols == numel), for Eq. 7
-    uint64_t n_tasks = 0, n_fin = 0, n_vec_chunks = 0;   // workgroups of the tile passes and of k_tile_finish1
+    std::vector<TileRow> tiles;   // how finalize walks each block
+    bool any_matrix = false;
+    uint64_t n_tasks = 0, n_fin = 0;   // workgroups of the finalize passes and of k_fold_means
     std::vector<Part> parts;      // of blocks of more than kDirectRows partial rows
-    uint64_t off_parts = 0;
-    uint64_t off_mats = 0, off_rvec = 0, off_cvec = 0, off_rowpart = 0, off_colpart = 0, off_residpart = 0, off_mu = 0,
-             off_psumpart = 0, off_veclist = 0, off_cand = 0, off_candcount = 0, off_scan3 = 0, off_finpart = 0, off_tilemat = 0, off_finmat = 0;
     uint64_t padded = 0;          // coordinates in m / v / g_prev
-    uint64_t off_m = 0, off_v = 0, off_gp = 0, off_partials = 0, off_chunks = 0, off_rows = 0,
-             off_rec = 0, off_hist = 0, off_selp = 0, off_selr = 0, off_ostat = 0, total = 0;
+    uint64_t off_m = 0, off_v = 0, off_gp = 0, off_partials = 0, off_chunks = 0;
+    uint64_t off_rows = 0, off_tiles = 0, off_parts = 0, off_task_block = 0, off_fin_block = 0;   // the first three are uploaded in one piece
+    uint64_t off_rec = 0, off_hist = 0, off_arrived = 0, off_selp = 0;                            // cleared up to off_selp
+    uint64_t off_selr = 0, off_scan3 = 0, off_rvec = 0, off_cvec = 0, off_residpart = 0, off_candcount = 0,
+             off_cand = 0, off_rowpart = 0, off_colpart = 0, total = 0;
 };
 
 struct baoc_profiler {
@@ -1411,13 +1360,12 @@ struct baoc_profiler {
     uint64_t max_end = 0;         // largest offset + numel over the blocks
     int sticky = BAOC_OK;
     std::vector<double> h_rec;
-    std::vector<float> h_ostat;
 };
 
 static uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 
-// Coordinates of a tile (one workgroup of the tile passes): doubled from the smallest until the layout's matrix blocks
-// need no more than kTileTarget tiles, which still fills the chip's 4 to 5 workgroups per CU twice.  A smaller tile pays
+// Coordinates of a tile (one workgroup of the tile passes): doubled from the smallest until the layout
+// needs no more than kTileTarget tiles, which still fills the chip's 4 to 5 workgroups per CU twice.  A smaller tile pays
 // for its histograms more often (finalize of 124 M coordinates, tiles of 65,536: 407 us, of 16,384: 470 us), and so does
 // a cap below 262,144 on large layouts (3.5 G coordinates: 6.21 ms, with 131,072 6.33 ms, with 1 M 6.55 ms).
 constexpr uint64_t kTileCoordsMin = 8192, kTileCoordsMax = 262144, kTileTarget = 2048;
@@ -1482,93 +1430,96 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
         r.grad_start = b.offset; r.state_start = state; r.numel = b.numel;
         r.first_chunk = (uint32_t)P.n_chunks;
         r.n_chunks = (uint32_t)((groups + per - 1) / per);
-        r.groups_per_chunk = (uint32_t)per; r.vec_first = 0;
+        r.groups_per_chunk = (uint32_t)per; r.pad_ = 0;
         const uint64_t prows = (uint64_t)r.n_chunks * P.slices, first_prow = P.n_chunks * P.slices;
         if (first_prow + prows > 0x7fffffffull) return BAOC_ERR_UNSUPPORTED;
         r.first_prow = (uint32_t)first_prow; r.n_prows = (uint32_t)prows;
         for (uint32_t q = 0; prows > kDirectRows && q < prows / kPartRows; ++q) P.parts.push_back(Part{i, q});
         P.n_chunks += r.n_chunks;
-        for (int q = 0; q < 2; ++q) {                                // ranks bracketing position q (d-1)
-            const double pos = (q == 0 ? 0.1 : 0.9) * (double)(b.numel - 1);
-            const uint64_t lo = (uint64_t)std::floor(pos);
-            r.rank[2 * q] = lo;
-            r.rank[2 * q + 1] = std::min<uint64_t>(lo + 1, b.numel - 1);
-        }
         state += groups * kQB;
         if (P.n_chunks > 0x7fffffffull) return BAOC_ERR_UNSUPPORTED;
     }
     P.padded = state;
     P.n_prows = P.n_chunks * P.slices;
-    // Finalize walks blocks with a real matrix shape tile-wise and the rest chunk-wise.  A shape with a
-    // single row or column is rank one by construction (F = 0 exactly) and stays on the chunk path.
-    P.mats.clear(); P.n_tasks = 0; P.n_fin = 0; P.n_vec_chunks = 0;
-    uint64_t n_r = 0, n_c = 0, n_rowpart = 0, n_colpart = 0, n_cand = 0, n_mat_coords = 0;
-    for (uint32_t i = 0; i < n; ++i)
-        if (blocks[i].rows >= 2 && blocks[i].cols >= 2) n_mat_coords += blocks[i].numel;
+    // Finalize walks blocks with a real matrix shape tile-wise and the rest in runs.  A shape with a
+    // single row or column is rank one by construction (F = 0 exactly) and counts as a run.
+    P.tiles.resize(n); P.any_matrix = false; P.n_tasks = 0; P.n_fin = 0;
+    uint64_t n_r = 0, n_c = 0, n_rowpart = 0, n_colpart = 0, n_cand = 0;
     uint64_t tile_coords = kTileCoordsMin;
-    while (tile_coords < kTileCoordsMax && tile_coords * kTileTarget < n_mat_coords) tile_coords *= 2;
+    while (tile_coords < kTileCoordsMax && tile_coords * kTileTarget < total) tile_coords *= 2;
+    // Blocks without a matrix shape leave nothing but task_block and 32 bytes per run: with the step's own partial rows to
+    // put them in, or 16 KB per block, the workspace stays what it is for any launch shape of the step kernel.
+    uint64_t run_coords = tile_coords;
+    while ((total / run_coords + n) * 36 > P.n_prows * kNumSums * 4 + n * 16384ull && run_coords < (1u << 30)) run_coords *= 2;
     for (uint32_t i = 0; i < n; ++i) {
         const baoc_block& b = blocks[i];
-        if (b.rows < 2 || b.cols < 2) {
-            P.rows[i].vec_first = (uint32_t)P.n_vec_chunks;
-            P.n_vec_chunks += P.rows[i].n_chunks;
-            continue;
+        TileRow& m = P.tiles[i];
+        m = TileRow{};
+        m.state_start = P.rows[i].state_start; m.grad_start = b.offset; m.numel = b.numel;
+        m.first_task = (uint32_t)P.n_tasks; m.first_fin = (uint32_t)P.n_fin;
+        for (int q = 0; q < 2; ++q) {                                // ranks bracketing position q (d-1)
+            const uint64_t lo = (uint64_t)std::floor((q == 0 ? 0.1 : 0.9) * (double)(b.numel - 1));
+            m.rank[2 * q] = (uint32_t)lo;
+            m.rank[2 * q + 1] = (uint32_t)std::min<uint64_t>(lo + 1, b.numel - 1);
         }
-        P.rows[i].vec_first = kNoVec;
-        MatRow m;
-        m.state_start = P.rows[i].state_start; m.grad_start = b.offset;
-        m.rows = b.rows; m.cols = b.cols;
-        // columns of a tile: 256, 128 or 64, the widest that leaves at most an eighth of the lanes without a column
-        m.wc_log = 2;
-        while (m.wc_log > 0 && align_up(b.cols, 64u << m.wc_log) * 8 > (uint64_t)b.cols * 9) --m.wc_log;
-        const uint64_t round_rows = (4u >> m.wc_log) * kRoundRows, tile_cols = 64u << m.wc_log;
-        m.seg_rows = (uint32_t)align_up(std::max<uint64_t>(1, tile_coords / std::min<uint64_t>(b.cols, tile_cols)), round_rows);
-        m.n_tiles = (uint32_t)((b.cols + tile_cols - 1) / tile_cols); m.n_segs = (uint32_t)(((uint64_t)b.rows + m.seg_rows - 1) / m.seg_rows);
-        m.off_r = n_r; m.off_c = n_c; m.off_rowpart = n_rowpart; m.off_colpart = n_colpart;
-        m.first_task = (uint32_t)P.n_tasks; m.first_fin = (uint32_t)P.n_fin; m.block = i;
-        n_r += b.rows; n_c += b.cols;
-        n_rowpart += (uint64_t)b.rows * m.n_tiles; n_colpart += (uint64_t)m.n_segs * b.cols;
-        const uint64_t tasks = (uint64_t)m.n_tiles * m.n_segs;
-        // one candidate list per wavefront; a block's lists have room for an eighth of its coordinates (the keys that
-        // share a selected first digit are a few per cent of a block unless its v is nearly constant; then a list
-        // overflows and the block takes the third scan)
-        m.cand_cap = (uint32_t)align_up((b.numel + 32 * tasks - 1) / (32 * tasks), 4);
-        m.cand_base = n_cand;
-        n_cand += tasks * 4 * m.cand_cap;
-        P.n_tasks += tasks; P.n_fin += ((uint64_t)b.rows + 63) / 64 + ((uint64_t)b.cols + 63) / 64;
-        if (P.n_tasks + P.n_fin > 0x7fffffffull) return BAOC_ERR_UNSUPPORTED;
-        P.mats.push_back(m);
+        uint64_t tasks;
+        if (b.rows < 2 || b.cols < 2) {
+            m.seg_len = (uint32_t)run_coords; m.n_tiles = 1;
+            tasks = (b.numel + run_coords - 1) / run_coords;
+            m.n_segs = (uint32_t)tasks;
+        } else {
+            P.any_matrix = true;
+            m.rows = b.rows; m.cols = b.cols;
+            // columns of a tile: 256, 128 or 64, the widest that leaves at most an eighth of the lanes without a column
+            m.wc_log = 2;
+            while (m.wc_log > 0 && align_up(b.cols, 64u << m.wc_log) * 8 > (uint64_t)b.cols * 9) --m.wc_log;
+            const uint64_t round_rows = (4u >> m.wc_log) * kRoundRows, tile_cols = 64u << m.wc_log;
+            m.seg_len = (uint32_t)align_up(std::max<uint64_t>(1, tile_coords / std::min<uint64_t>(b.cols, tile_cols)), round_rows);
+            m.n_tiles = (uint32_t)((b.cols + tile_cols - 1) / tile_cols); m.n_segs = (uint32_t)(((uint64_t)b.rows + m.seg_len - 1) / m.seg_len);
+            m.off_r = n_r; m.off_c = n_c; m.off_rowpart = n_rowpart; m.off_colpart = n_colpart;
+            n_r += b.rows; n_c += b.cols;
+            n_rowpart += (uint64_t)b.rows * m.n_tiles; n_colpart += (uint64_t)m.n_segs * b.cols;
+            tasks = (uint64_t)m.n_tiles * m.n_segs;
+            // one candidate list per wavefront; a block's lists have room for an eighth of its coordinates (the keys that
+            // share a selected first digit are a few per cent of a block unless its v is nearly constant; then a list
+            // overflows and the last digit takes another walk over v)
+            m.cand_cap = (uint32_t)align_up((b.numel + 32 * tasks - 1) / (32 * tasks), 4);
+            m.cand_base = n_cand;
+            n_cand += tasks * 4 * m.cand_cap;
+            P.n_fin += ((uint64_t)b.rows + 63) / 64 + ((uint64_t)b.cols + 63) / 64;
+        }
+        P.n_tasks += tasks;
+        if (P.n_tasks > 0x7fffffffull || P.n_fin > 0x7fffffffull) return BAOC_ERR_UNSUPPORTED;
     }
     const uint64_t gsz = prm->grad_dtype == BAOC_GRAD_F32 ? 4 : 2;
     uint64_t o = 0;
-    P.off_m = o;        o = align_up(o + P.padded * 4, 256);
-    P.off_v = o;        o = align_up(o + P.padded * 4, 256);
-    P.off_gp = o;       o = align_up(o + P.padded * gsz, 256);
-    P.off_partials = o; o = align_up(o + P.n_prows * kNumSums * 4, 256);   // also holds the per-chunk sums of Eq. 6
-    P.off_chunks = o;   o = align_up(o + P.n_chunks * sizeof(Chunk), 256);
-    P.off_rows = o;     o = align_up(o + (uint64_t)n * sizeof(BlockRow), 256);
-    P.off_rec = o;      o = align_up(o + (uint64_t)n * kRecDoubles * 8, 256);
-    P.off_hist = o;     o = align_up(o + (uint64_t)n * 4 * kBins * 4, 256);
-    P.off_selp = o;     o = align_up(o + (uint64_t)n * 4 * 4, 256);
-    P.off_selr = o;     o = align_up(o + (uint64_t)n * 4 * 4, 256);
-    P.off_ostat = o;    o = align_up(o + (uint64_t)n * 4 * 4, 256);
-    P.off_mats = o;     o = align_up(o + P.mats.size() * sizeof(MatRow), 256);
-    P.off_mu = o;       o = align_up(o + P.mats.size() * 8, 256);
-    P.off_rvec = o;     o = align_up(o + n_r * 4, 256);
-    P.off_cvec = o;     o = align_up(o + n_c * 4, 256);
-    P.off_residpart = o; o = align_up(o + P.n_tasks * 4 * 4, 256);
-    P.off_psumpart = o; o = align_up(o + P.n_tasks * 4, 256);
-    P.off_veclist = o;  o = align_up(o + P.n_vec_chunks * 4, 256);
-    P.off_parts = o;    o = align_up(o + P.parts.size() * sizeof(Part), 256);
-    P.off_candcount = o; o = align_up(o + P.n_tasks * 4 * 4, 256);
-    P.off_scan3 = o;    o = align_up(o + (uint64_t)n * 4, 256);
-    P.off_finpart = o;  o = align_up(o + P.n_fin * 8, 256);
-    P.off_tilemat = o;  o = align_up(o + P.n_tasks * 4, 256);
-    P.off_finmat = o;   o = align_up(o + P.n_fin * 4, 256);
-    // the row and column partial sums of pass 1 are folded before pass 2 writes the candidate lists in their place
-    P.off_cand = o;     P.off_rowpart = o; P.off_colpart = align_up(o + n_rowpart * 4, 256);
-    o = std::max(align_up(o + n_cand * 4, 256), align_up(P.off_colpart + n_colpart * 4, 256));
-    P.total = o;
+    auto place = [&](uint64_t& off, uint64_t bytes) { off = o; o = align_up(o + bytes, 256); };
+    place(P.off_m, P.padded * 4);
+    place(P.off_v, P.padded * 4);
+    place(P.off_gp, P.padded * gsz);
+    place(P.off_partials, P.n_prows * kNumSums * 4);
+    place(P.off_chunks, P.n_chunks * sizeof(Chunk));
+    place(P.off_rows, (uint64_t)n * sizeof(BlockRow));
+    place(P.off_tiles, (uint64_t)n * sizeof(TileRow));
+    place(P.off_parts, P.parts.size() * sizeof(Part));
+    place(P.off_task_block, P.n_tasks * 4);
+    place(P.off_fin_block, P.n_fin * 4);
+    place(P.off_rec, (uint64_t)n * kRecDoubles * 8);
+    place(P.off_hist, (uint64_t)n * kHistWords * 4);
+    place(P.off_arrived, (uint64_t)n * 4);
+    place(P.off_selp, (uint64_t)n * 4 * 4);
+    place(P.off_selr, (uint64_t)n * 4 * 4);
+    place(P.off_scan3, (uint64_t)n * 4);
+    place(P.off_rvec, n_r * 4);
+    place(P.off_cvec, n_c * 4);
+    // The partial rows of the step are free in finalize.  The first pass's sums per task are folded before the second
+    // leaves its own in their place.
+    const uint64_t per_task = align_up(P.n_tasks * 4 * 4, 256);
+    if (2 * per_task <= P.n_prows * kNumSums * 4) { P.off_residpart = P.off_partials; P.off_candcount = P.off_partials + per_task; }
+    else { place(P.off_residpart, per_task); place(P.off_candcount, per_task); }
+    // the row and column partial sums of the first pass are folded before the second writes the candidate lists in their place
+    P.off_cand = o; P.off_rowpart = o; P.off_colpart = align_up(o + n_rowpart * 4, 256);
+    P.total = std::max(align_up(o + n_cand * 4, 256), align_up(P.off_colpart + n_colpart * 4, 256));
     return BAOC_OK;
 }
 
@@ -1621,29 +1572,26 @@ static int begin_on(const baoc_block* blocks, uint32_t n_blocks, const baoc_prof
     h->blocks.assign(blocks, blocks + n_blocks);
     h->ws = static_cast<char*>(d_workspace);
     const Plan& P = h->plan;
-    // The first step treats m, v and g_prev as zero without reading them and writes all of them
-    // (padding included), so only the small tail of the workspace is cleared here.
-    hipError_t e = hipMemset(h->ws + P.off_rec, 0, P.off_mats - P.off_rec);
-    if (e == hipSuccess) e = hipMemcpy(h->ws + P.off_rows, P.rows.data(), P.rows.size() * sizeof(BlockRow), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !P.parts.empty())
-        e = hipMemcpy(h->ws + P.off_parts, P.parts.data(), P.parts.size() * sizeof(Part), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !P.mats.empty())
-        e = hipMemcpy(h->ws + P.off_mats, P.mats.data(), P.mats.size() * sizeof(MatRow), hipMemcpyHostToDevice);
+    // The tables go up in one piece.  The first step treats m, v and g_prev as zero without reading them and writes
+    // all of them (padding included), so only the records, histograms and counters are cleared.
+    std::vector<char> tables(P.off_task_block - P.off_rows);
+    std::memcpy(tables.data(), P.rows.data(), P.rows.size() * sizeof(BlockRow));
+    std::memcpy(tables.data() + (P.off_tiles - P.off_rows), P.tiles.data(), P.tiles.size() * sizeof(TileRow));
+    if (!P.parts.empty()) std::memcpy(tables.data() + (P.off_parts - P.off_rows), P.parts.data(), P.parts.size() * sizeof(Part));
+    hipError_t e = hipMemcpy(h->ws + P.off_rows, tables.data(), tables.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_build_chunks, dim3((uint32_t)((P.n_chunks + 255) / 256)), dim3(256), 0, nullptr,
-                           reinterpret_cast<const BlockRow*>(h->ws + P.off_rows), n_blocks,
+        const uint64_t n_clear = (P.off_selp - P.off_rec) / 16, work = std::max({P.n_chunks, P.n_tasks, P.n_fin, n_clear});
+        hipLaunchKernelGGL(k_build, dim3((uint32_t)std::min<uint64_t>((work + 255) / 256, 8192)), dim3(256), 0, nullptr,
+                           reinterpret_cast<const BlockRow*>(h->ws + P.off_rows), reinterpret_cast<const TileRow*>(h->ws + P.off_tiles), n_blocks,
                            reinterpret_cast<Chunk*>(h->ws + P.off_chunks), (uint32_t)P.n_chunks,
-                           reinterpret_cast<uint32_t*>(h->ws + P.off_veclist));
-        if (!P.mats.empty())
-            hipLaunchKernelGGL(k_build_tiles, dim3((uint32_t)((P.n_tasks + P.n_fin + 255) / 256)), dim3(256), 0, nullptr,
-                               reinterpret_cast<const MatRow*>(h->ws + P.off_mats), (uint32_t)P.mats.size(), (uint32_t)P.n_tasks, (uint32_t)P.n_fin,
-                               reinterpret_cast<uint32_t*>(h->ws + P.off_tilemat), reinterpret_cast<uint32_t*>(h->ws + P.off_finmat));
+                           reinterpret_cast<uint32_t*>(h->ws + P.off_task_block), (uint32_t)P.n_tasks,
+                           reinterpret_cast<uint32_t*>(h->ws + P.off_fin_block), (uint32_t)P.n_fin,
+                           reinterpret_cast<uint4*>(h->ws + P.off_rec), n_clear);
         e = hipGetLastError();
     }
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) { (void)hipGetLastError(); delete h; return BAOC_ERR_HIP; }
     h->h_rec.resize((size_t)n_blocks * kRecDoubles);
-    h->h_ostat.resize((size_t)n_blocks * 4);
     *out = h;
     return BAOC_OK;
 }
@@ -1728,106 +1676,48 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
     if (risk_params) rp = *risk_params; else baoc_risk_params_default(&rp);
     if (!(rp.A_high != rp.A_low) || !(rp.rho_high != rp.rho_low) || !(rp.eta_high != rp.eta_low)) return BAOC_ERR_INVALID;
 
-    const bool want_F = !rp.F_raw && rp.compute_F && !h->plan.mats.empty();
+    const bool want_F = !rp.F_raw && rp.compute_F && h->plan.any_matrix;
     const bool want_C = !rp.C_raw && rp.d_theta_flat;
     if (want_C && (rp.theta_numel < h->max_end || (rp.theta_dtype != BAOC_GRAD_F32 && rp.theta_dtype != BAOC_GRAD_BF16)))
         return BAOC_ERR_INVALID;
 
     const Plan& P = h->plan;
-    const uint32_t N = (uint32_t)P.rows.size(), nch = (uint32_t)P.n_chunks;
-    const uint32_t n_vec = (uint32_t)P.n_vec_chunks, n_mats = (uint32_t)P.mats.size(), n_tiles = (uint32_t)P.n_tasks;
+    const uint32_t N = (uint32_t)P.rows.size(), n_tasks = (uint32_t)P.n_tasks;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const float* v = reinterpret_cast<const float*>(h->ws + P.off_v);
-    const Chunk* ch = reinterpret_cast<const Chunk*>(h->ws + P.off_chunks);
-    const BlockRow* rows = reinterpret_cast<const BlockRow*>(h->ws + P.off_rows);
-    const uint32_t* vec_list = reinterpret_cast<const uint32_t*>(h->ws + P.off_veclist);
-    const MatRow* mats = reinterpret_cast<const MatRow*>(h->ws + P.off_mats);
-    uint32_t* hist = reinterpret_cast<uint32_t*>(h->ws + P.off_hist);
-    uint32_t* selp = reinterpret_cast<uint32_t*>(h->ws + P.off_selp);
-    uint32_t* selr = reinterpret_cast<uint32_t*>(h->ws + P.off_selr);
-    float* ostat = reinterpret_cast<float*>(h->ws + P.off_ostat);
-    float* rvec = reinterpret_cast<float*>(h->ws + P.off_rvec);
-    float* cvec = reinterpret_cast<float*>(h->ws + P.off_cvec);
-    float* rowpart = reinterpret_cast<float*>(h->ws + P.off_rowpart);
-    float* colpart = reinterpret_cast<float*>(h->ws + P.off_colpart);
-    float* residpart = reinterpret_cast<float*>(h->ws + P.off_residpart);
-    float* psumpart = reinterpret_cast<float*>(h->ws + P.off_psumpart);
-    double* mu = reinterpret_cast<double*>(h->ws + P.off_mu);
-    float* part = reinterpret_cast<float*>(h->ws + P.off_partials);
+    auto f32_at = [&](uint64_t off) { return reinterpret_cast<float*>(h->ws + off); };
+    auto u32_at = [&](uint64_t off) { return reinterpret_cast<uint32_t*>(h->ws + off); };
+    const float* v = f32_at(P.off_v);
+    const TileRow* tiles = reinterpret_cast<const TileRow*>(h->ws + P.off_tiles);
+    const uint32_t* task_block = u32_at(P.off_task_block);
+    uint32_t *arrived = u32_at(P.off_arrived), *scan3 = u32_at(P.off_scan3), *cand = u32_at(P.off_cand), *cand_count = u32_at(P.off_candcount);
+    float *rvec = f32_at(P.off_rvec), *cvec = f32_at(P.off_cvec), *residpart = f32_at(P.off_residpart);
     double* rec = reinterpret_cast<double*>(h->ws + P.off_rec);
+    const Selection sel{u32_at(P.off_hist), u32_at(P.off_selp), u32_at(P.off_selr)};
     const float epsf = (float)h->params.eps;
     // v above which eps stays below a thousandth of sqrt(v) (and v is a normal number)
     const float eps_low = std::max(std::numeric_limits<float>::min(), (float)(1e6 * h->params.eps * h->params.eps));
-    const bool th32 = rp.theta_dtype == BAOC_GRAD_F32;
-    const float* th_f = static_cast<const float*>(rp.d_theta_flat);
-    const uint16_t* th_h = static_cast<const uint16_t*>(rp.d_theta_flat);
-    const uint64_t hist_words = (uint64_t)N * 4 * kBins;
-    const uint32_t fill_grid = (uint32_t)std::min<uint64_t>((hist_words + 255) / 256, 4096);
 
-    uint32_t* cand = reinterpret_cast<uint32_t*>(h->ws + P.off_cand);
-    uint32_t* cand_count = reinterpret_cast<uint32_t*>(h->ws + P.off_candcount);
-    uint32_t* scan3 = reinterpret_cast<uint32_t*>(h->ws + P.off_scan3);
-    const uint32_t* tile_mat = reinterpret_cast<const uint32_t*>(h->ws + P.off_tilemat);
-    const uint32_t* fin_mat = reinterpret_cast<const uint32_t*>(h->ws + P.off_finmat);
-    const uint32_t* no_list = nullptr;
-    const uint32_t* no_flags = nullptr;
-
-    // pass 1 over v: first digit everywhere; row/column sums and the sum of p on the way
-    hipLaunchKernelGGL(k_fill_u32, dim3(fill_grid), dim3(256), 0, st, hist, hist_words, 0u);
-    if (n_mats)
-        hipLaunchKernelGGL(k_tile_pass1, dim3(n_tiles), dim3(256), 0, st, v, mats, tile_mat, rowpart, colpart, psumpart, hist, epsf, eps_low, want_C);
-    if (n_vec) {
-        hipLaunchKernelGGL(k_hist<1>, dim3(std::min(n_vec, kHistGrid)), dim3(256), 0, st, v, ch, vec_list, n_vec, selp, hist, rows, no_flags);
-        if (want_C) {
-            if (th32) hipLaunchKernelGGL((k_distortion<BAOC_GRAD_F32, 1>), dim3(n_vec), dim3(256), 0, st, v, th_f, ch, vec_list, rows, rec, part, epsf);
-            else hipLaunchKernelGGL((k_distortion<BAOC_GRAD_BF16, 1>), dim3(n_vec), dim3(256), 0, st, v, th_h, ch, vec_list, rows, rec, part, epsf);
-            hipLaunchKernelGGL(k_reduce_partials, dim3(N), dim3(256), 0, st, part, rows, rec, 1u, (uint32_t)R_PSUM);
-        }
-    }
-    if (n_mats) {
-        double* finpart = reinterpret_cast<double*>(h->ws + P.off_finpart);
-        hipLaunchKernelGGL(k_tile_finish1, dim3((uint32_t)P.n_fin), dim3(256), 0, st, mats, fin_mat, rowpart, colpart, rvec, cvec, finpart);
-        hipLaunchKernelGGL(k_tile_finish1_sum, dim3(n_mats), dim3(256), 0, st, mats, finpart, psumpart, mu, rec);
-    }
-    hipLaunchKernelGGL(k_pick<1>, dim3(N * 4), dim3(64), 0, st, hist, rows, selp, selr, ostat, scan3);
-
-    // pass 2 over v (and theta): second digit; rank-1 residual and distortion on the way; matrix blocks
-    // also set aside the keys that carry a selected first digit
-    hipLaunchKernelGGL(k_fill_u32, dim3(fill_grid), dim3(256), 0, st, hist, hist_words, 0u);
-    if (n_mats) {
-        auto pass2 = [&](auto tt, auto f, auto c, const auto* theta) {
-            hipLaunchKernelGGL((k_tile_pass2<decltype(tt)::value, decltype(f)::value, decltype(c)::value>), dim3(n_tiles), dim3(256), 0, st,
-                               v, theta, rp.theta_numel, mats, tile_mat, rvec, cvec, mu, rec, selp, residpart, hist, cand, cand_count, scan3, epsf, eps_low);
-        };
-        const std::true_type yes; const std::false_type no;
-        const std::integral_constant<int, BAOC_GRAD_F32> t32; const std::integral_constant<int, BAOC_GRAD_BF16> t16;
-        if (!want_C) { if (want_F) pass2(t32, yes, no, th_f); else pass2(t32, no, no, th_f); }
-        else if (th32) { if (want_F) pass2(t32, yes, yes, th_f); else pass2(t32, no, yes, th_f); }
-        else if (want_F) pass2(t16, yes, yes, th_h);
-        else pass2(t16, no, yes, th_h);
-        hipLaunchKernelGGL(k_tile_finish2, dim3(n_mats), dim3(256), 0, st, mats, residpart, rec);
-    }
-    if (n_vec) {
-        hipLaunchKernelGGL(k_hist<2>, dim3(std::min(n_vec, kHistGrid)), dim3(256), 0, st, v, ch, vec_list, n_vec, selp, hist, rows, no_flags);
-        if (want_C) {
-            if (th32) hipLaunchKernelGGL((k_distortion<BAOC_GRAD_F32, 2>), dim3(n_vec), dim3(256), 0, st, v, th_f, ch, vec_list, rows, rec, part, epsf);
-            else hipLaunchKernelGGL((k_distortion<BAOC_GRAD_BF16, 2>), dim3(n_vec), dim3(256), 0, st, v, th_h, ch, vec_list, rows, rec, part, epsf);
-            hipLaunchKernelGGL(k_reduce_partials, dim3(N), dim3(256), 0, st, part, rows, rec, 2u, (uint32_t)R_CNUM);
-        }
-    }
-    hipLaunchKernelGGL(k_pick<2>, dim3(N * 4), dim3(64), 0, st, hist, rows, selp, selr, ostat, scan3);
-
-    // last digit: on the candidate lists of the matrix blocks; by a third scan of v for the blocks walked
-    // chunk-wise and for matrix blocks whose lists overflowed (scan3 flags, skipped a block at a time otherwise)
-    hipLaunchKernelGGL(k_fill_u32, dim3(fill_grid), dim3(256), 0, st, hist, hist_words, 0u);
-    if (n_mats)
-        hipLaunchKernelGGL(k_cand_hist3, dim3(n_tiles), dim3(256), 0, st, mats, tile_mat, cand, cand_count, selp, scan3, hist);
-    hipLaunchKernelGGL(k_hist<3>, dim3(std::min(nch, kHistGrid)), dim3(256), 0, st, v, ch, no_list, nch, selp, hist, rows, static_cast<const uint32_t*>(scan3));
-    hipLaunchKernelGGL(k_pick<3>, dim3(N * 4), dim3(64), 0, st, hist, rows, selp, selr, ostat, scan3);
+    hipLaunchKernelGGL(k_final1, dim3(n_tasks), dim3(256), 0, st, v, tiles, task_block, f32_at(P.off_rowpart), f32_at(P.off_colpart),
+                       reinterpret_cast<double*>(residpart), sel, arrived, scan3, rec, epsf, eps_low, want_C);
+    if (want_F)
+        hipLaunchKernelGGL(k_fold_means, dim3((uint32_t)P.n_fin), dim3(256), 0, st, tiles, u32_at(P.off_fin_block), f32_at(P.off_rowpart),
+                           f32_at(P.off_colpart), rvec, cvec);
+    auto final2 = [&](auto tt, auto f, auto c) {
+        constexpr int TT = decltype(tt)::value;
+        hipLaunchKernelGGL((k_final2<TT, decltype(f)::value, decltype(c)::value>), dim3(n_tasks), dim3(256), 0, st,
+                           v, static_cast<const typename GradIO<TT>::elem*>(rp.d_theta_flat), rp.theta_numel, tiles, task_block, rvec, cvec,
+                           residpart, sel, arrived, cand, cand_count, scan3, rec, epsf, eps_low);
+    };
+    const std::true_type yes; const std::false_type no;
+    const std::integral_constant<int, BAOC_GRAD_F32> t32; const std::integral_constant<int, BAOC_GRAD_BF16> t16;
+    if (!want_C) { if (want_F) final2(t32, yes, no); else final2(t32, no, no); }
+    else if (rp.theta_dtype == BAOC_GRAD_F32) { if (want_F) final2(t32, yes, yes); else final2(t32, no, yes); }
+    else if (want_F) final2(t16, yes, yes);
+    else final2(t16, no, yes);
+    hipLaunchKernelGGL(k_final3, dim3(n_tasks), dim3(256), 0, st, v, tiles, task_block, cand, cand_count, sel, arrived, scan3, rec);
 
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(h->h_rec.data(), h->ws + P.off_rec, h->h_rec.size() * 8, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(h->h_ostat.data(), ostat, h->h_ostat.size() * 4, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(h->h_rec.data(), rec, h->h_rec.size() * 8, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) { (void)hipGetLastError(); h->sticky = BAOC_ERR_HIP; return BAOC_ERR_HIP; }
 
@@ -1839,13 +1729,13 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
         for (int s = 0; s < (int)kNumSums; ++s) r.sums[s] = rec[s];
         r.rho_bar = rec[R_RHO]; r.cos_last = rec[R_COS];
         r.n_cos = (uint32_t)rec[R_NCOS]; r.steps = (uint32_t)rec[R_STEPS];
-        for (int t = 0; t < 4; ++t) r.order_stat[t] = h->h_ostat[(size_t)i * 4 + t];
+        for (int t = 0; t < 4; ++t) r.order_stat[t] = (float)rec[R_ORDER + t];
         const double p10 = 0.1 * (double)(r.numel - 1), p90 = 0.9 * (double)(r.numel - 1);
         r.frac10 = p10 - std::floor(p10); r.frac90 = p90 - std::floor(p90);
         const double eps = h->params.eps;
         double C_raw = rp.C_raw ? rp.C_raw[i] : 0.0, F_raw = rp.F_raw ? rp.F_raw[i] : 0.0;
         if (want_C) C_raw = std::sqrt(rec[R_CNUM]) / (std::sqrt(rec[R_CDEN]) + eps);                  // Eq. 6
-        if (want_F && P.rows[i].vec_first == kNoVec) F_raw = std::sqrt(rec[R_FRES]) / (std::sqrt(rec[S_VV]) + eps);   // Eq. 7
+        if (want_F && P.tiles[i].rows) F_raw = std::sqrt(rec[R_FRES]) / (std::sqrt(rec[S_VV]) + eps);   // Eq. 7
         block_metrics(r, eps, rp, C_raw, F_raw, &stats[i]);
     }
     if (out_stats) std::memcpy(out_stats, stats.data(), sizeof(baoc_block_stats) * N);

@@ -539,3 +539,30 @@ def test_matrix_tiles_at_their_edges(env, dtype, pad):
     w.buffer_numel = max(b.offset + b.numel for b in w.blocks)
     run_both(env, w, 3, seed=9, theta_dtype=torch.float32)
     run_both(env, w, 2, seed=10, theta_dtype=torch.bfloat16)
+
+
+@pytest.mark.parametrize("chunk_groups", [0, 4096])
+def test_vector_runs_at_their_edges_and_finalize_again(env, chunk_groups):
+    """Vectors of one run and of several, a coordinate more or less than a run, next to matrices of one tile and of
+    several; every finalize leaves its histograms and counters as it found them, so a second one gives the same bits and
+    one after further steps is right."""
+    torch, binding = env["torch"], env["binding"]
+    blocks = [W._vec(f"v{n}", n) for n in (1, 2, 1023, 1024, 8191, 8192, 8193, 16384, 40001)] + [W._mat("one", 40, 70), W._mat("some", 300, 200)]
+    w = W.Workload("runs", blocks, 5, "f32", "cycle", **W.K6)
+    W.layout(w, 1); W.draw_stream_params(w, 6)
+    device = env["device"]
+    params = binding.default_profile_params(chunk_groups=chunk_groups)
+    prof, orc, buf = binding.Profiler(w.blocks, params), OracleRunner(w.blocks, **oracle_params(params)), device.new_buffer(w)
+    theta = 0.02 * torch.randn(w.buffer_numel, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(3))
+    for t in range(1, 5):
+        device.fill(w, buf, 4, t)
+        prof.step(buf); orc.step_from_device(buf)
+        if t % 2:
+            continue
+        stats, risk = prof.finalize(w.configs, theta=theta)
+        again, risk2 = prof.finalize(w.configs, theta=theta)
+        assert bytes(stats) == bytes(again) and np.array_equal(risk, risk2)
+        ostats, orisk = orc.finalize(w.configs, shapes=[(b.rows, b.cols) for b in w.blocks], theta=theta)
+        for i in range(len(w.blocks)):
+            assert_stats_close(stats[i], ostats[i], f"step {t}, block {i} ({w.blocks[i].name})")
+        assert_risk_close(risk, orisk, f"step {t}")
