@@ -51,6 +51,13 @@ struct StepConsts {
     float beta_m, beta_v, om_m, om_v, eps_u;
 };
 
+struct FoldArgs {
+    const BlockRow* rows;
+    uint32_t* arrived;
+    double* rec_all;
+    double beta_rho, eps;
+};
+
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 
@@ -202,6 +209,64 @@ template <> struct GradIO<BAOC_GRAD_BF16> {
 };
 
 // ---------------------------------------------------------------------------
+// what crosses workgroups inside a launch
+// ---------------------------------------------------------------------------
+
+// Written by device-scope atomics and stores that go through to memory, and read the same way, so no cache is written back
+// or invalidated; vmcnt(0) before the arrival counter is all the order they need.
+template <typename T> __device__ __forceinline__ void st_device(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T> __device__ __forceinline__ T ld_device(const T* p) { return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+constexpr uint32_t kArriveStride = 32;    // words from one block's arrival counter to the next: atomics on one cache line queue up
+
+// Called by a whole workgroup: true in the last of the n that share the counter, which is then back at zero.
+__device__ __forceinline__ bool arrive_last(uint32_t* counter, uint32_t n)
+{
+    __shared__ uint32_t last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this wavefront's stores and atomics have been performed
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        last = n == 1 || __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+        if (last && n > 1) st_device(counter, 0u);
+    }
+    __syncthreads();
+    return last;
+}
+
+// ---------------------------------------------------------------------------
+// a step's sums into the block's record
+// ---------------------------------------------------------------------------
+
+// Thread s < 16 of the workgroup holds sum s of the block.
+__device__ __forceinline__ void fold_step(double total, double* rec, double beta_rho, double eps)
+{
+    const uint32_t tid = threadIdx.x;
+    if (tid < kNumSums) rec[tid] = total;
+    // Fold the step into the running direction stability (Eq. 5, left):
+    //   cos_t = <g_t,g_{t-1}> / (|g_t| |g_{t-1}| + eps), NaN -> 0 (App. A.1);
+    //   the first cosine initialises rho_bar, later ones enter with weight 1 - beta_rho.
+    static_assert(S_GG == 0 && S_GP == 1, "lane 0 holds |g|^2 and takes <g, g'> from lane 1");
+    if (tid < 64) {
+        const double S_gp = __shfl_down(total, 1);
+        if (tid == 0) {
+            // The step index lives in the block's record, not in a launch argument: a captured launch of a
+            // steady-state step can be replayed for later steps.
+            const uint32_t step = (uint32_t)rec[R_STEPS] + 1u;
+            if (step >= 2) {
+                double c = S_gp / (sqrt(total) * sqrt(rec[R_SPP]) + eps);
+                if (c != c) c = 0.0;
+                const double cosines = rec[R_NCOS];
+                rec[R_RHO] = (cosines == 0.0) ? c : beta_rho * rec[R_RHO] + (1.0 - beta_rho) * c;
+                rec[R_COS] = c;
+                rec[R_NCOS] = cosines + 1.0;
+            }
+            rec[R_SPP] = total;
+            rec[R_STEPS] = (double)step;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // the fused per-step pass
 // ---------------------------------------------------------------------------
 
@@ -211,13 +276,15 @@ template <> struct GradIO<BAOC_GRAD_BF16> {
 // other (G * 1 KB of m and of v per wavefront and round); the workgroup covers NW * G groups per round.
 // The loads of a round are issued together, one round ahead of their use.  With the default shapes a
 // slice is a single round, so no wavefront ever waits on its own stores.
-template <int GT, bool FIRST, int G, int NW>
+// FOLD (small layouts): the workgroup of a block that arrives last adds the block's partial rows and folds the step into
+// its record; otherwise k_reduce does.
+template <int GT, bool FIRST, int G, int NW, bool FOLD>
 __global__ __launch_bounds__(64 * NW) void k_step(
     const typename GradIO<GT>::elem* __restrict__ grad,
     float* __restrict__ m_all, float* __restrict__ v_all,
     typename GradIO<GT>::elem* __restrict__ gp_all,
     const Chunk* __restrict__ chunks, float* __restrict__ partials, StepConsts k,
-    uint32_t slices, uint32_t slice_groups)
+    uint32_t slices, uint32_t slice_groups, FoldArgs fold)
 {
     typedef GradIO<GT> IO;
     const uint32_t chunk = blockIdx.x / slices, slice = blockIdx.x - chunk * slices;
@@ -375,7 +442,25 @@ __global__ __launch_bounds__(64 * NW) void k_step(
         float s = 0.f;
 #pragma unroll
         for (int q = 0; q < NW * 4; ++q) s += red[q * kNumSums + threadIdx.x];
-        partials[(uint64_t)blockIdx.x * kNumSums + threadIdx.x] = s;
+        float* out = partials + (uint64_t)blockIdx.x * kNumSums + threadIdx.x;
+        if (FOLD) st_device(out, s); else *out = s;
+    }
+    if (FOLD) {
+        const uint32_t n = fold.rows[ck.block].n_prows;
+        if (!arrive_last(fold.arrived + ck.block * kArriveStride, n)) return;
+        __shared__ double sh[NW * 4][kNumSums];
+        const float* base = partials + (uint64_t)fold.rows[ck.block].first_prow * kNumSums;
+        double t = 0.0;
+#pragma unroll 8
+        for (uint32_t r = threadIdx.x / kNumSums; r < n; r += NW * 4) t += (double)ld_device(base + (uint64_t)r * kNumSums + threadIdx.x % kNumSums);
+        sh[threadIdx.x / kNumSums][threadIdx.x % kNumSums] = t;
+        __syncthreads();
+        double total = 0.0;
+        if (threadIdx.x < kNumSums) {
+#pragma unroll
+            for (int q = 0; q < NW * 4; ++q) total += sh[q][threadIdx.x];
+        }
+        fold_step(total, fold.rec_all + (uint64_t)ck.block * kRecDoubles, fold.beta_rho, fold.eps);
     }
 }
 
@@ -461,29 +546,7 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
             for (int q = 0; q < 16; ++q) total += sh[q][tid];
         }
     }
-    if (tid < kNumSums) rec[tid] = total;
-    // Fold the step into the running direction stability (Eq. 5, left):
-    //   cos_t = <g_t,g_{t-1}> / (|g_t| |g_{t-1}| + eps), NaN -> 0 (App. A.1);
-    //   the first cosine initialises rho_bar, later ones enter with weight 1 - beta_rho.
-    static_assert(S_GG == 0 && S_GP == 1, "lane 0 holds |g|^2 and takes <g, g'> from lane 1");
-    if (tid < 64) {
-        const double S_gp = __shfl_down(total, 1);
-        if (tid == 0) {
-            // The step index lives in the block's record, not in a launch argument: a captured launch of a
-            // steady-state step can be replayed for later steps.
-            const uint32_t step = (uint32_t)rec[R_STEPS] + 1u;
-            if (step >= 2) {
-                double c = S_gp / (sqrt(total) * sqrt(rec[R_SPP]) + eps);
-                if (c != c) c = 0.0;
-                const double cosines = rec[R_NCOS];
-                rec[R_RHO] = (cosines == 0.0) ? c : beta_rho * rec[R_RHO] + (1.0 - beta_rho) * c;
-                rec[R_COS] = c;
-                rec[R_NCOS] = cosines + 1.0;
-            }
-            rec[R_SPP] = total;
-            rec[R_STEPS] = (double)step;
-        }
-    }
+    fold_step(total, rec, beta_rho, eps);
 }
 
 // ---------------------------------------------------------------------------
@@ -498,27 +561,8 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
 // The workgroup of a block that finishes last folds what the others left: the digit of the four ranks, the block's
 // sums.  As launches of their own (fills, picks, partial sums, separate walks over the blocks without a matrix shape: 19
 // launches, now 4) that took longer than the passes themselves: finalize of 25.6 M coordinates 247 -> 151 us, of 60 M
-// of odd shapes 435 -> 277 us, of 32,768 104 -> 52 us.  What crosses workgroups inside a launch is written by
-// device-scope atomics and stores that go through to memory and read the same way, so no cache is written back or
-// invalidated; vmcnt(0) before the arrival counter is all the order they need.
+// of odd shapes 435 -> 277 us, of 32,768 104 -> 52 us.
 // ---------------------------------------------------------------------------
-
-template <typename T> __device__ __forceinline__ void st_device(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-template <typename T> __device__ __forceinline__ T ld_device(const T* p) { return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
-// Called by a whole workgroup: true in the last of the n that share the counter, which is then back at zero.
-__device__ __forceinline__ bool arrive_last(uint32_t* counter, uint32_t n)
-{
-    __shared__ uint32_t last;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this wavefront's stores and atomics have been performed
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        last = n == 1 || __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
-        if (last && n > 1) st_device(counter, 0u);
-    }
-    __syncthreads();
-    return last;
-}
 
 // How finalize walks a block: tiles of a matrix (rows, cols > 0) or runs of coordinates (rows = cols = 0), a
 // workgroup (task) each.
@@ -1004,7 +1048,7 @@ __global__ __launch_bounds__(256) void k_final1(
     const bool single = n_tasks == 1;
     if (threadIdx.x == 0) { st_device(&taskpart[2 * blockIdx.x], total); st_device(&taskpart[2 * blockIdx.x + 1], psum); }
     if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, kBins1);
-    if (!arrive_last(arrived + block, n_tasks)) return;
+    if (!arrive_last(arrived + block * kArriveStride, n_tasks)) return;
     double* rec = rec_all + (uint64_t)block * kRecDoubles;
     pick_digit<1>(sel, m, block, single, h, lane, wave, rec);
     double a = 0.0, p = 0.0;
@@ -1256,7 +1300,7 @@ __global__ __launch_bounds__(256) void k_final2(
     const uint32_t n_tasks = m.n_tiles * m.n_segs;
     const bool single = n_tasks == 1;
     if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, d.n * kBins2);
-    if (!arrive_last(arrived + block, n_tasks)) return;
+    if (!arrive_last(arrived + block * kArriveStride, n_tasks)) return;
     double* rec = rec_all + (uint64_t)block * kRecDoubles;
     pick_digit<2>(sel, m, block, single, h, lane, wave, rec);
 #pragma unroll
@@ -1312,7 +1356,7 @@ __global__ __launch_bounds__(256) void k_final3(
     const uint32_t n_tasks = m.n_tiles * m.n_segs;
     const bool single = n_tasks == 1;
     if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, d.n * kBins3);
-    if (!arrive_last(arrived + block, n_tasks)) return;
+    if (!arrive_last(arrived + block * kArriveStride, n_tasks)) return;
     pick_digit<3>(sel, m, block, single, h, lane, wave, rec_all + (uint64_t)block * kRecDoubles);
 }
 
@@ -1337,6 +1381,7 @@ struct Plan {
     uint64_t n_chunks = 0;
     uint32_t gpw = 1, nw = 4, slices = 1, slice_groups = 4, resident = 8;   // launch shape of the step kernel
     uint64_t n_prows = 0;         // partial rows of the step kernel = n_chunks * slices
+    bool fold_in_step = false;    // the step kernel folds its own partial rows
     std::vector<BlockRow> rows;
     std::vector<TileRow> tiles;   // how finalize walks each block
     bool any_matrix = false;
@@ -1363,6 +1408,12 @@ struct baoc_profiler {
 };
 
 static uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
+
+// Layouts whose step kernel folds its own partial rows: up to this many rows in all and in one block.  It saves a launch
+// (32,768 coordinates: 9.3 -> 6.5 us a step, 1 M in 64 blocks 9.3 -> 8.0) and costs every workgroup the wait for its
+// stores and an arrival, about 25 ns each where they share a counter: 256 rows of one block take 11.4 us instead of 9.4,
+// 2,000 rows of 100 blocks 14.2 instead of 13.4, 2,048 rows of 16 blocks 15.5 instead of 13.5.
+constexpr uint64_t kFoldRows = 1024, kFoldBlockRows = 64;
 
 // Coordinates of a tile (one workgroup of the tile passes): doubled from the smallest until the layout
 // needs no more than kTileTarget tiles, which still fills the chip's 4 to 5 workgroups per CU twice.  A smaller tile pays
@@ -1441,6 +1492,9 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     }
     P.padded = state;
     P.n_prows = P.n_chunks * P.slices;
+    uint32_t most_prows = 0;
+    for (const BlockRow& r : P.rows) most_prows = std::max(most_prows, r.n_prows);
+    P.fold_in_step = P.n_prows <= kFoldRows && most_prows <= kFoldBlockRows;
     // Finalize walks blocks with a real matrix shape tile-wise and the rest in runs.  A shape with a
     // single row or column is rank one by construction (F = 0 exactly) and counts as a run.
     P.tiles.resize(n); P.any_matrix = false; P.n_tasks = 0; P.n_fin = 0;
@@ -1506,7 +1560,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     place(P.off_fin_block, P.n_fin * 4);
     place(P.off_rec, (uint64_t)n * kRecDoubles * 8);
     place(P.off_hist, (uint64_t)n * kHistWords * 4);
-    place(P.off_arrived, (uint64_t)n * 4);
+    place(P.off_arrived, (uint64_t)n * kArriveStride * 4);
     place(P.off_selp, (uint64_t)n * 4 * 4);
     place(P.off_selr, (uint64_t)n * 4 * 4);
     place(P.off_scan3, (uint64_t)n * 4);
@@ -1523,19 +1577,21 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     return BAOC_OK;
 }
 
-template <int GT, bool FIRST, int G, int NW>
-static void launch_step_as(uint32_t grid, uint32_t lds, hipStream_t st, const typename GradIO<GT>::elem* g, float* m, float* v,
-                           typename GradIO<GT>::elem* gp, const Chunk* ch, float* part, StepConsts k, uint32_t slices, uint32_t slice_groups)
+template <int GT, int G, int NW, typename... Args>
+static void launch_step_as(bool first, bool fold, uint32_t grid, uint32_t lds, hipStream_t st, Args... a)
 {
-    hipLaunchKernelGGL((k_step<GT, FIRST, G, NW>), dim3(grid), dim3(64 * NW), lds, st, g, m, v, gp, ch, part, k, slices, slice_groups);
+    const dim3 g(grid), b(64 * NW);
+    if (first && fold) hipLaunchKernelGGL((k_step<GT, true, G, NW, true>), g, b, lds, st, a...);
+    else if (first) hipLaunchKernelGGL((k_step<GT, true, G, NW, false>), g, b, lds, st, a...);
+    else if (fold) hipLaunchKernelGGL((k_step<GT, false, G, NW, true>), g, b, lds, st, a...);
+    else hipLaunchKernelGGL((k_step<GT, false, G, NW, false>), g, b, lds, st, a...);
 }
 
-// The instantiation for (first step?, groups per wavefront, wavefronts per workgroup); the values were validated at begin.
+// The instantiation for groups per wavefront and wavefronts per workgroup; the values were validated at begin.
 template <int GT, typename... Args>
-static void launch_step(bool first, uint32_t gpw, uint32_t nw, Args... a)
+static void launch_step(uint32_t gpw, uint32_t nw, Args... a)
 {
-#define BAOC_STEP_CASE(GG, NN) \
-    if (gpw == GG && nw == NN) { if (first) launch_step_as<GT, true, GG, NN>(a...); else launch_step_as<GT, false, GG, NN>(a...); return; }
+#define BAOC_STEP_CASE(GG, NN) if (gpw == GG && nw == NN) { launch_step_as<GT, GG, NN>(a...); return; }
     BAOC_STEP_CASE(1, 1) BAOC_STEP_CASE(2, 1) BAOC_STEP_CASE(1, 2) BAOC_STEP_CASE(2, 2) BAOC_STEP_CASE(1, 4) BAOC_STEP_CASE(2, 4)
 #undef BAOC_STEP_CASE
 }
@@ -1639,23 +1695,26 @@ extern "C" int baoc_profile_step(baoc_profiler* h, const void* d_grad_flat, uint
     // The first launch is bound by its arithmetic and runs at full residency.  Later launches are bound
     // by DRAM and run with fewer resident workgroups: each is given so much unused LDS that only about
     // `resident` of them fit a compute unit (allocations are counted in multiples of 2 KB here).
-    const uint32_t static_lds = P.nw * 4 * kNumSums * 4;
+    const uint32_t static_lds = P.nw * 4 * kNumSums * (P.fold_in_step ? 4 + 8 : 4) + (P.fold_in_step ? 8 : 0);
     uint32_t lds = 0;
     if (!first && P.resident * P.nw < 32) lds = kLdsBytesPerCU / P.resident / 2048 * 2048 - static_lds;
     const uint32_t grid = (uint32_t)P.n_prows;
-    if (q.grad_dtype == BAOC_GRAD_F32)
-        launch_step<BAOC_GRAD_F32>(first, P.gpw, P.nw, grid, lds, st, static_cast<const float*>(d_grad_flat), m, v,
-                                   reinterpret_cast<float*>(h->ws + P.off_gp), ch, part, k, P.slices, P.slice_groups);
-    else
-        launch_step<BAOC_GRAD_BF16>(first, P.gpw, P.nw, grid, lds, st, static_cast<const uint16_t*>(d_grad_flat), m, v,
-                                    reinterpret_cast<uint16_t*>(h->ws + P.off_gp), ch, part, k, P.slices, P.slice_groups);
-    h->steps += 1;
     const BlockRow* rows = reinterpret_cast<const BlockRow*>(h->ws + P.off_rows);
-    if (!P.parts.empty())
-        hipLaunchKernelGGL(k_reduce_parts, dim3((uint32_t)P.parts.size()), dim3(256), 0, st,
-                           part, rows, reinterpret_cast<const Part*>(h->ws + P.off_parts));
-    hipLaunchKernelGGL(k_reduce, dim3((uint32_t)P.rows.size()), dim3(256), 0, st,
-                       part, rows, reinterpret_cast<double*>(h->ws + P.off_rec), q.beta_rho, q.eps);
+    double* rec = reinterpret_cast<double*>(h->ws + P.off_rec);
+    const FoldArgs fold{rows, reinterpret_cast<uint32_t*>(h->ws + P.off_arrived), rec, q.beta_rho, q.eps};
+    if (q.grad_dtype == BAOC_GRAD_F32)
+        launch_step<BAOC_GRAD_F32>(P.gpw, P.nw, first, P.fold_in_step, grid, lds, st, static_cast<const float*>(d_grad_flat), m, v,
+                                   reinterpret_cast<float*>(h->ws + P.off_gp), ch, part, k, P.slices, P.slice_groups, fold);
+    else
+        launch_step<BAOC_GRAD_BF16>(P.gpw, P.nw, first, P.fold_in_step, grid, lds, st, static_cast<const uint16_t*>(d_grad_flat), m, v,
+                                    reinterpret_cast<uint16_t*>(h->ws + P.off_gp), ch, part, k, P.slices, P.slice_groups, fold);
+    h->steps += 1;
+    if (!P.fold_in_step) {
+        if (!P.parts.empty())
+            hipLaunchKernelGGL(k_reduce_parts, dim3((uint32_t)P.parts.size()), dim3(256), 0, st,
+                               part, rows, reinterpret_cast<const Part*>(h->ws + P.off_parts));
+        hipLaunchKernelGGL(k_reduce, dim3((uint32_t)P.rows.size()), dim3(256), 0, st, part, rows, rec, q.beta_rho, q.eps);
+    }
     if (hipGetLastError() != hipSuccess) { h->sticky = BAOC_ERR_HIP; return BAOC_ERR_HIP; }
     return BAOC_OK;
 }

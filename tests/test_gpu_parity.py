@@ -566,3 +566,13 @@ def test_vector_runs_at_their_edges_and_finalize_again(env, chunk_groups):
         for i in range(len(w.blocks)):
             assert_stats_close(stats[i], ostats[i], f"step {t}, block {i} ({w.blocks[i].name})")
         assert_risk_close(risk, orisk, f"step {t}")
+
+
+@pytest.mark.parametrize("count", [1, 16, 17])
+@pytest.mark.parametrize("per", [65536, 65537])
+def test_step_folds_its_own_rows_up_to_the_edge(env, per, count):
+    """Blocks of 64 and 65 partial rows, 1,024 rows in all and one block more: the step kernel folds its sums itself or
+    leaves them to the reduction, with the same statistics."""
+    w = W.Workload("fold", [W._vec(f"b{i}", per) for i in range(count)] + [W._vec("end", 5)] * (count == 1), 3, "f32", "cycle", **W.K6)
+    W.layout(w, 1); W.draw_stream_params(w, 2)
+    run_both(env, w, 3, seed=11)
