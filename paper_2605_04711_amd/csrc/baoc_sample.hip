@@ -31,7 +31,8 @@ struct alignas(8) SampleRow {
     uint32_t pad_;
 };
 
-constexpr uint32_t kTile = 1024;    // samples per workgroup
+constexpr uint32_t kBatch = 8;             // samples per thread, all in flight
+constexpr uint32_t kTile = 256 * kBatch;   // samples per workgroup
 
 __host__ __device__ inline uint64_t mix64(uint64_t x)
 {
@@ -40,12 +41,17 @@ __host__ __device__ inline uint64_t mix64(uint64_t x)
     return x ^ (x >> 31);
 }
 
+// The block of a workgroup: 64 candidates compared at a time, two dependent loads for up to 4,096 blocks where a bisection
+// takes twelve.  Every wavefront comes to the same answer.
 __device__ inline uint32_t find_row(const SampleRow* __restrict__ rows, uint32_t n, uint32_t tile)
 {
-    uint32_t lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const uint32_t mid = (lo + hi + 1) >> 1;
-        if (rows[mid].first_tile <= tile) lo = mid; else hi = mid - 1;
+    uint32_t lo = 0, len = n;
+    const uint32_t lane = threadIdx.x & 63u;
+    while (len > 1) {
+        const uint32_t step = (len + 63) / 64, at = lane * step;
+        const uint64_t le = __ballot(at < len && rows[lo + at].first_tile <= tile);
+        const uint32_t k = (63u - (uint32_t)__builtin_clzll(le)) * step;     // the first candidate always qualifies
+        lo += k; len = min(step, len - k);
     }
     return lo;
 }
@@ -78,17 +84,56 @@ __global__ __launch_bounds__(256) void k_draw(const SampleRow* __restrict__ rows
     }
 }
 
+// Bound by the cache lines of the source that the samples touch, all of those of a sampled row where one of ten columns
+// is taken.  A matrix sample is a product of rows and columns: sample (a, c) stands idx[first of row a] + idx[c] - idx[0]
+// into the source, so only the table's first row and first column are read, and 8 bytes a sample stay in memory.  A lane has
+// eight samples in flight.
+// Measured (1 % of 3.5 G bf16 coordinates, 35 M samples; before: every table entry read, four samples in flight):
+// 193 -> 150 us (with the step on the sample 335 -> 278; with 1,024 samples per workgroup 279, with 4,096 287).
 template <typename T>
 __global__ __launch_bounds__(256) void k_gather(const SampleRow* __restrict__ rows, uint32_t n_rows,
                                                 const uint64_t* __restrict__ idx, const T* __restrict__ src,
                                                 T* __restrict__ dst)
 {
-    const uint32_t b = find_row(rows, n_rows, blockIdx.x);
+    const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane((int)find_row(rows, n_rows, blockIdx.x));
     const SampleRow r = rows[b];
     const uint64_t j0 = (uint64_t)(blockIdx.x - r.first_tile) * kTile;
-    const uint64_t j1 = min(r.count, j0 + kTile);
-#pragma unroll 4
-    for (uint64_t j = j0 + threadIdx.x; j < j1; j += 256) dst[r.dst_offset + j] = src[idx[r.idx_start + j]];
+    const uint32_t n = (uint32_t)min(r.count - j0, (uint64_t)kTile);
+    const uint64_t* ix = idx + r.idx_start;
+    T* out = dst + (r.dst_offset + j0);
+    uint32_t t[kBatch];
+    uint64_t at[kBatch];
+    T x[kBatch];
+#pragma unroll
+    for (uint32_t q = 0; q < kBatch; ++q) t[q] = min(threadIdx.x + 256 * q, n - 1);
+    if (r.sub_rows) {
+        const uint64_t a0 = j0 / r.sub_cols, c0 = j0 - a0 * r.sub_cols, first = ix[0];
+        const uint32_t sc = r.sub_cols;
+        uint32_t a[kBatch];                                // row of sample j0 + t, from a0
+        if (sc >= kTile) {
+#pragma unroll
+            for (uint32_t q = 0; q < kBatch; ++q) a[q] = c0 + t[q] >= sc;
+        } else {
+#pragma unroll
+            for (uint32_t q = 0; q < kBatch; ++q) a[q] = ((uint32_t)c0 + t[q]) / sc;
+        }
+        uint64_t row[kBatch], col[kBatch];
+#pragma unroll
+        for (uint32_t q = 0; q < kBatch; ++q) {
+            row[q] = ix[(a0 + a[q]) * sc];
+            col[q] = ix[c0 + t[q] - (uint64_t)a[q] * sc];
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < kBatch; ++q) at[q] = row[q] + (col[q] - first);
+    } else {
+#pragma unroll
+        for (uint32_t q = 0; q < kBatch; ++q) at[q] = ix[j0 + t[q]];
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kBatch; ++q) x[q] = src[at[q]];
+#pragma unroll
+    for (uint32_t q = 0; q < kBatch; ++q)
+        if (threadIdx.x + 256 * q < n) out[threadIdx.x + 256 * q] = x[q];
 }
 
 int make_rows(const baoc_block* blocks, uint32_t n, double ratio, std::vector<SampleRow>* rows,

@@ -189,3 +189,23 @@ def test_pure_stream_of_the_benchmark_stays_in_bounds(env):  # noqa: F811
     assert not torch.equal(gp[:n], gp0[:n])
     assert L.synth_mix_stream(n + 1, m.data_ptr(), v.data_ptr(), gp.data_ptr(), g.data_ptr(), st) == -1
     assert L.synth_mix_stream(n, 0, v.data_ptr(), gp.data_ptr(), g.data_ptr(), st) == -1
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_gather_tiles_at_their_edges(env, dtype):  # noqa: F811
+    """Sub-matrices narrower than a workgroup's 2,048 samples (many rows in a tile) and
+    wider (one row or two), samples of more and fewer than 64 blocks: the buffer the gather writes is the source at
+    the published indices."""
+    torch, binding = env["torch"], env["binding"]
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    shapes = [(2, 2), (3, 5000), (5000, 3), (64, 32), (17, 241), (1, 2049), (1, 2048), (2, 2048), (2, 2047), (3, 2049), (9, 8191), (300, 77)]
+    for extra in (0, 60, 80):
+        blocks, at = [], 3
+        for r, c in shapes + [(1, 70)] * extra:
+            blocks.append((at, r * c, r if r > 1 else 0, c if r > 1 else 0)); at += r * c + 1
+        src = torch.randn(at, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(2)).to(tdt)
+        for ratio in (1.0, 0.3):
+            smp = binding.Sampler(blocks, ratio, seed=5)
+            out = smp.gather(src)
+            for i, (o, n, _, _) in enumerate(smp.compact_blocks):
+                assert torch.equal(out[o:o + n], src[smp.indices(i)]), f"block {i}, ratio {ratio}"
