@@ -134,7 +134,7 @@ def sampled_windows(a, w, ring, theta, params, mem, tc, b_mem, cap):
         window(a.warmup)
     total, g_ms, s_ms, rest_ms = window(K)
     g_avg = sum(g_ms) / len(g_ms); s_avg = sum(s_ms[1:]) / max(1, len(s_ms) - 1)
-    gather_bytes = samples * (8 + 2 * esz)                # index, element read, element written
+    gather_bytes = samples * 2 * esz                      # element read, element written
     return {"metric": "gradient elements covered/sec with sparse sampling", "value": K * D / total, "unit": "elements/s",
             "n_gpus": 1, "steps": K, "warmup": a.warmup, "ms_per_step": total * 1e3 / K, "higher_is_better": True,
             "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",

@@ -762,9 +762,10 @@ __device__ __forceinline__ double group_sum(double x, uint32_t lane, uint32_t wa
 // In the second pass the keys that carry a selected first digit (a few per cent) are appended to a candidate list
 // per wavefront; the second digit is counted on the list at the end, the last digit by k_final3.
 // Large layouts are bound by HBM with the vector ALUs close behind, small ones by the number of wavefronts in flight.
-// Measured (pass 1 / pass 2, us; before: one wavefront per 256 x 256 tile, scalar loads where a row is not a
-// multiple of 4, keys stored as they were found): 25.6 M coordinates of convolutions 189 / 416 -> 26 / 53,
-// 124 M 136 / 323 -> 93 / 159, 60 M of odd shapes 254 / 535 -> 51 / 104, 3.5 G 2492 / 3887 -> 2353 / 3640.
+// Measured (first / second pass, us; before: one wavefront per 256 x 256 tile, scalar loads where a row is not a
+// multiple of 4, keys stored as they were found; now with the folds of the last workgroup): 25.6 M coordinates of
+// convolutions 189 / 416 -> 37 / 48, 124 M 136 / 323 -> 110 / 155, 60 M of odd shapes, a third of them vectors,
+// 254 / 535 -> 74 / 136, 3.5 G 2492 / 3887 -> 2340 / 3610 (5.9 and 6.0 TB/s).
 // ---------------------------------------------------------------------------
 
 constexpr uint32_t kQuads = 4;                        // loads of 4 rows a wavefront has in flight
