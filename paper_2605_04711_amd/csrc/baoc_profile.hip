@@ -13,7 +13,8 @@
 // slices, one workgroup (1, 2 or 4 wavefronts, a launch-shape parameter) and one partial row each.  A
 // wavefront owns whole 256-coordinate quantisation groups (4 coordinates per lane, one or two groups
 // next to each other), so a group's absmax is a DPP reduction inside the wavefront.  Sums go wavefront
-// (DPP) -> workgroup (LDS) -> one partial row per workgroup -> per parameter block in fp64 (second kernel).
+// (DPP) -> workgroup (LDS) -> one partial row per workgroup -> per parameter block in fp64 (by the block's last
+// workgroup on small layouts, by a second kernel on others).
 // No float atomics anywhere: two runs give identical bits.
 #include <hip/hip_runtime.h>
 
