@@ -1118,7 +1118,15 @@ __global__ __launch_bounds__(256) void k_final2(
     float inv_pbar = 0.f;
     if (C) inv_pbar = (float)((double)m.numel / rec_in[R_PSUM]);
     auto count2 = [&](uint32_t bits) { count_match(h, d, kBins2, (bits >> kShift1) & (kBins1 - 1), (bits >> kShift2) & (kBins2 - 1)); };
+    // A lane adds at most 256 terms in fp32 before they go to fp64 (16 at the edges, where narrow matrices stay all the way): the sums
+    // of a constant theta drift with the length of the chain (300,000 x 4 in a large layout: C off by 3e-5 with a chain over the
+    // tile, by 6e-8 now).
     float res = 0.f, cn = 0.f, cd = 0.f;
+    double rsum = 0.0, nsum = 0.0, dsum = 0.0;
+    auto settle = [&]() {
+        if (F) { rsum += (double)res; res = 0.f; }
+        if (C) { nsum += (double)cn; dsum += (double)cd; cn = 0.f; cd = 0.f; }
+    };
     if (m.rows) {
         const TilePart t = tile_part(m, blockIdx.x, lane, wave);
         const float* src = v_all + m.state_start;
@@ -1226,6 +1234,7 @@ __global__ __launch_bounds__(256) void k_final2(
                 if (__builtin_amdgcn_ballot_w64(!(low > eps_low)) == 0) distort([&](float v) { return preconditioner_series(v, eps); });
                 else distort([&](float v) { return preconditioner(v, eps); });
             }
+            if ((i + 1) % kSubRounds == 0) settle();
         }
         for (uint32_t i = t.full; t.any && i < t.rounds; ++i) {
             const uint32_t first = round_row(t, i);
@@ -1257,7 +1266,9 @@ __global__ __launch_bounds__(256) void k_final2(
                 }
                 if (n_stage >= 64) flush(false);
             }
+            settle();
         }
+        settle();
         flush(true);
         if (lane == 0) {
             cand_count[blockIdx.x * 4 + wave] = n_cand;
@@ -1277,7 +1288,6 @@ __global__ __launch_bounds__(256) void k_final2(
     } else {
         for (uint32_t i = threadIdx.x; i < 4 * kBins2; i += 256) h[i] = 0;
         __syncthreads();
-        double an = 0.0, ad = 0.0;
         walk_run<TT, C>(v_all, theta, m, [&](const float x[4], const float th[4], uint32_t n) {
             float yn = 0.f, yd = 0.f;
 #pragma unroll
@@ -1290,15 +1300,14 @@ __global__ __launch_bounds__(256) void k_final2(
                         yd = __builtin_fmaf(th[k], th[k], yd);
                     }
                 }
-            an += (double)yn; ad += (double)yd;
+            nsum += (double)yn; dsum += (double)yd;
         });
-        cn = (float)an; cd = (float)ad;
     }
-    res = wave_sum(res); cn = wave_sum(cn); cd = wave_sum(cd);
+    res = wave_sum((float)rsum); cn = wave_sum((float)nsum); cd = wave_sum((float)dsum);
     if (lane == 0) { red[wave][0] = res; red[wave][1] = cn; red[wave][2] = cd; }
     __syncthreads();
     if (threadIdx.x < 3)
-        st_device(&residpart[(uint64_t)blockIdx.x * 4 + threadIdx.x], (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]));
+        st_device(&residpart[(uint64_t)blockIdx.x * 4 + threadIdx.x], (float)(((double)red[0][threadIdx.x] + (double)red[1][threadIdx.x]) + ((double)red[2][threadIdx.x] + (double)red[3][threadIdx.x])));
     const uint32_t n_tasks = m.n_tiles * m.n_segs;
     const bool single = n_tasks == 1;
     if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, d.n * kBins2);
@@ -1422,6 +1431,11 @@ constexpr uint64_t kFoldRows = 1024, kFoldBlockRows = 64;
 // for its histograms more often (finalize of 124 M coordinates, tiles of 65,536: 407 us, of 16,384: 470 us), and so does
 // a cap below 262,144 on large layouts (3.5 G coordinates: 6.21 ms, with 131,072 6.33 ms, with 1 M 6.55 ms).
 constexpr uint64_t kTileCoordsMin = 8192, kTileCoordsMax = 262144, kTileTarget = 2048;
+// Rows of a tile: those of a 64-column tile of the largest size.  A matrix of fewer columns still occupies 64 columns of lanes, so
+// without this line its workgroups walk up to 131,072 rows one round after another (40 matrices of 50,000 x 4 and 32 of 4,096 x
+// 4,096: finalize 4.13 -> 1.26 ms, one of 300,000 x 4 next to 566 M coordinates 5.30 -> 1.59 ms; with 2,048 rows 1.37 and 1.61 ms,
+// with 1,024 1.41 and 1.62 ms).
+constexpr uint64_t kTileRowsMax = kTileCoordsMax / 64;
 
 static int check_params(const baoc_profile_params* p)
 {
@@ -1530,7 +1544,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
             m.wc_log = 2;
             while (m.wc_log > 0 && align_up(b.cols, 64u << m.wc_log) * 8 > (uint64_t)b.cols * 9) --m.wc_log;
             const uint64_t round_rows = (4u >> m.wc_log) * kRoundRows, tile_cols = 64u << m.wc_log;
-            m.seg_len = (uint32_t)align_up(std::max<uint64_t>(1, tile_coords / std::min<uint64_t>(b.cols, tile_cols)), round_rows);
+            m.seg_len = (uint32_t)align_up(std::min<uint64_t>(kTileRowsMax, tile_coords / std::min<uint64_t>(b.cols, tile_cols)), round_rows);
             m.n_tiles = (uint32_t)((b.cols + tile_cols - 1) / tile_cols); m.n_segs = (uint32_t)(((uint64_t)b.rows + m.seg_len - 1) / m.seg_len);
             m.off_r = n_r; m.off_c = n_c; m.off_rowpart = n_rowpart; m.off_colpart = n_colpart;
             n_r += b.rows; n_c += b.cols;

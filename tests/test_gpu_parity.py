@@ -576,3 +576,28 @@ def test_step_folds_its_own_rows_up_to_the_edge(env, per, count):
     w = W.Workload("fold", [W._vec(f"b{i}", per) for i in range(count)] + [W._vec("end", 5)] * (count == 1), 3, "f32", "cycle", **W.K6)
     W.layout(w, 1); W.draw_stream_params(w, 2)
     run_both(env, w, 3, seed=11)
+
+
+@pytest.mark.parametrize("rows,cols", [(300000, 4), (300001, 2), (200003, 3), (100000, 16), (20000, 100)])
+def test_eq6_and_eq7_sums_of_tall_matrices_in_a_large_layout(env, rows, cols):
+    """Tall matrices next to a vector that makes the tiles as large as they get, theta constant (every term of the sum of
+    theta^2 rounds the same way): C and F against fp64 on the same v.  Bound: a lane adds at most 256 terms in fp32, the lanes
+    of a tile another dozen; at 2^-24 per addition that is 1.6e-5 on each of the two sums behind C, half of it behind
+    the root.  Narrow matrices go through the edges, with 16 terms: 1.7e-6, and 1e-6 for p itself."""
+    torch, binding = env["torch"], env["binding"]
+    n, at = rows * cols, (rows * cols + 63) // 64 * 64
+    blocks, numel = [(0, n, rows, cols), (at, 270_000_000)], at + 270_000_000
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    grad = 1e-3 * torch.randn(numel, device="cuda:0", generator=gen)
+    theta = torch.full((numel,), 0.0123, device="cuda:0")
+    prof = binding.Profiler(blocks, binding.default_profile_params())
+    prof.step(grad); prof.step(grad)
+    stats, _ = prof.finalize(theta=theta)
+    eps, v = 1e-12, prof.state(0)[1].double()
+    p, t = 1.0 / (v.sqrt() + eps), theta[:n].double()
+    C = (((p / p.mean() - 1.0) * t).norm() / (t.norm() + eps)).item()
+    S = v.view(rows, cols)
+    F = ((S - torch.outer(S.mean(1), S.mean(0)) / S.mean()).norm() / (S.norm() + eps)).item()
+    tol = 2.7e-6 if cols < 64 else 1.7e-5
+    assert abs(stats[0].C - C) <= tol * C, (stats[0].C, C)
+    assert abs(stats[0].F - F) <= tol * F, (stats[0].F, F)
