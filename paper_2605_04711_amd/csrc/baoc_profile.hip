@@ -1517,14 +1517,41 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     uint64_t n_r = 0, n_c = 0, n_rowpart = 0, n_colpart = 0, n_cand = 0;
     uint64_t tile_coords = kTileCoordsMin;
     while (tile_coords < kTileCoordsMax && tile_coords * kTileTarget < total) tile_coords *= 2;
-    // Blocks without a matrix shape leave nothing but task_block and 32 bytes per run: with the step's own partial rows to
-    // put them in, or 16 KB per block, the workspace stays what it is for any launch shape of the step kernel.
-    uint64_t run_coords = tile_coords;
-    while ((total / run_coords + n) * 36 > P.n_prows * kNumSums * 4 + n * 16384ull && run_coords < (1u << 30)) run_coords *= 2;
+    uint64_t matrix_tasks = 0, run_budget = 0;
     for (uint32_t i = 0; i < n; ++i) {
         const baoc_block& b = blocks[i];
         TileRow& m = P.tiles[i];
         m = TileRow{};
+        if (b.rows < 2 || b.cols < 2) { run_budget += 15360 + 4ull * P.rows[i].n_chunks; continue; }
+        m.rows = b.rows; m.cols = b.cols;
+        // columns of a tile: 256, 128 or 64, the widest that leaves at most an eighth of the lanes without a column
+        m.wc_log = 2;
+        while (m.wc_log > 0 && align_up(b.cols, 64u << m.wc_log) * 8 > (uint64_t)b.cols * 9) --m.wc_log;
+        const uint64_t round_rows = (4u >> m.wc_log) * kRoundRows, tile_cols = 64u << m.wc_log;
+        m.seg_len = (uint32_t)align_up(std::min<uint64_t>(kTileRowsMax, tile_coords / std::min<uint64_t>(b.cols, tile_cols)), round_rows);
+        m.n_tiles = (uint32_t)((b.cols + tile_cols - 1) / tile_cols); m.n_segs = (uint32_t)(((uint64_t)b.rows + m.seg_len - 1) / m.seg_len);
+        matrix_tasks += (uint64_t)m.n_tiles * m.n_segs;
+    }
+    // The tasks' sums (16 bytes each) and the lengths of their candidate lists (16 bytes, only where there are matrices) go where
+    // the step's partial rows are, as far as these have room.
+    auto task_bytes = [](uint64_t tasks) { return align_up(tasks * 16, 256); };
+    const uint64_t partial_bytes = P.n_prows * kNumSums * 4;
+    auto sums_fit = [&](uint64_t tasks) { return task_bytes(tasks) <= partial_bytes; };
+    auto counts_fit = [&](uint64_t tasks) { return 2 * task_bytes(tasks) <= partial_bytes; };
+    // Coordinates of a run.  A run takes 4 bytes in task_block and up to 32 for what does not fit there (with large chunks the
+    // partial rows are few).  Runs are lengthened until that is within run_budget, 15 KB per block and 4 bytes per chunk, which keeps
+    // the workspace of a layout from growing with the number of runs whatever the launch shape.
+    uint64_t run_coords = tile_coords;
+    for (; run_coords < (1u << 30); run_coords = align_up(run_coords * 5 / 4, 1024)) {
+        uint64_t runs = 0;
+        for (uint32_t i = 0; i < n; ++i)
+            if (P.tiles[i].rows == 0) runs += (blocks[i].numel + run_coords - 1) / run_coords;
+        const uint64_t tasks = matrix_tasks + runs;
+        if (runs * (4 + (sums_fit(tasks) ? 0 : 16) + (matrix_tasks == 0 || counts_fit(tasks) ? 0 : 16)) <= run_budget) break;
+    }
+    for (uint32_t i = 0; i < n; ++i) {
+        const baoc_block& b = blocks[i];
+        TileRow& m = P.tiles[i];
         m.state_start = P.rows[i].state_start; m.grad_start = b.offset; m.numel = b.numel;
         m.first_task = (uint32_t)P.n_tasks; m.first_fin = (uint32_t)P.n_fin;
         for (int q = 0; q < 2; ++q) {                                // ranks bracketing position q (d-1)
@@ -1533,19 +1560,12 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
             m.rank[2 * q + 1] = (uint32_t)std::min<uint64_t>(lo + 1, b.numel - 1);
         }
         uint64_t tasks;
-        if (b.rows < 2 || b.cols < 2) {
+        if (m.rows == 0) {
             m.seg_len = (uint32_t)run_coords; m.n_tiles = 1;
             tasks = (b.numel + run_coords - 1) / run_coords;
             m.n_segs = (uint32_t)tasks;
         } else {
             P.any_matrix = true;
-            m.rows = b.rows; m.cols = b.cols;
-            // columns of a tile: 256, 128 or 64, the widest that leaves at most an eighth of the lanes without a column
-            m.wc_log = 2;
-            while (m.wc_log > 0 && align_up(b.cols, 64u << m.wc_log) * 8 > (uint64_t)b.cols * 9) --m.wc_log;
-            const uint64_t round_rows = (4u >> m.wc_log) * kRoundRows, tile_cols = 64u << m.wc_log;
-            m.seg_len = (uint32_t)align_up(std::min<uint64_t>(kTileRowsMax, tile_coords / std::min<uint64_t>(b.cols, tile_cols)), round_rows);
-            m.n_tiles = (uint32_t)((b.cols + tile_cols - 1) / tile_cols); m.n_segs = (uint32_t)(((uint64_t)b.rows + m.seg_len - 1) / m.seg_len);
             m.off_r = n_r; m.off_c = n_c; m.off_rowpart = n_rowpart; m.off_colpart = n_colpart;
             n_r += b.rows; n_c += b.cols;
             n_rowpart += (uint64_t)b.rows * m.n_tiles; n_colpart += (uint64_t)m.n_segs * b.cols;
@@ -1584,9 +1604,9 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     place(P.off_cvec, n_c * 4);
     // The partial rows of the step are free in finalize.  The first pass's sums per task are folded before the second
     // leaves its own in their place.
-    const uint64_t per_task = align_up(P.n_tasks * 4 * 4, 256);
-    if (2 * per_task <= P.n_prows * kNumSums * 4) { P.off_residpart = P.off_partials; P.off_candcount = P.off_partials + per_task; }
-    else { place(P.off_residpart, per_task); place(P.off_candcount, per_task); }
+    const uint64_t per_task = task_bytes(P.n_tasks);
+    if (sums_fit(P.n_tasks)) P.off_residpart = P.off_partials; else place(P.off_residpart, per_task);
+    if (counts_fit(P.n_tasks)) P.off_candcount = P.off_partials + per_task; else if (P.any_matrix) place(P.off_candcount, per_task);
     // the row and column partial sums of the first pass are folded before the second writes the candidate lists in their place
     P.off_cand = o; P.off_rowpart = o; P.off_colpart = align_up(o + n_rowpart * 4, 256);
     P.total = std::max(align_up(o + n_cand * 4, 256), align_up(P.off_colpart + n_colpart * 4, 256));

@@ -54,6 +54,22 @@ def test_workspace_size_tracks_the_state_bytes():
         assert per * w.numel <= n <= (per + 0.5) * w.numel * 1.02 + (1 << 20) + 40_000 * len(w.blocks)   # + candidate lists: 4 bytes per 8 coordinates
 
 
+@pytest.mark.parametrize("n,chunk_groups,chunk_slices,bf16", [
+    (832832657, 4096, 2, 1), (1066753667, 4096, 1, 0), (60651394, 512, 2, 0), (14811333, 128, 2, 0), (16071401, 64, 1, 0), (8592499, 64, 1, 1)])
+def test_workspace_of_large_chunks_does_not_grow_with_the_runs_of_finalize(n, chunk_groups, chunk_slices, bf16):
+    """One vector cut into few large chunks: its states, 64 bytes per partial row, 28 per chunk and 33,500 for the block are enough."""
+    groups = -(-n // 256)
+    per = -(-groups // -(-groups // chunk_groups))
+    chunks = -(-groups // per)
+    bound = groups * 256 * (8 + (2 if bf16 else 4)) + chunks * (chunk_slices * 64 + 28) + 33500
+    assert ws([(0, n)], grad_dtype=bf16, chunk_groups=chunk_groups, chunk_slices=chunk_slices) <= bound
+
+
+@pytest.mark.parametrize("n,chunk_groups,chunk_slices,bf16", [(13410560, 64, 1, 1), (13414400, 128, 1, 1), (11176448, 64, 1, 0), (11177472, 128, 2, 0)])
+def test_largest_vectors_of_the_static_workspace(n, chunk_groups, chunk_slices, bf16):
+    assert ws([(0, n)], grad_dtype=bf16, chunk_groups=chunk_groups, chunk_slices=chunk_slices) <= binding.STATIC_WORKSPACE_BYTES
+
+
 def test_layout_validation():
     def status(blocks, **kw):
         with pytest.raises(binding.BaocError) as e:
