@@ -575,7 +575,8 @@ struct alignas(8) TileRow {
     uint64_t off_rowpart, off_colpart;    // into the partial-sum arrays (floats): [tile][row] and [seg][column]
     uint64_t cand_base;                   // the block's first candidate list (words into the candidate buffer)
     uint32_t rows, cols;
-    uint32_t n_tiles, n_segs;
+    uint32_t n_tiles, n_segs;             // tiles side by side and below each other
+    uint32_t strips, n_across;            // neighbouring tiles that a task takes one after another; tasks side by side
     uint32_t seg_len;                     // rows of a tile, or coordinates of a run
     uint32_t wc_log;                      // a tile is seg_len x (64 << wc_log)
     uint32_t first_task;
@@ -791,11 +792,21 @@ struct TilePart {
     uint32_t base;                        // the lane's first column (clamped to an existing one)
 };
 
-__device__ __forceinline__ TilePart tile_part(const TileRow& m, uint32_t wg, uint32_t lane, uint32_t wave)
+// The tiles of a workgroup: [tile, last) of the segment.
+struct Task { uint32_t seg, tile, last; };
+template <bool STRIPS>
+__device__ __forceinline__ Task task_of(const TileRow& m, uint32_t wg)
+{
+    const uint32_t local = wg - m.first_task, seg = local / m.n_across, across = local - seg * m.n_across;
+    if (!STRIPS) return Task{seg, across, across + 1};
+    const uint32_t tile = across * m.strips;
+    return Task{seg, tile, min(m.n_tiles, tile + m.strips)};
+}
+
+__device__ __forceinline__ TilePart tile_part(const TileRow& m, uint32_t seg, uint32_t tile, uint32_t lane, uint32_t wave)
 {
     TilePart t;
-    const uint32_t local = wg - m.first_task;
-    t.seg = local / m.n_tiles; t.tile = local - t.seg * m.n_tiles;
+    t.seg = seg; t.tile = tile;
     t.wr = 4u >> m.wc_log;
     t.wcol = wave & ((1u << m.wc_log) - 1u); t.wrow = wave >> m.wc_log;
     t.row0 = t.seg * m.seg_len; t.row1 = min(m.rows, t.row0 + m.seg_len);
@@ -854,20 +865,20 @@ __device__ __forceinline__ void load_edge(typename GradIO<TT>::vec4 (&x)[kQuads]
 
 constexpr uint64_t kAnywhere = ~0ull;                 // v may be read past its end: g_prev follows it in the workspace
 
-// First pass over a tile.  Returns the lane's sum of p and leaves the thread's part of the sum of v in `total`; counts
-// into h (cleared here).
-__device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, const TileRow& m, uint32_t lane, uint32_t wave,
+// First pass over a tile.  Returns the lane's sum of p and adds the thread's part of the sum of v to `total`; counts
+// into h, which the `first` tile of the workgroup clears.
+__device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, const TileRow& m, const TilePart& t, bool first, uint32_t lane, uint32_t wave,
                                              float* __restrict__ rowpart, float* __restrict__ colpart, uint32_t* h, float* rowsum, double* colsum,
                                              float eps, float eps_low, bool want_p, double& total)
 {
-    const TilePart t = tile_part(m, blockIdx.x, lane, wave);
     const float* src = v_all + m.state_start;
     const uint32_t cols = scalar_u32(m.cols);
     f4 nx[kQuads];
 #pragma unroll
     for (uint32_t q = 0; q < kQuads; ++q) nx[q] = f4{0.f, 0.f, 0.f, 0.f};
     if (t.full) load_full<BAOC_GRAD_F32>(nx, src, t, cols, 0);
-    for (uint32_t i = threadIdx.x; i < kBins1; i += 256) h[i] = 0;
+    if (first)
+        for (uint32_t i = threadIdx.x; i < kBins1; i += 256) h[i] = 0;
     // Column sums and the sum of p run over many rows per lane: kept in fp64 so that a constant
     // v (rank one, p constant) comes out as such to ~1e-7 instead of the ~1e-5 of a long fp32 chain.
     double cs[4] = {0.0, 0.0, 0.0, 0.0}, psum = 0.0;
@@ -896,13 +907,13 @@ __device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, co
                     else add_p([&](float v) { return preconditioner(v, eps); });
                 }
             } else {
-                const uint32_t first = round_row(t, i);
+                const uint32_t row = round_row(t, i);
                 f4 ex[kQuads];
                 load_edge<BAOC_GRAD_F32>(ex, src, kAnywhere, t, cols, i);
 #pragma unroll
                 for (uint32_t q = 0; q < kQuads; ++q) {
                     x[q][0] = ex[q].x; x[q][1] = ex[q].y; x[q][2] = ex[q].z; x[q][3] = ex[q].w;
-                    const bool in_row = first + 4 * q + t.lrow < t.row1;
+                    const bool in_row = row + 4 * q + t.lrow < t.row1;
                     float prow = 0.f;
 #pragma unroll
                     for (uint32_t k = 0; k < 4; ++k) {
@@ -1017,6 +1028,9 @@ __device__ __forceinline__ void walk_run(const float* __restrict__ v_all, const 
     }
 }
 
+// STRIPS: the layout has blocks whose tasks take several tiles.  Layouts without such blocks have kernels without the loop over tiles
+// (with it finalize of 1.5 G coordinates takes 3.72 instead of 3.70 ms).
+template <bool STRIPS>
 __global__ __launch_bounds__(256) void k_final1(
     const float* __restrict__ v_all, const TileRow* __restrict__ tiles, const uint32_t* __restrict__ task_block,
     float* __restrict__ rowpart, float* __restrict__ colpart, double* __restrict__ taskpart,
@@ -1029,7 +1043,10 @@ __global__ __launch_bounds__(256) void k_final1(
     const TileRow& m = tiles[block];
     double psum = 0.0, total = 0.0;
     if (m.rows) {
-        psum = tile_pass1(v_all, m, lane, wave, rowpart, colpart, h, rowsum, colsum, eps, eps_low, want_p, total);
+        const Task k = task_of<STRIPS>(m, blockIdx.x);
+        for (uint32_t tile = k.tile; tile < k.last; ++tile)
+            psum += tile_pass1(v_all, m, tile_part(m, k.seg, tile, lane, wave), tile == k.tile, lane, wave, rowpart, colpart, h, rowsum, colsum,
+                               eps, eps_low, want_p, total);
     } else {
         for (uint32_t i = threadIdx.x; i < kBins1; i += 256) h[i] = 0;
         __syncthreads();
@@ -1046,7 +1063,7 @@ __global__ __launch_bounds__(256) void k_final1(
     }
     total = group_sum(total, lane, wave, sums);
     psum = group_sum(psum, lane, wave, sums + 4);             // ends with every wavefront's counts in h
-    const uint32_t n_tasks = m.n_tiles * m.n_segs;
+    const uint32_t n_tasks = m.n_across * m.n_segs;
     const bool single = n_tasks == 1;
     if (threadIdx.x == 0) { st_device(&taskpart[2 * blockIdx.x], total); st_device(&taskpart[2 * blockIdx.x + 1], psum); }
     if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, kBins1);
@@ -1099,8 +1116,8 @@ __global__ __launch_bounds__(256) void k_fold_means(const TileRow* __restrict__ 
 constexpr uint32_t kStage = 320;                      // words per wavefront in which matching keys gather
 
 // F, C: Eq. 7 and Eq. 6 are wanted.
-template <int TT, bool F, bool C>
-__global__ __launch_bounds__(256) void k_final2(
+template <int TT, bool F, bool C, bool STRIPS>
+__global__ __launch_bounds__(256, STRIPS ? 4 : 1) void k_final2(
     const float* __restrict__ v_all, const typename GradIO<TT>::elem* __restrict__ theta, uint64_t theta_numel,
     const TileRow* __restrict__ tiles, const uint32_t* __restrict__ task_block, const float* __restrict__ rvec, const float* __restrict__ cvec,
     float* __restrict__ residpart, Selection sel, uint32_t* __restrict__ arrived, uint32_t* cand, uint32_t* __restrict__ cand_count,
@@ -1131,7 +1148,8 @@ __global__ __launch_bounds__(256) void k_final2(
     for (uint32_t i = threadIdx.x; i < 4 * kBins2; i += 256) h[i] = 0;
     __syncthreads();
     if (m.rows) {
-        const TilePart t = tile_part(m, blockIdx.x, lane, wave);
+        const Task k = task_of<STRIPS>(m, blockIdx.x);
+        TilePart t = tile_part(m, k.seg, k.tile, lane, wave);
         const float* src = v_all + m.state_start;
         const typename IO::elem* tsrc = theta + m.grad_start;
         const uint64_t tleft = theta_numel - m.grad_start;
@@ -1149,13 +1167,19 @@ __global__ __launch_bounds__(256) void k_final2(
                 for (uint32_t q = 0; q < kQuads; ++q) nr[q] = (p + 4 * q)[t.lrow];
             }
         };
-        if (t.full) issue(0);
+        // tiles side by side have one round each, which the loop over the edges takes
+        const bool one = !STRIPS || m.strips == 1;
+        const uint32_t full = one ? t.full : 0, rounds = one ? t.rounds : k.last - k.tile;
+        if (full) issue(0);
         const double mu = F ? rec_in[R_MU] : 0.0;
         // c_j / mu is formed in fp64 (mu may lie below the fp32 normal range); S~ = 0 when mu = 0
         float cm[4];
+        auto load_means = [&]() {
 #pragma unroll
-        for (uint32_t k = 0; k < 4; ++k)
-            cm[k] = (F && k < t.n_ok && mu != 0.0) ? (float)((double)cvec[m.off_c + t.col + k] / mu) : 0.f;
+            for (uint32_t e = 0; e < 4; ++e)
+                cm[e] = (F && e < t.n_ok && mu != 0.0) ? (float)((double)cvec[m.off_c + t.col + e] / mu) : 0.f;
+        };
+        load_means();
         uint32_t* list = cand + m.cand_base + ((uint64_t)(blockIdx.x - m.first_task) * 4 + wave) * cap;
         uint32_t n_cand = 0;                                      // uniform over the wavefront; may grow past the list
         // Matching keys gather in LDS and leave 64 at a time: stores of a few keys each would be waited for together with
@@ -1182,7 +1206,7 @@ __global__ __launch_bounds__(256) void k_final2(
         };
         static_assert(kStage >= 63 + 64 * 4, "a quad of keys and what the last flush left");
         const uint32_t p0 = d.pre[0], p1 = d.pre[1];
-        for (uint32_t i = 0; i < t.full; ++i) {
+        for (uint32_t i = 0; i < full; ++i) {
             float x[kQuads][4], th[kQuads][4], ri[kQuads];
 #pragma unroll
             for (uint32_t q = 0; q < kQuads; ++q) {
@@ -1190,7 +1214,7 @@ __global__ __launch_bounds__(256) void k_final2(
                 IO::unpack(nt[q], th[q]);
                 ri[q] = nr[q];
             }
-            if (i + 1 < t.full) issue(i + 1);
+            if (i + 1 < full) issue(i + 1);
             if (d.n <= 2) {
 #pragma unroll
                 for (uint32_t q = 0; q < kQuads; ++q) {
@@ -1241,11 +1265,13 @@ __global__ __launch_bounds__(256) void k_final2(
             }
             if ((i + 1) % kSubRounds == 0) settle();
         }
-        for (uint32_t i = t.full; t.any && i < t.rounds; ++i) {
-            const uint32_t first = round_row(t, i);
+        for (uint32_t i = full; i < rounds; ++i) {
+            if (!one && i > 0) { t = tile_part(m, k.seg, k.tile + i, lane, wave); load_means(); }
+            if (!t.any) break;
+            const uint32_t round = one ? i : 0, first = round_row(t, round);
             f4 ex[kQuads]; TV et[kQuads];
-            load_edge<BAOC_GRAD_F32>(ex, src, kAnywhere, t, cols, i);
-            if (C) load_edge<TT>(et, tsrc, tleft, t, cols, i);
+            load_edge<BAOC_GRAD_F32>(ex, src, kAnywhere, t, cols, round);
+            if (C) load_edge<TT>(et, tsrc, tleft, t, cols, round);
 #pragma unroll
             for (uint32_t q = 0; q < kQuads; ++q) {
                 const bool in_row = first + 4 * q + t.lrow < t.row1;
@@ -1302,7 +1328,7 @@ __global__ __launch_bounds__(256) void k_final2(
     __syncthreads();
     if (threadIdx.x < 3)
         st_device(&residpart[(uint64_t)blockIdx.x * 4 + threadIdx.x], (float)(((double)red[0][threadIdx.x] + (double)red[1][threadIdx.x]) + ((double)red[2][threadIdx.x] + (double)red[3][threadIdx.x])));
-    const uint32_t n_tasks = m.n_tiles * m.n_segs;
+    const uint32_t n_tasks = m.n_across * m.n_segs;
     const bool single = n_tasks == 1;
     if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, d.n * kBins2);
     if (!arrive_last(arrived + block * kArriveStride, n_tasks)) return;
@@ -1341,24 +1367,27 @@ __global__ __launch_bounds__(256) void k_final3(
         const uint32_t* list = cand + m.cand_base + ((uint64_t)(blockIdx.x - m.first_task) * 4 + wave) * m.cand_cap;
         for (uint32_t i = lane; i < n; i += 64) count3(list[i]);
     } else {
-        const TilePart t = tile_part(m, blockIdx.x, lane, wave);
         const float* src = v_all + m.state_start;
-        for (uint32_t i = 0; t.any && i < t.rounds; ++i) {
-            f4 x[kQuads];
-            if (i < t.full) load_full<BAOC_GRAD_F32>(x, src, t, m.cols, i);
-            else load_edge<BAOC_GRAD_F32>(x, src, kAnywhere, t, m.cols, i);
+        const Task k = task_of<true>(m, blockIdx.x);
+        for (uint32_t tile = k.tile; tile < k.last; ++tile) {
+            const TilePart t = tile_part(m, k.seg, tile, lane, wave);
+            for (uint32_t i = 0; t.any && i < t.rounds; ++i) {
+                f4 x[kQuads];
+                if (i < t.full) load_full<BAOC_GRAD_F32>(x, src, t, m.cols, i);
+                else load_edge<BAOC_GRAD_F32>(x, src, kAnywhere, t, m.cols, i);
 #pragma unroll
-            for (uint32_t q = 0; q < kQuads; ++q) {
-                if (round_row(t, i) + 4 * q + t.lrow >= t.row1) continue;
-                const float xv[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+                for (uint32_t q = 0; q < kQuads; ++q) {
+                    if (round_row(t, i) + 4 * q + t.lrow >= t.row1) continue;
+                    const float xv[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
 #pragma unroll
-                for (uint32_t k = 0; k < 4; ++k)
-                    if (k < t.n_ok) count3(__builtin_bit_cast(uint32_t, xv[k]));
+                    for (uint32_t e = 0; e < 4; ++e)
+                        if (e < t.n_ok) count3(__builtin_bit_cast(uint32_t, xv[e]));
+                }
             }
         }
     }
     __syncthreads();
-    const uint32_t n_tasks = m.n_tiles * m.n_segs;
+    const uint32_t n_tasks = m.n_across * m.n_segs;
     const bool single = n_tasks == 1;
     if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, d.n * kBins3);
     if (!arrive_last(arrived + block * kArriveStride, n_tasks)) return;
@@ -1389,7 +1418,7 @@ struct Plan {
     bool fold_in_step = false;    // the step kernel folds its own partial rows
     std::vector<BlockRow> rows;
     std::vector<TileRow> tiles;   // how finalize walks each block
-    bool any_matrix = false;
+    bool any_matrix = false, any_strips = false;
     uint64_t n_tasks = 0, n_fin = 0;   // workgroups of the finalize passes and of k_fold_means
     std::vector<Part> parts;      // of blocks of more than kDirectRows partial rows
     uint64_t padded = 0;          // coordinates in m / v / g_prev
@@ -1507,7 +1536,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     P.fold_in_step = P.n_prows <= kFoldRows && most_prows <= kFoldBlockRows;
     // Finalize walks blocks with a real matrix shape tile-wise and the rest in runs.  A shape with a
     // single row or column is rank one by construction (F = 0 exactly) and counts as a run.
-    P.tiles.resize(n); P.any_matrix = false; P.n_tasks = 0; P.n_fin = 0;
+    P.tiles.resize(n); P.any_matrix = P.any_strips = false; P.n_tasks = 0; P.n_fin = 0;
     uint64_t n_r = 0, n_c = 0, n_rowpart = 0, n_colpart = 0, n_cand = 0;
     uint64_t tile_coords = kTileCoordsMin;
     while (tile_coords < kTileCoordsMax && tile_coords * kTileTarget < total) tile_coords *= 2;
@@ -1518,13 +1547,19 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
         m = TileRow{};
         if (b.rows < 2 || b.cols < 2) { run_budget += 15360 + 4ull * P.rows[i].n_chunks; continue; }
         m.rows = b.rows; m.cols = b.cols;
-        // columns of a tile: 256, 128 or 64, the widest that leaves at most an eighth of the lanes without a column
+        // columns of a tile: 256, 128 or 64, the widest that leaves at most an eighth of the lanes without a column, or the
+        // narrowest that has rows for wavefronts below each other
         m.wc_log = 2;
-        while (m.wc_log > 0 && align_up(b.cols, 64u << m.wc_log) * 8 > (uint64_t)b.cols * 9) --m.wc_log;
+        while (m.wc_log > 0 && b.rows > (4u >> m.wc_log) * kRoundRows && align_up(b.cols, 64u << m.wc_log) * 8 > (uint64_t)b.cols * 9) --m.wc_log;
         const uint64_t round_rows = (4u >> m.wc_log) * kRoundRows, tile_cols = 64u << m.wc_log;
         m.seg_len = (uint32_t)align_up(std::min<uint64_t>(kTileRowsMax, tile_coords / std::min<uint64_t>(b.cols, tile_cols)), round_rows);
         m.n_tiles = (uint32_t)((b.cols + tile_cols - 1) / tile_cols); m.n_segs = (uint32_t)(((uint64_t)b.rows + m.seg_len - 1) / m.seg_len);
-        matrix_tasks += (uint64_t)m.n_tiles * m.n_segs;
+        // A matrix of so few rows that its tiles have a single round: a task takes as many of them side by side as make up the
+        // smallest tile (16 of 2 x 262,144: finalize 432 -> 245 us, 400 of 8 x 4,096 264 -> 189 us, 4,000 of 2 x 300 852 -> 443 us).
+        m.strips = b.rows > round_rows ? 1 : (uint32_t)std::min<uint64_t>(m.n_tiles, std::max<uint64_t>(1, kTileCoordsMin / (b.rows * tile_cols)));
+        m.n_across = (m.n_tiles + m.strips - 1) / m.strips;
+        P.any_strips |= m.strips > 1;
+        matrix_tasks += (uint64_t)m.n_across * m.n_segs;
     }
     // The tasks' sums (16 bytes each) and the lengths of their candidate lists (16 bytes, only where there are matrices) go where
     // the step's partial rows are, as far as these have room.
@@ -1555,7 +1590,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
         }
         uint64_t tasks;
         if (m.rows == 0) {
-            m.seg_len = (uint32_t)run_coords; m.n_tiles = 1;
+            m.seg_len = (uint32_t)run_coords; m.n_tiles = m.strips = m.n_across = 1;
             tasks = (b.numel + run_coords - 1) / run_coords;
             m.n_segs = (uint32_t)tasks;
         } else {
@@ -1563,7 +1598,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
             m.off_r = n_r; m.off_c = n_c; m.off_rowpart = n_rowpart; m.off_colpart = n_colpart;
             n_r += b.rows; n_c += b.cols;
             n_rowpart += (uint64_t)b.rows * m.n_tiles; n_colpart += (uint64_t)m.n_segs * b.cols;
-            tasks = (uint64_t)m.n_tiles * m.n_segs;
+            tasks = (uint64_t)m.n_across * m.n_segs;
             // one candidate list per wavefront; a block's lists have room for an eighth of its coordinates (the keys that
             // share a selected first digit are a few per cent of a block unless its v is nearly constant; then a list
             // overflows and the last digit takes another walk over v)
@@ -1786,14 +1821,15 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
     // v above which eps stays below a thousandth of sqrt(v) (and v is a normal number)
     const float eps_low = std::max(std::numeric_limits<float>::min(), (float)(1e6 * h->params.eps * h->params.eps));
 
-    hipLaunchKernelGGL(k_final1, dim3(n_tasks), dim3(256), 0, st, v, tiles, task_block, f32_at(P.off_rowpart), f32_at(P.off_colpart),
-                       reinterpret_cast<double*>(residpart), sel, arrived, scan3, rec, epsf, eps_low, want_C);
+    hipLaunchKernelGGL(P.any_strips ? k_final1<true> : k_final1<false>, dim3(n_tasks), dim3(256), 0, st, v, tiles, task_block, f32_at(P.off_rowpart),
+                       f32_at(P.off_colpart), reinterpret_cast<double*>(residpart), sel, arrived, scan3, rec, epsf, eps_low, want_C);
     if (want_F)
         hipLaunchKernelGGL(k_fold_means, dim3((uint32_t)P.n_fin), dim3(256), 0, st, tiles, u32_at(P.off_fin_block), f32_at(P.off_rowpart),
                            f32_at(P.off_colpart), rvec, cvec);
     auto final2 = [&](auto tt, auto f, auto c) {
         constexpr int TT = decltype(tt)::value;
-        hipLaunchKernelGGL((k_final2<TT, decltype(f)::value, decltype(c)::value>), dim3(n_tasks), dim3(256), 0, st,
+        constexpr bool F = decltype(f)::value, C = decltype(c)::value;
+        hipLaunchKernelGGL((P.any_strips ? k_final2<TT, F, C, true> : k_final2<TT, F, C, false>), dim3(n_tasks), dim3(256), 0, st,
                            v, static_cast<const typename GradIO<TT>::elem*>(rp.d_theta_flat), rp.theta_numel, tiles, task_block, rvec, cvec,
                            residpart, sel, arrived, cand, cand_count, scan3, rec, epsf, eps_low);
     };

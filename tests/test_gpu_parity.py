@@ -630,3 +630,19 @@ def test_quantiles_where_candidate_lists_fill_up(env, value, share):
         for got, q in ((stats[i].q10, 0.1), (stats[i].q90, 0.9)):
             want = np.quantile(v, q)
             assert abs(got - want) <= 1e-12 * want, f"block {i}, quantile {q}: {got} {want}"
+
+
+@pytest.mark.parametrize("dtype,pad", [("f32", 1), ("bf16", 1)])
+def test_tiles_side_by_side_at_their_edges(env, dtype, pad):
+    """Matrices of so few rows that a workgroup takes several tiles side by side: up to 16, 17 and 33 of them, widths around a tile
+    and around all of a workgroup's, rows around what one round of its wavefronts covers, and a last block that ends with
+    the parameter buffer."""
+    torch = env["torch"]
+    shapes = [(2, 4095), (2, 4096), (2, 4097), (2, 8193), (3, 2731), (5, 1700), (8, 1025), (16, 511), (16, 512), (16, 513), (17, 256), (17, 513),
+              (17, 385), (31, 300), (32, 257), (33, 129), (33, 193), (64, 129), (65, 129), (15, 256), (2, 300), (4, 257), (2, 65)]
+    blocks = [W._mat(f"m{r}x{c}", r, c) for r, c in shapes]
+    w = W.Workload("strips", blocks, 3, dtype, "cycle", **W.K6)
+    W.layout(w, pad); W.draw_stream_params(w, 13)
+    w.buffer_numel = max(b.offset + b.numel for b in w.blocks)
+    run_both(env, w, 3, seed=12, theta_dtype=torch.float32)
+    run_both(env, w, 2, seed=13, theta_dtype=torch.bfloat16)

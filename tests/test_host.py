@@ -70,6 +70,16 @@ def test_largest_vectors_of_the_static_workspace(n, chunk_groups, chunk_slices, 
     assert ws([(0, n)], grad_dtype=bf16, chunk_groups=chunk_groups, chunk_slices=chunk_slices) <= binding.STATIC_WORKSPACE_BYTES
 
 
+@pytest.mark.parametrize("rows,cols", [(2, 8 << 20), (2, 1 << 20), (4, 4 << 20), (3, 5000003)])
+def test_matrices_of_few_rows_are_not_cut_into_a_task_per_tile(rows, cols):
+    """Finalize keeps 4 bytes per task of its own.  Besides that a matrix takes more than a vector: its row and column
+    means, an owner for every 64 of them, and either candidate lists of 4 bytes per 8 coordinates or the partial sums per tile of 256
+    columns, whichever is more.  A task per tile would be 16 to 120 KB."""
+    n, tiles = rows * cols, -(-cols // 256)
+    more = 4 * (rows + cols) + 4 * (cols // 64 + 2) + max(n // 2, 4 * (rows * tiles + cols))
+    assert ws([(0, n, rows, cols)]) - ws([(0, n)]) <= more + 8192
+
+
 def test_layout_validation():
     def status(blocks, **kw):
         with pytest.raises(binding.BaocError) as e:
