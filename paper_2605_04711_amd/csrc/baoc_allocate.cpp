@@ -272,9 +272,14 @@ constexpr uint64_t kDefaultExactWork = 16'000'000ull;
 constexpr size_t kDefaultFrontCap = 256;
 
 // What the recursion spends its time on: the bounds of a state under up to 28 multiplier pairs and their test for each
-// configuration.  Rooms are formed once per state in plain loops the vector unit takes, magnitudes are bounded once per
-// instance, and only what lies closer to the cutoff than rounding reaches is looked at exactly (62 -> 36 ms on an
-// instance of 686 x 21 with 114,000 states).
+// configuration.  The reduced costs of a level are tabled, rooms are formed once per state in plain loops the vector unit
+// takes, magnitudes are bounded once per instance, and only what lies closer to the cutoff than rounding reaches is looked
+// at exactly (62 -> 36 ms on an instance of 686 x 21 with 114,000 states).
+// A list of fewer than kTableStates does not repay its level's table in the first run: where no budget binds that is the
+// only run and every list holds a single state (20,000 x 6: 43 ms with tables, 33 ms without).  Later runs table every
+// level, since the cutoffs may rise many times (16 instances of 62 x 6 to 686 x 21: a tenth faster).
+constexpr size_t kTableStates = 4;
+constexpr size_t kTableRows = 1u << 18;                  // configurations whose tables are kept from one run to the next (58 MB at most)
 // Loops over the multiplier pairs, four at a time (arrays are padded to whole fours with pairs that never cut).
 typedef double d4 __attribute__((vector_size(32), aligned(8)));
 constexpr size_t kPairs = 4;
@@ -311,26 +316,26 @@ struct Levels {
     // least and largest use of each row by the levels before i, for feasibility and for the clamp
     std::vector<int64_t> preMinW, preMinT, preMaxW, preMaxT;
     // preRC[m][i] = sum over the levels before i of the least reduced cost, minus the budget terms; and the
-    // double images of the multipliers: a bound far from the cutoff is decided in floating point, only a near
-    // miss is evaluated exactly
+    // double images of it ([level][pair]) and of the multipliers: a bound far from the cutoff is decided in floating
+    // point, only a near miss is evaluated exactly
     std::vector<std::vector<i128>> preRC;
-    std::vector<double> Sd, L1d, L2d;
-    std::vector<std::vector<double>> preRCd;
+    std::vector<double> Sd, L1d, L2d, preRCd;
     std::vector<std::vector<State>> lists;
-    // Per level and configuration, ascending in the reduced cost under the first multiplier pair: the configuration, and
-    // its reduced cost under every pair ([configuration][pair]).  pre_of[i * Mp + m] = preRCd[m][i].
-    std::vector<std::vector<uint32_t>> by_cost;
-    std::vector<std::vector<double>> cost;
-    std::vector<double> pre_of;
-    std::vector<double> scale;                           // per pair: magnitude that the terms of a bound stay below
+    // Per tabled level, from row table_at[level] on and ascending in the reduced cost under the first multiplier pair: the
+    // configurations, and their reduced costs under every pair ([row][pair]).
+    std::vector<uint32_t> by_cost;
+    std::vector<double> cost, first_cost;
+    std::vector<size_t> table_at;
+    size_t table_rows = 0;
+    uint64_t runs = 0;
+    std::vector<double> scale;                           // per pair: magnitude that the terms of a bound stay below; empty until needed
     std::vector<State> cand, merged;
     std::vector<std::vector<State>> by_item;
     Stair stair;
 
     Levels(const Instance& inst, const std::vector<Multiplier>& m)
         : I(inst), mult(m), N(inst.N), M(m.size()), Mp((m.size() + kPairs - 1) / kPairs * kPairs), preMinW(N + 1, 0), preMinT(N + 1, 0), preMaxW(N + 1, 0), preMaxT(N + 1, 0),
-          preRC(M, std::vector<i128>(N + 1)), Sd(Mp, 0.0), L1d(Mp, 0.0), L2d(Mp, 0.0), preRCd(M, std::vector<double>(N + 1)), lists(N + 1), by_cost(N), cost(N),
-          pre_of((N + 1) * Mp, 0.0), scale(M, 0.0)
+          preRC(M, std::vector<i128>(N + 1)), Sd(Mp, 0.0), L1d(Mp, 0.0), L2d(Mp, 0.0), preRCd((N + 1) * Mp, 0.0), lists(N + 1)
     {
         for (uint32_t i = 0; i < N; ++i) {
             int64_t lw = kInf64, lt = kInf64, hw = -kInf64, ht = -kInf64;
@@ -351,41 +356,71 @@ struct Levels {
                 preRC[k][i + 1] = preRC[k][i] + best;
             }
             Sd[k] = (double)mult[k].S; L1d[k] = (double)mult[k].L1; L2d[k] = (double)mult[k].L2;
-            for (uint32_t i = 0; i <= N; ++i) preRCd[k][i] = (double)preRC[k][i];
-        }
-        std::vector<double> first;
-        double most_z = 0, most_w = std::fabs((double)I.B1), most_t = std::fabs((double)I.B2);
-        for (uint32_t i = 0; i < N; ++i) {
-            const std::vector<Item>& v = I.items[i];
-            std::vector<uint32_t>& o = by_cost[i];
-            first.resize(v.size()); o.resize(v.size()); cost[i].assign(v.size() * Mp, 0.0);
-            double z = 0, w = 0, t = 0;
-            for (uint32_t k = 0; k < v.size(); ++k) {
-                o[k] = k; first[k] = (double)v[k].phi * Sd[0] + L1d[0] * (double)v[k].w + L2d[0] * (double)v[k].t;
-                z = std::max(z, std::fabs((double)v[k].phi)); w = std::max(w, std::fabs((double)v[k].w)); t = std::max(t, std::fabs((double)v[k].t));
-            }
-            most_z += z; most_w += w; most_t += t;
-            std::sort(o.begin(), o.end(), [&](uint32_t a, uint32_t b) { return first[a] < first[b]; });
-            for (uint32_t j = 0; j < v.size(); ++j)
-                for (size_t m = 0; m < M; ++m)
-                    cost[i][j * Mp + m] = (double)v[o[j]].phi * Sd[m] + L1d[m] * (double)v[o[j]].w + L2d[m] * (double)v[o[j]].t;
-        }
-        for (size_t m = 0; m < M; ++m) {
-            scale[m] = 4.0 * (most_z * Sd[m] + most_w * L1d[m] + most_t * L2d[m]);
-            for (uint32_t i = 0; i <= N; ++i) pre_of[i * Mp + m] = preRCd[m][i];
+            for (uint32_t i = 0; i <= N; ++i) preRCd[i * Mp + k] = (double)preRC[k][i];
         }
     }
 
+    void bound_magnitudes()
+    {
+        double most_z = 0, most_w = std::fabs((double)I.B1), most_t = std::fabs((double)I.B2);
+        for (const std::vector<Item>& v : I.items) {
+            double z = 0, w = 0, t = 0;
+            for (const Item& it : v) {
+                z = std::max(z, std::fabs((double)it.phi)); w = std::max(w, std::fabs((double)it.w)); t = std::max(t, std::fabs((double)it.t));
+            }
+            most_z += z; most_w += w; most_t += t;
+        }
+        scale.resize(M);
+        for (size_t m = 0; m < M; ++m) scale[m] = 4.0 * (most_z * Sd[m] + most_w * L1d[m] + most_t * L2d[m]);
+    }
+
+    // The first row of a level's table, which is built when it is first asked for (and again each time once kTableRows are taken).
+    size_t table(size_t i)
+    {
+        constexpr size_t none = ~(size_t)0;
+        if (table_at.empty()) table_at.assign(N, none);
+        if (table_at[i] != none) return table_at[i];
+        const std::vector<Item>& v = I.items[i];
+        const size_t n = v.size(), at = table_rows;
+        if (by_cost.size() < at + n) { by_cost.resize(at + n); cost.resize((at + n) * Mp); }
+        if (at + n <= kTableRows) { table_at[i] = at; table_rows += n; }
+        first_cost.resize(n);
+        for (uint32_t k = 0; k < n; ++k) {
+            by_cost[at + k] = k; first_cost[k] = (double)v[k].phi * Sd[0] + L1d[0] * (double)v[k].w + L2d[0] * (double)v[k].t;
+        }
+        std::sort(by_cost.begin() + at, by_cost.begin() + at + n, [&](uint32_t a, uint32_t b) { return first_cost[a] < first_cost[b]; });
+        for (size_t j = at; j < at + n; ++j) {
+            const Item& it = v[by_cost[j]];
+            const double z = (double)it.phi, w = (double)it.w, t = (double)it.t;
+            for (size_t m = 0; m < Mp; ++m) cost[j * Mp + m] = z * Sd[m] + L1d[m] * w + L2d[m] * t;
+        }
+        return at;
+    }
+
     // Whether no completion of a state of the levels i.. by the levels before i reaches the cutoff under pair m.
-    bool cut_by(const State& c, size_t m, int i, int64_t cutoff) const
+    bool cut_by(const State& c, size_t m, size_t i, int64_t cutoff) const
     {
         const double a = (double)c.Z * Sd[m], b = L1d[m] * (double)c.W, d = L2d[m] * (double)c.T;
-        const double lhs_d = a + b + d + preRCd[m][i], rhs_d = (double)cutoff * Sd[m];
-        const double tol = 1e-9 * (std::fabs(a) + std::fabs(b) + std::fabs(d) + std::fabs(preRCd[m][i]) + std::fabs(rhs_d));
+        const double lhs_d = a + b + d + preRCd[i * Mp + m], rhs_d = (double)cutoff * Sd[m];
+        const double tol = 1e-9 * (std::fabs(a) + std::fabs(b) + std::fabs(d) + std::fabs(preRCd[i * Mp + m]) + std::fabs(rhs_d));
         if (lhs_d > rhs_d + tol) return true;
         if (lhs_d < rhs_d - tol) return false;
         const i128 lhs = (i128)c.Z * mult[m].S + mult[m].L1 * (i128)c.W + mult[m].L2 * (i128)c.T + preRC[m][i];
         return lhs > (i128)cutoff * mult[m].S;
+    }
+
+    // The candidates of a level whose list is short, into cand, in order.
+    void extend_few(size_t i, int64_t cutoff, int64_t floorW, int64_t floorT)
+    {
+        for (const State& s : lists[i + 1])
+            for (const Item& it : I.items[i]) {
+                const State c{s.Z + it.phi, std::max(s.W + it.w, floorW), std::max(s.T + it.t, floorT)};
+                if (c.W + preMinW[i] > I.B1 || c.T + preMinT[i] > I.B2) continue;
+                bool cut = false;
+                for (size_t m = 0; m < M && !cut; ++m) cut = cut_by(c, m, i, cutoff);
+                if (!cut) cand.push_back(c);
+            }
+        std::sort(cand.begin(), cand.end(), state_before);
     }
 
     // The candidates of a level, kept per configuration, into cand: merged, shortest first, where each run is in order.
@@ -407,10 +442,10 @@ struct Levels {
     // of the assignment on the levels i..N-1.
     int run(int64_t cutoff, uint64_t limit)
     {
+        ++runs;
         uint64_t total = 1;
         // A bound in floating point is within 1e-12 of its scale; what is closer to the cutoff is decided by cut_by.
-        std::vector<double> room(Mp), rhs(Mp, std::numeric_limits<double>::infinity()), tol(Mp, 0.0);
-        for (size_t m = 0; m < M; ++m) { rhs[m] = (double)cutoff * Sd[m]; tol[m] = 1e-12 * (scale[m] + std::fabs(rhs[m])); }
+        std::vector<double> room, rhs, tol;
         lists[N].assign(1, State{0, 0, 0});
         for (int i = (int)N - 1; i >= 0; --i) {
             // A row that no choice for the levels before i can push over its budget any more is not a constraint
@@ -418,10 +453,24 @@ struct Levels {
             // states undercut others.
             const int64_t floorW = I.B1 - preMaxW[i], floorT = I.B2 - preMaxT[i];
             const size_t n_items = I.items[i].size();
+            cand.clear();
+            if (lists[i + 1].size() < kTableStates && (runs == 1 || table_rows >= kTableRows)) {
+                extend_few(i, cutoff, floorW, floorT);
+                if (cand.empty()) return kRunEmpty;
+                keep_undercut_free_sorted(cand, lists[i], stair);
+                total += lists[i].size();
+                if (total > limit) return kRunLimit;
+                continue;
+            }
+            if (scale.empty()) bound_magnitudes();
+            if (room.empty()) {
+                room.resize(Mp); rhs.assign(Mp, std::numeric_limits<double>::infinity()); tol.assign(Mp, 0.0);
+                for (size_t m = 0; m < M; ++m) { rhs[m] = (double)cutoff * Sd[m]; tol[m] = 1e-12 * (scale[m] + std::fabs(rhs[m])); }
+            }
+            const size_t row0 = table(i);
             // Candidates of a long list are kept per configuration and merged, those of a short one sorted (an instance of
             // 686 x 21 with 114,000 states 36 -> 29 ms; where the lists hold a dozen states merging costs a fifth more).
             const bool split = lists[i + 1].size() >= 64;
-            cand.clear();
             if (split) {
                 if (by_item.size() < n_items) by_item.resize(n_items);
                 for (size_t j = 0; j < n_items; ++j) by_item[j].clear();
@@ -432,13 +481,13 @@ struct Levels {
                 // cutoff.  The clamp only raises a state, so what is cut without it is cut with it; the
                 // configurations come in ascending reduced cost under the first pair, which ends the loop.
                 const double z = (double)s.Z, w0 = (double)s.W, t0 = (double)s.T;
-                const double* pre = &pre_of[(size_t)i * Mp];
+                const double* pre = &preRCd[(size_t)i * Mp];
                 room[0] = rhs[0] - (z * Sd[0] + w0 * L1d[0] + t0 * L2d[0] + pre[0]);
                 bool have = false;
                 for (size_t j = 0; j < n_items; ++j) {
-                    const double* q = &cost[i][j * Mp];
+                    const double* q = &cost[(row0 + j) * Mp];
                     if (q[0] > room[0] + tol[0]) break;
-                    const Item& it = I.items[i][by_cost[i][j]];
+                    const Item& it = I.items[i][by_cost[row0 + j]];
                     const int64_t w = s.W + it.w, t = s.T + it.t;
                     const State c{s.Z + it.phi, std::max(w, floorW), std::max(t, floorT)};
                     if (c.W + preMinW[i] > I.B1 || c.T + preMinT[i] > I.B2) continue;

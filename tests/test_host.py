@@ -435,3 +435,22 @@ def test_host_entry_points_under_address_and_ub_sanitizers(tmp_path):
     r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
     assert "allocate: ok" in r.stdout and "partition: ok 400" in r.stdout and "runtime error" not in r.stderr
+
+
+def test_allocation_with_slack_budgets_builds_no_tables(tmp_path):
+    """Where no budget binds every list of the search holds one state and nothing is tabled for the levels: at most 12.5 calls of
+    operator new per block with 4 candidates and 17.5 with 21 (the candidate vectors, mostly; a table per level would
+    add four)."""
+    import shutil
+    import subprocess
+    if shutil.which("g++") is None:
+        pytest.skip("no g++")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    src, exe = os.path.join(root, "paper_2605_04711_amd", "csrc"), str(tmp_path / "alloc_count")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(root, "include"), "-I", src, "-o", exe,
+                    os.path.join(root, "tests", "alloc_count.cpp"), os.path.join(src, "baoc_allocate.cpp")], check=True, capture_output=True, timeout=300)
+    lines = subprocess.run([exe], check=True, capture_output=True, text=True, timeout=120).stdout.split("\n")[:-1]
+    assert len(lines) == 6
+    for line in lines:
+        n, k, rc, calls, _ = line.split()
+        assert int(rc) == 0 and float(calls) <= (12.5 if k == "4" else 17.5), line
