@@ -28,11 +28,17 @@ struct alignas(8) SampleRow {
     uint32_t first_tile;
     uint32_t rows, cols;      // matrix shape of the block, or 0, 0
     uint32_t sub_rows, sub_cols;   // shape of the sampled sub-matrix (product form), or 0, 0 for the flat draw
-    uint32_t pad_;
+    uint32_t tile_len;        // samples per workgroup: the block's samples over as many workgroups as kTile asks for, evenly
 };
 
-constexpr uint32_t kBatch = 8;             // samples per thread, all in flight
-constexpr uint32_t kTile = 256 * kBatch;   // samples per workgroup
+constexpr uint32_t kBatch = 4;             // samples per thread, all in flight
+constexpr uint32_t kTile = 256 * kBatch;   // most samples of a workgroup
+// A block's samples are spread evenly over its workgroups: full workgroups and a small one behind leave the last round of the
+// chip to the small ones (20,000 matrices of 1,190 samples: 143 -> 126 us, 4,097 vectors of 1,200: 45 -> 38 us).
+// Up to kDirect samples are read straight through the index table: with so few, addressing from the first row and column costs more
+// than the table's 8 bytes a sample, and most loads of a batch would be repeats (20,000 matrices of 300 samples: 62 us with
+// batches of eight, 46 with one load after another and a bisection over all blocks, 27 now; 29 with 256 here).
+constexpr uint32_t kDirect = 512;
 
 __host__ __device__ inline uint64_t mix64(uint64_t x)
 {
@@ -41,19 +47,22 @@ __host__ __device__ inline uint64_t mix64(uint64_t x)
     return x ^ (x >> 31);
 }
 
-// The block of a workgroup: 64 candidates compared at a time, two dependent loads for up to 4,096 blocks where a bisection
-// takes twelve.  Every wavefront comes to the same answer.
+// The block of a workgroup.  Every block has at least one of the launch's workgroups, so it lies at most `spare` before the
+// workgroup's own number: exactly there where all blocks have one.  Bisection down to 64 candidates, which are compared at
+// once.  Every wavefront comes to the same answer.
+// A comparison of 64 from the start takes fewer dependent loads but 64 lines each time, which is what many small blocks then wait
+// for (20,000 blocks of 3,000 coordinates and up: 107 -> 98 us a gather of matrices, 184 -> 180 us of vectors).
 __device__ inline uint32_t find_row(const SampleRow* __restrict__ rows, uint32_t n, uint32_t tile)
 {
-    uint32_t lo = 0, len = n;
-    const uint32_t lane = threadIdx.x & 63u;
-    while (len > 1) {
-        const uint32_t step = (len + 63) / 64, at = lane * step;
-        const uint64_t le = __ballot(at < len && rows[lo + at].first_tile <= tile);
-        const uint32_t k = (63u - (uint32_t)__builtin_clzll(le)) * step;     // the first candidate always qualifies
-        lo += k; len = min(step, len - k);
+    const uint32_t lane = threadIdx.x & 63u, spare = gridDim.x - n;
+    uint32_t lo = tile > spare ? tile - spare : 0, len = min(n - 1, tile) - lo + 1;
+    while (len > 64) {
+        const uint32_t half = (len + 1) / 2;
+        if (rows[lo + half].first_tile <= tile) { lo += half; len -= half; } else len = half;
     }
-    return lo;
+    if (len == 1) return lo;
+    const uint64_t le = __ballot(lane < len && rows[lo + lane].first_tile <= tile);
+    return lo + 63u - (uint32_t)__builtin_clzll(le);          // the first candidate always qualifies
 }
 
 // idx[idx_start + j] = src_offset + lo_j + mix(...) % (hi_j - lo_j): absolute positions in the flat buffer
@@ -63,10 +72,10 @@ __global__ __launch_bounds__(256) void k_draw(const SampleRow* __restrict__ rows
     const uint32_t b = find_row(rows, n_rows, blockIdx.x);
     const SampleRow r = rows[b];
     const uint64_t key = mix64(mix64(seed) + b);
-    const uint64_t j0 = (uint64_t)(blockIdx.x - r.first_tile) * kTile;
+    const uint64_t j0 = (uint64_t)(blockIdx.x - r.first_tile) * r.tile_len;
     if (r.sub_rows) {                                      // product form: sample j is (row a, column c) of the sub-matrix
         const uint64_t key_r = mix64(key + 0x52), key_c = mix64(key + 0x43);
-        for (uint64_t j = j0 + threadIdx.x; j < min(r.count, j0 + kTile); j += 256) {
+        for (uint64_t j = j0 + threadIdx.x; j < min(r.count, j0 + r.tile_len); j += 256) {
             const uint64_t a = j / r.sub_cols, c = j - a * r.sub_cols;
             const uint64_t rlo = a * r.rows / r.sub_rows, rhi = (a + 1) * r.rows / r.sub_rows;
             const uint64_t clo = c * r.cols / r.sub_cols, chi = (c + 1) * r.cols / r.sub_cols;
@@ -76,7 +85,7 @@ __global__ __launch_bounds__(256) void k_draw(const SampleRow* __restrict__ rows
         }
         return;
     }
-    for (uint64_t j = j0 + threadIdx.x; j < min(r.count, j0 + kTile); j += 256) {
+    for (uint64_t j = j0 + threadIdx.x; j < min(r.count, j0 + r.tile_len); j += 256) {
         const uint64_t lo = (uint64_t)(((unsigned __int128)j * r.numel) / r.count);
         const uint64_t hi = (uint64_t)(((unsigned __int128)(j + 1) * r.numel) / r.count);
         const uint64_t h = mix64(key + (j + 1) * 0x9E3779B97F4A7C15ull);
@@ -87,9 +96,10 @@ __global__ __launch_bounds__(256) void k_draw(const SampleRow* __restrict__ rows
 // Bound by the cache lines of the source that the samples touch, all of those of a sampled row where one of ten columns
 // is taken.  A matrix sample is a product of rows and columns: sample (a, c) stands idx[first of row a] + idx[c] - idx[0]
 // into the source, so only the table's first row and first column are read, and 8 bytes a sample stay in memory.  A lane has
-// eight samples in flight.
-// Measured (1 % of 3.5 G bf16 coordinates, 35 M samples; before: every table entry read, four samples in flight):
-// 193 -> 150 us (with the step on the sample 335 -> 278; with 1,024 samples per workgroup 279, with 4,096 287).
+// four samples in flight.
+// Measured (1 % of 3.5 G bf16 coordinates, 35 M samples): 193 us with every table entry read, 155 now (with the step on the sample
+// 335 and 270; eight in flight and 2,048 samples per workgroup 274).  1 % of 1,086 bf16 vectors of 233,493: 53 us with every
+// entry read one after another, 65 with eight in flight, 50 now.
 template <typename T>
 __global__ __launch_bounds__(256) void k_gather(const SampleRow* __restrict__ rows, uint32_t n_rows,
                                                 const uint64_t* __restrict__ idx, const T* __restrict__ src,
@@ -97,17 +107,21 @@ __global__ __launch_bounds__(256) void k_gather(const SampleRow* __restrict__ ro
 {
     const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane((int)find_row(rows, n_rows, blockIdx.x));
     const SampleRow r = rows[b];
-    const uint64_t j0 = (uint64_t)(blockIdx.x - r.first_tile) * kTile;
-    const uint32_t n = (uint32_t)min(r.count - j0, (uint64_t)kTile);
+    const uint64_t j0 = (uint64_t)(blockIdx.x - r.first_tile) * r.tile_len;
+    const uint32_t n = (uint32_t)min(r.count - j0, (uint64_t)r.tile_len);
     const uint64_t* ix = idx + r.idx_start;
     T* out = dst + (r.dst_offset + j0);
+    if (n <= kDirect) {
+        for (uint32_t t = threadIdx.x; t < n; t += 256) out[t] = src[ix[j0 + t]];
+        return;
+    }
     uint32_t t[kBatch];
     uint64_t at[kBatch];
     T x[kBatch];
 #pragma unroll
     for (uint32_t q = 0; q < kBatch; ++q) t[q] = min(threadIdx.x + 256 * q, n - 1);
     if (r.sub_rows) {
-        const uint64_t a0 = j0 / r.sub_cols, c0 = j0 - a0 * r.sub_cols, first = ix[0];
+        const uint64_t a0 = j0 == 0 ? 0 : j0 / r.sub_cols, c0 = j0 - a0 * r.sub_cols, first = ix[0];
         const uint32_t sc = r.sub_cols;
         uint32_t a[kBatch];                                // row of sample j0 + t, from a0
         if (sc >= kTile) {
@@ -160,8 +174,10 @@ int make_rows(const baoc_block* blocks, uint32_t n, double ratio, std::vector<Sa
             const uint64_t sr = (uint64_t)rr, sc = std::min<uint64_t>(b.cols, (r.count + sr - 1) / sr);
             if (sr >= 2 && sc >= 2) { r.sub_rows = (uint32_t)sr; r.sub_cols = (uint32_t)sc; r.count = sr * sc; }
         }
-        r.idx_start = idx; r.first_tile = (uint32_t)tiles; r.pad_ = 0;
-        dst += r.count; idx += r.count; tiles += (r.count + kTile - 1) / kTile;
+        r.idx_start = idx; r.first_tile = (uint32_t)tiles;
+        const uint64_t n_tiles_here = (r.count + kTile - 1) / kTile;
+        r.tile_len = (uint32_t)((r.count + n_tiles_here - 1) / n_tiles_here);
+        dst += r.count; idx += r.count; tiles += n_tiles_here;
         if (tiles > 0x7fffffffull) return BAOC_ERR_UNSUPPORTED;
         end = std::max(end, b.offset + b.numel);
     }

@@ -209,3 +209,25 @@ def test_gather_tiles_at_their_edges(env, dtype):  # noqa: F811
             out = smp.gather(src)
             for i, (o, n, _, _) in enumerate(smp.compact_blocks):
                 assert torch.equal(out[o:o + n], src[smp.indices(i)]), f"block {i}, ratio {ratio}"
+
+
+@pytest.mark.parametrize("count,size", [(1, 1), (63, 700), (64, 9000), (65, 20), (129, 9000), (200, 5), (1500, 40)])
+@pytest.mark.parametrize("big", [0, 1, 3])
+def test_gather_finds_the_block_of_every_workgroup(env, count, size, big):  # noqa: F811
+    """Few and many blocks of one workgroup or several, alone and with large blocks in front, in the middle and behind (a
+    workgroup's number is then far from its block's); sample counts around the 512 that are read through the index table."""
+    torch, binding = env["torch"], env["binding"]
+    sizes = [(size + i % 3, 0, 0) for i in range(count)] + [(n, 0, 0) for n in (511, 512, 513)] + [(512, 32, 16), (513, 27, 19), (510, 2, 255)]
+    for at in (0, len(sizes) // 2, len(sizes))[:big]:
+        sizes.insert(at, (300000, 600, 500))
+    blocks, at = [], 1
+    for n, r, c in sizes:
+        blocks.append((at, n, r, c)); at += n + 1
+    src = torch.randn(at, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(4))
+    for ratio in (1.0, 0.07):
+        smp = binding.Sampler(blocks, ratio, seed=6)
+        out = smp.gather(src)
+        for i, (o, n, _, _) in enumerate(smp.compact_blocks):
+            assert torch.equal(out[o:o + n], src[smp.indices(i)]), f"block {i}, ratio {ratio}"
+            ix = smp.indices(i)
+            assert int(ix.min()) >= blocks[i][0] and int(ix.max()) < blocks[i][0] + blocks[i][1]
