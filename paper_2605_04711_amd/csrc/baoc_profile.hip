@@ -1459,6 +1459,12 @@ constexpr uint64_t kTileCoordsMin = 8192, kTileCoordsMax = 262144, kTileTarget =
 // 4,096: finalize 4.13 -> 1.26 ms, one of 300,000 x 4 next to 566 M coordinates 5.30 -> 1.59 ms; with 2,048 rows 1.37 and 1.61 ms,
 // with 1,024 1.41 and 1.62 ms).
 constexpr uint64_t kTileRowsMax = kTileCoordsMax / 64;
+// Coordinates of a run of a block without a matrix shape, in layouts whose tiles are larger.  Blocks of very different sizes leave the last
+// workgroups few and long, most of all where many coordinates share a key and the histogram's bins are what everything waits for
+// (finalize of 3,000 vectors, 300 M coordinates, 70 % of them zero: 2.64 ms with one chunk at a time, 3.66 with runs of
+// 262,144, 3.03 with 131,072, 2.62 with 65,536, 2.47 with 32,768; dense 1.20, 0.99, 0.91, 0.92 and 0.95).  A single block of
+// 1.2 G coordinates takes 2.43 ms with 262,144 and 2.48 with 65,536, since all its runs meet in one histogram and one counter.
+constexpr uint64_t kRunCoords = 32768;
 
 static int check_params(const baoc_profile_params* p)
 {
@@ -1567,14 +1573,20 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     const uint64_t partial_bytes = P.n_prows * kNumSums * 4;
     auto sums_fit = [&](uint64_t tasks) { return task_bytes(tasks) <= partial_bytes; };
     auto counts_fit = [&](uint64_t tasks) { return 2 * task_bytes(tasks) <= partial_bytes; };
-    // Coordinates of a run.  A run takes 4 bytes in task_block and up to 32 for what does not fit there (with large chunks the
-    // partial rows are few).  Runs are lengthened until that is within run_budget, 15 KB per block and 4 bytes per chunk, which keeps
-    // the workspace of a layout from growing with the number of runs whatever the launch shape.
-    uint64_t run_coords = tile_coords;
-    for (; run_coords < (1u << 30); run_coords = align_up(run_coords * 5 / 4, 1024)) {
+    // Coordinates of a run: kRunCoords, or as many as leave a block 2,048 runs; and at least `least`.  A run takes 4 bytes in
+    // task_block and up to 32 for what does not fit the partial rows (with large chunks these are few).  Runs are lengthened
+    // until that is within run_budget, 15 KB per block and 4 bytes per chunk, which keeps the workspace of a layout from growing
+    // with the number of runs whatever the launch shape.
+    uint64_t least = kTileCoordsMin;
+    auto run_coords = [&](uint64_t numel) {
+        uint64_t r = std::min(tile_coords, kRunCoords);
+        while (r < tile_coords && r * kTileTarget < numel) r *= 2;
+        return std::max(r, least);
+    };
+    for (; least < (1u << 30); least = align_up(least * 5 / 4, 1024)) {
         uint64_t runs = 0;
         for (uint32_t i = 0; i < n; ++i)
-            if (P.tiles[i].rows == 0) runs += (blocks[i].numel + run_coords - 1) / run_coords;
+            if (P.tiles[i].rows == 0) { const uint64_t r = run_coords(blocks[i].numel); runs += (blocks[i].numel + r - 1) / r; }
         const uint64_t tasks = matrix_tasks + runs;
         if (runs * (4 + (sums_fit(tasks) ? 0 : 16) + (matrix_tasks == 0 || counts_fit(tasks) ? 0 : 16)) <= run_budget) break;
     }
@@ -1590,8 +1602,8 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
         }
         uint64_t tasks;
         if (m.rows == 0) {
-            m.seg_len = (uint32_t)run_coords; m.n_tiles = m.strips = m.n_across = 1;
-            tasks = (b.numel + run_coords - 1) / run_coords;
+            m.seg_len = (uint32_t)run_coords(b.numel); m.n_tiles = m.strips = m.n_across = 1;
+            tasks = (b.numel + m.seg_len - 1) / m.seg_len;
             m.n_segs = (uint32_t)tasks;
         } else {
             P.any_matrix = true;

@@ -646,3 +646,34 @@ def test_tiles_side_by_side_at_their_edges(env, dtype, pad):
     w.buffer_numel = max(b.offset + b.numel for b in w.blocks)
     run_both(env, w, 3, seed=12, theta_dtype=torch.float32)
     run_both(env, w, 2, seed=13, theta_dtype=torch.bfloat16)
+
+
+@pytest.mark.parametrize("share", [0.0, 0.6])
+def test_runs_of_several_lengths_in_one_layout(env, share):
+    """A vector large enough for runs of 131,072 coordinates next to vectors around 32,768, 65,536 and 131,072 of them, a share
+    of the coordinates zero: quantiles and C against fp64 on the same v.  The p of a block are added in fp64 and a thread's share
+    of Eq. 6 four terms at a time, the lanes of a workgroup in fp32: 12 roundings of 2^-24 on each of the two sums behind C, and
+    1e-6 for p itself."""
+    torch, binding = env["torch"], env["binding"]
+    blocks, at = [], 3
+    for n in (32767, 32768, 32769, 65537, 150_000_001, 131072, 131073, 1, 200000):
+        blocks.append((at, n)); at += n + 1
+    gen = torch.Generator(device="cuda:0").manual_seed(21)
+    grad = torch.rand(at, device="cuda:0", generator=gen) + 0.5
+    theta = 0.02 * torch.randn(at, device="cuda:0", generator=gen)
+    if share:
+        grad[torch.rand(at, device="cuda:0", generator=gen) < share] = 0.0
+    prof = binding.Profiler(blocks, binding.default_profile_params(eps=1e-4))
+    prof.step(grad)
+    stats, _ = prof.finalize(theta=theta)
+    for i, (o, n) in enumerate(blocks):
+        v = prof.state(i)[1]
+        s = torch.sort(v).values
+        for got, q in ((stats[i].q10, 0.1), (stats[i].q90, 0.9)):
+            lo = int(np.floor(q * (n - 1))); frac = q * (n - 1) - lo
+            a, b = float(s[lo].double()), float(s[min(lo + 1, n - 1)].double())
+            assert abs(got - (a + frac * (b - a))) <= 1e-12 * b, f"block {i}, quantile {q}"
+        p, t = 1.0 / (v.double().sqrt() + 1e-4), theta[o:o + n].double()
+        C = (((p / p.mean() - 1.0) * t).norm() / (t.norm() + 1e-4)).item()
+        assert abs(stats[i].C - C) <= 2e-6 * C + 1e-7, f"block {i}: {stats[i].C} {C}"
+        del s, p, t
