@@ -673,7 +673,7 @@ __device__ __forceinline__ void count_match(uint32_t* h, const Prefixes& d, uint
 // The digit of one rank, by one wavefront: the bin of its histogram that holds the rank, and the rank inside the bin.
 // Bins i * 64 + lane of the NB are read by `load`.
 template <uint32_t NB, typename L>
-__device__ __forceinline__ uint2 pick_bin(uint32_t rank, uint32_t lane, L load)
+__device__ __forceinline__ uint3 pick_bin(uint32_t rank, uint32_t lane, L load)
 {
     uint32_t c[NB / 64];
 #pragma unroll
@@ -703,7 +703,7 @@ __device__ __forceinline__ uint2 pick_bin(uint32_t rank, uint32_t lane, L load)
     }
     const uint64_t holders = __ballot(rank >= incl - mine && rank < incl);
     const uint32_t owner = holders ? (uint32_t)__builtin_ctzll(holders) : 63u;
-    return uint2{at + owner, rank - (uint32_t)__builtin_amdgcn_readlane((int)(incl - mine), owner)};
+    return uint3{at + owner, rank - (uint32_t)__builtin_amdgcn_readlane((int)(incl - mine), owner), (uint32_t)__builtin_amdgcn_readlane((int)mine, owner)};
 }
 
 struct Selection { uint32_t *hist, *prefix, *rank; };     // per block: histogram words; four key prefixes; four ranks within them
@@ -713,7 +713,7 @@ struct Selection { uint32_t *hist, *prefix, *rank; };     // per block: histogra
 // Counts fit 32 bits (numel < 2^32).
 template <int PASS>
 __device__ __forceinline__ void pick_digit(const Selection& sel, const TileRow& row, uint32_t block, bool single, const uint32_t* h,
-                                           uint32_t lane, uint32_t wave, double* rec)
+                                           uint32_t lane, uint32_t wave, double* rec, uint32_t* n_keys = nullptr)
 {
     constexpr uint32_t NB = PASS == 1 ? kBins1 : (PASS == 2 ? kBins2 : kBins3);
     const uint32_t id = block * 4 + wave;
@@ -724,12 +724,13 @@ __device__ __forceinline__ void pick_digit(const Selection& sel, const TileRow& 
         slot = wave == 0 ? d.slot_of[0] : (wave == 1 ? d.slot_of[1] : (wave == 2 ? d.slot_of[2] : d.slot_of[3]));
         rank = sel.rank[id]; prefix = sel.prefix[id];
     }
-    const uint2 p = single ? pick_bin<NB>(rank, lane, [&](uint32_t i) { return h[slot * NB + i]; })
+    const uint3 p = single ? pick_bin<NB>(rank, lane, [&](uint32_t i) { return h[slot * NB + i]; })
                            : pick_bin<NB>(rank, lane, [&](uint32_t i) { return ld_device(hist + slot * NB + i); });
     __syncthreads();                                          // all four have read the prefixes and the histogram
     prefix = PASS == 1 ? p.x : ((prefix << (PASS == 2 ? kBits2 : kBits3)) | p.x);
     if (lane == 0) {
         if (PASS < 3) { sel.prefix[id] = prefix; sel.rank[id] = p.y; }
+        if (PASS == 1) { n_keys[2 * wave] = prefix; n_keys[2 * wave + 1] = p.z; }
         else rec[R_ORDER + wave] = (double)__builtin_bit_cast(float, prefix);
     }
     if (!single)
@@ -988,11 +989,11 @@ __device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, co
 // 16 exist) with the loads of a round issued together.  Runs start on a multiple of 4 coordinates, so a quad of v is
 // aligned and inside the padded state; theta is read at any alignment and not past the block's last coordinate.
 template <int TT, bool THETA, typename Fn>
-__device__ __forceinline__ void walk_run(const float* __restrict__ v_all, const typename GradIO<TT>::elem* __restrict__ theta, const TileRow& m, Fn f)
+__device__ __forceinline__ void walk_run(const float* __restrict__ v_all, const typename GradIO<TT>::elem* __restrict__ theta, const TileRow& m, uint32_t len, Fn f)
 {
     typedef GradIO<TT> IO;
-    const uint64_t e0 = (uint64_t)(blockIdx.x - m.first_task) * m.seg_len;
-    const uint32_t n = (uint32_t)min((uint64_t)m.seg_len, m.numel - e0);
+    const uint64_t e0 = (uint64_t)(blockIdx.x - m.first_task) * len;
+    const uint32_t n = e0 < m.numel ? (uint32_t)min((uint64_t)len, m.numel - e0) : 0u;
     const float* src = v_all + m.state_start + e0;
     const typename IO::elem* tsrc = theta + (m.grad_start + e0);
     for (uint32_t at = threadIdx.x * 4; at < n; at += 4096) {
@@ -1050,7 +1051,7 @@ __global__ __launch_bounds__(256) void k_final1(
     } else {
         for (uint32_t i = threadIdx.x; i < kBins1; i += 256) h[i] = 0;
         __syncthreads();
-        walk_run<BAOC_GRAD_F32, false>(v_all, nullptr, m, [&](const float x[4], const float*, uint32_t n) {
+        walk_run<BAOC_GRAD_F32, false>(v_all, nullptr, m, m.seg_len, [&](const float x[4], const float*, uint32_t n) {
             float prow = 0.f;
 #pragma unroll
             for (uint32_t k = 0; k < 4; ++k)
@@ -1069,7 +1070,8 @@ __global__ __launch_bounds__(256) void k_final1(
     if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, kBins1);
     if (!arrive_last(arrived + block * kArriveStride, n_tasks)) return;
     double* rec = rec_all + (uint64_t)block * kRecDoubles;
-    pick_digit<1>(sel, m, block, single, h, lane, wave, rec);
+    __shared__ uint32_t n_keys[8];                        // per rank: first digit, keys that share it
+    pick_digit<1>(sel, m, block, single, h, lane, wave, rec, n_keys);
     double a = 0.0, p = 0.0;
     for (uint32_t i = threadIdx.x; i < n_tasks; i += 256) {
         a += ld_device(&taskpart[2 * (m.first_task + i)]);
@@ -1081,7 +1083,18 @@ __global__ __launch_bounds__(256) void k_final1(
         // mu is the mean of the row means to the last bit of what they are made of: the tiles' row sums, added in fp64
         if (m.rows) rec[R_MU] = a / ((double)m.rows * (double)m.cols);
         rec[R_PSUM] = p;
-        scan3[block] = m.rows == 0;                       // raised by k_final2 where a candidate list overflows
+        // Where the keys that carry a selected first digit would fill three quarters of the lists of a whole tile, the block goes without
+        // lists: its keys are counted as they come, and the last digit takes another walk over v, which is cheaper from about
+        // there on.  k_final2 raises the flag where a single list overflows.  (39 blocks of 2,405 x 3,443, 20 % of them zero: finalize 2.18 ms with lists that overflow and
+        // a second walk over their tiles, 1.55 with the keys past their end counted at once, 1.32 now; 4,096 x 4,096 1.70, 1.20, 1.02.)
+        uint64_t keys = 0;
+        for (uint32_t t = 0; t < 4; ++t) {
+            bool fresh = true;
+            for (uint32_t u = 0; u < t; ++u) fresh = fresh && n_keys[2 * u] != n_keys[2 * t];
+            if (fresh) keys += n_keys[2 * t + 1];
+        }
+        const uint64_t part = (uint64_t)min(m.rows, m.seg_len) * min(m.cols, m.strips * (64u << m.wc_log));   // coordinates of a whole task
+        scan3[block] = m.rows == 0 || keys * part > 3ull * m.cand_cap * m.numel;
     }
 }
 
@@ -1154,7 +1167,9 @@ __global__ __launch_bounds__(256, STRIPS ? 4 : 1) void k_final2(
         const typename IO::elem* tsrc = theta + m.grad_start;
         const uint64_t tleft = theta_numel - m.grad_start;
         const float* rr = rvec + m.off_r;
-        const uint32_t cols = scalar_u32(m.cols), cap = scalar_u32(m.cand_cap);
+        // no room where the first pass has found the block to go without lists (or a list of this pass overflowed meanwhile, which comes
+        // to the same: the last digit is then not taken from the lists)
+        const uint32_t cols = scalar_u32(m.cols), cap = scalar_u32(scan3[block] ? 0u : m.cand_cap);
         f4 nx[kQuads]; TV nt[kQuads]; float nr[kQuads];
 #pragma unroll
         for (uint32_t q = 0; q < kQuads; ++q) { nx[q] = f4{0.f, 0.f, 0.f, 0.f}; nt[q] = TV{}; nr[q] = 0.f; }
@@ -1191,9 +1206,7 @@ __global__ __launch_bounds__(256, STRIPS ? 4 : 1) void k_final2(
             if (hit) stage[n_stage + at] = bits;
             n_stage += (uint32_t)__builtin_popcountll(hits);
         };
-        // Whole sets of 64 go to the list; what is left moves to the front.  Keys for which the list has no room are counted
-        // here instead of in another walk over the tile (4 blocks of 4,096 x 4,096 equal values: finalize 821 -> 759 us; 164 M
-        // coordinates, an embedding with 60 % of its rows untouched the largest block: 1316 -> 1186 us).
+        // Whole sets of 64 go to the list; what is left moves to the front.  Keys for which the list has no room are counted here.
         auto flush = [&](bool all) {
             const uint32_t n = all ? n_stage : n_stage & ~63u;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // lanes read what other lanes staged
@@ -1308,7 +1321,7 @@ __global__ __launch_bounds__(256, STRIPS ? 4 : 1) void k_final2(
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");    // lanes read what other lanes stored
         for (uint32_t i = lane; i < min(n_cand, cap); i += 64) count2(list[i]);
     } else {
-        walk_run<TT, C>(v_all, theta, m, [&](const float x[4], const float th[4], uint32_t n) {
+        walk_run<TT, C>(v_all, theta, m, m.seg_len, [&](const float x[4], const float th[4], uint32_t n) {
             float yn = 0.f, yd = 0.f;
 #pragma unroll
             for (uint32_t k = 0; k < 4; ++k)
@@ -1356,38 +1369,21 @@ __global__ __launch_bounds__(256) void k_final3(
     const Prefixes d = distinct_prefixes(sel.prefix, block);
     auto count3 = [&](uint32_t bits) { count_match(h, d, kBins3, (bits & 0x7fffffffu) >> kShift2, bits & (kBins3 - 1)); };
     __syncthreads();
-    if (m.rows == 0) {
-        walk_run<BAOC_GRAD_F32, false>(v_all, nullptr, m, [&](const float x[4], const float*, uint32_t n) {
-#pragma unroll
-            for (uint32_t k = 0; k < 4; ++k)
-                if (k < n) count3(__builtin_bit_cast(uint32_t, x[k]));
-        });
-    } else if (!scan3[block]) {
+    const uint32_t n_tasks = m.n_across * m.n_segs;
+    if (m.rows && !scan3[block]) {
         const uint32_t n = min(cand_count[blockIdx.x * 4 + wave], m.cand_cap);
         const uint32_t* list = cand + m.cand_base + ((uint64_t)(blockIdx.x - m.first_task) * 4 + wave) * m.cand_cap;
         for (uint32_t i = lane; i < n; i += 64) count3(list[i]);
     } else {
-        const float* src = v_all + m.state_start;
-        const Task k = task_of<true>(m, blockIdx.x);
-        for (uint32_t tile = k.tile; tile < k.last; ++tile) {
-            const TilePart t = tile_part(m, k.seg, tile, lane, wave);
-            for (uint32_t i = 0; t.any && i < t.rounds; ++i) {
-                f4 x[kQuads];
-                if (i < t.full) load_full<BAOC_GRAD_F32>(x, src, t, m.cols, i);
-                else load_edge<BAOC_GRAD_F32>(x, src, kAnywhere, t, m.cols, i);
+        // a matrix is no more than its coordinates here, shared evenly over its tasks
+        const uint32_t len = m.rows ? (uint32_t)((m.numel + n_tasks - 1) / n_tasks + 3) & ~3u : m.seg_len;
+        walk_run<BAOC_GRAD_F32, false>(v_all, nullptr, m, len, [&](const float x[4], const float*, uint32_t n) {
 #pragma unroll
-                for (uint32_t q = 0; q < kQuads; ++q) {
-                    if (round_row(t, i) + 4 * q + t.lrow >= t.row1) continue;
-                    const float xv[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
-#pragma unroll
-                    for (uint32_t e = 0; e < 4; ++e)
-                        if (e < t.n_ok) count3(__builtin_bit_cast(uint32_t, xv[e]));
-                }
-            }
-        }
+            for (uint32_t k = 0; k < 4; ++k)
+                if (k < n) count3(__builtin_bit_cast(uint32_t, x[k]));
+        });
     }
     __syncthreads();
-    const uint32_t n_tasks = m.n_across * m.n_segs;
     const bool single = n_tasks == 1;
     if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, d.n * kBins3);
     if (!arrive_last(arrived + block * kArriveStride, n_tasks)) return;
@@ -1560,6 +1556,8 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
         const uint64_t round_rows = (4u >> m.wc_log) * kRoundRows, tile_cols = 64u << m.wc_log;
         m.seg_len = (uint32_t)align_up(std::min<uint64_t>(kTileRowsMax, tile_coords / std::min<uint64_t>(b.cols, tile_cols)), round_rows);
         m.n_tiles = (uint32_t)((b.cols + tile_cols - 1) / tile_cols); m.n_segs = (uint32_t)(((uint64_t)b.rows + m.seg_len - 1) / m.seg_len);
+        // even shares of the rows (39 blocks of 2,405 x 3,443 without theta: 750 -> 676 us, with 70 % zeros 3.03 -> 2.72 ms)
+        m.seg_len = (uint32_t)align_up(((uint64_t)b.rows + m.n_segs - 1) / m.n_segs, round_rows);
         // A matrix of so few rows that its tiles have a single round: a task takes as many of them side by side as make up the
         // smallest tile (16 of 2 x 262,144: finalize 432 -> 245 us, 400 of 8 x 4,096 264 -> 189 us, 4,000 of 2 x 300 852 -> 443 us).
         m.strips = b.rows > round_rows ? 1 : (uint32_t)std::min<uint64_t>(m.n_tiles, std::max<uint64_t>(1, kTileCoordsMin / (b.rows * tile_cols)));

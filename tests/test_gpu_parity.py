@@ -604,21 +604,21 @@ def test_eq6_and_eq7_sums_of_tall_matrices_in_a_large_layout(env, rows, cols):
 
 
 @pytest.mark.parametrize("value", [0.0, 3.0])
-@pytest.mark.parametrize("share", [0.05, 0.11, 0.125, 0.13, 0.3, 1.0])
+@pytest.mark.parametrize("share", [0.05, 0.09, 0.1, 0.11, 0.125, 0.13, 0.3, 1.0])
 def test_quantiles_where_candidate_lists_fill_up(env, value, share):
     """A share of the coordinates with one and the same v, at the low or the high end, scattered or in one piece (some
     wavefronts then have nothing but such keys and others none): the lists hold an eighth of a block, so some of them just fit,
     some overflow by a few keys and some by nearly all.  The quantiles are those of v itself, and a second finalize gives the
     same bits."""
     torch, binding = env["torch"], env["binding"]
-    shapes = [(513, 300), (64, 64), (2, 5000), (4000, 5), (1030, 257)] * 2
+    shapes = [(513, 300), (64, 64), (2, 5000), (4000, 5), (1030, 257), (2405, 343)] * 2
     blocks, at = [], 1
     for r, c in shapes:
         blocks.append((at, r * c, r, c)); at += r * c + 1
     gen = torch.Generator(device="cuda:0").manual_seed(11)
     grad = torch.rand(at, device="cuda:0", generator=gen) + 0.5
     for i, (o, n, _, _) in enumerate(blocks):
-        hit = torch.rand(n, device="cuda:0", generator=gen) < share if i < 5 else torch.arange(n, device="cuda:0") < share * n
+        hit = torch.rand(n, device="cuda:0", generator=gen) < share if i < 6 else torch.arange(n, device="cuda:0") < share * n
         grad[o:o + n][hit] = value
     prof = binding.Profiler(blocks, binding.default_profile_params())
     prof.step(grad)
