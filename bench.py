@@ -134,7 +134,8 @@ def sampled_windows(a, w, ring, theta, params, mem, tc, b_mem, cap):
         window(a.warmup)
     total, g_ms, s_ms, rest_ms = window(K)
     g_avg = sum(g_ms) / len(g_ms); s_avg = sum(s_ms[1:]) / max(1, len(s_ms) - 1)
-    gather_bytes = samples * 2 * esz                      # element read, element written
+    flat = sum(b[1] for b in smp.compact_blocks if b[2] == 0)                  # samples of blocks without a matrix shape
+    gather_bytes = samples * 2 * esz + flat * 8           # element read, element written; those have their index read as well
     return {"metric": "gradient elements covered/sec with sparse sampling", "value": K * D / total, "unit": "elements/s",
             "n_gpus": 1, "steps": K, "warmup": a.warmup, "ms_per_step": total * 1e3 / K, "higher_is_better": True,
             "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",

@@ -175,14 +175,12 @@ template <> struct GradIO<BAOC_GRAD_F32> {
     __device__ static __forceinline__ vec4 loadv(const elem* p) { return ld_stream<f4>(p); }
     __device__ static __forceinline__ vec4 loadv_any(const elem* p) { return ld_stream<vec4_any>(p); }
     __device__ static __forceinline__ void unpack(vec4 t, float g[4]) { g[0] = t.x; g[1] = t.y; g[2] = t.z; g[3] = t.w; }
-    __device__ static __forceinline__ void load4(const elem* p, float g[4]) { unpack(loadv(p), g); }
     __device__ static __forceinline__ float load1(const elem* p) { return *p; }
     __device__ static __forceinline__ void store4(elem* p, const float g[4])
     {
         f4 t = {g[0], g[1], g[2], g[3]};
         st_stream<f4>(p, t);
     }
-    static constexpr uintptr_t kAlignMask = 15;
 };
 
 template <> struct GradIO<BAOC_GRAD_BF16> {
@@ -196,7 +194,6 @@ template <> struct GradIO<BAOC_GRAD_BF16> {
         g[0] = __builtin_bit_cast(float, t.x << 16); g[1] = __builtin_bit_cast(float, t.x & 0xffff0000u);
         g[2] = __builtin_bit_cast(float, t.y << 16); g[3] = __builtin_bit_cast(float, t.y & 0xffff0000u);
     }
-    __device__ static __forceinline__ void load4(const elem* p, float g[4]) { unpack(loadv(p), g); }
     __device__ static __forceinline__ float load1(const elem* p) { return bf16_widen(*p); }
     // g holds exact bf16 values: the upper half of each word is the stored pattern
     __device__ static __forceinline__ void store4(elem* p, const float g[4])
@@ -206,7 +203,6 @@ template <> struct GradIO<BAOC_GRAD_BF16> {
         t.y = (__builtin_bit_cast(uint32_t, g[2]) >> 16) | (__builtin_bit_cast(uint32_t, g[3]) & 0xffff0000u);
         st_stream<u2>(p, t);
     }
-    static constexpr uintptr_t kAlignMask = 7;
 };
 
 // ---------------------------------------------------------------------------
@@ -414,7 +410,7 @@ __global__ __launch_bounds__(64 * NW) void k_step(
     // Sixteen sums held by sixteen lanes: a halving exchange inside each row of 16 lanes (after the
     // level that pairs lanes differing in bit b, a lane keeps only the sums whose index has its own
     // bit b) leaves lane l of a row with that row's total of sum l & 15, in 8+4+2+1 DPP additions.
-    // Then LDS (4 wavefronts x 4 rows) -> one partial row per chunk, in a fixed order.
+    // Then LDS (4 wavefronts x 4 rows) -> one partial row per workgroup, in a fixed order.
     static_assert(kNumSums == 16, "the exchange below is written for 16 sums");
     {
         const bool b3 = lane & 8u, b2 = lane & 4u, b1 = lane & 2u, b0 = lane & 1u;
@@ -763,7 +759,8 @@ __device__ __forceinline__ double group_sum(double x, uint32_t lane, uint32_t wa
 // once, and narrow or odd-sized matrices keep their lanes busy.  Loads are issued one round of kQuads * 4 rows
 // ahead of their use; rounds with a missing row or column load for themselves.
 // In the second pass the keys that carry a selected first digit (a few per cent) are appended to a candidate list
-// per wavefront; the second digit is counted on the list at the end, the last digit by k_final3.
+// per wavefront; the second digit is counted on the list at the end, the last digit by k_final3.  Keys that find no room are
+// counted as they come, and the last digit then takes a walk over v.
 // Large layouts are bound by HBM with the vector ALUs close behind, small ones by the number of wavefronts in flight.
 // Measured (first / second pass, us; before: one wavefront per 256 x 256 tile, scalar loads where a row is not a
 // multiple of 4, keys stored as they were found; now with the folds of the last workgroup): 25.6 M coordinates of
@@ -1445,8 +1442,9 @@ static uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 // 2,000 rows of 100 blocks 14.2 instead of 13.4, 2,048 rows of 16 blocks 15.5 instead of 13.5.
 constexpr uint64_t kFoldRows = 1024, kFoldBlockRows = 64;
 
-// Coordinates of a tile (one workgroup of the tile passes): doubled from the smallest until the layout
-// needs no more than kTileTarget tiles, which still fills the chip's 4 to 5 workgroups per CU twice.  A smaller tile pays
+// Coordinates of a tile (one workgroup of the tile passes): doubled from the smallest until kTileTarget of them hold the layout,
+// or to the cap.  Doubling ends between 1,024 and 2,048 whole tiles; partial tiles come on top, and beyond 537 M coordinates the
+// cap leaves more.  The chip holds 1,024 workgroups of k_final2 and 1,280 of k_final1 at a time.  A smaller tile pays
 // for its histograms more often (finalize of 124 M coordinates, tiles of 65,536: 407 us, of 16,384: 470 us), and so does
 // a cap below 262,144 on large layouts (3.5 G coordinates: 6.21 ms, with 131,072 6.33 ms, with 1 M 6.55 ms).
 constexpr uint64_t kTileCoordsMin = 8192, kTileCoordsMax = 262144, kTileTarget = 2048;
@@ -1609,9 +1607,8 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
             n_r += b.rows; n_c += b.cols;
             n_rowpart += (uint64_t)b.rows * m.n_tiles; n_colpart += (uint64_t)m.n_segs * b.cols;
             tasks = (uint64_t)m.n_across * m.n_segs;
-            // one candidate list per wavefront; a block's lists have room for an eighth of its coordinates (the keys that
-            // share a selected first digit are a few per cent of a block unless its v is nearly constant; then a list
-            // overflows and the last digit takes another walk over v)
+            // One candidate list per wavefront; a block's lists have room for an eighth of its coordinates.  The keys that share a
+            // selected first digit are a few per cent of a block unless many coordinates have the same v.
             m.cand_cap = (uint32_t)align_up((b.numel + 32 * tasks - 1) / (32 * tasks), 4);
             m.cand_base = n_cand;
             n_cand += tasks * 4 * m.cand_cap;

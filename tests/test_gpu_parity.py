@@ -513,10 +513,11 @@ def test_error_paths(env):
     assert binding.load_library().baoc_profile_begin(arr, 1, C.byref(p), ws.data_ptr() + 1, 10 ** 9, C.byref(h)) == binding.ERR_WORKSPACE
 
 
-@pytest.mark.parametrize("rows_per_step", [3071, 3072, 3073, 4096, 4097])
+@pytest.mark.parametrize("rows_per_step", [3071, 3072, 3073, 4095, 4096, 4097, 5119])
 def test_partial_row_sums_around_the_two_stage_edge(env, rows_per_step):
-    """Blocks of just below and above the number of partial rows that takes a second stage, one of them with a
-    last part of a single row (4097 = 4 x 1024 + 1), next to a block of a single row."""
+    """Blocks of just below and above the number of partial rows that takes a second stage, next to a block of a single row.
+    Parts have 1,024 rows and the last one takes the remainder as well: 1,025 rows of 4,097 and, the most there can be,
+    2,047 of 4,095 and of 5,119."""
     per = 2 * 256                                            # coordinates per partial row with this launch shape
     n = rows_per_step * per - 3
     w = W.Workload("parts", [W._vec("a", 7), W._vec("b", n), W._vec("c", 300)], 3, "f32", "cycle", **W.K6)
