@@ -1556,9 +1556,11 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
         m.n_tiles = (uint32_t)((b.cols + tile_cols - 1) / tile_cols); m.n_segs = (uint32_t)(((uint64_t)b.rows + m.seg_len - 1) / m.seg_len);
         // even shares of the rows (39 blocks of 2,405 x 3,443 without theta: 750 -> 676 us, with 70 % zeros 3.03 -> 2.72 ms)
         m.seg_len = (uint32_t)align_up(((uint64_t)b.rows + m.n_segs - 1) / m.n_segs, round_rows);
-        // A matrix of so few rows that its tiles have a single round: a task takes as many of them side by side as make up the
-        // smallest tile (16 of 2 x 262,144: finalize 432 -> 245 us, 400 of 8 x 4,096 264 -> 189 us, 4,000 of 2 x 300 852 -> 443 us).
-        m.strips = b.rows > round_rows ? 1 : (uint32_t)std::min<uint64_t>(m.n_tiles, std::max<uint64_t>(1, kTileCoordsMin / (b.rows * tile_cols)));
+        // A matrix of so few rows that its tiles, 256 columns wide, have a single round: a task takes as many of them side by side as
+        // make up the smallest tile (16 of 2 x 262,144: finalize 432 -> 241 us, 400 of 8 x 4,096 264 -> 188 us, 4,000 of 2 x 300 852 -> 438
+        // us).  With more rows a tile is worth its workgroup (a model of 64 channels, 1.5 M coordinates: 92 us, with two tiles
+        // of 64 x 64 to a task 98 us).
+        m.strips = b.rows > kRoundRows ? 1 : (uint32_t)std::min<uint64_t>(m.n_tiles, std::max<uint64_t>(1, kTileCoordsMin / (b.rows * tile_cols)));
         m.n_across = (m.n_tiles + m.strips - 1) / m.strips;
         P.any_strips |= m.strips > 1;
         matrix_tasks += (uint64_t)m.n_across * m.n_segs;
