@@ -1456,9 +1456,10 @@ constexpr uint64_t kTileRowsMax = kTileCoordsMax / 64;
 // Coordinates of a run of a block without a matrix shape, in layouts whose tiles are larger.  Blocks of very different sizes leave the last
 // workgroups few and long, most of all where many coordinates share a key and the histogram's bins are what everything waits for
 // (finalize of 3,000 vectors, 300 M coordinates, 70 % of them zero: 2.64 ms with one chunk at a time, 3.66 with runs of
-// 262,144, 3.03 with 131,072, 2.62 with 65,536, 2.47 with 32,768; dense 1.20, 0.99, 0.91, 0.92 and 0.95).  A single block of
-// 1.2 G coordinates takes 2.43 ms with 262,144 and 2.48 with 65,536, since all its runs meet in one histogram and one counter.
-constexpr uint64_t kRunCoords = 32768;
+// 262,144, 3.03 with 131,072, 2.62 with 65,536, 2.47 with 32,768; dense 1.20, 0.99, 0.91, 0.92 and 0.95).  All runs of a block meet in
+// one histogram and one counter, so a large block has longer ones (3 blocks of 579 M coordinates in all 1.68 ms with 262,144 and up
+// to 512 runs a block, 1.75 with up to 2,048; 28 of 430 M 1.16, 1.21 and 1.26).
+constexpr uint64_t kRunCoords = 32768, kBlockRuns = 512;
 
 static int check_params(const baoc_profile_params* p)
 {
@@ -1571,14 +1572,14 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     const uint64_t partial_bytes = P.n_prows * kNumSums * 4;
     auto sums_fit = [&](uint64_t tasks) { return task_bytes(tasks) <= partial_bytes; };
     auto counts_fit = [&](uint64_t tasks) { return 2 * task_bytes(tasks) <= partial_bytes; };
-    // Coordinates of a run: kRunCoords, or as many as leave a block 2,048 runs; and at least `least`.  A run takes 4 bytes in
+    // Coordinates of a run: kRunCoords, or as many as leave a block kBlockRuns of them; and at least `least`.  A run takes 4 bytes in
     // task_block and up to 32 for what does not fit the partial rows (with large chunks these are few).  Runs are lengthened
     // until that is within run_budget, 15 KB per block and 4 bytes per chunk, which keeps the workspace of a layout from growing
     // with the number of runs whatever the launch shape.
     uint64_t least = kTileCoordsMin;
     auto run_coords = [&](uint64_t numel) {
         uint64_t r = std::min(tile_coords, kRunCoords);
-        while (r < tile_coords && r * kTileTarget < numel) r *= 2;
+        while (r < tile_coords && r * kBlockRuns < numel) r *= 2;
         return std::max(r, least);
     };
     for (; least < (1u << 30); least = align_up(least * 5 / 4, 1024)) {
