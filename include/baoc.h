@@ -68,8 +68,8 @@ typedef struct {
     /* Launch shape of the per-step kernel; 0 = the default measured best for the gradient type
      * (fp32 layouts of fewer than 2^26 coordinates: 4 wavefronts x 1 group, 4 resident).
      * None of the five changes any result bit except through the order of the partial sums. */
-    uint32_t chunk_groups;        /* quantisation groups per chunk, the unit of the tables and of the
-                                   * finalize passes (default 8 for bf16 gradients, 4 for fp32)       */
+    uint32_t chunk_groups;        /* quantisation groups per chunk, the unit of the step's tables
+                                   * (default 8 for bf16 gradients, 4 for fp32)                       */
     uint32_t chunk_slices;        /* workgroups of the step kernel per chunk (default: as many as
                                    * make a slice one round, chunk_groups / (waves * groups_per_wave)) */
     uint32_t groups_per_wave;     /* adjacent groups a wavefront loads together: 1 or 2 (default 2)   */

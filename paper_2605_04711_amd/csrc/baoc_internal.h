@@ -13,8 +13,8 @@ constexpr uint32_t kNumSums = 16;        // floats in one partial-sum row
 // Launch shape of the step kernel, per gradient type (fp32, bf16).  Measured: a DRAM stream of 4 reads
 // and 3 writes per coordinate runs fastest with few, fat requesters; more resident wavefronts only add
 // row conflicts.  fp32 gradients: single-wavefront workgroups of two adjacent groups, about 10 resident
-// per compute unit; bf16: 4 wavefronts x 2 groups, 3 resident.  A chunk (the unit of the tables and of
-// the finalize passes) is cut into slices of one round each.
+// per compute unit; bf16: 4 wavefronts x 2 groups, 3 resident.  A chunk (the unit of the step's
+// tables) is cut into slices of one round each.
 struct LaunchShape { uint32_t chunk_groups, groups_per_wave, waves_per_workgroup, resident_workgroups; };
 constexpr LaunchShape kDefaultShape[2] = {{4, 2, 1, 10}, {8, 2, 4, 3}};
 constexpr LaunchShape kSmallF32Shape = {4, 1, 4, 4};          // fp32 layouts below kSmallLayout coordinates
