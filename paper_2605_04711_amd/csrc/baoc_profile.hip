@@ -753,11 +753,16 @@ __device__ __forceinline__ double group_sum(double x, uint32_t lane, uint32_t wa
 
 // ---------------------------------------------------------------------------
 // Matrix blocks (v viewed as rows x cols), tiled.
-// A workgroup takes a tile of 64 * wc columns and seg_len rows; its four wavefronts stand wc across the columns
+// A workgroup takes 64 * wc columns and up to seg_len rows; its four wavefronts stand wc across the columns
 // and 4 / wc down the rows.  A wavefront reads 4 rows x 64 columns (256 bytes a row) with one load, a lane 4
 // consecutive columns of a row, at any alignment: a row sum then takes four exchange levels for four rows at
 // once, and narrow or odd-sized matrices keep their lanes busy.  Loads are issued one round of kQuads * 4 rows
 // ahead of their use; rounds with a missing row or column load for themselves.
+// The rows of a workgroup are not next to each other: of the n_segs workgroups of a tile column each takes every n_segs-th round.
+// What is read at one time then lies close together, whatever the row length, where workgroups a power of two apart meet
+// in the same memory channels (a plain read of 4,096 x 4,096 matrices in this pattern: runs of 256 or 1,024 rows 6.0 - 6.3 TB/s, every
+// n_segs-th 16 rows 6.7 - 6.9; 4,096 x 11,008 6.8 - 7.0 either way.  Finalize passes of 3.5 G coordinates: 2323 -> 2270 and
+// 3580 -> 3516 us, 124 M unchanged).
 // In the second pass the keys that carry a selected first digit (a few per cent) are appended to a candidate list
 // per wavefront; the second digit is counted on the list at the end, the last digit by k_final3.  Keys that find no room are
 // counted as they come, and the last digit then takes a walk over v.
@@ -779,7 +784,8 @@ __device__ __forceinline__ uint32_t scalar_wave_index() { return scalar_u32(thre
 // readfirstlane), so that the task and every address derived from it live in scalar registers.
 struct TilePart {
     uint32_t tile, seg;
-    uint32_t row0, row1;                  // the tile's rows
+    uint32_t rows;                        // of the block
+    uint32_t first, stride;               // first row of the wavefront's first round; rows from one round to the next
     uint32_t wcol, wrow, wr;              // place of the wavefront in the workgroup; wavefronts down the rows
     uint32_t col;                         // first of the lane's 4 columns
     uint32_t lrow;                        // the lane's row in a quad
@@ -807,22 +813,25 @@ __device__ __forceinline__ TilePart tile_part(const TileRow& m, uint32_t seg, ui
     t.seg = seg; t.tile = tile;
     t.wr = 4u >> m.wc_log;
     t.wcol = wave & ((1u << m.wc_log) - 1u); t.wrow = wave >> m.wc_log;
-    t.row0 = t.seg * m.seg_len; t.row1 = min(m.rows, t.row0 + m.seg_len);
+    t.rows = m.rows;
+    const uint32_t mine = t.seg * t.wr + t.wrow, step = m.n_segs * t.wr;      // in rounds
+    t.first = mine * kRoundRows; t.stride = step * kRoundRows;
     const uint32_t col0 = ((t.tile << m.wc_log) + t.wcol) * 64;
     t.col = col0 + 4 * (lane & 15u); t.lrow = lane >> 4;
     t.n_ok = t.col < m.cols ? min(4u, m.cols - t.col) : 0u;
     t.any = col0 < m.cols;
-    const uint32_t blocks = (t.row1 - t.row0) / kRoundRows, log_wr = 2 - m.wc_log;
-    t.rounds = (t.row1 - t.row0 + (kRoundRows << log_wr) - 1) / (kRoundRows << log_wr);
+    const uint32_t log_wr = 2 - m.wc_log, stripes = (m.rows + (kRoundRows << log_wr) - 1) / (kRoundRows << log_wr);
+    t.rounds = (stripes - t.seg + m.n_segs - 1) / m.n_segs;
     // offsets of a full round are 32-bit byte offsets
-    t.full = col0 + 64 <= m.cols && m.cols < (1u << 28) && blocks > t.wrow ? ((blocks - t.wrow - 1) >> log_wr) + 1 : 0;
+    const uint32_t whole = m.rows / kRoundRows;
+    t.full = col0 + 64 <= m.cols && m.cols < (1u << 28) && whole > mine ? (whole - mine - 1) / step + 1 : 0;
     t.offset = t.lrow * m.cols + t.col;
     t.base = min(t.col, m.cols - 1);
     return t;
 }
 
 // First row (of the block) of a wavefront's round.
-__device__ __forceinline__ uint32_t round_row(const TilePart& t, uint32_t i) { return t.row0 + (i * t.wr + t.wrow) * kRoundRows; }
+__device__ __forceinline__ uint32_t round_row(const TilePart& t, uint32_t i) { return t.first + i * t.stride; }
 
 // Four elements per lane and quad of a full round.  The address is a scalar base and a 32-bit lane offset.
 template <int TT>
@@ -838,18 +847,18 @@ __device__ __forceinline__ void load_full(typename GradIO<TT>::vec4 (&x)[kQuads]
     }
 }
 
-// The same at the edge of a tile.  Rows past the tile are replaced by its last one, columns past the matrix by its
-// last one; a lane then reads up to 3 elements past its row.  `left`: elements from src that may be read.
+// The same at the edge of a matrix.  Rows and columns past the matrix are replaced by its last ones; a lane then reads up to 3
+// elements past its row.  `left`: elements from src that may be read.
 template <int TT>
 __device__ __forceinline__ void load_edge(typename GradIO<TT>::vec4 (&x)[kQuads], const typename GradIO<TT>::elem* __restrict__ src,
                                           uint64_t left, const TilePart& t, uint32_t cols, uint32_t i)
 {
     typedef GradIO<TT> IO;
     const uint32_t first = round_row(t, i);
-    const bool wide = (uint64_t)t.row1 * cols + 3 <= left;     // the same for the whole tile
+    const bool wide = (uint64_t)min(first + kRoundRows, t.rows) * cols + 3 <= left;     // the same for the whole wavefront
 #pragma unroll
     for (uint32_t q = 0; q < kQuads; ++q) {
-        const typename IO::elem* p = src + ((uint64_t)min(first + 4 * q + t.lrow, t.row1 - 1) * cols + t.base);
+        const typename IO::elem* p = src + ((uint64_t)min(first + 4 * q + t.lrow, t.rows - 1) * cols + t.base);
         if (wide) {
             x[q] = IO::loadv_any(p);
         } else {
@@ -911,7 +920,7 @@ __device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, co
 #pragma unroll
                 for (uint32_t q = 0; q < kQuads; ++q) {
                     x[q][0] = ex[q].x; x[q][1] = ex[q].y; x[q][2] = ex[q].z; x[q][3] = ex[q].w;
-                    const bool in_row = row + 4 * q + t.lrow < t.row1;
+                    const bool in_row = row + 4 * q + t.lrow < t.rows;
                     float prow = 0.f;
 #pragma unroll
                     for (uint32_t k = 0; k < 4; ++k) {
@@ -950,17 +959,19 @@ __device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, co
             }
         }
         if ((i + 1) % kSubRounds == 0 || i + 1 == t.rounds) {
-            // row sums of the sub-segment: rowpart is tile-major ([tile][row]), so the workgroup writes one run
+            // row sums of the last rounds: rowpart is tile-major ([tile][row]); a round of the workgroup is a run of 16, 32 or 64 rows
             __syncthreads();
-            const uint32_t r0 = t.row0 + i / kSubRounds * kSubRounds * t.wr * kRoundRows;
-            const uint32_t n = min(t.row1 - r0, kSubRounds * t.wr * kRoundRows);
+            const uint32_t i0 = i / kSubRounds * kSubRounds, n = (i + 1 - i0) * t.wr * kRoundRows;
+            const uint32_t first_row = t.seg * t.wr * kRoundRows + i0 * t.stride;
             const uint32_t n_wc = min(1u << m.wc_log, (m.cols - ((t.tile << m.wc_log) * 64) + 63) / 64);   // wavefronts that have columns
             for (uint32_t rs = threadIdx.x; rs < n; rs += 256) {
                 const uint32_t step = rs / kRoundRows, wrow = step & (t.wr - 1), ii = step >> (2 - m.wc_log);
+                const uint32_t row = first_row + ii * t.stride + rs % (t.wr * kRoundRows);
+                if (row >= t.rows) break;
                 const float* in = rowsum + (wrow << m.wc_log) * 256 + ii * kRoundRows + rs % kRoundRows;
                 float sum = in[0];
                 for (uint32_t w = 1; w < n_wc; ++w) sum += in[w * 256];
-                rowpart[m.off_rowpart + (uint64_t)t.tile * m.rows + r0 + rs] = sum;
+                rowpart[m.off_rowpart + (uint64_t)t.tile * m.rows + row] = sum;
                 total += (double)sum;
             }
             __syncthreads();
@@ -1284,8 +1295,8 @@ __global__ __launch_bounds__(256, STRIPS ? 4 : 1) void k_final2(
             if (C) load_edge<TT>(et, tsrc, tleft, t, cols, round);
 #pragma unroll
             for (uint32_t q = 0; q < kQuads; ++q) {
-                const bool in_row = first + 4 * q + t.lrow < t.row1;
-                const float ri = F ? rr[min(first + 4 * q + t.lrow, t.row1 - 1)] : 0.f, x[4] = {ex[q].x, ex[q].y, ex[q].z, ex[q].w};
+                const bool in_row = first + 4 * q + t.lrow < t.rows;
+                const float ri = F ? rr[min(first + 4 * q + t.lrow, t.rows - 1)] : 0.f, x[4] = {ex[q].x, ex[q].y, ex[q].z, ex[q].w};
                 float th[4] = {0.f, 0.f, 0.f, 0.f};
                 if (C) IO::unpack(et[q], th);
 #pragma unroll
