@@ -547,18 +547,21 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
 }
 
 // ---------------------------------------------------------------------------
-// Finalize: three passes over the blocks' workgroups
+// Finalize: three passes over the blocks' workgroups, and two small launches between them
 //   k_final1: first radix digit (Eq. 4); sum of p = 1/(sqrt(v)+eps) (Eq. 6); matrix blocks: mu, row and
-//             column partial sums (Eq. 7), folded to r and c by k_fold_means
+//             column partial sums (Eq. 7)
+//   k_fold1:  first digit of the ranks, sums, r and c, where a block has several workgroups
 //   k_final2: second digit; ((p/p-bar - 1) theta)^2 and theta^2 (Eq. 6); |S - r c^T / mu|^2 (Eq. 7; |S|^2 is the
 //             step's own sum of v^2)
+//   k_fold2:  second digit of the ranks, sums, where a block has several workgroups
 //   k_final3: last digit
 // The quantiles are exact order statistics, found by a three-digit radix selection on the bit patterns (v >= 0, so
 // the pattern order is the value order).  Digits: bits 30..19, 18..9, 8..0.  Four ranks per block share every pass.
-// The workgroup of a block that finishes last folds what the others left: the digit of the four ranks, the block's
-// sums.  As launches of their own (fills, picks, partial sums, separate walks over the blocks without a matrix shape: 19
-// launches, now 4) that took longer than the passes themselves: finalize of 25.6 M coordinates 247 -> 151 us, of 60 M
-// of odd shapes 435 -> 277 us, of 32,768 104 -> 52 us.
+// A block of one workgroup is folded by it, from LDS.  A block of several is folded between the passes: with a counter per block and
+// the last workgroup to arrive doing it, every workgroup holds its place until its atomics and the counter have answered, and the last
+// one's chain of loads ends the pass (passes of 25.6 M coordinates 36 + 49 us, now 27 + 43 and 5 + 5 for the launches between them; 124 M
+// 106 + 146, now 94 + 141 and 6 + 5; 32,768 coordinates, one workgroup a block, 29 us of kernels, now 18).  Pass 3 is short, and its
+// last workgroup does fold.
 // ---------------------------------------------------------------------------
 
 // How finalize walks a block: tiles of a matrix (rows, cols > 0) or runs of coordinates (rows = cols = 0), a
@@ -577,9 +580,9 @@ struct alignas(8) TileRow {
     uint32_t wc_log;                      // a tile is seg_len x (64 << wc_log)
     uint32_t first_task;
     uint32_t cand_cap;                    // words per candidate list (one list per wavefront)
-    uint32_t first_fin;                   // first workgroup of the block in k_fold_means
+    uint32_t first_fin;                   // first of the block's workgroups that fold row and column sums in k_fold1
+    uint32_t n_tasks;                     // workgroups of a pass over the block
     uint32_t rank[4];                     // order statistics wanted from v: lo(0.1), lo+1, lo(0.9), lo+1
-    uint32_t pad_;
 };
 
 constexpr uint32_t kHistWords = 4096;     // histogram words a block owns
@@ -590,7 +593,7 @@ static_assert(kBins1 <= kHistWords && 4 * kBins2 <= kHistWords && 4 * kBins3 <= 
 
 // Tables that begin() leaves on the device, and the clearing of what must start at zero: chunks from the block rows
 // (the owning block by bisection on first_chunk; a block's groups are split evenly over its chunks, whole groups
-// each) and the owning block of every workgroup of the finalize passes and of k_fold_means.
+// each) and the owning block of every workgroup of the finalize passes and of k_fold1.
 __global__ __launch_bounds__(256) void k_build(const BlockRow* __restrict__ rows, const TileRow* __restrict__ tiles, uint32_t n_blocks,
                                                Chunk* __restrict__ chunks, uint32_t n_chunks, uint32_t* __restrict__ task_block, uint32_t n_tasks,
                                                uint32_t* __restrict__ fin_block, uint32_t n_fin, uint4* __restrict__ clear, uint64_t n_clear)
@@ -666,71 +669,115 @@ __device__ __forceinline__ void count_match(uint32_t* h, const Prefixes& d, uint
     if (hit) atomicAdd(&h[at], 1u);
 }
 
-// The digit of one rank, by one wavefront: the bin of its histogram that holds the rank, and the rank inside the bin.
-// Bins i * 64 + lane of the NB are read by `load`.
-template <uint32_t NB, typename L>
-__device__ __forceinline__ uint3 pick_bin(uint32_t rank, uint32_t lane, L load)
+// Inclusive sum over the lanes of a wavefront.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x)
 {
-    uint32_t c[NB / 64];
-#pragma unroll
-    for (uint32_t i = 0; i < NB / 64; ++i) c[i] = load(i * 64 + lane);
-    uint32_t mine = 0, at = 0;                                // the 64 bins that hold the rank
-    bool found = false;
-#pragma unroll
-    for (uint32_t i = 0; i < NB / 64; ++i) {
-        uint32_t x = c[i];
-        x += dpp_u32<0xB1, 0xf>(0u, x);
-        x += dpp_u32<0x4E, 0xf>(0u, x);
-        x += dpp_u32<0x124, 0xf>(0u, x);
-        x += dpp_u32<0x128, 0xf>(0u, x);
-        x += dpp_u32<0x142, 0xa>(0u, x);
-        x += dpp_u32<0x143, 0xc>(0u, x);
-        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
-        if (!found) {
-            if (rank < total || i == NB / 64 - 1) { found = true; mine = c[i]; at = i * 64; }
-            else rank -= total;
-        }
-    }
-    uint32_t incl = mine;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t o = __shfl_up(incl, d);
-        if ((int)lane >= d) incl += o;
-    }
-    const uint64_t holders = __ballot(rank >= incl - mine && rank < incl);
-    const uint32_t owner = holders ? (uint32_t)__builtin_ctzll(holders) : 63u;
-    return uint3{at + owner, rank - (uint32_t)__builtin_amdgcn_readlane((int)(incl - mine), owner), (uint32_t)__builtin_amdgcn_readlane((int)mine, owner)};
+    x += dpp_u32<0x111, 0xf>(0u, x);                          // row_shr:1, 2, 4, 8, then the rows' totals upwards
+    x += dpp_u32<0x112, 0xf>(0u, x);
+    x += dpp_u32<0x114, 0xf>(0u, x);
+    x += dpp_u32<0x118, 0xf>(0u, x);
+    x += dpp_u32<0x142, 0xa>(0u, x);
+    x += dpp_u32<0x143, 0xc>(0u, x);
+    return x;
 }
 
 struct Selection { uint32_t *hist, *prefix, *rank; };     // per block: histogram words; four key prefixes; four ranks within them
+struct Digit { uint32_t bin, rank, count; };              // the bin that holds a rank, the rank inside it, the bin's keys
 
-// The PASS-th digit of a block's four ranks, a wavefront each, by the workgroup that arrived last.  A block of a
-// single workgroup never left LDS (h); others added theirs to the block's global histogram, which is cleared again.
-// Counts fit 32 bits (numel < 2^32).
-template <int PASS>
-__device__ __forceinline__ void pick_digit(const Selection& sel, const TileRow& row, uint32_t block, bool single, const uint32_t* h,
-                                           uint32_t lane, uint32_t wave, double* rec, uint32_t* n_keys = nullptr)
+constexpr uint32_t kBinsPerLane = kBins2 / 64;            // consecutive bins of a lane: 256 lanes cover the first digit, 64 one of the others
+static_assert(kBins1 == 256 * kBinsPerLane && kBins3 == 64 * kBinsPerLane / 2, "shares of the lanes");
+
+// The bin among the lane's N consecutive ones, the first of which starts at key number `at`, that holds `rank`.
+template <uint32_t N>
+__device__ __forceinline__ Digit bin_of(const uint32_t (&c)[N], uint32_t first_bin, uint32_t at, uint32_t rank)
 {
-    constexpr uint32_t NB = PASS == 1 ? kBins1 : (PASS == 2 ? kBins2 : kBins3);
+    Digit d{first_bin, rank - at, c[0]};
+    uint32_t below = 0;
+#pragma unroll
+    for (uint32_t i = 1; i < N; ++i) {
+        below += c[i - 1];
+        if (rank - at >= below) d = Digit{first_bin + i, rank - at - below, c[i]};
+    }
+    return d;
+}
+
+// N consecutive words; `hist` is LDS or, in another launch than the one that counted, global memory.
+template <uint32_t N>
+__device__ __forceinline__ void load_bins(uint32_t (&c)[N], const uint32_t* hist)
+{
+#pragma unroll
+    for (uint32_t i = 0; i < N / 4; ++i) {
+        const uint4 x = reinterpret_cast<const uint4*>(hist)[i];
+        c[4 * i] = x.x; c[4 * i + 1] = x.y; c[4 * i + 2] = x.z; c[4 * i + 3] = x.w;
+    }
+}
+
+// First digit of a block's four ranks from its histogram, which the threads leave cleared; the block's sums of v (`total`) and p
+// (`psum`), known to thread 0; the flag of blocks that go without candidate lists.  Called by a whole workgroup.  Counts fit 32
+// bits (numel < 2^32).
+__device__ __forceinline__ void fold_first(const Selection& sel, const TileRow& m, uint32_t block, uint32_t* hist, double total, double psum,
+                                           uint32_t lane, uint32_t wave, double* rec, uint32_t* __restrict__ scan3)
+{
+    __shared__ uint32_t sums[4];
+    __shared__ Digit found[4];
+    uint32_t c[kBinsPerLane], mine = 0;
+    hist += threadIdx.x * kBinsPerLane;
+    load_bins(c, hist);
+#pragma unroll
+    for (uint32_t i = 0; i < kBinsPerLane; ++i) mine += c[i];
+    const uint32_t incl = wave_scan(mine);
+    if (lane == 63) sums[wave] = incl;
+    __syncthreads();
+    uint32_t at = incl - mine;
+    for (uint32_t w = 0; w < wave; ++w) at += sums[w];
+#pragma unroll
+    for (uint32_t t = 0; t < 4; ++t)
+        if (m.rank[t] >= at && m.rank[t] - at < mine) found[t] = bin_of(c, threadIdx.x * kBinsPerLane, at, m.rank[t]);
+    for (uint32_t i = 0; i < kBinsPerLane / 4; ++i) reinterpret_cast<uint4*>(hist)[i] = uint4{0u, 0u, 0u, 0u};
+    __syncthreads();
+    if (threadIdx.x < 4) { sel.prefix[block * 4 + threadIdx.x] = found[threadIdx.x].bin; sel.rank[block * 4 + threadIdx.x] = found[threadIdx.x].rank; }
+    if (threadIdx.x == 0) {
+        // mu is the mean of the row means to the last bit of what they are made of: the tiles' row sums, added in fp64
+        if (m.rows) rec[R_MU] = total / ((double)m.rows * (double)m.cols);
+        rec[R_PSUM] = psum;
+        // Where the keys that carry a selected first digit would fill three quarters of the lists of a whole task, the block goes without
+        // lists: its keys are counted as they come, and the last digit takes another walk over v, which is cheaper from about
+        // there on.  k_final2 raises the flag where a single list overflows.  (39 blocks of 2,405 x 3,443, 20 % of them zero: finalize 2.18 ms with lists that overflow and
+        // a second walk over their tiles, 1.55 with the keys past their end counted at once, 1.32 now; 4,096 x 4,096 1.70, 1.20, 1.02.)
+        uint64_t keys = 0;
+        for (uint32_t t = 0; t < 4; ++t) {
+            bool fresh = true;
+            for (uint32_t u = 0; u < t; ++u) fresh = fresh && found[u].bin != found[t].bin;
+            if (fresh) keys += found[t].count;
+        }
+        const uint64_t part = (uint64_t)min(m.rows, m.seg_len) * min(m.cols, m.strips * (64u << m.wc_log));   // coordinates of a whole task
+        scan3[block * kArriveStride] = m.rows == 0 || keys * part > 3ull * m.cand_cap * m.numel;
+    }
+}
+
+// The PASS-th digit (2 or 3) of a block's four ranks, a wavefront each; `hist` has a histogram for every distinct prefix and is left
+// cleared.  `load` reads consecutive bins.  Called by a whole workgroup.
+template <int PASS, typename L>
+__device__ __forceinline__ void pick_digit(const Selection& sel, uint32_t block, uint32_t* hist, uint32_t lane, uint32_t wave, double* rec, L load)
+{
+    constexpr uint32_t NB = PASS == 2 ? kBins2 : kBins3, N = NB / 64;
     const uint32_t id = block * 4 + wave;
-    uint32_t* hist = sel.hist + (uint64_t)block * kHistWords;
-    uint32_t slot = 0, rank = row.rank[wave], prefix = 0;
-    if (PASS > 1) {
-        const Prefixes d = distinct_prefixes(sel.prefix, block);
-        slot = wave == 0 ? d.slot_of[0] : (wave == 1 ? d.slot_of[1] : (wave == 2 ? d.slot_of[2] : d.slot_of[3]));
-        rank = sel.rank[id]; prefix = sel.prefix[id];
-    }
-    const uint3 p = single ? pick_bin<NB>(rank, lane, [&](uint32_t i) { return h[slot * NB + i]; })
-                           : pick_bin<NB>(rank, lane, [&](uint32_t i) { return ld_device(hist + slot * NB + i); });
+    const Prefixes d = distinct_prefixes(sel.prefix, block);
+    const uint32_t slot = wave == 0 ? d.slot_of[0] : (wave == 1 ? d.slot_of[1] : (wave == 2 ? d.slot_of[2] : d.slot_of[3]));
+    const uint32_t rank = sel.rank[id], prefix = sel.prefix[id];
+    uint32_t c[N], mine = 0;
+    load(c, hist + slot * NB + lane * N);
+#pragma unroll
+    for (uint32_t i = 0; i < N; ++i) mine += c[i];
+    const uint32_t at = wave_scan(mine) - mine;
     __syncthreads();                                          // all four have read the prefixes and the histogram
-    prefix = PASS == 1 ? p.x : ((prefix << (PASS == 2 ? kBits2 : kBits3)) | p.x);
-    if (lane == 0) {
-        if (PASS < 3) { sel.prefix[id] = prefix; sel.rank[id] = p.y; }
-        if (PASS == 1) { n_keys[2 * wave] = prefix; n_keys[2 * wave + 1] = p.z; }
-        else rec[R_ORDER + wave] = (double)__builtin_bit_cast(float, prefix);
+    if (rank >= at && rank - at < mine) {
+        const Digit f = bin_of(c, lane * N, at, rank);
+        const uint32_t key = (prefix << (PASS == 2 ? kBits2 : kBits3)) | f.bin;
+        if (PASS == 2) { sel.prefix[id] = key; sel.rank[id] = f.rank; }
+        else rec[R_ORDER + wave] = (double)__builtin_bit_cast(float, key);
     }
-    if (!single)
-        for (uint32_t i = threadIdx.x; i < (PASS == 1 ? NB : 4 * NB); i += 256) hist[i] = 0;
+    for (uint32_t i = threadIdx.x; i < NB; i += 256) reinterpret_cast<uint4*>(hist)[i] = uint4{0u, 0u, 0u, 0u};
 }
 
 // Adds a workgroup's LDS histogram to the block's.
@@ -768,9 +815,9 @@ __device__ __forceinline__ double group_sum(double x, uint32_t lane, uint32_t wa
 // counted as they come, and the last digit then takes a walk over v.
 // Large layouts are bound by HBM with the vector ALUs close behind, small ones by the number of wavefronts in flight.
 // Measured (first / second pass, us; before: one wavefront per 256 x 256 tile, scalar loads where a row is not a
-// multiple of 4, keys stored as they were found; now with the folds of the last workgroup): 25.6 M coordinates of
-// convolutions 189 / 416 -> 37 / 48, 124 M 136 / 323 -> 110 / 155, 60 M of odd shapes, a third of them vectors,
-// 254 / 535 -> 74 / 136, 3.5 G 2492 / 3887 -> 2340 / 3610 (5.9 and 6.0 TB/s).
+// multiple of 4, keys stored as they were found): 25.6 M coordinates of
+// convolutions 189 / 416 -> 27 / 43, 124 M 136 / 323 -> 94 / 141, 60 M of odd shapes, a third of them vectors,
+// 254 / 535 -> 60 / 119, 3.5 G 2492 / 3887 -> 2250 / 3505 (6.2 and 6.0 TB/s).
 // ---------------------------------------------------------------------------
 
 constexpr uint32_t kQuads = 4;                        // loads of 4 rows a wavefront has in flight
@@ -875,7 +922,8 @@ constexpr uint64_t kAnywhere = ~0ull;                 // v may be read past its 
 // First pass over a tile.  Returns the lane's sum of p and adds the thread's part of the sum of v to `total`; counts
 // into h, which the `first` tile of the workgroup clears.
 __device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, const TileRow& m, const TilePart& t, bool first, uint32_t lane, uint32_t wave,
-                                             float* __restrict__ rowpart, float* __restrict__ colpart, uint32_t* h, float* rowsum, double* colsum,
+                                             float* __restrict__ rowpart, float* __restrict__ colpart, float* __restrict__ rvec, float* __restrict__ cvec,
+                                             uint32_t* h, float* rowsum, double* colsum,
                                              float eps, float eps_low, bool want_p, double& total)
 {
     const float* src = v_all + m.state_start;
@@ -971,7 +1019,8 @@ __device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, co
                 const float* in = rowsum + (wrow << m.wc_log) * 256 + ii * kRoundRows + rs % kRoundRows;
                 float sum = in[0];
                 for (uint32_t w = 1; w < n_wc; ++w) sum += in[w * 256];
-                rowpart[m.off_rowpart + (uint64_t)t.tile * m.rows + row] = sum;
+                if (m.n_tiles == 1) rvec[m.off_r + row] = (float)((double)sum / (double)m.cols);
+                else rowpart[m.off_rowpart + (uint64_t)t.tile * m.rows + row] = sum;
                 total += (double)sum;
             }
             __syncthreads();
@@ -988,7 +1037,8 @@ __device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, co
     if (threadIdx.x < tile_cols && col < m.cols) {
         double a = 0.0;
         for (uint32_t w = 0; w < t.wr; ++w) a += colsum[w * tile_cols + threadIdx.x];
-        colpart[m.off_colpart + (uint64_t)t.seg * m.cols + col] = (float)a;
+        if (m.n_segs == 1) cvec[m.off_c + col] = (float)((double)(float)a / (double)m.rows);
+        else colpart[m.off_colpart + (uint64_t)t.seg * m.cols + col] = (float)a;
     }
     return psum;
 }
@@ -1042,10 +1092,10 @@ __device__ __forceinline__ void walk_run(const float* __restrict__ v_all, const 
 template <bool STRIPS>
 __global__ __launch_bounds__(256) void k_final1(
     const float* __restrict__ v_all, const TileRow* __restrict__ tiles, const uint32_t* __restrict__ task_block,
-    float* __restrict__ rowpart, float* __restrict__ colpart, double* __restrict__ taskpart,
-    Selection sel, uint32_t* __restrict__ arrived, uint32_t* __restrict__ scan3, double* __restrict__ rec_all, float eps, float eps_low, bool want_p)
+    float* __restrict__ rowpart, float* __restrict__ colpart, float* __restrict__ rvec, float* __restrict__ cvec, double2* __restrict__ taskpart,
+    Selection sel, uint32_t* __restrict__ scan3, double* __restrict__ rec_all, float eps, float eps_low, bool want_p)
 {
-    __shared__ uint32_t h[kBins1];
+    __shared__ alignas(16) uint32_t h[kBins1];
     __shared__ float rowsum[4 * 256];                     // [wavefront][its rows of a sub-segment]
     __shared__ double colsum[4 * 64], sums[8];
     const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index(), block = task_block[blockIdx.x];
@@ -1054,7 +1104,7 @@ __global__ __launch_bounds__(256) void k_final1(
     if (m.rows) {
         const Task k = task_of<STRIPS>(m, blockIdx.x);
         for (uint32_t tile = k.tile; tile < k.last; ++tile)
-            psum += tile_pass1(v_all, m, tile_part(m, k.seg, tile, lane, wave), tile == k.tile, lane, wave, rowpart, colpart, h, rowsum, colsum,
+            psum += tile_pass1(v_all, m, tile_part(m, k.seg, tile, lane, wave), tile == k.tile, lane, wave, rowpart, colpart, rvec, cvec, h, rowsum, colsum,
                                eps, eps_low, want_p, total);
     } else {
         for (uint32_t i = threadIdx.x; i < kBins1; i += 256) h[i] = 0;
@@ -1072,51 +1122,41 @@ __global__ __launch_bounds__(256) void k_final1(
     }
     total = group_sum(total, lane, wave, sums);
     psum = group_sum(psum, lane, wave, sums + 4);             // ends with every wavefront's counts in h
-    const uint32_t n_tasks = m.n_across * m.n_segs;
-    const bool single = n_tasks == 1;
-    if (threadIdx.x == 0) { st_device(&taskpart[2 * blockIdx.x], total); st_device(&taskpart[2 * blockIdx.x + 1], psum); }
-    if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, kBins1);
-    if (!arrive_last(arrived + block * kArriveStride, n_tasks)) return;
-    double* rec = rec_all + (uint64_t)block * kRecDoubles;
-    __shared__ uint32_t n_keys[8];                        // per rank: first digit, keys that share it
-    pick_digit<1>(sel, m, block, single, h, lane, wave, rec, n_keys);
-    double a = 0.0, p = 0.0;
-    for (uint32_t i = threadIdx.x; i < n_tasks; i += 256) {
-        a += ld_device(&taskpart[2 * (m.first_task + i)]);
-        p += ld_device(&taskpart[2 * (m.first_task + i) + 1]);
+    if (m.n_tasks == 1) {
+        fold_first(sel, m, block, h, total, psum, lane, wave, rec_all + (uint64_t)block * kRecDoubles, scan3);
+        return;
     }
-    a = group_sum(a, lane, wave, sums);
-    p = group_sum(p, lane, wave, sums + 4);
-    if (threadIdx.x == 0) {
-        // mu is the mean of the row means to the last bit of what they are made of: the tiles' row sums, added in fp64
-        if (m.rows) rec[R_MU] = a / ((double)m.rows * (double)m.cols);
-        rec[R_PSUM] = p;
-        // Where the keys that carry a selected first digit would fill three quarters of the lists of a whole tile, the block goes without
-        // lists: its keys are counted as they come, and the last digit takes another walk over v, which is cheaper from about
-        // there on.  k_final2 raises the flag where a single list overflows.  (39 blocks of 2,405 x 3,443, 20 % of them zero: finalize 2.18 ms with lists that overflow and
-        // a second walk over their tiles, 1.55 with the keys past their end counted at once, 1.32 now; 4,096 x 4,096 1.70, 1.20, 1.02.)
-        uint64_t keys = 0;
-        for (uint32_t t = 0; t < 4; ++t) {
-            bool fresh = true;
-            for (uint32_t u = 0; u < t; ++u) fresh = fresh && n_keys[2 * u] != n_keys[2 * t];
-            if (fresh) keys += n_keys[2 * t + 1];
-        }
-        const uint64_t part = (uint64_t)min(m.rows, m.seg_len) * min(m.cols, m.strips * (64u << m.wc_log));   // coordinates of a whole task
-        scan3[block] = m.rows == 0 || keys * part > 3ull * m.cand_cap * m.numel;
-    }
+    if (threadIdx.x == 0) taskpart[blockIdx.x] = double2{total, psum};
+    flush_hist(sel.hist + (uint64_t)block * kHistWords, h, kBins1);
 }
 
-// r_i and c_j (fp32 for the second pass) from the partial sums of the first.  A workgroup takes 64 rows or 64 columns of
-// a block, summed over the tiles or segments by 4 wavefronts in parallel: a 50257 x 768 block has hundreds of
-// segments, whose loads would otherwise wait for each other (62 -> 6 us on that layout).
-__global__ __launch_bounds__(256) void k_fold_means(const TileRow* __restrict__ tiles, const uint32_t* __restrict__ fin_block,
-                                                    const float* __restrict__ rowpart, const float* __restrict__ colpart,
-                                                    float* __restrict__ rvec, float* __restrict__ cvec)
+// Between the first two passes, for blocks of several tasks: the first n_multi workgroups fold what a block's tasks left (digit of the
+// ranks, sums), the others r_i and c_j (fp32 for the second pass) from the partial sums of the first, 64 rows or 64 columns each, summed
+// over the tiles or segments by 4 wavefronts in parallel: a 50257 x 768 block has hundreds of segments, whose loads would
+// otherwise wait for each other (62 -> 6 us on that layout).
+__global__ __launch_bounds__(256) void k_fold1(const TileRow* __restrict__ tiles, const uint32_t* __restrict__ multi, uint32_t n_multi,
+                                               const uint32_t* __restrict__ fin_block, const float* __restrict__ rowpart, const float* __restrict__ colpart,
+                                               float* __restrict__ rvec, float* __restrict__ cvec, const double2* __restrict__ taskpart,
+                                               Selection sel, uint32_t* __restrict__ scan3, double* __restrict__ rec_all)
 {
     __shared__ double sh[4][64];
-    const TileRow& m = tiles[fin_block[blockIdx.x]];
     const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index();
-    const uint32_t local = blockIdx.x - m.first_fin, row_wgs = (m.rows + 63) / 64;
+    if (blockIdx.x < n_multi) {
+        const uint32_t block = multi[blockIdx.x];
+        const TileRow& m = tiles[block];
+        double total = 0.0, psum = 0.0;
+        for (uint32_t i = threadIdx.x; i < m.n_tasks; i += 256) {
+            const double2 x = taskpart[m.first_task + i];
+            total += x.x; psum += x.y;
+        }
+        total = group_sum(total, lane, wave, sh[0]);
+        psum = group_sum(psum, lane, wave, sh[1]);
+        fold_first(sel, m, block, sel.hist + (uint64_t)block * kHistWords, total, psum, lane, wave, rec_all + (uint64_t)block * kRecDoubles, scan3);
+        return;
+    }
+    const uint32_t unit = blockIdx.x - n_multi;
+    const TileRow& m = tiles[fin_block[unit]];
+    const uint32_t local = unit - m.first_fin, row_wgs = m.n_tiles > 1 ? (m.rows + 63) / 64 : 0;
     const bool is_row = local < row_wgs;
     const uint32_t at = (is_row ? local : local - row_wgs) * 64 + lane, len = is_row ? m.rows : m.cols;
     const uint32_t count = is_row ? m.n_tiles : m.n_segs;
@@ -1138,18 +1178,17 @@ constexpr uint32_t kStage = 320;                      // words per wavefront in 
 
 // F, C: Eq. 7 and Eq. 6 are wanted.
 template <int TT, bool F, bool C, bool STRIPS>
-__global__ __launch_bounds__(256, STRIPS ? 4 : 1) void k_final2(
+__global__ __launch_bounds__(256, 4) void k_final2(
     const float* __restrict__ v_all, const typename GradIO<TT>::elem* __restrict__ theta, uint64_t theta_numel,
     const TileRow* __restrict__ tiles, const uint32_t* __restrict__ task_block, const float* __restrict__ rvec, const float* __restrict__ cvec,
-    float* __restrict__ residpart, Selection sel, uint32_t* __restrict__ arrived, uint32_t* cand, uint32_t* __restrict__ cand_count,
+    float4* __restrict__ residpart, Selection sel, uint32_t* cand, uint32_t* __restrict__ cand_count,
     uint32_t* __restrict__ scan3, double* __restrict__ rec_all, float eps, float eps_low)
 {
     typedef GradIO<TT> IO;
     typedef typename IO::vec4 TV;
-    __shared__ uint32_t h[4 * kBins2];                    // a histogram per distinct prefix
+    __shared__ alignas(16) uint32_t h[4 * kBins2];        // a histogram per distinct prefix
     __shared__ uint32_t staged[4 * kStage];
     __shared__ float red[4][4];
-    __shared__ double sums[4];
     const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index(), block = task_block[blockIdx.x];
     const TileRow& m = tiles[block];
     const Prefixes d = distinct_prefixes(sel.prefix, block);
@@ -1177,7 +1216,7 @@ __global__ __launch_bounds__(256, STRIPS ? 4 : 1) void k_final2(
         const float* rr = rvec + m.off_r;
         // no room where the first pass has found the block to go without lists (or a list of this pass overflowed meanwhile, which comes
         // to the same: the last digit is then not taken from the lists)
-        const uint32_t cols = scalar_u32(m.cols), cap = scalar_u32(scan3[block] ? 0u : m.cand_cap);
+        const uint32_t cols = scalar_u32(m.cols), cap = scalar_u32(scan3[block * kArriveStride] ? 0u : m.cand_cap);
         f4 nx[kQuads]; TV nt[kQuads]; float nr[kQuads];
 #pragma unroll
         for (uint32_t q = 0; q < kQuads; ++q) { nx[q] = f4{0.f, 0.f, 0.f, 0.f}; nt[q] = TV{}; nr[q] = 0.f; }
@@ -1324,7 +1363,7 @@ __global__ __launch_bounds__(256, STRIPS ? 4 : 1) void k_final2(
         flush(true);
         if (lane == 0) {
             cand_count[blockIdx.x * 4 + wave] = n_cand;
-            if (n_cand > cap) scan3[block] = 1u;              // list too short: the last digit of the block takes another walk over v
+            if (n_cand > cap) scan3[block * kArriveStride] = 1u;              // list too short: the last digit of the block takes another walk over v
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");    // lanes read what other lanes stored
         for (uint32_t i = lane; i < min(n_cand, cap); i += 64) count2(list[i]);
@@ -1347,21 +1386,35 @@ __global__ __launch_bounds__(256, STRIPS ? 4 : 1) void k_final2(
     res = wave_sum((float)rsum); cn = wave_sum((float)nsum); cd = wave_sum((float)dsum);
     if (lane == 0) { red[wave][0] = res; red[wave][1] = cn; red[wave][2] = cd; }
     __syncthreads();
-    if (threadIdx.x < 3)
-        st_device(&residpart[(uint64_t)blockIdx.x * 4 + threadIdx.x], (float)(((double)red[0][threadIdx.x] + (double)red[1][threadIdx.x]) + ((double)red[2][threadIdx.x] + (double)red[3][threadIdx.x])));
-    const uint32_t n_tasks = m.n_across * m.n_segs;
-    const bool single = n_tasks == 1;
-    if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, d.n * kBins2);
-    if (!arrive_last(arrived + block * kArriveStride, n_tasks)) return;
+    auto task_sum = [&](uint32_t q) { return (float)(((double)red[0][q] + (double)red[1][q]) + ((double)red[2][q] + (double)red[3][q])); };
     double* rec = rec_all + (uint64_t)block * kRecDoubles;
-    pick_digit<2>(sel, m, block, single, h, lane, wave, rec);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-        double a = 0.0;
-        for (uint32_t i = threadIdx.x; i < n_tasks; i += 256) a += (double)ld_device(&residpart[(uint64_t)(m.first_task + i) * 4 + q]);
-        a = group_sum(a, lane, wave, sums);
-        if (threadIdx.x == 0) rec[q == 0 ? R_FRES : (q == 1 ? R_CNUM : R_CDEN)] = a;
+    if (m.n_tasks == 1) {
+        if (threadIdx.x == 0) { rec[R_FRES] = (double)task_sum(0); rec[R_CNUM] = (double)task_sum(1); rec[R_CDEN] = (double)task_sum(2); }
+        pick_digit<2>(sel, block, h, lane, wave, rec, [](auto& c, const uint32_t* at) { load_bins(c, at); });
+        return;
     }
+    if (threadIdx.x == 0) residpart[blockIdx.x] = float4{task_sum(0), task_sum(1), task_sum(2), 0.f};
+    flush_hist(sel.hist + (uint64_t)block * kHistWords, h, d.n * kBins2);
+}
+
+// Between the last two passes, for blocks of several tasks: second digit of the ranks, sums of Eq. 7 and Eq. 6.
+__global__ __launch_bounds__(256) void k_fold2(const TileRow* __restrict__ tiles, const uint32_t* __restrict__ multi, const float4* __restrict__ residpart,
+                                               Selection sel, double* __restrict__ rec_all)
+{
+    __shared__ double sh[3][4];
+    const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index(), block = multi[blockIdx.x];
+    const TileRow& m = tiles[block];
+    double* rec = rec_all + (uint64_t)block * kRecDoubles;
+    double res = 0.0, cn = 0.0, cd = 0.0;
+    for (uint32_t i = threadIdx.x; i < m.n_tasks; i += 256) {
+        const float4 x = residpart[m.first_task + i];
+        res += (double)x.x; cn += (double)x.y; cd += (double)x.z;
+    }
+    res = group_sum(res, lane, wave, sh[0]);
+    cn = group_sum(cn, lane, wave, sh[1]);
+    cd = group_sum(cd, lane, wave, sh[2]);
+    if (threadIdx.x == 0) { rec[R_FRES] = res; rec[R_CNUM] = cn; rec[R_CDEN] = cd; }
+    pick_digit<2>(sel, block, sel.hist + (uint64_t)block * kHistWords, lane, wave, rec, [](auto& c, const uint32_t* at) { load_bins(c, at); });
 }
 
 // Last digit: on the candidate lists that the second pass wrote, or on v where a block has none or one of them
@@ -1370,21 +1423,20 @@ __global__ __launch_bounds__(256) void k_final3(
     const float* __restrict__ v_all, const TileRow* __restrict__ tiles, const uint32_t* __restrict__ task_block, const uint32_t* __restrict__ cand,
     const uint32_t* __restrict__ cand_count, Selection sel, uint32_t* __restrict__ arrived, const uint32_t* __restrict__ scan3, double* __restrict__ rec_all)
 {
-    __shared__ uint32_t h[4 * kBins3];
+    __shared__ alignas(16) uint32_t h[4 * kBins3];
     const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index(), block = task_block[blockIdx.x];
     const TileRow& m = tiles[block];
     for (uint32_t i = threadIdx.x; i < 4 * kBins3; i += 256) h[i] = 0;
     const Prefixes d = distinct_prefixes(sel.prefix, block);
     auto count3 = [&](uint32_t bits) { count_match(h, d, kBins3, (bits & 0x7fffffffu) >> kShift2, bits & (kBins3 - 1)); };
     __syncthreads();
-    const uint32_t n_tasks = m.n_across * m.n_segs;
-    if (m.rows && !scan3[block]) {
+    if (m.rows && !scan3[block * kArriveStride]) {
         const uint32_t n = min(cand_count[blockIdx.x * 4 + wave], m.cand_cap);
         const uint32_t* list = cand + m.cand_base + ((uint64_t)(blockIdx.x - m.first_task) * 4 + wave) * m.cand_cap;
         for (uint32_t i = lane; i < n; i += 64) count3(list[i]);
     } else {
         // a matrix is no more than its coordinates here, shared evenly over its tasks
-        const uint32_t len = m.rows ? (uint32_t)((m.numel + n_tasks - 1) / n_tasks + 3) & ~3u : m.seg_len;
+        const uint32_t len = m.rows ? (uint32_t)((m.numel + m.n_tasks - 1) / m.n_tasks + 3) & ~3u : m.seg_len;
         walk_run<BAOC_GRAD_F32, false>(v_all, nullptr, m, len, [&](const float x[4], const float*, uint32_t n) {
 #pragma unroll
             for (uint32_t k = 0; k < 4; ++k)
@@ -1392,10 +1444,18 @@ __global__ __launch_bounds__(256) void k_final3(
         });
     }
     __syncthreads();
-    const bool single = n_tasks == 1;
-    if (!single) flush_hist(sel.hist + (uint64_t)block * kHistWords, h, d.n * kBins3);
-    if (!arrive_last(arrived + block * kArriveStride, n_tasks)) return;
-    pick_digit<3>(sel, m, block, single, h, lane, wave, rec_all + (uint64_t)block * kRecDoubles);
+    double* rec = rec_all + (uint64_t)block * kRecDoubles;
+    uint32_t* hist = sel.hist + (uint64_t)block * kHistWords;
+    if (m.n_tasks == 1) {
+        pick_digit<3>(sel, block, h, lane, wave, rec, [](auto& c, const uint32_t* at) { load_bins(c, at); });
+        return;
+    }
+    flush_hist(hist, h, d.n * kBins3);
+    if (!arrive_last(arrived + block * kArriveStride, m.n_tasks)) return;
+    pick_digit<3>(sel, block, hist, lane, wave, rec, [](auto& c, const uint32_t* at) {
+#pragma unroll
+        for (uint32_t i = 0; i < kBins3 / 64; ++i) c[i] = ld_device(at + i);
+    });
 }
 
 }  // namespace baoc
@@ -1423,13 +1483,14 @@ struct Plan {
     std::vector<BlockRow> rows;
     std::vector<TileRow> tiles;   // how finalize walks each block
     bool any_matrix = false, any_strips = false;
-    uint64_t n_tasks = 0, n_fin = 0;   // workgroups of the finalize passes and of k_fold_means
+    uint64_t n_tasks = 0, n_fin = 0;   // workgroups of the finalize passes; those of k_fold1 that fold row and column sums
     std::vector<Part> parts;      // of blocks of more than kDirectRows partial rows
+    std::vector<uint32_t> multi;  // blocks of several tasks
     uint64_t padded = 0;          // coordinates in m / v / g_prev
     uint64_t off_m = 0, off_v = 0, off_gp = 0, off_partials = 0, off_chunks = 0;
-    uint64_t off_rows = 0, off_tiles = 0, off_parts = 0, off_task_block = 0, off_fin_block = 0;   // the first three are uploaded in one piece
+    uint64_t off_rows = 0, off_tiles = 0, off_parts = 0, off_multi = 0, off_task_block = 0, off_fin_block = 0;   // the first four are uploaded in one piece
     uint64_t off_rec = 0, off_hist = 0, off_arrived = 0, off_selp = 0;                            // cleared up to off_selp
-    uint64_t off_selr = 0, off_scan3 = 0, off_rvec = 0, off_cvec = 0, off_residpart = 0, off_candcount = 0,
+    uint64_t off_selr = 0, off_rvec = 0, off_cvec = 0, off_residpart = 0, off_candcount = 0,
              off_cand = 0, off_rowpart = 0, off_colpart = 0, total = 0;
 };
 
@@ -1521,7 +1582,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     const uint32_t cg = prm->chunk_groups ? prm->chunk_groups : std::max(ds.chunk_groups, round);
     P.slices = prm->chunk_slices ? std::min(prm->chunk_slices, cg) : std::max(1u, cg / round);   // default: one round per slice
     P.slice_groups = (cg + P.slices - 1) / P.slices;
-    P.n_chunks = 0; P.rows.resize(n); P.parts.clear();
+    P.n_chunks = 0; P.rows.resize(n); P.parts.clear(); P.multi.clear();
     uint64_t state = 0;
     for (uint32_t i = 0; i < n; ++i) {
         const baoc_block& b = blocks[i];
@@ -1619,15 +1680,17 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
             P.any_matrix = true;
             m.off_r = n_r; m.off_c = n_c; m.off_rowpart = n_rowpart; m.off_colpart = n_colpart;
             n_r += b.rows; n_c += b.cols;
-            n_rowpart += (uint64_t)b.rows * m.n_tiles; n_colpart += (uint64_t)m.n_segs * b.cols;
+            if (m.n_tiles > 1) { n_rowpart += (uint64_t)b.rows * m.n_tiles; P.n_fin += ((uint64_t)b.rows + 63) / 64; }
+            if (m.n_segs > 1) { n_colpart += (uint64_t)m.n_segs * b.cols; P.n_fin += ((uint64_t)b.cols + 63) / 64; }
             tasks = (uint64_t)m.n_across * m.n_segs;
             // One candidate list per wavefront; a block's lists have room for an eighth of its coordinates.  The keys that share a
             // selected first digit are a few per cent of a block unless many coordinates have the same v.
             m.cand_cap = (uint32_t)align_up((b.numel + 32 * tasks - 1) / (32 * tasks), 4);
             m.cand_base = n_cand;
             n_cand += tasks * 4 * m.cand_cap;
-            P.n_fin += ((uint64_t)b.rows + 63) / 64 + ((uint64_t)b.cols + 63) / 64;
         }
+        m.n_tasks = (uint32_t)tasks;
+        if (tasks > 1) P.multi.push_back(i);
         P.n_tasks += tasks;
         if (P.n_tasks > 0x7fffffffull || P.n_fin > 0x7fffffffull) return BAOC_ERR_UNSUPPORTED;
     }
@@ -1642,6 +1705,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     place(P.off_rows, (uint64_t)n * sizeof(BlockRow));
     place(P.off_tiles, (uint64_t)n * sizeof(TileRow));
     place(P.off_parts, P.parts.size() * sizeof(Part));
+    place(P.off_multi, P.multi.size() * 4);
     place(P.off_task_block, P.n_tasks * 4);
     place(P.off_fin_block, P.n_fin * 4);
     place(P.off_rec, (uint64_t)n * kRecDoubles * 8);
@@ -1649,7 +1713,6 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     place(P.off_arrived, (uint64_t)n * kArriveStride * 4);
     place(P.off_selp, (uint64_t)n * 4 * 4);
     place(P.off_selr, (uint64_t)n * 4 * 4);
-    place(P.off_scan3, (uint64_t)n * 4);
     place(P.off_rvec, n_r * 4);
     place(P.off_cvec, n_c * 4);
     // The partial rows of the step are free in finalize.  The first pass's sums per task are folded before the second
@@ -1720,6 +1783,7 @@ static int begin_on(const baoc_block* blocks, uint32_t n_blocks, const baoc_prof
     std::memcpy(tables.data(), P.rows.data(), P.rows.size() * sizeof(BlockRow));
     std::memcpy(tables.data() + (P.off_tiles - P.off_rows), P.tiles.data(), P.tiles.size() * sizeof(TileRow));
     if (!P.parts.empty()) std::memcpy(tables.data() + (P.off_parts - P.off_rows), P.parts.data(), P.parts.size() * sizeof(Part));
+    if (!P.multi.empty()) std::memcpy(tables.data() + (P.off_multi - P.off_rows), P.multi.data(), P.multi.size() * 4);
     hipError_t e = hipMemcpy(h->ws + P.off_rows, tables.data(), tables.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) {
         const uint64_t n_clear = (P.off_selp - P.off_rec) / 16, work = std::max({P.n_chunks, P.n_tasks, P.n_fin, n_clear});
@@ -1834,25 +1898,29 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
     const float* v = f32_at(P.off_v);
     const TileRow* tiles = reinterpret_cast<const TileRow*>(h->ws + P.off_tiles);
     const uint32_t* task_block = u32_at(P.off_task_block);
-    uint32_t *arrived = u32_at(P.off_arrived), *scan3 = u32_at(P.off_scan3), *cand = u32_at(P.off_cand), *cand_count = u32_at(P.off_candcount);
-    float *rvec = f32_at(P.off_rvec), *cvec = f32_at(P.off_cvec), *residpart = f32_at(P.off_residpart);
+    uint32_t *arrived = u32_at(P.off_arrived), *scan3 = arrived + 1, *cand = u32_at(P.off_cand), *cand_count = u32_at(P.off_candcount);   // scan3: a block's flag stands next to its counter
+    const uint32_t* multi = u32_at(P.off_multi);
+    const uint32_t n_multi = (uint32_t)P.multi.size(), n_fold1 = n_multi + (want_F ? (uint32_t)P.n_fin : 0);
+    float *rvec = f32_at(P.off_rvec), *cvec = f32_at(P.off_cvec), *rowpart = f32_at(P.off_rowpart), *colpart = f32_at(P.off_colpart);
+    double2* taskpart = reinterpret_cast<double2*>(h->ws + P.off_residpart);
+    float4* residpart = reinterpret_cast<float4*>(h->ws + P.off_residpart);
     double* rec = reinterpret_cast<double*>(h->ws + P.off_rec);
     const Selection sel{u32_at(P.off_hist), u32_at(P.off_selp), u32_at(P.off_selr)};
     const float epsf = (float)h->params.eps;
     // v above which eps stays below a thousandth of sqrt(v) (and v is a normal number)
     const float eps_low = std::max(std::numeric_limits<float>::min(), (float)(1e6 * h->params.eps * h->params.eps));
 
-    hipLaunchKernelGGL(P.any_strips ? k_final1<true> : k_final1<false>, dim3(n_tasks), dim3(256), 0, st, v, tiles, task_block, f32_at(P.off_rowpart),
-                       f32_at(P.off_colpart), reinterpret_cast<double*>(residpart), sel, arrived, scan3, rec, epsf, eps_low, want_C);
-    if (want_F)
-        hipLaunchKernelGGL(k_fold_means, dim3((uint32_t)P.n_fin), dim3(256), 0, st, tiles, u32_at(P.off_fin_block), f32_at(P.off_rowpart),
-                           f32_at(P.off_colpart), rvec, cvec);
+    hipLaunchKernelGGL(P.any_strips ? k_final1<true> : k_final1<false>, dim3(n_tasks), dim3(256), 0, st, v, tiles, task_block, rowpart, colpart,
+                       rvec, cvec, taskpart, sel, scan3, rec, epsf, eps_low, want_C);
+    if (n_fold1)
+        hipLaunchKernelGGL(k_fold1, dim3(n_fold1), dim3(256), 0, st, tiles, multi, n_multi, u32_at(P.off_fin_block), rowpart, colpart, rvec, cvec,
+                           taskpart, sel, scan3, rec);
     auto final2 = [&](auto tt, auto f, auto c) {
         constexpr int TT = decltype(tt)::value;
         constexpr bool F = decltype(f)::value, C = decltype(c)::value;
         hipLaunchKernelGGL((P.any_strips ? k_final2<TT, F, C, true> : k_final2<TT, F, C, false>), dim3(n_tasks), dim3(256), 0, st,
                            v, static_cast<const typename GradIO<TT>::elem*>(rp.d_theta_flat), rp.theta_numel, tiles, task_block, rvec, cvec,
-                           residpart, sel, arrived, cand, cand_count, scan3, rec, epsf, eps_low);
+                           residpart, sel, cand, cand_count, scan3, rec, epsf, eps_low);
     };
     const std::true_type yes; const std::false_type no;
     const std::integral_constant<int, BAOC_GRAD_F32> t32; const std::integral_constant<int, BAOC_GRAD_BF16> t16;
@@ -1860,6 +1928,7 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
     else if (rp.theta_dtype == BAOC_GRAD_F32) { if (want_F) final2(t32, yes, yes); else final2(t32, no, yes); }
     else if (want_F) final2(t16, yes, yes);
     else final2(t16, no, yes);
+    if (n_multi) hipLaunchKernelGGL(k_fold2, dim3(n_multi), dim3(256), 0, st, tiles, multi, residpart, sel, rec);
     hipLaunchKernelGGL(k_final3, dim3(n_tasks), dim3(256), 0, st, v, tiles, task_block, cand, cand_count, sel, arrived, scan3, rec);
 
     hipError_t e = hipGetLastError();
