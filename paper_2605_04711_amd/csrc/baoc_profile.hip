@@ -810,9 +810,9 @@ __device__ __forceinline__ double group_sum(double x, uint32_t lane, uint32_t wa
 // in the same memory channels (a plain read of 4,096 x 4,096 matrices in this pattern: runs of 256 or 1,024 rows 6.0 - 6.3 TB/s, every
 // n_segs-th 16 rows 6.7 - 6.9; 4,096 x 11,008 6.8 - 7.0 either way.  Finalize passes of 3.5 G coordinates: 2323 -> 2270 and
 // 3580 -> 3516 us, 124 M unchanged).
-// In the second pass the keys that carry a selected first digit (a few per cent) are appended to a candidate list
-// per wavefront; the second digit is counted on the list at the end, the last digit by k_final3.  Keys that find no room are
-// counted as they come, and the last digit then takes a walk over v.
+// In the second pass the keys that carry a selected first digit (a few per cent) gather in LDS, a thousand at a time
+// are counted by their second digit and appended to a candidate list per wavefront; k_final3 counts the last digit on the lists.  Where
+// a list has no room the last digit takes a walk over v.
 // Large layouts are bound by HBM with the vector ALUs close behind, small ones by the number of wavefronts in flight.
 // Measured (first / second pass, us; before: one wavefront per 256 x 256 tile, scalar loads where a row is not a
 // multiple of 4, keys stored as they were found): 25.6 M coordinates of
@@ -1174,7 +1174,9 @@ __global__ __launch_bounds__(256) void k_fold1(const TileRow* __restrict__ tiles
     else cvec[m.off_c + at] = (float)(s / (double)m.rows);
 }
 
-constexpr uint32_t kStage = 320;                      // words per wavefront in which matching keys gather
+// Words per wavefront in which matching keys gather: with the histogram 37 KB of LDS, which leaves the four workgroups per CU that the
+// registers allow.
+constexpr uint32_t kStage = 1280;
 
 // F, C: Eq. 7 and Eq. 6 are wanted.
 template <int TT, bool F, bool C, bool STRIPS>
@@ -1244,7 +1246,7 @@ __global__ __launch_bounds__(256, 4) void k_final2(
         load_means();
         uint32_t* list = cand + m.cand_base + ((uint64_t)(blockIdx.x - m.first_task) * 4 + wave) * cap;
         uint32_t n_cand = 0;                                      // uniform over the wavefront; may grow past the list
-        // Matching keys gather in LDS and leave 64 at a time: stores of a few keys each would be waited for together with
+        // Matching keys gather in LDS and leave many at a time: stores of a few keys each would be waited for together with
         // the next round's loads.
         uint32_t* stage = staged + wave * kStage;
         uint32_t n_stage = 0;
@@ -1253,12 +1255,23 @@ __global__ __launch_bounds__(256, 4) void k_final2(
             if (hit) stage[n_stage + at] = bits;
             n_stage += (uint32_t)__builtin_popcountll(hits);
         };
-        // Whole sets of 64 go to the list; what is left moves to the front.  Keys for which the list has no room are counted here.
+        // Whole sets of 64 are counted and go to the list as far as it has room; what is left moves to the front.  The list is written
+        // through to memory: left in the L2 the lines go out one by one later, between the reads (3.5 G coordinates, 0.25 GB of keys:
+        // the pass takes 3470 us with plain stores, 3405 with nontemporal ones, 3355 so, 3210 with no stores at all).
         auto flush = [&](bool all) {
             const uint32_t n = all ? n_stage : n_stage & ~63u;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // lanes read what other lanes staged
-            for (uint32_t i = lane; i < n; i += 64)
-                if (n_cand + i < cap) list[n_cand + i] = stage[i]; else count2(stage[i]);
+            for (uint32_t i = lane; i < n; i += 256) {
+                uint32_t key[4];
+#pragma unroll
+                for (uint32_t q = 0; q < 4; ++q) key[q] = stage[min(i + 64 * q, kStage - 1)];
+#pragma unroll
+                for (uint32_t q = 0; q < 4; ++q)
+                    if (i + 64 * q < n) {
+                        if (n_cand + i + 64 * q < cap) st_device(&list[n_cand + i + 64 * q], key[q]);
+                        count2(key[q]);
+                    }
+            }
             n_cand += n; n_stage -= n;
             const uint32_t rest = lane < n_stage ? stage[n + lane] : 0u;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1283,7 +1296,7 @@ __global__ __launch_bounds__(256, 4) void k_final2(
                         const uint32_t bits = __builtin_bit_cast(uint32_t, x[q][k]), hi = (bits >> kShift1) & (kBins1 - 1);
                         append(hi == p0 || hi == p1, __builtin_amdgcn_ballot_w64(hi == p0) | __builtin_amdgcn_ballot_w64(hi == p1), bits);
                     }
-                    if (n_stage >= 64) flush(false);
+                    if (n_stage >= kStage - 256) flush(false);
                 }
             } else {
 #pragma unroll
@@ -1294,7 +1307,7 @@ __global__ __launch_bounds__(256, 4) void k_final2(
                         const bool hit = hi == p0 || hi == p1 || hi == d.pre[2] || hi == d.pre[3];
                         append(hit, __builtin_amdgcn_ballot_w64(hit), bits);
                     }
-                    if (n_stage >= 64) flush(false);
+                    if (n_stage >= kStage - 256) flush(false);
                 }
             }
             if (F) {
@@ -1355,7 +1368,7 @@ __global__ __launch_bounds__(256, 4) void k_final2(
                         cd = __builtin_fmaf(tk, tk, cd);
                     }
                 }
-                if (n_stage >= 64) flush(false);
+                if (n_stage >= kStage - 256) flush(false);
             }
             settle();
         }
@@ -1365,8 +1378,6 @@ __global__ __launch_bounds__(256, 4) void k_final2(
             cand_count[blockIdx.x * 4 + wave] = n_cand;
             if (n_cand > cap) scan3[block * kArriveStride] = 1u;              // list too short: the last digit of the block takes another walk over v
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");    // lanes read what other lanes stored
-        for (uint32_t i = lane; i < min(n_cand, cap); i += 64) count2(list[i]);
     } else {
         walk_run<TT, C>(v_all, theta, m, m.seg_len, [&](const float x[4], const float th[4], uint32_t n) {
             float yn = 0.f, yd = 0.f;
@@ -1433,7 +1444,14 @@ __global__ __launch_bounds__(256) void k_final3(
     if (m.rows && !scan3[block * kArriveStride]) {
         const uint32_t n = min(cand_count[blockIdx.x * 4 + wave], m.cand_cap);
         const uint32_t* list = cand + m.cand_base + ((uint64_t)(blockIdx.x - m.first_task) * 4 + wave) * m.cand_cap;
-        for (uint32_t i = lane; i < n; i += 64) count3(list[i]);
+        for (uint32_t at = lane; at < n; at += 512) {          // eight loads in flight
+            uint32_t key[8];
+#pragma unroll
+            for (uint32_t q = 0; q < 8; ++q) key[q] = list[min(at + 64 * q, n - 1)];
+#pragma unroll
+            for (uint32_t q = 0; q < 8; ++q)
+                if (at + 64 * q < n) count3(key[q]);
+        }
     } else {
         // a matrix is no more than its coordinates here, shared evenly over its tasks
         const uint32_t len = m.rows ? (uint32_t)((m.numel + m.n_tasks - 1) / m.n_tasks + 3) & ~3u : m.seg_len;
