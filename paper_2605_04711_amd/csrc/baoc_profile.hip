@@ -174,6 +174,7 @@ template <> struct GradIO<BAOC_GRAD_F32> {
     typedef f4 vec4_any __attribute__((aligned(4)));
     __device__ static __forceinline__ vec4 loadv(const elem* p) { return ld_stream<f4>(p); }
     __device__ static __forceinline__ vec4 loadv_any(const elem* p) { return ld_stream<vec4_any>(p); }
+    __device__ static __forceinline__ vec4 loadv_shared(const elem* p) { return *reinterpret_cast<const vec4_any*>(p); }
     __device__ static __forceinline__ void unpack(vec4 t, float g[4]) { g[0] = t.x; g[1] = t.y; g[2] = t.z; g[3] = t.w; }
     __device__ static __forceinline__ float load1(const elem* p) { return *p; }
     __device__ static __forceinline__ void store4(elem* p, const float g[4])
@@ -189,6 +190,7 @@ template <> struct GradIO<BAOC_GRAD_BF16> {
     typedef u2 vec4_any __attribute__((aligned(2)));
     __device__ static __forceinline__ vec4 loadv(const elem* p) { return ld_stream<u2>(p); }
     __device__ static __forceinline__ vec4 loadv_any(const elem* p) { return ld_stream<vec4_any>(p); }
+    __device__ static __forceinline__ vec4 loadv_shared(const elem* p) { return *reinterpret_cast<const vec4_any*>(p); }
     __device__ static __forceinline__ void unpack(vec4 t, float g[4])
     {
         g[0] = __builtin_bit_cast(float, t.x << 16); g[1] = __builtin_bit_cast(float, t.x & 0xffff0000u);
@@ -804,7 +806,8 @@ __device__ __forceinline__ double group_sum(double x, uint32_t lane, uint32_t wa
 // and 4 / wc down the rows.  A wavefront reads 4 rows x 64 columns (256 bytes a row) with one load, a lane 4
 // consecutive columns of a row, at any alignment: a row sum then takes four exchange levels for four rows at
 // once, and narrow or odd-sized matrices keep their lanes busy.  Loads are issued one round of kQuads * 4 rows
-// ahead of their use; rounds with a missing row or column load for themselves.
+// ahead of their use; only rounds with a missing row load for themselves.  A wavefront that lacks columns keeps the others of its workgroup
+// waiting at every row-sum exchange, and it did load for itself: 500 M coordinates of odd shapes 434 + 487 -> 411 + 461 us.
 // The rows of a workgroup are not next to each other: of the n_segs workgroups of a tile column each takes every n_segs-th round.
 // What is read at one time then lies close together, whatever the row length, where workgroups a power of two apart meet
 // in the same memory channels (a plain read of 4,096 x 4,096 matrices in this pattern: runs of 256 or 1,024 rows 6.0 - 6.3 TB/s, every
@@ -837,8 +840,8 @@ struct TilePart {
     uint32_t col;                         // first of the lane's 4 columns
     uint32_t lrow;                        // the lane's row in a quad
     uint32_t n_ok;                        // how many of the lane's columns exist (0..4)
-    uint32_t rounds, full;                // rounds of the workgroup; rounds of the wavefront without a missing row or column
-    bool any;                             // some of the wavefront's columns exist
+    uint32_t rounds, full;                // rounds of the workgroup; rounds of the wavefront without a missing row
+    bool any, all;                        // some, all of the wavefront's columns exist
     uint32_t offset;                      // the lane's first element of a full round, from the round's first row
     uint32_t base;                        // the lane's first column (clamped to an existing one)
 };
@@ -854,7 +857,8 @@ __device__ __forceinline__ Task task_of(const TileRow& m, uint32_t wg)
     return Task{seg, tile, min(m.n_tiles, tile + m.strips)};
 }
 
-__device__ __forceinline__ TilePart tile_part(const TileRow& m, uint32_t seg, uint32_t tile, uint32_t lane, uint32_t wave)
+// `left`: elements from the block's first one that may be read.
+__device__ __forceinline__ TilePart tile_part(const TileRow& m, uint32_t seg, uint32_t tile, uint32_t lane, uint32_t wave, uint64_t left)
 {
     TilePart t;
     t.seg = seg; t.tile = tile;
@@ -866,31 +870,49 @@ __device__ __forceinline__ TilePart tile_part(const TileRow& m, uint32_t seg, ui
     const uint32_t col0 = ((t.tile << m.wc_log) + t.wcol) * 64;
     t.col = col0 + 4 * (lane & 15u); t.lrow = lane >> 4;
     t.n_ok = t.col < m.cols ? min(4u, m.cols - t.col) : 0u;
-    t.any = col0 < m.cols;
+    t.any = col0 < m.cols; t.all = col0 + 64 <= m.cols;
     const uint32_t log_wr = 2 - m.wc_log, stripes = (m.rows + (kRoundRows << log_wr) - 1) / (kRoundRows << log_wr);
     t.rounds = (stripes - t.seg + m.n_segs - 1) / m.n_segs;
-    // offsets of a full round are 32-bit byte offsets
-    const uint32_t whole = m.rows / kRoundRows;
-    t.full = col0 + 64 <= m.cols && m.cols < (1u << 28) && whole > mine ? (whole - mine - 1) / step + 1 : 0;
-    t.offset = t.lrow * m.cols + t.col;
+    // Offsets of a full round are 32-bit byte offsets.  Where columns are missing its loads reach up to 3 elements past their row.
+    uint32_t whole = m.rows / kRoundRows;
+    if (!t.all && (uint64_t)whole * kRoundRows * m.cols + 3 > left) --whole;
+    t.full = t.any && m.cols < (1u << 28) && whole > mine ? (whole - mine - 1) / step + 1 : 0;
     t.base = min(t.col, m.cols - 1);
+    t.offset = t.lrow * m.cols + t.base;
     return t;
 }
 
 // First row (of the block) of a wavefront's round.
 __device__ __forceinline__ uint32_t round_row(const TilePart& t, uint32_t i) { return t.first + i * t.stride; }
 
-// Four elements per lane and quad of a full round.  The address is a scalar base and a 32-bit lane offset.
+// Whether rows start on cache lines.  Where they do not, wavefronts side by side share a line at every row's joint, and a line that
+// is loaded with the nontemporal hint is gone when the second one asks for it (303 M coordinates in rows of 1,500 and 4,031, bf16
+// parameters: passes 262 + 480 us with the hint, 248 + 412 without; in rows of 1,536 and 4,096 223 + 340 with it, 249 + 387 without).
+template <typename E> __device__ __forceinline__ bool whole_lines(const E* src, uint32_t cols)
+{
+    return ((reinterpret_cast<uintptr_t>(src) | (uintptr_t)cols * sizeof(E)) & 127u) == 0;
+}
+
+// Keeps the compiler from making one load of two that differ in the hint alone.
+__device__ __forceinline__ void apart() { asm volatile(""); }
+
+// Four elements per lane and quad of a full round (of lanes without a column, some).  The address is a scalar base and a 32-bit lane offset.
 template <int TT>
-__device__ __forceinline__ void load_full(typename GradIO<TT>::vec4 (&x)[kQuads], const typename GradIO<TT>::elem* __restrict__ src,
+__device__ __forceinline__ void load_full(typename GradIO<TT>::vec4 (&x)[kQuads], const typename GradIO<TT>::elem* __restrict__ src, bool lines,
                                           const TilePart& t, uint32_t cols, uint32_t i)
 {
     typedef typename GradIO<TT>::elem E;
     const char* p = reinterpret_cast<const char*>(src) + (uint64_t)round_row(t, i) * cols * sizeof(E);
+    const uint32_t lane = (uint32_t)(t.offset * sizeof(E));
+    const uint64_t step = (uint64_t)cols * (4 * sizeof(E));
+    if (lines) {
 #pragma unroll
-    for (uint32_t q = 0; q < kQuads; ++q) {
-        x[q] = GradIO<TT>::loadv_any(reinterpret_cast<const E*>(p + (uint32_t)(t.offset * sizeof(E))));
-        p += (uint64_t)cols * (4 * sizeof(E));
+        for (uint32_t q = 0; q < kQuads; ++q) x[q] = GradIO<TT>::loadv_any(reinterpret_cast<const E*>(p + q * step + lane));
+    } else {
+        apart();
+#pragma unroll
+        for (uint32_t q = 0; q < kQuads; ++q) x[q] = GradIO<TT>::loadv_shared(reinterpret_cast<const E*>(p + q * step + lane));
+        apart();
     }
 }
 
@@ -907,7 +929,7 @@ __device__ __forceinline__ void load_edge(typename GradIO<TT>::vec4 (&x)[kQuads]
     for (uint32_t q = 0; q < kQuads; ++q) {
         const typename IO::elem* p = src + ((uint64_t)min(first + 4 * q + t.lrow, t.rows - 1) * cols + t.base);
         if (wide) {
-            x[q] = IO::loadv_any(p);
+            x[q] = IO::loadv_shared(p);
         } else {
             typename IO::elem e[4];
 #pragma unroll
@@ -928,10 +950,11 @@ __device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, co
 {
     const float* src = v_all + m.state_start;
     const uint32_t cols = scalar_u32(m.cols);
+    const bool lines = whole_lines(src, cols);
     f4 nx[kQuads];
 #pragma unroll
     for (uint32_t q = 0; q < kQuads; ++q) nx[q] = f4{0.f, 0.f, 0.f, 0.f};
-    if (t.full) load_full<BAOC_GRAD_F32>(nx, src, t, cols, 0);
+    if (t.full) load_full<BAOC_GRAD_F32>(nx, src, lines, t, cols, 0);
     if (first)
         for (uint32_t i = threadIdx.x; i < kBins1; i += 256) h[i] = 0;
     // Column sums and the sum of p run over many rows per lane: kept in fp64 so that a constant
@@ -941,10 +964,12 @@ __device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, co
     for (uint32_t i = 0; i < t.rounds; ++i) {
         if (t.any) {
             float x[kQuads][4];
-            if (i < t.full) {
+            const bool full = i < t.full;
+            if (!full) load_edge<BAOC_GRAD_F32>(nx, src, kAnywhere, t, cols, i);
 #pragma unroll
-                for (uint32_t q = 0; q < kQuads; ++q) { x[q][0] = nx[q].x; x[q][1] = nx[q].y; x[q][2] = nx[q].z; x[q][3] = nx[q].w; }
-                if (i + 1 < t.full) load_full<BAOC_GRAD_F32>(nx, src, t, cols, i + 1);
+            for (uint32_t q = 0; q < kQuads; ++q) { x[q][0] = nx[q].x; x[q][1] = nx[q].y; x[q][2] = nx[q].z; x[q][3] = nx[q].w; }
+            if (i + 1 < t.full) load_full<BAOC_GRAD_F32>(nx, src, lines, t, cols, i + 1);
+            if (full && t.all) {
 #pragma unroll
                 for (uint32_t q = 0; q < kQuads; ++q)
 #pragma unroll
@@ -963,11 +988,8 @@ __device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, co
                 }
             } else {
                 const uint32_t row = round_row(t, i);
-                f4 ex[kQuads];
-                load_edge<BAOC_GRAD_F32>(ex, src, kAnywhere, t, cols, i);
 #pragma unroll
                 for (uint32_t q = 0; q < kQuads; ++q) {
-                    x[q][0] = ex[q].x; x[q][1] = ex[q].y; x[q][2] = ex[q].z; x[q][3] = ex[q].w;
                     const bool in_row = row + 4 * q + t.lrow < t.rows;
                     float prow = 0.f;
 #pragma unroll
@@ -1043,8 +1065,8 @@ __device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, co
     return psum;
 }
 
-// A run of a block without a matrix shape: 16 coordinates per thread and round.  Calls f(v, theta, how many of the
-// 16 exist) with the loads of a round issued together.  Runs start on a multiple of 4 coordinates, so a quad of v is
+// A run of a block without a matrix shape: 16 coordinates per thread and round.  Calls f(v, theta, how many of
+// the 4 exist); the loads of a round are issued together, one round ahead.  Runs start on a multiple of 4 coordinates, so a quad of v is
 // aligned and inside the padded state; theta is read at any alignment and not past the block's last coordinate.
 template <int TT, bool THETA, typename Fn>
 __device__ __forceinline__ void walk_run(const float* __restrict__ v_all, const typename GradIO<TT>::elem* __restrict__ theta, const TileRow& m, uint32_t len, Fn f)
@@ -1054,27 +1076,39 @@ __device__ __forceinline__ void walk_run(const float* __restrict__ v_all, const 
     const uint32_t n = e0 < m.numel ? (uint32_t)min((uint64_t)len, m.numel - e0) : 0u;
     const float* src = v_all + m.state_start + e0;
     const typename IO::elem* tsrc = theta + (m.grad_start + e0);
-    for (uint32_t at = threadIdx.x * 4; at < n; at += 4096) {
-        f4 x[4];
-        typename IO::vec4 th[4];
-#pragma unroll
-        for (uint32_t q = 0; q < 4; ++q) { x[q] = f4{0.f, 0.f, 0.f, 0.f}; th[q] = typename IO::vec4{}; }
+    const bool lines = THETA && whole_lines(tsrc, 0);
+    f4 nx[4];
+    typename IO::vec4 nt[4];
+    auto issue = [&](uint32_t at) {
 #pragma unroll
         for (uint32_t q = 0; q < 4; ++q)
-            if (at + q * 1024 < n) x[q] = ld_stream<f4>(src + at + q * 1024);
+            if (at + q * 1024 < n) nx[q] = ld_stream<f4>(src + at + q * 1024);
         if (THETA) {
 #pragma unroll
             for (uint32_t q = 0; q < 4; ++q) {
                 const uint32_t e = at + q * 1024;
-                if (e + 4 <= n) th[q] = IO::loadv_any(tsrc + e);
-                else if (e < n) {
+                if (e + 4 <= n) {
+                    if (lines) nt[q] = IO::loadv_any(tsrc + e);
+                    else { apart(); nt[q] = IO::loadv_shared(tsrc + e); apart(); }
+                }
+                if (e < n && e + 4 > n) {
                     typename IO::elem part[4];
 #pragma unroll
                     for (uint32_t k = 0; k < 4; ++k) part[k] = e + k < n ? tsrc[e + k] : typename IO::elem(0);
-                    th[q] = __builtin_bit_cast(typename IO::vec4, part);
+                    nt[q] = __builtin_bit_cast(typename IO::vec4, part);
                 }
             }
         }
+    };
+#pragma unroll
+    for (uint32_t q = 0; q < 4; ++q) { nx[q] = f4{0.f, 0.f, 0.f, 0.f}; nt[q] = typename IO::vec4{}; }
+    issue(threadIdx.x * 4);
+    for (uint32_t at = threadIdx.x * 4; at < n; at += 4096) {
+        f4 x[4];
+        typename IO::vec4 th[4];
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) { x[q] = nx[q]; th[q] = nt[q]; }
+        if (at + 4096 < n) issue(at + 4096);
 #pragma unroll
         for (uint32_t q = 0; q < 4; ++q) {
             const uint32_t e = at + q * 1024;
@@ -1090,7 +1124,7 @@ __device__ __forceinline__ void walk_run(const float* __restrict__ v_all, const 
 // STRIPS: the layout has blocks whose tasks take several tiles.  Layouts without such blocks have kernels without the loop over tiles
 // (with it finalize of 1.5 G coordinates takes 3.72 instead of 3.70 ms).
 template <bool STRIPS>
-__global__ __launch_bounds__(256) void k_final1(
+__global__ __launch_bounds__(256, STRIPS ? 4 : 5) void k_final1(
     const float* __restrict__ v_all, const TileRow* __restrict__ tiles, const uint32_t* __restrict__ task_block,
     float* __restrict__ rowpart, float* __restrict__ colpart, float* __restrict__ rvec, float* __restrict__ cvec, double2* __restrict__ taskpart,
     Selection sel, uint32_t* __restrict__ scan3, double* __restrict__ rec_all, float eps, float eps_low, bool want_p)
@@ -1104,7 +1138,7 @@ __global__ __launch_bounds__(256) void k_final1(
     if (m.rows) {
         const Task k = task_of<STRIPS>(m, blockIdx.x);
         for (uint32_t tile = k.tile; tile < k.last; ++tile)
-            psum += tile_pass1(v_all, m, tile_part(m, k.seg, tile, lane, wave), tile == k.tile, lane, wave, rowpart, colpart, rvec, cvec, h, rowsum, colsum,
+            psum += tile_pass1(v_all, m, tile_part(m, k.seg, tile, lane, wave, kAnywhere), tile == k.tile, lane, wave, rowpart, colpart, rvec, cvec, h, rowsum, colsum,
                                eps, eps_low, want_p, total);
     } else {
         for (uint32_t i = threadIdx.x; i < kBins1; i += 256) h[i] = 0;
@@ -1211,20 +1245,21 @@ __global__ __launch_bounds__(256, 4) void k_final2(
     __syncthreads();
     if (m.rows) {
         const Task k = task_of<STRIPS>(m, blockIdx.x);
-        TilePart t = tile_part(m, k.seg, k.tile, lane, wave);
         const float* src = v_all + m.state_start;
         const typename IO::elem* tsrc = theta + m.grad_start;
-        const uint64_t tleft = theta_numel - m.grad_start;
+        const uint64_t tleft = C ? theta_numel - m.grad_start : kAnywhere;
+        TilePart t = tile_part(m, k.seg, k.tile, lane, wave, tleft);
         const float* rr = rvec + m.off_r;
         // no room where the first pass has found the block to go without lists (or a list of this pass overflowed meanwhile, which comes
         // to the same: the last digit is then not taken from the lists)
         const uint32_t cols = scalar_u32(m.cols), cap = scalar_u32(scan3[block * kArriveStride] ? 0u : m.cand_cap);
+        const bool lines = whole_lines(src, cols), tlines = C && whole_lines(tsrc, cols);
         f4 nx[kQuads]; TV nt[kQuads]; float nr[kQuads];
 #pragma unroll
         for (uint32_t q = 0; q < kQuads; ++q) { nx[q] = f4{0.f, 0.f, 0.f, 0.f}; nt[q] = TV{}; nr[q] = 0.f; }
         auto issue = [&](uint32_t i) {
-            load_full<BAOC_GRAD_F32>(nx, src, t, cols, i);
-            if (C) load_full<TT>(nt, tsrc, t, cols, i);
+            load_full<BAOC_GRAD_F32>(nx, src, lines, t, cols, i);
+            if (C) load_full<TT>(nt, tsrc, tlines, t, cols, i);
             if (F) {
                 const float* p = rr + round_row(t, i);
 #pragma unroll
@@ -1279,7 +1314,36 @@ __global__ __launch_bounds__(256, 4) void k_final2(
         };
         static_assert(kStage >= 63 + 64 * 4, "a quad of keys and what the last flush left");
         const uint32_t p0 = d.pre[0], p1 = d.pre[1];
-        for (uint32_t i = 0; i < full; ++i) {
+        // a round that lacks rows or columns
+        auto masked = [&](const f4 (&vx)[kQuads], const TV (&vt)[kQuads], const float (&vr)[kQuads], uint32_t first) {
+#pragma unroll
+            for (uint32_t q = 0; q < kQuads; ++q) {
+                const bool in_row = first + 4 * q + t.lrow < t.rows;
+                const float x[4] = {vx[q].x, vx[q].y, vx[q].z, vx[q].w};
+                float th[4] = {0.f, 0.f, 0.f, 0.f};
+                if (C) IO::unpack(vt[q], th);
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) {
+                    const bool in = in_row && k < t.n_ok;
+                    const uint32_t bits = __builtin_bit_cast(uint32_t, x[k]), hi = (bits >> kShift1) & (kBins1 - 1);
+                    const bool hit = in && (hi == p0 || hi == p1 || hi == d.pre[2] || hi == d.pre[3]);
+                    append(hit, __builtin_amdgcn_ballot_w64(hit), bits);
+                    if (F) {
+                        const float dd = in ? __builtin_fmaf(-vr[q], cm[k], x[k]) : 0.f;
+                        res = __builtin_fmaf(dd, dd, res);
+                    }
+                    if (C) {
+                        const float tk = in ? th[k] : 0.f;
+                        const float y = in ? __builtin_fmaf(preconditioner(x[k], eps), inv_pbar, -1.0f) * tk : 0.f;
+                        cn = __builtin_fmaf(y, y, cn);
+                        cd = __builtin_fmaf(tk, tk, cd);
+                    }
+                }
+                if (n_stage >= kStage - 256) flush(false);
+            }
+            settle();
+        };
+        for (uint32_t i = 0, n = t.all ? full : 0; i < n; ++i) {
             float x[kQuads][4], th[kQuads][4], ri[kQuads];
 #pragma unroll
             for (uint32_t q = 0; q < kQuads; ++q) {
@@ -1338,39 +1402,25 @@ __global__ __launch_bounds__(256, 4) void k_final2(
             }
             if ((i + 1) % kSubRounds == 0) settle();
         }
+        if (!t.all) {
+            for (uint32_t i = 0; i < full; ++i) {
+                f4 ex[kQuads]; TV et[kQuads]; float er[kQuads];
+#pragma unroll
+                for (uint32_t q = 0; q < kQuads; ++q) { ex[q] = nx[q]; et[q] = nt[q]; er[q] = nr[q]; }
+                if (i + 1 < full) issue(i + 1);
+                masked(ex, et, er, round_row(t, i));
+            }
+        }
         for (uint32_t i = full; i < rounds; ++i) {
-            if (!one && i > 0) { t = tile_part(m, k.seg, k.tile + i, lane, wave); load_means(); }
+            if (!one && i > 0) { t = tile_part(m, k.seg, k.tile + i, lane, wave, tleft); load_means(); }
             if (!t.any) break;
             const uint32_t round = one ? i : 0, first = round_row(t, round);
-            f4 ex[kQuads]; TV et[kQuads];
+            f4 ex[kQuads]; TV et[kQuads]; float er[kQuads];
             load_edge<BAOC_GRAD_F32>(ex, src, kAnywhere, t, cols, round);
+#pragma unroll
+            for (uint32_t q = 0; q < kQuads; ++q) { et[q] = TV{}; er[q] = F ? rr[min(first + 4 * q + t.lrow, t.rows - 1)] : 0.f; }
             if (C) load_edge<TT>(et, tsrc, tleft, t, cols, round);
-#pragma unroll
-            for (uint32_t q = 0; q < kQuads; ++q) {
-                const bool in_row = first + 4 * q + t.lrow < t.rows;
-                const float ri = F ? rr[min(first + 4 * q + t.lrow, t.rows - 1)] : 0.f, x[4] = {ex[q].x, ex[q].y, ex[q].z, ex[q].w};
-                float th[4] = {0.f, 0.f, 0.f, 0.f};
-                if (C) IO::unpack(et[q], th);
-#pragma unroll
-                for (uint32_t k = 0; k < 4; ++k) {
-                    const bool in = in_row && k < t.n_ok;
-                    const uint32_t bits = __builtin_bit_cast(uint32_t, x[k]), hi = (bits >> kShift1) & (kBins1 - 1);
-                    const bool hit = in && (hi == p0 || hi == p1 || hi == d.pre[2] || hi == d.pre[3]);
-                    append(hit, __builtin_amdgcn_ballot_w64(hit), bits);
-                    if (F) {
-                        const float dd = in ? __builtin_fmaf(-ri, cm[k], x[k]) : 0.f;
-                        res = __builtin_fmaf(dd, dd, res);
-                    }
-                    if (C) {
-                        const float tk = in ? th[k] : 0.f;
-                        const float y = in ? __builtin_fmaf(preconditioner(x[k], eps), inv_pbar, -1.0f) * tk : 0.f;
-                        cn = __builtin_fmaf(y, y, cn);
-                        cd = __builtin_fmaf(tk, tk, cd);
-                    }
-                }
-                if (n_stage >= kStage - 256) flush(false);
-            }
-            settle();
+            masked(ex, et, er, first);
         }
         settle();
         flush(true);
@@ -1532,11 +1582,12 @@ static uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 // 2,000 rows of 100 blocks 14.2 instead of 13.4, 2,048 rows of 16 blocks 15.5 instead of 13.5.
 constexpr uint64_t kFoldRows = 1024, kFoldBlockRows = 64;
 
-// Coordinates of a tile (one workgroup of the tile passes): doubled from the smallest until kTileTarget of them hold the layout,
-// or to the cap.  Doubling ends between 1,024 and 2,048 whole tiles; partial tiles come on top, and beyond 537 M coordinates the
-// cap leaves more.  The chip holds 1,024 workgroups of k_final2 and 1,280 of k_final1 at a time.  A smaller tile pays
-// for its histograms more often (finalize of 124 M coordinates, tiles of 65,536: 407 us, of 16,384: 470 us), and so does
-// a cap below 262,144 on large layouts (3.5 G coordinates: 6.21 ms, with 131,072 6.33 ms, with 1 M 6.55 ms).
+// Coordinates of a tile (one workgroup of the tile passes): the layout's by kTileTarget, between the smallest and the cap.  Partial tiles
+// come on top, and beyond 537 M coordinates the cap leaves more.  The chip holds 1,024 workgroups of k_final2 and 1,280 of k_final1
+// at a time.  In powers of two a layout just past one had little more than 1,024 of them, and a second round of a few (303 M coordinates,
+// rows of 1,500 and 4,031: passes 282 + 540 us, now 262 + 478).  A smaller tile pays for its histograms more often (kernels of a finalize
+// of 124 M coordinates with 3,000 tiles 273 us, with 4,000 285, now 262; 25.6 M 93, 107 and 90; layouts of odd shapes gain up to 5 %), and
+// so does a cap below 262,144 on large layouts (3.5 G coordinates: 5.92 ms with 131,072, 5.68 now).
 constexpr uint64_t kTileCoordsMin = 8192, kTileCoordsMax = 262144, kTileTarget = 2048;
 // Rows of a tile: those of a 64-column tile of the largest size.  A matrix of fewer columns still occupies 64 columns of lanes, so
 // without this line its workgroups walk up to 131,072 rows one round after another (40 matrices of 50,000 x 4 and 32 of 4,096 x
@@ -1629,8 +1680,9 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     // single row or column is rank one by construction (F = 0 exactly) and counts as a run.
     P.tiles.resize(n); P.any_matrix = P.any_strips = false; P.n_tasks = 0; P.n_fin = 0;
     uint64_t n_r = 0, n_c = 0, n_rowpart = 0, n_colpart = 0, n_cand = 0;
-    uint64_t tile_coords = kTileCoordsMin;
-    while (tile_coords < kTileCoordsMax && tile_coords * kTileTarget < total) tile_coords *= 2;
+    const uint64_t tile_coords = std::min(kTileCoordsMax, std::max(kTileCoordsMin, align_up(total / kTileTarget, 1024)));
+    uint64_t run_max = kTileCoordsMin;                               // the longest run: a power of two
+    while (run_max < tile_coords) run_max *= 2;
     uint64_t matrix_tasks = 0, run_budget = 0;
     for (uint32_t i = 0; i < n; ++i) {
         const baoc_block& b = blocks[i];
@@ -1668,8 +1720,8 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     // with the number of runs whatever the launch shape.
     uint64_t least = kTileCoordsMin;
     auto run_coords = [&](uint64_t numel) {
-        uint64_t r = std::min(tile_coords, kRunCoords);
-        while (r < tile_coords && r * kBlockRuns < numel) r *= 2;
+        uint64_t r = std::min(run_max, kRunCoords);
+        while (r < run_max && r * kBlockRuns < numel) r *= 2;
         return std::max(r, least);
     };
     for (; least < (1u << 30); least = align_up(least * 5 / 4, 1024)) {
@@ -1701,9 +1753,10 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
             if (m.n_tiles > 1) { n_rowpart += (uint64_t)b.rows * m.n_tiles; P.n_fin += ((uint64_t)b.rows + 63) / 64; }
             if (m.n_segs > 1) { n_colpart += (uint64_t)m.n_segs * b.cols; P.n_fin += ((uint64_t)b.cols + 63) / 64; }
             tasks = (uint64_t)m.n_across * m.n_segs;
-            // One candidate list per wavefront; a block's lists have room for an eighth of its coordinates.  The keys that share a
-            // selected first digit are a few per cent of a block unless many coordinates have the same v.
-            m.cand_cap = (uint32_t)align_up((b.numel + 32 * tasks - 1) / (32 * tasks), 4);
+            // One candidate list per wavefront; a block's lists have room for an eighth of its coordinates, less the 48 bytes that a task
+            // takes elsewhere.  The keys that share a selected first digit are a few per cent of a block unless many coordinates have
+            // the same v.
+            m.cand_cap = (uint32_t)((std::max<uint64_t>(b.numel / (32 * tasks), 3) - 3) / 4 * 4);
             m.cand_base = n_cand;
             n_cand += tasks * 4 * m.cand_cap;
         }
