@@ -15,10 +15,15 @@ constexpr uint32_t kNumSums = 16;        // floats in one partial-sum row
 // row conflicts.  fp32 gradients: single-wavefront workgroups of two adjacent groups, about 10 resident
 // per compute unit; bf16: 4 wavefronts x 2 groups, 3 resident.  A chunk (the unit of the step's
 // tables) is cut into slices of one round each.
+// Layouts that do not keep the chip busy for long take more wavefronts, and fp32 ones other workgroups (us a step, fp32: 4 wavefronts x 1
+// group with 4 resident, the same with 7, 2 wavefronts x 2 groups with 6, the shape of large layouts: 17 M coordinates 78.6, 74.8, 75.8,
+// 81.7; 25.6 M 115.9, 110.2, 111.8, 120.1; 40 M 185, 182.7, 178.9, 187; 66 M 318.9, 322.8, 314.4, 318.1; 90 M 423, 430, 420, 414.  bf16 with
+// 3 and 4 resident: 17 M 62.6, 61.9, 25.6 M 91.2, 89.2, 66 M 229.3, 227.7, 90 M 317.8, 324.2).
 struct LaunchShape { uint32_t chunk_groups, groups_per_wave, waves_per_workgroup, resident_workgroups; };
 constexpr LaunchShape kDefaultShape[2] = {{4, 2, 1, 10}, {8, 2, 4, 3}};
-constexpr LaunchShape kSmallF32Shape = {4, 1, 4, 4};          // fp32 layouts below kSmallLayout coordinates
-constexpr uint64_t kSmallLayout = 1ull << 26;
+constexpr LaunchShape kMediumShape[2] = {{4, 2, 2, 6}, {8, 2, 4, 4}};         // below kMediumLayout coordinates
+constexpr LaunchShape kSmallShape[2] = {{4, 1, 4, 7}, {8, 2, 4, 4}};          // below kSmallLayout coordinates
+constexpr uint64_t kMediumLayout = 1ull << 26, kSmallLayout = 1ull << 25;
 constexpr uint32_t kLdsBytesPerCU = 160 * 1024;   // gfx950
 
 // order of the sums in a partial row and in the per-block raw record

@@ -1656,8 +1656,9 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     Plan& P = *out;
     uint64_t total = 0;
     for (uint32_t i = 0; i < n; ++i) total += blocks[i].numel;
-    // fp32 layouts too small to keep the chip busy for long (ResNet-50-sized) run faster with the 4-wavefront shape
-    const LaunchShape& ds = (prm->grad_dtype == BAOC_GRAD_F32 && total < kSmallLayout) ? kSmallF32Shape : kDefaultShape[prm->grad_dtype];
+    // a caller's own groups or wavefronts stand next to the small shape's: the medium one's other half would mean more workgroups
+    const bool medium = total < kMediumLayout && !prm->groups_per_wave && !prm->waves_per_workgroup;
+    const LaunchShape& ds = (medium && total >= kSmallLayout ? kMediumShape : (total < kMediumLayout ? kSmallShape : kDefaultShape))[prm->grad_dtype];
     P.gpw = prm->groups_per_wave ? prm->groups_per_wave : ds.groups_per_wave;
     P.nw = prm->waves_per_workgroup ? prm->waves_per_workgroup : ds.waves_per_workgroup;
     P.resident = prm->resident_workgroups ? prm->resident_workgroups : ds.resident_workgroups;
