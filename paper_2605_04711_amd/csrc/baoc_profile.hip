@@ -23,6 +23,7 @@
 #include <cstdio>
 #include <cstring>
 #include <limits>
+#include <mutex>
 #include <new>
 #include <type_traits>
 #include <vector>
@@ -772,9 +773,9 @@ __device__ __forceinline__ void fold_first(const Selection& sel, const TileRow& 
 }
 
 // The PASS-th digit (2 or 3) of a block's four ranks, a wavefront each; `hist` has a histogram for every distinct prefix and is left
-// cleared.  `load` reads consecutive bins.  Called by a whole workgroup.
+// cleared.  `load` reads consecutive bins; the last digit completes the order statistics.  Called by a whole workgroup.
 template <int PASS, typename L>
-__device__ __forceinline__ void pick_digit(const Selection& sel, uint32_t block, uint32_t* hist, uint32_t lane, uint32_t wave, double* rec, L load)
+__device__ __forceinline__ void pick_digit(const Selection& sel, uint32_t block, uint32_t* hist, uint32_t lane, uint32_t wave, double* order, L load)
 {
     constexpr uint32_t NB = PASS == 2 ? kBins2 : kBins3, N = NB / 64;
     const uint32_t id = block * 4 + wave;
@@ -791,7 +792,7 @@ __device__ __forceinline__ void pick_digit(const Selection& sel, uint32_t block,
         const Digit f = bin_of(c, lane * N, at, rank);
         const uint32_t key = (prefix << (PASS == 2 ? kBits2 : kBits3)) | f.bin;
         if (PASS == 2) { sel.prefix[id] = key; sel.rank[id] = f.rank; }
-        else rec[R_ORDER + wave] = (double)__builtin_bit_cast(float, key);
+        else order[wave] = (double)__builtin_bit_cast(float, key);
     }
     for (uint32_t i = threadIdx.x; i < NB; i += 256) reinterpret_cast<uint4*>(hist)[i] = uint4{0u, 0u, 0u, 0u};
 }
@@ -1465,7 +1466,7 @@ __global__ __launch_bounds__(256, 4) void k_final2(
     double* rec = rec_all + (uint64_t)block * kRecDoubles;
     if (m.n_tasks == 1) {
         if (threadIdx.x == 0) { rec[R_FRES] = (double)task_sum(0); rec[R_CNUM] = (double)task_sum(1); rec[R_CDEN] = (double)task_sum(2); }
-        pick_digit<2>(sel, block, h, lane, wave, rec, [](auto& c, const uint32_t* at) { load_bins(c, at); });
+        pick_digit<2>(sel, block, h, lane, wave, nullptr, [](auto& c, const uint32_t* at) { load_bins(c, at); });
         return;
     }
     if (threadIdx.x == 0) residpart[blockIdx.x] = float4{task_sum(0), task_sum(1), task_sum(2), 0.f};
@@ -1489,14 +1490,14 @@ __global__ __launch_bounds__(256) void k_fold2(const TileRow* __restrict__ tiles
     cn = group_sum(cn, lane, wave, sh[1]);
     cd = group_sum(cd, lane, wave, sh[2]);
     if (threadIdx.x == 0) { rec[R_FRES] = res; rec[R_CNUM] = cn; rec[R_CDEN] = cd; }
-    pick_digit<2>(sel, block, sel.hist + (uint64_t)block * kHistWords, lane, wave, rec, [](auto& c, const uint32_t* at) { load_bins(c, at); });
+    pick_digit<2>(sel, block, sel.hist + (uint64_t)block * kHistWords, lane, wave, nullptr, [](auto& c, const uint32_t* at) { load_bins(c, at); });
 }
 
 // Last digit: on the candidate lists that the second pass wrote, or on v where a block has none or one of them
-// overflowed.
+// overflowed.  Leaves the records in `out_all`, host memory or the records themselves.
 __global__ __launch_bounds__(256) void k_final3(
     const float* __restrict__ v_all, const TileRow* __restrict__ tiles, const uint32_t* __restrict__ task_block, const uint32_t* __restrict__ cand,
-    const uint32_t* __restrict__ cand_count, Selection sel, uint32_t* __restrict__ arrived, const uint32_t* __restrict__ scan3, double* __restrict__ rec_all)
+    const uint32_t* __restrict__ cand_count, Selection sel, uint32_t* __restrict__ arrived, const uint32_t* __restrict__ scan3, const double* __restrict__ rec_all, double* __restrict__ out_all)
 {
     __shared__ alignas(16) uint32_t h[4 * kBins3];
     const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index(), block = task_block[blockIdx.x];
@@ -1526,15 +1527,21 @@ __global__ __launch_bounds__(256) void k_final3(
         });
     }
     __syncthreads();
-    double* rec = rec_all + (uint64_t)block * kRecDoubles;
+    // the block's record as it leaves the device; the order statistics are new
+    auto finish = [&](uint32_t* hist, auto load) {
+        const double* rec = rec_all + (uint64_t)block * kRecDoubles;
+        double* out = out_all + (uint64_t)block * kRecDoubles;
+        if (out != rec && threadIdx.x < kRecDoubles && threadIdx.x - R_ORDER >= 4) out[threadIdx.x] = rec[threadIdx.x];
+        pick_digit<3>(sel, block, hist, lane, wave, out + R_ORDER, load);
+    };
     uint32_t* hist = sel.hist + (uint64_t)block * kHistWords;
     if (m.n_tasks == 1) {
-        pick_digit<3>(sel, block, h, lane, wave, rec, [](auto& c, const uint32_t* at) { load_bins(c, at); });
+        finish(h, [](auto& c, const uint32_t* at) { load_bins(c, at); });
         return;
     }
     flush_hist(hist, h, d.n * kBins3);
     if (!arrive_last(arrived + block * kArriveStride, m.n_tasks)) return;
-    pick_digit<3>(sel, block, hist, lane, wave, rec, [](auto& c, const uint32_t* at) {
+    finish(hist, [](auto& c, const uint32_t* at) {
 #pragma unroll
         for (uint32_t i = 0; i < kBins3 / 64; ++i) c[i] = ld_device(at + i);
     });
@@ -1585,8 +1592,46 @@ struct baoc_profiler {
     uint32_t steps = 0;
     uint64_t max_end = 0;         // largest offset + numel over the blocks
     int sticky = BAOC_OK;
+    double* host_rec = nullptr;   // where finalize leaves the records: memory of the pool below, or h_rec
+    uint64_t host_bytes = 0;      // its size in the pool
     std::vector<double> h_rec;
 };
+
+// Pinned host memory that the last kernel of finalize writes the records to.  A copy to pageable memory is staged by the runtime after the
+// kernels have ended (finalize of 25.6 M coordinates, 41 KB: 135 us with the copy, 125 so; of 32,768 49.6 and 40.5).  Pinning takes longer than that, so buffers
+// are kept for the next handle: at most kPoolBytes in all are ever pinned, in powers of two up to kPoolBuffer; a handle that finds none, and
+// a static one, which allocates nothing, has the copy.
+constexpr uint64_t kPoolBytes = 4ull << 20, kPoolBuffer = 1ull << 20;
+static std::mutex g_pool_mutex;
+static std::vector<std::pair<double*, uint64_t>> g_pool_free;
+static uint64_t g_pool_pinned = 0;
+
+static double* pool_take(uint64_t bytes, uint64_t* got)
+{
+    uint64_t size = 4096;
+    while (size < bytes) size *= 2;
+    if (size > kPoolBuffer) return nullptr;
+    std::lock_guard<std::mutex> lock(g_pool_mutex);
+    for (size_t i = 0; i < g_pool_free.size(); ++i)
+        if (g_pool_free[i].second >= size) {
+            double* p = g_pool_free[i].first;
+            *got = g_pool_free[i].second;
+            g_pool_free[i] = g_pool_free.back(); g_pool_free.pop_back();
+            return p;
+        }
+    if (g_pool_pinned + size > kPoolBytes) return nullptr;
+    void* p = nullptr;
+    if (hipHostMalloc(&p, size, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess || !p) { (void)hipGetLastError(); return nullptr; }
+    g_pool_pinned += size;
+    *got = size;
+    return static_cast<double*>(p);
+}
+
+static void pool_give(double* p, uint64_t bytes)
+{
+    std::lock_guard<std::mutex> lock(g_pool_mutex);
+    g_pool_free.emplace_back(p, bytes);
+}
 
 static uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 
@@ -1852,7 +1897,7 @@ extern "C" int baoc_profile_workspace_bytes(const baoc_block* blocks, uint32_t n
 
 // Shared by the two begin calls: plan, carve `d_workspace`, clear what must start at zero, upload the tables.
 static int begin_on(const baoc_block* blocks, uint32_t n_blocks, const baoc_profile_params* params,
-                    void* d_workspace, uint64_t workspace_bytes, baoc_profiler** out)
+                    void* d_workspace, uint64_t workspace_bytes, bool pinned, baoc_profiler** out)
 {
     baoc_profiler* h = new (std::nothrow) baoc_profiler();
     if (!h) return BAOC_ERR_INVALID;
@@ -1883,7 +1928,9 @@ static int begin_on(const baoc_block* blocks, uint32_t n_blocks, const baoc_prof
     }
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) { (void)hipGetLastError(); delete h; return BAOC_ERR_HIP; }
-    h->h_rec.resize((size_t)n_blocks * kRecDoubles);
+    const uint64_t rec_bytes = (uint64_t)n_blocks * kRecDoubles * sizeof(double);
+    if (pinned) h->host_rec = pool_take(rec_bytes, &h->host_bytes);
+    if (!h->host_rec) h->h_rec.resize((size_t)n_blocks * kRecDoubles);
     *out = h;
     return BAOC_OK;
 }
@@ -1893,7 +1940,7 @@ extern "C" int baoc_profile_begin(const baoc_block* blocks, uint32_t n_blocks,
                                   void* d_workspace, uint64_t workspace_bytes, baoc_profiler** out)
 {
     if (!out || !d_workspace) return BAOC_ERR_INVALID;
-    return begin_on(blocks, n_blocks, params, d_workspace, workspace_bytes, out);
+    return begin_on(blocks, n_blocks, params, d_workspace, workspace_bytes, true, out);
 }
 
 extern "C" int baoc_profile_begin_static(const baoc_block* blocks, uint32_t n_blocks,
@@ -1909,7 +1956,7 @@ extern "C" int baoc_profile_begin_static(const baoc_block* blocks, uint32_t n_bl
         if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) { (void)hipGetLastError(); return BAOC_ERR_HIP; }
         g_scratch_ptr[dev] = ptr;
     }
-    const int rc = begin_on(blocks, n_blocks, params, g_scratch_ptr[dev], BAOC_STATIC_WORKSPACE_BYTES, out);
+    const int rc = begin_on(blocks, n_blocks, params, g_scratch_ptr[dev], BAOC_STATIC_WORKSPACE_BYTES, false, out);
     if (rc == BAOC_OK) { (*out)->static_device = dev; g_scratch_busy[dev] = true; }
     return rc;
 }
@@ -2015,17 +2062,18 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
     else if (want_F) final2(t16, yes, yes);
     else final2(t16, no, yes);
     if (n_multi) hipLaunchKernelGGL(k_fold2, dim3(n_multi), dim3(256), 0, st, tiles, multi, residpart, sel, rec);
-    hipLaunchKernelGGL(k_final3, dim3(n_tasks), dim3(256), 0, st, v, tiles, task_block, cand, cand_count, sel, arrived, scan3, rec);
+    hipLaunchKernelGGL(k_final3, dim3(n_tasks), dim3(256), 0, st, v, tiles, task_block, cand, cand_count, sel, arrived, scan3, rec,
+                       h->host_rec ? h->host_rec : rec);
 
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(h->h_rec.data(), rec, h->h_rec.size() * 8, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess && !h->host_rec) e = hipMemcpyAsync(h->h_rec.data(), rec, h->h_rec.size() * 8, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) { (void)hipGetLastError(); h->sticky = BAOC_ERR_HIP; return BAOC_ERR_HIP; }
 
     std::vector<baoc_block_stats> stats(N);
     for (uint32_t i = 0; i < N; ++i) {
         RawBlock r;
-        const double* rec = &h->h_rec[(size_t)i * kRecDoubles];
+        const double* rec = (h->host_rec ? h->host_rec : h->h_rec.data()) + (size_t)i * kRecDoubles;
         r.numel = P.rows[i].numel;
         for (int s = 0; s < (int)kNumSums; ++s) r.sums[s] = rec[s];
         r.rho_bar = rec[R_RHO]; r.cos_last = rec[R_COS];
@@ -2065,6 +2113,7 @@ extern "C" int baoc_profile_end(baoc_profiler* h)
 {
     if (!h) return BAOC_ERR_INVALID;
     if (h->static_device >= 0) g_scratch_busy[h->static_device] = false;
+    if (h->host_rec) pool_give(h->host_rec, h->host_bytes);
     delete h;
     return BAOC_OK;
 }
