@@ -253,8 +253,13 @@ __device__ __forceinline__ bool arrive_last(uint32_t* counter, uint32_t n)
 // a step's sums into the block's record
 // ---------------------------------------------------------------------------
 
-// Thread s < 16 of the workgroup holds sum s of the block.
-__device__ __forceinline__ void fold_step(double total, double* rec, double beta_rho, double eps)
+// What fold_step needs of the record, asked for by every thread before the sums: five loads one after another at the end of a launch
+// are what a small step then waits for.
+__device__ __forceinline__ double fold_state(const double* rec) { return rec[R_SPP + (threadIdx.x & 7u)]; }
+static_assert(R_RHO == R_SPP + 1 && R_NCOS == R_SPP + 3 && R_STEPS == R_SPP + 4 && R_SPP + 8 <= kRecDoubles, "lanes of fold_state");
+
+// Thread s < 16 of the workgroup holds sum s of the block; `state` is fold_state's.
+__device__ __forceinline__ void fold_step(double total, double state, double* rec, double beta_rho, double eps)
 {
     const uint32_t tid = threadIdx.x;
     if (tid < kNumSums) rec[tid] = total;
@@ -264,15 +269,15 @@ __device__ __forceinline__ void fold_step(double total, double* rec, double beta
     static_assert(S_GG == 0 && S_GP == 1, "lane 0 holds |g|^2 and takes <g, g'> from lane 1");
     if (tid < 64) {
         const double S_gp = __shfl_down(total, 1);
+        const double spp = __shfl(state, 0), rho = __shfl(state, 1), cosines = __shfl(state, 3), steps = __shfl(state, 4);
         if (tid == 0) {
             // The step index lives in the block's record, not in a launch argument: a captured launch of a
             // steady-state step can be replayed for later steps.
-            const uint32_t step = (uint32_t)rec[R_STEPS] + 1u;
+            const uint32_t step = (uint32_t)steps + 1u;
             if (step >= 2) {
-                double c = S_gp / (sqrt(total) * sqrt(rec[R_SPP]) + eps);
+                double c = S_gp / (sqrt(total) * sqrt(spp) + eps);
                 if (c != c) c = 0.0;
-                const double cosines = rec[R_NCOS];
-                rec[R_RHO] = (cosines == 0.0) ? c : beta_rho * rec[R_RHO] + (1.0 - beta_rho) * c;
+                rec[R_RHO] = (cosines == 0.0) ? c : beta_rho * rho + (1.0 - beta_rho) * c;
                 rec[R_COS] = c;
                 rec[R_NCOS] = cosines + 1.0;
             }
@@ -306,6 +311,14 @@ __global__ __launch_bounds__(64 * NW) void k_step(
     const uint32_t chunk = blockIdx.x / slices, slice = blockIdx.x - chunk * slices;
     const Chunk ck = chunks[chunk];
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    uint32_t fold_rows = 0, fold_first = 0;
+    double* fold_rec = nullptr;
+    double fold_before = 0.0;
+    if (FOLD) {
+        fold_rows = fold.rows[ck.block].n_prows; fold_first = fold.rows[ck.block].first_prow;
+        fold_rec = fold.rec_all + (uint64_t)ck.block * kRecDoubles;
+        fold_before = fold_state(fold_rec);
+    }
     // this workgroup's groups of the chunk: [g_begin, ngroups)
     const uint32_t g_begin = slice * slice_groups;
     const uint32_t ngroups = min((ck.count + (kQB - 1)) / kQB, g_begin + slice_groups);
@@ -452,29 +465,32 @@ __global__ __launch_bounds__(64 * NW) void k_step(
     __shared__ float red[NW * 4 * kNumSums];              // [wavefront * 4 + row][sum]
     red[threadIdx.x] = acc[0];
     __syncthreads();
+    float s = 0.f;
     if (threadIdx.x < kNumSums) {
-        float s = 0.f;
 #pragma unroll
         for (int q = 0; q < NW * 4; ++q) s += red[q * kNumSums + threadIdx.x];
         float* out = partials + (uint64_t)blockIdx.x * kNumSums + threadIdx.x;
-        if (FOLD) st_device(out, s); else *out = s;
+        if (!FOLD) *out = s;
+        else if (fold_rows > 1) st_device(out, s);
     }
     if (FOLD) {
-        const uint32_t n = fold.rows[ck.block].n_prows;
-        if (!arrive_last(fold.arrived + ck.block * kArriveStride, n)) return;
-        __shared__ double sh[NW * 4][kNumSums];
-        const float* base = partials + (uint64_t)fold.rows[ck.block].first_prow * kNumSums;
-        double t = 0.0;
+        double total = (double)s;
+        if (fold_rows > 1) {
+            if (!arrive_last(fold.arrived + ck.block * kArriveStride, fold_rows)) return;
+            __shared__ double sh[NW * 4][kNumSums];
+            const float* base = partials + (uint64_t)fold_first * kNumSums;
+            double t = 0.0;
 #pragma unroll 8
-        for (uint32_t r = threadIdx.x / kNumSums; r < n; r += NW * 4) t += (double)ld_device(base + (uint64_t)r * kNumSums + threadIdx.x % kNumSums);
-        sh[threadIdx.x / kNumSums][threadIdx.x % kNumSums] = t;
-        __syncthreads();
-        double total = 0.0;
-        if (threadIdx.x < kNumSums) {
+            for (uint32_t r = threadIdx.x / kNumSums; r < fold_rows; r += NW * 4) t += (double)ld_device(base + (uint64_t)r * kNumSums + threadIdx.x % kNumSums);
+            sh[threadIdx.x / kNumSums][threadIdx.x % kNumSums] = t;
+            __syncthreads();
+            total = 0.0;
+            if (threadIdx.x < kNumSums) {
 #pragma unroll
-            for (int q = 0; q < NW * 4; ++q) total += sh[q][threadIdx.x];
+                for (int q = 0; q < NW * 4; ++q) total += sh[q][threadIdx.x];
+            }
         }
-        fold_step(total, fold.rec_all + (uint64_t)ck.block * kRecDoubles, fold.beta_rho, fold.eps);
+        fold_step(total, fold_before, fold_rec, fold.beta_rho, fold.eps);
     }
 }
 
@@ -544,6 +560,7 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
     const uint32_t tid = threadIdx.x, n_prows = rows[blockIdx.x].n_prows;
     const float* base = partials + (uint64_t)rows[blockIdx.x].first_prow * kNumSums;
     double* rec = rec_all + (uint64_t)blockIdx.x * kRecDoubles;
+    const double before = fold_state(rec);
     double total = 0.0;
     if (n_prows <= kDirectRows) {
         total = sum_rows(base, n_prows, sh);
@@ -560,7 +577,7 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
             for (int q = 0; q < 16; ++q) total += sh[q][tid];
         }
     }
-    fold_step(total, rec, beta_rho, eps);
+    fold_step(total, before, rec, beta_rho, eps);
 }
 
 // ---------------------------------------------------------------------------
