@@ -66,8 +66,9 @@ typedef struct {
     uint32_t quant_block;  /* coordinates per 8-bit absmax group; only 256 is built     */
     uint32_t grad_dtype;   /* BAOC_GRAD_F32 | BAOC_GRAD_BF16 (states are always fp32)   */
     /* Launch shape of the per-step kernel; 0 = the default measured best for the gradient type
-     * (fp32 layouts of fewer than 2^25 coordinates: 4 wavefronts x 1 group, 7 resident, of fewer than
-     * 2^26: 2 x 2 groups, 6 resident; bf16 layouts of fewer than 2^26: 4 resident).
+     * and the size (fp32 layouts of fewer than 2^25 coordinates: 4 wavefronts x 1 group, 7 resident, of
+     * fewer than 2^26: 2 x 2 groups, 6 resident, larger ones whose blocks are mostly matrices: 1 x 1 group,
+     * 16 resident; bf16 layouts of fewer than 2^26: 4 resident).
      * None of the five changes any result bit except through the order of the partial sums. */
     uint32_t chunk_groups;        /* quantisation groups per chunk, the unit of the step's tables
                                    * (default 8 for bf16 gradients, 4 for fp32)                       */

@@ -540,21 +540,21 @@ __device__ __forceinline__ double sum_rows(const float* __restrict__ partials, u
     return total;
 }
 
-// A block's rows are cut into n_prows / kPartRows parts, the last one with the remainder (so no part has fewer than
+// A block's rows are cut into n_prows / part_rows parts (part_rows is kPartRows, or twice as much where there are twice as many rows), the last one with the remainder (so no part has fewer than
 // two rows).  The part's sums take the place of its first two rows, which nobody else reads.
-__global__ __launch_bounds__(256) void k_reduce_parts(float* partials, const BlockRow* __restrict__ rows, const Part* __restrict__ parts)
+__global__ __launch_bounds__(256) void k_reduce_parts(float* partials, const BlockRow* __restrict__ rows, const Part* __restrict__ parts, uint32_t part_rows)
 {
     __shared__ double sh[16][kNumSums];
     const Part p = parts[blockIdx.x];
-    const uint32_t first = p.part * kPartRows, left = rows[p.block].n_prows - first;
-    const uint32_t n = left < 2 * kPartRows ? left : kPartRows;
+    const uint32_t first = p.part * part_rows, left = rows[p.block].n_prows - first;
+    const uint32_t n = left < 2 * part_rows ? left : part_rows;
     float* mine = partials + (uint64_t)(rows[p.block].first_prow + first) * kNumSums;
     const double total = sum_rows(mine, n, sh);
     if (threadIdx.x < kNumSums) reinterpret_cast<double*>(mine)[threadIdx.x] = total;
 }
 
 __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partials, const BlockRow* __restrict__ rows,
-                                                double* __restrict__ rec_all, double beta_rho, double eps)
+                                                double* __restrict__ rec_all, double beta_rho, double eps, uint32_t part_rows)
 {
     __shared__ double sh[16][kNumSums];
     const uint32_t tid = threadIdx.x, n_prows = rows[blockIdx.x].n_prows;
@@ -562,14 +562,14 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
     double* rec = rec_all + (uint64_t)blockIdx.x * kRecDoubles;
     const double before = fold_state(rec);
     double total = 0.0;
-    if (n_prows <= kDirectRows) {
+    if (n_prows <= part_rows * (kDirectRows / kPartRows)) {
         total = sum_rows(base, n_prows, sh);
     } else {
-        const uint32_t s = tid & 15u, g = tid >> 4, n_parts = n_prows / kPartRows;
+        const uint32_t s = tid & 15u, g = tid >> 4, n_parts = n_prows / part_rows;
         double t = 0.0;
 #pragma unroll 4
         for (uint32_t q = g; q < n_parts; q += 16)
-            t += reinterpret_cast<const double*>(base + (uint64_t)q * kPartRows * kNumSums)[s];
+            t += reinterpret_cast<const double*>(base + (uint64_t)q * part_rows * kNumSums)[s];
         sh[g][s] = t;
         __syncthreads();
         if (tid < kNumSums) {
@@ -1585,6 +1585,7 @@ struct Plan {
     uint64_t n_chunks = 0;
     uint32_t gpw = 1, nw = 4, slices = 1, slice_groups = 4, resident = 8;   // launch shape of the step kernel
     uint64_t n_prows = 0;         // partial rows of the step kernel = n_chunks * slices
+    uint32_t part_rows = kPartRows;
     bool fold_in_step = false;    // the step kernel folds its own partial rows
     std::vector<BlockRow> rows;
     std::vector<TileRow> tiles;   // how finalize walks each block
@@ -1593,7 +1594,7 @@ struct Plan {
     std::vector<Part> parts;      // of blocks of more than kDirectRows partial rows
     std::vector<uint32_t> multi;  // blocks of several tasks
     uint64_t padded = 0;          // coordinates in m / v / g_prev
-    uint64_t off_m = 0, off_v = 0, off_gp = 0, off_partials = 0, off_chunks = 0;
+    uint64_t off_m = 0, off_v = 0, off_gp = 0, off_partials = 0, off_step_rows = 0, off_chunks = 0;   // the step's rows stand at off_step_rows
     uint64_t off_rows = 0, off_tiles = 0, off_parts = 0, off_multi = 0, off_task_block = 0, off_fin_block = 0;   // the first four are uploaded in one piece
     uint64_t off_rec = 0, off_hist = 0, off_arrived = 0, off_selp = 0;                            // cleared up to off_selp
     uint64_t off_selr = 0, off_rvec = 0, off_cvec = 0, off_residpart = 0, off_candcount = 0,
@@ -1871,6 +1872,17 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     // the row and column partial sums of the first pass are folded before the second writes the candidate lists in their place
     P.off_cand = o; P.off_rowpart = o; P.off_colpart = align_up(o + n_rowpart * 4, 256);
     P.total = std::max(align_up(o + n_cand * 4, 256), align_up(P.off_colpart + n_colpart * 4, 256));
+    // Large fp32 layouts: single-wavefront workgroups of one group, 16 resident, write twice the partial rows.  They stand where finalize
+    // has its lists, if these leave room (the matrix blocks' lists take half a byte a coordinate, the rows a quarter), so that the
+    // workspace stays as it is (in one process, two groups and 10 resident against this: 90 M 414 -> 399 us a step, 124 M 546 -> 543,
+    // 1.3 G 5752 -> 5617; 66 M, two wavefronts x two groups, 314).
+    P.off_step_rows = P.off_partials; P.part_rows = kPartRows;
+    const bool own_shape = prm->chunk_groups || prm->chunk_slices || prm->groups_per_wave || prm->waves_per_workgroup || prm->resident_workgroups;
+    if (&ds == &kDefaultShape[BAOC_GRAD_F32] && !own_shape && 2 * P.n_prows <= 0x7fffffffull && 2 * P.n_prows * kNumSums * 4 <= P.total - P.off_cand) {
+        P.gpw = 1; P.slices *= 2; P.slice_groups = 1; P.resident = 16; P.part_rows = 2 * kPartRows;
+        P.n_prows *= 2; P.off_step_rows = P.off_cand;
+        for (BlockRow& r : P.rows) { r.first_prow *= 2; r.n_prows *= 2; }
+    }
     return BAOC_OK;
 }
 
@@ -1990,7 +2002,7 @@ extern "C" int baoc_profile_step(baoc_profiler* h, const void* d_grad_flat, uint
     float* m = reinterpret_cast<float*>(h->ws + P.off_m);
     float* v = reinterpret_cast<float*>(h->ws + P.off_v);
     const Chunk* ch = reinterpret_cast<const Chunk*>(h->ws + P.off_chunks);
-    float* part = reinterpret_cast<float*>(h->ws + P.off_partials);
+    float* part = reinterpret_cast<float*>(h->ws + P.off_step_rows);
     const bool first = h->steps == 0;
     // The first launch is bound by its arithmetic and runs at full residency.  Later launches are bound
     // by DRAM and run with fewer resident workgroups: each is given so much unused LDS that only about
@@ -2012,8 +2024,8 @@ extern "C" int baoc_profile_step(baoc_profiler* h, const void* d_grad_flat, uint
     if (!P.fold_in_step) {
         if (!P.parts.empty())
             hipLaunchKernelGGL(k_reduce_parts, dim3((uint32_t)P.parts.size()), dim3(256), 0, st,
-                               part, rows, reinterpret_cast<const Part*>(h->ws + P.off_parts));
-        hipLaunchKernelGGL(k_reduce, dim3((uint32_t)P.rows.size()), dim3(256), 0, st, part, rows, rec, q.beta_rho, q.eps);
+                               part, rows, reinterpret_cast<const Part*>(h->ws + P.off_parts), P.part_rows);
+        hipLaunchKernelGGL(k_reduce, dim3((uint32_t)P.rows.size()), dim3(256), 0, st, part, rows, rec, q.beta_rho, q.eps, P.part_rows);
     }
     if (hipGetLastError() != hipSuccess) { h->sticky = BAOC_ERR_HIP; return BAOC_ERR_HIP; }
     return BAOC_OK;
