@@ -1638,6 +1638,7 @@ static double* pool_take(uint64_t bytes, uint64_t* got)
             return p;
         }
     if (g_pool_pinned + size > kPoolBytes) return nullptr;
+    try { g_pool_free.reserve(kPoolBytes / 4096); } catch (const std::bad_alloc&) { return nullptr; }   // giving back never allocates
     void* p = nullptr;
     if (hipHostMalloc(&p, size, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess || !p) { (void)hipGetLastError(); return nullptr; }
     g_pool_pinned += size;
