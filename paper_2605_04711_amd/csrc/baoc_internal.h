@@ -20,7 +20,7 @@ constexpr uint32_t kNumSums = 16;        // floats in one partial-sum row
 // 81.7; 25.6 M 115.9, 110.2, 111.8, 120.1; 40 M 185, 182.7, 178.9, 187; 66 M 318.9, 322.8, 314.4, 318.1; 90 M 423, 430, 420, 414.  bf16 with
 // 3 and 4 resident: 17 M 62.6, 61.9, 25.6 M 91.2, 89.2, 66 M 229.3, 227.7, 90 M 317.8, 324.2).
 struct LaunchShape { uint32_t chunk_groups, groups_per_wave, waves_per_workgroup, resident_workgroups; };
-// (make_plan has single-wavefront workgroups of one group for large fp32 layouts where the workspace has room for their rows.)
+// (make_plan has single-wavefront workgroups of one group, 16 resident, for large fp32 layouts where the workspace has room for their rows.)
 constexpr LaunchShape kDefaultShape[2] = {{4, 2, 1, 10}, {8, 2, 4, 3}};
 constexpr LaunchShape kMediumShape[2] = {{4, 2, 2, 6}, {8, 2, 4, 4}};         // below kMediumLayout coordinates
 constexpr LaunchShape kSmallShape[2] = {{4, 1, 4, 7}, {8, 2, 4, 4}};          // below kSmallLayout coordinates

@@ -1695,6 +1695,13 @@ static int check_params(const baoc_profile_params* p)
     return BAOC_OK;
 }
 
+// Groups per chunk where a block's groups are spread evenly over as few chunks of up to `most` groups as hold them.
+static uint64_t even_groups(uint64_t groups, uint32_t most)
+{
+    const uint64_t chunks = (groups + most - 1) / most;
+    return (groups + chunks - 1) / chunks;
+}
+
 static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_params* prm, Plan* out, uint64_t* max_end)
 {
     if (!blocks || n == 0) return BAOC_ERR_INVALID;
@@ -1730,28 +1737,33 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     const uint32_t cg = prm->chunk_groups ? prm->chunk_groups : std::max(ds.chunk_groups, round);
     P.slices = prm->chunk_slices ? std::min(prm->chunk_slices, cg) : std::max(1u, cg / round);   // default: one round per slice
     P.slice_groups = (cg + P.slices - 1) / P.slices;
-    P.n_chunks = 0; P.rows.resize(n); P.parts.clear(); P.multi.clear();
-    uint64_t state = 0;
-    for (uint32_t i = 0; i < n; ++i) {
-        const baoc_block& b = blocks[i];
-        const uint64_t groups = (b.numel + kQB - 1) / kQB;
-        const uint64_t nch = (groups + cg - 1) / cg;
-        const uint64_t per = (groups + nch - 1) / nch;               // balanced, whole groups
-        BlockRow& r = P.rows[i];
-        r.grad_start = b.offset; r.state_start = state; r.numel = b.numel;
-        r.first_chunk = (uint32_t)P.n_chunks;
-        r.n_chunks = (uint32_t)((groups + per - 1) / per);
-        r.groups_per_chunk = (uint32_t)per; r.pad_ = 0;
-        const uint64_t prows = (uint64_t)r.n_chunks * P.slices, first_prow = P.n_chunks * P.slices;
-        if (first_prow + prows > 0x7fffffffull) return BAOC_ERR_UNSUPPORTED;
-        r.first_prow = (uint32_t)first_prow; r.n_prows = (uint32_t)prows;
-        for (uint32_t q = 0; prows > kDirectRows && q < prows / kPartRows; ++q) P.parts.push_back(Part{i, q});
-        P.n_chunks += r.n_chunks;
-        state += groups * kQB;
-        if (P.n_chunks > 0x7fffffffull) return BAOC_ERR_UNSUPPORTED;
-    }
-    P.padded = state;
-    P.n_prows = P.n_chunks * P.slices;
+    // Cuts the blocks into chunks of up to `groups` groups, `slices` workgroups each.
+    auto cut = [&](uint32_t groups_max, uint32_t slices, uint32_t part_rows) {
+        P.n_chunks = 0; P.rows.resize(n); P.parts.clear();
+        uint64_t state = 0;
+        for (uint32_t i = 0; i < n; ++i) {
+            const baoc_block& b = blocks[i];
+            const uint64_t groups = (b.numel + kQB - 1) / kQB, per = even_groups(groups, groups_max);
+            BlockRow& r = P.rows[i];
+            r.grad_start = b.offset; r.state_start = state; r.numel = b.numel;
+            r.first_chunk = (uint32_t)P.n_chunks;
+            r.n_chunks = (uint32_t)((groups + per - 1) / per);
+            r.groups_per_chunk = (uint32_t)per; r.pad_ = 0;
+            const uint64_t prows = (uint64_t)r.n_chunks * slices, first_prow = P.n_chunks * slices;
+            if (first_prow + prows > 0x7fffffffull) return false;
+            r.first_prow = (uint32_t)first_prow; r.n_prows = (uint32_t)prows;
+            for (uint32_t q = 0; prows > part_rows * (kDirectRows / kPartRows) && q < prows / part_rows; ++q) P.parts.push_back(Part{i, q});
+            P.n_chunks += r.n_chunks;
+            state += groups * kQB;
+            if (P.n_chunks > 0x7fffffffull) return false;
+        }
+        P.padded = state;
+        P.n_prows = P.n_chunks * slices;
+        P.slices = slices; P.part_rows = part_rows;
+        return true;
+    };
+    if (!cut(cg, P.slices, kPartRows)) return BAOC_ERR_UNSUPPORTED;
+    P.multi.clear();
     uint32_t most_prows = 0;
     for (const BlockRow& r : P.rows) most_prows = std::max(most_prows, r.n_prows);
     P.fold_in_step = P.n_prows <= kFoldRows && most_prows <= kFoldBlockRows;
@@ -1844,13 +1856,33 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
         P.n_tasks += tasks;
         if (P.n_tasks > 0x7fffffffull || P.n_fin > 0x7fffffffull) return BAOC_ERR_UNSUPPORTED;
     }
+    // the row and column partial sums of the first pass are folded before the second writes the candidate lists in their place
+    const uint64_t list_bytes = std::max(align_up(n_cand * 4, 256), align_up(n_rowpart * 4, 256) + align_up(n_colpart * 4, 256));
+    // Large fp32 layouts: single-wavefront workgroups of one group, 16 resident.  They write twice the partial rows, which stand where
+    // finalize has its lists if these leave room (the matrix blocks' lists take half a byte a coordinate, the rows a quarter), so that
+    // the workspace stays as it is.  Every workgroup reads its chunk's table entry, so chunks have eight groups: with four the step
+    // moves 1.022 of its algorithmic bytes, with eight 1.016.  Blocks of a few groups leave workgroups of such a chunk without
+    // one; where that would be more than a sixteenth of all, chunks have four groups.
+    // (In one process, us a step: two groups and 10 resident, this shape with chunks of four and of eight groups: 74 M coordinates of odd
+    // shapes 340, 348, 340; 100 M 457, 445, 443; 860 M 3720, 3657, 3650; 1.3 G 5632, 5586, 5578.)
+    const bool own_shape = prm->chunk_groups || prm->chunk_slices || prm->groups_per_wave || prm->waves_per_workgroup || prm->resident_workgroups;
+    uint32_t fine = 0;                                               // groups, and workgroups, of a chunk
+    for (uint32_t g = 8; g >= 4 && !fine && !own_shape && &ds == &kDefaultShape[BAOC_GRAD_F32]; g -= 4) {
+        uint64_t rows = 0, groups = 0;
+        for (const BlockRow& r : P.rows) {
+            const uint64_t all = (r.numel + kQB - 1) / kQB, per = even_groups(all, g);
+            groups += all; rows += (all + per - 1) / per * g;
+        }
+        if (rows <= 0x7fffffffull && rows * kNumSums * 4 <= list_bytes && (g == 4 || rows <= groups + groups / 16)) fine = g;
+    }
+    if (fine) { cut(fine, fine, 2 * kPartRows); P.gpw = P.nw = P.slice_groups = 1; P.resident = 16; }
     const uint64_t gsz = prm->grad_dtype == BAOC_GRAD_F32 ? 4 : 2;
     uint64_t o = 0;
     auto place = [&](uint64_t& off, uint64_t bytes) { off = o; o = align_up(o + bytes, 256); };
     place(P.off_m, P.padded * 4);
     place(P.off_v, P.padded * 4);
     place(P.off_gp, P.padded * gsz);
-    place(P.off_partials, P.n_prows * kNumSums * 4);
+    place(P.off_partials, partial_bytes);
     place(P.off_chunks, P.n_chunks * sizeof(Chunk));
     place(P.off_rows, (uint64_t)n * sizeof(BlockRow));
     place(P.off_tiles, (uint64_t)n * sizeof(TileRow));
@@ -1870,20 +1902,9 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     const uint64_t per_task = task_bytes(P.n_tasks);
     if (sums_fit(P.n_tasks)) P.off_residpart = P.off_partials; else place(P.off_residpart, per_task);
     if (counts_fit(P.n_tasks)) P.off_candcount = P.off_partials + per_task; else if (P.any_matrix) place(P.off_candcount, per_task);
-    // the row and column partial sums of the first pass are folded before the second writes the candidate lists in their place
     P.off_cand = o; P.off_rowpart = o; P.off_colpart = align_up(o + n_rowpart * 4, 256);
-    P.total = std::max(align_up(o + n_cand * 4, 256), align_up(P.off_colpart + n_colpart * 4, 256));
-    // Large fp32 layouts: single-wavefront workgroups of one group, 16 resident, write twice the partial rows.  They stand where finalize
-    // has its lists, if these leave room (the matrix blocks' lists take half a byte a coordinate, the rows a quarter), so that the
-    // workspace stays as it is (in one process, two groups and 10 resident against this: 90 M 414 -> 399 us a step, 124 M 546 -> 543,
-    // 1.3 G 5752 -> 5617; 66 M, two wavefronts x two groups, 314).
-    P.off_step_rows = P.off_partials; P.part_rows = kPartRows;
-    const bool own_shape = prm->chunk_groups || prm->chunk_slices || prm->groups_per_wave || prm->waves_per_workgroup || prm->resident_workgroups;
-    if (&ds == &kDefaultShape[BAOC_GRAD_F32] && !own_shape && 2 * P.n_prows <= 0x7fffffffull && 2 * P.n_prows * kNumSums * 4 <= P.total - P.off_cand) {
-        P.gpw = 1; P.slices *= 2; P.slice_groups = 1; P.resident = 16; P.part_rows = 2 * kPartRows;
-        P.n_prows *= 2; P.off_step_rows = P.off_cand;
-        for (BlockRow& r : P.rows) { r.first_prow *= 2; r.n_prows *= 2; }
-    }
+    P.total = o + list_bytes;
+    P.off_step_rows = fine ? P.off_cand : P.off_partials;
     return BAOC_OK;
 }
 

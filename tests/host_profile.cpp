@@ -1,0 +1,111 @@
+// The host side of the profiler without a GPU: the library's own source, compiled for the host alone, on a HIP runtime that only keeps a
+// record of the calls made to it.  argv[1] names the check; a failed one prints what is wrong and returns 1.
+#include "baoc_profile.hip"
+
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+#include <string>
+
+#define CHECK(cond, ...) do { if (!(cond)) { std::printf("line %d: %s ", __LINE__, #cond); std::printf(__VA_ARGS__); std::printf("\n"); return 1; } } while (0)
+
+// ---------------------------------------------------------------------------
+// the runtime
+// ---------------------------------------------------------------------------
+
+extern "C" {
+void** __hipRegisterFatBinary(const void*) { static void* handle = nullptr; return &handle; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*, void*, int*) {}
+void __hipRegisterVar(void**, void*, char*, const char*, int, size_t, int, int) {}
+hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void*) { *p = scratch; return hipSuccess; }
+hipError_t hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = std::calloc(1, n); return *p ? hipSuccess : hipErrorOutOfMemory; }
+}
+
+// ---------------------------------------------------------------------------
+// layouts
+// ---------------------------------------------------------------------------
+
+static void add(std::vector<baoc_block>& l, uint64_t rows, uint64_t cols, uint32_t times = 1)
+{
+    for (; times; --times) {
+        const uint64_t at = l.empty() ? 0 : l.back().offset + l.back().numel;
+        l.push_back(cols ? baoc_block{at, rows * cols, (uint32_t)rows, (uint32_t)cols} : baoc_block{at, rows, 0, 0});
+    }
+}
+
+static baoc_profile_params params_of(uint32_t dtype)
+{
+    baoc_profile_params p;
+    baoc_profile_params_default(&p);
+    p.grad_dtype = dtype;
+    return p;
+}
+
+// ---------------------------------------------------------------------------
+// the plan of a step
+// ---------------------------------------------------------------------------
+
+// Workgroups of the step and of the reduction cover every group and every row once, and the rows stand inside the workspace.
+static int check_step(const Plan& P, const char* name)
+{
+    uint64_t chunks = 0, rows = 0, part = 0;
+    for (const BlockRow& r : P.rows) {
+        const uint64_t groups = (r.numel + kQB - 1) / kQB;
+        CHECK(r.first_chunk == chunks && r.first_prow == rows && r.n_prows == (uint64_t)r.n_chunks * P.slices, "%s", name);
+        CHECK((uint64_t)r.n_chunks * r.groups_per_chunk >= groups && (uint64_t)(r.n_chunks - 1) * r.groups_per_chunk < groups, "%s", name);
+        CHECK((uint64_t)P.slices * P.slice_groups >= r.groups_per_chunk, "%s", name);
+        for (uint32_t q = 0; part < P.parts.size() && P.parts[part].block == (uint32_t)(&r - P.rows.data()); ++q, ++part)
+            CHECK(P.parts[part].part == q, "%s", name);
+        chunks += r.n_chunks; rows += r.n_prows;
+    }
+    CHECK(chunks == P.n_chunks && rows == P.n_prows && part == P.parts.size(), "%s", name);
+    CHECK(P.off_step_rows == P.off_partials ? P.off_step_rows + rows * kNumSums * 4 <= P.off_chunks : P.off_step_rows == P.off_cand, "%s", name);
+    CHECK(P.off_step_rows + rows * kNumSums * 4 <= P.total && P.off_chunks + chunks * sizeof(Chunk) <= P.off_rows, "%s", name);
+    return 0;
+}
+
+// Large fp32 layouts: workgroups of one wavefront and one group, chunks of eight groups unless these would leave many workgroups
+// without one, rows in the region of the lists; elsewhere, and next to a caller's own values, the other shapes.
+static int check_plans()
+{
+    struct Want { const char* name; uint32_t dtype, gpw, nw, slices, resident; bool in_lists; };
+    auto run = [&](const std::vector<baoc_block>& l, baoc_profile_params p, Want w) {
+        Plan P;
+        CHECK(make_plan(l.data(), (uint32_t)l.size(), &p, &P, nullptr) == BAOC_OK, "%s", w.name);
+        CHECK(P.gpw == w.gpw && P.nw == w.nw && P.slices == w.slices && P.resident == w.resident, "%s: %u %u %u %u", w.name, P.gpw, P.nw, P.slices, P.resident);
+        CHECK((P.off_step_rows == P.off_cand) == w.in_lists, "%s", w.name);
+        return check_step(P, w.name);
+    };
+    std::vector<baoc_block> matrices, vectors, tiny, below, edges;
+    add(matrices, 4096, 2048, 9); add(matrices, 2049, 4099); add(matrices, 5, 0, 7);
+    add(vectors, (1u << 26) + 5, 0);
+    add(tiny, 30, 40, 60000);
+    add(below, 4096, 2048, 7);
+    for (uint64_t g : {1u, 7u, 8u, 9u, 3064u, 3071u, 3072u, 3073u, 3080u, 4095u, 4097u, 5119u, 6144u, 6145u}) { add(edges, g, 256); add(edges, 1, 0); }
+    add(edges, 4096, 8192, 2);
+    const baoc_profile_params f32 = params_of(BAOC_GRAD_F32), bf16 = params_of(BAOC_GRAD_BF16);
+    baoc_profile_params own = f32;
+    own.resident_workgroups = 12;
+    return run(matrices, f32, {"matrices", 0, 1, 1, 8, 16, true}) || run(edges, f32, {"edges", 0, 1, 1, 8, 16, true}) ||
+           run(vectors, f32, {"vectors", 0, 2, 1, 2, 10, false}) || run(tiny, f32, {"tiny", 0, 1, 1, 4, 16, true}) ||
+           run(below, f32, {"below", 0, 2, 2, 1, 6, false}) || run(matrices, own, {"own", 0, 2, 1, 2, 12, false}) ||
+           run(matrices, bf16, {"bf16", 1, 2, 4, 1, 3, false});
+}
+
+int main(int argc, char** argv)
+{
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "plans") return check_plans();
+    std::printf("no check named '%s'\n", what.c_str());
+    return 2;
+}

@@ -1,0 +1,34 @@
+"""Host side of the profiler (plans, launches, pinned memory, index arithmetic) on the CPU: tests/host_profile.cpp is the library's own
+source compiled for the host, on a HIP runtime that only records what is called."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2605_04711_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def host_profile(tmp_path_factory):
+    """-> function that runs one check of tests/host_profile.cpp."""
+    if shutil.which("hipcc") is None or shutil.which("g++") is None:
+        pytest.skip("no compiler")
+    out = tmp_path_factory.mktemp("host_profile")
+    obj, exe = str(out / "host_profile.o"), str(out / "host_profile")
+    inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
+    subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-std=c++17", "-O1", "-g", *inc, "-c", "-o", obj,
+                    os.path.join(ROOT, "tests", "host_profile.cpp")], check=True, capture_output=True, timeout=300)
+    # no device code: the symbol that would hold it stays undefined
+    subprocess.run(["g++", "-std=c++17", "-O1", "-no-pie", "-Wl,--unresolved-symbols=ignore-all", *inc, "-o", exe, obj,
+                    os.path.join(CSRC, "baoc_risk.cpp"), "-lpthread"], check=True, capture_output=True, timeout=300)
+
+    def run(check):
+        r = subprocess.run([exe, check], capture_output=True, text=True, timeout=300)
+        assert r.returncode == 0, f"{r.returncode}\n{r.stdout}{r.stderr}"
+    return run
+
+
+def test_step_plans_of_large_layouts(host_profile):
+    host_profile("plans")
