@@ -498,13 +498,15 @@ __global__ __launch_bounds__(64 * NW) void k_step(
 // (k_reduce_parts, one workgroup each); k_reduce adds a block's rows, or the sums of its parts, and folds the
 // step into the block's record.
 // Bound by latency: a chain of descriptor load, row loads and reduction, and for the largest layouts by the
-// rows themselves (64 B for every 512 coordinates of an fp32 layout).  A lane reads 16 bytes of a row, a
+// rows themselves (64 B for every 256 coordinates of a large fp32 layout).  A lane reads 16 bytes of a row, a
 // wavefront 1 KB at a time, a workgroup 32 KB per round; the 64 row slots of a sum meet in two exchange
-// levels and one trip through LDS.  Measured (16 LDS trees of eight barriers and parts of 4,096 rows before):
-// 32,768 coordinates 14.3 -> 3.0 us, 124 M fp32 38.8 -> 9.9 us, 1.3 G fp32 44 -> 29.7 us.  One launch in which the
-// last part of a block to arrive folds it was slower where there are many parts (1.3 G: 106 us): its
+// levels and one trip through LDS.  Measured (16 LDS trees of eight barriers and parts of 4,096 rows before): 32,768
+// coordinates 14.3 -> 3.0 us.  Both launches: 124 M fp32, 486,000 rows, 17 us; 860 M 50 us; 1.3 G 68 us, where the rows, 329 MB, are
+// more than the memory-side cache holds (half as many rows took 30).  One launch in which the
+// last part of a block to arrive folds it was slower where there are many parts (1.3 G with half the rows: 106 us): its
 // release writes back the whole L2 of an XCD for every part.
-// kDirectRows: the second launch costs 4.7 us, about what six rounds take.
+// kDirectRows: the second launch costs 4.7 us, about what six rounds take.  (With 6,144 rows and parts of 2,048 k_reduce of 860 M in 686 blocks
+// takes 12.6 us instead of 7.5, a step of 74 M coordinates 340 instead of 333.)
 constexpr uint32_t kPartRows = 1024, kDirectRows = 3072;
 
 struct alignas(8) Part { uint32_t block, part; };
@@ -540,21 +542,21 @@ __device__ __forceinline__ double sum_rows(const float* __restrict__ partials, u
     return total;
 }
 
-// A block's rows are cut into n_prows / part_rows parts (part_rows is kPartRows, or twice as much where there are twice as many rows), the last one with the remainder (so no part has fewer than
+// A block's rows are cut into n_prows / kPartRows parts, the last one with the remainder (so no part has fewer than
 // two rows).  The part's sums take the place of its first two rows, which nobody else reads.
-__global__ __launch_bounds__(256) void k_reduce_parts(float* partials, const BlockRow* __restrict__ rows, const Part* __restrict__ parts, uint32_t part_rows)
+__global__ __launch_bounds__(256) void k_reduce_parts(float* partials, const BlockRow* __restrict__ rows, const Part* __restrict__ parts)
 {
     __shared__ double sh[16][kNumSums];
     const Part p = parts[blockIdx.x];
-    const uint32_t first = p.part * part_rows, left = rows[p.block].n_prows - first;
-    const uint32_t n = left < 2 * part_rows ? left : part_rows;
+    const uint32_t first = p.part * kPartRows, left = rows[p.block].n_prows - first;
+    const uint32_t n = left < 2 * kPartRows ? left : kPartRows;
     float* mine = partials + (uint64_t)(rows[p.block].first_prow + first) * kNumSums;
     const double total = sum_rows(mine, n, sh);
     if (threadIdx.x < kNumSums) reinterpret_cast<double*>(mine)[threadIdx.x] = total;
 }
 
 __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partials, const BlockRow* __restrict__ rows,
-                                                double* __restrict__ rec_all, double beta_rho, double eps, uint32_t part_rows)
+                                                double* __restrict__ rec_all, double beta_rho, double eps)
 {
     __shared__ double sh[16][kNumSums];
     const uint32_t tid = threadIdx.x, n_prows = rows[blockIdx.x].n_prows;
@@ -562,14 +564,14 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
     double* rec = rec_all + (uint64_t)blockIdx.x * kRecDoubles;
     const double before = fold_state(rec);
     double total = 0.0;
-    if (n_prows <= part_rows * (kDirectRows / kPartRows)) {
+    if (n_prows <= kDirectRows) {
         total = sum_rows(base, n_prows, sh);
     } else {
-        const uint32_t s = tid & 15u, g = tid >> 4, n_parts = n_prows / part_rows;
+        const uint32_t s = tid & 15u, g = tid >> 4, n_parts = n_prows / kPartRows;
         double t = 0.0;
 #pragma unroll 4
         for (uint32_t q = g; q < n_parts; q += 16)
-            t += reinterpret_cast<const double*>(base + (uint64_t)q * part_rows * kNumSums)[s];
+            t += reinterpret_cast<const double*>(base + (uint64_t)q * kPartRows * kNumSums)[s];
         sh[g][s] = t;
         __syncthreads();
         if (tid < kNumSums) {
@@ -1585,7 +1587,6 @@ struct Plan {
     uint64_t n_chunks = 0;
     uint32_t gpw = 1, nw = 4, slices = 1, slice_groups = 4, resident = 8;   // launch shape of the step kernel
     uint64_t n_prows = 0;         // partial rows of the step kernel = n_chunks * slices
-    uint32_t part_rows = kPartRows;
     bool fold_in_step = false;    // the step kernel folds its own partial rows
     std::vector<BlockRow> rows;
     std::vector<TileRow> tiles;   // how finalize walks each block
@@ -1738,7 +1739,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     P.slices = prm->chunk_slices ? std::min(prm->chunk_slices, cg) : std::max(1u, cg / round);   // default: one round per slice
     P.slice_groups = (cg + P.slices - 1) / P.slices;
     // Cuts the blocks into chunks of up to `groups` groups, `slices` workgroups each.
-    auto cut = [&](uint32_t groups_max, uint32_t slices, uint32_t part_rows) {
+    auto cut = [&](uint32_t groups_max, uint32_t slices) {
         P.n_chunks = 0; P.rows.resize(n); P.parts.clear();
         uint64_t state = 0;
         for (uint32_t i = 0; i < n; ++i) {
@@ -1752,17 +1753,17 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
             const uint64_t prows = (uint64_t)r.n_chunks * slices, first_prow = P.n_chunks * slices;
             if (first_prow + prows > 0x7fffffffull) return false;
             r.first_prow = (uint32_t)first_prow; r.n_prows = (uint32_t)prows;
-            for (uint32_t q = 0; prows > part_rows * (kDirectRows / kPartRows) && q < prows / part_rows; ++q) P.parts.push_back(Part{i, q});
+            for (uint32_t q = 0; prows > kDirectRows && q < prows / kPartRows; ++q) P.parts.push_back(Part{i, q});
             P.n_chunks += r.n_chunks;
             state += groups * kQB;
             if (P.n_chunks > 0x7fffffffull) return false;
         }
         P.padded = state;
         P.n_prows = P.n_chunks * slices;
-        P.slices = slices; P.part_rows = part_rows;
+        P.slices = slices;
         return true;
     };
-    if (!cut(cg, P.slices, kPartRows)) return BAOC_ERR_UNSUPPORTED;
+    if (!cut(cg, P.slices)) return BAOC_ERR_UNSUPPORTED;
     P.multi.clear();
     uint32_t most_prows = 0;
     for (const BlockRow& r : P.rows) most_prows = std::max(most_prows, r.n_prows);
@@ -1863,8 +1864,8 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     // the workspace stays as it is.  Every workgroup reads its chunk's table entry, so chunks have eight groups: with four the step
     // moves 1.022 of its algorithmic bytes, with eight 1.016.  Blocks of a few groups leave workgroups of such a chunk without
     // one; where that would be more than a sixteenth of all, chunks have four groups.
-    // (In one process, us a step: two groups and 10 resident, this shape with chunks of four and of eight groups: 74 M coordinates of odd
-    // shapes 340, 348, 340; 100 M 457, 445, 443; 860 M 3720, 3657, 3650; 1.3 G 5632, 5586, 5578.)
+    // (In one process, us a step: two groups and 10 resident against this: 74 M coordinates of odd shapes 340 and 333, 100 M 457 and
+    // 436, 124 M 544 and 540, 860 M 3720 and 3646, 1.3 G 5632 and 5579.)
     const bool own_shape = prm->chunk_groups || prm->chunk_slices || prm->groups_per_wave || prm->waves_per_workgroup || prm->resident_workgroups;
     uint32_t fine = 0;                                               // groups, and workgroups, of a chunk
     for (uint32_t g = 8; g >= 4 && !fine && !own_shape && &ds == &kDefaultShape[BAOC_GRAD_F32]; g -= 4) {
@@ -1875,7 +1876,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
         }
         if (rows <= 0x7fffffffull && rows * kNumSums * 4 <= list_bytes && (g == 4 || rows <= groups + groups / 16)) fine = g;
     }
-    if (fine) { cut(fine, fine, 2 * kPartRows); P.gpw = P.nw = P.slice_groups = 1; P.resident = 16; }
+    if (fine) { cut(fine, fine); P.gpw = P.nw = P.slice_groups = 1; P.resident = 16; }
     const uint64_t gsz = prm->grad_dtype == BAOC_GRAD_F32 ? 4 : 2;
     uint64_t o = 0;
     auto place = [&](uint64_t& off, uint64_t bytes) { off = o; o = align_up(o + bytes, 256); };
@@ -2046,8 +2047,8 @@ extern "C" int baoc_profile_step(baoc_profiler* h, const void* d_grad_flat, uint
     if (!P.fold_in_step) {
         if (!P.parts.empty())
             hipLaunchKernelGGL(k_reduce_parts, dim3((uint32_t)P.parts.size()), dim3(256), 0, st,
-                               part, rows, reinterpret_cast<const Part*>(h->ws + P.off_parts), P.part_rows);
-        hipLaunchKernelGGL(k_reduce, dim3((uint32_t)P.rows.size()), dim3(256), 0, st, part, rows, rec, q.beta_rho, q.eps, P.part_rows);
+                               part, rows, reinterpret_cast<const Part*>(h->ws + P.off_parts));
+        hipLaunchKernelGGL(k_reduce, dim3((uint32_t)P.rows.size()), dim3(256), 0, st, part, rows, rec, q.beta_rho, q.eps);
     }
     if (hipGetLastError() != hipSuccess) { h->sticky = BAOC_ERR_HIP; return BAOC_ERR_HIP; }
     return BAOC_OK;
