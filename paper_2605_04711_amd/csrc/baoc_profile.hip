@@ -1613,6 +1613,7 @@ struct baoc_profiler {
     int sticky = BAOC_OK;
     double* host_rec = nullptr;   // where finalize leaves the records: memory of the pool below, or h_rec
     uint64_t host_bytes = 0;      // its size in the pool
+    bool host_lost = false;       // waiting for a finalize failed: a kernel may still write to host_rec
     std::vector<double> h_rec;
 };
 
@@ -2119,8 +2120,10 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
 
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && !h->host_rec) e = hipMemcpyAsync(h->h_rec.data(), rec, h->h_rec.size() * 8, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) { (void)hipGetLastError(); h->sticky = BAOC_ERR_HIP; return BAOC_ERR_HIP; }
+    // after an error too: the kernels are in flight, and the last one writes to host memory
+    const hipError_t waited = hipStreamSynchronize(st);
+    if (waited != hipSuccess) h->host_lost = true;
+    if (e != hipSuccess || waited != hipSuccess) { (void)hipGetLastError(); h->sticky = BAOC_ERR_HIP; return BAOC_ERR_HIP; }
 
     std::vector<baoc_block_stats> stats(N);
     for (uint32_t i = 0; i < N; ++i) {
@@ -2165,7 +2168,7 @@ extern "C" int baoc_profile_end(baoc_profiler* h)
 {
     if (!h) return BAOC_ERR_INVALID;
     if (h->static_device >= 0) g_scratch_busy[h->static_device] = false;
-    if (h->host_rec) pool_give(h->host_rec, h->host_bytes);
+    if (h->host_rec && !h->host_lost) pool_give(h->host_rec, h->host_bytes);   // a lost buffer stays counted as pinned
     delete h;
     return BAOC_OK;
 }

@@ -13,6 +13,10 @@
 // the runtime
 // ---------------------------------------------------------------------------
 
+static std::string g_calls;                               // L launch, S wait for a stream, P pinned allocation
+static hipError_t g_last_error = hipSuccess, g_wait = hipSuccess;   // what the next hipGetLastError and every wait return
+static void* g_pinned = nullptr;                          // the last pinned allocation
+
 extern "C" {
 void** __hipRegisterFatBinary(const void*) { static void* handle = nullptr; return &handle; }
 void __hipUnregisterFatBinary(void**) {}
@@ -20,15 +24,20 @@ void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, vo
 void __hipRegisterVar(void**, void*, char*, const char*, int, size_t, int, int) {}
 hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { return hipSuccess; }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) { g_calls += 'L'; return hipSuccess; }
+hipError_t hipGetLastError() { const hipError_t e = g_last_error; g_last_error = hipSuccess; return e; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { g_calls += 'S'; return g_wait; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** p, const void*) { *p = scratch; return hipSuccess; }
 hipError_t hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipSuccess; }
 hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = std::calloc(1, n); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned)
+{
+    g_calls += 'P';
+    *p = g_pinned = std::calloc(1, n);
+    return *p ? hipSuccess : hipErrorOutOfMemory;
+}
 }
 
 // ---------------------------------------------------------------------------
@@ -104,10 +113,59 @@ static int check_plans()
            run(matrices, bf16, {"bf16", 1, 2, 4, 1, 3, false});
 }
 
+// ---------------------------------------------------------------------------
+// pinned memory
+// ---------------------------------------------------------------------------
+
+static baoc_profiler* stepped(const std::vector<baoc_block>& l, void* workspace, uint64_t bytes)
+{
+    const baoc_profile_params p = params_of(BAOC_GRAD_F32);
+    baoc_profiler* h = nullptr;
+    if (baoc_profile_begin(l.data(), (uint32_t)l.size(), &p, workspace, bytes, &h) != BAOC_OK) return nullptr;
+    return baoc_profile_step(h, workspace, l.back().offset + l.back().numel, nullptr) == BAOC_OK ? h : nullptr;
+}
+
+// The last kernel of finalize writes the records to pinned memory.  After an error it may still be in flight: the call waits before it
+// returns, and where waiting fails the buffer goes to no other handle.
+static int check_finalize_error()
+{
+    std::vector<baoc_block> l;
+    add(l, 64, 64, 8);
+    const baoc_profile_params p = params_of(BAOC_GRAD_F32);
+    uint64_t bytes = 0;
+    CHECK(baoc_profile_workspace_bytes(l.data(), (uint32_t)l.size(), &p, &bytes) == BAOC_OK, " ");
+    void* workspace = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
+    std::vector<baoc_block_stats> stats(l.size());
+    auto finalize = [&](baoc_profiler* h) { return baoc_profile_finalize(h, nullptr, 0, nullptr, stats.data(), nullptr, nullptr); };
+
+    baoc_profiler* h = stepped(l, workspace, bytes);
+    CHECK(h && finalize(h) == BAOC_OK, " ");
+    const void* first = g_pinned;
+    CHECK(first && baoc_profile_end(h) == BAOC_OK, " ");
+
+    h = stepped(l, workspace, bytes);                         // takes the buffer that was given back
+    CHECK(h && g_pinned == first, " ");
+    g_calls.clear();
+    g_last_error = hipErrorInvalidValue;                      // of a launch, or the caller's own
+    CHECK(finalize(h) == BAOC_ERR_HIP, " ");
+    CHECK(g_calls.rfind('S') != std::string::npos && g_calls.rfind('S') > g_calls.rfind('L'), "%s", g_calls.c_str());
+    CHECK(finalize(h) == BAOC_ERR_HIP && baoc_profile_end(h) == BAOC_OK, " ");
+
+    h = stepped(l, workspace, bytes);                         // waited for: the buffer is free
+    CHECK(h && g_pinned == first, " ");
+    g_wait = hipErrorLaunchFailure;
+    CHECK(finalize(h) == BAOC_ERR_HIP && baoc_profile_end(h) == BAOC_OK, " ");
+    g_wait = hipSuccess;
+    h = stepped(l, workspace, bytes);
+    CHECK(h && g_pinned != first && finalize(h) == BAOC_OK && baoc_profile_end(h) == BAOC_OK, " ");
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "plans") return check_plans();
+    if (what == "finalize_error") return check_finalize_error();
     std::printf("no check named '%s'\n", what.c_str());
     return 2;
 }

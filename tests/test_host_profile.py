@@ -32,3 +32,7 @@ def host_profile(tmp_path_factory):
 
 def test_step_plans_of_large_layouts(host_profile):
     host_profile("plans")
+
+
+def test_finalize_waits_before_it_reports_an_error(host_profile):
+    host_profile("finalize_error")
