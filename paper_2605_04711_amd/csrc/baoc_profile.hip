@@ -1621,26 +1621,29 @@ struct baoc_profiler {
 // kernels have ended (finalize of 25.6 M coordinates, 41 KB: 135 us with the copy, 125 so; of 32,768 49.6 and 40.5).  Pinning takes longer than that, so buffers
 // are kept for the next handle: at most kPoolBytes in all are ever pinned, in powers of two up to kPoolBuffer; a handle that finds none, and
 // a static one, which allocates nothing, has the copy.
-constexpr uint64_t kPoolBytes = 4ull << 20, kPoolBuffer = 1ull << 20;
+constexpr uint64_t kPoolBytes = 4ull << 20, kPoolBuffer = 1ull << 20, kPoolSmallest = 4096;
+// Objects without destructors: a handle may be ended while the program's own are running.
+struct Pinned { double* p; uint64_t bytes; };
 static std::mutex g_pool_mutex;
-static std::vector<std::pair<double*, uint64_t>> g_pool_free;
+static_assert(std::is_trivially_destructible<std::mutex>::value, "lives until the process ends");
+static Pinned g_pool_free[kPoolBytes / kPoolSmallest];
+static uint32_t g_pool_n = 0;                 // buffers in g_pool_free
 static uint64_t g_pool_pinned = 0;
 
 static double* pool_take(uint64_t bytes, uint64_t* got)
 {
-    uint64_t size = 4096;
+    uint64_t size = kPoolSmallest;
     while (size < bytes) size *= 2;
     if (size > kPoolBuffer) return nullptr;
     std::lock_guard<std::mutex> lock(g_pool_mutex);
-    for (size_t i = 0; i < g_pool_free.size(); ++i)
-        if (g_pool_free[i].second >= size) {
-            double* p = g_pool_free[i].first;
-            *got = g_pool_free[i].second;
-            g_pool_free[i] = g_pool_free.back(); g_pool_free.pop_back();
-            return p;
+    for (uint32_t i = 0; i < g_pool_n; ++i)
+        if (g_pool_free[i].bytes >= size) {
+            const Pinned found = g_pool_free[i];
+            g_pool_free[i] = g_pool_free[--g_pool_n];
+            *got = found.bytes;
+            return found.p;
         }
     if (g_pool_pinned + size > kPoolBytes) return nullptr;
-    try { g_pool_free.reserve(kPoolBytes / 4096); } catch (const std::bad_alloc&) { return nullptr; }   // giving back never allocates
     void* p = nullptr;
     if (hipHostMalloc(&p, size, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess || !p) { (void)hipGetLastError(); return nullptr; }
     g_pool_pinned += size;
@@ -1651,7 +1654,7 @@ static double* pool_take(uint64_t bytes, uint64_t* got)
 static void pool_give(double* p, uint64_t bytes)
 {
     std::lock_guard<std::mutex> lock(g_pool_mutex);
-    g_pool_free.emplace_back(p, bytes);
+    g_pool_free[g_pool_n++] = Pinned{p, bytes};
 }
 
 static uint64_t align_up(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }

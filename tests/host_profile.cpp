@@ -1,11 +1,38 @@
 // The host side of the profiler without a GPU: the library's own source, compiled for the host alone, on a HIP runtime that only keeps a
 // record of the calls made to it.  argv[1] names the check; a failed one prints what is wrong and returns 1.
-#include "baoc_profile.hip"
-
+#include <cstdint>
 #include <cstdio>
 #include <cstdlib>
-#include <random>
+#include <cstring>
+#include <new>
+
+// Constructed before the library's own objects and so destroyed after them, as an object of a program that loads the library later.
+static struct AtExit { void (*last)() = nullptr; ~AtExit() { if (last) last(); } } g_at_exit;
+
+#include "baoc_profile.hip"
+
 #include <string>
+
+// Freed memory is kept, filled with a pattern, once g_keep_freed is set.
+static bool g_keep_freed = false;
+static struct { unsigned char* p; size_t n; } g_freed[4096];
+static size_t g_n_freed = 0;
+void* operator new(size_t n)
+{
+    auto* p = static_cast<size_t*>(std::malloc(n + 16));
+    if (!p) throw std::bad_alloc();
+    *p = n;
+    return reinterpret_cast<char*>(p) + 16;
+}
+void operator delete(void* p) noexcept
+{
+    if (!p) return;
+    size_t* whole = reinterpret_cast<size_t*>(static_cast<char*>(p) - 16);
+    if (!g_keep_freed || g_n_freed == 4096) { std::free(whole); return; }
+    std::memset(p, 0xdd, *whole);
+    g_freed[g_n_freed].p = static_cast<unsigned char*>(p); g_freed[g_n_freed++].n = *whole;
+}
+void operator delete(void* p, size_t) noexcept { operator delete(p); }
 
 #define CHECK(cond, ...) do { if (!(cond)) { std::printf("line %d: %s ", __LINE__, #cond); std::printf(__VA_ARGS__); std::printf("\n"); return 1; } } while (0)
 
@@ -161,11 +188,33 @@ static int check_finalize_error()
     return 0;
 }
 
+// A handle that is ended by the last destructor of the program, after the library's own objects: nothing of theirs is touched.
+static baoc_profiler* g_last_handle = nullptr;
+static int check_end_at_exit()
+{
+    static std::vector<baoc_block> l;
+    add(l, 64, 64, 8);
+    static std::vector<char> workspace(64 << 20);
+    baoc_profiler* a = stepped(l, reinterpret_cast<void*>((reinterpret_cast<uintptr_t>(workspace.data()) + 255) / 256 * 256), 32 << 20);
+    baoc_profiler* b = stepped(l, reinterpret_cast<void*>((reinterpret_cast<uintptr_t>(workspace.data()) + (32 << 20) + 255) / 256 * 256), 31 << 20);
+    CHECK(a && b && baoc_profile_end(a) == BAOC_OK, " ");
+    g_last_handle = b;
+    g_keep_freed = true;
+    g_at_exit.last = [] {
+        int bad = baoc_profile_end(g_last_handle) != BAOC_OK;
+        for (size_t i = 0; i < g_n_freed; ++i)
+            for (size_t k = 0; k < g_freed[i].n; ++k) bad |= g_freed[i].p[k] != 0xdd;
+        if (bad) { std::printf("memory that was given back is written\n"); std::fflush(stdout); std::_Exit(1); }
+    };
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "plans") return check_plans();
     if (what == "finalize_error") return check_finalize_error();
+    if (what == "end_at_exit") return check_end_at_exit();
     std::printf("no check named '%s'\n", what.c_str());
     return 2;
 }

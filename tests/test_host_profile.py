@@ -36,3 +36,7 @@ def test_step_plans_of_large_layouts(host_profile):
 
 def test_finalize_waits_before_it_reports_an_error(host_profile):
     host_profile("finalize_error")
+
+
+def test_a_handle_may_outlive_the_library_s_own_objects(host_profile):
+    host_profile("end_at_exit")
