@@ -155,7 +155,7 @@ __device__ __forceinline__ float preconditioner(float v, float eps)
 
 // Every array is touched exactly once per pass: the states are loaded with the nontemporal hint so the
 // stream does not displace anything in L2 / MALL on its way through.
-template <typename T> __device__ __forceinline__ T ld_stream(const void* p)
+template <typename T> __host__ __device__ __forceinline__ T ld_stream(const void* p)
 {
     return __builtin_nontemporal_load(reinterpret_cast<const T*>(p));
 }
@@ -190,9 +190,9 @@ template <> struct GradIO<BAOC_GRAD_F32> {
     typedef float elem;
     typedef f4 vec4;                                      // four elements as loaded
     typedef f4 vec4_any __attribute__((aligned(4)));
-    __device__ static __forceinline__ vec4 loadv(const elem* p) { return ld_stream<f4>(p); }
-    __device__ static __forceinline__ vec4 loadv_any(const elem* p) { return ld_stream<vec4_any>(p); }
-    __device__ static __forceinline__ vec4 loadv_shared(const elem* p) { return *reinterpret_cast<const vec4_any*>(p); }
+    __host__ __device__ static __forceinline__ vec4 loadv(const elem* p) { return ld_stream<f4>(p); }
+    __host__ __device__ static __forceinline__ vec4 loadv_any(const elem* p) { return ld_stream<vec4_any>(p); }
+    __host__ __device__ static __forceinline__ vec4 loadv_shared(const elem* p) { return *reinterpret_cast<const vec4_any*>(p); }
     __device__ static __forceinline__ void unpack(vec4 t, float g[4]) { g[0] = t.x; g[1] = t.y; g[2] = t.z; g[3] = t.w; }
     __device__ static __forceinline__ float load1(const elem* p) { return *p; }
     __device__ static __forceinline__ void store4(StateArray a, uint32_t e, const float g[4])
@@ -205,9 +205,9 @@ template <> struct GradIO<BAOC_GRAD_BF16> {
     typedef uint16_t elem;
     typedef u2 vec4;
     typedef u2 vec4_any __attribute__((aligned(2)));
-    __device__ static __forceinline__ vec4 loadv(const elem* p) { return ld_stream<u2>(p); }
-    __device__ static __forceinline__ vec4 loadv_any(const elem* p) { return ld_stream<vec4_any>(p); }
-    __device__ static __forceinline__ vec4 loadv_shared(const elem* p) { return *reinterpret_cast<const vec4_any*>(p); }
+    __host__ __device__ static __forceinline__ vec4 loadv(const elem* p) { return ld_stream<u2>(p); }
+    __host__ __device__ static __forceinline__ vec4 loadv_any(const elem* p) { return ld_stream<vec4_any>(p); }
+    __host__ __device__ static __forceinline__ vec4 loadv_shared(const elem* p) { return *reinterpret_cast<const vec4_any*>(p); }
     __device__ static __forceinline__ void unpack(vec4 t, float g[4])
     {
         g[0] = __builtin_bit_cast(float, t.x << 16); g[1] = __builtin_bit_cast(float, t.x & 0xffff0000u);
@@ -864,6 +864,9 @@ constexpr uint32_t kSubRounds = 256 / kRoundRows;     // rounds between two row-
 __device__ __forceinline__ uint32_t scalar_u32(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 __device__ __forceinline__ uint32_t scalar_wave_index() { return scalar_u32(threadIdx.x >> 6); }
 
+// Where a wavefront reads (task_of, tile_part, load_full, load_edge and what they call) is host code as well, for the tests: a read past the parameters
+// shows there against a page without access and would not on the GPU.
+
 // A wavefront's part of its workgroup's tile.  `wave` must be uniform over the wavefront (callers pass it through
 // readfirstlane), so that the task and every address derived from it live in scalar registers.
 struct TilePart {
@@ -883,16 +886,16 @@ struct TilePart {
 // The tiles of a workgroup: [tile, last) of the segment.
 struct Task { uint32_t seg, tile, last; };
 template <bool STRIPS>
-__device__ __forceinline__ Task task_of(const TileRow& m, uint32_t wg)
+__host__ __device__ __forceinline__ Task task_of(const TileRow& m, uint32_t wg)
 {
     const uint32_t local = wg - m.first_task, seg = local / m.n_across, across = local - seg * m.n_across;
     if (!STRIPS) return Task{seg, across, across + 1};
     const uint32_t tile = across * m.strips;
-    return Task{seg, tile, min(m.n_tiles, tile + m.strips)};
+    return Task{seg, tile, (uint32_t)min(m.n_tiles, tile + m.strips)};
 }
 
 // `left`: elements from the block's first one that may be read.
-__device__ __forceinline__ TilePart tile_part(const TileRow& m, uint32_t seg, uint32_t tile, uint32_t lane, uint32_t wave, uint64_t left)
+__host__ __device__ __forceinline__ TilePart tile_part(const TileRow& m, uint32_t seg, uint32_t tile, uint32_t lane, uint32_t wave, uint64_t left)
 {
     TilePart t;
     t.seg = seg; t.tile = tile;
@@ -917,22 +920,22 @@ __device__ __forceinline__ TilePart tile_part(const TileRow& m, uint32_t seg, ui
 }
 
 // First row (of the block) of a wavefront's round.
-__device__ __forceinline__ uint32_t round_row(const TilePart& t, uint32_t i) { return t.first + i * t.stride; }
+__host__ __device__ __forceinline__ uint32_t round_row(const TilePart& t, uint32_t i) { return t.first + i * t.stride; }
 
 // Whether rows start on cache lines.  Where they do not, wavefronts side by side share a line at every row's joint, and a line that
 // is loaded with the nontemporal hint is gone when the second one asks for it (303 M coordinates in rows of 1,500 and 4,031, bf16
 // parameters: passes 262 + 480 us with the hint, 248 + 412 without; in rows of 1,536 and 4,096 223 + 340 with it, 249 + 387 without).
-template <typename E> __device__ __forceinline__ bool whole_lines(const E* src, uint32_t cols)
+template <typename E> __host__ __device__ __forceinline__ bool whole_lines(const E* src, uint32_t cols)
 {
     return ((reinterpret_cast<uintptr_t>(src) | (uintptr_t)cols * sizeof(E)) & 127u) == 0;
 }
 
 // Keeps the compiler from making one load of two that differ in the hint alone.
-__device__ __forceinline__ void apart() { asm volatile(""); }
+__host__ __device__ __forceinline__ void apart() { asm volatile(""); }
 
 // Four elements per lane and quad of a full round (of lanes without a column, some).  The address is a scalar base and a 32-bit lane offset.
 template <int TT>
-__device__ __forceinline__ void load_full(typename GradIO<TT>::vec4 (&x)[kQuads], const typename GradIO<TT>::elem* __restrict__ src, bool lines,
+__host__ __device__ __forceinline__ void load_full(typename GradIO<TT>::vec4 (&x)[kQuads], const typename GradIO<TT>::elem* __restrict__ src, bool lines,
                                           const TilePart& t, uint32_t cols, uint32_t i)
 {
     typedef typename GradIO<TT>::elem E;
@@ -953,7 +956,7 @@ __device__ __forceinline__ void load_full(typename GradIO<TT>::vec4 (&x)[kQuads]
 // The same at the edge of a matrix.  Rows and columns past the matrix are replaced by its last ones; a lane then reads up to 3
 // elements past its row.  `left`: elements from src that may be read.
 template <int TT>
-__device__ __forceinline__ void load_edge(typename GradIO<TT>::vec4 (&x)[kQuads], const typename GradIO<TT>::elem* __restrict__ src,
+__host__ __device__ __forceinline__ void load_edge(typename GradIO<TT>::vec4 (&x)[kQuads], const typename GradIO<TT>::elem* __restrict__ src,
                                           uint64_t left, const TilePart& t, uint32_t cols, uint32_t i)
 {
     typedef GradIO<TT> IO;

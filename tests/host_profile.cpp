@@ -12,6 +12,9 @@ static struct AtExit { void (*last)() = nullptr; ~AtExit() { if (last) last(); }
 #include "baoc_profile.hip"
 
 #include <string>
+#include <sys/mman.h>
+#include <sys/wait.h>
+#include <unistd.h>
 
 // Freed memory is kept, filled with a pattern, once g_keep_freed is set.
 static bool g_keep_freed = false;
@@ -209,11 +212,104 @@ static int check_end_at_exit()
     return 0;
 }
 
+// ---------------------------------------------------------------------------
+// reads of the second finalize pass
+// ---------------------------------------------------------------------------
+
+// Memory that ends with a page without access: room for `n` elements right before it.
+template <typename E> static E* before_wall(uint64_t n)
+{
+    const uint64_t page = 4096, bytes = (n * sizeof(E) + page - 1) / page * page;
+    char* p = static_cast<char*>(mmap(nullptr, bytes + page, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS, -1, 0));
+    if (p == MAP_FAILED || mprotect(p + bytes, page, PROT_NONE) != 0) std::abort();
+    return reinterpret_cast<E*>(p + bytes) - n;
+}
+
+// Every load of every lane of a pass over the last block of a layout, in the order of k_final2, by the kernel's own functions.  `behind` elements past
+// the block may be read; the pass is told that `claimed` may.  Counts how often an element is given to a lane that uses it.
+template <int TT>
+static int read_block(const Plan& P, uint64_t behind, uint64_t claimed)
+{
+    typedef typename GradIO<TT>::elem E;
+    const TileRow& m = P.tiles.back();
+    const uint64_t n = m.numel;
+    E* const src = before_wall<E>(n + behind);
+    for (uint64_t i = 0; i < n; ++i) src[i] = TT == BAOC_GRAD_F32 ? (E)(i % 8191) : (E)(i % 65521);
+    std::vector<uint8_t> used(n, 0);
+    const uint64_t left = claimed == kAnywhere ? kAnywhere : n + claimed;
+    const bool lines = whole_lines(src, m.cols);
+    typename GradIO<TT>::vec4 x[kQuads];
+    auto take = [&](const TilePart& t, uint32_t i) {
+        for (uint32_t q = 0; q < kQuads; ++q) {
+            E e[4];
+            std::memcpy(e, &x[q], sizeof e);
+            const uint64_t row = round_row(t, i) + 4 * q + t.lrow;
+            for (uint32_t k = 0; k < t.n_ok && row < t.rows; ++k) {
+                const uint64_t at = row * m.cols + t.col + k;
+                if (e[k] != src[at]) return false;
+                ++used[at];
+            }
+        }
+        return true;
+    };
+    for (uint32_t wg = m.first_task; wg < m.first_task + m.n_tasks; ++wg) {
+        const Task task = task_of<true>(m, wg);
+        for (uint32_t thread = 0; thread < 256; ++thread)
+            for (uint32_t tile = task.tile; tile < task.last; ++tile) {
+                const TilePart t = tile_part(m, task.seg, tile, thread & 63u, thread >> 6, left);
+                const uint32_t full = tile == task.tile ? t.full : 0;            // of tiles side by side only the first has its loads issued ahead
+                CHECK(t.full <= t.rounds && (m.strips == 1 || t.rounds == 1), "%u x %u", m.rows, m.cols);
+                for (uint32_t i = 0; i < t.rounds && t.any; ++i) {
+                    if (i < full) load_full<TT>(x, src, lines, t, m.cols, i);
+                    else load_edge<TT>(x, src, left, t, m.cols, i);
+                    CHECK(take(t, i), "%u x %u: round %u of thread %u", m.rows, m.cols, i, thread);
+                }
+            }
+    }
+    for (uint64_t i = 0; i < n; ++i) CHECK(used[i] == 1, "%u x %u: element %llu is used %u times", m.rows, m.cols, (unsigned long long)i, used[i]);
+    return 0;
+}
+
+// Whether reading ends at the wall.
+template <int TT> static bool hits_wall(const Plan& P, uint64_t behind, uint64_t claimed)
+{
+    std::fflush(stdout);
+    const pid_t child = fork();
+    if (child == 0) std::_Exit(read_block<TT>(P, behind, claimed) ? 3 : 0);
+    int status = 0;
+    waitpid(child, &status, 0);
+    return WIFSIGNALED(status) && WTERMSIG(status) == SIGSEGV;
+}
+
+// The parameters' last block, at any alignment: nothing behind it is read, every element is used once.  v may be read up to three elements past
+// the block.  A pass that is told of three elements more than there are runs into the wall where its last round has all rows and lacks columns.
+static int check_reads()
+{
+    static const uint32_t shapes[][2] = {{2, 2}, {2, 3}, {3, 5}, {15, 63}, {16, 2}, {17, 2}, {16, 64}, {16, 65}, {32, 63}, {48, 67}, {64, 127}, {64, 128}, {65, 127}, {160, 129},
+                                         {16, 1027}, {16, 2049}, {5, 2049}, {256, 257}, {512, 61}, {513, 66}, {1025, 62}, {129, 4}, {4097, 5}, {130, 256}, {48, 100}};
+    for (const auto& shape : shapes)
+        for (uint32_t vector : {0u, 1u << 29}) {                             // next to a large block tiles are the largest
+            std::vector<baoc_block> l;
+            if (vector) add(l, vector, 0);
+            add(l, shape[0], shape[1]);
+            const baoc_profile_params p = params_of(BAOC_GRAD_BF16);
+            Plan P;
+            CHECK(make_plan(l.data(), (uint32_t)l.size(), &p, &P, nullptr) == BAOC_OK, "%u x %u", shape[0], shape[1]);
+            if (read_block<BAOC_GRAD_F32>(P, 0, 0) || read_block<BAOC_GRAD_BF16>(P, 0, 0) || read_block<BAOC_GRAD_F32>(P, 3, kAnywhere)) return 1;
+            // a lane without a column reads from the last one on, the last lane with one from its own
+            const uint32_t rest = shape[1] % 64, past = rest <= 60 ? 3 : 64 - rest;
+            if (shape[0] % kRoundRows == 0 && rest != 0)
+                CHECK(hits_wall<BAOC_GRAD_F32>(P, 0, 3) && hits_wall<BAOC_GRAD_BF16>(P, 0, 3) && hits_wall<BAOC_GRAD_F32>(P, past - 1, kAnywhere), "%u x %u", shape[0], shape[1]);
+        }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "plans") return check_plans();
     if (what == "finalize_error") return check_finalize_error();
+    if (what == "reads") return check_reads();
     if (what == "end_at_exit") return check_end_at_exit();
     std::printf("no check named '%s'\n", what.c_str());
     return 2;

@@ -528,8 +528,8 @@ def test_partial_row_sums_around_the_two_stage_edge(env, rows_per_step):
 @pytest.mark.parametrize("dtype,pad", [("f32", 1), ("bf16", 1), ("bf16", 64)])
 def test_matrix_tiles_at_their_edges(env, dtype, pad):
     """Widths around the 64, 128 and 256 columns of a tile, heights around the 16 rows of a wavefront's round and the
-    rows of a tile, rows that start at any alignment, and a last block that ends with the parameter buffer (nothing
-    behind it may be read): statistics, F and C as the oracle has them, once with every digit prefix distinct
+    rows of a tile, rows that start at any alignment, and a last block that ends with the parameter buffer (where its
+    reads end: test_host_profile.py): statistics, F and C as the oracle has them, once with every digit prefix distinct
     (blocks of a few coordinates) and once with two."""
     torch = env["torch"]
     shapes = [(16, 64), (15, 63), (17, 65), (64, 128), (65, 127), (63, 129), (48, 257), (33, 255), (130, 256), (31, 192), (7, 321),

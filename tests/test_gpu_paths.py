@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("rows,cols", [(16, 65), (32, 63), (48, 67), (64, 127), (160, 129), (16, 1027), (256, 257), (512, 61)])
 def test_last_rounds_of_a_matrix_that_ends_with_the_parameters(env, rows, cols):
-    """All rows present and some columns missing: the last round's loads would reach past the parameters and takes the careful path."""
+    """All rows present and some columns missing: the last round takes the path whose loads end with the parameters.  The values; where the
+    loads end is checked on the host, in test_host_profile.py."""
     torch = env["torch"]
     for dtype, theta in (("f32", torch.float32), ("bf16", torch.bfloat16)):
         w = W.Workload("end", [W._vec("v", 5), W._mat("m", 300, 70), W._mat("last", rows, cols)], 2, dtype, "cycle", **W.K6)

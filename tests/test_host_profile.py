@@ -40,3 +40,7 @@ def test_finalize_waits_before_it_reports_an_error(host_profile):
 
 def test_a_handle_may_outlive_the_library_s_own_objects(host_profile):
     host_profile("end_at_exit")
+
+
+def test_matrix_loads_stay_inside_the_parameters(host_profile):
+    host_profile("reads")
