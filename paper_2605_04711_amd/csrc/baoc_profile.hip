@@ -1103,8 +1103,10 @@ __device__ __forceinline__ double tile_pass1(const float* __restrict__ v_all, co
 }
 
 // A run of a block without a matrix shape: 16 coordinates per thread and round.  Calls f(v, theta, how many of
-// the 4 exist); the loads of a round are issued together, one round ahead.  Runs start on a multiple of 4 coordinates, so a quad of v is
-// aligned and inside the padded state; theta is read at any alignment and not past the block's last coordinate.
+// the 4 exist); the loads of a round are issued together.  Runs start on a multiple of 4 coordinates, so a quad of v is
+// aligned and inside the padded state; theta is read at any alignment and not past the block's last coordinate.  (Loads a round ahead of
+// their use, with theta's hint by alignment: bf16 theta on runs that start on lines 777 -> 832 us, finalize of 28 vectors of 300 M
+// coordinates in all, 3 of 1.2 G 2777 -> 3041; 60 M of odd shapes, a third vectors, 214 -> 216.)
 template <int TT, bool THETA, typename Fn>
 __device__ __forceinline__ void walk_run(const float* __restrict__ v_all, const typename GradIO<TT>::elem* __restrict__ theta, const TileRow& m, uint32_t len, Fn f)
 {
@@ -1113,39 +1115,27 @@ __device__ __forceinline__ void walk_run(const float* __restrict__ v_all, const 
     const uint32_t n = e0 < m.numel ? (uint32_t)min((uint64_t)len, m.numel - e0) : 0u;
     const float* src = v_all + m.state_start + e0;
     const typename IO::elem* tsrc = theta + (m.grad_start + e0);
-    const bool lines = THETA && whole_lines(tsrc, 0);
-    f4 nx[4];
-    typename IO::vec4 nt[4];
-    auto issue = [&](uint32_t at) {
-#pragma unroll
-        for (uint32_t q = 0; q < 4; ++q)
-            if (at + q * 1024 < n) nx[q] = ld_stream<f4>(src + at + q * 1024);
-        if (THETA) {
-#pragma unroll
-            for (uint32_t q = 0; q < 4; ++q) {
-                const uint32_t e = at + q * 1024;
-                if (e + 4 <= n) {
-                    if (lines) nt[q] = IO::loadv_any(tsrc + e);
-                    else { apart(); nt[q] = IO::loadv_shared(tsrc + e); apart(); }
-                }
-                if (e < n && e + 4 > n) {
-                    typename IO::elem part[4];
-#pragma unroll
-                    for (uint32_t k = 0; k < 4; ++k) part[k] = e + k < n ? tsrc[e + k] : typename IO::elem(0);
-                    nt[q] = __builtin_bit_cast(typename IO::vec4, part);
-                }
-            }
-        }
-    };
-#pragma unroll
-    for (uint32_t q = 0; q < 4; ++q) { nx[q] = f4{0.f, 0.f, 0.f, 0.f}; nt[q] = typename IO::vec4{}; }
-    issue(threadIdx.x * 4);
     for (uint32_t at = threadIdx.x * 4; at < n; at += 4096) {
         f4 x[4];
         typename IO::vec4 th[4];
 #pragma unroll
-        for (uint32_t q = 0; q < 4; ++q) { x[q] = nx[q]; th[q] = nt[q]; }
-        if (at + 4096 < n) issue(at + 4096);
+        for (uint32_t q = 0; q < 4; ++q) { x[q] = f4{0.f, 0.f, 0.f, 0.f}; th[q] = typename IO::vec4{}; }
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q)
+            if (at + q * 1024 < n) x[q] = ld_stream<f4>(src + at + q * 1024);
+        if (THETA) {
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) {
+                const uint32_t e = at + q * 1024;
+                if (e + 4 <= n) th[q] = IO::loadv_any(tsrc + e);
+                else if (e < n) {
+                    typename IO::elem part[4];
+#pragma unroll
+                    for (uint32_t k = 0; k < 4; ++k) part[k] = e + k < n ? tsrc[e + k] : typename IO::elem(0);
+                    th[q] = __builtin_bit_cast(typename IO::vec4, part);
+                }
+            }
+        }
 #pragma unroll
         for (uint32_t q = 0; q < 4; ++q) {
             const uint32_t e = at + q * 1024;
