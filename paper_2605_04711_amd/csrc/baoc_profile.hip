@@ -1239,6 +1239,9 @@ __global__ __launch_bounds__(256) void k_fold1(const TileRow* __restrict__ tiles
 // registers allow.
 constexpr uint32_t kStage = 1280;
 
+// The same value, unknown to the compiler: what is cheap to form from it again keeps no register over a loop.
+__device__ __forceinline__ uint32_t again(uint32_t x) { asm("" : "+v"(x)); return x; }
+
 // F, C: Eq. 7 and Eq. 6 are wanted.
 template <int TT, bool F, bool C, bool STRIPS>
 __global__ __launch_bounds__(256, 4) void k_final2(
@@ -1288,9 +1291,12 @@ __global__ __launch_bounds__(256, 4) void k_final2(
             load_full<BAOC_GRAD_F32>(nx, src, lines, t, cols, i);
             if (C) load_full<TT>(nt, tsrc, tlines, t, cols, i);
             if (F) {
-                const float* p = rr + round_row(t, i);
+                // a scalar base and a 32-bit lane offset that is not kept: as a 64-bit address per lane it makes the registers spill with fp32
+                // theta (finalize of 1.3 G coordinates 2651 -> 2640 us)
+                const char* p = reinterpret_cast<const char*>(rr + round_row(t, i));
+                const uint32_t at = again(lane) >> 4 << 2;
 #pragma unroll
-                for (uint32_t q = 0; q < kQuads; ++q) nr[q] = (p + 4 * q)[t.lrow];
+                for (uint32_t q = 0; q < kQuads; ++q) nr[q] = *reinterpret_cast<const float*>(p + 16 * q + at);
             }
         };
         // tiles side by side have one round each, which the loop over the edges takes

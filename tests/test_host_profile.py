@@ -6,6 +6,8 @@ import subprocess
 
 import pytest
 
+from paper_2605_04711_amd import binding
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2605_04711_amd", "csrc")
 
@@ -44,3 +46,13 @@ def test_a_handle_may_outlive_the_library_s_own_objects(host_profile):
 
 def test_matrix_loads_stay_inside_the_parameters(host_profile):
     host_profile("reads")
+
+
+def test_no_kernel_spills_registers_or_uses_scratch():
+    """The kernels' metadata in the built library: a zero behind every such key."""
+    binding.load_library()
+    with open(binding._build.LIB, "rb") as f:
+        lib = f.read()
+    for key in (b".private_segment_fixed_size", b".vgpr_spill_count"):
+        values = [lib[i + len(key)] for i in range(len(lib)) if lib.startswith(key, i)]
+        assert len(values) > 50 and set(values) == {0}, (key, values)
