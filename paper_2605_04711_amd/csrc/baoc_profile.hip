@@ -160,25 +160,33 @@ template <typename T> __host__ __device__ __forceinline__ T ld_stream(const void
     return __builtin_nontemporal_load(reinterpret_cast<const T*>(p));
 }
 
-// A chunk's part of one state array, as a buffer: stores into it carry the hint and go through to memory (no builtin sets that bit on a
-// 16-byte global store), so that no line stays in the L2 to be written back between the reads of others.  Steps, same inputs, hint on all
-// accesses -> stores through -> and the gradient without the hint: 3.5 G coordinates bf16 12.96 -> 12.77 -> 12.29 ms,
-// 1.3 G fp32 5.88 -> 5.80 -> 5.74 ms, 60 M bf16 at odd offsets 214 -> 213 -> 203 us.  Without the hint on the state loads the 3.5 G take
-// 14.5 ms, without it on the stores 14.9 ms.
+// How a step's stores pass the caches (states are always loaded with the hint, the gradient without it):
+//   kThrough  stores carry the hint and go through to memory, so that no line stays in the L2 to be written back between the reads of others.
+//             Large layouts.  (On one workspace, hint on all accesses -> stores through -> the gradient without the hint: 3.5 G
+//             coordinates bf16 12.79 -> 12.60 -> 12.22 ms, 1.3 G fp32 5.76 -> 5.67 -> 5.67, bf16 4.83 -> 4.73 -> 4.56, 60 M bf16 at odd offsets 216 ->
+//             212 -> 202 us.)
+//   kKept     stores go through to memory without the hint and stay in the memory-side cache.  Layouts whose states fill half of it at most.
+// us a step, kThrough and kKept: fp32 2 M coordinates 14.1 and 13.0, 8 M 39.6 and 38.4, 17 M 77 and 76, 25 M 108 and 124; bf16 2 M 12.8 and 11.5, 8 M
+// 33.3 and 30.9, 17 M 62 and 59, 25 M 88 and 94.  (In a training step other kernels pass between two of these, so the line lies below
+// the 170 to 200 MB where kKept begins to lose here.)
+enum Memory : int { kThrough, kKept };
+constexpr uint64_t kKeptBytes = 128ull << 20;             // of states
+template <int MEM> constexpr int kStoreBits = MEM == kThrough ? 2 | 16 : 16;     // nt = 2, sc1 = 16
+
+// A chunk's part of one state array, as a buffer: no builtin sets these bits on a 16-byte global store.
 typedef __amdgpu_buffer_rsrc_t StateArray;
 template <typename E> __device__ __forceinline__ StateArray state_array(E* first, uint32_t n)
 {
     return __builtin_amdgcn_make_buffer_rsrc(first, 0, n * sizeof(E), 0x00020000);
 }
-constexpr int kStoreThrough = 2 | 16;                     // nt, sc1
-__device__ __forceinline__ void st_through(StateArray a, uint32_t byte, f4 x)
+template <int MEM> __device__ __forceinline__ void st_state(StateArray a, uint32_t byte, f4 x)
 {
     typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, x), a, byte, 0, kStoreThrough);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, x), a, byte, 0, kStoreBits<MEM>);
 }
-__device__ __forceinline__ void st_through(StateArray a, uint32_t byte, u2 x)
+template <int MEM> __device__ __forceinline__ void st_state(StateArray a, uint32_t byte, u2 x)
 {
-    __builtin_amdgcn_raw_buffer_store_b64(x, a, byte, 0, kStoreThrough);
+    __builtin_amdgcn_raw_buffer_store_b64(x, a, byte, 0, kStoreBits<MEM>);
 }
 
 template <int GT> struct GradIO;
@@ -195,9 +203,9 @@ template <> struct GradIO<BAOC_GRAD_F32> {
     __host__ __device__ static __forceinline__ vec4 loadv_shared(const elem* p) { return *reinterpret_cast<const vec4_any*>(p); }
     __device__ static __forceinline__ void unpack(vec4 t, float g[4]) { g[0] = t.x; g[1] = t.y; g[2] = t.z; g[3] = t.w; }
     __device__ static __forceinline__ float load1(const elem* p) { return *p; }
-    __device__ static __forceinline__ void store4(StateArray a, uint32_t e, const float g[4])
+    template <int MEM> __device__ static __forceinline__ void store4(StateArray a, uint32_t e, const float g[4])
     {
-        st_through(a, e * 4, f4{g[0], g[1], g[2], g[3]});
+        st_state<MEM>(a, e * 4, f4{g[0], g[1], g[2], g[3]});
     }
 };
 
@@ -215,12 +223,12 @@ template <> struct GradIO<BAOC_GRAD_BF16> {
     }
     __device__ static __forceinline__ float load1(const elem* p) { return bf16_widen(*p); }
     // g holds exact bf16 values: the upper half of each word is the stored pattern
-    __device__ static __forceinline__ void store4(StateArray a, uint32_t e, const float g[4])
+    template <int MEM> __device__ static __forceinline__ void store4(StateArray a, uint32_t e, const float g[4])
     {
         u2 t;
         t.x = (__builtin_bit_cast(uint32_t, g[0]) >> 16) | (__builtin_bit_cast(uint32_t, g[1]) & 0xffff0000u);
         t.y = (__builtin_bit_cast(uint32_t, g[2]) >> 16) | (__builtin_bit_cast(uint32_t, g[3]) & 0xffff0000u);
-        st_through(a, e * 2, t);
+        st_state<MEM>(a, e * 2, t);
     }
 };
 
@@ -299,7 +307,7 @@ __device__ __forceinline__ void fold_step(double total, double state, double* re
 // slice is a single round, so no wavefront ever waits on its own stores.
 // FOLD (small layouts): the workgroup of a block that arrives last adds the block's partial rows and folds the step into
 // its record; otherwise k_reduce does.
-template <int GT, bool FIRST, int G, int NW, bool FOLD>
+template <int GT, bool FIRST, int G, int NW, bool FOLD, int MEM>
 __global__ __launch_bounds__(64 * NW) void k_step(
     const typename GradIO<GT>::elem* __restrict__ grad,
     float* __restrict__ m_all, float* __restrict__ v_all,
@@ -386,10 +394,10 @@ __global__ __launch_bounds__(64 * NW) void k_step(
                 v[j] = __builtin_fmaf(k.beta_v, v[j], tv);
             }
             {
-                st_through(m_dst, e * 4, f4{m[0], m[1], m[2], m[3]});
-                st_through(v_dst, e * 4, f4{v[0], v[1], v[2], v[3]});
+                st_state<MEM>(m_dst, e * 4, f4{m[0], m[1], m[2], m[3]});
+                st_state<MEM>(v_dst, e * 4, f4{v[0], v[1], v[2], v[3]});
             }
-            IO::store4(gp_dst, e, g);
+            IO::template store4<MEM>(gp_dst, e, g);
 
             // group absmax of the 256 coordinates this wavefront holds
             const float a_m = wave_max_nonneg(fmaxf(fmaxf(fabsf(m[0]), fabsf(m[1])), fmaxf(fabsf(m[2]), fabsf(m[3]))));
@@ -1587,6 +1595,7 @@ struct Plan {
     uint32_t gpw = 1, nw = 4, slices = 1, slice_groups = 4, resident = 8;   // launch shape of the step kernel
     uint64_t n_prows = 0;         // partial rows of the step kernel = n_chunks * slices
     bool fold_in_step = false;    // the step kernel folds its own partial rows
+    Memory memory = kThrough;
     std::vector<BlockRow> rows;
     std::vector<TileRow> tiles;   // how finalize walks each block
     bool any_matrix = false, any_strips = false;
@@ -1767,6 +1776,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
         return true;
     };
     if (!cut(cg, P.slices)) return BAOC_ERR_UNSUPPORTED;
+    P.memory = P.padded * (prm->grad_dtype == BAOC_GRAD_F32 ? 12 : 10) <= kKeptBytes ? kKept : kThrough;
     P.multi.clear();
     uint32_t most_prows = 0;
     for (const BlockRow& r : P.rows) most_prows = std::max(most_prows, r.n_prows);
@@ -1912,21 +1922,24 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     return BAOC_OK;
 }
 
-template <int GT, int G, int NW, typename... Args>
+template <int GT, int G, int NW, int MEM, typename... Args>
 static void launch_step_as(bool first, bool fold, uint32_t grid, uint32_t lds, hipStream_t st, Args... a)
 {
     const dim3 g(grid), b(64 * NW);
-    if (first && fold) hipLaunchKernelGGL((k_step<GT, true, G, NW, true>), g, b, lds, st, a...);
-    else if (first) hipLaunchKernelGGL((k_step<GT, true, G, NW, false>), g, b, lds, st, a...);
-    else if (fold) hipLaunchKernelGGL((k_step<GT, false, G, NW, true>), g, b, lds, st, a...);
-    else hipLaunchKernelGGL((k_step<GT, false, G, NW, false>), g, b, lds, st, a...);
+    if (first && fold) hipLaunchKernelGGL((k_step<GT, true, G, NW, true, MEM>), g, b, lds, st, a...);
+    else if (first) hipLaunchKernelGGL((k_step<GT, true, G, NW, false, MEM>), g, b, lds, st, a...);
+    else if (fold) hipLaunchKernelGGL((k_step<GT, false, G, NW, true, MEM>), g, b, lds, st, a...);
+    else hipLaunchKernelGGL((k_step<GT, false, G, NW, false, MEM>), g, b, lds, st, a...);
 }
 
-// The instantiation for groups per wavefront and wavefronts per workgroup; the values were validated at begin.
+// The instantiation for groups per wavefront and wavefronts per workgroup; the values were validated at begin.  What small layouts do with
+// the caches is built for the shapes that they have by default.
 template <int GT, typename... Args>
-static void launch_step(uint32_t gpw, uint32_t nw, Args... a)
+static void launch_step(uint32_t gpw, uint32_t nw, Memory memory, Args... a)
 {
-#define BAOC_STEP_CASE(GG, NN) if (gpw == GG && nw == NN) { launch_step_as<GT, GG, NN>(a...); return; }
+    constexpr uint32_t G = kSmallShape[GT].groups_per_wave, N = kSmallShape[GT].waves_per_workgroup;
+    if (gpw == G && nw == N && memory == kKept) { launch_step_as<GT, G, N, kKept>(a...); return; }
+#define BAOC_STEP_CASE(GG, NN) if (gpw == GG && nw == NN) { launch_step_as<GT, GG, NN, kThrough>(a...); return; }
     BAOC_STEP_CASE(1, 1) BAOC_STEP_CASE(2, 1) BAOC_STEP_CASE(1, 2) BAOC_STEP_CASE(2, 2) BAOC_STEP_CASE(1, 4) BAOC_STEP_CASE(2, 4)
 #undef BAOC_STEP_CASE
 }
@@ -2041,10 +2054,10 @@ extern "C" int baoc_profile_step(baoc_profiler* h, const void* d_grad_flat, uint
     double* rec = reinterpret_cast<double*>(h->ws + P.off_rec);
     const FoldArgs fold{rows, reinterpret_cast<uint32_t*>(h->ws + P.off_arrived), rec, q.beta_rho, q.eps};
     if (q.grad_dtype == BAOC_GRAD_F32)
-        launch_step<BAOC_GRAD_F32>(P.gpw, P.nw, first, P.fold_in_step, grid, lds, st, static_cast<const float*>(d_grad_flat), m, v,
+        launch_step<BAOC_GRAD_F32>(P.gpw, P.nw, P.memory, first, P.fold_in_step, grid, lds, st, static_cast<const float*>(d_grad_flat), m, v,
                                    reinterpret_cast<float*>(h->ws + P.off_gp), ch, part, k, P.slices, P.slice_groups, fold);
     else
-        launch_step<BAOC_GRAD_BF16>(P.gpw, P.nw, first, P.fold_in_step, grid, lds, st, static_cast<const uint16_t*>(d_grad_flat), m, v,
+        launch_step<BAOC_GRAD_BF16>(P.gpw, P.nw, P.memory, first, P.fold_in_step, grid, lds, st, static_cast<const uint16_t*>(d_grad_flat), m, v,
                                     reinterpret_cast<uint16_t*>(h->ws + P.off_gp), ch, part, k, P.slices, P.slice_groups, fold);
     h->steps += 1;
     if (!P.fold_in_step) {

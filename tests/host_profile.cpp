@@ -304,11 +304,28 @@ static int check_reads()
     return 0;
 }
 
+// States that fill half of the memory-side cache at most stay there, larger ones go past it.
+static int check_memory()
+{
+    for (uint32_t dtype : {BAOC_GRAD_F32, BAOC_GRAD_BF16}) {
+        const uint64_t most = (128ull << 20) / (dtype == BAOC_GRAD_F32 ? 12 : 10) / kQB * kQB;
+        for (const auto& [n, want] : {std::pair<uint64_t, Memory>{1, kKept}, {most, kKept}, {most + 1, kThrough}, {1u << 28, kThrough}}) {
+            std::vector<baoc_block> l;
+            add(l, n, 0);
+            const baoc_profile_params p = params_of(dtype);
+            Plan P;
+            CHECK(make_plan(l.data(), 1, &p, &P, nullptr) == BAOC_OK && P.memory == want, "%llu", (unsigned long long)n);
+        }
+    }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "plans") return check_plans();
     if (what == "finalize_error") return check_finalize_error();
+    if (what == "memory") return check_memory();
     if (what == "reads") return check_reads();
     if (what == "end_at_exit") return check_end_at_exit();
     std::printf("no check named '%s'\n", what.c_str());

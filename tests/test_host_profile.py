@@ -36,6 +36,10 @@ def test_step_plans_of_large_layouts(host_profile):
     host_profile("plans")
 
 
+def test_states_of_small_layouts_stay_in_the_memory_side_cache(host_profile):
+    host_profile("memory")
+
+
 def test_finalize_waits_before_it_reports_an_error(host_profile):
     host_profile("finalize_error")
 
