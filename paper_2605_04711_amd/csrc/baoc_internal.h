@@ -12,19 +12,20 @@ constexpr uint32_t kNumSums = 16;        // floats in one partial-sum row
 
 // Launch shape of the step kernel, per gradient type (fp32, bf16).  Measured: a DRAM stream of 4 reads
 // and 3 writes per coordinate runs fastest with few, fat requesters; more resident wavefronts only add
-// row conflicts.  fp32 gradients: single-wavefront workgroups of two adjacent groups, about 10 resident
-// per compute unit; bf16: 4 wavefronts x 2 groups, 3 resident.  A chunk (the unit of the step's
-// tables) is cut into slices of one round each.
-// Layouts that do not keep the chip busy for long take more wavefronts, and fp32 ones other workgroups (us a step, fp32: 4 wavefronts x 1
-// group with 4 resident, the same with 7, 2 wavefronts x 2 groups with 6, the shape of large layouts: 17 M coordinates 78.6, 74.8, 75.8,
-// 81.7; 25.6 M 115.9, 110.2, 111.8, 120.1; 40 M 185, 182.7, 178.9, 187; 66 M 318.9, 322.8, 314.4, 318.1; 90 M 423, 430, 420, 414.  bf16 with
-// 3 and 4 resident: 17 M 62.6, 61.9, 25.6 M 91.2, 89.2, 66 M 229.3, 227.7, 90 M 317.8, 324.2).
+// row conflicts.  A chunk (the unit of the step's tables) is cut into slices of one round each.
+// fp32: large layouts have single-wavefront workgroups of one group, 16 resident per compute unit, where the workspace has room for their
+// rows (make_plan), of two adjacent groups, 10 resident, elsewhere.  bf16: 4 wavefronts x 2 groups, 3 resident.
+// Layouts that do not keep the chip busy for long take more wavefronts, and fp32 ones other workgroups.  (us a step, fp32 with stores through
+// to memory, 4 wavefronts x 1 group with 4 resident, the same with 7, 2 wavefronts x 2 groups with 5, 1 x 2 with 10: 33 M coordinates
+// 147, 141, 148, 153; 60 M 276, 289, 268, 270; 66 M 300, 305, 292, 296.  Between kSmallLayout and kHintedLayout 4 x 1 with 4 and the hint on
+// all accesses: 42 M 185 to 192, the others 187 to 211.  bf16 with 3 and 4 resident: 17 M 62.6, 61.9, 25.6 M 91.2, 89.2, 66 M 229.3, 227.7, 90 M
+// 317.8, 324.2.)
 struct LaunchShape { uint32_t chunk_groups, groups_per_wave, waves_per_workgroup, resident_workgroups; };
-// (make_plan has single-wavefront workgroups of one group, 16 resident, for large fp32 layouts where the workspace has room for their rows.)
 constexpr LaunchShape kDefaultShape[2] = {{4, 2, 1, 10}, {8, 2, 4, 3}};
-constexpr LaunchShape kMediumShape[2] = {{4, 2, 2, 6}, {8, 2, 4, 4}};         // below kMediumLayout coordinates
-constexpr LaunchShape kSmallShape[2] = {{4, 1, 4, 7}, {8, 2, 4, 4}};          // below kSmallLayout coordinates
-constexpr uint64_t kMediumLayout = 1ull << 26, kSmallLayout = 1ull << 25;
+constexpr LaunchShape kMediumF32Shape = {4, 2, 2, 5};                         // below kMediumLayout coordinates
+constexpr LaunchShape kHintedF32Shape = {4, 1, 4, 4};                         // below kHintedLayout
+constexpr LaunchShape kSmallShape[2] = {{4, 1, 4, 7}, {8, 2, 4, 4}};          // fp32 below kSmallLayout, bf16 below kMediumLayout
+constexpr uint64_t kMediumLayout = 1ull << 26, kHintedLayout = 7ull << 23, kSmallLayout = 35'000'000;
 constexpr uint32_t kLdsBytesPerCU = 160 * 1024;   // gfx950
 
 // order of the sums in a partial row and in the per-block raw record

@@ -160,18 +160,20 @@ template <typename T> __host__ __device__ __forceinline__ T ld_stream(const void
     return __builtin_nontemporal_load(reinterpret_cast<const T*>(p));
 }
 
-// How a step's stores pass the caches (states are always loaded with the hint, the gradient without it):
-//   kThrough  stores carry the hint and go through to memory, so that no line stays in the L2 to be written back between the reads of others.
-//             Large layouts.  (On one workspace, hint on all accesses -> stores through -> the gradient without the hint: 3.5 G
-//             coordinates bf16 12.79 -> 12.60 -> 12.22 ms, 1.3 G fp32 5.76 -> 5.67 -> 5.67, bf16 4.83 -> 4.73 -> 4.56, 60 M bf16 at odd offsets 216 ->
-//             212 -> 202 us.)
+// How a step's stores and gradient loads pass the caches (states are always loaded with the hint):
+//   kThrough  stores carry the hint and go through to memory, so that no line stays in the L2 to be written back between the reads of others;
+//             the gradient is loaded without the hint.  Large layouts.  (On one workspace, hint on all accesses -> stores through -> the gradient
+//             without the hint: 3.5 G coordinates bf16 12.79 -> 12.60 -> 12.22 ms, 1.3 G fp32 5.76 -> 5.67 -> 5.67, bf16 4.83 -> 4.73 -> 4.56,
+//             60 M bf16 at odd offsets 216 -> 212 -> 202 us.)
 //   kKept     stores go through to memory without the hint and stay in the memory-side cache.  Layouts whose states fill half of it at most.
+//   kHinted   the hint on all accesses, stores wait in the L2.  fp32 layouts between kSmallLayout and kHintedLayout.
 // us a step, kThrough and kKept: fp32 2 M coordinates 14.1 and 13.0, 8 M 39.6 and 38.4, 17 M 77 and 76, 25 M 108 and 124; bf16 2 M 12.8 and 11.5, 8 M
 // 33.3 and 30.9, 17 M 62 and 59, 25 M 88 and 94.  (In a training step other kernels pass between two of these, so the line lies below
-// the 170 to 200 MB where kKept begins to lose here.)
-enum Memory : int { kThrough, kKept };
+// the 170 to 200 MB where kKept begins to lose here.)  kThrough and kHinted, each with its best workgroups, fp32: 34 M 147 to 159 and 152 to
+// 161, 42 M 189 to 198 and 185 to 192, 48 M 214 to 236 and 211 to 234, 55 M 245 to 253 and 245 to 255, 62 M 277 to 286 and 279 to 291.
+enum Memory : int { kThrough, kKept, kHinted };
 constexpr uint64_t kKeptBytes = 128ull << 20;             // of states
-template <int MEM> constexpr int kStoreBits = MEM == kThrough ? 2 | 16 : 16;     // nt = 2, sc1 = 16
+template <int MEM> constexpr int kStoreBits = MEM == kThrough ? 2 | 16 : MEM == kKept ? 16 : 2;   // nt = 2, sc1 = 16
 
 // A chunk's part of one state array, as a buffer: no builtin sets these bits on a 16-byte global store.
 typedef __amdgpu_buffer_rsrc_t StateArray;
@@ -352,7 +354,7 @@ __global__ __launch_bounds__(64 * NW) void k_step(
                 const uint32_t e = grp * kQB + lane * 4;
                 const uint64_t si = ck.state_start + e;   // states are padded to whole groups
                 if (!FIRST) { nm[i] = ld_stream<f4>(m_all + si); nv[i] = ld_stream<f4>(v_all + si); np[i] = IO::loadv(gp_all + si); }
-                if (e + 4 <= ck.count) ng[i] = IO::loadv_shared(gsrc + e);
+                if (e + 4 <= ck.count) ng[i] = MEM == kHinted ? IO::loadv_any(gsrc + e) : IO::loadv_shared(gsrc + e);
             }
         }
     };
@@ -1740,9 +1742,11 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     Plan& P = *out;
     uint64_t total = 0;
     for (uint32_t i = 0; i < n; ++i) total += blocks[i].numel;
-    // a caller's own groups or wavefronts stand next to the small shape's: the medium one's other half would mean more workgroups
-    const bool medium = total < kMediumLayout && !prm->groups_per_wave && !prm->waves_per_workgroup;
-    const LaunchShape& ds = (medium && total >= kSmallLayout ? kMediumShape : (total < kMediumLayout ? kSmallShape : kDefaultShape))[prm->grad_dtype];
+    // a caller's own groups or wavefronts do not stand next to the medium shape's: its other half would mean more workgroups
+    const bool f32 = prm->grad_dtype == BAOC_GRAD_F32, medium = total >= kHintedLayout && !prm->groups_per_wave && !prm->waves_per_workgroup;
+    const LaunchShape& ds = total >= kMediumLayout ? kDefaultShape[prm->grad_dtype]
+                            : f32 && medium        ? kMediumF32Shape
+                            : f32 && total >= kSmallLayout ? kHintedF32Shape : kSmallShape[prm->grad_dtype];
     P.gpw = prm->groups_per_wave ? prm->groups_per_wave : ds.groups_per_wave;
     P.nw = prm->waves_per_workgroup ? prm->waves_per_workgroup : ds.waves_per_workgroup;
     P.resident = prm->resident_workgroups ? prm->resident_workgroups : ds.resident_workgroups;
@@ -1776,7 +1780,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
         return true;
     };
     if (!cut(cg, P.slices)) return BAOC_ERR_UNSUPPORTED;
-    P.memory = P.padded * (prm->grad_dtype == BAOC_GRAD_F32 ? 12 : 10) <= kKeptBytes ? kKept : kThrough;
+    P.memory = P.padded * (f32 ? 12 : 10) <= kKeptBytes ? kKept : f32 && total >= kSmallLayout && total < kHintedLayout ? kHinted : kThrough;
     P.multi.clear();
     uint32_t most_prows = 0;
     for (const BlockRow& r : P.rows) most_prows = std::max(most_prows, r.n_prows);
@@ -1939,6 +1943,8 @@ static void launch_step(uint32_t gpw, uint32_t nw, Memory memory, Args... a)
 {
     constexpr uint32_t G = kSmallShape[GT].groups_per_wave, N = kSmallShape[GT].waves_per_workgroup;
     if (gpw == G && nw == N && memory == kKept) { launch_step_as<GT, G, N, kKept>(a...); return; }
+    if constexpr (GT == BAOC_GRAD_F32)
+        if (gpw == G && nw == N && memory == kHinted) { launch_step_as<GT, G, N, kHinted>(a...); return; }
 #define BAOC_STEP_CASE(GG, NN) if (gpw == GG && nw == NN) { launch_step_as<GT, GG, NN, kThrough>(a...); return; }
     BAOC_STEP_CASE(1, 1) BAOC_STEP_CASE(2, 1) BAOC_STEP_CASE(1, 2) BAOC_STEP_CASE(2, 2) BAOC_STEP_CASE(1, 4) BAOC_STEP_CASE(2, 4)
 #undef BAOC_STEP_CASE

@@ -38,7 +38,7 @@ def _layout(kind, total):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("kind,total", [("vectors", 1_000_003), ("matrices", 1 << 23), ("matrices", 1 << 24), ("matrices", (1 << 25) + 1), ("vectors", (1 << 25) + 1), ("matrices", (1 << 26) + 1), ("vectors", (1 << 26) + 1), ("edges", (1 << 26) + 1)])
+@pytest.mark.parametrize("kind,total", [("vectors", 1_000_003), ("matrices", 1 << 23), ("matrices", 1 << 24), ("matrices", (1 << 25) + 1), ("vectors", (1 << 25) + 1), ("matrices", 45_000_001), ("vectors", 60_000_001), ("matrices", (1 << 26) + 1), ("vectors", (1 << 26) + 1), ("edges", (1 << 26) + 1)])
 def test_default_step_shape_of_every_size_against_an_explicit_one(env, dtype, kind, total):
     """States to the bit, statistics up to the order of the partial sums, across a finalize whose lists may stand where the step's rows do."""
     torch, binding = env["torch"], env["binding"]
