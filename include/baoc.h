@@ -19,7 +19,8 @@
  *   - "d_" arguments are DEVICE pointers (HIP, current device); all other
  *     pointers are HOST pointers.
  *   - The caller owns every buffer it passes in, including the device
- *     workspace; the library owns only the opaque handle.
+ *     workspace; the library owns the opaque handle and up to 4 MB of pinned host
+ *     memory for all handles together (baoc_profile_begin).
  *   - A handle is not thread safe; different handles are independent.
  *   - The profiler takes every coordinate of the blocks it is given (Omega_i = all of B_i);
  *     to profile a subset, gather it first (baoc_sample_*) and describe the compact buffer.
@@ -65,20 +66,26 @@ typedef struct {
     float    eps_update;   /* epsilon inside u = m / (sqrt(v) + eps_update), Eq. 8 (1e-8); > 0 */
     uint32_t quant_block;  /* coordinates per 8-bit absmax group; only 256 is built     */
     uint32_t grad_dtype;   /* BAOC_GRAD_F32 | BAOC_GRAD_BF16 (states are always fp32)   */
-    /* Launch shape of the per-step kernel; 0 = the default measured best for the gradient type
-     * and the size (fp32 layouts of fewer than 2^25 coordinates: 4 wavefronts x 1 group, 7 resident, of
-     * fewer than 2^26: 2 x 2 groups, 6 resident, larger ones whose blocks are mostly matrices: 1 x 1 group,
-     * 16 resident; bf16 layouts of fewer than 2^26: 4 resident).
+    /* Launch shape of the per-step kernel; 0 = the default measured best for the gradient type and the
+     * size.  wavefronts x groups of a workgroup, workgroups resident per compute unit, groups per chunk:
+     *   fp32, below 35 M coordinates        4 x 1,  7, 4
+     *         below 7/8 of 2^26             4 x 1,  4, 4
+     *         below 2^26                    2 x 2,  5, 4
+     *         larger, mostly matrices       1 x 1, 16, 8 (4 where blocks have few groups)
+     *         larger, others                1 x 2, 10, 4
+     *   bf16, below 2^26                    4 x 2,  4, 8
+     *         larger                        4 x 2,  3, 8
+     * A caller's own value stands next to the others of its line, with two exceptions: where any of the five is
+     * set, larger fp32 layouts have the line 1 x 2 for the others, and where groups or wavefronts are set, those of
+     * the line 2 x 2 have the one above it.
      * None of the five changes any result bit except through the order of the partial sums. */
-    uint32_t chunk_groups;        /* quantisation groups per chunk, the unit of the step's tables
-                                   * (default 8 for bf16 gradients, 4 for fp32)                       */
-    uint32_t chunk_slices;        /* workgroups of the step kernel per chunk (default: as many as
+    uint32_t chunk_groups;        /* quantisation groups per chunk, the unit of the step's tables, up to 4096 */
+    uint32_t chunk_slices;        /* workgroups of the step kernel per chunk, up to 64 (default: as many as
                                    * make a slice one round, chunk_groups / (waves * groups_per_wave)) */
-    uint32_t groups_per_wave;     /* adjacent groups a wavefront loads together: 1 or 2 (default 2)   */
-    uint32_t waves_per_workgroup; /* 1, 2 or 4 (default 4 for bf16 gradients, 1 for fp32)             */
+    uint32_t groups_per_wave;     /* adjacent groups a wavefront loads together: 1 or 2               */
+    uint32_t waves_per_workgroup; /* 1, 2 or 4                                                        */
     uint32_t resident_workgroups; /* workgroups of the steady-state step kernel resident per compute
-                                   * unit, 3..32, held by launching with unused LDS (default 3 for
-                                   * bf16 gradients, 10 for fp32)                                     */
+                                   * unit, 3..32, held by launching with unused LDS                   */
 } baoc_profile_params;
 
 /* A candidate configuration c = (y_a, y_m, y_d, y_f, b) of Def. 3.1:
@@ -145,6 +152,9 @@ int baoc_profile_workspace_bytes(const baoc_block* blocks, uint32_t n_blocks,
  * workspace_bytes long, owned by the caller and kept alive until
  * baoc_profile_end) and upload the layout tables.  The states start at zero: the
  * first step does not read them, it writes them.  Synchronous on the null stream.
+ * Takes a pinned host buffer for the records of finalize (256 bytes per block, up to
+ * 4,096 blocks), which baoc_profile_end leaves to later handles: at most 4 MB are ever
+ * pinned, until the process ends; a handle that finds no room has its records copied.
  * *out receives the handle.  Errors: INVALID, WORKSPACE, UNSUPPORTED, HIP. */
 int baoc_profile_begin(const baoc_block* blocks, uint32_t n_blocks,
                        const baoc_profile_params* params,
@@ -154,7 +164,7 @@ int baoc_profile_begin(const baoc_block* blocks, uint32_t n_blocks,
  * end of a HIP graph capture, serving loops, harnesses that forbid hipMalloc): the workspace is an
  * array of BAOC_STATIC_WORKSPACE_BYTES that the library holds on every GPU it is loaded on, from load
  * until the process ends.  The call, and the step / finalize / end calls on its handle, allocate no
- * device memory.  Everything else is as in baoc_profile_begin: the same kernels, bit-identical results.
+ * device memory and pin no host memory.  Everything else is as in baoc_profile_begin: the same kernels, bit-identical results.
  * The array keeps what the last handle left in it (begin clears what must start at zero), and all
  * handles begun this way on one GPU share it: only one may be alive per GPU at a time (a second begin
  * before baoc_profile_end returns STATE), and work still queued on a stream for an ended handle races

@@ -10,16 +10,15 @@ namespace baoc {
 constexpr uint32_t kQB = 256;            // coordinates per 8-bit absmax group = one wavefront x 4
 constexpr uint32_t kNumSums = 16;        // floats in one partial-sum row
 
-// Launch shape of the step kernel, per gradient type (fp32, bf16).  Measured: a DRAM stream of 4 reads
-// and 3 writes per coordinate runs fastest with few, fat requesters; more resident wavefronts only add
-// row conflicts.  A chunk (the unit of the step's tables) is cut into slices of one round each.
-// fp32: large layouts have single-wavefront workgroups of one group, 16 resident per compute unit, where the workspace has room for their
-// rows (make_plan), of two adjacent groups, 10 resident, elsewhere.  bf16: 4 wavefronts x 2 groups, 3 resident.
-// Layouts that do not keep the chip busy for long take more wavefronts, and fp32 ones other workgroups.  (us a step, fp32 with stores through
-// to memory, 4 wavefronts x 1 group with 4 resident, the same with 7, 2 wavefronts x 2 groups with 5, 1 x 2 with 10: 33 M coordinates
-// 147, 141, 148, 153; 60 M 276, 289, 268, 270; 66 M 300, 305, 292, 296.  Between kSmallLayout and kHintedLayout 4 x 1 with 4 and the hint on
-// all accesses: 42 M 185 to 192, the others 187 to 211.  bf16 with 3 and 4 resident: 17 M 62.6, 61.9, 25.6 M 91.2, 89.2, 66 M 229.3, 227.7, 90 M
-// 317.8, 324.2.)
+// Launch shape of the step kernel, per gradient type (fp32, bf16).  Measured: a DRAM stream of 4 reads and 3 writes per
+// coordinate runs fastest with few, fat requesters; more resident wavefronts only add row conflicts.  A chunk (the unit of the
+// step's tables) is cut into slices of one round each. fp32: large layouts have single-wavefront workgroups of one group, 16
+// resident per compute unit, where the workspace has room for their rows (make_plan), of two adjacent groups, 10 resident,
+// elsewhere.  bf16: 4 wavefronts x 2 groups, 3 resident. Layouts that do not keep the chip busy for long take more wavefronts,
+// and fp32 ones other workgroups.  (us a step, fp32 with stores through to memory, 4 wavefronts x 1 group with 4 resident, the
+// same with 7, 2 wavefronts x 2 groups with 5, 1 x 2 with 10: 33 M coordinates 147, 141, 148, 153; 60 M 276, 289, 268, 270; 66 M
+// 300, 305, 292, 296.  Between kSmallLayout and kHintedLayout 4 x 1 with 4 and the hint on all accesses: 42 M 185 to 192, the
+// others 187 to 211.  bf16 with 3 and 4 resident: 17 M 62.6, 61.9, 25.6 M 91.2, 89.2, 66 M 229.3, 227.7, 90 M 317.8, 324.2.)
 struct LaunchShape { uint32_t chunk_groups, groups_per_wave, waves_per_workgroup, resident_workgroups; };
 constexpr LaunchShape kDefaultShape[2] = {{4, 2, 1, 10}, {8, 2, 4, 3}};
 constexpr LaunchShape kMediumF32Shape = {4, 2, 2, 5};                         // below kMediumLayout coordinates

@@ -161,16 +161,18 @@ template <typename T> __host__ __device__ __forceinline__ T ld_stream(const void
 }
 
 // How a step's stores and gradient loads pass the caches (states are always loaded with the hint):
-//   kThrough  stores carry the hint and go through to memory, so that no line stays in the L2 to be written back between the reads of others;
-//             the gradient is loaded without the hint.  Large layouts.  (On one workspace, hint on all accesses -> stores through -> the gradient
-//             without the hint: 3.5 G coordinates bf16 12.79 -> 12.60 -> 12.22 ms, 1.3 G fp32 5.76 -> 5.67 -> 5.67, bf16 4.83 -> 4.73 -> 4.56,
-//             60 M bf16 at odd offsets 216 -> 212 -> 202 us.)
-//   kKept     stores go through to memory without the hint and stay in the memory-side cache.  Layouts whose states fill half of it at most.
+//   kThrough  stores carry the hint and go through to memory, so that no line stays in the L2 to be written back between the
+//             reads of others; the gradient is loaded without the hint.  Large layouts.  (On one workspace, hint on all accesses ->
+//             stores through -> the gradient without the hint: 3.5 G coordinates bf16 12.79 -> 12.60 -> 12.22 ms, 1.3 G fp32 5.76 ->
+//             5.67 -> 5.67, bf16 4.83 -> 4.73 -> 4.56, 60 M bf16 at odd offsets 216 -> 212 -> 202 us.)
+//   kKept     stores go through to memory without the hint and stay in the memory-side cache.  Layouts whose states fill half of it
+//             at most.
 //   kHinted   the hint on all accesses, stores wait in the L2.  fp32 layouts between kSmallLayout and kHintedLayout.
-// us a step, kThrough and kKept: fp32 2 M coordinates 14.1 and 13.0, 8 M 39.6 and 38.4, 17 M 77 and 76, 25 M 108 and 124; bf16 2 M 12.8 and 11.5, 8 M
-// 33.3 and 30.9, 17 M 62 and 59, 25 M 88 and 94.  (In a training step other kernels pass between two of these, so the line lies below
-// the 170 to 200 MB where kKept begins to lose here.)  kThrough and kHinted, each with its best workgroups, fp32: 34 M 147 to 159 and 152 to
-// 161, 42 M 189 to 198 and 185 to 192, 48 M 214 to 236 and 211 to 234, 55 M 245 to 253 and 245 to 255, 62 M 277 to 286 and 279 to 291.
+// us a step, kThrough and kKept: fp32 2 M coordinates 14.1 and 13.0, 8 M 39.6 and 38.4, 17 M 77 and 76, 25 M 108 and 124; bf16 2 M 12.8
+// and 11.5, 8 M 33.3 and 30.9, 17 M 62 and 59, 25 M 88 and 94.  (In a training step other kernels pass between two of these, so the line
+// lies below the 170 to 200 MB where kKept begins to lose here.)  kThrough and kHinted, each with its best workgroups, fp32: 34 M 147 to
+// 159 and 152 to 161, 42 M 189 to 198 and 185 to 192, 48 M 214 to 236 and 211 to 234, 55 M 245 to 253 and 245 to 255, 62 M 277 to 286
+// and 279 to 291.
 enum Memory : int { kThrough, kKept, kHinted };
 constexpr uint64_t kKeptBytes = 128ull << 20;             // of states
 template <int MEM> constexpr int kStoreBits = MEM == kThrough ? 2 | 16 : MEM == kKept ? 16 : 2;   // nt = 2, sc1 = 16
@@ -504,19 +506,17 @@ __global__ __launch_bounds__(64 * NW) void k_step(
     }
 }
 
-// Per-block sums of the partial rows, in fp64.  A block of more than kDirectRows rows is summed in parts first
-// (k_reduce_parts, one workgroup each); k_reduce adds a block's rows, or the sums of its parts, and folds the
-// step into the block's record.
-// Bound by latency: a chain of descriptor load, row loads and reduction, and for the largest layouts by the
-// rows themselves (64 B for every 256 coordinates of a large fp32 layout).  A lane reads 16 bytes of a row, a
-// wavefront 1 KB at a time, a workgroup 32 KB per round; the 64 row slots of a sum meet in two exchange
-// levels and one trip through LDS.  Measured (16 LDS trees of eight barriers and parts of 4,096 rows before): 32,768
-// coordinates 14.3 -> 3.0 us.  Both launches: 124 M fp32, 486,000 rows, 17 us; 860 M 50 us; 1.3 G 68 us, where the rows, 329 MB, are
-// more than the memory-side cache holds (half as many rows took 30).  One launch in which the
-// last part of a block to arrive folds it was slower where there are many parts (1.3 G with half the rows: 106 us): its
-// release writes back the whole L2 of an XCD for every part.
-// kDirectRows: the second launch costs 4.7 us, about what six rounds take.  (With 6,144 rows and parts of 2,048 k_reduce of 860 M in 686 blocks
-// takes 12.6 us instead of 7.5, a step of 74 M coordinates 340 instead of 333.)
+// Per-block sums of the partial rows, in fp64.  A block of more than kDirectRows rows is summed in parts first (k_reduce_parts,
+// one workgroup each); k_reduce adds a block's rows, or the sums of its parts, and folds the step into the block's record. Bound
+// by latency: a chain of descriptor load, row loads and reduction, and for the largest layouts by the rows themselves (64 B for
+// every 256 coordinates of a large fp32 layout).  A lane reads 16 bytes of a row, a wavefront 1 KB at a time, a workgroup 32 KB
+// per round; the 64 row slots of a sum meet in two exchange levels and one trip through LDS.  Measured (16 LDS trees of eight
+// barriers and parts of 4,096 rows before): 32,768 coordinates 14.3 -> 3.0 us.  Both launches: 124 M fp32, 486,000 rows, 17 us;
+// 860 M 50 us; 1.3 G 68 us, where the rows, 329 MB, are more than the memory-side cache holds (half as many rows took 30).  One
+// launch in which the last part of a block to arrive folds it was slower where there are many parts (1.3 G with half the rows:
+// 106 us): its release writes back the whole L2 of an XCD for every part. kDirectRows: the second launch costs 4.7 us, about what
+// six rounds take.  (With 6,144 rows and parts of 2,048 k_reduce of 860 M in 686 blocks takes 12.6 us instead of 7.5, a step of
+// 74 M coordinates 340 instead of 333.)
 constexpr uint32_t kPartRows = 1024, kDirectRows = 3072;
 
 struct alignas(8) Part { uint32_t block, part; };
@@ -786,10 +786,11 @@ __device__ __forceinline__ void fold_first(const Selection& sel, const TileRow& 
         // mu is the mean of the row means to the last bit of what they are made of: the tiles' row sums, added in fp64
         if (m.rows) rec[R_MU] = total / ((double)m.rows * (double)m.cols);
         rec[R_PSUM] = psum;
-        // Where the keys that carry a selected first digit would fill three quarters of the lists of a whole task, the block goes without
-        // lists: its keys are counted as they come, and the last digit takes another walk over v, which is cheaper from about
-        // there on.  k_final2 raises the flag where a single list overflows.  (39 blocks of 2,405 x 3,443, 20 % of them zero: finalize 2.18 ms with lists that overflow and
-        // a second walk over their tiles, 1.55 with the keys past their end counted at once, 1.32 now; 4,096 x 4,096 1.70, 1.20, 1.02.)
+        // Where the keys that carry a selected first digit would fill three quarters of the lists of a whole task, the block goes
+        // without lists: its keys are counted as they come, and the last digit takes another walk over v, which is cheaper from
+        // about there on.  k_final2 raises the flag where a single list overflows.  (39 blocks of 2,405 x 3,443, 20 % of them
+        // zero: finalize 2.18 ms with lists that overflow and a second walk over their tiles, 1.55 with the keys past their end
+        // counted at once, 1.32 now; 4,096 x 4,096 1.70, 1.20, 1.02.)
         uint64_t keys = 0;
         for (uint32_t t = 0; t < 4; ++t) {
             bool fresh = true;
@@ -874,8 +875,8 @@ constexpr uint32_t kSubRounds = 256 / kRoundRows;     // rounds between two row-
 __device__ __forceinline__ uint32_t scalar_u32(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 __device__ __forceinline__ uint32_t scalar_wave_index() { return scalar_u32(threadIdx.x >> 6); }
 
-// Where a wavefront reads (task_of, tile_part, load_full, load_edge and what they call) is host code as well, for the tests: a read past the parameters
-// shows there against a page without access and would not on the GPU.
+// Where a wavefront reads (task_of, tile_part, load_full, load_edge and what they call) is host code as well, for the tests: a
+// read past the parameters shows there against a page without access and would not on the GPU.
 
 // A wavefront's part of its workgroup's tile.  `wave` must be uniform over the wavefront (callers pass it through
 // readfirstlane), so that the task and every address derived from it live in scalar registers.
@@ -943,7 +944,8 @@ template <typename E> __host__ __device__ __forceinline__ bool whole_lines(const
 // Keeps the compiler from making one load of two that differ in the hint alone.
 __host__ __device__ __forceinline__ void apart() { asm volatile(""); }
 
-// Four elements per lane and quad of a full round (of lanes without a column, some).  The address is a scalar base and a 32-bit lane offset.
+// Four elements per lane and quad of a full round (of lanes without a column, some).  The address is a scalar base and a 32-bit
+// lane offset.
 template <int TT>
 __host__ __device__ __forceinline__ void load_full(typename GradIO<TT>::vec4 (&x)[kQuads], const typename GradIO<TT>::elem* __restrict__ src, bool lines,
                                           const TilePart& t, uint32_t cols, uint32_t i)
@@ -1245,8 +1247,11 @@ __global__ __launch_bounds__(256) void k_fold1(const TileRow* __restrict__ tiles
     else cvec[m.off_c + at] = (float)(s / (double)m.rows);
 }
 
-// Words per wavefront in which matching keys gather: with the histogram 37 KB of LDS, which leaves the four workgroups per CU that the
-// registers allow.
+// Words per wavefront in which matching keys gather: with the histogram 37 KB of LDS, four workgroups per CU.  Where theta is read the
+// registers allow no more (104 to 128).  Without theta (61 to 81 registers) five would fit with 960 words and six with 480, which
+// pays where v has many equal values and costs elsewhere (finalize without theta, us with 1,280, 960 and 480 words: 39 matrices of 2,405 x
+// 3,443 with 20 % zeros 874, 859, 854, without 569, 572, 576; 124 M 251, 250, 250; 500 M of odd shapes 1015, 1019, 1026; 1.3 G 1811,
+// 1830, 1844).
 constexpr uint32_t kStage = 1280;
 
 // The same value, unknown to the compiler: what is cheap to form from it again keeps no register over a loop.
@@ -1301,8 +1306,8 @@ __global__ __launch_bounds__(256, 4) void k_final2(
             load_full<BAOC_GRAD_F32>(nx, src, lines, t, cols, i);
             if (C) load_full<TT>(nt, tsrc, tlines, t, cols, i);
             if (F) {
-                // a scalar base and a 32-bit lane offset that is not kept: as a 64-bit address per lane it makes the registers spill with fp32
-                // theta (finalize of 1.3 G coordinates 2651 -> 2640 us)
+                // a scalar base and a 32-bit lane offset that is not kept: as a 64-bit address per lane it makes the registers
+                // spill with fp32 theta (finalize of 1.3 G coordinates 2651 -> 2640 us)
                 const char* p = reinterpret_cast<const char*>(rr + round_row(t, i));
                 const uint32_t at = again(lane) >> 4 << 2;
 #pragma unroll
@@ -1469,7 +1474,8 @@ __global__ __launch_bounds__(256, 4) void k_final2(
         flush(true);
         if (lane == 0) {
             cand_count[blockIdx.x * 4 + wave] = n_cand;
-            if (n_cand > cap) scan3[block * kArriveStride] = 1u;              // list too short: the last digit of the block takes another walk over v
+            // list too short: the last digit of the block takes another walk over v
+            if (n_cand > cap) scan3[block * kArriveStride] = 1u;
         }
     } else {
         walk_run<TT, C>(v_all, theta, m, m.seg_len, [&](const float x[4], const float th[4], uint32_t n) {
@@ -1627,10 +1633,10 @@ struct baoc_profiler {
     std::vector<double> h_rec;
 };
 
-// Pinned host memory that the last kernel of finalize writes the records to.  A copy to pageable memory is staged by the runtime after the
-// kernels have ended (finalize of 25.6 M coordinates, 41 KB: 135 us with the copy, 125 so; of 32,768 49.6 and 40.5).  Pinning takes longer than that, so buffers
-// are kept for the next handle: at most kPoolBytes in all are ever pinned, in powers of two up to kPoolBuffer; a handle that finds none, and
-// a static one, which allocates nothing, has the copy.
+// Pinned host memory that the last kernel of finalize writes the records to.  A copy to pageable memory is staged by the runtime
+// after the kernels have ended (finalize of 25.6 M coordinates, 41 KB: 135 us with the copy, 125 so; of 32,768 49.6 and 40.5).
+// Pinning takes longer than that, so buffers are kept for the next handle: at most kPoolBytes in all are ever pinned, in powers
+// of two up to kPoolBuffer; a handle that finds none, and a static one, which allocates nothing, has the copy.
 constexpr uint64_t kPoolBytes = 4ull << 20, kPoolBuffer = 1ull << 20, kPoolSmallest = 4096;
 // Objects without destructors: a handle may be ended while the program's own are running.
 struct Pinned { double* p; uint64_t bytes; };
@@ -2105,7 +2111,8 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
     const float* v = f32_at(P.off_v);
     const TileRow* tiles = reinterpret_cast<const TileRow*>(h->ws + P.off_tiles);
     const uint32_t* task_block = u32_at(P.off_task_block);
-    uint32_t *arrived = u32_at(P.off_arrived), *scan3 = arrived + 1, *cand = u32_at(P.off_cand), *cand_count = u32_at(P.off_candcount);   // scan3: a block's flag stands next to its counter
+    uint32_t *arrived = u32_at(P.off_arrived), *scan3 = arrived + 1;         // a block's flag stands next to its counter
+    uint32_t *cand = u32_at(P.off_cand), *cand_count = u32_at(P.off_candcount);
     const uint32_t* multi = u32_at(P.off_multi);
     const uint32_t n_multi = (uint32_t)P.multi.size(), n_fold1 = n_multi + (want_F ? (uint32_t)P.n_fin : 0);
     float *rvec = f32_at(P.off_rvec), *cvec = f32_at(P.off_cvec), *rowpart = f32_at(P.off_rowpart), *colpart = f32_at(P.off_colpart);
