@@ -1897,7 +1897,8 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
             const uint64_t all = (r.numel + kQB - 1) / kQB, per = even_groups(all, g);
             groups += all; rows += (all + per - 1) / per * g;
         }
-        if (rows <= 0x7fffffffull && rows * kNumSums * 4 <= list_bytes && (g == 4 || rows <= groups + groups / 16)) fine = g;
+        // a launch has fewer than 2^32 threads (reached at 17.2 G coordinates)
+        if (rows * 64 <= 0xffffffffull && rows * kNumSums * 4 <= list_bytes && (g == 4 || rows <= groups + groups / 16)) fine = g;
     }
     if (fine) { cut(fine, fine); P.gpw = P.nw = P.slice_groups = 1; P.resident = 16; }
     const uint64_t gsz = prm->grad_dtype == BAOC_GRAD_F32 ? 4 : 2;

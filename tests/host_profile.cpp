@@ -111,6 +111,7 @@ static int check_step(const Plan& P, const char* name)
     }
     CHECK(chunks == P.n_chunks && rows == P.n_prows && part == P.parts.size(), "%s", name);
     CHECK(P.off_step_rows == P.off_partials ? P.off_step_rows + rows * kNumSums * 4 <= P.off_chunks : P.off_step_rows == P.off_cand, "%s", name);
+    CHECK(P.n_prows * 64 * P.nw <= 0xffffffffull, "%s: a launch has fewer than 2^32 threads", name);
     CHECK(P.off_step_rows + rows * kNumSums * 4 <= P.total && P.off_chunks + chunks * sizeof(Chunk) <= P.off_rows, "%s", name);
     return 0;
 }
@@ -127,17 +128,18 @@ static int check_plans()
         CHECK((P.off_step_rows == P.off_cand) == w.in_lists, "%s", w.name);
         return check_step(P, w.name);
     };
-    std::vector<baoc_block> matrices, vectors, tiny, below, edges;
+    std::vector<baoc_block> matrices, vectors, tiny, below, edges, huge;
     add(matrices, 4096, 2048, 9); add(matrices, 2049, 4099); add(matrices, 5, 0, 7);
     add(vectors, (1u << 26) + 5, 0);
     add(tiny, 30, 40, 60000);
     add(below, 4096, 2048, 7);
     for (uint64_t g : {1u, 7u, 8u, 9u, 3064u, 3071u, 3072u, 3073u, 3080u, 4095u, 4097u, 5119u, 6144u, 6145u}) { add(edges, g, 256); add(edges, 1, 0); }
     add(edges, 4096, 8192, 2);
+    add(huge, 65535, 65535, 4); add(huge, 4096, 4096);                      // 17.2 G coordinates, 67.2 M groups
     const baoc_profile_params f32 = params_of(BAOC_GRAD_F32), bf16 = params_of(BAOC_GRAD_BF16);
     baoc_profile_params own = f32;
     own.resident_workgroups = 12;
-    return run(matrices, f32, {"matrices", 0, 1, 1, 8, 16, true}) || run(edges, f32, {"edges", 0, 1, 1, 8, 16, true}) ||
+    return run(matrices, f32, {"matrices", 0, 1, 1, 8, 16, true}) || run(edges, f32, {"edges", 0, 1, 1, 8, 16, true}) || run(huge, f32, {"huge", 0, 2, 1, 2, 10, false}) ||
            run(vectors, f32, {"vectors", 0, 2, 1, 2, 10, false}) || run(tiny, f32, {"tiny", 0, 1, 1, 4, 16, true}) ||
            run(below, f32, {"below", 0, 2, 2, 1, 5, false}) || run(matrices, own, {"own", 0, 2, 1, 2, 12, false}) ||
            run(matrices, bf16, {"bf16", 1, 2, 4, 1, 3, false});
