@@ -1,5 +1,5 @@
-// The host side of the profiler without a GPU: the library's own source, compiled for the host alone, on a HIP runtime that only keeps a
-// record of the calls made to it.  argv[1] names the check; a failed one prints what is wrong and returns 1.
+// The host side of the profiler without a GPU: the library's own source, compiled for the host alone, on a HIP runtime that
+// only keeps a record of the calls made to it.  argv[1] names the check; a failed one prints what is wrong and returns 1.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -37,7 +37,8 @@ void operator delete(void* p) noexcept
 }
 void operator delete(void* p, size_t) noexcept { operator delete(p); }
 
-#define CHECK(cond, ...) do { if (!(cond)) { std::printf("line %d: %s ", __LINE__, #cond); std::printf(__VA_ARGS__); std::printf("\n"); return 1; } } while (0)
+#define CHECK(cond, ...) \
+    do { if (!(cond)) { std::printf("line %d: %s ", __LINE__, #cond); std::printf(__VA_ARGS__); std::printf("\n"); return 1; } } while (0)
 
 // ---------------------------------------------------------------------------
 // the runtime
@@ -106,7 +107,8 @@ static int check_step(const Plan& P, const char* name)
         // what six rounds of a workgroup take is summed in one launch, more in parts of at most 2,047 rows
         const uint32_t n_parts = r.n_prows > kDirectRows ? r.n_prows / kPartRows : 0;
         for (uint32_t q = 0; q < n_parts; ++q, ++part)
-            CHECK(part < P.parts.size() && P.parts[part].block == (uint32_t)(&r - P.rows.data()) && P.parts[part].part == q, "%s: %u rows", name, r.n_prows);
+            CHECK(part < P.parts.size() && P.parts[part].block == (uint32_t)(&r - P.rows.data()) && P.parts[part].part == q, "%s: %u rows", name,
+                  r.n_prows);
         chunks += r.n_chunks; rows += r.n_prows;
     }
     CHECK(chunks == P.n_chunks && rows == P.n_prows && part == P.parts.size(), "%s", name);
@@ -124,7 +126,8 @@ static int check_plans()
     auto run = [&](const std::vector<baoc_block>& l, baoc_profile_params p, Want w) {
         Plan P;
         CHECK(make_plan(l.data(), (uint32_t)l.size(), &p, &P, nullptr) == BAOC_OK, "%s", w.name);
-        CHECK(P.gpw == w.gpw && P.nw == w.nw && P.slices == w.slices && P.resident == w.resident, "%s: %u %u %u %u", w.name, P.gpw, P.nw, P.slices, P.resident);
+        CHECK(P.gpw == w.gpw && P.nw == w.nw && P.slices == w.slices && P.resident == w.resident, "%s: %u %u %u %u", w.name, P.gpw, P.nw,
+              P.slices, P.resident);
         CHECK((P.off_step_rows == P.off_cand) == w.in_lists, "%s", w.name);
         return check_step(P, w.name);
     };
@@ -139,8 +142,8 @@ static int check_plans()
     const baoc_profile_params f32 = params_of(BAOC_GRAD_F32), bf16 = params_of(BAOC_GRAD_BF16);
     baoc_profile_params own = f32;
     own.resident_workgroups = 12;
-    return run(matrices, f32, {"matrices", 0, 1, 1, 8, 16, true}) || run(edges, f32, {"edges", 0, 1, 1, 8, 16, true}) || run(huge, f32, {"huge", 0, 2, 1, 2, 10, false}) ||
-           run(vectors, f32, {"vectors", 0, 2, 1, 2, 10, false}) || run(tiny, f32, {"tiny", 0, 1, 1, 4, 16, true}) ||
+    return run(matrices, f32, {"matrices", 0, 1, 1, 8, 16, true}) || run(edges, f32, {"edges", 0, 1, 1, 8, 16, true}) ||
+           run(huge, f32, {"huge", 0, 2, 1, 2, 10, false}) || run(vectors, f32, {"vectors", 0, 2, 1, 2, 10, false}) || run(tiny, f32, {"tiny", 0, 1, 1, 4, 16, true}) ||
            run(below, f32, {"below", 0, 2, 2, 1, 5, false}) || run(matrices, own, {"own", 0, 2, 1, 2, 12, false}) ||
            run(matrices, bf16, {"bf16", 1, 2, 4, 1, 3, false});
 }
@@ -157,8 +160,8 @@ static baoc_profiler* stepped(const std::vector<baoc_block>& l, void* workspace,
     return baoc_profile_step(h, workspace, l.back().offset + l.back().numel, nullptr) == BAOC_OK ? h : nullptr;
 }
 
-// The last kernel of finalize writes the records to pinned memory.  After an error it may still be in flight: the call waits before it
-// returns, and where waiting fails the buffer goes to no other handle.
+// The last kernel of finalize writes the records to pinned memory.  After an error it may still be in flight: the call waits
+// before it returns, and where waiting fails the buffer goes to no other handle.
 static int check_finalize_error()
 {
     std::vector<baoc_block> l;
@@ -227,8 +230,9 @@ template <typename E> static E* before_wall(uint64_t n)
     return reinterpret_cast<E*>(p + bytes) - n;
 }
 
-// Every load of every lane of a pass over the last block of a layout, in the order of k_final2, by the kernel's own functions.  `behind` elements past
-// the block may be read; the pass is told that `claimed` may.  Counts how often an element is given to a lane that uses it.
+// Every load of every lane of a pass over the last block of a layout, in the order of k_final2, by the kernel's own
+// functions.  `behind` elements past the block may be read; the pass is told that `claimed` may.  Counts how often an element
+// is given to a lane that uses it.
 template <int TT>
 static int read_block(const Plan& P, uint64_t behind, uint64_t claimed)
 {
@@ -283,12 +287,14 @@ template <int TT> static bool hits_wall(const Plan& P, uint64_t behind, uint64_t
     return WIFSIGNALED(status) && WTERMSIG(status) == SIGSEGV;
 }
 
-// The parameters' last block, at any alignment: nothing behind it is read, every element is used once.  v may be read up to three elements past
-// the block.  A pass that is told of three elements more than there are runs into the wall where its last round has all rows and lacks columns.
+// The parameters' last block, at any alignment: nothing behind it is read, every element is used once.  v may be read up to
+// three elements past the block.  A pass that is told of three elements more than there are runs into the wall where its last
+// round has all rows and lacks columns.
 static int check_reads()
 {
-    static const uint32_t shapes[][2] = {{2, 2}, {2, 3}, {3, 5}, {15, 63}, {16, 2}, {17, 2}, {16, 64}, {16, 65}, {32, 63}, {48, 67}, {64, 127}, {64, 128}, {65, 127}, {160, 129},
-                                         {16, 1027}, {16, 2049}, {5, 2049}, {256, 257}, {512, 61}, {513, 66}, {1025, 62}, {129, 4}, {4097, 5}, {130, 256}, {48, 100}};
+    static const uint32_t shapes[][2] = {{2, 2}, {2, 3}, {3, 5}, {15, 63}, {16, 2}, {17, 2}, {16, 64}, {16, 65}, {32, 63}, {48, 67}, {64, 127},
+                                         {64, 128}, {65, 127}, {160, 129}, {16, 1027}, {16, 2049}, {5, 2049}, {256, 257}, {512, 61}, {513, 66},
+                                         {1025, 62}, {129, 4}, {4097, 5}, {130, 256}, {48, 100}};
     for (const auto& shape : shapes)
         for (uint32_t vector : {0u, 1u << 29}) {                             // next to a large block tiles are the largest
             std::vector<baoc_block> l;
@@ -301,7 +307,8 @@ static int check_reads()
             // a lane without a column reads from the last one on, the last lane with one from its own
             const uint32_t rest = shape[1] % 64, past = rest <= 60 ? 3 : 64 - rest;
             if (shape[0] % kRoundRows == 0 && rest != 0)
-                CHECK(hits_wall<BAOC_GRAD_F32>(P, 0, 3) && hits_wall<BAOC_GRAD_BF16>(P, 0, 3) && hits_wall<BAOC_GRAD_F32>(P, past - 1, kAnywhere), "%u x %u", shape[0], shape[1]);
+                CHECK(hits_wall<BAOC_GRAD_F32>(P, 0, 3) && hits_wall<BAOC_GRAD_BF16>(P, 0, 3) && hits_wall<BAOC_GRAD_F32>(P, past - 1, kAnywhere),
+                      "%u x %u", shape[0], shape[1]);
         }
     return 0;
 }
@@ -313,8 +320,8 @@ static int check_memory()
     for (uint32_t dtype : {BAOC_GRAD_F32, BAOC_GRAD_BF16}) {
         const uint64_t most = (128ull << 20) / (dtype == BAOC_GRAD_F32 ? 12 : 10) / kQB * kQB;
         const Memory middle = dtype == BAOC_GRAD_F32 ? kHinted : kThrough;
-        for (const auto& [n, want] : {std::pair<uint64_t, Memory>{1, kKept}, {most, kKept}, {most + 1, kThrough}, {kSmallLayout - 1, kThrough}, {kSmallLayout, middle},
-                                      {kHintedLayout - 1, middle}, {kHintedLayout, kThrough}, {1u << 28, kThrough}}) {
+        for (const auto& [n, want] : {std::pair<uint64_t, Memory>{1, kKept}, {most, kKept}, {most + 1, kThrough},
+                                      {kSmallLayout - 1, kThrough}, {kSmallLayout, middle}, {kHintedLayout - 1, middle}, {kHintedLayout, kThrough}, {1u << 28, kThrough}}) {
             std::vector<baoc_block> l;
             add(l, n, 0);
             const baoc_profile_params p = params_of(dtype);

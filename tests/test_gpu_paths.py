@@ -27,8 +27,10 @@ def _layout(kind, total):
         shapes = [(4096, 2048), (2049, 4099), (1, 0)]
     elif kind == "vectors":
         shapes = [(total // 2 + 1, 0), (300, 70), (1023, 0)]
-    else:      # partial rows (of large fp32 layouts, one per 256 coordinates and up to 7 more) around 3,072, where the second launch begins, and last parts of up to 2,040
-        shapes = [(3064, 256), (3072, 256), (3073, 256), (4088, 256), (4095, 256), (5112, 256), (5119, 256), (6144, 256), (1, 0), (8192, 4096)]
+    else:      # partial rows (of large fp32 layouts, one per 256 coordinates and up to 7 more) around 3,072, where the second
+               # launch begins, and last parts of up to 2,040
+        shapes = [(3064, 256), (3072, 256), (3073, 256), (4088, 256), (4095, 256), (5112, 256), (5119, 256), (6144, 256), (1, 0),
+                  (8192, 4096)]
     out, at, k = [], 0, 0
     while at < total:
         r, c = shapes[k % len(shapes)]; k += 1
@@ -38,7 +40,9 @@ def _layout(kind, total):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("kind,total", [("vectors", 1_000_003), ("matrices", 1 << 23), ("matrices", 1 << 24), ("matrices", (1 << 25) + 1), ("vectors", (1 << 25) + 1), ("matrices", 45_000_001), ("vectors", 60_000_001), ("matrices", (1 << 26) + 1), ("vectors", (1 << 26) + 1), ("edges", (1 << 26) + 1)])
+@pytest.mark.parametrize("kind,total", [
+    ("vectors", 1_000_003), ("matrices", 1 << 23), ("matrices", 1 << 24), ("matrices", (1 << 25) + 1), ("vectors", (1 << 25) + 1),
+    ("matrices", 45_000_001), ("vectors", 60_000_001), ("matrices", (1 << 26) + 1), ("vectors", (1 << 26) + 1), ("edges", (1 << 26) + 1)])
 def test_default_step_shape_of_every_size_against_an_explicit_one(env, dtype, kind, total):
     """States to the bit, statistics up to the order of the partial sums, across a finalize whose lists may stand where the step's rows do."""
     torch, binding = env["torch"], env["binding"]
