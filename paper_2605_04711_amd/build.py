@@ -25,7 +25,7 @@ def is_stale():
     if not os.path.exists(LIB):
         return True
     t = os.path.getmtime(LIB)
-    deps = sources() + [os.path.join(CSRC, "baoc_internal.h"), os.path.join(ROOT, "include", "baoc.h")]
+    deps = sources() + [os.path.join(CSRC, "baoc_internal.h"), os.path.join(CSRC, "baoc_once.h"), os.path.join(ROOT, "include", "baoc.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
 

@@ -38,6 +38,7 @@ enum Sum : int {
 enum Rec : int {
     R_SPP = 16, R_RHO, R_COS, R_NCOS, R_STEPS, R_PSUM, R_CNUM, R_CDEN, R_FRES, R_MU,
     R_ORDER,                             // four order statistics of v
+    R_REDO = R_ORDER + 4,                // the one pass did not settle the block
     kRecDoubles = 32
 };
 

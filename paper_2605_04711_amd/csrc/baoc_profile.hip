@@ -637,6 +637,25 @@ constexpr uint32_t kShift1 = kBits2 + kBits3, kShift2 = kBits3;   // key >> kShi
 constexpr uint32_t kBins1 = 1u << (31 - kShift1), kBins2 = 1u << kBits2, kBins3 = 1u << kBits3;
 static_assert(kBins1 <= kHistWords && 4 * kBins2 <= kHistWords && 4 * kBins3 <= kHistWords, "one first-digit histogram, four of the others");
 
+// A block's share of the pass that reads v once (baoc_once.h).  Offsets count 64-byte units from the vectors r and c on.
+struct alignas(16) OnceRow {
+    uint32_t first_task, first_wide;          // of the tasks of 8 and of those of 16 wavefronts
+    uint32_t n_tasks;                         // 0: the block goes through the passes here
+    uint32_t first_unit;                      // of k_once_select
+    uint32_t geom;                            // lanes_log | strips << 4 | across << 8 | down << 16 | 16 wavefronts << 24
+    uint32_t off_list, list_cap;              // a list per task; its words
+    uint32_t off_cols;                        // [task][column] float2, then the collected keys of both intervals
+};
+
+// Words of a block's arrival line.
+enum Line : uint32_t { L_COUNT, L_SCAN3, L_REDO, L_ARRIVED, L_KEYS, L_BRACKET = 8, L_INV_P0 = 12, L_PREFIX = 16, L_RANK = 20 };
+
+// Whether the one pass has done with a block; `scan3` points at L_SCAN3 of the first block.
+__device__ __forceinline__ bool settled(const OnceRow* once, const uint32_t* scan3, uint32_t block)
+{
+    return once && once[block].n_tasks && !scan3[block * kArriveStride + (L_REDO - L_SCAN3)];
+}
+
 // Tables that begin() leaves on the device, and the clearing of what must start at zero: chunks from the block rows
 // (the owning block by bisection on first_chunk; a block's groups are split evenly over its chunks, whole groups
 // each) and the owning block of every workgroup of the finalize passes and of k_fold1.
@@ -685,7 +704,7 @@ __device__ __forceinline__ Prefixes distinct_prefixes(const uint32_t* __restrict
     for (int j = 0; j < 4; ++j) d.pre[j] = kNoPrefix;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        const uint32_t p = sel_prefix[block * 4 + t];
+        const uint32_t p = sel_prefix[block * kArriveStride + t];
         uint32_t slot = 4;
 #pragma unroll
         for (int j = 3; j >= 0; --j)
@@ -727,7 +746,7 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t x)
     return x;
 }
 
-struct Selection { uint32_t *hist, *prefix, *rank; };     // per block: histogram words; four key prefixes; four ranks within them
+struct Selection { uint32_t *hist, *prefix, *rank; };     // per block: histogram words; four key prefixes and four ranks within them, in its arrival line
 struct Digit { uint32_t bin, rank, count; };              // the bin that holds a rank, the rank inside it, the bin's keys
 
 constexpr uint32_t kBinsPerLane = kBins2 / 64;            // consecutive bins of a lane: 256 lanes cover the first digit, 64 one of the others
@@ -781,7 +800,7 @@ __device__ __forceinline__ void fold_first(const Selection& sel, const TileRow& 
         if (m.rank[t] >= at && m.rank[t] - at < mine) found[t] = bin_of(c, threadIdx.x * kBinsPerLane, at, m.rank[t]);
     for (uint32_t i = 0; i < kBinsPerLane / 4; ++i) reinterpret_cast<uint4*>(hist)[i] = uint4{0u, 0u, 0u, 0u};
     __syncthreads();
-    if (threadIdx.x < 4) { sel.prefix[block * 4 + threadIdx.x] = found[threadIdx.x].bin; sel.rank[block * 4 + threadIdx.x] = found[threadIdx.x].rank; }
+    if (threadIdx.x < 4) { sel.prefix[block * kArriveStride + threadIdx.x] = found[threadIdx.x].bin; sel.rank[block * kArriveStride + threadIdx.x] = found[threadIdx.x].rank; }
     if (threadIdx.x == 0) {
         // mu is the mean of the row means to the last bit of what they are made of: the tiles' row sums, added in fp64
         if (m.rows) rec[R_MU] = total / ((double)m.rows * (double)m.cols);
@@ -808,7 +827,7 @@ template <int PASS, typename L>
 __device__ __forceinline__ void pick_digit(const Selection& sel, uint32_t block, uint32_t* hist, uint32_t lane, uint32_t wave, double* order, L load)
 {
     constexpr uint32_t NB = PASS == 2 ? kBins2 : kBins3, N = NB / 64;
-    const uint32_t id = block * 4 + wave;
+    const uint32_t id = block * kArriveStride + wave;
     const Prefixes d = distinct_prefixes(sel.prefix, block);
     const uint32_t slot = wave == 0 ? d.slot_of[0] : (wave == 1 ? d.slot_of[1] : (wave == 2 ? d.slot_of[2] : d.slot_of[3]));
     const uint32_t rank = sel.rank[id], prefix = sel.prefix[id];
@@ -1166,12 +1185,13 @@ template <bool STRIPS>
 __global__ __launch_bounds__(256, STRIPS ? 4 : 5) void k_final1(
     const float* __restrict__ v_all, const TileRow* __restrict__ tiles, const uint32_t* __restrict__ task_block,
     float* __restrict__ rowpart, float* __restrict__ colpart, float* __restrict__ rvec, float* __restrict__ cvec, double2* __restrict__ taskpart,
-    Selection sel, uint32_t* __restrict__ scan3, double* __restrict__ rec_all, float eps, float eps_low, bool want_p)
+    Selection sel, uint32_t* __restrict__ scan3, double* __restrict__ rec_all, float eps, float eps_low, bool want_p, const OnceRow* __restrict__ once)
 {
     __shared__ alignas(16) uint32_t h[kBins1];
     __shared__ float rowsum[4 * 256];                     // [wavefront][its rows of a sub-segment]
     __shared__ double colsum[4 * 64], sums[8];
     const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index(), block = task_block[blockIdx.x];
+    if (settled(once, scan3, block)) return;
     const TileRow& m = tiles[block];
     double psum = 0.0, total = 0.0;
     if (m.rows) {
@@ -1210,12 +1230,13 @@ __global__ __launch_bounds__(256, STRIPS ? 4 : 5) void k_final1(
 __global__ __launch_bounds__(256) void k_fold1(const TileRow* __restrict__ tiles, const uint32_t* __restrict__ multi, uint32_t n_multi,
                                                const uint32_t* __restrict__ fin_block, const float* __restrict__ rowpart, const float* __restrict__ colpart,
                                                float* __restrict__ rvec, float* __restrict__ cvec, const double2* __restrict__ taskpart,
-                                               Selection sel, uint32_t* __restrict__ scan3, double* __restrict__ rec_all)
+                                               Selection sel, uint32_t* __restrict__ scan3, double* __restrict__ rec_all, const OnceRow* __restrict__ once)
 {
     __shared__ double sh[4][64];
     const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index();
     if (blockIdx.x < n_multi) {
         const uint32_t block = multi[blockIdx.x];
+        if (settled(once, scan3, block)) return;
         const TileRow& m = tiles[block];
         double total = 0.0, psum = 0.0;
         for (uint32_t i = threadIdx.x; i < m.n_tasks; i += 256) {
@@ -1228,6 +1249,7 @@ __global__ __launch_bounds__(256) void k_fold1(const TileRow* __restrict__ tiles
         return;
     }
     const uint32_t unit = blockIdx.x - n_multi;
+    if (settled(once, scan3, fin_block[unit])) return;
     const TileRow& m = tiles[fin_block[unit]];
     const uint32_t local = unit - m.first_fin, row_wgs = m.n_tiles > 1 ? (m.rows + 63) / 64 : 0;
     const bool is_row = local < row_wgs;
@@ -1263,7 +1285,7 @@ __global__ __launch_bounds__(256, 4) void k_final2(
     const float* __restrict__ v_all, const typename GradIO<TT>::elem* __restrict__ theta, uint64_t theta_numel,
     const TileRow* __restrict__ tiles, const uint32_t* __restrict__ task_block, const float* __restrict__ rvec, const float* __restrict__ cvec,
     float4* __restrict__ residpart, Selection sel, uint32_t* cand, uint32_t* __restrict__ cand_count,
-    uint32_t* __restrict__ scan3, double* __restrict__ rec_all, float eps, float eps_low)
+    uint32_t* __restrict__ scan3, double* __restrict__ rec_all, float eps, float eps_low, const OnceRow* __restrict__ once)
 {
     typedef GradIO<TT> IO;
     typedef typename IO::vec4 TV;
@@ -1271,6 +1293,7 @@ __global__ __launch_bounds__(256, 4) void k_final2(
     __shared__ uint32_t staged[4 * kStage];
     __shared__ float red[4][4];
     const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index(), block = task_block[blockIdx.x];
+    if (settled(once, scan3, block)) return;
     const TileRow& m = tiles[block];
     const Prefixes d = distinct_prefixes(sel.prefix, block);
     const double* rec_in = rec_all + (uint64_t)block * kRecDoubles;
@@ -1509,10 +1532,11 @@ __global__ __launch_bounds__(256, 4) void k_final2(
 
 // Between the last two passes, for blocks of several tasks: second digit of the ranks, sums of Eq. 7 and Eq. 6.
 __global__ __launch_bounds__(256) void k_fold2(const TileRow* __restrict__ tiles, const uint32_t* __restrict__ multi, const float4* __restrict__ residpart,
-                                               Selection sel, double* __restrict__ rec_all)
+                                               Selection sel, const uint32_t* __restrict__ scan3, double* __restrict__ rec_all, const OnceRow* __restrict__ once)
 {
     __shared__ double sh[3][4];
     const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index(), block = multi[blockIdx.x];
+    if (settled(once, scan3, block)) return;
     const TileRow& m = tiles[block];
     double* rec = rec_all + (uint64_t)block * kRecDoubles;
     double res = 0.0, cn = 0.0, cd = 0.0;
@@ -1531,10 +1555,12 @@ __global__ __launch_bounds__(256) void k_fold2(const TileRow* __restrict__ tiles
 // overflowed.  Leaves the records in `out_all`, host memory or the records themselves.
 __global__ __launch_bounds__(256) void k_final3(
     const float* __restrict__ v_all, const TileRow* __restrict__ tiles, const uint32_t* __restrict__ task_block, const uint32_t* __restrict__ cand,
-    const uint32_t* __restrict__ cand_count, Selection sel, uint32_t* __restrict__ arrived, const uint32_t* __restrict__ scan3, const double* __restrict__ rec_all, double* __restrict__ out_all)
+    const uint32_t* __restrict__ cand_count, Selection sel, uint32_t* __restrict__ arrived, const uint32_t* __restrict__ scan3, const double* __restrict__ rec_all, double* __restrict__ out_all,
+    const OnceRow* __restrict__ once)
 {
     __shared__ alignas(16) uint32_t h[4 * kBins3];
     const uint32_t lane = threadIdx.x & 63u, wave = scalar_wave_index(), block = task_block[blockIdx.x];
+    if (settled(once, scan3, block)) return;
     const TileRow& m = tiles[block];
     for (uint32_t i = threadIdx.x; i < 4 * kBins3; i += 256) h[i] = 0;
     const Prefixes d = distinct_prefixes(sel.prefix, block);
@@ -1583,6 +1609,8 @@ __global__ __launch_bounds__(256) void k_final3(
 
 }  // namespace baoc
 
+#include "baoc_once.h"
+
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
@@ -1610,11 +1638,17 @@ struct Plan {
     uint64_t n_tasks = 0, n_fin = 0;   // workgroups of the finalize passes; those of k_fold1 that fold row and column sums
     std::vector<Part> parts;      // of blocks of more than kDirectRows partial rows
     std::vector<uint32_t> multi;  // blocks of several tasks
+    std::vector<OnceRow> once;    // every block's share of the one pass
+    uint32_t once_tasks = 0, once_narrow = 0;   // its workgroups, and those of 8 wavefronts among them; 0: the layout goes through the passes
+    uint32_t once_units = 0, once_multi = 0;    // workgroups of k_once_select; blocks of several tasks
+    bool once_all = false;        // every block takes it
+    bool once_lines = true;       // rows are whole cache lines
+    uint64_t off_once_sums = 0, off_once_units = 0;
     uint64_t padded = 0;          // coordinates in m / v / g_prev
     uint64_t off_m = 0, off_v = 0, off_gp = 0, off_partials = 0, off_step_rows = 0, off_chunks = 0;   // the step's rows stand at off_step_rows
-    uint64_t off_rows = 0, off_tiles = 0, off_parts = 0, off_multi = 0, off_task_block = 0, off_fin_block = 0;   // the first four are uploaded in one piece
-    uint64_t off_rec = 0, off_hist = 0, off_arrived = 0, off_selp = 0;                            // cleared up to off_selp
-    uint64_t off_selr = 0, off_rvec = 0, off_cvec = 0, off_residpart = 0, off_candcount = 0,
+    uint64_t off_rows = 0, off_tiles = 0, off_parts = 0, off_multi = 0, off_once = 0, off_task_block = 0, off_fin_block = 0;   // the first five are uploaded in one piece
+    uint64_t off_rec = 0, off_hist = 0, off_arrived = 0, off_cleared = 0;                         // cleared up to off_cleared
+    uint64_t off_rvec = 0, off_cvec = 0, off_residpart = 0, off_candcount = 0,
              off_cand = 0, off_rowpart = 0, off_colpart = 0, total = 0;
 };
 
@@ -1721,6 +1755,94 @@ static uint64_t even_groups(uint64_t groups, uint32_t most)
 {
     const uint64_t chunks = (groups + most - 1) / most;
     return (groups + chunks - 1) / chunks;
+}
+
+// The blocks' shares of the one pass, in the memory that the passes have for r, c and the candidate lists.  A block takes part where a
+// workgroup's wavefronts hold a whole row of it: up to 6,144 columns with 8 wavefronts, 12,288 with 16; and up to 2^28 coordinates, where a bin
+// still has fewer keys than can be ordered.  A layout takes part where these blocks have kOnceSmallest coordinates and no others are there, or
+// kOnceSmallestPart next to others, which go through the passes: a sample, a workgroup's start and end (25 us) and the selection cost
+// more than a second read where there is little to read.  Whole finalize, us, passes and one pass: 25.6 M 127 and 172, 124 M (148 blocks) 305 and 330,
+// 134 M (8 blocks) 292 and 254, 178 M 410 and 375, 252 M (15 blocks) 496 and 379, (240 blocks) 530 and 444, 503 M 904 and 658, 1.3 G 2670 and
+// 2110, 3.5 G 5700 and 4450.  Next to others: 26 M of 150 M 325 and 398, 229 M of 252 M 715 and 766, 319 M of 430 M 1061 and 1081, 371 M of 436 M 1196
+// and 1125, 430 M of 851 M 1498 and 1206.
+constexpr uint64_t kOnceSmallest = 1ull << 27, kOnceSmallestPart = 3ull << 27;
+constexpr uint64_t kOnceBlock = 1ull << 28;
+constexpr uint64_t kOnceSingle = 65536;                   // coordinates that one workgroup reads again for its quantiles, from the L2
+constexpr uint32_t kOnceColumns = 768;                    // per wavefront
+static void plan_once(Plan& P, uint64_t total)
+{
+    const uint32_t n = (uint32_t)P.tiles.size();
+    P.once.assign(n, OnceRow{});
+    P.once_tasks = 0;
+    if (total < kOnceSmallest) return;
+    const uint64_t room = (P.total - P.off_rvec) / 64;                         // 64-byte units
+    auto units64 = [](uint64_t bytes) { return (bytes + 63) / 64; };
+    for (uint64_t share = std::min<uint64_t>(1u << 19, std::max<uint64_t>(1u << 14, total / 1024)); share <= 4 << 20; share *= 2) {
+        double listed = 0.0;
+        uint64_t narrow = 0, wide = 0, columns = 0, at = 0, multi = 0, part = 0, taking = 0, broken = 0, aligned = 0;
+        for (uint32_t i = 0; i < n; ++i) {
+            const TileRow& m = P.tiles[i];
+            OnceRow& o = P.once[i];
+            o = OnceRow{};
+            o.first_task = (uint32_t)narrow; o.first_wide = (uint32_t)wide;
+            if (m.numel > kOnceBlock || m.numel < 4 || (m.rows && (m.cols < 4 || m.cols > 16 * kOnceColumns))) continue;
+            ++part; taking += m.numel;
+            const uint32_t waves = m.rows && m.cols > 8 * kOnceColumns ? 16 : 8;
+            uint64_t most = (m.numel + waves * 1024 - 1) / (waves * 1024);      // batches or rounds
+            if (m.rows) {
+                ((m.state_start | m.cols | m.grad_start) & 63u ? broken : aligned) += m.numel;
+                // lanes of a row in a load, strips of a wavefront, wavefronts side by side: as few lanes without columns, wavefronts
+                // without rows and batches without work as possible
+                double best = 0.0;
+                for (uint32_t lanes_log = m.rows >= 4 ? 4 : m.rows >= 2 ? 5 : 6; lanes_log <= 6; ++lanes_log)
+                    for (uint32_t strips = 1; strips <= 3; ++strips) {
+                        const uint32_t width = 4u << lanes_log, across = (uint32_t)((m.cols + (uint64_t)width * strips - 1) / (width * strips));
+                        if (across > waves) continue;
+                        const uint32_t down = waves / across, loads = strips == 1 ? 4 : strips == 2 ? 2 : 1, batch = down * (loads << (6 - lanes_log));
+                        const double use = (double)m.cols / ((double)across * strips * width) * (across * down) / waves * m.rows / (double)align_up(m.rows, batch)
+                                           * (across == 1 ? 1.1 : 1.0) * (strips == 1 ? 1.02 : 1.0) * (lanes_log == 6 ? 1.03 : 1.0);
+                        if (use <= best) continue;
+                        best = use;
+                        o.geom = lanes_log | strips << 4 | across << 8 | down << 16 | (waves == 16 ? 1u << 24 : 0u);
+                        most = (m.rows + batch - 1) / batch;
+                    }
+            }
+            o.n_tasks = m.numel <= kOnceSingle && waves == 8 ? 1 : (uint32_t)std::max<uint64_t>(2, std::min(most, (m.numel + share / 2) / share));
+            (waves == 16 ? wide : narrow) += o.n_tasks;
+            if (o.n_tasks == 1) continue;
+            ++multi;
+            columns += once_col_units(m.rows, m.cols);
+            listed += listed_share(m.numel) * (double)m.numel;
+            o.off_cols = (uint32_t)at;
+            at += once_cols_units(o.n_tasks, m.rows ? m.cols : 0) + units64(once_keys_cap(m.numel) * 8);
+        }
+        // the lists have room for 1.2 to 1.5 times what is expected on them
+        const uint64_t tasks = narrow + wide, units_at = at + units64(tasks * sizeof(OnceSums)), most_units = columns + tasks + (uint64_t)(listed / 2048.0) + multi;
+        const uint64_t lists_at = units_at + units64(most_units * sizeof(OnceUnit));
+        if (taking < (part == n ? kOnceSmallest : kOnceSmallestPart) || tasks > 0x7fffffffull || most_units > 0x7fffffffull) return;
+        if (lists_at + tasks > room || (double)(room - lists_at - tasks) * 16.0 < 1.2 * listed) continue;
+        const double words = multi ? std::min(1.5, (double)(room - lists_at - tasks) * 16.0 / listed) : 0.0;
+        P.off_once_sums = P.off_rvec + at * 64; P.off_once_units = P.off_rvec + units_at * 64;
+        at = lists_at;
+        for (uint32_t i = 0; i < n; ++i) {
+            OnceRow& o = P.once[i];
+            if (o.n_tasks < 2) continue;
+            const TileRow& m = P.tiles[i];
+            o.off_list = (uint32_t)at;
+            o.list_cap = (uint32_t)(words * listed_share(m.numel) * (double)m.numel / o.n_tasks) / 16 * 16;
+            at += (uint64_t)o.n_tasks * o.list_cap / 16;
+        }
+        uint64_t units = 0;
+        for (uint32_t i = 0; i < n; ++i) {
+            OnceRow& o = P.once[i];
+            o.first_unit = (uint32_t)units;
+            if (o.n_tasks > 1) units += once_list_units(o.n_tasks, o.list_cap) + once_col_units(P.tiles[i].rows, P.tiles[i].cols);
+        }
+        if (at > room || units > most_units) return;
+        P.once_narrow = (uint32_t)narrow; P.once_units = (uint32_t)units; P.once_multi = (uint32_t)multi; P.once_all = part == n;
+        P.once_tasks = (uint32_t)tasks; P.once_lines = broken <= aligned;
+        return;
+    }
 }
 
 static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_params* prm, Plan* out, uint64_t* max_end)
@@ -1913,13 +2035,13 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     place(P.off_tiles, (uint64_t)n * sizeof(TileRow));
     place(P.off_parts, P.parts.size() * sizeof(Part));
     place(P.off_multi, P.multi.size() * 4);
+    place(P.off_once, (uint64_t)n * sizeof(OnceRow));
     place(P.off_task_block, P.n_tasks * 4);
     place(P.off_fin_block, P.n_fin * 4);
     place(P.off_rec, (uint64_t)n * kRecDoubles * 8);
     place(P.off_hist, (uint64_t)n * kHistWords * 4);
     place(P.off_arrived, (uint64_t)n * kArriveStride * 4);
-    place(P.off_selp, (uint64_t)n * 4 * 4);
-    place(P.off_selr, (uint64_t)n * 4 * 4);
+    P.off_cleared = o;
     place(P.off_rvec, n_r * 4);
     place(P.off_cvec, n_c * 4);
     // The partial rows of the step are free in finalize.  The first pass's sums per task are folded before the second
@@ -1930,6 +2052,7 @@ static int make_plan(const baoc_block* blocks, uint32_t n, const baoc_profile_pa
     P.off_cand = o; P.off_rowpart = o; P.off_colpart = align_up(o + n_rowpart * 4, 256);
     P.total = o + list_bytes;
     P.off_step_rows = fine ? P.off_cand : P.off_partials;
+    plan_once(P, total);
     return BAOC_OK;
 }
 
@@ -1996,9 +2119,10 @@ static int begin_on(const baoc_block* blocks, uint32_t n_blocks, const baoc_prof
     std::memcpy(tables.data() + (P.off_tiles - P.off_rows), P.tiles.data(), P.tiles.size() * sizeof(TileRow));
     if (!P.parts.empty()) std::memcpy(tables.data() + (P.off_parts - P.off_rows), P.parts.data(), P.parts.size() * sizeof(Part));
     if (!P.multi.empty()) std::memcpy(tables.data() + (P.off_multi - P.off_rows), P.multi.data(), P.multi.size() * 4);
+    std::memcpy(tables.data() + (P.off_once - P.off_rows), P.once.data(), P.once.size() * sizeof(OnceRow));
     hipError_t e = hipMemcpy(h->ws + P.off_rows, tables.data(), tables.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) {
-        const uint64_t n_clear = (P.off_selp - P.off_rec) / 16, work = std::max({P.n_chunks, P.n_tasks, P.n_fin, n_clear});
+        const uint64_t n_clear = (P.off_cleared - P.off_rec) / 16, work = std::max({P.n_chunks, P.n_tasks, P.n_fin, n_clear});
         hipLaunchKernelGGL(k_build, dim3((uint32_t)std::min<uint64_t>((work + 255) / 256, 8192)), dim3(256), 0, nullptr,
                            reinterpret_cast<const BlockRow*>(h->ws + P.off_rows), reinterpret_cast<const TileRow*>(h->ws + P.off_tiles), n_blocks,
                            reinterpret_cast<Chunk*>(h->ws + P.off_chunks), (uint32_t)P.n_chunks,
@@ -2112,7 +2236,7 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
     const float* v = f32_at(P.off_v);
     const TileRow* tiles = reinterpret_cast<const TileRow*>(h->ws + P.off_tiles);
     const uint32_t* task_block = u32_at(P.off_task_block);
-    uint32_t *arrived = u32_at(P.off_arrived), *scan3 = arrived + 1;         // a block's flag stands next to its counter
+    uint32_t *arrived = u32_at(P.off_arrived), *scan3 = arrived + L_SCAN3;   // a block's flag stands next to its counter
     uint32_t *cand = u32_at(P.off_cand), *cand_count = u32_at(P.off_candcount);
     const uint32_t* multi = u32_at(P.off_multi);
     const uint32_t n_multi = (uint32_t)P.multi.size(), n_fold1 = n_multi + (want_F ? (uint32_t)P.n_fin : 0);
@@ -2120,44 +2244,82 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
     double2* taskpart = reinterpret_cast<double2*>(h->ws + P.off_residpart);
     float4* residpart = reinterpret_cast<float4*>(h->ws + P.off_residpart);
     double* rec = reinterpret_cast<double*>(h->ws + P.off_rec);
-    const Selection sel{u32_at(P.off_hist), u32_at(P.off_selp), u32_at(P.off_selr)};
+    const Selection sel{u32_at(P.off_hist), arrived + L_PREFIX, arrived + L_RANK};
     const float epsf = (float)h->params.eps;
     // v above which eps stays below a thousandth of sqrt(v) (and v is a normal number)
     const float eps_low = std::max(std::numeric_limits<float>::min(), (float)(1e6 * h->params.eps * h->params.eps));
 
-    hipLaunchKernelGGL(P.any_strips ? k_final1<true> : k_final1<false>, dim3(n_tasks), dim3(256), 0, st, v, tiles, task_block, rowpart, colpart,
-                       rvec, cvec, taskpart, sel, scan3, rec, epsf, eps_low, want_C);
-    if (n_fold1)
-        hipLaunchKernelGGL(k_fold1, dim3(n_fold1), dim3(256), 0, st, tiles, multi, n_multi, u32_at(P.off_fin_block), rowpart, colpart, rvec, cvec,
-                           taskpart, sel, scan3, rec);
-    auto final2 = [&](auto tt, auto f, auto c) {
-        constexpr int TT = decltype(tt)::value;
-        constexpr bool F = decltype(f)::value, C = decltype(c)::value;
-        hipLaunchKernelGGL((P.any_strips ? k_final2<TT, F, C, true> : k_final2<TT, F, C, false>), dim3(n_tasks), dim3(256), 0, st,
-                           v, static_cast<const typename GradIO<TT>::elem*>(rp.d_theta_flat), rp.theta_numel, tiles, task_block, rvec, cvec,
-                           residpart, sel, cand, cand_count, scan3, rec, epsf, eps_low);
-    };
     const std::true_type yes; const std::false_type no;
     const std::integral_constant<int, BAOC_GRAD_F32> t32; const std::integral_constant<int, BAOC_GRAD_BF16> t16;
-    if (!want_C) { if (want_F) final2(t32, yes, no); else final2(t32, no, no); }
-    else if (rp.theta_dtype == BAOC_GRAD_F32) { if (want_F) final2(t32, yes, yes); else final2(t32, no, yes); }
-    else if (want_F) final2(t16, yes, yes);
-    else final2(t16, no, yes);
-    if (n_multi) hipLaunchKernelGGL(k_fold2, dim3(n_multi), dim3(256), 0, st, tiles, multi, residpart, sel, rec);
-    hipLaunchKernelGGL(k_final3, dim3(n_tasks), dim3(256), 0, st, v, tiles, task_block, cand, cand_count, sel, arrived, scan3, rec,
-                       h->host_rec ? h->host_rec : rec);
-
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess && !h->host_rec) e = hipMemcpyAsync(h->h_rec.data(), rec, h->h_rec.size() * 8, hipMemcpyDeviceToHost, st);
-    // after an error too: the kernels are in flight, and the last one writes to host memory
-    const hipError_t waited = hipStreamSynchronize(st);
-    if (waited != hipSuccess) h->host_lost = true;
-    if (e != hipSuccess || waited != hipSuccess) { (void)hipGetLastError(); h->sticky = BAOC_ERR_HIP; return BAOC_ERR_HIP; }
+    auto with_kinds = [&](auto f) {                            // calls f(type of theta, F wanted, C wanted)
+        if (!want_C) { if (want_F) f(t32, yes, no); else f(t32, no, no); }
+        else if (rp.theta_dtype == BAOC_GRAD_F32) { if (want_F) f(t32, yes, yes); else f(t32, no, yes); }
+        else if (want_F) f(t16, yes, yes);
+        else f(t16, no, yes);
+    };
+    double* const out = h->host_rec ? h->host_rec : rec;
+    const OnceRow* once = P.once_tasks ? reinterpret_cast<const OnceRow*>(h->ws + P.off_once) : nullptr;
+    auto one_pass = [&]() {
+        const OnceMem mem{h->ws + P.off_rvec, reinterpret_cast<OnceSums*>(h->ws + P.off_once_sums), reinterpret_cast<OnceUnit*>(h->ws + P.off_once_units),
+                          once, N, P.once_narrow, arrived, sel.hist, rec, out};
+        if (P.once_multi) hipLaunchKernelGGL(k_bracket, dim3(N), dim3(1024), 0, st, v, tiles, mem, epsf);
+        with_kinds([&](auto tt, auto f, auto c) {
+            constexpr int TT = decltype(tt)::value;
+            constexpr bool F = decltype(f)::value, C = decltype(c)::value;
+            auto pass = [&](auto waves, uint32_t tasks) {
+                constexpr uint32_t NW = decltype(waves)::value;
+                if (tasks)
+                    hipLaunchKernelGGL((P.once_lines ? k_once<NW, TT, F, C, true> : k_once<NW, TT, F, C, false>), dim3(tasks), dim3(64 * NW), 0, st,
+                                       v, static_cast<const typename GradIO<TT>::elem*>(rp.d_theta_flat), tiles, mem, epsf, eps_low);
+            };
+            pass(std::integral_constant<uint32_t, 16>(), P.once_tasks - P.once_narrow);
+            pass(std::integral_constant<uint32_t, 8>(), P.once_narrow);
+            if (P.once_units) hipLaunchKernelGGL((k_once_select<F, C>), dim3(P.once_units), dim3(256), 0, st, tiles, mem);
+        });
+    };
+    auto passes = [&]() {
+        hipLaunchKernelGGL(P.any_strips ? k_final1<true> : k_final1<false>, dim3(n_tasks), dim3(256), 0, st, v, tiles, task_block, rowpart, colpart,
+                           rvec, cvec, taskpart, sel, scan3, rec, epsf, eps_low, want_C, once);
+        if (n_fold1)
+            hipLaunchKernelGGL(k_fold1, dim3(n_fold1), dim3(256), 0, st, tiles, multi, n_multi, u32_at(P.off_fin_block), rowpart, colpart, rvec, cvec,
+                               taskpart, sel, scan3, rec, once);
+        with_kinds([&](auto tt, auto f, auto c) {
+            constexpr int TT = decltype(tt)::value;
+            constexpr bool F = decltype(f)::value, C = decltype(c)::value;
+            hipLaunchKernelGGL((P.any_strips ? k_final2<TT, F, C, true> : k_final2<TT, F, C, false>), dim3(n_tasks), dim3(256), 0, st,
+                               v, static_cast<const typename GradIO<TT>::elem*>(rp.d_theta_flat), rp.theta_numel, tiles, task_block, rvec, cvec,
+                               residpart, sel, cand, cand_count, scan3, rec, epsf, eps_low, once);
+        });
+        if (n_multi) hipLaunchKernelGGL(k_fold2, dim3(n_multi), dim3(256), 0, st, tiles, multi, residpart, sel, scan3, rec, once);
+        hipLaunchKernelGGL(k_final3, dim3(n_tasks), dim3(256), 0, st, v, tiles, task_block, cand, cand_count, sel, arrived, scan3, rec, out, once);
+    };
+    // Waits for the records.  After an error too: the kernels are in flight, and the last one writes to host memory.
+    auto wait = [&]() {
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess && !h->host_rec) e = hipMemcpyAsync(h->h_rec.data(), rec, h->h_rec.size() * 8, hipMemcpyDeviceToHost, st);
+        const hipError_t waited = hipStreamSynchronize(st);
+        if (waited != hipSuccess) h->host_lost = true;
+        if (e == hipSuccess && waited == hipSuccess) return true;
+        (void)hipGetLastError(); h->sticky = BAOC_ERR_HIP;
+        return false;
+    };
+    const double* host = h->host_rec ? h->host_rec : h->h_rec.data();
+    if (once) one_pass();
+    if (!once || !P.once_all) passes();                       // and what the one pass left
+    if (!wait()) return BAOC_ERR_HIP;
+    if (once && P.once_all) {
+        bool redo = false;
+        for (uint32_t i = 0; i < N; ++i) redo |= host[(size_t)i * kRecDoubles + R_REDO] != 0.0;
+        if (redo) {
+            passes();
+            if (!wait()) return BAOC_ERR_HIP;
+        }
+    }
 
     std::vector<baoc_block_stats> stats(N);
     for (uint32_t i = 0; i < N; ++i) {
         RawBlock r;
-        const double* rec = (h->host_rec ? h->host_rec : h->h_rec.data()) + (size_t)i * kRecDoubles;
+        const double* rec = host + (size_t)i * kRecDoubles;
         r.numel = P.rows[i].numel;
         for (int s = 0; s < (int)kNumSums; ++s) r.sums[s] = rec[s];
         r.rho_bar = rec[R_RHO]; r.cos_last = rec[R_COS];

@@ -333,6 +333,84 @@ static int check_memory()
     return 0;
 }
 
+// ---------------------------------------------------------------------------
+// finalize with one read of v
+// ---------------------------------------------------------------------------
+
+// Every element of a block is given to one lane that counts it, and no load leaves its row.
+static int check_once_loads(const OnceRow& o, const TileRow& m)
+{
+    const uint32_t waves = o.geom >> 24 ? 16 : 8, lanes_log = o.geom & 15u, strips = (o.geom >> 4) & 15u, across = (o.geom >> 8) & 255u, down = (o.geom >> 16) & 255u;
+    const uint32_t rpl = 6 - lanes_log, loads = strips == 1 ? 4 : strips == 2 ? 2 : 1, my_rows = loads << rpl, batch = down * my_rows;
+    uint32_t wide = 1;
+    while (wide < across) wide *= 2;
+    CHECK(across * down <= waves && down >= 1 && lanes_log >= 4 && lanes_log <= 6 && strips >= 1 && strips <= 3, "%u x %u", m.rows, m.cols);
+    CHECK((uint64_t)across * strips * (4u << lanes_log) >= m.cols && (1u << rpl) <= m.rows, "%u x %u", m.rows, m.cols);
+    CHECK(across == 1 || down * wide * 16 <= waves * 32, "%u x %u: sums of a batch's rows", m.rows, m.cols);
+    std::vector<uint8_t> used(m.numel, 0);
+    for (uint32_t task = 0; task < o.n_tasks; ++task)
+        for (uint32_t first = task * batch; first < m.rows; first += batch * o.n_tasks)
+            for (uint32_t wave = 0; wave < across * down; ++wave)
+                for (uint32_t q = 0; q < loads; ++q)
+                    for (uint32_t k = 0; k < strips; ++k)
+                        for (uint32_t lane = 0; lane < 64; ++lane) {
+                            const uint32_t row = first + wave / across * my_rows + (q << rpl), lrow = lane >> lanes_log;
+                            const uint32_t col = ((wave % across * strips + k) << (lanes_log + 2)) + 4 * (lane & ((1u << lanes_log) - 1u));
+                            const uint32_t r = once_first_row(row, rpl, m.rows) + lrow, c = once_first_col(col, m.cols);
+                            CHECK(r < m.rows && c + 4 <= m.cols, "%u x %u: row %u, column %u", m.rows, m.cols, r, c);
+                            for (uint32_t e = once_skip(row, lrow, rpl, m.rows, col, m.cols); e < 4; ++e) ++used[(uint64_t)r * m.cols + c + e];
+                        }
+    for (uint64_t i = 0; i < m.numel; ++i) CHECK(used[i] == 1, "%u x %u: element %llu is counted %u times", m.rows, m.cols, (unsigned long long)i, used[i]);
+    return 0;
+}
+
+// Which layouts and blocks take the one pass, and that its memory is what the passes have for r, c and the lists, each part of it apart.
+static int check_once()
+{
+    std::vector<baoc_block> edges, few, small, vectors, many;
+    for (uint32_t c : {2u, 3u, 4u, 5u, 63u, 64u, 65u, 127u, 128u, 129u, 191u, 192u, 193u, 255u, 256u, 257u, 511u, 513u, 767u, 768u, 769u, 1023u, 1025u, 2305u, 4095u,
+                       4097u, 4608u, 6143u, 6144u, 6145u, 11008u, 12287u, 12288u, 12289u, 30000u})
+        for (uint32_t r : {2u, 3u, 5u, 17u, 33u}) add(edges, r, c);
+    add(edges, 1030, 67); add(edges, 300, 2304); add(edges, 41, 11008); add(edges, 700, 100); add(edges, 3, 0); add(edges, 4, 0); add(edges, 65536, 0); add(edges, 65537, 0);
+    few = edges;
+    add(edges, 16384, 8192, 3); add(edges, 16385, 16384);                    // the latter has more than 2^28 coordinates
+    add(few, 16384, 8192, 2);                                                // blocks that do not take part next to fewer than 3 * 2^27
+    add(small, 16384, 8191);                                                 // below 2^27 in all
+    add(vectors, 1u << 28, 0);                                               // no matrix: no room for lists
+    add(many, 1024, 1024, 600); add(many, 4096, 11008, 3); add(many, 50000, 0, 100);
+    for (uint32_t dtype : {BAOC_GRAD_F32, BAOC_GRAD_BF16})
+        for (const auto* l : {&edges, &few, &small, &vectors, &many}) {
+            const baoc_profile_params p = params_of(dtype);
+            Plan P;
+            CHECK(make_plan(l->data(), (uint32_t)l->size(), &p, &P, nullptr) == BAOC_OK, " ");
+            CHECK((P.once_tasks != 0) == (l == &edges || l == &many), "%u tasks", P.once_tasks);
+            if (!P.once_tasks) continue;
+            uint64_t narrow = 0, wide = 0, units = 0, part = 0, fixed = 0, lists = 0, first_list = ~0ull;
+            for (size_t i = 0; i < l->size(); ++i) {
+                const OnceRow& o = P.once[i];
+                const TileRow& m = P.tiles[i];
+                const bool takes = m.numel >= 4 && m.numel <= 1ull << 28 && (!m.rows || (m.cols >= 4 && m.cols <= 12288));
+                CHECK((o.n_tasks != 0) == takes && o.first_task == narrow && o.first_wide == wide && o.first_unit == units, "%u x %u", m.rows, m.cols);
+                if (!takes) continue;
+                ++part;
+                CHECK((o.geom >> 24 != 0) == (m.rows && m.cols > 6144) && (m.numel > 65536 ? o.n_tasks > 1 : o.n_tasks == 1 || o.geom >> 24), "%u x %u", m.rows, m.cols);
+                if (m.rows && m.numel < 1u << 21 && check_once_loads(o, m)) return 1;
+                (o.geom >> 24 ? wide : narrow) += o.n_tasks;
+                if (o.n_tasks == 1) continue;
+                units += once_list_units(o.n_tasks, o.list_cap) + once_col_units(m.rows, m.cols);
+                CHECK(o.off_cols == fixed && o.list_cap % 16 == 0 && o.list_cap > 0, "%u x %u", m.rows, m.cols);
+                fixed += once_cols_units(o.n_tasks, m.rows ? m.cols : 0) + ((uint64_t)once_keys_cap(m.numel) * 8 + 63) / 64;
+                first_list = std::min<uint64_t>(first_list, o.off_list);
+                CHECK(lists == 0 || o.off_list == lists, "%u x %u", m.rows, m.cols);
+                lists = o.off_list + (uint64_t)o.n_tasks * o.list_cap / 16;
+            }
+            CHECK(narrow == P.once_narrow && narrow + wide == P.once_tasks && units == P.once_units && P.once_all == (part == l->size()), " ");
+            CHECK(P.off_rvec + fixed * 64 <= P.off_once_sums && P.off_once_sums + P.once_tasks * sizeof(OnceSums) <= P.off_once_units, " ");
+            CHECK(P.off_once_units + units * sizeof(OnceUnit) <= P.off_rvec + first_list * 64 && P.off_rvec + lists * 64 <= P.total, " ");
+        }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
@@ -341,6 +419,7 @@ int main(int argc, char** argv)
     if (what == "memory") return check_memory();
     if (what == "reads") return check_reads();
     if (what == "end_at_exit") return check_end_at_exit();
+    if (what == "once") return check_once();
     std::printf("no check named '%s'\n", what.c_str());
     return 2;
 }

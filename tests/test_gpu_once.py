@@ -1,0 +1,102 @@
+"""Finalize with one read of v (large layouts): the edges of its geometry against the oracle, large blocks against
+64 bits, and the blocks that it hands on to the passes.  Needs an MI355X."""
+import numpy as np
+import pytest
+
+from oracle.runner import OracleRunner, assert_stats_close, oracle_params
+from test_gpu_parity import env  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+# Columns around a lane's four, a load's 64, 128 and 256, two and three of these, a workgroup of 8 wavefronts (6,144) and of 16 (12,288; more go
+# through the passes); rows around a load's and a batch's; blocks around the largest that one workgroup takes (65,536) and where the sample grows.
+EDGES = [(2, 4), (3, 5), (5, 4), (16, 64), (33, 63), (65, 65), (130, 127), (17, 128), (1030, 67), (64, 1024), (64, 1025), (300, 255), (257, 256), (259, 257),
+         (129, 511), (128, 513), (100, 767), (100, 769), (41, 2305), (23, 4097), (12, 6143), (11, 6144), (10, 6145), (6, 11008), (7, 12287), (3, 12288),
+         (9, 12289), (2, 30000), (5000, 3), (900, 2048), (3, 0), (4, 0), (5, 0), (8191, 0), (65535, 0), (65536, 0), (65537, 0), (524289, 0), (4194305, 0)]
+FILLER = (16384, 8192)
+
+
+def _layout(pad):
+    out, at = [], 0
+    for r, c in EDGES + 3 * [FILLER]:                        # 3 * 2^27 coordinates next to the blocks that do not take part
+        at = -(-at // pad) * pad
+        n = r * c if c else r
+        out.append((at, n, r if c else 0, c)); at += n
+    return out, at
+
+
+@pytest.mark.parametrize("grad,theta,pad", [("f32", "f32", 1), ("bf16", "bf16", 1), ("bf16", "f32", 64), ("f32", "bf16", 64), ("f32", None, 1)])
+def test_edges_of_the_geometry(env, grad, theta, pad):  # noqa: F811
+    torch, binding = env["torch"], env["binding"]
+    blocks, numel = _layout(pad)
+    params = binding.default_profile_params(grad_dtype=1 if grad == "bf16" else 0)
+    prof = binding.Profiler(blocks, params)
+    only = list(range(len(EDGES)))
+
+    class Named:                                             # what OracleRunner asks of a block
+        def __init__(self, b): self.offset, self.numel, self.rows, self.cols = b
+    orc = OracleRunner([Named(b) for b in blocks], only, **oracle_params(params))
+    gen = torch.Generator(device="cuda:0").manual_seed(17)
+    dtype = {"f32": torch.float32, "bf16": torch.bfloat16}
+    scale = torch.randn(numel, device="cuda:0", generator=gen).mul_(0.7).exp_()
+    for _ in range(2):
+        g = torch.randn(numel, device="cuda:0", generator=gen).mul_(scale).mul_(1e-2).to(dtype[grad])
+        prof.step(g)
+        orc.step_from_device(g)
+    th = None if theta is None else (0.02 * torch.randn(numel, device="cuda:0", generator=gen)).to(dtype[theta])
+    stats, _ = prof.finalize(theta=th)
+    again, _ = prof.finalize(theta=th)
+    assert bytes(stats) == bytes(again)
+    want, _ = orc.finalize([], shapes=[b[2:] for b in blocks], theta=th)
+    for i in only:
+        assert_stats_close(stats[i], want[i], f"block {i} {EDGES[i]}")
+    # the large block, against 64 bits: sums of 1.3e8 fp64 terms
+    o, n, r, c = blocks[-1]
+    v = prof.state(len(blocks) - 1)[1].double().view(r, c)
+    row, col = v.mean(1), v.mean(0)
+    F = ((v - row[:, None] * col[None, :] / row.mean()).pow(2).sum().sqrt() / v.pow(2).sum().sqrt()).item()
+    assert abs(stats[len(blocks) - 1].F - F) <= 1e-6 * F
+    if th is not None:
+        p, t = 1.0 / (v.view(-1).sqrt() + 1e-12), th[o:o + n].double()
+        C = (((p / p.mean() - 1.0) * t).pow(2).sum().sqrt() / t.pow(2).sum().sqrt()).item()
+        assert abs(stats[len(blocks) - 1].C - C) <= 1e-6 * C
+    order = v.view(-1).sort().values
+    for got, q in ((stats[len(blocks) - 1].q10, 0.1), (stats[len(blocks) - 1].q90, 0.9)):
+        at = q * (n - 1); lo = int(at)
+        w = order[lo].item() + (at - lo) * (order[lo + 1].item() - order[lo].item())
+        assert abs(got - w) <= 1e-12 * w
+
+
+@pytest.mark.parametrize("kind", ["zeros", "constant", "two values", "nan", "inf", "rank one", "rows apart"])
+def test_blocks_that_the_sample_does_not_settle(env, kind):  # noqa: F811
+    """A block of 1.5 M coordinates, as a matrix and as a vector, next to ordinary ones: untouched coordinates around and well above a tenth,
+    equal keys in an interval, values without order, v of rank one, rows of very different size.  The quantiles are those of v itself; F and C are what
+    a layout below the line, which goes through the passes, has."""
+    torch, binding = env["torch"], env["binding"]
+    r, c = 1500, 1000
+    blocks = [(0, r * c, r, c), (r * c, r * c), (2 * r * c, *[FILLER[0] * FILLER[1], *FILLER])]
+    numel = 2 * r * c + FILLER[0] * FILLER[1]
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    g = torch.randn(numel, device="cuda:0", generator=gen).mul_(1e-2)
+    for k in range(2):
+        b = g[k * r * c:(k + 1) * r * c]
+        hit = torch.rand(r * c, device="cuda:0", generator=gen)
+        if kind == "zeros": b[hit < (0.3, 0.1)[k]] = 0.0
+        if kind == "constant": b.fill_(0.125)
+        if kind == "two values": b.fill_(0.125); b[hit < 0.5] = 0.25
+        if kind == "nan": b[12345] = float("nan")
+        if kind == "inf": b[12345] = float("inf")
+        if kind == "rank one": b.copy_((torch.arange(r, device="cuda:0")[:, None] % 7 + 1.0).mul(torch.arange(c, device="cuda:0")[None, :] % 5 + 1.0).mul(0.25).reshape(-1))
+        if kind == "rows apart": b.view(r, c).mul_(torch.randn(r, 1, device="cuda:0", generator=gen).mul_(3.0).exp_())
+    theta = 0.02 * torch.randn(numel, device="cuda:0", generator=gen)
+    got = binding.Profiler(blocks)
+    ref = binding.Profiler(blocks[:2])                        # 3 M coordinates: the passes
+    got.step(g); ref.step(g[:2 * r * c])
+    a, b = got.finalize(theta=theta)[0], ref.finalize(theta=theta[:2 * r * c])[0]
+    for i in range(2):
+        assert_stats_close(a[i], b[i], f"{kind} {i}")
+        if kind == "rank one":
+            assert (a[0].F <= 1e-6) and abs(a[i].C - b[i].C) <= 1e-6 * b[i].C
+        for f in ("q10", "q90"):
+            assert np.array_equal([getattr(a[i], f)], [getattr(b[i], f)], equal_nan=True)
+    assert bytes(a) == bytes(got.finalize(theta=theta)[0])

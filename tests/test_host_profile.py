@@ -52,6 +52,10 @@ def test_matrix_loads_stay_inside_the_parameters(host_profile):
     host_profile("reads")
 
 
+def test_one_pass_reads_every_coordinate_once_inside_its_rows(host_profile):
+    host_profile("once")
+
+
 def test_no_kernel_spills_registers_or_uses_scratch():
     """The kernels' metadata in the built library: a zero behind every such key."""
     binding.load_library()
