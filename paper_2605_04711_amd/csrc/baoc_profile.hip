@@ -594,6 +594,7 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
 
 // ---------------------------------------------------------------------------
 // Finalize: three passes over the blocks' workgroups, and two small launches between them
+// (large layouts read v once instead, see baoc_once.h, and come here with the blocks that this leaves)
 //   k_final1: first radix digit (Eq. 4); sum of p = 1/(sqrt(v)+eps) (Eq. 6); matrix blocks: mu, row and
 //             column partial sums (Eq. 7)
 //   k_fold1:  first digit of the ranks, sums, r and c, where a block has several workgroups
