@@ -1766,7 +1766,9 @@ static uint64_t even_groups(uint64_t groups, uint32_t most)
 // 134 M (8 blocks) 292 and 254, 178 M 410 and 375, 252 M (15 blocks) 496 and 379, (240 blocks) 530 and 444, 503 M 904 and 658, 1.3 G 2670 and
 // 2110, 3.5 G 5700 and 4450.  Next to others: 26 M of 150 M 325 and 398, 229 M of 252 M 715 and 766, 319 M of 430 M 1061 and 1081, 371 M of 436 M 1196
 // and 1125, 430 M of 851 M 1498 and 1206.
-constexpr uint64_t kOnceSmallest = 1ull << 27, kOnceSmallestPart = 3ull << 27;
+// Layouts of many small blocks keep the passes as well: 2,100 of 65,536 coordinates 472 and 602, 1,000 of 160,000 536 and 658, 300 of 490,000 414
+// and 358, 240 of 1 M 530 and 440.
+constexpr uint64_t kOnceSmallest = 1ull << 27, kOnceSmallestPart = 3ull << 27, kOnceMeanBlock = 3ull << 17;
 constexpr uint64_t kOnceBlock = 1ull << 28;
 constexpr uint64_t kOnceSingle = 65536;                   // coordinates that one workgroup reads again for its quantiles, from the L2
 constexpr uint32_t kOnceColumns = 768;                    // per wavefront
@@ -1820,7 +1822,7 @@ static void plan_once(Plan& P, uint64_t total)
         // the lists have room for 1.2 to 1.5 times what is expected on them
         const uint64_t tasks = narrow + wide, units_at = at + units64(tasks * sizeof(OnceSums)), most_units = columns + tasks + (uint64_t)(listed / 2048.0) + multi;
         const uint64_t lists_at = units_at + units64(most_units * sizeof(OnceUnit));
-        if (taking < (part == n ? kOnceSmallest : kOnceSmallestPart) || tasks > 0x7fffffffull || most_units > 0x7fffffffull) return;
+        if (taking < (part == n ? kOnceSmallest : kOnceSmallestPart) || taking < n * kOnceMeanBlock || tasks > 0x7fffffffull || most_units > 0x7fffffffull) return;
         if (lists_at + tasks > room || (double)(room - lists_at - tasks) * 16.0 < 1.2 * listed) continue;
         const double words = multi ? std::min(1.5, (double)(room - lists_at - tasks) * 16.0 / listed) : 0.0;
         P.off_once_sums = P.off_rvec + at * 64; P.off_once_units = P.off_rvec + units_at * 64;

@@ -367,7 +367,7 @@ static int check_once_loads(const OnceRow& o, const TileRow& m)
 // Which layouts and blocks take the one pass, and that its memory is what the passes have for r, c and the lists, each part of it apart.
 static int check_once()
 {
-    std::vector<baoc_block> edges, few, small, vectors, many;
+    std::vector<baoc_block> edges, few, small, vectors, many, tiny;
     for (uint32_t c : {2u, 3u, 4u, 5u, 63u, 64u, 65u, 127u, 128u, 129u, 191u, 192u, 193u, 255u, 256u, 257u, 511u, 513u, 767u, 768u, 769u, 1023u, 1025u, 2305u, 4095u,
                        4097u, 4608u, 6143u, 6144u, 6145u, 11008u, 12287u, 12288u, 12289u, 30000u})
         for (uint32_t r : {2u, 3u, 5u, 17u, 33u}) add(edges, r, c);
@@ -377,9 +377,10 @@ static int check_once()
     add(few, 16384, 8192, 2);                                                // blocks that do not take part next to fewer than 3 * 2^27
     add(small, 16384, 8191);                                                 // below 2^27 in all
     add(vectors, 1u << 28, 0);                                               // no matrix: no room for lists
+    add(tiny, 600, 500, 1000);                                               // blocks of 300,000 coordinates
     add(many, 1024, 1024, 600); add(many, 4096, 11008, 3); add(many, 50000, 0, 100);
     for (uint32_t dtype : {BAOC_GRAD_F32, BAOC_GRAD_BF16})
-        for (const auto* l : {&edges, &few, &small, &vectors, &many}) {
+        for (const auto* l : {&edges, &few, &small, &vectors, &many, &tiny}) {
             const baoc_profile_params p = params_of(dtype);
             Plan P;
             CHECK(make_plan(l->data(), (uint32_t)l->size(), &p, &P, nullptr) == BAOC_OK, " ");
