@@ -14,7 +14,9 @@ namespace baoc {
 //          interval, a list or a buffer is too short, or a sum is not finite, the block is marked and goes through the passes above.
 //          (Which keys are listed where is not the same from run to run; what is taken from them is, and so is what is marked.)
 //   Eq. 6  With q = p / p0 - 1 for a fixed p0, sum ((p/p-bar - 1) theta)^2 = k^2 sum (q theta)^2 + 2 k (k-1) sum q theta^2 +
-//          (k-1)^2 sum theta^2, k = p0 / p-bar.  Nothing cancels where p0 is a mean of some of the block's p.
+//          (k-1)^2 sum theta^2, k = p0 / p-bar.  For k well above 1 the terms are k^2 times their sum, so a rare large p (v = 0 at a
+//          coordinate or two) must not raise p0: it is the median of the means of 16 parts of the sample, and the mean of all p where one
+//          workgroup has the block.  Where the terms cancel all the same (distortion_cancels) the block is marked.
 //   Eq. 7  |S - r c^T / mu|^2 = |S|^2 - (2/mu) sum_j c_j t_j + |r|^2 |c|^2 / mu^2 with t = S^T r.  A workgroup reads whole rows, so
 //          that r_i is there while the row still is in registers; everything is summed in fp64, products of fp32 numbers being exact
 //          there, since for a rank-one S the three terms cancel.
@@ -193,7 +195,7 @@ __global__ __launch_bounds__(1024) void k_bracket(const float* __restrict__ v_al
     for (uint32_t q = 0; q < 16; ++q) {
         x[q] = f4{0.f, 0.f, 0.f, 0.f};
         if (q < mine) {
-            const uint32_t piece = q * 1024 + threadIdx.x;
+            const uint32_t piece = q * 1024 + lane * 16 + wave;   // a wavefront's lie all over the block
             uint32_t z = (piece + 1) * 0x9E3779B9u;
             z ^= z >> 16; z *= 0x85EBCA6Bu; z ^= z >> 13; z *= 0xC2B2AE35u; z ^= z >> 16;
             uint32_t at = piece * share + (uint32_t)(((uint64_t)z * share) >> 32);
@@ -218,15 +220,22 @@ __global__ __launch_bounds__(1024) void k_bracket(const float* __restrict__ v_al
                 for (uint32_t k = 0; k < 4; ++k) f(__builtin_bit_cast(uint32_t, e[k]) & 0x7fffffffu);
             }
     }, rank, h, sel, sums, lane, wave);
+    uint32_t* line = mem.line + block * kArriveStride;
+    if (threadIdx.x < 16) {
+        // the patterns' order is the values'
+        const uint32_t own = __builtin_bit_cast(uint32_t, sh[threadIdx.x]);
+        uint32_t below = 0;
+        for (uint32_t w = 0; w < 16; ++w) {
+            const uint32_t x = __builtin_bit_cast(uint32_t, sh[w]);
+            below += x < own || (x == own && w < threadIdx.x);
+        }
+        if (below == 7) line[L_INV_P0] = __builtin_bit_cast(uint32_t, 1.0f / fmaxf(sh[threadIdx.x] / (float)(n / 16), kLeastP0));
+    }
     if (threadIdx.x == 0) {
-        double total_p = 0.0;
-        for (uint32_t w = 0; w < 16; ++w) total_p += (double)sh[w];
-        uint32_t* line = mem.line + block * kArriveStride;
         // half open; zeros are below
         const uint32_t b[4] = {max(sel[0] << kBits3, 1u), (sel[1] + 1) << kBits3, max(sel[2] << kBits3, 1u), (sel[3] + 1) << kBits3};
         line[L_REDO] = b[3] > 0x7f800000u || b[1] > b[2];
         for (uint32_t i = 0; i < 4; ++i) line[L_BRACKET + i] = b[i];
-        line[L_INV_P0] = __builtin_bit_cast(uint32_t, 1.0f / fmaxf((float)(total_p / (double)n), kLeastP0));
     }
 }
 
@@ -310,11 +319,19 @@ __device__ __forceinline__ double once_residual(double s2, double cross, double 
     return res < 0.0 ? 0.0 : res;
 }
 
-__device__ __forceinline__ double once_distortion(double a, double b, double d, double q, double numel)
+struct Distortion { double num; bool bad; };
+
+// a, b and d have relative errors of about 1e-7 (groups of up to 256 terms in fp32).  Up to eight times the result the terms leave it within
+// 1e-6; and what is below 1e-7 of d, C below 3e-4, within an error of C of 1e-7, which is that of q.
+__host__ __device__ __forceinline__ bool distortion_cancels(double terms, double num, double d) { return terms > 8.0 * num && terms > 1e-7 * d; }
+
+__host__ __device__ __forceinline__ Distortion once_distortion(double a, double b, double d, double q, double numel)
 {
     const double k = numel / (numel + q);                 // p0 / p-bar
-    const double num = k * k * a + 2.0 * k * (k - 1.0) * b + (k - 1.0) * (k - 1.0) * d;
-    return num < 0.0 && num > -INFINITY ? 0.0 : num;
+    const double ka = k * k * a, kb = 2.0 * k * (k - 1.0) * b, kd = (k - 1.0) * (k - 1.0) * d;
+    const double num = ka + kb + kd;
+    const bool bad = !(fabs(num) < INFINITY) || distortion_cancels(ka + fabs(kb) + kd, num, d);
+    return Distortion{num < 0.0 ? 0.0 : num, bad};
 }
 
 // The pass.  A workgroup of NW wavefronts takes a task: of a matrix every n_tasks-th batch of whole rows, of another block every
@@ -349,7 +366,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
     const TileRow& m = tiles[block];
     const uint32_t n_tasks = scalar_u32(o.n_tasks), local = blockIdx.x - scalar_u32(NW == 8 ? o.first_task : o.first_wide);
     const uint32_t rows = scalar_u32(m.rows), cols = scalar_u32(m.cols);
-    const bool single = n_tasks == 1;
+    const bool single = NW == 8 && n_tasks == 1;              // see plan_once
     uint32_t* line = mem.line + block * kArriveStride;
     const float* src = v_all + m.state_start;
     const E* tsrc = theta + m.grad_start;
@@ -366,8 +383,29 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
         for (int i = 0; i < 2; ++i) shift[i] = once_shift(end[2 * i + 1] - end[2 * i], bins_log);
         inv_p0 = __builtin_bit_cast(float, scalar_u32(line[L_INV_P0]));
     } else if (C) {
-        const float p = wave_sum(preconditioner(src[(uint64_t)m.numel * lane >> 6], eps));
-        inv_p0 = 1.0f / fmaxf(p * (1.0f / 64.0f), kLeastP0);
+        // the mean of all p: the pass below and the quantiles read these lines from the L2
+        const uint32_t numel = (uint32_t)m.numel;
+        double psum = 0.0;
+        for (uint32_t first = tid * 4; first < numel; first += THREADS * 16) {
+            f4 x[4];
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) x[q] = *reinterpret_cast<const f4*>(src + min(first + q * (THREADS * 4), (numel - 1) & ~3u));
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) {
+                const uint32_t at = first + q * (THREADS * 4);
+                const float e[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+                float p = 0.f;
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) p += at + k < numel ? preconditioner(e[k], eps) : 0.f;
+                psum += (double)p;
+            }
+        }
+        psum = wave_total(psum);
+        if (lane == 0) part[wave][0] = psum;
+        __syncthreads();
+        psum = 0.0;
+        for (uint32_t w = 0; w < NW; ++w) psum += part[w][0];
+        inv_p0 = (float)((double)numel / fmax(psum, (double)numel * (double)kLeastP0));
     }
     const float eps_p0 = -eps * inv_p0;
     __syncthreads();
@@ -755,8 +793,8 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
     double* out = mem.out + (uint64_t)block * kRecDoubles;
     if (tid < 32) {
         const double res = F && rows ? once_residual(total[4], total[7], total[9] / (double)cols, total[6], total[8]) : 0.0;
-        const double num = C ? once_distortion(total[1], total[2], total[3], total[0], (double)numel) : 0.0;
-        leave_record(rec, out, res, num, total[3], !(fabs(res) < INFINITY) || !(fabs(num) < INFINITY), line + L_REDO);
+        const Distortion c = C ? once_distortion(total[1], total[2], total[3], total[0], (double)numel) : Distortion{0.0, false};
+        leave_record(rec, out, res, c.num, total[3], !(fabs(res) < INFINITY) || c.bad, line + L_REDO);
         if (tid < 4) out[R_ORDER + tid] = (double)__builtin_bit_cast(float, sel[tid]);
     }
 }
@@ -970,8 +1008,8 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
     __syncthreads();
     if (tid < 32) {
         const double res = F && rows ? once_residual(x[4], x[7], x[9] / (double)cols, x[6], x[8]) : 0.0;
-        const double num = C ? once_distortion(x[1], x[2], x[3], x[0], (double)m.numel) : 0.0;
-        leave_record(rec, out, res, num, x[3], scans[0] != 0 || !(fabs(res) < INFINITY) || !(fabs(num) < INFINITY), line + L_REDO);
+        const Distortion c = C ? once_distortion(x[1], x[2], x[3], x[0], (double)m.numel) : Distortion{0.0, false};
+        leave_record(rec, out, res, c.num, x[3], scans[0] != 0 || !(fabs(res) < INFINITY) || c.bad, line + L_REDO);
     }
     if (tid >= 64 && tid < 66) st_device(line + L_KEYS + (tid - 64), 0u);
     for (uint32_t i = tid; i < 2u << bins_log; i += 256) hist[i] = 0;

@@ -100,3 +100,39 @@ def test_blocks_that_the_sample_does_not_settle(env, kind):  # noqa: F811
         for f in ("q10", "q90"):
             assert np.array_equal([getattr(a[i], f)], [getattr(b[i], f)], equal_nan=True)
     assert bytes(a) == bytes(got.finalize(theta=theta)[0])
+
+
+def _sampled(numel, pieces, piece):
+    """First of the four coordinates that k_bracket reads as a block's `piece`-th piece."""
+    z = (piece + 1) * 0x9E3779B9 & 0xffffffff
+    z ^= z >> 16; z = z * 0x85EBCA6B & 0xffffffff; z ^= z >> 13; z = z * 0xC2B2AE35 & 0xffffffff; z ^= z >> 16
+    share = numel // pieces
+    return min(piece * share + (z * share >> 32), numel - 4) & ~3
+
+
+@pytest.mark.parametrize("theta", ["f32", "bf16"])
+@pytest.mark.parametrize("dead", [1, 4, 200])
+def test_distortion_where_a_rare_p_is_large(env, dead, theta):  # noqa: F811
+    """Coordinates with v = 0 and theta = 0 (a pruned or padded weight), at a block's start, where a block of several workgroups samples v, and
+    over a whole row: p is 1e12 there and 1e2 elsewhere, so that the typical p of a sample that hits one says nothing about p-bar.  C against 64 bits:
+    (p/p-bar - 1)^2 theta^2 and theta^2 are summed from fp32 terms of at most three roundings, which are independent; 1e-6 is eight of them."""
+    torch, binding = env["torch"], env["binding"]
+    shapes = [(65536, 0), (16384, 0), (4096, 0), (256, 256), (64, 64), (3, 1365), (65537, 0), (1500, 1000), (1500000, 0), FILLER]
+    blocks, at = [], 0
+    for r, c in shapes:
+        n = r * c if c else r
+        blocks.append((at, n, r if c else 0, c)); at += n
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    g = torch.rand(at, device="cuda:0", generator=gen).add_(0.5).mul_(0.3)
+    th = (0.02 * torch.randn(at, device="cuda:0", generator=gen)).to({"f32": torch.float32, "bf16": torch.bfloat16}[theta])
+    for o, n, r, c in blocks:
+        pieces = 1024 * (16 if n >= 1 << 27 else 2)
+        for first, count in [(0, c if dead == 200 and c else dead)] + ([(_sampled(n, pieces, 5), min(dead, 4))] if n > 65536 else []):
+            g[o + first:o + first + count] = 0.0; th[o + first:o + first + count] = 0.0
+    prof = binding.Profiler(blocks)
+    prof.step(g)
+    stats = prof.finalize(theta=th)[0]
+    for i, (o, n, _, _) in enumerate(blocks):
+        p, t = 1.0 / (prof.state(i)[1].double().sqrt() + 1e-12), th[o:o + n].double()
+        C = (((p / p.mean() - 1.0) * t).pow(2).sum().sqrt() / t.pow(2).sum().sqrt()).item()
+        assert abs(stats[i].C - C) <= 1e-6 * C, f"{shapes[i]}: {stats[i].C} {C}"
