@@ -10,8 +10,11 @@ namespace baoc {
 //   k_once_select: the order statistics from the keys that lay in the intervals, the sums; leaves the records
 // What the passes above read v twice for, and how it is had from one read:
 //   Eq. 4  The quantiles' first digits are not known in advance, but a sample of 16,384 coordinates places them within 1.2 % of the
-//          ranks: keys inside the two intervals are listed, those below are counted.  Where a rank turns out to lie outside its
-//          interval, a list or a buffer is too short, or a sum is not finite, the block is marked and goes through the passes above.
+//          ranks: keys inside the two intervals are listed, those below are counted.  Equal keys: zeros lie below every interval; an
+//          interval of at most 512 keys is counted key by key and not listed; of more keys in a rank's bins than can be ordered, k_once_select
+//          counts those of 256 to 1,024 cells of the bins, and a cell that holds one value gives the rank.  Where a rank turns out to
+//          lie outside its interval, a list is too short, a crowded cell has several values, or a sum is not finite, the block is marked and goes
+//          through the passes above.
 //          (Which keys are listed where is not the same from run to run; what is taken from them is, and so is what is marked.)
 //   Eq. 6  With q = p / p0 - 1 for a fixed p0, sum ((p/p-bar - 1) theta)^2 = k^2 sum (q theta)^2 + 2 k (k-1) sum q theta^2 +
 //          (k-1)^2 sum theta^2, k = p0 / p-bar.  For k well above 1 the terms are k^2 times their sum, so a rare large p (v = 0 at a
@@ -91,14 +94,38 @@ template <typename Fn> __device__ __forceinline__ uint32_t find_owner(uint32_t n
 }
 
 // An interval of a small block has fewer bins, since every task adds all of its own to the block's: a bin is left with about a hundred keys.
-__device__ __forceinline__ uint32_t once_bins_log(uint32_t numel) { return min(11u, max(7u, 19u - (uint32_t)__builtin_clz(numel))); }
+__host__ __device__ __forceinline__ uint32_t once_bins_log(uint32_t numel) { return min(11u, max(7u, 19u - (uint32_t)__builtin_clz(numel))); }
+__host__ __device__ __forceinline__ uint32_t once_slots_log(uint32_t bins_log) { return max(9u, bins_log); }   // words of an interval in the histogram
 static_assert(kOnceBins == 1u << 11, "once_bins_log");
 
-// Shift that leaves 1 << bins_log bins of an interval of `width` keys.
-__device__ __forceinline__ uint32_t once_shift(uint32_t width, uint32_t bins_log)
+// Shift that leaves 1 << n_log of `width` keys; and that of an interval, none where it has the keys of one prefix of two digits.
+__host__ __device__ __forceinline__ uint32_t width_shift(uint32_t width, uint32_t n_log)
 {
     const uint32_t bits = width > 1 ? 32u - (uint32_t)__builtin_clz(width - 1) : 0u;
-    return bits > bins_log ? bits - bins_log : 0u;
+    return bits > n_log ? bits - n_log : 0u;
+}
+__host__ __device__ __forceinline__ uint32_t once_shift(uint32_t width, uint32_t bins_log) { return width <= 1u << kBits3 ? 0u : width_shift(width, bins_log); }
+
+// Where k_once_select collects a block's keys: those of the lower interval, then those of the upper one.  Of more keys than can be ordered, the
+// range's cells: counts, largest keys and complements of the smallest ones, 1 << once_cells_log() words each.
+__device__ __forceinline__ uint32_t* once_found(const OnceMem& mem, const OnceRow& o, uint32_t cols)
+{
+    return reinterpret_cast<uint32_t*>(mem.base + ((uint64_t)o.off_cols + once_cols_units(o.n_tasks, cols)) * 64);
+}
+__host__ __device__ __forceinline__ uint32_t once_cells_log(uint32_t keys_cap) { return 29u - (uint32_t)__builtin_clz(keys_cap); }
+static_assert(kOnceKeys == 1u << 12, "1,024 cells at most");
+
+// The intervals of a block from the two-digit prefixes at the ends of its quantiles' ranks: [end[0], end[1]) and [end[2], end[3]).  Zeros are
+// below.  Where they overlap most of the block has one prefix; both quantiles then are in one interval, the second is empty, and that interval
+// must leave zeros out or hold one prefix: false if not, or if there are values without order.
+__host__ __device__ __forceinline__ bool once_intervals(const uint32_t (&prefix)[4], uint32_t (&end)[4])
+{
+    end[0] = max(prefix[0] << kBits3, 1u); end[1] = (prefix[1] + 1) << kBits3;
+    end[2] = max(prefix[2] << kBits3, 1u); end[3] = (prefix[3] + 1) << kBits3;
+    if (end[3] > 0x7f800000u) return false;
+    if (end[1] <= end[2]) return true;
+    end[1] = end[2] = end[3];
+    return prefix[2] == 0 || prefix[0] == prefix[3];
 }
 
 // The keys at four ranks of what `walk` hands out, exactly.  h: kHistWords words of LDS; sel: eight words of LDS, of which the first
@@ -176,8 +203,8 @@ __device__ __forceinline__ double wave_total(double x)
 }
 
 // The pieces are drawn one from each of equal shares of the block.  An interval reaches 5 standard deviations of the sample's rank to either
-// side, at the resolution of two digits.  Zeros are left out of it and counted as below: a q10 of a block with untouched coordinates is then known
-// to be 0 however many there are.  Bound by latency (loads, two rounds of counting) up to about 100 blocks, 20 us, then by the lines.
+// side, at the resolution of two digits.  Zeros are left out of it and counted as below: a quantile of a block with untouched coordinates is then
+// known to be 0 however many there are.  Bound by latency (loads, two rounds of counting) up to about 100 blocks, 20 us, then by the lines.
 __global__ __launch_bounds__(1024) void k_bracket(const float* __restrict__ v_all, const TileRow* __restrict__ tiles, OnceMem mem, float eps)
 {
     __shared__ alignas(16) uint32_t h[kHistWords];
@@ -232,11 +259,14 @@ __global__ __launch_bounds__(1024) void k_bracket(const float* __restrict__ v_al
         if (below == 7) line[L_INV_P0] = __builtin_bit_cast(uint32_t, 1.0f / fmaxf(sh[threadIdx.x] / (float)(n / 16), kLeastP0));
     }
     if (threadIdx.x == 0) {
-        // half open; zeros are below
-        const uint32_t b[4] = {max(sel[0] << kBits3, 1u), (sel[1] + 1) << kBits3, max(sel[2] << kBits3, 1u), (sel[3] + 1) << kBits3};
-        line[L_REDO] = b[3] > 0x7f800000u || b[1] > b[2];
-        for (uint32_t i = 0; i < 4; ++i) line[L_BRACKET + i] = b[i];
+        const uint32_t prefix[4] = {sel[0], sel[1], sel[2], sel[3]};
+        uint32_t end[4];
+        line[L_REDO] = !once_intervals(prefix, end);
+        for (uint32_t i = 0; i < 4; ++i) line[L_BRACKET + i] = end[i];
     }
+    const uint32_t keys_cap = once_keys_cap(m.numel), words = 3u << once_cells_log(keys_cap);
+    uint32_t* found = once_found(mem, mem.rows[block], m.rows ? m.cols : 0u);
+    for (uint32_t i = threadIdx.x; i < words; i += 1024) found[i] = found[keys_cap + i] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -371,11 +401,11 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
     const float* src = v_all + m.state_start;
     const E* tsrc = theta + m.grad_start;
     if (tid == 0) n_listed = 0;
-    const uint32_t bins_log = scalar_u32(once_bins_log((uint32_t)m.numel));
+    const uint32_t bins_log = scalar_u32(once_bins_log((uint32_t)m.numel)), slots = 1u << once_slots_log(bins_log);
     uint32_t end[4] = {0, 0, 0, 0}, shift[2] = {0, 0};
     float inv_p0 = 0.f;
     if (!single) {
-        for (uint32_t i = tid; i < 2u << bins_log; i += THREADS) hist[i] = 0;
+        for (uint32_t i = tid; i < 2 * slots; i += THREADS) hist[i] = 0;
         const bool none = scalar_u32(line[L_REDO]) != 0;      // nothing is listed
 #pragma unroll
         for (int i = 0; i < 4; ++i) end[i] = none ? 0u : scalar_u32(line[L_BRACKET + i]);
@@ -426,15 +456,33 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
     uint32_t* list = reinterpret_cast<uint32_t*>(mem.base + (uint64_t)o.off_list * 64) + (uint64_t)local * cap;
     auto flush = [&](bool all) {
         const uint32_t n = all ? n_stage : n_stage & ~63u;
-        uint32_t first = 0;
-        if (lane == 0) first = atomicAdd(&n_listed, n);
-        first = scalar_u32(first);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        for (uint32_t i = lane; i < n; i += 64) {
-            const uint32_t key = stage[i];
-            if (first + i < cap) st_device(&list[first + i], key);
-            const bool high = key >= end[2];
-            atomicAdd(&hist[high ? (1u << bins_log) + ((key - end[2]) >> shift[1]) : (key - end[0]) >> shift[0]], 1u);
+        auto bin_of_key = [&](uint32_t key) { return key >= end[2] ? slots + ((key - end[2]) >> shift[1]) : (key - end[0]) >> shift[0]; };
+        // (next to zeros, or empty, an interval has hardly a key)
+        const bool counted = (shift[0] == 0 && end[0] > 1) || (shift[1] == 0 && end[2] > 1 && end[2] != end[3]);
+        if (!counted) {
+            uint32_t first = 0;
+            if (lane == 0) first = atomicAdd(&n_listed, n);
+            first = scalar_u32(first);
+            for (uint32_t i = lane; i < n; i += 64) {
+                const uint32_t key = stage[i];
+                if (first + i < cap) st_device(&list[first + i], key);
+                atomicAdd(&hist[bin_of_key(key)], 1u);
+            }
+        } else {
+            // An interval that is counted key by key is not listed.  Most keys may be equal: they are added together.  (503 M coordinates,
+            // finalize, us: the sign of the gradient 5,440 by the passes, 1,000 so; clipped at 1.2 standard deviations 1,480 and 776.)
+            for (uint32_t i = lane; i < n; i += 64) {
+                const uint32_t key = stage[i], bin = bin_of_key(key);
+                const bool listed = shift[key >= end[2]] != 0, like_first = bin == scalar_u32(bin);
+                const uint64_t to_list = __builtin_amdgcn_ballot_w64(listed), alike = __builtin_amdgcn_ballot_w64(like_first);
+                uint32_t first = 0;
+                if (to_list && lane == 0) first = atomicAdd(&n_listed, (uint32_t)__builtin_popcountll(to_list));
+                first = __builtin_amdgcn_mbcnt_hi((uint32_t)(to_list >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)to_list, scalar_u32(first)));
+                if (listed && first < cap) st_device(&list[first], key);
+                if (!like_first) atomicAdd(&hist[bin], 1u);
+                else if (lane == 0) atomicAdd(&hist[bin], (uint32_t)__builtin_popcountll(alike));
+            }
         }
         n_stage -= n;
         const uint32_t rest = lane < n_stage ? stage[n + lane] : 0u;
@@ -770,7 +818,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
         }
         if (tid == 128) sums->n_list = n_listed;
         uint32_t* to = mem.hist + (uint64_t)block * kHistWords;
-        for (uint32_t i = tid; i < 2u << bins_log; i += THREADS)
+        for (uint32_t i = tid; i < 2 * slots; i += THREADS)
             if (hist[i]) atomicAdd(&to[i], hist[i]);
         return;
     }
@@ -825,7 +873,7 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
 {
     __shared__ alignas(16) uint32_t keys[2 * kOnceKeys];      // a unit's of either interval; then the block's of one, 512 more than there are at most
     __shared__ double red[4][10];
-    __shared__ uint32_t n_below[2], n_in[2], n_mine[2], first_mine[2], n_over, bin[4], bin_at[4], scans[4];
+    __shared__ uint32_t n_below[2], n_in[2], n_mine[2], first_mine[2], n_over, bin[4], bin_at[4], bin_n[4], scans[4];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = scalar_wave_index();
     const uint32_t block = find_owner(mem.n_blocks, blockIdx.x, lane, [&](uint32_t i) { return mem.rows[i].first_unit; });
     const OnceRow& o = mem.rows[block];
@@ -835,9 +883,9 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
     const OnceSums* sums = mem.sums + (o.geom >> 24 ? mem.narrow_tasks + o.first_wide : o.first_task);
     uint32_t* line = mem.line + block * kArriveStride;
     uint32_t* hist = mem.hist + (uint64_t)block * kHistWords;
-    const uint32_t keys_cap = once_keys_cap(m.numel);
-    uint32_t* found = reinterpret_cast<uint32_t*>(mem.base + ((uint64_t)o.off_cols + once_cols_units(n_tasks, rows ? cols : 0u)) * 64);
-    const uint32_t bins_log = scalar_u32(once_bins_log((uint32_t)m.numel));
+    const uint32_t keys_cap = once_keys_cap(m.numel), cells_log = once_cells_log(keys_cap);
+    uint32_t* found = once_found(mem, o, rows ? cols : 0u);
+    const uint32_t bins_log = scalar_u32(once_bins_log((uint32_t)m.numel)), slots = 1u << once_slots_log(bins_log);
     bool bad = scalar_u32(line[L_REDO]) != 0;             // then there are no intervals
     uint32_t end[4], shift[2];
 #pragma unroll
@@ -845,10 +893,13 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
 #pragma unroll
     for (int i = 0; i < 2; ++i) shift[i] = once_shift(end[2 * i + 1] - end[2 * i], bins_log);
 
-    // Keys below and in the intervals, the bins that hold the ranks and the keys before these.
+    const bool one_interval = end[2] == end[3];               // both quantiles are in the first
+    auto interval_of = [&](uint32_t t) { return one_interval ? 0u : t >> 1; };
+
+    // Keys below and in the intervals, the bins that hold the ranks, the keys before these and in them.
     auto digits = [&]() {
         if (tid < 2) n_below[tid] = n_mine[tid] = 0;
-        if (tid < 4) { bin[tid] = ~0u; bin_at[tid] = 0; }
+        if (tid < 4) { bin[tid] = ~0u; bin_at[tid] = bin_n[tid] = 0; }
         if (tid == 4) n_over = 0;
         __syncthreads();
         uint32_t n[2] = {0, 0}, over = 0;
@@ -862,11 +913,11 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
             if (lane == 63) atomicAdd(&n_below[j], all);
         }
         if (over) n_over = 1;
-        const uint32_t q = wave >> 1, mine_at = (tid & 127u) * kBinsPerLane, bins = 1u << bins_log;
+        const uint32_t q = wave >> 1, mine_at = (tid & 127u) * kBinsPerLane;
         uint32_t c[kBinsPerLane], mine = 0;
 #pragma unroll
         for (uint32_t i = 0; i < kBinsPerLane; ++i) c[i] = 0;
-        if (mine_at < bins) load_bins(c, hist + q * bins + mine_at);
+        if (mine_at < slots) load_bins(c, hist + q * slots + mine_at);
 #pragma unroll
         for (uint32_t i = 0; i < kBinsPerLane; ++i) mine += c[i];
         const uint32_t incl = wave_scan(mine);
@@ -875,16 +926,31 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
         const uint32_t at = incl - mine + (wave & 1u ? scans[wave - 1] : 0u);
         if (tid < 2) n_in[tid] = scans[2 * tid] + scans[2 * tid + 1];
 #pragma unroll
-        for (uint32_t t = 0; t < 2; ++t) {
-            const uint32_t rank = (q ? m.rank[2 + t] : m.rank[t]) - n_below[q];
-            if (rank >= at && rank - at < mine) {       // a rank below the interval wraps around
+        for (uint32_t t = 0; t < 4; ++t) {
+            const uint32_t rank = m.rank[t] - n_below[q];
+            if (interval_of(t) == q && rank >= at && rank - at < mine) {       // a rank below the interval wraps around
                 const Digit f = bin_of(c, mine_at, at, rank);
-                bin[2 * q + t] = f.bin; bin_at[2 * q + t] = rank - f.rank;
+                bin[t] = f.bin; bin_at[t] = rank - f.rank; bin_n[t] = f.count;
             }
         }
         __syncthreads();
     };
     static_assert(kOnceBins == 128 * kBinsPerLane && kBinsPerLane <= 1u << 7, "two wavefronts an interval");
+    // The bins of an interval's ranks, and those between them, are one range of keys.
+    struct Range { uint32_t first, width, before, n, shift; bool crowded; };
+    auto range_of = [&](uint32_t q) {
+        uint32_t lo = ~0u, hi = 0, before = 0, end_at = 0;
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t)
+            if (interval_of(t) == q && bin[t] != ~0u) {        // ~0: a zero, below the interval
+                if (lo == ~0u) { lo = bin[t]; before = bin_at[t]; }
+                hi = bin[t]; end_at = bin_at[t] + bin_n[t];
+            }
+        const uint32_t n = scalar_u32(end_at - before), sh = q ? shift[1] : shift[0];
+        // nothing is wanted of keys that have a bin each
+        const uint32_t width = scalar_u32(lo == ~0u || sh == 0 ? 0u : (hi - lo + 1) << sh);
+        return Range{(q ? end[2] : end[0]) + (scalar_u32(lo) << sh), width, scalar_u32(before), n, width_shift(width, cells_log), n > keys_cap && width != 0};
+    };
 
     const uint32_t cap = scalar_u32(o.list_cap), parts = once_parts(cap), id = unit * 4 + wave, task = id / max(parts, 1u);
     const uint32_t part_at = (id - task * parts) * kOncePart, all = unit < lists && task < n_tasks ? min(scalar_u32(sums[task].n_list), cap) : 0u;
@@ -894,19 +960,29 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
         have = true;
         digits();
         const uint32_t* list = reinterpret_cast<const uint32_t*>(mem.base + (uint64_t)o.off_list * 64);
-        // A rank's bin and that of the next one, and the empty ones between them, are one range of keys.
-        uint32_t from_key[2], width[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const uint32_t b1 = scalar_u32(bin[2 * q + 1]), b0 = min(scalar_u32(bin[2 * q]), b1);   // the lower may be a zero, below the interval
-            from_key[q] = end[2 * q] + (b0 << shift[q]);
-            width[q] = b1 != ~0u ? (b1 - b0 + 1) << shift[q] : 0u;
+        const Range r[2] = {range_of(0), range_of(1)};
+        for (uint32_t i = tid; i < 3u << cells_log; i += 256) {
+            if (r[0].crowded) keys[i] = 0;
+            if (r[1].crowded) keys[kOnceKeys + i] = 0;
         }
+        __syncthreads();
         auto take = [&](uint32_t key, bool there) {
-            const bool low = key - from_key[0] < width[0], high = key - from_key[1] < width[1];
+            const bool low = key - r[0].first < r[0].width, high = key - r[1].first < r[1].width;
             if ((low || high) && there) {
-                const uint32_t at = atomicAdd(&n_mine[high], 1u);
-                if (at < kOnceKeys) keys[high * kOnceKeys + at] = key;
+                if (high ? r[1].crowded : r[0].crowded) {
+                    const uint32_t cell = (high ? (key - r[1].first) >> r[1].shift : (key - r[0].first) >> r[0].shift);
+                    uint32_t* at = keys + high * kOnceKeys + cell;
+                    const bool like_first = cell + high * kOnceKeys == scalar_u32(cell + high * kOnceKeys);
+                    const uint64_t alike = __builtin_amdgcn_ballot_w64(like_first);
+                    if (!like_first) atomicAdd(at, 1u);
+                    else if (__builtin_amdgcn_mbcnt_hi((uint32_t)(alike >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)alike, 0u)) == 0)
+                        atomicAdd(at, (uint32_t)__builtin_popcountll(alike));
+                    if (at[1u << cells_log] < key) atomicMax(at + (1u << cells_log), key);
+                    if (at[2u << cells_log] < ~key) atomicMax(at + (2u << cells_log), ~key);
+                } else {
+                    const uint32_t at = atomicAdd(&n_mine[high], 1u);
+                    if (at < kOnceKeys) keys[high * kOnceKeys + at] = key;
+                }
             }
         };
         const uint32_t* from = list + (uint64_t)task * cap + part_at;   // a multiple of 16 words, as cap is
@@ -926,8 +1002,19 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
         __syncthreads();
 #pragma unroll
         for (uint32_t q = 0; q < 2; ++q)
+        {
             for (uint32_t i = tid; i < min(n_mine[q], kOnceKeys) && first_mine[q] + i < keys_cap; i += 256)
                 st_device(&found[q * keys_cap + first_mine[q] + i], keys[q * kOnceKeys + i]);
+            if (!r[q].crowded) continue;
+            for (uint32_t i = tid; i < 1u << cells_log; i += 256) {
+                const uint32_t* cell = keys + q * kOnceKeys + i;
+                uint32_t* to = found + q * keys_cap + i;
+                if (cell[0] == 0) continue;
+                atomicAdd(to, cell[0]);
+                atomicMax(to + (1u << cells_log), cell[1u << cells_log]);
+                atomicMax(to + (2u << cells_log), cell[2u << cells_log]);
+            }
+        }
     } else if (F && unit >= lists) {
         // 64 columns, a quarter of the tasks to each wavefront
         const uint32_t at = (unit - lists) * 64 + lane;
@@ -969,22 +1056,40 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
     // a wavefront per rank
     const double* rec = mem.rec + (uint64_t)block * kRecDoubles;
     double* out = mem.out + (uint64_t)block * kRecDoubles;
-    const uint32_t q = wave >> 1, rank = wave == 0 ? m.rank[0] : wave == 1 ? m.rank[1] : wave == 2 ? m.rank[2] : m.rank[3];
+    const uint32_t q = interval_of(wave), rank = wave == 0 ? m.rank[0] : wave == 1 ? m.rank[1] : wave == 2 ? m.rank[2] : m.rank[3];
     bad |= n_over != 0;
     uint32_t value = 0;
 #pragma unroll
-    for (uint32_t half = 0; half < 2; ++half) {                // one interval after the other: its keys to LDS, then its two ranks
+    for (uint32_t half = 0; half < 2; ++half) {                // one interval after the other: its keys to LDS, then its ranks
+        const Range r = range_of(half);
         const uint32_t n_keys = ld_device(line + L_KEYS + half), n = min(n_keys, keys_cap), first = end[2 * half], sh = shift[half];
+        const uint32_t* from = found + half * keys_cap;
         __syncthreads();
-        for (uint32_t i = tid; i < n + 512; i += 256) keys[i] = i < n ? ld_device(&found[half * keys_cap + i]) : ~0u;
+        if (r.crowded)
+            for (uint32_t i = tid; i < 1024; i += 256)
+                for (uint32_t k = 0; k < 3; ++k) keys[k * 1024 + i] = i < 1u << cells_log ? ld_device(from + (k << cells_log) + i) : 0u;
+        else
+            for (uint32_t i = tid; i < n + 512; i += 256) keys[i] = i < n ? ld_device(from + i) : ~0u;
         __syncthreads();
         if (q != half) continue;
-        const uint32_t b0 = bin[2 * half], b = bin[wave];
+        const uint32_t b = bin[wave], want = rank - n_below[half] - r.before;
         if (rank < n_below[half]) bad |= first != 1;           // 0 is the only key below 1
-        else if (rank - n_below[half] >= n_in[half] || n_keys > keys_cap || b == ~0u) bad = true;
+        else if (rank - n_below[half] >= n_in[half] || b == ~0u) bad = true;
+        else if (sh == 0) value = first + b;
+        else if (r.crowded) {
+            uint32_t c[16], mine = 0;
+            load_bins(c, keys + lane * 16);
+#pragma unroll
+            for (uint32_t i = 0; i < 16; ++i) mine += c[i];
+            const uint32_t at = wave_scan(mine) - mine;
+            const bool here = want >= at && want - at < mine;
+            const uint32_t cell = here ? bin_of(c, lane * 16, at, want).bin : 0u, least = ~keys[2048 + cell], most = keys[1024 + cell];
+            const uint64_t owner = __builtin_amdgcn_ballot_w64(here), one_value = __builtin_amdgcn_ballot_w64(here && least == most);
+            bad |= one_value == 0;
+            if (owner) value = (uint32_t)__builtin_amdgcn_readlane((int)most, (int)__builtin_ctzll(owner));
+        } else if (n_keys > keys_cap) bad = true;
         else {
-            const uint32_t want = rank - n_below[half] - (b0 != ~0u ? bin_at[2 * half] : bin_at[2 * half + 1]) + 1;
-            uint32_t lo = first + (b << sh), hi = lo + (1u << sh) - 1;                       // the least key with `want` keys up to it
+            uint32_t lo = first + (b << sh), hi = lo + (1u << sh) - 1;                       // the least key with `want` + 1 keys up to it
             while (lo < hi) {
                 const uint32_t mid = lo + ((hi - lo) >> 1);
                 uint32_t upto = 0;
@@ -995,7 +1100,7 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
 #pragma unroll
                     for (uint32_t k = 0; k < 8; ++k) upto += (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(key[k] <= mid));
                 }
-                if (upto >= want) hi = mid; else lo = mid + 1;
+                if (upto > want) hi = mid; else lo = mid + 1;
             }
             value = lo;
         }
@@ -1012,7 +1117,7 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
         leave_record(rec, out, res, c.num, x[3], scans[0] != 0 || !(fabs(res) < INFINITY) || c.bad, line + L_REDO);
     }
     if (tid >= 64 && tid < 66) st_device(line + L_KEYS + (tid - 64), 0u);
-    for (uint32_t i = tid; i < 2u << bins_log; i += 256) hist[i] = 0;
+    for (uint32_t i = tid; i < 2 * slots; i += 256) hist[i] = 0;
 }
 
 }  // namespace baoc

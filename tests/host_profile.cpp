@@ -364,6 +364,33 @@ static int check_once_loads(const OnceRow& o, const TileRow& m)
     return 0;
 }
 
+// Keys of an interval have bins, and those of a crowded range cells, inside their words; intervals are in order and apart.
+static int check_once_intervals()
+{
+    for (uint32_t numel : {12290u, 65537u, (1u << 20) - 1, 1u << 21, 1u << 28}) {
+        const uint32_t bins_log = once_bins_log(numel), slots = 1u << once_slots_log(bins_log), cap = once_keys_cap(numel), cells = 1u << once_cells_log(cap);
+        CHECK(2 * slots <= kHistWords && 3 * cells <= cap && cells <= 1024 && cap <= kOnceKeys, "%u", numel);
+        for (uint32_t bits = 0; bits < 31; ++bits)
+            for (uint32_t width : {(1u << bits) - 1, 1u << bits, (1u << bits) + 1}) {
+                if (width == 0) continue;
+                CHECK((width - 1) >> once_shift(width, bins_log) < slots && (width - 1) >> width_shift(width, once_cells_log(cap)) < cells, "%u of %u", width, numel);
+            }
+    }
+    const uint32_t n = 1u << 22, top = 0x7f800000u >> kBits3;
+    const struct { uint32_t prefix[4]; bool ok, one; } cases[] = {
+        {{100, 200, 300, 400}, true, false}, {{0, 0, 300, 400}, true, false}, {{0, 0, 0, 400}, true, true}, {{0, 0, 0, 0}, true, true},
+        {{7, 7, 7, 7}, true, true}, {{100, 200, 200, 300}, false, true}, {{100, 200, 201, 300}, true, false}, {{100, 200, 300, top}, false, false},
+        {{top, n - 1, n - 1, n - 1}, false, false}};
+    for (const auto& c : cases) {
+        uint32_t end[4];
+        CHECK(once_intervals(c.prefix, end) == c.ok, "%u %u %u %u", c.prefix[0], c.prefix[1], c.prefix[2], c.prefix[3]);
+        if (!c.ok) continue;
+        CHECK(end[0] >= 1 && end[0] < end[1] && end[1] <= end[2] && (end[2] == end[3]) == c.one && end[2] <= end[3], "%u %u %u %u", end[0], end[1], end[2], end[3]);
+        CHECK(end[3] == (c.prefix[3] + 1) << kBits3, "%u", end[3]);
+    }
+    return 0;
+}
+
 // Which layouts and blocks take the one pass, and that its memory is what the passes have for r, c and the lists, each part of it apart.
 static int check_once()
 {
@@ -421,6 +448,7 @@ int main(int argc, char** argv)
     if (what == "reads") return check_reads();
     if (what == "end_at_exit") return check_end_at_exit();
     if (what == "once") return check_once();
+    if (what == "once_intervals") return check_once_intervals();
     std::printf("no check named '%s'\n", what.c_str());
     return 2;
 }

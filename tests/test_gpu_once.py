@@ -136,3 +136,57 @@ def test_distortion_where_a_rare_p_is_large(env, dead, theta):  # noqa: F811
         p, t = 1.0 / (prof.state(i)[1].double().sqrt() + 1e-12), th[o:o + n].double()
         C = (((p / p.mean() - 1.0) * t).pow(2).sum().sqrt() / t.pow(2).sum().sqrt()).item()
         assert abs(stats[i].C - C) <= 1e-6 * C, f"{shapes[i]}: {stats[i].C} {C}"
+
+
+def _marked(prof, blocks, stats):
+    """The blocks that the one pass has handed on to the passes.  The records follow the states in the workspace (found by the sum of v of the last
+    block, the fourth of its 32 numbers), then 16 KB of histogram a block, then a line of 32 words a block, whose third is the mark."""
+    torch, last = prof._torch, len(blocks) - 1
+    tail = prof.state(last)[2]
+    first = -(-(tail.data_ptr() + tail.numel() * tail.element_size() - prof.workspace.data_ptr()) // 256) * 256
+    words = prof.workspace[first:first + (prof.workspace.numel() - first) // 8 * 8].view(torch.float64)
+    at = [8 * (int(i) - 3 - 32 * last) for i in (words == stats[last].v_l1).nonzero().flatten()]
+    at = [first + i for i in at if i >= 0 and i % 256 == 0]
+    assert len(at) == 1
+    hist = -(-(at[0] + 256 * len(blocks)) // 256) * 256
+    lines = prof.workspace[hist + 16384 * len(blocks):hist + (16384 + 128) * len(blocks)].view(torch.int32).view(-1, 32)
+    return lines[:, 2].nonzero().flatten().tolist()
+
+
+def _quantiles(v):
+    v = v.reshape(-1).sort().values
+    out = []
+    for q in (0.1, 0.9):
+        at = q * (v.numel() - 1); lo = int(at)
+        a, b = v[lo].item(), v[min(lo + 1, v.numel() - 1)].item()
+        out.append(a + (at - lo) * (b - a))
+    return out
+
+
+@pytest.mark.parametrize("kind", ["zero", "constant", "zeros 95", "zeros 90", "clipped", "bf16"])
+def test_equal_keys_take_one_read(env, kind):  # noqa: F811
+    """After one step: dead blocks, mostly untouched ones, gradients clipped by value, constant ones, and bf16 gradients of large blocks
+    (42,000 of 16.8 M have the same v at the upper quantile).  Quantiles are those of the sorted v, and no block goes through the passes."""
+    torch, binding = env["torch"], env["binding"]
+    shapes = [(1500, 1000), (1500000, 0), (4096, 4096), FILLER]
+    blocks, at = [], 0
+    for r, c in shapes:
+        n = r * c if c else r
+        blocks.append((at, n, r if c else 0, c)); at += n
+    gen = torch.Generator(device="cuda:0").manual_seed(8)
+    g = torch.randn(at, device="cuda:0", generator=gen).mul_(1e-2)
+    for o, n, r, c in blocks[:3]:
+        b = g[o:o + n]
+        if kind == "zero": b.zero_()
+        if kind == "constant": b.fill_(0.125)
+        if kind.startswith("zeros"): b[torch.rand(n, device="cuda:0", generator=gen) < 0.01 * int(kind[6:])] = 0.0
+        if kind == "clipped": b.clamp_(-0.012, 0.012)
+    prof = binding.Profiler(blocks, binding.default_profile_params(grad_dtype=1 if kind == "bf16" else 0))
+    prof.step(g.to(torch.bfloat16) if kind == "bf16" else g)
+    for _ in range(2):
+        stats = prof.finalize()[0]
+        assert _marked(prof, blocks, stats) == []
+        for i in range(len(blocks)):
+            want = _quantiles(prof.state(i)[1])
+            for got, w in zip((stats[i].q10, stats[i].q90), want):
+                assert abs(got - w) <= 1e-12 * w, f"{shapes[i]}: {got} {w}"

@@ -56,6 +56,10 @@ def test_one_pass_reads_every_coordinate_once_inside_its_rows(host_profile):
     host_profile("once")
 
 
+def test_intervals_of_the_one_pass(host_profile):
+    host_profile("once_intervals")
+
+
 def test_no_kernel_spills_registers_or_uses_scratch():
     """The kernels' metadata in the built library: a zero behind every such key."""
     binding.load_library()
