@@ -12,9 +12,9 @@ namespace baoc {
 //   Eq. 4  The quantiles' first digits are not known in advance, but a sample of 16,384 coordinates places them within 1.2 % of the
 //          ranks: keys inside the two intervals are listed, those below are counted.  Equal keys: zeros lie below every interval; an
 //          interval of at most 512 keys is counted key by key and not listed; of more keys in a rank's bins than can be ordered, k_once_select
-//          counts those of 256 to 1,024 cells of the bins, and a cell that holds one value gives the rank.  Where a rank turns out to
-//          lie outside its interval, a list is too short, a crowded cell has several values, or a sum is not finite, the block is marked and goes
-//          through the passes above.
+//          counts those of 256 to 1,024 cells of the bins, and a cell of one value gives the rank.
+//          Where a rank turns out to lie outside its interval, the lists are too short, a crowded cell has several values, or a sum is not finite,
+//          the block is marked and goes through the passes above.
 //          (Which keys are listed where is not the same from run to run; what is taken from them is, and so is what is marked.)
 //   Eq. 6  With q = p / p0 - 1 for a fixed p0, sum ((p/p-bar - 1) theta)^2 = k^2 sum (q theta)^2 + 2 k (k-1) sum q theta^2 +
 //          (k-1)^2 sum theta^2, k = p0 / p-bar.  For k well above 1 the terms are k^2 times their sum, so a rare large p (v = 0 at a
@@ -56,7 +56,7 @@ struct OnceMem {
 __host__ __device__ __forceinline__ uint64_t once_cols_units(uint32_t tasks, uint32_t cols) { return ((uint64_t)tasks * cols * 8 + 63) / 64; }
 constexpr uint32_t kOncePart = 8192;                      // words of a list that a wavefront of k_once_select takes
 __host__ __device__ __forceinline__ uint32_t once_parts(uint32_t cap) { return (cap + kOncePart - 1) / kOncePart; }
-__host__ __device__ __forceinline__ uint32_t once_list_units(uint32_t tasks, uint32_t cap) { return (uint32_t)(((uint64_t)tasks * once_parts(cap) + 3) / 4); }
+__host__ __device__ __forceinline__ uint32_t once_list_units(const OnceRow& o) { return (uint32_t)(((uint64_t)o.n_tasks * once_parts(o.list_cap) + once_parts(o.spill_cap) + 3) / 4); }
 __host__ __device__ __forceinline__ uint32_t once_col_units(uint32_t rows, uint32_t cols) { return rows ? (cols + 63) / 64 : 0u; }
 __host__ __device__ __forceinline__ uint32_t once_keys_cap(uint64_t numel) { return (uint32_t)max((uint64_t)1024, min((uint64_t)kOnceKeys, numel >> 10)); }
 
@@ -68,6 +68,7 @@ __host__ __device__ __forceinline__ uint32_t sample_pieces(uint64_t numel)
 {
     return numel >= (1u << 27) ? 16u : numel >= (1u << 26) ? 8u : numel >= (1u << 22) ? 4u : 2u;
 }
+constexpr float kListSlack = 1.2f;                        // a block's lists have at least this much more room
 inline double listed_share(uint64_t numel) { return 2.0 * 2.0 * 1.5 / std::sqrt(4096.0 * sample_pieces(numel)); }
 
 // Where a load of 1 << rpl rows starts that wants `row` and those after it, and a lane that wants four columns from `col` on: rows past the
@@ -202,13 +203,17 @@ __device__ __forceinline__ double wave_total(double x)
     return x;
 }
 
-// The pieces are drawn one from each of equal shares of the block.  An interval reaches 5 standard deviations of the sample's rank to either
-// side, at the resolution of two digits.  Zeros are left out of it and counted as below: a quantile of a block with untouched coordinates is then
-// known to be 0 however many there are.  Bound by latency (loads, two rounds of counting) up to about 100 blocks, 20 us, then by the lines.
+// The pieces are drawn one from each of equal shares of the block, independently.  An interval reaches 5 standard deviations of the sample's rank to
+// either side, at the resolution of two digits.  The four coordinates of a piece are neighbours and may be alike (kernels, rows, neurons of different
+// scale), which gives a rank up to twice the deviation that independent coordinates would: it is estimated from how the counts differ from piece
+// to piece, and where it is more than a tenth above the latter the intervals are taken again, at most as wide as the lists have room for.  (240
+// blocks of 1 M, 9 neighbours of one scale: 2 of them were marked without that, finalize 511 us, 460 so.)
+// Zeros are left out of an interval and counted as below: a quantile of a block with untouched coordinates is then known to be 0 however many there are.
+// Bound by latency (loads, two rounds of counting) up to about 100 blocks, 20 us, then by the lines.
 __global__ __launch_bounds__(1024) void k_bracket(const float* __restrict__ v_all, const TileRow* __restrict__ tiles, OnceMem mem, float eps)
 {
     __shared__ alignas(16) uint32_t h[kHistWords];
-    __shared__ uint32_t sel[8], sums[4];
+    __shared__ uint32_t sel[8], sums[4], moment[4];
     __shared__ float sh[16];
     const uint32_t block = blockIdx.x, lane = threadIdx.x & 63u, wave = scalar_wave_index();
     if (mem.rows[block].n_tasks < 2) return;
@@ -235,18 +240,51 @@ __global__ __launch_bounds__(1024) void k_bracket(const float* __restrict__ v_al
         if (q < mine) psum += (preconditioner(x[q].x, eps) + preconditioner(x[q].y, eps)) + (preconditioner(x[q].z, eps) + preconditioner(x[q].w, eps));
     const float wave_p = wave_sum(psum);
     if (lane == 0) sh[wave] = wave_p;                         // order_stats has barriers
+    auto of_piece = [&](uint32_t q, auto f) {
+        const float e[4] = {x[q].x, x[q].y, x[q].z, x[q].w};   // (a bit cast of a vector's element takes the first one)
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) f(__builtin_bit_cast(uint32_t, e[k]) & 0x7fffffffu);
+    };
+    auto walk = [&](auto f) {
+#pragma unroll
+        for (uint32_t q = 0; q < 16; ++q)
+            if (q < mine) of_piece(q, f);
+    };
+    const OnceRow& o = mem.rows[block];
+    const uint32_t lo = n / 10, hi = n - 1 - n / 10;
     const float spread = 1.5f * __builtin_amdgcn_sqrtf((float)n);           // 5 sqrt(0.1 * 0.9 n)
-    const uint32_t d = (uint32_t)spread + 1, lo = n / 10, hi = n - 1 - n / 10;
-    const uint32_t rank[4] = {lo - d, lo + d, hi - d, hi + d};
-    order_stats<1024, false>([&](auto f) {
+    if (threadIdx.x < 4) moment[threadIdx.x] = 0;
+    auto ends = [&](float reach) {
+        const uint32_t d = (uint32_t)reach + 1, rank[4] = {lo - d, lo + d, hi - d, hi + d};
+        order_stats<1024, false>(walk, rank, h, sel, sums, lane, wave);
+    };
+    ends(spread);
+    // Keys below the inner ends, of all pieces: their number and the sum of the squares of a piece's.
+    const uint32_t inner[2] = {(sel[1] + 1) << kBits3, sel[2] << kBits3};
+#pragma unroll
+    for (uint32_t t = 0; t < 2; ++t) {
+        uint32_t first = 0, second = 0;
 #pragma unroll
         for (uint32_t q = 0; q < 16; ++q)
             if (q < mine) {
-                const float e[4] = {x[q].x, x[q].y, x[q].z, x[q].w};   // (a bit cast of a vector's element takes the first one)
-#pragma unroll
-                for (uint32_t k = 0; k < 4; ++k) f(__builtin_bit_cast(uint32_t, e[k]) & 0x7fffffffu);
+                uint32_t c = 0;
+                of_piece(q, [&](uint32_t key) { c += key < inner[t]; });
+                first += c; second += c * c;
             }
-    }, rank, h, sel, sums, lane, wave);
+        first = wave_scan(first); second = wave_scan(second);
+        if (lane == 63) { atomicAdd(&moment[2 * t], first); atomicAdd(&moment[2 * t + 1], second); }
+    }
+    __syncthreads();
+    float more = 0.f;                                         // times the variance of independent coordinates
+#pragma unroll
+    for (uint32_t t = 0; t < 2; ++t) {
+        const float first = (float)moment[2 * t], second = (float)moment[2 * t + 1];
+        if (first > 0.f && first < (float)n) more = fmaxf(more, (second - first * (first / (float)pieces)) / (first * (1.0f - first / (float)n)));
+    }
+    // as wide as the lists have room for: two intervals, two sides, a quarter to spare (the share of alike neighbours between two ranks varies, too)
+    const float room = ((float)o.list_cap * (float)o.n_tasks + (float)o.spill_cap) / (float)m.numel * (float)n * 0.2f;
+    const float wide = fminf(spread * __builtin_amdgcn_sqrtf(more), room);
+    if (wide > 1.1f * spread) ends(wide);
     uint32_t* line = mem.line + block * kArriveStride;
     if (threadIdx.x < 16) {
         // the patterns' order is the values'
@@ -262,6 +300,7 @@ __global__ __launch_bounds__(1024) void k_bracket(const float* __restrict__ v_al
         const uint32_t prefix[4] = {sel[0], sel[1], sel[2], sel[3]};
         uint32_t end[4];
         line[L_REDO] = !once_intervals(prefix, end);
+        line[L_SPILL] = 0;
         for (uint32_t i = 0; i < 4; ++i) line[L_BRACKET + i] = end[i];
     }
     const uint32_t keys_cap = once_keys_cap(m.numel), words = 3u << once_cells_log(keys_cap);
@@ -322,6 +361,16 @@ __device__ __forceinline__ void share_rows(float (&r)[4], float a)
 }
 __device__ __forceinline__ void share_rows(float (&r)[2], float a) { r[0] = dpp<0x150, 0xf>(0.f, a); r[1] = dpp<0x158, 0xf>(0.f, a); }
 __device__ __forceinline__ void share_rows(float (&r)[1], float a) { r[0] = a; }
+
+// h[i] += 1; lanes that agree with the first one there are added together (all keys of a block may be equal).
+__device__ __forceinline__ void count_alike(uint32_t* h, uint32_t i)
+{
+    const bool like_first = i == scalar_u32(i);
+    const uint64_t alike = __builtin_amdgcn_ballot_w64(like_first);
+    if (!like_first) atomicAdd(&h[i], 1u);
+    else if (__builtin_amdgcn_mbcnt_hi((uint32_t)(alike >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)alike, 0u)) == 0)
+        atomicAdd(&h[i], (uint32_t)__builtin_popcountll(alike));
+}
 
 // Barrier for what passes through LDS: loads from memory stay in flight.
 __device__ __forceinline__ void lds_barrier()
@@ -454,6 +503,25 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
     uint32_t* stage = staged + wave * kOnceStage;
     const uint32_t cap = scalar_u32(o.list_cap);
     uint32_t* list = reinterpret_cast<uint32_t*>(mem.base + (uint64_t)o.off_list * 64) + (uint64_t)local * cap;
+    // Room for n keys of the wavefront; from `cap` on, which stands after the tasks' lists, it is the block's common list: tasks may have very
+    // different shares of the keys.
+    struct Slots { uint32_t first, spilled, at; };
+    auto reserve = [&](uint32_t n) {
+        uint32_t x = 0;
+        if (lane == 0) x = atomicAdd(&n_listed, n);
+        Slots r{scalar_u32(x), 0, 0};
+        if (r.first + n > cap) {
+            r.spilled = max(r.first, cap);
+            if (lane == 0) x = atomicAdd(&line[L_SPILL], r.first + n - r.spilled);
+            r.at = scalar_u32(x);
+        }
+        return r;
+    };
+    auto put = [&](const Slots& r, uint32_t i, uint32_t key) {
+        const uint32_t slot = r.first + i, common = r.at + (slot - r.spilled);
+        if (slot < cap) st_device(&list[slot], key);
+        else if (common < o.spill_cap) st_device(&list[(n_tasks - local) * cap + common], key);
+    };
     auto flush = [&](bool all) {
         const uint32_t n = all ? n_stage : n_stage & ~63u;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -461,27 +529,26 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
         // (next to zeros, or empty, an interval has hardly a key)
         const bool counted = (shift[0] == 0 && end[0] > 1) || (shift[1] == 0 && end[2] > 1 && end[2] != end[3]);
         if (!counted) {
-            uint32_t first = 0;
-            if (lane == 0) first = atomicAdd(&n_listed, n);
-            first = scalar_u32(first);
+            const Slots r = reserve(n);
+            const bool fits = r.first + n <= cap;
             for (uint32_t i = lane; i < n; i += 64) {
                 const uint32_t key = stage[i];
-                if (first + i < cap) st_device(&list[first + i], key);
+                if (fits) st_device(&list[r.first + i], key); else put(r, i, key);
                 atomicAdd(&hist[bin_of_key(key)], 1u);
             }
         } else {
             // An interval that is counted key by key is not listed.  Most keys may be equal: they are added together.  (503 M coordinates,
             // finalize, us: the sign of the gradient 5,440 by the passes, 1,000 so; clipped at 1.2 standard deviations 1,480 and 776.)
             for (uint32_t i = lane; i < n; i += 64) {
-                const uint32_t key = stage[i], bin = bin_of_key(key);
-                const bool listed = shift[key >= end[2]] != 0, like_first = bin == scalar_u32(bin);
-                const uint64_t to_list = __builtin_amdgcn_ballot_w64(listed), alike = __builtin_amdgcn_ballot_w64(like_first);
-                uint32_t first = 0;
-                if (to_list && lane == 0) first = atomicAdd(&n_listed, (uint32_t)__builtin_popcountll(to_list));
-                first = __builtin_amdgcn_mbcnt_hi((uint32_t)(to_list >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)to_list, scalar_u32(first)));
-                if (listed && first < cap) st_device(&list[first], key);
-                if (!like_first) atomicAdd(&hist[bin], 1u);
-                else if (lane == 0) atomicAdd(&hist[bin], (uint32_t)__builtin_popcountll(alike));
+                const uint32_t key = stage[i];
+                const bool listed = shift[key >= end[2]] != 0;
+                const uint64_t to_list = __builtin_amdgcn_ballot_w64(listed);
+                if (to_list) {
+                    const Slots r = reserve((uint32_t)__builtin_popcountll(to_list));
+                    const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(to_list >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)to_list, 0u));
+                    if (listed) put(r, at, key);
+                }
+                count_alike(hist, bin_of_key(key));
             }
         }
         n_stage -= n;
@@ -847,39 +914,23 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
     }
 }
 
-// Sums over a workgroup of four wavefronts in a fixed order; every thread has them.
-template <int N> __device__ __forceinline__ void group_sums(double (&x)[N], uint32_t lane, uint32_t wave, double (*sh)[10])
-{
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1)
-#pragma unroll
-        for (int j = 0; j < N; ++j) x[j] += __shfl_xor(x[j], d);
-    if (lane == 0) {
-#pragma unroll
-        for (int j = 0; j < N; ++j) sh[wave][j] = x[j];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < N; ++j) x[j] = (sh[0][j] + sh[1][j]) + (sh[2][j] + sh[3][j]);
-}
-
 // Units of a block: the first walk its tasks' lists for the keys that share the ranks' bins, the others sum 64 columns over its tasks. The
 // last to arrive orders the keys, adds the sums and leaves the record.  A chain of dependent loads for a small layout (32 blocks of 1 M 23 us),
 // HBM for the lists and the column sums of large ones (3.5 G coordinates, 0.9 GB, 250 us).  Keys are collected in LDS first, since an atomic on
 // the block's counter is a round trip of more than a microsecond (148 blocks, 124 M: 110 us with one for each key, 43 so), and counted eight
 // reads at a time (8 blocks of 131 M, 2,000 keys each: 122 us with one read after another, 63 so).
 template <bool F, bool C>
-__global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__ tiles, OnceMem mem)
+__global__ __launch_bounds__(256, 4) void k_once_select(const TileRow* __restrict__ tiles, OnceMem mem)
 {
     __shared__ alignas(16) uint32_t keys[2 * kOnceKeys];      // a unit's of either interval; then the block's of one, 512 more than there are at most
     __shared__ double red[4][10];
-    __shared__ uint32_t n_below[2], n_in[2], n_mine[2], first_mine[2], n_over, bin[4], bin_at[4], bin_n[4], scans[4];
+    __shared__ uint32_t n_below[2], n_in[2], n_mine[2], first_mine[2], bin[4], bin_at[4], bin_n[4], scans[4], near_key[4], open;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = scalar_wave_index();
     const uint32_t block = find_owner(mem.n_blocks, blockIdx.x, lane, [&](uint32_t i) { return mem.rows[i].first_unit; });
     const OnceRow& o = mem.rows[block];
     const TileRow& m = tiles[block];
     const uint32_t n_tasks = scalar_u32(o.n_tasks), rows = scalar_u32(m.rows), cols = scalar_u32(m.cols);
-    const uint32_t unit = blockIdx.x - scalar_u32(o.first_unit), lists = once_list_units(n_tasks, o.list_cap), units = lists + once_col_units(rows, cols);
+    const uint32_t unit = blockIdx.x - scalar_u32(o.first_unit), lists = once_list_units(o), units = lists + once_col_units(rows, cols);
     const OnceSums* sums = mem.sums + (o.geom >> 24 ? mem.narrow_tasks + o.first_wide : o.first_task);
     uint32_t* line = mem.line + block * kArriveStride;
     uint32_t* hist = mem.hist + (uint64_t)block * kHistWords;
@@ -899,20 +950,16 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
     // Keys below and in the intervals, the bins that hold the ranks, the keys before these and in them.
     auto digits = [&]() {
         if (tid < 2) n_below[tid] = n_mine[tid] = 0;
-        if (tid < 4) { bin[tid] = ~0u; bin_at[tid] = bin_n[tid] = 0; }
-        if (tid == 4) n_over = 0;
+        if (tid < 4) { bin[tid] = ~0u; bin_at[tid] = bin_n[tid] = near_key[tid] = 0; }
+        if (tid == 4) open = 0;
         __syncthreads();
-        uint32_t n[2] = {0, 0}, over = 0;
-        for (uint32_t i = tid; i < n_tasks; i += 256) {
-            n[0] += sums[i].n[0]; n[1] += sums[i].n[1];
-            over |= sums[i].n_list > o.list_cap;
-        }
+        uint32_t n[2] = {0, 0};
+        for (uint32_t i = tid; i < n_tasks; i += 256) { n[0] += sums[i].n[0]; n[1] += sums[i].n[1]; }
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const uint32_t all = wave_scan(n[j]);
             if (lane == 63) atomicAdd(&n_below[j], all);
         }
-        if (over) n_over = 1;
         const uint32_t q = wave >> 1, mine_at = (tid & 127u) * kBinsPerLane;
         uint32_t c[kBinsPerLane], mine = 0;
 #pragma unroll
@@ -952,57 +999,66 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
         return Range{(q ? end[2] : end[0]) + (scalar_u32(lo) << sh), width, scalar_u32(before), n, width_shift(width, cells_log), n > keys_cap && width != 0};
     };
 
-    const uint32_t cap = scalar_u32(o.list_cap), parts = once_parts(cap), id = unit * 4 + wave, task = id / max(parts, 1u);
-    const uint32_t part_at = (id - task * parts) * kOncePart, all = unit < lists && task < n_tasks ? min(scalar_u32(sums[task].n_list), cap) : 0u;
-    const uint32_t n = all > part_at ? min(all - part_at, kOncePart) : 0u;
+    // a wavefront's part of a task's list, or of the common one that stands after these
+    const uint32_t cap = scalar_u32(o.list_cap), spilled = scalar_u32(line[L_SPILL]), parts = once_parts(cap), id = unit * 4 + wave;
+    struct Part { uint32_t* from; uint32_t n; };
+    auto part_of = [&](uint32_t id) {
+        const uint32_t task = min(id / max(parts, 1u), n_tasks), at = (id - task * parts) * kOncePart, whole = task < n_tasks ? cap : o.spill_cap;
+        const uint32_t all = min(whole, task < n_tasks ? sums[task].n_list : spilled);
+        return Part{reinterpret_cast<uint32_t*>(mem.base + (uint64_t)o.off_list * 64) + ((uint64_t)task * cap + at), all > at ? (uint32_t)min(all - at, kOncePart) : 0u};
+    };
+    Part own = unit < lists ? part_of(id) : Part{nullptr, 0u};
+    own.n = scalar_u32(own.n);
     bool have = false;
-    if (unit < lists && __syncthreads_or(n != 0)) {
+    if (unit < lists && __syncthreads_or(own.n != 0)) {
         have = true;
         digits();
-        const uint32_t* list = reinterpret_cast<const uint32_t*>(mem.base + (uint64_t)o.off_list * 64);
         const Range r[2] = {range_of(0), range_of(1)};
-        for (uint32_t i = tid; i < 3u << cells_log; i += 256) {
-            if (r[0].crowded) keys[i] = 0;
-            if (r[1].crowded) keys[kOnceKeys + i] = 0;
-        }
-        __syncthreads();
-        auto take = [&](uint32_t key, bool there) {
-            const bool low = key - r[0].first < r[0].width, high = key - r[1].first < r[1].width;
-            if ((low || high) && there) {
-                if (high ? r[1].crowded : r[0].crowded) {
-                    const uint32_t cell = (high ? (key - r[1].first) >> r[1].shift : (key - r[0].first) >> r[0].shift);
-                    uint32_t* at = keys + high * kOnceKeys + cell;
-                    const bool like_first = cell + high * kOnceKeys == scalar_u32(cell + high * kOnceKeys);
-                    const uint64_t alike = __builtin_amdgcn_ballot_w64(like_first);
-                    if (!like_first) atomicAdd(at, 1u);
-                    else if (__builtin_amdgcn_mbcnt_hi((uint32_t)(alike >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)alike, 0u)) == 0)
-                        atomicAdd(at, (uint32_t)__builtin_popcountll(alike));
-                    if (at[1u << cells_log] < key) atomicMax(at + (1u << cells_log), key);
-                    if (at[2u << cells_log] < ~key) atomicMax(at + (2u << cells_log), ~key);
-                } else {
-                    const uint32_t at = atomicAdd(&n_mine[high], 1u);
-                    if (at < kOnceKeys) keys[high * kOnceKeys + at] = key;
+        auto keep = [&](uint32_t key, bool high) {
+            const uint32_t at = atomicAdd(&n_mine[high], 1u);
+            if (at < kOnceKeys) keys[high * kOnceKeys + at] = key;
+        };
+        // a part starts on a multiple of 16 words, as cap is one
+        auto walk = [&](auto f) {
+            for (uint32_t i = 4 * lane; i < own.n; i += 1024) {
+                uint4 quad[4];
+#pragma unroll
+                for (uint32_t q = 0; q < 4; ++q) quad[q] = *reinterpret_cast<const uint4*>(own.from + min(i + 256 * q, (own.n - 1) & ~3u));
+#pragma unroll
+                for (uint32_t q = 0; q < 4; ++q) {
+                    const uint32_t at = i + 256 * q;
+                    f(quad[q].x, at < own.n); f(quad[q].y, at + 1 < own.n); f(quad[q].z, at + 2 < own.n); f(quad[q].w, at + 3 < own.n);
                 }
             }
         };
-        const uint32_t* from = list + (uint64_t)task * cap + part_at;   // a multiple of 16 words, as cap is
-        for (uint32_t i = 4 * lane; i < n; i += 1024) {
-            uint4 key[4];
-#pragma unroll
-            for (uint32_t q = 0; q < 4; ++q) key[q] = *reinterpret_cast<const uint4*>(from + min(i + 256 * q, (n - 1) & ~3u));
-#pragma unroll
-            for (uint32_t q = 0; q < 4; ++q) {
-                const uint32_t at = i + 256 * q;
-                take(key[q].x, at < n); take(key[q].y, at + 1 < n); take(key[q].z, at + 2 < n); take(key[q].w, at + 3 < n);
+        if (!r[0].crowded && !r[1].crowded) {
+            walk([&](uint32_t key, bool there) {
+                const bool low = key - r[0].first < r[0].width, high = key - r[1].first < r[1].width;
+                if ((low || high) && there) keep(key, high);
+            });
+        } else {
+            for (uint32_t i = tid; i < 3u << cells_log; i += 256) {
+                if (r[0].crowded) keys[i] = 0;
+                if (r[1].crowded) keys[kOnceKeys + i] = 0;
             }
+            __syncthreads();
+            walk([&](uint32_t key, bool there) {
+                const bool low = key - r[0].first < r[0].width, high = key - r[1].first < r[1].width;
+                const bool to_cell = there && ((low && r[0].crowded) || (high && r[1].crowded));
+                if (to_cell) {
+                    uint32_t* cell = keys + high * kOnceKeys + (high ? (key - r[1].first) >> r[1].shift : (key - r[0].first) >> r[0].shift);
+                    count_alike(keys, (uint32_t)(cell - keys));
+                    if (cell[1u << cells_log] < key) atomicMax(cell + (1u << cells_log), key);
+                    if (cell[2u << cells_log] < ~key) atomicMax(cell + (2u << cells_log), ~key);
+                } else if ((low || high) && there) keep(key, high);
+            });
         }
         // the unit's keys go to the block's in one piece: an atomic for each would be a round trip for each
         __syncthreads();
         if (tid < 2 && n_mine[tid]) first_mine[tid] = atomicAdd(&line[L_KEYS + tid], n_mine[tid]);
         __syncthreads();
 #pragma unroll
-        for (uint32_t q = 0; q < 2; ++q)
-        {
+        for (uint32_t q = 0; q < 2; ++q) {
             for (uint32_t i = tid; i < min(n_mine[q], kOnceKeys) && first_mine[q] + i < keys_cap; i += 256)
                 st_device(&found[q * keys_cap + first_mine[q] + i], keys[q * kOnceKeys + i]);
             if (!r[q].crowded) continue;
@@ -1041,24 +1097,34 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
     if (!arrive_last(line + L_ARRIVED, units)) return;
 
     if (!have) digits();
-    double x[10] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (uint32_t i = tid; i < n_tasks; i += 256) {
-        const double* s = reinterpret_cast<const double*>(sums + i);
+    {
+        double x[10] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        for (uint32_t i = tid; i < n_tasks; i += 256) {
+            const double* s = reinterpret_cast<const double*>(sums + i);
 #pragma unroll
-        for (int j = 0; j < 7; ++j) x[j] += s[j];
-    }
-    if (F)
-        for (uint32_t u = lists + tid; u < units; u += 256) {
-            const OnceUnit* from = mem.units + (blockIdx.x - unit + u);
-            x[7] += ld_device(&from->cross); x[8] += ld_device(&from->c2); x[9] += ld_device(&from->c1);
+            for (int j = 0; j < 7; ++j) x[j] += s[j];
         }
-    group_sums(x, lane, wave, red);
+        if (F)
+            for (uint32_t u = lists + tid; u < units; u += 256) {
+                const OnceUnit* from = mem.units + (blockIdx.x - unit + u);
+                x[7] += ld_device(&from->cross); x[8] += ld_device(&from->c2); x[9] += ld_device(&from->c1);
+            }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1)
+#pragma unroll
+            for (int j = 0; j < 10; ++j) x[j] += __shfl_xor(x[j], d);
+        if (lane == 0) {
+#pragma unroll
+            for (int j = 0; j < 10; ++j) red[wave][j] = x[j];
+        }
+    }
     // a wavefront per rank
     const double* rec = mem.rec + (uint64_t)block * kRecDoubles;
     double* out = mem.out + (uint64_t)block * kRecDoubles;
     const uint32_t q = interval_of(wave), rank = wave == 0 ? m.rank[0] : wave == 1 ? m.rank[1] : wave == 2 ? m.rank[2] : m.rank[3];
-    bad |= n_over != 0;
+    bad |= spilled > o.spill_cap;
     uint32_t value = 0;
+    bool near = false;                                        // of a crowded interval: the value, or the first key of its cell
 #pragma unroll
     for (uint32_t half = 0; half < 2; ++half) {                // one interval after the other: its keys to LDS, then its ranks
         const Range r = range_of(half);
@@ -1082,11 +1148,13 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
 #pragma unroll
             for (uint32_t i = 0; i < 16; ++i) mine += c[i];
             const uint32_t at = wave_scan(mine) - mine;
-            const bool here = want >= at && want - at < mine;
-            const uint32_t cell = here ? bin_of(c, lane * 16, at, want).bin : 0u, least = ~keys[2048 + cell], most = keys[1024 + cell];
-            const uint64_t owner = __builtin_amdgcn_ballot_w64(here), one_value = __builtin_amdgcn_ballot_w64(here && least == most);
-            bad |= one_value == 0;
-            if (owner) value = (uint32_t)__builtin_amdgcn_readlane((int)most, (int)__builtin_ctzll(owner));
+            if (want >= at && want - at < mine) {
+                const Digit f = bin_of(c, lane * 16, at, want);
+                const uint32_t least = ~keys[2048 + f.bin], most = keys[1024 + f.bin];
+                near_key[wave] = least == most ? most : r.first + (f.bin << r.shift);
+                if (least != most) atomicOr(&open, 1u << wave);
+            }
+            near = true;
         } else if (n_keys > keys_cap) bad = true;
         else {
             uint32_t lo = first + (b << sh), hi = lo + (1u << sh) - 1;                       // the least key with `want` + 1 keys up to it
@@ -1105,13 +1173,17 @@ __global__ __launch_bounds__(256) void k_once_select(const TileRow* __restrict__
             value = lo;
         }
     }
-    if (lane == 0) out[R_ORDER + wave] = (double)__builtin_bit_cast(float, value);
     __syncthreads();
+    if (near) { value = near_key[wave]; bad |= (open >> wave & 1u) != 0; }
+    if (lane == 0) out[R_ORDER + wave] = (double)__builtin_bit_cast(float, value);
     if (tid == 0) scans[0] = 0;
     __syncthreads();
     if (bad && lane == 0) scans[0] = 1;
     __syncthreads();
     if (tid < 32) {
+        double x[10];
+#pragma unroll
+        for (int j = 0; j < 10; ++j) x[j] = (red[0][j] + red[1][j]) + (red[2][j] + red[3][j]);
         const double res = F && rows ? once_residual(x[4], x[7], x[9] / (double)cols, x[6], x[8]) : 0.0;
         const Distortion c = C ? once_distortion(x[1], x[2], x[3], x[0], (double)m.numel) : Distortion{0.0, false};
         leave_record(rec, out, res, c.num, x[3], scans[0] != 0 || !(fabs(res) < INFINITY) || c.bad, line + L_REDO);

@@ -644,12 +644,13 @@ struct alignas(16) OnceRow {
     uint32_t n_tasks;                         // 0: the block goes through the passes here
     uint32_t first_unit;                      // of k_once_select
     uint32_t geom;                            // lanes_log | strips << 4 | across << 8 | down << 16 | 16 wavefronts << 24
-    uint32_t off_list, list_cap;              // a list per task; its words
+    uint32_t off_list, list_cap, spill_cap;   // a list per task, then one for what these have no room for; their words
     uint32_t off_cols;                        // [task][column] float2, then the collected keys of both intervals
+    uint32_t pad_[3];
 };
 
 // Words of a block's arrival line.
-enum Line : uint32_t { L_COUNT, L_SCAN3, L_REDO, L_ARRIVED, L_KEYS, L_BRACKET = 8, L_INV_P0 = 12, L_PREFIX = 16, L_RANK = 20 };
+enum Line : uint32_t { L_COUNT, L_SCAN3, L_REDO, L_ARRIVED, L_KEYS, L_SPILL = L_KEYS + 2, L_BRACKET = 8, L_INV_P0 = 12, L_PREFIX = 16, L_RANK = 20 };
 
 // Whether the one pass has done with a block; `scan3` points at L_SCAN3 of the first block.
 __device__ __forceinline__ bool settled(const OnceRow* once, const uint32_t* scan3, uint32_t block)
@@ -1819,12 +1820,13 @@ static void plan_once(Plan& P, uint64_t total)
             o.off_cols = (uint32_t)at;
             at += once_cols_units(o.n_tasks, m.rows ? m.cols : 0) + units64(once_keys_cap(m.numel) * 8);
         }
-        // the lists have room for 1.2 to 1.5 times what is expected on them
+        // The lists have room for 1.2 to 2.4 times what independent coordinates bring: neighbours that are alike bring up to twice as much.  A third of
+        // it is common to a block's tasks.
         const uint64_t tasks = narrow + wide, units_at = at + units64(tasks * sizeof(OnceSums)), most_units = columns + tasks + (uint64_t)(listed / 2048.0) + multi;
         const uint64_t lists_at = units_at + units64(most_units * sizeof(OnceUnit));
         if (taking < (part == n ? kOnceSmallest : kOnceSmallestPart) || taking < n * kOnceMeanBlock || tasks > 0x7fffffffull || most_units > 0x7fffffffull) return;
-        if (lists_at + tasks > room || (double)(room - lists_at - tasks) * 16.0 < 1.2 * listed) continue;
-        const double words = multi ? std::min(1.5, (double)(room - lists_at - tasks) * 16.0 / listed) : 0.0;
+        if (lists_at + tasks > room || (double)(room - lists_at - tasks) * 16.0 < kListSlack * listed) continue;
+        const double words = multi ? std::min(2.0 * kListSlack, (double)(room - lists_at - tasks) * 16.0 / listed) : 0.0;
         P.off_once_sums = P.off_rvec + at * 64; P.off_once_units = P.off_rvec + units_at * 64;
         at = lists_at;
         for (uint32_t i = 0; i < n; ++i) {
@@ -1832,14 +1834,16 @@ static void plan_once(Plan& P, uint64_t total)
             if (o.n_tasks < 2) continue;
             const TileRow& m = P.tiles[i];
             o.off_list = (uint32_t)at;
-            o.list_cap = (uint32_t)(words * listed_share(m.numel) * (double)m.numel / o.n_tasks) / 16 * 16;
-            at += (uint64_t)o.n_tasks * o.list_cap / 16;
+            const double block = words * listed_share(m.numel) * (double)m.numel;
+            o.list_cap = (uint32_t)(block * (2.0 / 3.0) / o.n_tasks) / 16 * 16;
+            o.spill_cap = (uint32_t)(block - (double)o.n_tasks * o.list_cap) / 16 * 16;
+            at += ((uint64_t)o.n_tasks * o.list_cap + o.spill_cap) / 16;
         }
         uint64_t units = 0;
         for (uint32_t i = 0; i < n; ++i) {
             OnceRow& o = P.once[i];
             o.first_unit = (uint32_t)units;
-            if (o.n_tasks > 1) units += once_list_units(o.n_tasks, o.list_cap) + once_col_units(P.tiles[i].rows, P.tiles[i].cols);
+            if (o.n_tasks > 1) units += once_list_units(o) + once_col_units(P.tiles[i].rows, P.tiles[i].cols);
         }
         if (at > room || units > most_units) return;
         P.once_narrow = (uint32_t)narrow; P.once_units = (uint32_t)units; P.once_multi = (uint32_t)multi; P.once_all = part == n;

@@ -181,8 +181,8 @@ def test_equal_keys_take_one_read(env, kind):  # noqa: F811
         if kind == "constant": b.fill_(0.125)
         if kind.startswith("zeros"): b[torch.rand(n, device="cuda:0", generator=gen) < 0.01 * int(kind[6:])] = 0.0
         if kind == "clipped": b.clamp_(-0.012, 0.012)
-    prof = binding.Profiler(blocks, binding.default_profile_params(grad_dtype=1 if kind == "bf16" else 0))
-    prof.step(g.to(torch.bfloat16) if kind == "bf16" else g)
+    prof = binding.Profiler(blocks, binding.default_profile_params(grad_dtype=1 if kind.startswith("bf16") else 0))
+    prof.step(g.to(torch.bfloat16) if kind.startswith("bf16") else g)
     for _ in range(2):
         stats = prof.finalize()[0]
         assert _marked(prof, blocks, stats) == []
@@ -190,3 +190,24 @@ def test_equal_keys_take_one_read(env, kind):  # noqa: F811
             want = _quantiles(prof.state(i)[1])
             for got, w in zip((stats[i].q10, stats[i].q90), want):
                 assert abs(got - w) <= 1e-12 * w, f"{shapes[i]}: {got} {w}"
+
+
+@pytest.mark.parametrize("kind", ["nine neighbours", "rows"])
+def test_neighbours_that_are_alike_take_one_read(env, kind):  # noqa: F811
+    """240 blocks of 1 M and one of 16.8 M whose neighbouring coordinates share their scale: the sample's ranks vary more than those of
+    independent coordinates.  No block's rank is outside its interval, no list too short."""
+    torch, binding = env["torch"], env["binding"]
+    blocks = [(i << 20, 1 << 20, 1024, 1024) for i in range(240)] + [(240 << 20, 1 << 24, 4096, 4096)]
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    g = torch.randn(256 << 20, device="cuda:0", generator=gen).mul_(1e-2)
+    for o, n, r, c in blocks:
+        b = g[o:o + n]
+        if kind == "nine neighbours": b[:n // 9 * 9].view(-1, 9).mul_(torch.randn(n // 9, 1, device="cuda:0", generator=gen).mul_(2.0).exp_())
+        if kind == "rows": b.view(r, c).mul_(torch.randn(r, 1, device="cuda:0", generator=gen).mul_(2.0).exp_())
+    prof = binding.Profiler(blocks)
+    prof.step(g)
+    stats = prof.finalize()[0]
+    assert _marked(prof, blocks, stats) == []
+    for i in range(0, len(blocks), 16):
+        for got, w in zip((stats[i].q10, stats[i].q90), _quantiles(prof.state(i)[1])):
+            assert abs(got - w) <= 1e-12 * w, f"{i}: {got} {w}"
