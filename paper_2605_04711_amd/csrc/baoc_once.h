@@ -12,9 +12,9 @@ namespace baoc {
 //   Eq. 4  The quantiles' first digits are not known in advance, but a sample of 16,384 coordinates places them within 1.2 % of the
 //          ranks: keys inside the two intervals are listed, those below are counted.  Equal keys: zeros lie below every interval; an
 //          interval of at most 512 keys is counted key by key and not listed; of more keys in a rank's bins than can be ordered, k_once_select
-//          counts those of 256 to 1,024 cells of the bins, and a cell of one value gives the rank.
-//          Where a rank turns out to lie outside its interval, the lists are too short, a crowded cell has several values, or a sum is not finite,
-//          the block is marked and goes through the passes above.
+//          counts those of 256 to 1,024 cells of the bins, and a cell of one value gives the rank, one of several another walk over the lists.
+//          Where a rank turns out to lie outside its interval, the lists are too short, or a sum is not finite, the block is marked and goes through
+//          the passes above.
 //          (Which keys are listed where is not the same from run to run; what is taken from them is, and so is what is marked.)
 //   Eq. 6  With q = p / p0 - 1 for a fixed p0, sum ((p/p-bar - 1) theta)^2 = k^2 sum (q theta)^2 + 2 k (k-1) sum q theta^2 +
 //          (k-1)^2 sum theta^2, k = p0 / p-bar.  For k well above 1 the terms are k^2 times their sum, so a rare large p (v = 0 at a
@@ -924,7 +924,7 @@ __global__ __launch_bounds__(256, 4) void k_once_select(const TileRow* __restric
 {
     __shared__ alignas(16) uint32_t keys[2 * kOnceKeys];      // a unit's of either interval; then the block's of one, 512 more than there are at most
     __shared__ double red[4][10];
-    __shared__ uint32_t n_below[2], n_in[2], n_mine[2], first_mine[2], bin[4], bin_at[4], bin_n[4], scans[4], near_key[4], open;
+    __shared__ uint32_t n_below[2], n_in[2], n_mine[2], first_mine[2], bin[4], bin_at[4], bin_n[4], scans[4], near_key[4], near_rank[4], open;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = scalar_wave_index();
     const uint32_t block = find_owner(mem.n_blocks, blockIdx.x, lane, [&](uint32_t i) { return mem.rows[i].first_unit; });
     const OnceRow& o = mem.rows[block];
@@ -950,7 +950,7 @@ __global__ __launch_bounds__(256, 4) void k_once_select(const TileRow* __restric
     // Keys below and in the intervals, the bins that hold the ranks, the keys before these and in them.
     auto digits = [&]() {
         if (tid < 2) n_below[tid] = n_mine[tid] = 0;
-        if (tid < 4) { bin[tid] = ~0u; bin_at[tid] = bin_n[tid] = near_key[tid] = 0; }
+        if (tid < 4) { bin[tid] = ~0u; bin_at[tid] = bin_n[tid] = near_key[tid] = near_rank[tid] = 0; }
         if (tid == 4) open = 0;
         __syncthreads();
         uint32_t n[2] = {0, 0};
@@ -1001,13 +1001,14 @@ __global__ __launch_bounds__(256, 4) void k_once_select(const TileRow* __restric
 
     // a wavefront's part of a task's list, or of the common one that stands after these
     const uint32_t cap = scalar_u32(o.list_cap), spilled = scalar_u32(line[L_SPILL]), parts = once_parts(cap), id = unit * 4 + wave;
-    struct Part { uint32_t* from; uint32_t n; };
+    struct Part { uint32_t* from; uint32_t n, room; };
     auto part_of = [&](uint32_t id) {
         const uint32_t task = min(id / max(parts, 1u), n_tasks), at = (id - task * parts) * kOncePart, whole = task < n_tasks ? cap : o.spill_cap;
         const uint32_t all = min(whole, task < n_tasks ? sums[task].n_list : spilled);
-        return Part{reinterpret_cast<uint32_t*>(mem.base + (uint64_t)o.off_list * 64) + ((uint64_t)task * cap + at), all > at ? (uint32_t)min(all - at, kOncePart) : 0u};
+        return Part{reinterpret_cast<uint32_t*>(mem.base + (uint64_t)o.off_list * 64) + ((uint64_t)task * cap + at), all > at ? (uint32_t)min(all - at, kOncePart) : 0u,
+                    (uint32_t)min(whole - at, kOncePart)};
     };
-    Part own = unit < lists ? part_of(id) : Part{nullptr, 0u};
+    Part own = unit < lists ? part_of(id) : Part{nullptr, 0u, 0u};
     own.n = scalar_u32(own.n);
     bool have = false;
     if (unit < lists && __syncthreads_or(own.n != 0)) {
@@ -1042,16 +1043,23 @@ __global__ __launch_bounds__(256, 4) void k_once_select(const TileRow* __restric
                 if (r[1].crowded) keys[kOnceKeys + i] = 0;
             }
             __syncthreads();
+            uint32_t kept = 0;
             walk([&](uint32_t key, bool there) {
                 const bool low = key - r[0].first < r[0].width, high = key - r[1].first < r[1].width;
                 const bool to_cell = there && ((low && r[0].crowded) || (high && r[1].crowded));
+                // the part keeps these keys, in front, for the case that their cell has several values
+                const uint64_t hits = __builtin_amdgcn_ballot_w64(to_cell);
                 if (to_cell) {
+                    st_device(&own.from[__builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, kept))], key);
                     uint32_t* cell = keys + high * kOnceKeys + (high ? (key - r[1].first) >> r[1].shift : (key - r[0].first) >> r[0].shift);
                     count_alike(keys, (uint32_t)(cell - keys));
                     if (cell[1u << cells_log] < key) atomicMax(cell + (1u << cells_log), key);
                     if (cell[2u << cells_log] < ~key) atomicMax(cell + (2u << cells_log), ~key);
                 } else if ((low || high) && there) keep(key, high);
+                kept += (uint32_t)__builtin_popcountll(hits);
             });
+            // how many, in the part's last word; a key there (keys are below 2^31) if it is full
+            if (own.n && lane == 0 && kept < own.room) st_device(&own.from[own.room - 1], kept | 1u << 31);
         }
         // the unit's keys go to the block's in one piece: an atomic for each would be a round trip for each
         __syncthreads();
@@ -1152,6 +1160,7 @@ __global__ __launch_bounds__(256, 4) void k_once_select(const TileRow* __restric
                 const Digit f = bin_of(c, lane * 16, at, want);
                 const uint32_t least = ~keys[2048 + f.bin], most = keys[1024 + f.bin];
                 near_key[wave] = least == most ? most : r.first + (f.bin << r.shift);
+                near_rank[wave] = f.rank;
                 if (least != most) atomicOr(&open, 1u << wave);
             }
             near = true;
@@ -1174,7 +1183,54 @@ __global__ __launch_bounds__(256, 4) void k_once_select(const TileRow* __restric
         }
     }
     __syncthreads();
-    if (near) { value = near_key[wave]; bad |= (open >> wave & 1u) != 0; }
+    // Ranks whose cell has several values: 11 bits at a time from what the parts have kept.
+    const uint32_t n_parts = n_tasks * parts + once_parts(o.spill_cap), share = max(1u, 256 / max(n_parts, 1u));      // threads a part
+#pragma unroll 1
+    for (uint32_t half = 0; half < 2; ++half) {
+        const uint32_t mine = scalar_u32(open) & (one_interval ? (half ? 0u : 15u) : 3u << (2 * half));
+        if (mine == 0) continue;
+        uint32_t left = range_of(half).shift;
+        while (left > 0) {
+            const uint32_t bits = min(left, 11u);
+            __syncthreads();
+            for (uint32_t i = tid; i < 2 * kOnceKeys; i += 256) keys[i] = 0;
+            __syncthreads();
+            const uint32_t from_key[4] = {near_key[0], near_key[1], near_key[2], near_key[3]};
+            for (uint32_t i = tid / share; i < n_parts; i += 256 / share) {
+                const Part p = part_of(i);
+                if (p.n == 0) continue;
+                const uint32_t word = ld_device(&p.from[p.room - 1]), n = word >> 31 ? word & 0x7fffffffu : p.room;
+                for (uint32_t k = tid % share; k < n; k += 8 * share) {
+                    uint32_t key[8];
+#pragma unroll
+                    for (uint32_t e = 0; e < 8; ++e) key[e] = ld_device(&p.from[min(k + e * share, n - 1)]);
+#pragma unroll
+                    for (uint32_t e = 0; e < 8; ++e)
+#pragma unroll
+                        for (uint32_t t = 0; t < 4; ++t) {
+                            const uint32_t off = key[e] - from_key[t];
+                            if (k + e * share < n && (mine >> t & 1u) && off < 1u << left) count_alike(keys, 2048 * t + (off >> (left - bits)));
+                        }
+                }
+            }
+            __syncthreads();
+            left -= bits;
+            if (mine >> wave & 1u) {
+                const uint32_t want = near_rank[wave];
+                uint32_t c[32], mine_n = 0;
+                load_bins(c, keys + 2048 * wave + 32 * lane);
+#pragma unroll
+                for (uint32_t i = 0; i < 32; ++i) mine_n += c[i];
+                const uint32_t at = wave_scan(mine_n) - mine_n;
+                if (want >= at && want - at < mine_n) {
+                    const Digit f = bin_of(c, 32 * lane, at, want);
+                    near_key[wave] += f.bin << left; near_rank[wave] = f.rank;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    if (near) value = near_key[wave];
     if (lane == 0) out[R_ORDER + wave] = (double)__builtin_bit_cast(float, value);
     if (tid == 0) scans[0] = 0;
     __syncthreads();

@@ -163,10 +163,10 @@ def _quantiles(v):
     return out
 
 
-@pytest.mark.parametrize("kind", ["zero", "constant", "zeros 95", "zeros 90", "clipped", "bf16"])
+@pytest.mark.parametrize("kind", ["zero", "constant", "zeros 95", "zeros 90", "clipped", "bf16", "half rounded", "bf16 rows"])
 def test_equal_keys_take_one_read(env, kind):  # noqa: F811
     """After one step: dead blocks, mostly untouched ones, gradients clipped by value, constant ones, and bf16 gradients of large blocks
-    (42,000 of 16.8 M have the same v at the upper quantile).  Quantiles are those of the sorted v, and no block goes through the passes."""
+    (42,000 of 16.8 M have the same v at the upper quantile), also next to others between them, and of rows of which most are untouched.  Quantiles are those of the sorted v, and no block goes through the passes."""
     torch, binding = env["torch"], env["binding"]
     shapes = [(1500, 1000), (1500000, 0), (4096, 4096), FILLER]
     blocks, at = [], 0
@@ -181,8 +181,11 @@ def test_equal_keys_take_one_read(env, kind):  # noqa: F811
         if kind == "constant": b.fill_(0.125)
         if kind.startswith("zeros"): b[torch.rand(n, device="cuda:0", generator=gen) < 0.01 * int(kind[6:])] = 0.0
         if kind == "clipped": b.clamp_(-0.012, 0.012)
+        if kind == "half rounded": b.copy_(torch.where(torch.rand(n, device="cuda:0", generator=gen) < 0.5, b.to(torch.bfloat16).float(), b))
+        if kind == "bf16 rows" and c: b.view(r, c)[torch.rand(r, device="cuda:0", generator=gen) < 0.8] = 0.0
     prof = binding.Profiler(blocks, binding.default_profile_params(grad_dtype=1 if kind.startswith("bf16") else 0))
     prof.step(g.to(torch.bfloat16) if kind.startswith("bf16") else g)
+    if kind == "bf16 rows": prof.step(g.flip(0).to(torch.bfloat16))
     for _ in range(2):
         stats = prof.finalize()[0]
         assert _marked(prof, blocks, stats) == []
@@ -192,9 +195,9 @@ def test_equal_keys_take_one_read(env, kind):  # noqa: F811
                 assert abs(got - w) <= 1e-12 * w, f"{shapes[i]}: {got} {w}"
 
 
-@pytest.mark.parametrize("kind", ["nine neighbours", "rows"])
+@pytest.mark.parametrize("kind", ["nine neighbours", "rows", "equal in a row"])
 def test_neighbours_that_are_alike_take_one_read(env, kind):  # noqa: F811
-    """240 blocks of 1 M and one of 16.8 M whose neighbouring coordinates share their scale: the sample's ranks vary more than those of
+    """240 blocks of 1 M and one of 16.8 M whose neighbouring coordinates share their scale, or their value: the sample's ranks vary more than those of
     independent coordinates.  No block's rank is outside its interval, no list too short."""
     torch, binding = env["torch"], env["binding"]
     blocks = [(i << 20, 1 << 20, 1024, 1024) for i in range(240)] + [(240 << 20, 1 << 24, 4096, 4096)]
@@ -204,6 +207,7 @@ def test_neighbours_that_are_alike_take_one_read(env, kind):  # noqa: F811
         b = g[o:o + n]
         if kind == "nine neighbours": b[:n // 9 * 9].view(-1, 9).mul_(torch.randn(n // 9, 1, device="cuda:0", generator=gen).mul_(2.0).exp_())
         if kind == "rows": b.view(r, c).mul_(torch.randn(r, 1, device="cuda:0", generator=gen).mul_(2.0).exp_())
+        if kind == "equal in a row": b.view(r, c).copy_(torch.randn(r, 1, device="cuda:0", generator=gen).expand(r, c))
     prof = binding.Profiler(blocks)
     prof.step(g)
     stats = prof.finalize()[0]
