@@ -435,7 +435,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
     __shared__ alignas(16) uint32_t hist[kHistWords];
     __shared__ alignas(16) uint32_t staged[NW * kOnceStage];
     __shared__ alignas(16) float rowsum[2][NW * 32];
-    __shared__ double settled_sums[C ? 4 : 1][C ? 64 * NW : 1];
+    __shared__ double settled_sums[C ? 3 : 1][C ? 64 * NW : 1];
     __shared__ double part[NW][10], total[10];
     __shared__ uint32_t n_listed, below[NW][2], sel[8], scans[4];
     constexpr uint32_t THREADS = 64 * NW;
@@ -490,14 +490,15 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
     __syncthreads();
 
     double s2 = 0.0, r2 = 0.0;
-    float fa = 0.f, fb = 0.f, fd = 0.f, fq = 0.f;
-    // A lane adds at most 256 terms in fp32 before they go to fp64, in LDS: there are no registers to spare
-    if (C) settled_sums[0][tid] = settled_sums[1][tid] = settled_sums[2][tid] = settled_sums[3][tid] = 0.0;
+    float fa = 0.f, fb = 0.f, fd = 0.f;
+    // A lane adds at most 256 terms in fp32 before they go to fp64, in LDS: there are no registers to spare.  q, whose sum makes p-bar, four.
+    double sum_q = 0.0;
+    if (C) settled_sums[0][tid] = settled_sums[1][tid] = settled_sums[2][tid] = 0.0;
     auto settle = [&]() {
         if (!C) return;
         const uint32_t at = wave * 64 + here(lane);
-        settled_sums[0][at] += (double)fq; settled_sums[1][at] += (double)fa; settled_sums[2][at] += (double)fb; settled_sums[3][at] += (double)fd;
-        fq = fa = fb = fd = 0.f;
+        settled_sums[0][at] += (double)fa; settled_sums[1][at] += (double)fb; settled_sums[2][at] += (double)fd;
+        fa = fb = fd = 0.f;
     };
     uint32_t n_below[2] = {0, 0}, n_stage = 0;
     uint32_t* stage = staged + wave * kOnceStage;
@@ -581,14 +582,16 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
     };
     auto general = [&](float v) { return __builtin_fmaf(preconditioner(v, eps), inv_p0, -1.0f); };
     auto distort = [&](const float (&x)[4], const float (&th)[4], auto q_of, auto ok) {
+        float four = 0.f;
 #pragma unroll
         for (uint32_t e = 0; e < 4; ++e) {
             const float q = ok(e) ? q_of(x[e]) : 0.f, z = q * th[e];
-            fq += q;
+            four += q;
             fa = __builtin_fmaf(z, z, fa);
             fb = __builtin_fmaf(z, th[e], fb);
             fd = __builtin_fmaf(th[e], th[e], fd);
         }
+        sum_q += (double)four;
     };
     // Four elements of which the first `skip` do not count: lanes past the end of a row, or of a block, read its last four again.
     auto masked = [&](float (&x)[4], TV vt, uint32_t skip) {
@@ -856,7 +859,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
         else { walk(three, one); }
     }
     settle();
-    const double mine[10] = {C ? settled_sums[0][tid] : 0.0, C ? settled_sums[1][tid] : 0.0, C ? settled_sums[2][tid] : 0.0, C ? settled_sums[3][tid] : 0.0,
+    const double mine[10] = {sum_q, C ? settled_sums[0][tid] : 0.0, C ? settled_sums[1][tid] : 0.0, C ? settled_sums[2][tid] : 0.0,
                              s2, 0.0, r2, cross, c2, c1};
     __syncthreads();                                          // `part` has been read
 #pragma unroll

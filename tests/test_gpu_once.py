@@ -215,3 +215,28 @@ def test_neighbours_that_are_alike_take_one_read(env, kind):  # noqa: F811
     for i in range(0, len(blocks), 16):
         for got, w in zip((stats[i].q10, stats[i].q90), _quantiles(prof.state(i)[1])):
             assert abs(got - w) <= 1e-12 * w, f"{i}: {got} {w}"
+
+
+@pytest.mark.parametrize("share", [0.15, 0.2, 0.3, 0.35, 0.45])
+def test_mean_of_p_over_long_runs_of_one_value(env, share):  # noqa: F811
+    """v is 1/4 over a block's first part and 1 over the rest, so that a lane adds one value of p / p0 - 1 again and again; theta is one at every 1,021st
+    coordinate, which leaves the other sums of C exact.  What is rounded are the two values, by at most 2^-25, and their squares, by 2^-24: C is within
+    2^-24 of 64 bits for these, and p-bar adds 2^-25 (p/p-bar) / |p/p-bar - 1|, at most 2^-24 * 1.5 for these shares; 1.5e-7 is 2^-24 * 2.5.
+    (Sums of 256 fp32 terms: up to 8.8e-7.)"""
+    torch, binding = env["torch"], env["binding"]
+    shapes = [(1 << 22, 0), (2048, 2048), (65536, 0), FILLER]
+    blocks, at = [], 0
+    for r, c in shapes:
+        n = r * c if c else r
+        blocks.append((at, n, r if c else 0, c)); at += n
+    g, th = torch.full((at,), 2.0, device="cuda:0"), torch.zeros(at, device="cuda:0")
+    for o, n, _, _ in blocks:
+        g[o:o + int(share * n)] = 1.0
+        th[o + 7:o + n:1021] = 1.0
+    prof = binding.Profiler(blocks, binding.default_profile_params(beta_v=0.75))
+    prof.step(g)
+    stats = prof.finalize(theta=th)[0]
+    for i, (o, n, _, _) in enumerate(blocks):
+        p, t = 1.0 / (prof.state(i)[1].double().sqrt() + 1e-12), th[o:o + n].double()
+        C = (((p / p.mean() - 1.0) * t).pow(2).sum().sqrt() / t.pow(2).sum().sqrt()).item()
+        assert abs(stats[i].C - C) <= 1.5e-7 * C, f"{shapes[i]}: {stats[i].C} {C}"
