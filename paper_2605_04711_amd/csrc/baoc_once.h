@@ -34,12 +34,12 @@ constexpr float kLeastP0 = 1e-30f;                        // where every p is ze
 typedef f4 f4_any __attribute__((aligned(4)));            // four elements at any alignment
 
 struct OnceSums {                                         // of a task
-    double q, a, b, d, s2, rho, r2;                      // rho = sum r^2 / sum r
+    double q, a, b, d, s2, rho, r2, all;                  // rho = sum r^2 / sum r; all = sum v
     uint32_t n[2];                                        // keys below the two intervals
     uint32_t n_list, pad_;
 };
 
-struct OnceUnit { double cross, c2, c1, pad_; };          // of 64 columns: sum of c t, c^2, c
+struct OnceUnit { double cross, c2; };                    // of 64 columns: sum of c t, c^2
 
 struct OnceMem {
     char* base;                                           // the region
@@ -313,9 +313,7 @@ __global__ __launch_bounds__(1024) void k_bracket(const float* __restrict__ v_al
 // The same value, formed anew where it stands: what is cheap to form from it is not kept over a loop.
 __device__ __forceinline__ uint32_t here(uint32_t x) { asm volatile("" : "+v"(x)); return x; }
 
-// Sums of Q values over rows of 16 lanes by a halving exchange: a lane is left with the sum number (lane >> kRowShift) & (Q - 1).
-template <uint32_t Q> constexpr uint32_t kRowShift = Q == 4 ? 2 : 3;
-template <uint32_t Q> constexpr uint32_t kRowLane = Q == 4 ? 3u : Q == 2 ? 7u : 15u;   // the bits of a lane that do not matter to it
+// Sums of four values over rows of 16 lanes by a halving exchange: a lane is left with the sum number (lane >> 2) & 3.
 __device__ __forceinline__ float rows_sum(const float (&s)[4], uint32_t lane)
 {
     const bool b3 = lane & 8u, b2 = lane & 4u;
@@ -326,20 +324,25 @@ __device__ __forceinline__ float rows_sum(const float (&s)[4], uint32_t lane)
     a += dpp<0x4E, 0xf>(0.f, a);
     return a + dpp<0xB1, 0xf>(0.f, a);
 }
-__device__ __forceinline__ float rows_sum(const float (&s)[2], uint32_t lane)
+__device__ __forceinline__ double scalar_f64(double x)
 {
-    const bool b3 = lane & 8u;
-    float a = (b3 ? s[1] : s[0]) + dpp<0x128, 0xf>(0.f, b3 ? s[0] : s[1]);
-    a += dpp<0xB1, 0xf>(0.f, a);
-    a += dpp<0x4E, 0xf>(0.f, a);
-    return a + dpp<0x141, 0xf>(0.f, a);
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    return __builtin_bit_cast(double, (uint64_t)scalar_u32((uint32_t)(b >> 32)) << 32 | scalar_u32((uint32_t)b));
 }
-__device__ __forceinline__ float rows_sum(const float (&s)[1], uint32_t)
+template <int CTRL> __device__ __forceinline__ double add_lane(double x)
 {
-    float a = s[0] + dpp<0xB1, 0xf>(0.f, s[0]);
-    a += dpp<0x4E, 0xf>(0.f, a);
-    a += dpp<0x141, 0xf>(0.f, a);
-    return a + dpp<0x128, 0xf>(0.f, a);
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = dpp_u32<CTRL, 0xf>(0u, (uint32_t)b), hi = dpp_u32<CTRL, 0xf>(0u, (uint32_t)(b >> 32));
+    return x + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+// Sum over the 4, 8 or 16 lanes that share one of a row's Q = 4, 2 or 1 numbers.
+template <uint32_t Q> __device__ __forceinline__ double part_sum(double x)
+{
+    x = add_lane<0xB1>(x);
+    x = add_lane<0x4E>(x);
+    if (Q <= 2) x = add_lane<0x141>(x);
+    if (Q == 1) x = add_lane<0x128>(x);
+    return x;
 }
 // A lane's value and that of the lane 16, or 32, away.  (The halves are copied out first: a bit cast of a vector's element takes the first.)
 __device__ __forceinline__ float add_rows16(float x)
@@ -663,7 +666,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
         }
         flush(true);
     }
-    double cross = 0.0, c2 = 0.0, c1 = 0.0;
+    double cross = 0.0, c2 = 0.0;
     auto walk = [&](auto strips, auto quads) {
         constexpr uint32_t K = decltype(strips)::value, Q = decltype(quads)::value;
         const uint32_t geom = scalar_u32(o.geom), lanes_log = geom & 15u, across = (geom >> 8) & 31u, down = (geom >> 16) & 255u;
@@ -677,7 +680,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
 #pragma unroll
         for (uint32_t k = 0; k < K; ++k) at[k] = lrow() * cols + once_first_col(first_col(k) + 4 * lcol(), cols);
         uint32_t wide = 1; while (wide < across) wide *= 2;
-        const float inv_cols = 1.0f / (float)cols;
+        const double inv_cols = scalar_f64(1.0 / (double)cols);
         auto first_row = [&](uint32_t row, uint32_t q) { return once_first_row(row + (q << rpl), rpl, rows); };
         f4 nx[Q][K]; TV nt[Q][K];
         auto issue = [&](uint32_t row) {
@@ -751,26 +754,33 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
             issue_theta(next);
             batch_done(i);
             if (F) {
-                // A row's sum: over the lanes, and over the wavefronts side by side through LDS, [row of a load][wavefront][load]
-                float r[Q];
+                // A row's sum: of a strip, 256 columns at most, in fp32 over the lanes; over the strips and the wavefronts side by side in fp64 through
+                // LDS, [row of a load][wavefront][load][strip], one of a row's loads for every 16 / Q lanes
+                float sums[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (uint32_t q = 0; q < Q; ++q) {
-                    r[q] = 0.f;
+                for (uint32_t q = 0; q < Q; ++q)
 #pragma unroll
-                    for (uint32_t k = 0; k < K; ++k) r[q] += (x[q][k][0] + x[q][k][1]) + (x[q][k][2] + x[q][k][3]);
-                }
-                float mine = rows_sum(r, lane);
+                    for (uint32_t k = 0; k < K; ++k) sums[q * K + k] = (x[q][k][0] + x[q][k][1]) + (x[q][k][2] + x[q][k][3]);
+                float mine = rows_sum(sums, lane);
                 if (lanes_log > 4) mine = add_rows16(mine);
                 if (lanes_log > 5) mine = add_rows32(mine);
                 float* rs = rowsum[i & 1] + wrow * (wide * 16);
                 const uint32_t l = here(lane);
-                if ((l & ((1u << lanes_log) - 16u + kRowLane<Q>)) == 0 && wrow < down)
-                    rs[((l >> lanes_log) * wide + wcol) * Q + ((l >> kRowShift<Q>) & (Q - 1))] = mine;
+                if ((l & ((1u << lanes_log) - 16u + 3u)) == 0 && wrow < down) rs[((l >> lanes_log) * wide + wcol) * 4 + ((l >> 2) & 3u)] = mine;
                 if (across > 1) lds_barrier(); else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                const bool there = (l & 15u) < across && wrow < down;
+                constexpr uint32_t kLanes = 16 / Q;           // lanes to a load
+                const float* from = rs + (l >> lanes_log) * wide * 4 + ((l & 15u) / kLanes) * K;
+                double row_sum = 0.0;
 #pragma unroll
-                for (uint32_t q = 0; q < Q; ++q) r[q] = there ? rs[((l >> lanes_log) * wide + (l & 15u)) * Q + q] : 0.f;
-                share_rows(r, rows_sum(r, lane) * inv_cols);
+                for (uint32_t w0 = 0; w0 < NW; w0 += kLanes) {
+                    const uint32_t w = w0 + (l & (kLanes - 1));
+                    if (w < across && wrow < down) {
+#pragma unroll
+                        for (uint32_t k = 0; k < K; ++k) row_sum += (double)from[w * 4 + k];
+                    }
+                }
+                float r[Q];
+                share_rows(r, (float)(part_sum<Q>(row_sum) * inv_cols));
 #pragma unroll
                 for (uint32_t q = 0; q < Q; ++q) {
                     const double rd = (double)r[q];
@@ -798,11 +808,12 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
         rho = wave_total(rho);
         if (lane == 0) { part[wave][0] = rho; part[wave][1] = t2; }
         __syncthreads();                                      // and the last keys have left `staged`
-        rho = t2 = 0.0;
+        double all = 0.0;
+        t2 = 0.0;
 #pragma unroll 1
-        for (uint32_t w = 0; w < NW; ++w) { rho += part[w][0]; t2 += part[w][1]; }
-        rho = rho > 0.0 ? t2 / rho * (double)cols : 0.0;
-        if (tid == 0) total[5] = rho;
+        for (uint32_t w = 0; w < NW; ++w) { all += part[w][0]; t2 += part[w][1]; }
+        rho = all > 0.0 ? t2 / all * (double)cols : 0.0;
+        if (tid == 0) { total[5] = rho; total[7] = all; }
         float2* to = reinterpret_cast<float2*>(mem.base + (uint64_t)o.off_cols * 64) + (uint64_t)local * cols;
         double* sh = reinterpret_cast<double*>(staged);       // 256 per wavefront
         static_assert(sizeof(staged) >= NW * 256 * sizeof(double), "a strip of every wavefront");
@@ -841,7 +852,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
                     if (single) {
                         const double mean = (double)(float)(cs[k][e] / (double)rows);
                         cross = __builtin_fma(mean, ts[k][e], cross);
-                        c2 = __builtin_fma(mean, mean, c2); c1 += mean;
+                        c2 = __builtin_fma(mean, mean, c2);
                     } else {
                         const float cf = (float)cs[k][e];
                         to[base + e] = float2{cf, rho != 0.0 ? (float)(ts[k][e] / rho - (double)cf) : 0.f};
@@ -860,11 +871,11 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
     }
     settle();
     const double mine[10] = {sum_q, C ? settled_sums[0][tid] : 0.0, C ? settled_sums[1][tid] : 0.0, C ? settled_sums[2][tid] : 0.0,
-                             s2, 0.0, r2, cross, c2, c1};
+                             s2, 0.0, r2, 0.0, cross, c2};
     __syncthreads();                                          // `part` has been read
 #pragma unroll
     for (int j = 0; j < 10; ++j) {
-        const double w = j < 7 || single ? wave_total(mine[j]) : 0.0;
+        const double w = j != 5 && j != 7 && (j < 7 || single) ? wave_total(mine[j]) : 0.0;
         if (lane == 0) part[wave][j] = w;
     }
     if (lane == 0) {
@@ -875,12 +886,12 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
         double x = 0.0;
 #pragma unroll 1
         for (uint32_t w = 0; w < NW; ++w) x += part[w][tid];
-        if (tid != 5) total[tid] = x;
+        if (tid != 5 && tid != 7) total[tid] = x;
     }
     __syncthreads();
     if (!single) {
         OnceSums* sums = mem.sums + (NW == 8 ? blockIdx.x : mem.narrow_tasks + blockIdx.x);
-        if (tid < 7) reinterpret_cast<double*>(sums)[tid] = total[tid];
+        if (tid < 8) reinterpret_cast<double*>(sums)[tid] = total[tid];
         if (tid >= 64 && tid < 66) {
             uint32_t n = 0;
             for (uint32_t w = 0; w < NW; ++w) n += below[w][tid - 64];
@@ -910,7 +921,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
     const double* rec = mem.rec + (uint64_t)block * kRecDoubles;
     double* out = mem.out + (uint64_t)block * kRecDoubles;
     if (tid < 32) {
-        const double res = F && rows ? once_residual(total[4], total[7], total[9] / (double)cols, total[6], total[8]) : 0.0;
+        const double res = F && rows ? once_residual(total[4], total[8], total[7] / ((double)rows * (double)cols), total[6], total[9]) : 0.0;
         const Distortion c = C ? once_distortion(total[1], total[2], total[3], total[0], (double)numel) : Distortion{0.0, false};
         leave_record(rec, out, res, c.num, total[3], !(fabs(res) < INFINITY) || c.bad, line + L_REDO);
         if (tid < 4) out[R_ORDER + tid] = (double)__builtin_bit_cast(float, sel[tid]);
@@ -1101,8 +1112,8 @@ __global__ __launch_bounds__(256, 4) void k_once_select(const TileRow* __restric
             c = (sh[lane] + sh[64 + lane]) + (sh[128 + lane] + sh[192 + lane]);
             t = (sh[256 + lane] + sh[320 + lane]) + (sh[384 + lane] + sh[448 + lane]);
             const double mean = at < cols ? (double)(float)(c / (double)rows) : 0.0;
-            const double cross = wave_total(mean * t), c2 = wave_total(mean * mean), c1 = wave_total(mean);
-            if (lane == 0) { OnceUnit* u = mem.units + blockIdx.x; st_device(&u->cross, cross); st_device(&u->c2, c2); st_device(&u->c1, c1); }
+            const double cross = wave_total(mean * t), c2 = wave_total(mean * mean);
+            if (lane == 0) { OnceUnit* u = mem.units + blockIdx.x; st_device(&u->cross, cross); st_device(&u->c2, c2); }
         }
     }
     if (!arrive_last(line + L_ARRIVED, units)) return;
@@ -1113,12 +1124,12 @@ __global__ __launch_bounds__(256, 4) void k_once_select(const TileRow* __restric
         for (uint32_t i = tid; i < n_tasks; i += 256) {
             const double* s = reinterpret_cast<const double*>(sums + i);
 #pragma unroll
-            for (int j = 0; j < 7; ++j) x[j] += s[j];
+            for (int j = 0; j < 8; ++j) x[j] += s[j];
         }
         if (F)
             for (uint32_t u = lists + tid; u < units; u += 256) {
                 const OnceUnit* from = mem.units + (blockIdx.x - unit + u);
-                x[7] += ld_device(&from->cross); x[8] += ld_device(&from->c2); x[9] += ld_device(&from->c1);
+                x[8] += ld_device(&from->cross); x[9] += ld_device(&from->c2);
             }
 #pragma unroll
         for (int d = 32; d > 0; d >>= 1)
@@ -1243,7 +1254,7 @@ __global__ __launch_bounds__(256, 4) void k_once_select(const TileRow* __restric
         double x[10];
 #pragma unroll
         for (int j = 0; j < 10; ++j) x[j] = (red[0][j] + red[1][j]) + (red[2][j] + red[3][j]);
-        const double res = F && rows ? once_residual(x[4], x[7], x[9] / (double)cols, x[6], x[8]) : 0.0;
+        const double res = F && rows ? once_residual(x[4], x[8], x[7] / ((double)rows * (double)cols), x[6], x[9]) : 0.0;
         const Distortion c = C ? once_distortion(x[1], x[2], x[3], x[0], (double)m.numel) : Distortion{0.0, false};
         leave_record(rec, out, res, c.num, x[3], scans[0] != 0 || !(fabs(res) < INFINITY) || c.bad, line + L_REDO);
     }
