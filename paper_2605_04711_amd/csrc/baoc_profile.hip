@@ -644,9 +644,8 @@ struct alignas(16) OnceRow {
     uint32_t n_tasks;                         // 0: the block goes through the passes here
     uint32_t first_unit;                      // of k_once_select
     uint32_t geom;                            // lanes_log | strips << 4 | across << 8 | down << 16 | 16 wavefronts << 24
-    uint32_t off_list, list_cap, spill_cap;   // a list per task, then one for what these have no room for; their words
+    uint32_t off_list, list_cap;              // a list per task, its words; then one of half their size for what these have no room for
     uint32_t off_cols;                        // [task][column] float2, then the collected keys of both intervals
-    uint32_t pad_[3];
 };
 
 // Words of a block's arrival line.
@@ -1834,10 +1833,8 @@ static void plan_once(Plan& P, uint64_t total)
             if (o.n_tasks < 2) continue;
             const TileRow& m = P.tiles[i];
             o.off_list = (uint32_t)at;
-            const double block = words * listed_share(m.numel) * (double)m.numel;
-            o.list_cap = (uint32_t)(block * (2.0 / 3.0) / o.n_tasks) / 16 * 16;
-            o.spill_cap = (uint32_t)(block - (double)o.n_tasks * o.list_cap) / 16 * 16;
-            at += ((uint64_t)o.n_tasks * o.list_cap + o.spill_cap) / 16;
+            o.list_cap = (uint32_t)(words * listed_share(m.numel) * (double)m.numel * (2.0 / 3.0) / o.n_tasks) / 16 * 16;
+            at += ((uint64_t)o.n_tasks * o.list_cap + once_spill(o)) / 16;
         }
         uint64_t units = 0;
         for (uint32_t i = 0; i < n; ++i) {

@@ -426,11 +426,11 @@ static int check_once()
                 (o.geom >> 24 ? wide : narrow) += o.n_tasks;
                 if (o.n_tasks == 1) continue;
                 units += once_list_units(o) + once_col_units(m.rows, m.cols);
-                CHECK(o.off_cols == fixed && o.list_cap % 16 == 0 && o.list_cap > 0 && o.spill_cap % 16 == 0, "%u x %u", m.rows, m.cols);
+                CHECK(o.off_cols == fixed && o.list_cap % 16 == 0 && o.list_cap > 0, "%u x %u", m.rows, m.cols);
                 fixed += once_cols_units(o.n_tasks, m.rows ? m.cols : 0) + ((uint64_t)once_keys_cap(m.numel) * 8 + 63) / 64;
                 first_list = std::min<uint64_t>(first_list, o.off_list);
                 CHECK(lists == 0 || o.off_list == lists, "%u x %u", m.rows, m.cols);
-                lists = o.off_list + ((uint64_t)o.n_tasks * o.list_cap + o.spill_cap) / 16;
+                lists = o.off_list + ((uint64_t)o.n_tasks * o.list_cap + once_spill(o)) / 16;
             }
             CHECK(narrow == P.once_narrow && narrow + wide == P.once_tasks && units == P.once_units && P.once_all == (part == l->size()), " ");
             CHECK(P.off_rvec + fixed * 64 <= P.off_once_sums && P.off_once_sums + P.once_tasks * sizeof(OnceSums) <= P.off_once_units, " ");

@@ -70,6 +70,14 @@ def test_largest_vectors_of_the_static_workspace(n, chunk_groups, chunk_slices, 
     assert ws([(0, n)], grad_dtype=bf16, chunk_groups=chunk_groups, chunk_slices=chunk_slices) <= binding.STATIC_WORKSPACE_BYTES
 
 
+@pytest.mark.parametrize("rows,cols,grad,count", [(64, 64, 1, 2214), (1, 0, 0, 6664), (1, 0, 1, 6838), (16, 16, 0, 6601), (300, 0, 1, 6049)])
+def test_static_workspace_takes_as_many_blocks_as_ever(rows, cols, grad, count):
+    """The largest numbers of equal blocks that fit it."""
+    n = rows * cols if cols else rows
+    blocks = [(i * n, n, rows if cols else 0, cols) for i in range(count)]
+    assert binding.workspace_bytes(blocks, binding.default_profile_params(grad_dtype=grad)) <= binding.STATIC_WORKSPACE_BYTES
+
+
 @pytest.mark.parametrize("rows,cols", [(2, 8 << 20), (2, 1 << 20), (4, 4 << 20), (3, 5000003)])
 def test_matrices_of_few_rows_are_not_cut_into_a_task_per_tile(rows, cols):
     """Finalize keeps 4 bytes per task of its own.  Besides that a matrix takes more than a vector: its row and column
