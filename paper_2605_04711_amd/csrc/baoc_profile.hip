@@ -649,7 +649,7 @@ struct alignas(16) OnceRow {
 };
 
 // Words of a block's arrival line.
-enum Line : uint32_t { L_COUNT, L_SCAN3, L_REDO, L_ARRIVED, L_KEYS, L_SPILL = L_KEYS + 2, L_BRACKET = 8, L_INV_P0 = 12, L_PREFIX = 16, L_RANK = 20 };
+enum Line : uint32_t { L_COUNT, L_SCAN3, L_REDO, L_ARRIVED, L_KEYS, L_SPILL = L_KEYS + 2, L_BRACKET = 8, L_INV_P0 = 12 };
 
 // Whether the one pass has done with a block; `scan3` points at L_SCAN3 of the first block.
 __device__ __forceinline__ bool settled(const OnceRow* once, const uint32_t* scan3, uint32_t block)
@@ -691,6 +691,11 @@ __global__ __launch_bounds__(256) void k_build(const BlockRow* __restrict__ rows
     for (uint64_t i = id0; i < n_clear; i += stride) clear[i] = uint4{0u, 0u, 0u, 0u};
 }
 
+// Per block: histogram words; four key prefixes and four ranks within them, which stand in the record where the order statistics come (not next to
+// the arrival counter, whose line goes back and forth between the last pass's workgroups).
+struct Selection { uint32_t *hist, *prefix, *rank; };
+constexpr uint32_t kSelStride = 2 * kRecDoubles;
+
 // The four ranks of a block usually share their key prefix pairwise (lo and lo+1 of a quantile fall
 // into one bin).  Elements are matched against the distinct prefixes only; slot_of[t] names the
 // histogram that serves rank t.
@@ -705,7 +710,7 @@ __device__ __forceinline__ Prefixes distinct_prefixes(const uint32_t* __restrict
     for (int j = 0; j < 4; ++j) d.pre[j] = kNoPrefix;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        const uint32_t p = sel_prefix[block * kArriveStride + t];
+        const uint32_t p = sel_prefix[block * kSelStride + t];
         uint32_t slot = 4;
 #pragma unroll
         for (int j = 3; j >= 0; --j)
@@ -747,7 +752,6 @@ __device__ __forceinline__ uint32_t wave_scan(uint32_t x)
     return x;
 }
 
-struct Selection { uint32_t *hist, *prefix, *rank; };     // per block: histogram words; four key prefixes and four ranks within them, in its arrival line
 struct Digit { uint32_t bin, rank, count; };              // the bin that holds a rank, the rank inside it, the bin's keys
 
 constexpr uint32_t kBinsPerLane = kBins2 / 64;            // consecutive bins of a lane: 256 lanes cover the first digit, 64 one of the others
@@ -801,7 +805,7 @@ __device__ __forceinline__ void fold_first(const Selection& sel, const TileRow& 
         if (m.rank[t] >= at && m.rank[t] - at < mine) found[t] = bin_of(c, threadIdx.x * kBinsPerLane, at, m.rank[t]);
     for (uint32_t i = 0; i < kBinsPerLane / 4; ++i) reinterpret_cast<uint4*>(hist)[i] = uint4{0u, 0u, 0u, 0u};
     __syncthreads();
-    if (threadIdx.x < 4) { sel.prefix[block * kArriveStride + threadIdx.x] = found[threadIdx.x].bin; sel.rank[block * kArriveStride + threadIdx.x] = found[threadIdx.x].rank; }
+    if (threadIdx.x < 4) { sel.prefix[block * kSelStride + threadIdx.x] = found[threadIdx.x].bin; sel.rank[block * kSelStride + threadIdx.x] = found[threadIdx.x].rank; }
     if (threadIdx.x == 0) {
         // mu is the mean of the row means to the last bit of what they are made of: the tiles' row sums, added in fp64
         if (m.rows) rec[R_MU] = total / ((double)m.rows * (double)m.cols);
@@ -828,7 +832,7 @@ template <int PASS, typename L>
 __device__ __forceinline__ void pick_digit(const Selection& sel, uint32_t block, uint32_t* hist, uint32_t lane, uint32_t wave, double* order, L load)
 {
     constexpr uint32_t NB = PASS == 2 ? kBins2 : kBins3, N = NB / 64;
-    const uint32_t id = block * kArriveStride + wave;
+    const uint32_t id = block * kSelStride + wave;
     const Prefixes d = distinct_prefixes(sel.prefix, block);
     const uint32_t slot = wave == 0 ? d.slot_of[0] : (wave == 1 ? d.slot_of[1] : (wave == 2 ? d.slot_of[2] : d.slot_of[3]));
     const uint32_t rank = sel.rank[id], prefix = sel.prefix[id];
@@ -2248,7 +2252,7 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
     double2* taskpart = reinterpret_cast<double2*>(h->ws + P.off_residpart);
     float4* residpart = reinterpret_cast<float4*>(h->ws + P.off_residpart);
     double* rec = reinterpret_cast<double*>(h->ws + P.off_rec);
-    const Selection sel{u32_at(P.off_hist), arrived + L_PREFIX, arrived + L_RANK};
+    const Selection sel{u32_at(P.off_hist), u32_at(P.off_rec) + 2 * R_ORDER, u32_at(P.off_rec) + 2 * R_ORDER + 4};
     const float epsf = (float)h->params.eps;
     // v above which eps stays below a thousandth of sqrt(v) (and v is a normal number)
     const float eps_low = std::max(std::numeric_limits<float>::min(), (float)(1e6 * h->params.eps * h->params.eps));
