@@ -138,9 +138,9 @@ def test_distortion_where_a_rare_p_is_large(env, dead, theta):  # noqa: F811
         assert abs(stats[i].C - C) <= 1e-6 * C, f"{shapes[i]}: {stats[i].C} {C}"
 
 
-def _marked(prof, blocks, stats):
-    """The blocks that the one pass has handed on to the passes.  The records follow the states in the workspace (found by the sum of v of the last
-    block, the fourth of its 32 numbers), then 16 KB of histogram a block, then a line of 32 words a block, whose third is the mark."""
+def _lines(prof, blocks, stats):
+    """Every block's line of 32 words.  The records follow the states in the workspace (found by the sum of v of the last block, the fourth of its 32
+    numbers), then 16 KB of histogram a block, then these."""
     torch, last = prof._torch, len(blocks) - 1
     tail = prof.state(last)[2]
     first = -(-(tail.data_ptr() + tail.numel() * tail.element_size() - prof.workspace.data_ptr()) // 256) * 256
@@ -149,8 +149,12 @@ def _marked(prof, blocks, stats):
     at = [first + i for i in at if i >= 0 and i % 256 == 0]
     assert len(at) == 1
     hist = -(-(at[0] + 256 * len(blocks)) // 256) * 256
-    lines = prof.workspace[hist + 16384 * len(blocks):hist + (16384 + 128) * len(blocks)].view(torch.int32).view(-1, 32)
-    return lines[:, 2].nonzero().flatten().tolist()
+    return prof.workspace[hist + 16384 * len(blocks):hist + (16384 + 128) * len(blocks)].view(torch.int32).view(-1, 32)
+
+
+def _marked(prof, blocks, stats):
+    """The blocks that the one pass has handed on to the passes."""
+    return _lines(prof, blocks, stats)[:, 2].nonzero().flatten().tolist()
 
 
 def _quantiles(v):
@@ -260,3 +264,111 @@ def test_row_totals_and_mu_have_no_error_of_their_own(env, seed):  # noqa: F811
     stats = prof.finalize()[0]
     for i, b in enumerate(blocks):
         assert stats[i].F <= 1.02 * 2.0 ** -24, f"{b[2:]}: {stats[i].F * 2.0 ** 24}"
+
+
+def _packed(shapes):
+    out, at = [], 0
+    for r, c in shapes:
+        n = r * c if c else r
+        out.append((at, n, r if c else 0, c)); at += n
+    return out, at
+
+
+@pytest.mark.parametrize("layout", ["edges", "special values"])
+def test_layouts_of_these_tests_take_one_read(env, layout):  # noqa: F811
+    """Blocks of several workgroups have intervals (words 8 to 11) if they take part."""
+    torch, binding = env["torch"], env["binding"]
+    blocks, numel = _layout(1) if layout == "edges" else _packed([(1500, 1000), (1500000, 0), FILLER])
+    prof = binding.Profiler(blocks)
+    prof.step(torch.randn(numel, device="cuda:0", generator=torch.Generator(device="cuda:0").manual_seed(2)))
+    lines = _lines(prof, blocks, prof.finalize()[0])[:, 9].cpu()
+    for i, (_, n, r, c) in enumerate(blocks):
+        several = n > 65536 or (r and c > 6144)
+        assert (int(lines[i]) != 0) == (several and not (r and c > 12288)), blocks[i]
+
+
+SPECIAL = ["zeros", "constant", "two values", "nan", "inf", "rank one", "dead start"]
+
+
+@pytest.mark.parametrize("kind", SPECIAL)
+@pytest.mark.parametrize("all_take_part", [True, False])
+def test_special_values_next_to_each_other(env, kind, all_take_part):  # noqa: F811
+    """Blocks of one workgroup (up to 65,536 coordinates) and of several, of untouched, equal and non-finite values.  Where a block of two columns is in
+    the layout, which cannot take part, the passes follow the one pass at once instead of after a look at the marks.  Against the passes alone, which a
+    layout of these blocks only goes through."""
+    torch, binding = env["torch"], env["binding"]
+    shapes = [(65536, 0), (256, 256), (5, 0), (33, 63), (16, 64), (4, 0), (65537, 0), (700, 500)] + ([] if all_take_part else [(40000, 2)])
+    blocks, small = _packed(shapes)
+    whole, numel = _packed(shapes + ([FILLER] if all_take_part else 3 * [FILLER]))
+    gen = torch.Generator(device="cuda:0").manual_seed(6)
+    g = torch.randn(numel, device="cuda:0", generator=gen).mul_(1e-2)
+    theta = 0.02 * torch.randn(numel, device="cuda:0", generator=gen)
+    for o, n, r, c in blocks:
+        b, hit = g[o:o + n], torch.rand(n, device="cuda:0", generator=gen)
+        if kind == "zeros": b[hit < 0.3] = 0.0
+        if kind == "constant": b.fill_(0.125)
+        if kind == "two values": b.fill_(0.125); b[hit < 0.5] = 0.25
+        if kind == "nan": b[n // 2] = float("nan")
+        if kind == "inf": b[n // 2] = float("inf")
+        if kind == "rank one" and c: b.copy_((torch.arange(r, device="cuda:0")[:, None] % 7 + 1.0).mul(torch.arange(c, device="cuda:0")[None, :] % 5 + 1.0).mul(0.25).reshape(-1))
+        if kind == "dead start": b[:c or n // 8] = 0.0; theta[o:o + (c or n // 8)] = 0.0
+    one, ref = binding.Profiler(whole), binding.Profiler(blocks)
+    one.step(g); ref.step(g[:small])
+    a, b = one.finalize(theta=theta)[0], ref.finalize(theta=theta[:small])[0]
+    if kind in ("nan", "inf"):
+        assert _marked(one, whole, a) == [i for i in range(len(shapes)) if (shapes[i][1] > 2 or (kind == "nan" and not shapes[i][1]))]
+    elif kind not in ("two values", "rank one"):             # few values, of which an interval's fill the lists
+        assert _marked(one, whole, a) == []
+    for i in range(len(shapes)):
+        assert_stats_close(a[i], b[i], f"{kind} {shapes[i]}")
+        assert np.array_equal([a[i].q10, a[i].q90], [b[i].q10, b[i].q90], equal_nan=True)
+    assert bytes(a) == bytes(one.finalize(theta=theta)[0])
+
+
+@pytest.mark.parametrize("theta", ["f32", "bf16", None])
+def test_without_F_and_with_a_given_one_on_another_stream(env, theta):  # noqa: F811
+    """compute_F=False and F_raw are kernels of their own: every other statistic is the same to the bit.  Geometries of 8 and of 16 wavefronts, vectors,
+    blocks of one workgroup and of several.  The calls are made on a stream of their own."""
+    torch, binding = env["torch"], env["binding"]
+    shapes = [(4096, 2048), (2000, 11008), (3000, 5000), (256, 256), (900000, 0), (50000, 0), FILLER]
+    blocks, numel = _packed(shapes)
+    gen = torch.Generator(device="cuda:0").manual_seed(12)
+    g = torch.randn(numel, device="cuda:0", generator=gen).mul_(1e-2)
+    th = None if theta is None else (0.02 * torch.randn(numel, device="cuda:0", generator=gen)).to({"f32": torch.float32, "bf16": torch.bfloat16}[theta])
+    prof = binding.Profiler(blocks)
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        prof.step(g)
+        full, none, given = (prof.finalize(theta=th, **kw)[0] for kw in ({}, dict(compute_F=False), dict(F_raw=[0.25] * len(blocks))))
+    assert _marked(prof, blocks, full) == []
+    for i in range(len(blocks)):
+        assert none[i].F == 0.0 and given[i].F == 0.25
+        for f, _ in full[i]._fields_:
+            if f in ("F", "s_F"):
+                continue
+            # without F a matrix of one workgroup has another order of its sums of C
+            same = abs(getattr(none[i], f) - getattr(full[i], f)) <= 2e-7 * abs(getattr(full[i], f))
+            assert same and getattr(none[i], f) == getattr(given[i], f), f"{shapes[i]} {f}"
+        v = prof.state(i)[1]
+        for got, w in zip((none[i].q10, none[i].q90), _quantiles(v)):
+            assert abs(got - w) <= 1e-12 * w
+
+
+def test_records_by_copy(env):  # noqa: F811
+    """4,097 blocks have their records copied, the halves of the layout write theirs to pinned memory; the first and the last block go through the passes.
+    Tasks are of one size in all three: the same bits."""
+    torch, binding = env["torch"], env["binding"]
+    blocks, numel = _packed(4097 * [(627, 628)])
+    gen = torch.Generator(device="cuda:0").manual_seed(13)
+    g = torch.empty(numel, dtype=torch.bfloat16, device="cuda:0")
+    for at in range(0, numel, 1 << 28):
+        part = g[at:at + (1 << 28)]
+        part.copy_(torch.randn(part.numel(), device="cuda:0", generator=gen).mul_(1e-2))
+    g[:1000] = float("inf"); g[-1000:] = float("nan")
+
+    def stats(part):
+        prof = binding.Profiler(part, binding.default_profile_params(grad_dtype=1))
+        prof.step(g)
+        return bytes(prof.finalize()[0])
+    assert stats(blocks[:2048]) + stats(blocks[2048:]) == stats(blocks)
