@@ -314,7 +314,7 @@ __global__ __launch_bounds__(1024) void k_bracket(const float* __restrict__ v_al
 // The same value, formed anew where it stands: what is cheap to form from it is not kept over a loop.
 __device__ __forceinline__ uint32_t here(uint32_t x) { asm volatile("" : "+v"(x)); return x; }
 
-// Sums of four values over rows of 16 lanes by a halving exchange: a lane is left with the sum number (lane >> 2) & 3.
+// Sums of Q values over rows of 16 lanes by a halving exchange: a lane is left with the sum number lane / (16 / Q) of its row.
 __device__ __forceinline__ float rows_sum(const float (&s)[4], uint32_t lane)
 {
     const bool b3 = lane & 8u, b2 = lane & 4u;
@@ -324,6 +324,21 @@ __device__ __forceinline__ float rows_sum(const float (&s)[4], uint32_t lane)
     float a = (b2 ? h[1] : h[0]) + dpp<0x141, 0xf>(0.f, b2 ? h[0] : h[1]);
     a += dpp<0x4E, 0xf>(0.f, a);
     return a + dpp<0xB1, 0xf>(0.f, a);
+}
+__device__ __forceinline__ float rows_sum(const float (&s)[2], uint32_t lane)
+{
+    const bool b3 = lane & 8u;
+    float a = (b3 ? s[1] : s[0]) + dpp<0x128, 0xf>(0.f, b3 ? s[0] : s[1]);
+    a += dpp<0xB1, 0xf>(0.f, a);
+    a += dpp<0x4E, 0xf>(0.f, a);
+    return a + dpp<0x141, 0xf>(0.f, a);
+}
+__device__ __forceinline__ float rows_sum(const float (&s)[1], uint32_t)
+{
+    float a = s[0] + dpp<0xB1, 0xf>(0.f, s[0]);
+    a += dpp<0x4E, 0xf>(0.f, a);
+    a += dpp<0x141, 0xf>(0.f, a);
+    return a + dpp<0x128, 0xf>(0.f, a);
 }
 __device__ __forceinline__ double scalar_f64(double x)
 {
@@ -336,13 +351,13 @@ template <int CTRL> __device__ __forceinline__ double add_lane(double x)
     const uint32_t lo = dpp_u32<CTRL, 0xf>(0u, (uint32_t)b), hi = dpp_u32<CTRL, 0xf>(0u, (uint32_t)(b >> 32));
     return x + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
-// Sum over the 4, 8 or 16 lanes that share one of a row's Q = 4, 2 or 1 numbers.
-template <uint32_t Q> __device__ __forceinline__ double part_sum(double x)
+// Sum over 4, 8 or 16 lanes.
+template <uint32_t LANES> __device__ __forceinline__ double part_sum(double x)
 {
     x = add_lane<0xB1>(x);
     x = add_lane<0x4E>(x);
-    if (Q <= 2) x = add_lane<0x141>(x);
-    if (Q == 1) x = add_lane<0x128>(x);
+    if (LANES >= 8) x = add_lane<0x141>(x);
+    if (LANES == 16) x = add_lane<0x128>(x);
     return x;
 }
 // A lane's value and that of the lane 16, or 32, away.  (The halves are copied out first: a bit cast of a vector's element takes the first.)
@@ -755,33 +770,47 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
             issue_theta(next);
             batch_done(i);
             if (F) {
-                // A row's sum: of a strip, 256 columns at most, in fp32 over the lanes; over the strips and the wavefronts side by side in fp64 through
-                // LDS, [row of a load][wavefront][load][strip], one of a row's loads for every 16 / Q lanes
-                float sums[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (uint32_t q = 0; q < Q; ++q)
-#pragma unroll
-                    for (uint32_t k = 0; k < K; ++k) sums[q * K + k] = (x[q][k][0] + x[q][k][1]) + (x[q][k][2] + x[q][k][3]);
-                float mine = rows_sum(sums, lane);
-                if (lanes_log > 4) mine = add_rows16(mine);
-                if (lanes_log > 5) mine = add_rows32(mine);
+                // A row's sum: over 16 to 64 lanes, 256 columns at most, in fp32; the rest in fp64 through LDS, where each of a row's loads has 16 / Q
+                // lanes.  One strip: [row of a load][wavefront][load].  Several: 16 lanes leave one number, [row of a load][load][wavefront][lanes].
                 float* rs = rowsum[i & 1] + wrow * (wide * 16);
-                const uint32_t l = here(lane);
-                if ((l & ((1u << lanes_log) - 16u + 3u)) == 0 && wrow < down) rs[((l >> lanes_log) * wide + wcol) * 4 + ((l >> 2) & 3u)] = mine;
-                if (across > 1) lds_barrier(); else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                constexpr uint32_t kLanes = 16 / Q;           // lanes to a load
-                const float* from = rs + (l >> lanes_log) * wide * 4 + ((l & 15u) / kLanes) * K;
+                const uint32_t l = here(lane), groups_log = lanes_log - 4, in_row = l >> lanes_log;
+                auto of_lane = [&](uint32_t q, uint32_t k) { return (x[q][k][0] + x[q][k][1]) + (x[q][k][2] + x[q][k][3]); };
+                auto meet = [&]() { if (across > 1) lds_barrier(); else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); };
+                constexpr uint32_t kLanes = Q == 1 ? NW : 16 / Q;           // that have numbers of their own
                 double row_sum = 0.0;
+                auto gather = [&](auto of_wave) {
 #pragma unroll
-                for (uint32_t w0 = 0; w0 < NW; w0 += kLanes) {
-                    const uint32_t w = w0 + (l & (kLanes - 1));
-                    if (w < across && wrow < down) {
-#pragma unroll
-                        for (uint32_t k = 0; k < K; ++k) row_sum += (double)from[w * 4 + k];
+                    for (uint32_t w0 = 0; w0 < NW; w0 += kLanes) {
+                        const uint32_t w = w0 + (l & (kLanes - 1));
+                        if (w < across && wrow < down) row_sum += of_wave(w);
                     }
+                };
+                float sums[Q];
+#pragma unroll
+                for (uint32_t q = 0; q < Q; ++q) {
+                    sums[q] = of_lane(q, 0);
+#pragma unroll
+                    for (uint32_t k = 1; k < K; ++k) sums[q] += of_lane(q, k);
+                }
+                float mine = rows_sum(sums, lane);
+                if constexpr (K == 1) {
+                    if (lanes_log > 4) mine = add_rows16(mine);
+                    if (lanes_log > 5) mine = add_rows32(mine);
+                    if ((l & ((1u << lanes_log) - 16u + 3u)) == 0 && wrow < down) rs[(in_row * wide + wcol) * 4 + ((l >> 2) & 3u)] = mine;
+                    meet();
+                    const float* from = rs + in_row * wide * 4 + ((l >> 2) & 3u);
+                    gather([&](uint32_t w) { return (double)from[w * 4]; });
+                } else {
+                    const uint32_t load = Q == 2 ? (l >> 3) & 1u : 0u;
+                    float* to = rs + (((in_row * Q + load) * wide) << groups_log);
+                    if ((l & (16u / Q - 1u)) == 0 && wrow < down) to[(wcol << groups_log) + ((l >> 4) & ((1u << groups_log) - 1u))] = mine;
+                    meet();
+                    if (groups_log == 2) gather([&](uint32_t w) { const f4 y = reinterpret_cast<const f4*>(to)[w]; return ((double)y.x + (double)y.y) + ((double)y.z + (double)y.w); });
+                    else if (groups_log == 1) gather([&](uint32_t w) { const float2 y = reinterpret_cast<const float2*>(to)[w]; return (double)y.x + (double)y.y; });
+                    else gather([&](uint32_t w) { return (double)to[w]; });
                 }
                 float r[Q];
-                share_rows(r, (float)(part_sum<Q>(row_sum) * inv_cols));
+                share_rows(r, (float)(part_sum<kLanes>(row_sum) * inv_cols));
 #pragma unroll
                 for (uint32_t q = 0; q < Q; ++q) {
                     const double rd = (double)r[q];
