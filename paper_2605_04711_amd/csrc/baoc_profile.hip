@@ -1647,6 +1647,7 @@ struct Plan {
     uint32_t once_tasks = 0, once_narrow = 0;   // its workgroups, and those of 8 wavefronts among them; 0: the layout goes through the passes
     uint32_t once_units = 0, once_multi = 0;    // workgroups of k_once_select; blocks of several tasks
     bool once_all = false;        // every block takes it
+    bool once_worth[2] = {};      // it is faster than the passes without theta, with theta
     bool once_lines = true;       // rows are whole cache lines
     uint64_t off_once_sums = 0, off_once_units = 0;
     uint64_t padded = 0;          // coordinates in m / v / g_prev
@@ -1772,7 +1773,34 @@ static uint64_t even_groups(uint64_t groups, uint32_t most)
 // and 1125, 430 M of 851 M 1498 and 1206.
 // Layouts of many small blocks keep the passes as well: 2,100 of 65,536 coordinates 472 and 602, 1,000 of 160,000 536 and 658, 300 of 490,000 414
 // and 358, 240 of 1 M 530 and 440.
+// And those whose matrices leave lanes or wavefronts of the one pass idle (see OnceCost).
 constexpr uint64_t kOnceSmallest = 1ull << 27, kOnceSmallestPart = 3ull << 27, kOnceMeanBlock = 3ull << 17;
+
+// Fewer tasks than this, those of 16 wavefronts counted twice, leave too much of the chip idle for the one pass (tasks grow until lists and column sums have
+// room): 150 of 1.3 M coordinates 486 us by the passes and 2,741 by the one pass, 447 of 0.36 M 416 and 770, 640 of 0.3 M 491 and 608; from 820 on as
+// OnceCost has it.
+constexpr uint64_t kOnceTasks = 768;
+
+// Whole finalize, us, of the blocks that take part, with theta [1] and without [0]: what each adds by either way, and what comes with it once.
+// `full` is the share of a task's lanes and rows that have work: where it is small, arithmetic costs more than the second read.  Rows that are no
+// whole cache lines cost the passes more, and so do vectors, whose v they read a third time.  Fitted to 230 layouts of 134 M to 3.5 G coordinates; the
+// residuals' deviation is 5 to 6 %, and the line leaves 2 % to the passes with theta and 8 % without, where fewer were measured.  Of 420 M, bf16 theta, us, passes and one pass: 100 of 4,096
+// columns 790 and 611, 3,328 (full = 0.81) 767 and 679, 4,864 (0.79) 759 and 717, 4,352 (0.71) 774 and 776; with 16 wavefronts 8,192 798 and 652, 10,240
+// (0.83) 786 and 735, 6,400 (0.78) 747 and 776, 9,216 (0.75) 758 and 857; 400 of 1,024 x 1,024 804 and 682, 712 of 768 x 768 852 and 759, 316 of 1,152 x
+// 1,152 (0.75) 825 and 855, 1,025 of 640 x 640 (0.83) 885 and 977, 606 of 832 x 832 (0.81) 843 and 1088.
+struct OnceCost {
+    double passes[2] = {63.0, 67.0}, once[2] = {112.0, 85.0};
+    void add(const TileRow& m, bool wide, double full)
+    {
+        const double n = 1e-6 * (double)m.numel;
+        const bool broken = m.rows && m.cols % 64, vector = m.rows == 0;
+        passes[0] += 0.23 + n * (1.32 + (broken ? 0.25 : vector ? 0.54 : 0.0));
+        passes[1] += 0.14 + n * (1.67 + (broken ? 0.48 : vector ? 0.48 : 0.0));
+        once[0] += 0.42 + n * (0.04 + (0.75 + (wide ? 0.15 : 0.0) + (broken ? 0.05 : 0.0)) / full);
+        once[1] += 0.29 + n * (0.41 + (0.81 + (wide ? 0.12 : 0.0) + (broken ? 0.10 : 0.0)) / full);
+    }
+    bool worth(bool with_theta) const { return (with_theta ? 1.02 : 1.0) * once[with_theta] < passes[with_theta]; }
+};
 constexpr uint64_t kOnceBlock = 1ull << 28;
 constexpr uint64_t kOnceSingle = 65536;                   // coordinates that one workgroup reads again for its quantiles, from the L2
 constexpr uint32_t kOnceColumns = 768;                    // per wavefront
@@ -1787,6 +1815,7 @@ static void plan_once(Plan& P, uint64_t total)
     for (uint64_t share = std::min<uint64_t>(1u << 19, std::max<uint64_t>(1u << 14, total / 1024)); share <= 4 << 20; share *= 2) {
         double listed = 0.0;
         uint64_t narrow = 0, wide = 0, columns = 0, at = 0, multi = 0, part = 0, taking = 0, broken = 0, aligned = 0;
+        OnceCost cost;
         for (uint32_t i = 0; i < n; ++i) {
             const TileRow& m = P.tiles[i];
             OnceRow& o = P.once[i];
@@ -1796,6 +1825,7 @@ static void plan_once(Plan& P, uint64_t total)
             ++part; taking += m.numel;
             const uint32_t waves = m.rows && m.cols > 8 * kOnceColumns ? 16 : 8;
             uint64_t most = (m.numel + waves * 1024 - 1) / (waves * 1024);      // batches or rounds
+            double full = 1.0;
             if (m.rows) {
                 ((m.state_start | m.cols | m.grad_start) & 63u ? broken : aligned) += m.numel;
                 // lanes of a row in a load, strips of a wavefront, wavefronts side by side: as few lanes without columns, wavefronts
@@ -1806,14 +1836,15 @@ static void plan_once(Plan& P, uint64_t total)
                         const uint32_t width = 4u << lanes_log, across = (uint32_t)((m.cols + (uint64_t)width * strips - 1) / (width * strips));
                         if (across > waves) continue;
                         const uint32_t down = waves / across, loads = strips == 1 ? 4 : strips == 2 ? 2 : 1, batch = down * (loads << (6 - lanes_log));
-                        const double use = (double)m.cols / ((double)across * strips * width) * (across * down) / waves * m.rows / (double)align_up(m.rows, batch)
-                                           * (across == 1 ? 1.1 : 1.0) * (strips == 1 ? 1.02 : 1.0) * (lanes_log == 6 ? 1.03 : 1.0);
+                        const double busy = (double)m.cols / ((double)across * strips * width) * (across * down) / waves * m.rows / (double)align_up(m.rows, batch);
+                        const double use = busy * (across == 1 ? 1.1 : 1.0) * (strips == 1 ? 1.02 : 1.0) * (lanes_log == 6 ? 1.03 : 1.0);
                         if (use <= best) continue;
-                        best = use;
+                        best = use; full = busy;
                         o.geom = lanes_log | strips << 4 | across << 8 | down << 16 | (waves == 16 ? 1u << 24 : 0u);
                         most = (m.rows + batch - 1) / batch;
                     }
             }
+            cost.add(m, waves == 16, full);
             o.n_tasks = m.numel <= kOnceSingle && waves == 8 ? 1 : (uint32_t)std::max<uint64_t>(2, std::min(most, (m.numel + share / 2) / share));
             (waves == 16 ? wide : narrow) += o.n_tasks;
             if (o.n_tasks == 1) continue;
@@ -1827,7 +1858,9 @@ static void plan_once(Plan& P, uint64_t total)
         // it is common to a block's tasks.
         const uint64_t tasks = narrow + wide, units_at = at + units64(tasks * sizeof(OnceSums)), most_units = columns + tasks + (uint64_t)(listed / 2048.0) + multi;
         const uint64_t lists_at = units_at + units64(most_units * sizeof(OnceUnit));
-        if (taking < (part == n ? kOnceSmallest : kOnceSmallestPart) || taking < n * kOnceMeanBlock || tasks > 0x7fffffffull || most_units > 0x7fffffffull) return;
+        if (taking < (part == n ? kOnceSmallest : kOnceSmallestPart) || taking < n * kOnceMeanBlock || narrow + 2 * wide < kOnceTasks || tasks > 0x7fffffffull || most_units > 0x7fffffffull) return;
+        for (int i = 0; i < 2; ++i) P.once_worth[i] = cost.worth(i);
+        if (!P.once_worth[0] && !P.once_worth[1]) return;
         if (lists_at + tasks > room || (double)(room - lists_at - tasks) * 16.0 < kListSlack * listed) continue;
         const double words = multi ? std::min(2.0 * kListSlack, (double)(room - lists_at - tasks) * 16.0 / listed) : 0.0;
         P.off_once_sums = P.off_rvec + at * 64; P.off_once_units = P.off_rvec + units_at * 64;
@@ -2266,7 +2299,7 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
         else f(t16, no, yes);
     };
     double* const out = h->host_rec ? h->host_rec : rec;
-    const OnceRow* once = P.once_tasks ? reinterpret_cast<const OnceRow*>(h->ws + P.off_once) : nullptr;
+    const OnceRow* once = P.once_tasks && P.once_worth[want_C] ? reinterpret_cast<const OnceRow*>(h->ws + P.off_once) : nullptr;
     auto one_pass = [&]() {
         const OnceMem mem{h->ws + P.off_rvec, reinterpret_cast<OnceSums*>(h->ws + P.off_once_sums), reinterpret_cast<OnceUnit*>(h->ws + P.off_once_units),
                           once, N, P.once_narrow, arrived, sel.hist, rec, out};

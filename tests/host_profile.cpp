@@ -394,7 +394,7 @@ static int check_once_intervals()
 // Which layouts and blocks take the one pass, and that its memory is what the passes have for r, c and the lists, each part of it apart.
 static int check_once()
 {
-    std::vector<baoc_block> edges, few, small, vectors, many, tiny;
+    std::vector<baoc_block> edges, few, small, vectors, many, tiny, idle, idle_wide, vectors_most, whole, whole_wide;
     for (uint32_t c : {2u, 3u, 4u, 5u, 63u, 64u, 65u, 127u, 128u, 129u, 191u, 192u, 193u, 255u, 256u, 257u, 511u, 513u, 767u, 768u, 769u, 1023u, 1025u, 2305u, 4095u,
                        4097u, 4608u, 6143u, 6144u, 6145u, 11008u, 12287u, 12288u, 12289u, 30000u})
         for (uint32_t r : {2u, 3u, 5u, 17u, 33u}) add(edges, r, c);
@@ -405,13 +405,17 @@ static int check_once()
     add(small, 16384, 8191);                                                 // below 2^27 in all
     add(vectors, 1u << 28, 0);                                               // no matrix: no room for lists
     add(tiny, 600, 500, 1000);                                               // blocks of 300,000 coordinates
+    add(idle, 1152, 1152, 316); add(idle_wide, 455, 9216, 100);              // a quarter of the lanes has no work; without theta the first are worth it
+    add(vectors_most, 20000000, 0, 7); add(vectors_most, 5802, 3484); add(vectors_most, 893, 11114); add(vectors_most, 979, 8138);   // room for long lists only
+    add(whole, 1024, 1024, 400); add(whole_wide, 512, 8192, 100);
     add(many, 1024, 1024, 600); add(many, 4096, 11008, 3); add(many, 50000, 0, 100);
     for (uint32_t dtype : {BAOC_GRAD_F32, BAOC_GRAD_BF16})
-        for (const auto* l : {&edges, &few, &small, &vectors, &many, &tiny}) {
+        for (const auto* l : {&edges, &few, &small, &vectors, &many, &tiny, &idle, &idle_wide, &vectors_most, &whole, &whole_wide}) {
             const baoc_profile_params p = params_of(dtype);
             Plan P;
             CHECK(make_plan(l->data(), (uint32_t)l->size(), &p, &P, nullptr) == BAOC_OK, " ");
-            CHECK((P.once_tasks != 0) == (l == &edges || l == &many), "%u tasks", P.once_tasks);
+            CHECK((P.once_tasks != 0 && P.once_worth[1]) == (l == &edges || l == &many || l == &whole || l == &whole_wide), "%u tasks", P.once_tasks);
+            CHECK((P.once_tasks != 0 && P.once_worth[0]) == (l == &edges || l == &many || l == &whole || l == &whole_wide || l == &idle), "%u tasks", P.once_tasks);
             if (!P.once_tasks) continue;
             uint64_t narrow = 0, wide = 0, units = 0, part = 0, fixed = 0, lists = 0, first_list = ~0ull;
             for (size_t i = 0; i < l->size(); ++i) {

@@ -372,3 +372,23 @@ def test_records_by_copy(env):  # noqa: F811
         prof.step(g)
         return bytes(prof.finalize()[0])
     assert stats(blocks[:2048]) + stats(blocks[2048:]) == stats(blocks)
+
+
+def test_one_read_without_theta_and_the_passes_with_it(env):  # noqa: F811
+    """Blocks of 1,152 columns, of which a quarter of a workgroup's lanes has none, are read once without theta and go through the passes with it: by turns
+    on one handle, each with the same bits every time; quantiles are the same, F of either is within the bound of the oracle's comparison."""
+    torch, binding = env["torch"], env["binding"]
+    blocks, numel = _packed(316 * [(1152, 1152)])
+    gen = torch.Generator(device="cuda:0").manual_seed(21)
+    prof = binding.Profiler(blocks, binding.default_profile_params(grad_dtype=1))
+    prof.step(torch.randn(numel, device="cuda:0", generator=gen).mul_(1e-2).to(torch.bfloat16))
+    theta = (0.02 * torch.randn(numel, device="cuda:0", generator=gen)).to(torch.bfloat16)
+    first = [prof.finalize(theta=t)[0] for t in (theta, None)]
+    for _ in range(2):
+        for t, want in zip((theta, None), first):
+            assert bytes(prof.finalize(theta=t)[0]) == bytes(want)
+    for a, b in zip(*first):
+        assert (a.q10, a.q90) == (b.q10, b.q90) and abs(a.F - b.F) <= 1e-6 * b.F and a.C > 0.0 and b.C == 0.0
+    for i in (0, 315):
+        for got, w in zip((first[0][i].q10, first[0][i].q90), _quantiles(prof.state(i)[1])):
+            assert abs(got - w) <= 1e-12 * w
