@@ -47,7 +47,6 @@ struct OnceMem {
     OnceUnit* units;
     const OnceRow* rows;
     uint32_t n_blocks, narrow_tasks;                      // tasks of 8 wavefronts; those of 16 come after them
-    uint32_t spill_log;                                   // see once_spill_log
     uint32_t* line;
     uint32_t* hist;
     const double* rec;
@@ -57,11 +56,8 @@ struct OnceMem {
 __host__ __device__ __forceinline__ uint64_t once_cols_units(uint32_t tasks, uint32_t cols) { return ((uint64_t)tasks * cols * 8 + 63) / 64; }
 constexpr uint32_t kOncePart = 8192;                      // words of a list that a wavefront of k_once_select takes
 __host__ __device__ __forceinline__ uint32_t once_parts(uint32_t cap) { return (cap + kOncePart - 1) / kOncePart; }
-__host__ __device__ __forceinline__ uint32_t once_spill(const OnceRow& o, uint32_t spill_log) { return o.n_tasks * o.list_cap >> spill_log & ~15u; }   // words of the common list
-__host__ __device__ __forceinline__ uint32_t once_list_units(const OnceRow& o, uint32_t spill_log)
-{
-    return (uint32_t)(((uint64_t)o.n_tasks * once_parts(o.list_cap) + once_parts(once_spill(o, spill_log)) + 3) / 4);
-}
+__host__ __device__ __forceinline__ uint32_t once_spill(const OnceRow& o) { return o.n_tasks * o.list_cap / 32 * 16; }   // words of the common list: half of the tasks'
+__host__ __device__ __forceinline__ uint32_t once_list_units(const OnceRow& o) { return (uint32_t)(((uint64_t)o.n_tasks * once_parts(o.list_cap) + once_parts(once_spill(o)) + 3) / 4); }
 __host__ __device__ __forceinline__ uint32_t once_col_units(uint32_t rows, uint32_t cols) { return rows ? (cols + 63) / 64 : 0u; }
 __host__ __device__ __forceinline__ uint32_t once_keys_cap(uint64_t numel) { return (uint32_t)max((uint64_t)1024, min((uint64_t)kOnceKeys, numel >> 10)); }
 
@@ -74,15 +70,6 @@ __host__ __device__ __forceinline__ uint32_t sample_pieces(uint64_t numel)
     return numel >= (1u << 27) ? 16u : numel >= (1u << 26) ? 8u : numel >= (1u << 22) ? 4u : 2u;
 }
 constexpr float kListSlack = 1.2f;                        // a block's lists have at least this much more room
-// The common list has 1 / (1 << once_spill_log) of the room of the tasks' lists, whose `words` are in all that many times what independent coordinates
-// bring.  These lists come first: a key for the common list costs an atomic in memory for every flush (134 M with 0.89 of what is expected in
-// the tasks' own lists 251 us, 234 with 1.25).
-inline uint32_t once_spill_log(double words)
-{
-    uint32_t s = 1;
-    while (s < 4 && words / (1.0 + 1.0 / (1 << s)) < (double)kListSlack) ++s;
-    return s;
-}
 inline double listed_share(uint64_t numel) { return 2.0 * 2.0 * 1.5 / std::sqrt(4096.0 * sample_pieces(numel)); }
 
 // Where a load of 1 << rpl rows starts that wants `row` and those after it, and a lane that wants four columns from `col` on: rows past the
@@ -296,7 +283,7 @@ __global__ __launch_bounds__(1024) void k_bracket(const float* __restrict__ v_al
         if (first > 0.f && first < (float)n) more = fmaxf(more, (second - first * (first / (float)pieces)) / (first * (1.0f - first / (float)n)));
     }
     // as wide as the lists have room for: two intervals, two sides, a quarter to spare (the share of alike neighbours between two ranks varies, too)
-    const float room = ((float)o.list_cap * (float)o.n_tasks + (float)once_spill(o, mem.spill_log)) / (float)m.numel * (float)n * 0.2f;
+    const float room = (float)o.list_cap * (float)o.n_tasks * 1.5f / (float)m.numel * (float)n * 0.2f;
     const float wide = fminf(spread * __builtin_amdgcn_sqrtf(more), room);
     if (wide > 1.1f * spread) ends(wide);
     uint32_t* line = mem.line + block * kArriveStride;
@@ -553,7 +540,7 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
     auto put = [&](const Slots& r, uint32_t i, uint32_t key) {
         const uint32_t slot = r.first + i, common = r.at + (slot - r.spilled);
         if (slot < cap) st_device(&list[slot], key);
-        else if (common < once_spill(o, mem.spill_log)) st_device(&list[(n_tasks - local) * cap + common], key);
+        else if (common < once_spill(o)) st_device(&list[(n_tasks - local) * cap + common], key);
     };
     auto flush = [&](bool all) {
         const uint32_t n = all ? n_stage : n_stage & ~63u;
@@ -987,7 +974,7 @@ __global__ __launch_bounds__(256, 4) void k_once_select(const TileRow* __restric
     const OnceRow& o = mem.rows[block];
     const TileRow& m = tiles[block];
     const uint32_t n_tasks = scalar_u32(o.n_tasks), rows = scalar_u32(m.rows), cols = scalar_u32(m.cols);
-    const uint32_t unit = blockIdx.x - scalar_u32(o.first_unit), lists = once_list_units(o, mem.spill_log), units = lists + once_col_units(rows, cols);
+    const uint32_t unit = blockIdx.x - scalar_u32(o.first_unit), lists = once_list_units(o), units = lists + once_col_units(rows, cols);
     const OnceSums* sums = mem.sums + (o.geom >> 24 ? mem.narrow_tasks + o.first_wide : o.first_task);
     uint32_t* line = mem.line + block * kArriveStride;
     uint32_t* hist = mem.hist + (uint64_t)block * kHistWords;
@@ -1060,7 +1047,7 @@ __global__ __launch_bounds__(256, 4) void k_once_select(const TileRow* __restric
     const uint32_t cap = scalar_u32(o.list_cap), spilled = scalar_u32(line[L_SPILL]), parts = once_parts(cap), id = unit * 4 + wave;
     struct Part { uint32_t* from; uint32_t n, room; };
     auto part_of = [&](uint32_t id) {
-        const uint32_t task = min(id / max(parts, 1u), n_tasks), at = (id - task * parts) * kOncePart, whole = task < n_tasks ? cap : once_spill(o, mem.spill_log);
+        const uint32_t task = min(id / max(parts, 1u), n_tasks), at = (id - task * parts) * kOncePart, whole = task < n_tasks ? cap : once_spill(o);
         const uint32_t all = min(whole, task < n_tasks ? sums[task].n_list : spilled);
         return Part{reinterpret_cast<uint32_t*>(mem.base + (uint64_t)o.off_list * 64) + ((uint64_t)task * cap + at), all > at ? (uint32_t)min(all - at, kOncePart) : 0u,
                     (uint32_t)min(whole - at, kOncePart)};
@@ -1187,7 +1174,7 @@ __global__ __launch_bounds__(256, 4) void k_once_select(const TileRow* __restric
     const double* rec = mem.rec + (uint64_t)block * kRecDoubles;
     double* out = mem.out + (uint64_t)block * kRecDoubles;
     const uint32_t q = interval_of(wave), rank = wave == 0 ? m.rank[0] : wave == 1 ? m.rank[1] : wave == 2 ? m.rank[2] : m.rank[3];
-    bad |= spilled > once_spill(o, mem.spill_log);
+    bad |= spilled > once_spill(o);
     uint32_t value = 0;
     bool near = false;                                        // of a crowded interval: the value, or the first key of its cell
 #pragma unroll
@@ -1241,7 +1228,7 @@ __global__ __launch_bounds__(256, 4) void k_once_select(const TileRow* __restric
     }
     __syncthreads();
     // Ranks whose cell has several values: 11 bits at a time from what the parts have kept.
-    const uint32_t n_parts = n_tasks * parts + once_parts(once_spill(o, mem.spill_log)), share = max(1u, 256 / max(n_parts, 1u));      // threads a part
+    const uint32_t n_parts = n_tasks * parts + once_parts(once_spill(o)), share = max(1u, 256 / max(n_parts, 1u));      // threads a part
 #pragma unroll 1
     for (uint32_t half = 0; half < 2; ++half) {
         const uint32_t mine = scalar_u32(open) & (one_interval ? (half ? 0u : 15u) : 3u << (2 * half));

@@ -644,7 +644,7 @@ struct alignas(16) OnceRow {
     uint32_t n_tasks;                         // 0: the block goes through the passes here
     uint32_t first_unit;                      // of k_once_select
     uint32_t geom;                            // lanes_log | strips << 4 | across << 8 | down << 16 | 16 wavefronts << 24
-    uint32_t off_list, list_cap;              // a list per task, its words; then a common one for what these have no room for
+    uint32_t off_list, list_cap;              // a list per task, its words; then one of half their size for what these have no room for
     uint32_t off_cols;                        // [task][column] float2, then the collected keys of both intervals
 };
 
@@ -1645,7 +1645,6 @@ struct Plan {
     std::vector<uint32_t> multi;  // blocks of several tasks
     std::vector<OnceRow> once;    // every block's share of the one pass
     uint32_t once_tasks = 0, once_narrow = 0;   // its workgroups, and those of 8 wavefronts among them; 0: the layout goes through the passes
-    uint32_t once_spill_log = 0;  // size of the blocks' common lists
     uint32_t once_units = 0, once_multi = 0;    // workgroups of k_once_select; blocks of several tasks
     bool once_all = false;        // every block takes it
     bool once_worth[2] = {};      // it is faster than the passes without theta, with theta
@@ -1855,8 +1854,8 @@ static void plan_once(Plan& P, uint64_t total)
             o.off_cols = (uint32_t)at;
             at += once_cols_units(o.n_tasks, m.rows ? m.cols : 0) + units64(once_keys_cap(m.numel) * 8);
         }
-        // The lists have room for 1.2 to 2.4 times what independent coordinates bring: neighbours that are alike bring up to twice as much.  A part of it, a
-        // third where there is most, is common to a block's tasks.
+        // The lists have room for 1.2 to 2.4 times what independent coordinates bring: neighbours that are alike bring up to twice as much.  A third of
+        // it is common to a block's tasks.
         const uint64_t tasks = narrow + wide, units_at = at + units64(tasks * sizeof(OnceSums)), most_units = columns + tasks + (uint64_t)(listed / 2048.0) + multi;
         const uint64_t lists_at = units_at + units64(most_units * sizeof(OnceUnit));
         if (taking < (part == n ? kOnceSmallest : kOnceSmallestPart) || taking < n * kOnceMeanBlock || narrow + 2 * wide < kOnceTasks || tasks > 0x7fffffffull || most_units > 0x7fffffffull) return;
@@ -1864,7 +1863,6 @@ static void plan_once(Plan& P, uint64_t total)
         if (!P.once_worth[0] && !P.once_worth[1]) return;
         if (lists_at + tasks > room || (double)(room - lists_at - tasks) * 16.0 < kListSlack * listed) continue;
         const double words = multi ? std::min(2.0 * kListSlack, (double)(room - lists_at - tasks) * 16.0 / listed) : 0.0;
-        const uint32_t spill_log = once_spill_log(words);
         P.off_once_sums = P.off_rvec + at * 64; P.off_once_units = P.off_rvec + units_at * 64;
         at = lists_at;
         for (uint32_t i = 0; i < n; ++i) {
@@ -1872,17 +1870,17 @@ static void plan_once(Plan& P, uint64_t total)
             if (o.n_tasks < 2) continue;
             const TileRow& m = P.tiles[i];
             o.off_list = (uint32_t)at;
-            o.list_cap = (uint32_t)(words / (1.0 + 1.0 / (1 << spill_log)) * listed_share(m.numel) * (double)m.numel / o.n_tasks) / 16 * 16;
-            at += ((uint64_t)o.n_tasks * o.list_cap + once_spill(o, spill_log)) / 16;
+            o.list_cap = (uint32_t)(words * listed_share(m.numel) * (double)m.numel * (2.0 / 3.0) / o.n_tasks) / 16 * 16;
+            at += ((uint64_t)o.n_tasks * o.list_cap + once_spill(o)) / 16;
         }
         uint64_t units = 0;
         for (uint32_t i = 0; i < n; ++i) {
             OnceRow& o = P.once[i];
             o.first_unit = (uint32_t)units;
-            if (o.n_tasks > 1) units += once_list_units(o, spill_log) + once_col_units(P.tiles[i].rows, P.tiles[i].cols);
+            if (o.n_tasks > 1) units += once_list_units(o) + once_col_units(P.tiles[i].rows, P.tiles[i].cols);
         }
         if (at > room || units > most_units) return;
-        P.once_narrow = (uint32_t)narrow; P.once_units = (uint32_t)units; P.once_multi = (uint32_t)multi; P.once_spill_log = spill_log; P.once_all = part == n;
+        P.once_narrow = (uint32_t)narrow; P.once_units = (uint32_t)units; P.once_multi = (uint32_t)multi; P.once_all = part == n;
         P.once_tasks = (uint32_t)tasks; P.once_lines = broken <= aligned;
         return;
     }
@@ -2304,7 +2302,7 @@ extern "C" int baoc_profile_finalize(baoc_profiler* h, const baoc_config* config
     const OnceRow* once = P.once_tasks && P.once_worth[want_C] ? reinterpret_cast<const OnceRow*>(h->ws + P.off_once) : nullptr;
     auto one_pass = [&]() {
         const OnceMem mem{h->ws + P.off_rvec, reinterpret_cast<OnceSums*>(h->ws + P.off_once_sums), reinterpret_cast<OnceUnit*>(h->ws + P.off_once_units),
-                          once, N, P.once_narrow, P.once_spill_log, arrived, sel.hist, rec, out};
+                          once, N, P.once_narrow, arrived, sel.hist, rec, out};
         if (P.once_multi) hipLaunchKernelGGL(k_bracket, dim3(N), dim3(1024), 0, st, v, tiles, mem, epsf);
         with_kinds([&](auto tt, auto f, auto c) {
             constexpr int TT = decltype(tt)::value;

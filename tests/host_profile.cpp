@@ -394,7 +394,7 @@ static int check_once_intervals()
 // Which layouts and blocks take the one pass, and that its memory is what the passes have for r, c and the lists, each part of it apart.
 static int check_once()
 {
-    std::vector<baoc_block> edges, few, small, vectors, many, tiny, idle, idle_wide, vectors_most, whole, whole_wide, least;
+    std::vector<baoc_block> edges, few, small, vectors, many, tiny, idle, idle_wide, vectors_most, whole, whole_wide;
     for (uint32_t c : {2u, 3u, 4u, 5u, 63u, 64u, 65u, 127u, 128u, 129u, 191u, 192u, 193u, 255u, 256u, 257u, 511u, 513u, 767u, 768u, 769u, 1023u, 1025u, 2305u, 4095u,
                        4097u, 4608u, 6143u, 6144u, 6145u, 11008u, 12287u, 12288u, 12289u, 30000u})
         for (uint32_t r : {2u, 3u, 5u, 17u, 33u}) add(edges, r, c);
@@ -408,15 +408,14 @@ static int check_once()
     add(idle, 1152, 1152, 316); add(idle_wide, 455, 9216, 100);              // a quarter of the lanes has no work; without theta the first are worth it
     add(vectors_most, 20000000, 0, 7); add(vectors_most, 5802, 3484); add(vectors_most, 893, 11114); add(vectors_most, 979, 8138);   // room for long lists only
     add(whole, 1024, 1024, 400); add(whole_wide, 512, 8192, 100);
-    add(least, 4096, 4096, 8);                                               // lists with little room to spare
     add(many, 1024, 1024, 600); add(many, 4096, 11008, 3); add(many, 50000, 0, 100);
     for (uint32_t dtype : {BAOC_GRAD_F32, BAOC_GRAD_BF16})
-        for (const auto* l : {&edges, &few, &small, &vectors, &many, &tiny, &idle, &idle_wide, &vectors_most, &whole, &whole_wide, &least}) {
+        for (const auto* l : {&edges, &few, &small, &vectors, &many, &tiny, &idle, &idle_wide, &vectors_most, &whole, &whole_wide}) {
             const baoc_profile_params p = params_of(dtype);
             Plan P;
             CHECK(make_plan(l->data(), (uint32_t)l->size(), &p, &P, nullptr) == BAOC_OK, " ");
-            CHECK((P.once_tasks != 0 && P.once_worth[1]) == (l == &edges || l == &many || l == &whole || l == &whole_wide || l == &least), "%u tasks", P.once_tasks);
-            CHECK((P.once_tasks != 0 && P.once_worth[0]) == (l == &edges || l == &many || l == &whole || l == &whole_wide || l == &least || l == &idle), "%u tasks", P.once_tasks);
+            CHECK((P.once_tasks != 0 && P.once_worth[1]) == (l == &edges || l == &many || l == &whole || l == &whole_wide), "%u tasks", P.once_tasks);
+            CHECK((P.once_tasks != 0 && P.once_worth[0]) == (l == &edges || l == &many || l == &whole || l == &whole_wide || l == &idle), "%u tasks", P.once_tasks);
             if (!P.once_tasks) continue;
             uint64_t narrow = 0, wide = 0, units = 0, part = 0, fixed = 0, lists = 0, first_list = ~0ull;
             for (size_t i = 0; i < l->size(); ++i) {
@@ -430,14 +429,12 @@ static int check_once()
                 if (m.rows && m.numel < 1u << 21 && check_once_loads(o, m)) return 1;
                 (o.geom >> 24 ? wide : narrow) += o.n_tasks;
                 if (o.n_tasks == 1) continue;
-                units += once_list_units(o, P.once_spill_log) + once_col_units(m.rows, m.cols);
+                units += once_list_units(o) + once_col_units(m.rows, m.cols);
                 CHECK(o.off_cols == fixed && o.list_cap % 16 == 0 && o.list_cap > 0, "%u x %u", m.rows, m.cols);
-                // the tasks' own lists have room for what independent coordinates bring; a common one is there
-                CHECK((double)o.n_tasks * o.list_cap >= 1.05 * listed_share(m.numel) * (double)m.numel && once_spill(o, P.once_spill_log) >= 16, "%u x %u", m.rows, m.cols);
                 fixed += once_cols_units(o.n_tasks, m.rows ? m.cols : 0) + ((uint64_t)once_keys_cap(m.numel) * 8 + 63) / 64;
                 first_list = std::min<uint64_t>(first_list, o.off_list);
                 CHECK(lists == 0 || o.off_list == lists, "%u x %u", m.rows, m.cols);
-                lists = o.off_list + ((uint64_t)o.n_tasks * o.list_cap + once_spill(o, P.once_spill_log)) / 16;
+                lists = o.off_list + ((uint64_t)o.n_tasks * o.list_cap + once_spill(o)) / 16;
             }
             CHECK(narrow == P.once_narrow && narrow + wide == P.once_tasks && units == P.once_units && P.once_all == (part == l->size()), " ");
             CHECK(P.off_rvec + fixed * 64 <= P.off_once_sums && P.off_once_sums + P.once_tasks * sizeof(OnceSums) <= P.off_once_units, " ");
