@@ -210,7 +210,7 @@ __device__ __forceinline__ double wave_total(double x)
 // to piece, and where it is more than a tenth above the latter the intervals are taken again, at most as wide as the lists have room for.  (240
 // blocks of 1 M, 9 neighbours of one scale: 2 of them were marked without that, finalize 511 us, 460 so.)
 // Zeros are left out of an interval and counted as below: a quantile of a block with untouched coordinates is then known to be 0 however many there are.
-// Bound by latency (loads, two rounds of counting) up to about 100 blocks, 20 us, then by the lines.
+// Bound by latency (loads, two rounds of counting) up to about 100 blocks, 23 us, then by the lines.
 __global__ __launch_bounds__(1024) void k_bracket(const float* __restrict__ v_all, const TileRow* __restrict__ tiles, OnceMem mem, float eps)
 {
     __shared__ alignas(16) uint32_t h[kHistWords];
@@ -441,8 +441,8 @@ __host__ __device__ __forceinline__ Distortion once_distortion(double a, double 
 // 1,140.  Loads of v are a batch ahead of their use, those of theta most of one.  Tasks have total / 1,024 coordinates, 524,288 at most: a
 // workgroup's start and end take 25 us, its rounds of 512 at a time leave the last one short (24 of 11,008 x 4,096 with 1 M a task 1,430 us, 1,292
 // so).  LINES: rows of most matrices are whole cache lines, and loads carry the nontemporal hint (see whole_lines).
-// Bound by HBM with the vector ALUs behind it: 60 matrices of 4,096 x 4,096, bf16 theta, 6.04 GB, 1,140 us, 5.3 TB/s; 29 vector instructions
-// per coordinate of a wavefront, ALUs busy 74 % of the time; 16 wavefronts, 24 of 4,096 x 11,008, 1,610 us, 4.0 TB/s (a barrier for 12 loads of
+// Bound by HBM with the vector ALUs behind it: 60 matrices of 4,096 x 4,096, bf16 theta, 6.04 GB, 1,200 us, 5.0 TB/s; 30 vector instructions
+// per coordinate (36 with 16 wavefronts), ALUs busy 83 % of the time; 16 wavefronts, 24 of 4,096 x 11,008, 6.5 GB, 1,575 us, 4.1 TB/s (a barrier for 12 loads of
 // every wavefront).  The passes read 10.07 GB for the first of these in 1,590 us.
 template <uint32_t NW, int TT, bool F, bool C, bool LINES>
 __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v_all, const typename GradIO<TT>::elem* __restrict__ theta,
@@ -959,8 +959,8 @@ __global__ __launch_bounds__(64 * NW, 4) void k_once(const float* __restrict__ v
 }
 
 // Units of a block: the first walk its tasks' lists for the keys that share the ranks' bins, the others sum 64 columns over its tasks. The
-// last to arrive orders the keys, adds the sums and leaves the record.  A chain of dependent loads for a small layout (32 blocks of 1 M 23 us),
-// HBM for the lists and the column sums of large ones (3.5 G coordinates, 0.9 GB, 250 us).  Keys are collected in LDS first, since an atomic on
+// last to arrive orders the keys, adds the sums and leaves the record.  A chain of dependent loads for a small layout (8 blocks of 16.8 M 27 us),
+// HBM for the lists and the column sums of large ones (3.5 G coordinates, 0.9 GB, 305 us).  Keys are collected in LDS first, since an atomic on
 // the block's counter is a round trip of more than a microsecond (148 blocks, 124 M: 110 us with one for each key, 43 so), and counted eight
 // reads at a time (8 blocks of 131 M, 2,000 keys each: 122 us with one read after another, 63 so).
 template <bool F, bool C>

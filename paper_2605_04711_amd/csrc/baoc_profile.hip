@@ -1784,10 +1784,10 @@ constexpr uint64_t kOnceTasks = 768;
 // Whole finalize, us, of the blocks that take part, with theta [1] and without [0]: what each adds by either way, and what comes with it once.
 // `full` is the share of a task's lanes and rows that have work: where it is small, arithmetic costs more than the second read.  Rows that are no
 // whole cache lines cost the passes more, and so do vectors, whose v they read a third time.  Fitted to 230 layouts of 134 M to 3.5 G coordinates; the
-// residuals' deviation is 5 to 6 %, and the line leaves 2 % to the passes with theta and 8 % without, where fewer were measured.  Of 420 M, bf16 theta, us, passes and one pass: 100 of 4,096
-// columns 790 and 611, 3,328 (full = 0.81) 767 and 679, 4,864 (0.79) 759 and 717, 4,352 (0.71) 774 and 776; with 16 wavefronts 8,192 798 and 652, 10,240
-// (0.83) 786 and 735, 6,400 (0.78) 747 and 776, 9,216 (0.75) 758 and 857; 400 of 1,024 x 1,024 804 and 682, 712 of 768 x 768 852 and 759, 316 of 1,152 x
-// 1,152 (0.75) 825 and 855, 1,025 of 640 x 640 (0.83) 885 and 977, 606 of 832 x 832 (0.81) 843 and 1088.
+// residuals' deviation is 5 to 6 %, and the line leaves 2 % to the passes with theta.  Of 420 M, bf16 theta, us, passes and one pass: 100 of 4,096
+// columns 790 and 611, 3,328 (full = 0.81) 767 and 679, 4,864 (0.79) 759 and 717, 4,352 (0.71) 774 and 776; with 16 wavefronts 8,192 798 and 652,
+// 10,240 (0.83) 786 and 735, 6,400 (0.78) 747 and 776, 9,216 (0.75) 758 and 857; 400 of 1,024 x 1,024 804 and 682, 712 of 768 x 768 852 and 759, 316 of
+// 1,152 x 1,152 (0.75) 825 and 855, 1,025 of 640 x 640 (0.83) 885 and 977, 606 of 832 x 832 (0.81) 843 and 1088.
 struct OnceCost {
     double passes[2] = {63.0, 67.0}, once[2] = {112.0, 85.0};
     void add(const TileRow& m, bool wide, double full)
@@ -1799,7 +1799,9 @@ struct OnceCost {
         once[0] += 0.42 + n * (0.04 + (0.75 + (wide ? 0.15 : 0.0) + (broken ? 0.05 : 0.0)) / full);
         once[1] += 0.29 + n * (0.41 + (0.81 + (wide ? 0.12 : 0.0) + (broken ? 0.10 : 0.0)) / full);
     }
-    bool worth(bool with_theta) const { return (with_theta ? 1.02 : 1.0) * once[with_theta] < passes[with_theta]; }
+    // Next to blocks that go through the passes more is left to these, whose workgroups are launched for all blocks (a UNet of 860 M coordinates in
+    // 686 blocks, 7 of which do not take part, 1,853 and 2,023 us; this says 1.06).
+    bool worth(bool with_theta, bool others) const { return (others ? 1.08 : with_theta ? 1.02 : 1.0) * once[with_theta] < passes[with_theta]; }
 };
 constexpr uint64_t kOnceBlock = 1ull << 28;
 constexpr uint64_t kOnceSingle = 65536;                   // coordinates that one workgroup reads again for its quantiles, from the L2
@@ -1859,7 +1861,7 @@ static void plan_once(Plan& P, uint64_t total)
         const uint64_t tasks = narrow + wide, units_at = at + units64(tasks * sizeof(OnceSums)), most_units = columns + tasks + (uint64_t)(listed / 2048.0) + multi;
         const uint64_t lists_at = units_at + units64(most_units * sizeof(OnceUnit));
         if (taking < (part == n ? kOnceSmallest : kOnceSmallestPart) || taking < n * kOnceMeanBlock || narrow + 2 * wide < kOnceTasks || tasks > 0x7fffffffull || most_units > 0x7fffffffull) return;
-        for (int i = 0; i < 2; ++i) P.once_worth[i] = cost.worth(i);
+        for (int i = 0; i < 2; ++i) P.once_worth[i] = cost.worth(i, part != n);
         if (!P.once_worth[0] && !P.once_worth[1]) return;
         if (lists_at + tasks > room || (double)(room - lists_at - tasks) * 16.0 < kListSlack * listed) continue;
         const double words = multi ? std::min(2.0 * kListSlack, (double)(room - lists_at - tasks) * 16.0 / listed) : 0.0;
